@@ -1,69 +1,719 @@
 // fp32 MLP stage (Linear -> ReLU -> ... -> Linear): the forward_pass of a peer in the
-// paper's Alg. 1 and its exact gradient, for stages small enough that launch latency,
-// not arithmetic, bounds them.  Plain LDS-tiled fp32 products with a fixed summation
-// order (deterministic).
+// paper's Alg. 1 and its exact gradient with the delayed update of Eq. 2.
 //
 // Stash per microbatch: the input of every Linear (a_0 .. a_{n-1}).  Because a_{i+1} =
 // ReLU(z_i), "a_{i+1} > 0" is the ReLU gate of layer i, so pre-activations are not kept.
+//
+// Every product runs on the fp32 matrix instructions (v_mfma_f32_32x32x2_f32 and
+// v_mfma_f32_16x16x4_f32: full fp32 products and sums at twice the rate of plain vector FMAs,
+// which may not be packed here), in a fixed order (deterministic).  Three forms:
+//   tiny   a whole forward, or a whole backward with its update, in ONE launch: workgroups
+//          repeat the small chain of activations (or of gradients) each for itself in LDS and
+//          share out the results, so that no layer waits for a launch of its own;
+//   split  a 32x32 result tile per workgroup, the contraction dealt out over its four or eight waves,
+//          operands straight from memory to registers;
+//   tiled  LDS tiles of 128x128 or 64x64 results, 32 deep, double buffered.
+// In split and tiled form one launch per layer and direction: the forward product; or the input
+// gradient, the weight gradient with the update in its epilogue, and the bias gradient together
+// (they read the same gradient and do not depend on one another).
+#include <new>
 #include "internal.h"
 
 namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef f32x4 f32x4_u __attribute__((aligned(4)));   // four floats at any float's address
+
+template <int V> struct Int { static constexpr int value = V; };   // a constant as an argument
+
+constexpr int kTinyLayers = 4, kTinyRows = 64;
 
 struct MlpPlan {
   int n = 0;
   std::vector<size_t> offW, offB;   // into the flat parameter vector
   std::vector<size_t> offA;         // a_i inside a stash slot (floats)
   size_t maxw = 0;
+  bool tiny = false;
 };
 
-constexpr int TS = 16;
-
-// C[M,N] = sum_k A(m,k) * B(k,n) with element strides; epilogue:
-//   bias != null : + bias[n];  relu : max(.,0);  gate != null : * (gate[m*N+n] > 0)
-__global__ __launch_bounds__(TS * TS) void gemm_f32_kernel(const float* __restrict__ A, int64_t sAm,
-                                                           int64_t sAk, const float* __restrict__ B,
-                                                           int64_t sBk, int64_t sBn,
-                                                           float* __restrict__ Cm, int M, int N,
-                                                           int K, const float* __restrict__ bias,
-                                                           int relu, const float* __restrict__ gate) {
-  __shared__ float As[TS][TS + 1];
-  __shared__ float Bs[TS][TS + 1];
-  const int tx = threadIdx.x % TS, ty = threadIdx.x / TS;
-  const int m = blockIdx.y * TS + ty, n = blockIdx.x * TS + tx;
-  float acc = 0.f;
-  for (int k0 = 0; k0 < K; k0 += TS) {
-    int ka = k0 + tx, kb = k0 + ty;
-    As[ty][tx] = (m < M && ka < K) ? A[m * sAm + ka * sAk] : 0.f;
-    Bs[ty][tx] = (kb < K && n < N) ? B[kb * sBk + n * sBn] : 0.f;
-    __syncthreads();
+// What happens to a finished parameter gradient: stored, and with the update of Eq. 2 (or its
+// momentum form) applied on the spot where one is due.  Offsets are into the flat vector.
+struct Upd {
+  float* grad;
+  float* w;            // null: gradient only
+  float* vel;          // null: plain step
+  float* ver;
+  float eta, mu, wd;
+};
+__device__ __forceinline__ float next_velocity(const Upd& u, float w, float v, float g) {   // as update_momentum_kernel
+  return __fmaf_rn(u.mu, v, __fmaf_rn(u.wd, w, g));
+}
+// N results of a lane at once: everything they read is requested before the first is formed (a
+// store between two loads keeps the second one waiting for a round trip of its own); ok[k] = false: no
+// such parameter (o[k] is a valid offset all the same).
+template <int N>
+__device__ __forceinline__ void apply(const Upd& u, const size_t (&o)[N], const float (&g)[N], const bool (&ok)[N]) {
+  float w[N], v[N];
+  if (u.w) {
 #pragma unroll
-    for (int k = 0; k < TS; ++k) acc = __fmaf_rn(As[ty][k], Bs[k][tx], acc);
+    for (int k = 0; k < N; ++k) w[k] = u.w[o[k]];
+    if (u.vel) {
+#pragma unroll
+      for (int k = 0; k < N; ++k) v[k] = u.vel[o[k]];
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        v[k] = next_velocity(u, w[k], v[k], g[k]);
+        w[k] = __fmaf_rn(-u.eta, v[k], w[k]);
+        if (ok[k]) u.vel[o[k]] = v[k];
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < N; ++k) w[k] = __fmaf_rn(-u.eta, g[k], w[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if (ok[k]) { u.w[o[k]] = w[k]; u.ver[o[k]] = w[k]; }
+  }
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+    if (ok[k]) u.grad[o[k]] = g[k];
+}
+
+// One product C[M,N] = sum_k A(m,k) B(k,n).  An operand is k-contiguous (A[m*lda + k],
+// B[n*ldb + k]) or k-major (A[k*lda + m], B[k*ldb + n]).
+struct Prod {
+  const float* A; const float* B;
+  int lda, ldb, M, N, K, tiles_n, tiles;
+};
+enum { FWD, DX, DW };
+struct Out {
+  float* C;            // FWD, DX: [M,N]
+  const float* bias;   // FWD
+  const float* gate;   // DX: kept where gate[m,n] > 0 (null: no gate)
+  int relu;            // FWD
+  Upd u; size_t off;   // DW: parameter offset of the tile's matrix
+};
+// R results of a lane, rows m[] of column n
+template <int OP, int R>
+__device__ __forceinline__ void finish(const Out& o, const int (&m)[R], int n, int M, int N, const float (&v)[R]) {
+  const int nc = n < N ? n : N - 1;
+  size_t i[R];
+  bool ok[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) { ok[r] = m[r] < M && n < N; i[r] = (size_t)(m[r] < M ? m[r] : M - 1) * N + nc; }
+  if (OP == FWD) {
+    const float b = o.bias[nc];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (ok[r]) o.C[i[r]] = o.relu ? fmaxf(v[r] + b, 0.f) : v[r] + b;
+  } else if (OP == DX) {
+    float g[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) g[r] = o.gate ? o.gate[i[r]] : 1.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (ok[r]) o.C[i[r]] = g[r] > 0.f ? v[r] : 0.f;
+  } else {
+#pragma unroll
+    for (int r = 0; r < R; ++r) i[r] += o.off;
+    apply<R>(o.u, i, v, ok);
+  }
+}
+
+// ---- tiled ---------------------------------------------------------------------------------
+// LDS keeps an operand the way memory has it: k-contiguous rows of 32 (pitch 36 floats: sixteen
+// rows of 16-byte reads fall on all 64 banks), k-major rows of the tile's width (pitch + 8: rows
+// k and k + 4, read together, are 32 banks apart).  A lane takes k = 8 g + 4 (lane / 32) + e,
+// e = 0..3, for the four matrix instructions of group g: one 16-byte read of a k-contiguous tile,
+// four 4-byte reads of a k-major one (transposing it on the way into LDS instead measured 3 - 8 % slower).
+constexpr int BK = 32;
+template <bool KM, int ROWS> struct Lds {
+  static constexpr int PITCH = KM ? ROWS + 8 : BK + 4;
+  static constexpr int FLOATS = KM ? BK * PITCH : ROWS * PITCH;
+  static constexpr int PIECES = ROWS * BK / 4 / 256;       // 16-byte pieces per thread and tile
+};
+
+// A thread's share of a tile.  INSIDE: the whole tile lies in the matrix - one load per piece at a
+// lane offset from a uniform base.  Otherwise element by element at clamped indexes, and what lies
+// past the end of k is zeroed when the piece is parked (results of rows past the other end are not
+// stored).
+template <bool INSIDE, bool KM, int ROWS>
+__device__ __forceinline__ void tile_load(f32x4* v, const float* __restrict__ g, int ld, int r0, int rows, int k0, int K) {
+  const float* base = KM ? g + (int64_t)k0 * ld + r0 : g + (int64_t)r0 * ld + k0;
+#pragma unroll
+  for (int i = 0; i < Lds<KM, ROWS>::PIECES; ++i) {
+    const int p = threadIdx.x + 256 * i;
+    const int k = KM ? p / (ROWS / 4) : p % (BK / 4) * 4, r = KM ? p % (ROWS / 4) * 4 : p / (BK / 4);
+    if (INSIDE) {
+      v[i] = *reinterpret_cast<const f32x4_u*>(base + (unsigned)(KM ? k * ld + r : r * ld + k));
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        int ke = KM ? k : k + e, re = KM ? r + e : r;
+        ke = k0 + ke < K ? ke : K - 1 - k0; re = r0 + re < rows ? re : rows - 1 - r0;
+        v[i][e] = base[KM ? (int64_t)ke * ld + re : (int64_t)re * ld + ke];
+      }
+    }
+  }
+}
+template <bool KM, int ROWS>
+__device__ __forceinline__ void tile_park(const f32x4* v, float* s, int left) {   // left: K - k0
+#pragma unroll
+  for (int i = 0; i < Lds<KM, ROWS>::PIECES; ++i) {
+    const int p = threadIdx.x + 256 * i;
+    const int row = KM ? p / (ROWS / 4) : p / (BK / 4), c = KM ? p % (ROWS / 4) : p % (BK / 4);
+    f32x4 x = v[i];
+    if (left < BK) {                                       // (uniform)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = (KM ? row : c * 4 + e) < left ? x[e] : 0.f;
+    }
+    *reinterpret_cast<f32x4*>(s + row * Lds<KM, ROWS>::PITCH + c * 4) = x;
+  }
+}
+template <bool KM, int ROWS>
+__device__ __forceinline__ f32x4 tile_frag(const float* s, int row0, int g) {
+  const int l = threadIdx.x & 63, row = row0 + (l & 31), k = 8 * g + 4 * (l >> 5);
+  constexpr int P = Lds<KM, ROWS>::PITCH;
+  if (!KM) return *reinterpret_cast<const f32x4*>(s + row * P + k);
+  return f32x4{s[k * P + row], s[(k + 1) * P + row], s[(k + 2) * P + row], s[(k + 3) * P + row]};
+}
+
+template <int BT, bool AKM, bool BKM, int OP>
+__device__ __forceinline__ void tiled_body(const Prod& p, const Out& o, int tile, float* smem) {
+  constexpr int W = BT / 2, T = W / 32;                    // four waves, 2 x 2, each W x W
+  constexpr int AF = Lds<AKM, BT>::FLOATS, BUF = AF + Lds<BKM, BT>::FLOATS;
+  const int m0 = tile / p.tiles_n * BT, n0 = tile % p.tiles_n * BT;
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int wm = (wave & 1) * W, wn = (wave >> 1) * W;
+  f32x16 acc[T][T];
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int j = 0; j < T; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  f32x4 va[Lds<AKM, BT>::PIECES], vb[Lds<BKM, BT>::PIECES];
+  const bool inside = m0 + BT <= p.M && n0 + BT <= p.N;
+  auto fetch = [&](int k0) {
+    if (inside && k0 + BK <= p.K) {                        // (uniform)
+      tile_load<true, AKM, BT>(va, p.A, p.lda, m0, p.M, k0, p.K);
+      tile_load<true, BKM, BT>(vb, p.B, p.ldb, n0, p.N, k0, p.K);
+    } else {
+      tile_load<false, AKM, BT>(va, p.A, p.lda, m0, p.M, k0, p.K);
+      tile_load<false, BKM, BT>(vb, p.B, p.ldb, n0, p.N, k0, p.K);
+    }
+  };
+  auto park = [&](float* s, int k0) { tile_park<AKM, BT>(va, s, p.K - k0); tile_park<BKM, BT>(vb, s + AF, p.K - k0); };
+  // While tile t is used, tile t + 1 is parked (group 1) and tile t + 2 requested (group 2): a load has
+  // nearly a whole tile's products to arrive in, and the barrier at the tile's end finds the writes done.
+  // With one or two waves per SIMD whatever is not issued in the shadow of a matrix instruction leaves
+  // the matrix core idle, so tiles with whole successors run without branches and every other
+  // instruction is dealt out behind the products.
+  const int nk = (p.K + BK - 1) / BK;
+  fetch(0);
+  park(smem, 0);
+  if (nk > 1) fetch(BK);
+  __syncthreads();
+  auto step = [&](int t, auto whole) {
+    constexpr bool WHOLE = decltype(whole)::value != 0;
+    const float* sa = smem + (t & 1) * BUF;
+    const float* sb = sa + AF;
+    f32x4 fa[2][T], fb[2][T];                              // fragments of group g + 1 are read behind the products of group g
+    auto frags = [&](int g) {
+#pragma unroll
+      for (int i = 0; i < T; ++i) fa[g & 1][i] = tile_frag<AKM, BT>(sa, wm + i * 32, g);
+#pragma unroll
+      for (int j = 0; j < T; ++j) fb[g & 1][j] = tile_frag<BKM, BT>(sb, wn + j * 32, g);
+    };
+    frags(0);
+#pragma unroll
+    for (int g = 0; g < BK / 8; ++g) {
+      if (g + 1 < BK / 8) frags(g + 1);
+      if (WHOLE) {
+        if (g == 1) {
+          float* nb = smem + ((t + 1) & 1) * BUF;
+          tile_park<AKM, BT>(va, nb, BK); tile_park<BKM, BT>(vb, nb + AF, BK);
+        }
+        if (g == 2) {
+          tile_load<true, AKM, BT>(va, p.A, p.lda, m0, p.M, (t + 2) * BK, p.K);
+          tile_load<true, BKM, BT>(vb, p.B, p.ldb, n0, p.N, (t + 2) * BK, p.K);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+          for (int j = 0; j < T; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[g & 1][i][e], fb[g & 1][j][e], acc[i][j], 0, 0, 0);
+      if (WHOLE) {
+#pragma unroll
+        for (int q = 0; q < 4 * T * T; ++q) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // a matrix instruction
+          __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);   // then vector arithmetic,
+          __builtin_amdgcn_sched_group_barrier(0x080, 1, 0);   // an LDS access
+          __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // and a load
+        }
+      } else if (g == 1) {
+        if (t + 1 < nk) park(smem + ((t + 1) & 1) * BUF, (t + 1) * BK);
+        if (t + 2 < nk) fetch((t + 2) * BK);
+      }
+    }
+    __syncthreads();
+  };
+  int t = 0;
+  if (inside)
+    for (; (t + 3) * BK <= p.K; ++t) step(t, Int<1>());
+  for (; t < nk; ++t) step(t, Int<0>());
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int j = 0; j < T; ++j)
+#pragma unroll
+      for (int rb = 0; rb < 16; rb += 8) {
+        int m[8];
+        float v[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          m[r] = m0 + wm + i * 32 + 8 * ((rb + r) >> 2) + 4 * (l >> 5) + (r & 3);
+          v[r] = acc[i][j][rb + r];
+        }
+        finish<OP, 8>(o, m, n0 + wn + j * 32 + (l & 31), p.M, p.N, v);
+      }
+}
+
+// ---- split ---------------------------------------------------------------------------------
+// NW waves on one 32x32 tile; wave w takes the 8-deep groups w, w + NW, ... of the contraction, eight of
+// them requested at a time; the partial tiles are added in wave order.
+constexpr int kSplitWaves = 8;
+template <bool KM>
+__device__ __forceinline__ f32x4 direct_frag(const float* __restrict__ g, int ld, int row, int k, int K, bool whole) {
+  f32x4 v;
+  if (whole) {
+    if (!KM) return *reinterpret_cast<const f32x4_u*>(g + (int64_t)row * ld + k);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = g[(int64_t)(k + e) * ld + row];
+    return v;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int kc = k + e < K ? k + e : K - 1;
+    const float x = KM ? g[(int64_t)kc * ld + row] : g[(int64_t)row * ld + kc];
+    v[e] = k + e < K ? x : 0.f;
+  }
+  return v;
+}
+template <int NW, bool AKM, bool BKM, int OP>
+__device__ __forceinline__ void split_body(const Prod& p, const Out& o, int tile, float* smem) {
+  const int m0 = tile / p.tiles_n * 32, n0 = tile % p.tiles_n * 32;
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, h = l >> 5;
+  const int ra = m0 + (l & 31) < p.M ? m0 + (l & 31) : p.M - 1, rb = n0 + (l & 31) < p.N ? n0 + (l & 31) : p.N - 1;
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  constexpr int U = 8;                                     // groups requested before the first is used
+  const int ng = (p.K + 7) / 8, whole = p.K / 8;
+  for (int g0 = wave; g0 < ng; g0 += U * NW) {
+    f32x4 fa[U], fb[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int g = g0 + u * NW;                  // wave-uniform
+      fa[u] = 0.f; fb[u] = 0.f;
+      if (g < ng) {
+        fa[u] = direct_frag<AKM>(p.A, p.lda, ra, 8 * g + 4 * h, p.K, g < whole);
+        fb[u] = direct_frag<BKM>(p.B, p.ldb, rb, 8 * g + 4 * h, p.K, g < whole);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u][e], fb[u][e], acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) smem[(wave * 32 + 8 * (r >> 2) + 4 * h + (r & 3)) * 33 + (l & 31)] = acc[r];
+  __syncthreads();
+  constexpr int R = 32 * 32 / (64 * NW);
+  int m[R];
+  float v[R];
+  const int nl = threadIdx.x & 31;
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const int ml = (threadIdx.x >> 5) + 2 * NW * i;
+    v[i] = smem[ml * 33 + nl];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v[i] += smem[(w * 32 + ml) * 33 + nl];
+    m[i] = m0 + ml;
+  }
+  finish<OP, R>(o, m, n0 + nl, p.M, p.N, v);
+}
+
+// column sums of D[M,N] (the bias gradient): 32 columns per workgroup, NT / 32 row lanes whose
+// sums are added in order
+template <int NT>
+__device__ __forceinline__ void bias_body(const float* __restrict__ D, int M, int N, const Upd& u, size_t off, int blk,
+                                          float* smem) {
+  constexpr int RL = NT / 32;
+  const int cl = threadIdx.x & 31, rl = threadIdx.x >> 5, c = blk * 32 + cl, cc = c < N ? c : N - 1;
+  float s[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int r = rl; r < M; r += 4 * RL) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int rr = r + q * RL;
+      const float x = D[(int64_t)(rr < M ? rr : M - 1) * N + cc];
+      s[q] += rr < M ? x : 0.f;
+    }
+  }
+  smem[rl * 33 + cl] = (s[0] + s[1]) + (s[2] + s[3]);
+  __syncthreads();
+  if (rl == 0 && c < N) {
+    float t = smem[cl];
+#pragma unroll
+    for (int w = 1; w < RL; ++w) t += smem[w * 33 + cl];
+    const size_t i[1] = {off + c};
+    const float g[1] = {t};
+    const bool ok[1] = {true};
+    apply<1>(u, i, g, ok);
+  }
+}
+
+// BT: 128 or 64 (tiled), 32 (split over NT / 64 waves)
+template <int BT, int NT, bool AKM, bool BKM> constexpr int mlp_lds_bytes() {
+  return 4 * (BT == 32 ? NT / 64 * 32 * 33 : 2 * (Lds<AKM, BT>::FLOATS + Lds<BKM, BT>::FLOATS));
+}
+template <int BT, int NT, bool AKM, bool BKM, int OP>
+__device__ __forceinline__ void mlp_body(const Prod& p, const Out& o, int tile, float* smem) {
+  if constexpr (BT == 32) {
+    split_body<NT / 64, AKM, BKM, OP>(p, o, tile, smem);
+  } else {
+    static_assert(NT == 256, "four waves");
+    tiled_body<BT, AKM, BKM, OP>(p, o, tile, smem);
+  }
+}
+extern __shared__ __align__(16) float mlp_smem[];
+
+template <int BT, int NT>
+__global__ __launch_bounds__(NT) void mlp_fwd_kernel(Prod p, Out o, float* __restrict__ copy) {
+  if (copy) {   // the stage's input goes into the stash beside the product that reads it
+    const int64_t n = (int64_t)p.M * p.K;
+    for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT) copy[i] = p.A[i];
+  }
+  mlp_body<BT, NT, false, true, FWD>(p, o, blockIdx.x, mlp_smem);
+}
+
+// input gradient (tiles 0 .. dx.tiles), weight gradient, bias gradient in one launch
+template <int BX, int BW, int NT>
+__global__ __launch_bounds__(NT) void mlp_bwd_kernel(Prod dx, Out ox, Prod dw, Out ow, const float* __restrict__ d, int M, int N,
+                                                     size_t offb) {
+  int b = blockIdx.x;
+  if (b < dx.tiles) { mlp_body<BX, NT, false, false, DX>(dx, ox, b, mlp_smem); return; }
+  b -= dx.tiles;
+  if (b < dw.tiles) { mlp_body<BW, NT, true, true, DW>(dw, ow, b, mlp_smem); return; }
+  bias_body<NT>(d, M, N, ow.u, offb, b - dw.tiles, mlp_smem);
+}
+
+Prod product(const float* A, int lda, const float* B, int ldb, int M, int N, int K, int bt) {
+  const int tn = (N + bt - 1) / bt;
+  return Prod{A, B, lda, ldb, M, N, K, tn, (M + bt - 1) / bt * tn};
+}
+int tile_count(int M, int N, int bt) { return (M + bt - 1) / bt * ((N + bt - 1) / bt); }
+constexpr int kCUs = 256;
+// The largest tile that still gives every CU one (of 64x64 tiles half of them: such a workgroup
+// keeps up with two CUs' worth of 32x32 ones, whose operands all come through L2).  Measured: forward
+// + backward + update of 1024-4096-4096-1024 on 1024 rows 11.0 -> 1.43 ms against plain 16x16 vector
+// tiles with separate bias and update launches (108 of 157 TFLOP/s; 4096^3 alone 128 / 140 / 133
+// TFLOP/s forward / input / weight gradient), 300-1000-1000-77 on 100 rows with momentum
+// 304 -> 74 us, where 64x64 tiles for the 100-row products would take 120.
+int pick(int M, int N) { return tile_count(M, N, 128) >= kCUs ? 128 : tile_count(M, N, 64) >= kCUs / 2 ? 64 : 32; }
+
+template <typename K>
+rv_status allow_lds(K kern, int bytes) {
+  return hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess ? RV_OK : RV_E_DEVICE;
+}
+template <int BT, int NT>
+rv_status launch_fwd(hipStream_t st, const Prod& p, const Out& o, float* copy) {
+  constexpr int lds = mlp_lds_bytes<BT, NT, false, true>();
+  static const rv_status ok = allow_lds(mlp_fwd_kernel<BT, NT>, lds);
+  RV_TRY(ok);
+  hipLaunchKernelGGL((mlp_fwd_kernel<BT, NT>), dim3(p.tiles), dim3(NT), lds, st, p, o, copy);
+  return rv_launch_status();
+}
+template <int BX, int BW, int NT>
+rv_status launch_bwd(hipStream_t st, const Prod& dx, const Out& ox, const Prod& dw, const Out& ow, const float* d, int M, int N,
+                     size_t offb) {
+  constexpr int l1 = mlp_lds_bytes<BX, NT, false, false>(), l2 = mlp_lds_bytes<BW, NT, true, true>(), lds = l1 > l2 ? l1 : l2;
+  static const rv_status ok = allow_lds(mlp_bwd_kernel<BX, BW, NT>, lds);
+  RV_TRY(ok);
+  hipLaunchKernelGGL((mlp_bwd_kernel<BX, BW, NT>), dim3(dx.tiles + dw.tiles + (N + 31) / 32), dim3(NT), lds, st, dx, ox, dw, ow, d, M,
+                     N, offb);
+  return rv_launch_status();
+}
+
+// ---- tiny ----------------------------------------------------------------------------------
+struct Tiny {
+  int n, mb, dim[kTinyLayers + 1];
+  unsigned offW[kTinyLayers], offB[kTinyLayers], offA[kTinyLayers];
+};
+constexpr int kTinyDepth = 128;   // contraction a wave requests at a time
+constexpr int kTinyThreads = 512, kTinyWaves = kTinyThreads / 64;
+__host__ __device__ constexpr int tiny_pitch(int w) { return (w + 15) / 16 * 16 + 4; }   // rows of whole 16-wide groups, 16-byte aligned
+
+// What bounds these kernels is one memory round trip after another (1 - 2 us each: the lines were
+// written by other launches, which leaves every XCD's L2 without them) and the number of lines a
+// load instruction touches.  So a wave requests everything its first tiles of a layer read one
+// layer ahead, the rows of a transposed weight tile come in 16-byte pieces, and no load waits behind
+// a branch: indexes past an end are clamped, their values unused.
+template <int N>
+__device__ __forceinline__ void pin(float (&v)[N]) {   // the values have arrived here
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
+}
+
+// One 16-column tile of a product over the activations in LDS: acc[t] = rows 16 t .. of
+// act[., 0..K) x B, kTinyDepth deep at a time.  A lane takes k = 16 u + 4 (lane / 16) + e; columns K .. of
+// act are zero.   BT = false: B(k, c) = W[k * ldw + c];   true: B(k, c) = W[c * ldw + k]
+template <bool BT>
+__device__ __forceinline__ void tiny_request(float (&b)[kTinyDepth / 4], const float* __restrict__ W, unsigned ldw, int K, int k0, int c) {
+  const int q = (threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int u = 0; u < kTinyDepth / 16; ++u) {
+    const int k = k0 + 16 * u + 4 * q;
+    if (BT && k0 + 16 * u + 16 <= K) {                     // (uniform)
+      const f32x4 v = *reinterpret_cast<const f32x4_u*>(W + c * ldw + (unsigned)k);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) b[4 * u + e] = v[e];
+    } else if (k0 + 16 * u < K) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const unsigned kc = k + e < K ? k + e : K - 1;
+        b[4 * u + e] = BT ? W[c * ldw + kc] : W[kc * ldw + c];
+      }
+    }
+  }
+}
+template <int MT, bool BT>
+__device__ __forceinline__ void tiny_tile(f32x4 (&acc)[MT], float (&b)[kTinyDepth / 4], const float* act, int pitch,
+                                          const float* __restrict__ W, unsigned ldw, int K, int c) {
+  const int l = threadIdx.x & 63, q = l >> 4;
+#pragma unroll
+  for (int t = 0; t < MT; ++t) acc[t] = 0.f;
+  for (int k0 = 0;;) {
+    pin(b);
+#pragma unroll
+    for (int u = 0; u < kTinyDepth / 16; ++u)
+      if (k0 + 16 * u < K) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+          const f32x4 a = *reinterpret_cast<const f32x4*>(act + (t * 16 + (l & 15)) * pitch + k0 + 16 * u + 4 * q);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[4 * u + e], acc[t], 0, 0, 0);
+        }
+      }
+    k0 += kTinyDepth;
+    if (k0 >= K) break;
+    tiny_request<BT>(b, W, ldw, K, k0, c);
+  }
+}
+
+// rows [mb][w] of memory -> LDS, rows and columns past the end zero
+template <int MT>
+__device__ __forceinline__ void tiny_rows(float* s, const float* __restrict__ g, int mb, int w) {
+  const int pitch = tiny_pitch(w), l = threadIdx.x & 63;
+  for (int m = threadIdx.x >> 6; m < 16 * MT; m += kTinyWaves)
+    for (int c = l; c < pitch; c += 64) {
+      const float x = g[(m < mb ? m : mb - 1) * w + (c < w ? c : w - 1)];
+      s[m * pitch + c] = m < mb && c < w ? x : 0.f;
+    }
+}
+
+struct TinyFwdReq { float b[kTinyDepth / 4], bias[1]; };
+template <int NL, int MT>
+__global__ __launch_bounds__(kTinyThreads) void tiny_fwd_kernel(Tiny p, const float* __restrict__ w, const float* __restrict__ in,
+                                                                float* __restrict__ stash, float* __restrict__ out, int half) {
+  extern __shared__ __align__(16) float act[];
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, q = l >> 4;
+  // every workgroup needs every hidden activation; the last layer is shared out
+  auto first = [&](int i) { return i == NL - 1 ? (int)blockIdx.x * kTinyWaves + wave : wave; };
+  auto request = [&](TinyFwdReq& r, int i, int t) {
+    const int N = p.dim[i + 1], c = t * 16 + (l & 15), cc = c < N ? c : N - 1;
+    tiny_request<false>(r.b, w + p.offW[i], N, p.dim[i], 0, cc);
+    r.bias[0] = w[p.offB[i] + cc];
+  };
+  TinyFwdReq cur, nxt;
+  request(cur, 0, first(0));
+  tiny_rows<MT>(act, in, p.mb, p.dim[0]);
+  for (int i = blockIdx.x * kTinyThreads + threadIdx.x; i < p.mb * p.dim[0]; i += gridDim.x * kTinyThreads) stash[p.offA[0] + i] = in[i];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    const int K = p.dim[i], N = p.dim[i + 1];
+    const bool last = i == NL - 1;
+    const float* src = act + (i & 1) * half;
+    float* dst = act + ((i + 1) & 1) * half;
+    const int dp = tiny_pitch(N), tiles = (N + 15) / 16, step = last ? kTinyWaves * gridDim.x : kTinyWaves;
+    nxt = cur;
+    if (!last) request(nxt, i + 1, first(i + 1));
+    for (int t = first(i); t < tiles; t += step) {
+      if (t != first(i)) request(cur, i, t);
+      const int c = t * 16 + (l & 15);
+      f32x4 acc[MT];
+      tiny_tile<MT, false>(acc, cur.b, src, tiny_pitch(K), w + p.offW[i], N, K, c < N ? c : N - 1);
+      pin(cur.bias);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = mt * 16 + 4 * q + r;
+          float v = acc[mt][r] + cur.bias[0];
+          if (!last) {
+            v = c < N ? fmaxf(v, 0.f) : 0.f;
+            dst[m * dp + c] = v;
+            if (t % gridDim.x == blockIdx.x && m < p.mb && c < N) stash[p.offA[i + 1] + m * N + c] = v;
+          } else if (m < p.mb && c < N) {
+            out[m * N + c] = v;
+          }
+        }
+    }
+    cur = nxt;
     __syncthreads();
   }
-  if (m < M && n < N) {
-    if (bias) acc += bias[n];
-    if (relu) acc = fmaxf(acc, 0.f);
-    if (gate) acc = gate[(int64_t)m * N + n] > 0.f ? acc : 0.f;
-    Cm[(int64_t)m * N + n] = acc;
+}
+
+template <int MT> struct TinyBwdReq { float b[kTinyDepth / 4], gate[4 * MT], a[4 * MT], w[4], v[4]; };
+template <int NL, int MT>
+__global__ __launch_bounds__(kTinyThreads) void tiny_bwd_kernel(Tiny p, const float* __restrict__ w, const float* __restrict__ stash,
+                                                                const float* __restrict__ dout, float* __restrict__ din, Upd u,
+                                                                int half) {
+  extern __shared__ __align__(16) float act[];
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, q = l >> 4;
+  const int waves = gridDim.x * kTinyWaves, me = blockIdx.x * kTinyWaves + wave;
+  // d_{i-1} = (d_i W_i^T) where a_i > 0: a whole copy per workgroup, the stage's own input gradient shared out
+  auto request_chain = [&](TinyBwdReq<MT>& r, int i, int t) {
+    const int K = p.dim[i], N = p.dim[i + 1], c = t * 16 + (l & 15), cc = c < K ? c : K - 1;
+    tiny_request<true>(r.b, w + p.offW[i], N, N, 0, cc);
+#pragma unroll
+    for (int k = 0; k < 4 * MT; ++k) {
+      const int m = k / 4 * 16 + 4 * q + k % 4;
+      r.gate[k] = stash[p.offA[i] + (unsigned)((m < p.mb ? m : p.mb - 1) * K + cc)];
+    }
+  };
+  // dW_i = a_i^T d_i and db_i = column sums of d_i (a row K of ones below a_i): 16x16 tiles dealt out over all waves
+  auto offset = [&](int i, int t, int r) -> size_t {
+    const int K = p.dim[i], N = p.dim[i + 1], tn = (N + 15) / 16, k = t / tn * 16 + 4 * q + r, c = t % tn * 16 + (l & 15);
+    const int cc = c < N ? c : N - 1;
+    return k < K ? p.offW[i] + (unsigned)(k * N + cc) : p.offB[i] + cc;
+  };
+  auto request_grad = [&](TinyBwdReq<MT>& r, int i, int t) {
+    const int K = p.dim[i], N = p.dim[i + 1], tn = (N + 15) / 16, kr = t / tn * 16 + (l & 15);
+#pragma unroll
+    for (int k = 0; k < 4 * MT; ++k) {
+      const int m = 4 * k + q;
+      r.a[k] = stash[p.offA[i] + (unsigned)((m < p.mb ? m : p.mb - 1) * K + (kr < K ? kr : K - 1))];
+    }
+    if (u.w) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) r.w[k] = u.w[offset(i, t, k)];
+      if (u.vel) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r.v[k] = u.vel[offset(i, t, k)];
+      }
+    }
+  };
+  auto grad_tiles = [&](int i) { return (p.dim[i] + 16) / 16 * ((p.dim[i + 1] + 15) / 16); };
+  auto request = [&](TinyBwdReq<MT>& r, int i, int tc, int tg) {
+    if (i > 0 || din) request_chain(r, i, tc);
+    request_grad(r, i, tg < grad_tiles(i) ? tg : 0);
+  };
+  auto first_chain = [&](int i) { return i == 0 ? me : wave; };
+
+  int tg = me;                                             // this wave's first tile of layer i (the deal goes on from layer to layer)
+  TinyBwdReq<MT> cur, nxt;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) { cur.w[k] = 0.f; cur.v[k] = 0.f; }
+  request(cur, NL - 1, first_chain(NL - 1), tg);
+  tiny_rows<MT>(act, dout, p.mb, p.dim[NL]);
+  __syncthreads();
+#pragma unroll
+  for (int i = NL - 1; i >= 0; --i) {
+    const int side = (NL - 1 - i) & 1;
+    const int K = p.dim[i], N = p.dim[i + 1];
+    const float* d = act + side * half;                    // dL/dz_i
+    float* below = act + (side ^ 1) * half;
+    const int dp = tiny_pitch(N), bp = tiny_pitch(K), gt = grad_tiles(i);
+    const int tg_next = ((tg - gt) % waves + waves) % waves;
+    nxt = cur;
+    if (i > 0) request(nxt, i - 1, first_chain(i - 1), tg_next);
+    if (i > 0 || din) {
+      const bool share = i == 0;
+      const int tiles = (K + 15) / 16;
+      for (int t = first_chain(i); t < tiles; t += share ? waves : kTinyWaves) {
+        if (t != first_chain(i)) request_chain(cur, i, t);
+        const int c = t * 16 + (l & 15);
+        f32x4 acc[MT];
+        tiny_tile<MT, true>(acc, cur.b, d, dp, w + p.offW[i], N, N, c < K ? c : K - 1);
+        pin(cur.gate);
+#pragma unroll
+        for (int k = 0; k < 4 * MT; ++k) {
+          const int m = k / 4 * 16 + 4 * q + k % 4;
+          const float v = acc[k / 4][k % 4];
+          if (!share) below[m * bp + c] = m < p.mb && c < K && cur.gate[k] > 0.f ? v : 0.f;
+          else if (m < p.mb && c < K) din[m * K + c] = v;
+        }
+      }
+    }
+    for (int t = tg; t < gt; t += waves) {
+      if (t != tg) request_grad(cur, i, t);
+      const int tn = (N + 15) / 16, kr = t / tn * 16 + (l & 15), c = t % tn * 16 + (l & 15);
+      f32x4 acc = 0.f;
+      pin(cur.a); pin(cur.w); pin(cur.v);
+#pragma unroll
+      for (int k = 0; k < 4 * MT; ++k)                     // four rows of the microbatch at a time; past its end d is zero
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kr < K ? cur.a[k] : 1.f, d[(4 * k + q) * dp + c], acc, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (c < N && t / tn * 16 + 4 * q + r <= K) {
+          const size_t o = offset(i, t, r);
+          u.grad[o] = acc[r];
+          if (u.w) {
+            float x = cur.w[r];
+            if (u.vel) {
+              const float v = next_velocity(u, x, cur.v[r], acc[r]);
+              u.vel[o] = v;
+              x = __fmaf_rn(-u.eta, v, x);
+            } else {
+              x = __fmaf_rn(-u.eta, acc[r], x);
+            }
+            u.w[o] = x;
+            u.ver[o] = x;
+          }
+        }
+    }
+    tg = tg_next;
+    cur = nxt;
+    __syncthreads();
   }
 }
 
-// out[n] = sum_m D[m,n]  (rows summed in order)
-__global__ void colsum_f32_kernel(const float* __restrict__ D, int M, int N, float* __restrict__ out) {
-  int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= N) return;
-  float acc = 0.f;
-  for (int m = 0; m < M; ++m) acc += D[(int64_t)m * N + n];
-  out[n] = acc;
+int tiny_half(const rv_stage* s) {   // floats of one LDS activation buffer
+  const int rows = (s->microbatch + 15) / 16;
+  return 16 * (rows > 2 ? 4 : rows) * tiny_pitch((int)((MlpPlan*)s->impl)->maxw);
 }
-
-void gemm(hipStream_t st, const float* A, int64_t sAm, int64_t sAk, const float* B, int64_t sBk,
-          int64_t sBn, float* C, int M, int N, int K, const float* bias, int relu, const float* gate) {
-  dim3 grid((N + TS - 1) / TS, (M + TS - 1) / TS);
-  hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(TS * TS), 0, st, A, sAm, sAk, B, sBk, sBn, C, M, N, K,
-                     bias, relu, gate);
+Tiny tiny_desc(const rv_stage* s) {
+  const MlpPlan* p = (const MlpPlan*)s->impl;
+  Tiny t = {};
+  t.n = p->n; t.mb = s->microbatch;
+  for (int i = 0; i <= p->n; ++i) t.dim[i] = (int)s->dims[i];
+  for (int i = 0; i < p->n; ++i) { t.offW[i] = (unsigned)p->offW[i]; t.offB[i] = (unsigned)p->offB[i]; t.offA[i] = (unsigned)p->offA[i]; }
+  return t;
 }
-
+template <typename F>
+rv_status tiny_by_shape(int n, int mt, F f) {   // layers and 16-row groups as constants
+  auto rows = [&](auto nl) { return mt == 1 ? f(nl, Int<1>()) : mt == 2 ? f(nl, Int<2>()) : f(nl, Int<4>()); };
+  return n == 1 ? rows(Int<1>()) : n == 2 ? rows(Int<2>()) : n == 3 ? rows(Int<3>()) : rows(Int<4>());
+}
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  return a && b && (const char*)a < (const char*)b + nb * 4 && (const char*)b < (const char*)a + na * 4;
+}
 }  // namespace
 
 rv_status rv_mlp_plan(rv_stage* s) {
@@ -84,6 +734,16 @@ rv_status rv_mlp_plan(rv_stage* s) {
   s->P = off;
   s->slot_bytes = offa * 4;
   s->work_bytes = 2 * (size_t)s->microbatch * p->maxw * 4;
+  // One launch per direction, or one per layer and direction?  Forward + backward of one microbatch
+  // back to back, us (one per direction / one per layer):
+  //   64-128-64       8 rows 13.6 / 19.0   64 rows 27.9 / 19.9     64-64-64-64      8 rows 15.4 / 27.3
+  //   128-256-128     8 rows 27.5 / 20.5                           200-200-200-200 16 rows 46.3 / 31.8
+  //   16-16-16        4 rows  9.1 / 14.9   256-256-256 8 / 64 rows 37.0 / 21.6, 87.6 / 23.4
+  // A launch costs about 5 us whatever it does; the repeated chain about 8 + 2.5 (g - 1) us and
+  // (0.2 + 0.11 g) ns per parameter, g = 1, 2, 4 groups of 16 rows.
+  const int g = s->microbatch <= 16 ? 1 : s->microbatch <= 32 ? 2 : 4;
+  p->tiny = p->n <= kTinyLayers && s->microbatch <= kTinyRows && p->maxw <= 256 &&
+            (20.0 + 11.0 * g) * (double)off < 1e5 * (10.0 * p->n - 5.5 - 2.5 * g);
   return RV_OK;
 }
 
@@ -97,39 +757,86 @@ rv_status rv_mlp_forward(rv_stage* s, rv_slot& slot, const void* in, void* out) 
   const float* w = (const float*)s->ver[slot.ver];
   float* stash = (float*)slot.base;
   const int mb = s->microbatch;
-  RV_HIP_TRY(hipMemcpyAsync(stash + p->offA[0], in, (size_t)mb * s->dims[0] * 4,
-                            hipMemcpyDeviceToDevice, s->st));
+  // a caller may hand the same buffer in and out: then nothing may be written before all of it is read
+  const bool in_place = overlap(in, (size_t)mb * s->dims[0], out, (size_t)mb * s->dims[p->n]);
+  if (p->tiny && !in_place) {
+    const Tiny t = tiny_desc(s);
+    const int half = tiny_half(s), mt = (mb + 15) / 16;
+    const int wgs = ((int)s->dims[p->n] + 16 * kTinyWaves - 1) / (16 * kTinyWaves);
+    const size_t lds = 2 * (size_t)half * 4;
+    return tiny_by_shape(p->n, mt, [&](auto nl, auto m) -> rv_status {
+      constexpr auto kern = tiny_fwd_kernel<decltype(nl)::value, decltype(m)::value>;
+      static const rv_status ok = allow_lds(kern, 160 * 1024);
+      RV_TRY(ok);
+      hipLaunchKernelGGL(kern, dim3(wgs), dim3(kTinyThreads), lds, s->st, t, w, (const float*)in, stash, (float*)out, half);
+      return rv_launch_status();
+    });
+  }
+  const bool copy_first = in_place && p->n == 1;
+  if (copy_first) RV_HIP_TRY(hipMemcpyAsync(stash, in, (size_t)mb * s->dims[0] * 4, hipMemcpyDeviceToDevice, s->st));
   for (int i = 0; i < p->n; ++i) {
-    const bool last = i == p->n - 1;
-    float* dst = last ? (float*)out : stash + p->offA[i + 1];
+    const bool last = i == p->n - 1, first = i == 0 && !copy_first;
     const int K = (int)s->dims[i], N = (int)s->dims[i + 1];
-    gemm(s->st, stash + p->offA[i], K, 1, w + p->offW[i], N, 1, dst, mb, N, K, w + p->offB[i],
-         last ? 0 : 1, nullptr);
+    const int bt = pick(mb, N);
+    const Prod pr = product(first ? (const float*)in : stash + p->offA[i], K, w + p->offW[i], N, mb, N, K, bt);
+    Out o = {};
+    o.C = last ? (float*)out : stash + p->offA[i + 1]; o.bias = w + p->offB[i]; o.relu = !last;
+    float* copy = first ? stash : nullptr;
+    const rv_status rc = bt == 128  ? launch_fwd<128, 256>(s->st, pr, o, copy)
+                         : bt == 64 ? launch_fwd<64, 256>(s->st, pr, o, copy)
+                                    : launch_fwd<32, 64 * kSplitWaves>(s->st, pr, o, copy);
+    RV_TRY(rc);
   }
   return rv_launch_status();
 }
 
+// The gradient of every layer, and the update where the epilogues can apply it (s->fused: plain
+// or momentum step of a backward that updates); otherwise the caller follows with rv_stage_update_range.
 rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void* grad_in) {
   MlpPlan* p = (MlpPlan*)s->impl;
   const float* w = (const float*)s->ver[slot.ver];
   const float* stash = (const float*)slot.base;
   const int mb = s->microbatch;
+  Upd u = {s->grad, nullptr, nullptr, nullptr, s->eta, s->momentum, s->weight_decay};
+  if (s->fused) { u.w = s->master; u.vel = s->vel; u.ver = (float*)s->ver[s->upd_dst]; }
+  if (p->tiny && !overlap(grad_out, (size_t)mb * s->dims[p->n], grad_in, (size_t)mb * s->dims[0])) {
+    const Tiny t = tiny_desc(s);
+    const int half = tiny_half(s), mt = (mb + 15) / 16;
+    int tiles = 0;
+    for (int i = 0; i < p->n; ++i) tiles += (t.dim[i] + 16) / 16 * ((t.dim[i + 1] + 15) / 16);
+    const int wgs = std::min(64, (tiles + kTinyWaves - 1) / kTinyWaves);
+    const size_t lds = 2 * (size_t)half * 4;
+    return tiny_by_shape(p->n, mt, [&](auto nl, auto m) -> rv_status {
+      constexpr auto kern = tiny_bwd_kernel<decltype(nl)::value, decltype(m)::value>;
+      static const rv_status ok = allow_lds(kern, 160 * 1024);
+      RV_TRY(ok);
+      hipLaunchKernelGGL(kern, dim3(wgs), dim3(kTinyThreads), lds, s->st, t, w, stash, (const float*)grad_out, (float*)grad_in, u,
+                         half);
+      return rv_launch_status();
+    });
+  }
   float* ping = (float*)s->work;
   float* pong = ping + (size_t)mb * p->maxw;
   const float* d = (const float*)grad_out;   // dL/dz_i, already gated
   for (int i = p->n - 1; i >= 0; --i) {
     const int K = (int)s->dims[i], N = (int)s->dims[i + 1];
     const float* a = stash + p->offA[i];
-    // dW_i[K,N] = a_i^T d ; db_i = column sums of d
-    gemm(s->st, a, 1, K, d, N, 1, s->grad + p->offW[i], K, N, mb, nullptr, 0, nullptr);
-    hipLaunchKernelGGL(colsum_f32_kernel, dim3((N + 127) / 128), dim3(128), 0, s->st, d, mb, N,
-                       s->grad + p->offB[i]);
-    // d_{i-1}[mb,K] = (d W_i^T) gated by a_i > 0 (no gate in front of the first layer)
-    if (i > 0 || grad_in) {
-      float* dst = i == 0 ? (float*)grad_in : (d == ping ? pong : ping);
-      gemm(s->st, d, N, 1, w + p->offW[i], 1, N, dst, mb, K, N, nullptr, 0, i > 0 ? a : nullptr);
-      d = dst;
-    }
+    const bool want_dx = i > 0 || grad_in;
+    float* dst = i == 0 ? (float*)grad_in : (d == ping ? pong : ping);
+    const int bx = pick(mb, K), bw = pick(K, N);
+    Prod px = product(d, N, w + p->offW[i], N, mb, K, N, bx);
+    const Prod pw = product(a, K, d, N, K, N, mb, bw);
+    if (!want_dx) px.tiles = 0;
+    Out ox = {}, ow = {};
+    ox.C = dst; ox.gate = i > 0 ? a : nullptr;
+    ow.u = u; ow.off = p->offW[i];
+    auto go = [&](auto launch) { return launch(s->st, px, ox, pw, ow, d, mb, N, p->offB[i]); };
+    rv_status rc;
+    if (bx == 128) rc = bw == 128 ? go(launch_bwd<128, 128, 256>) : bw == 64 ? go(launch_bwd<128, 64, 256>) : go(launch_bwd<128, 32, 256>);
+    else if (bx == 64) rc = bw == 128 ? go(launch_bwd<64, 128, 256>) : bw == 64 ? go(launch_bwd<64, 64, 256>) : go(launch_bwd<64, 32, 256>);
+    else rc = bw == 128 ? go(launch_bwd<32, 128, 256>) : bw == 64 ? go(launch_bwd<32, 64, 256>) : go(launch_bwd<32, 32, 64 * kSplitWaves>);
+    RV_TRY(rc);
+    if (want_dx) d = dst;
   }
   return rv_launch_status();
 }

@@ -323,20 +323,20 @@ rv_status do_backward(rv_stage* s, int slot_i, const void* grad_out, void* grad_
       if (s->ver_ref[v] == 0) dst = (int)v;
     if (dst < 0) return RV_E_DEVICE;  // unreachable by the counting argument above
   }
-  // Plain Eq. 2 on a decoder stage is applied in the epilogues that produce the gradient (the
-  // weight-gradient products, the column reductions); momentum, accumulation and deferred steps
-  // take the separate update kernels.
-  s->fused = s->kind == RV_DECODER && updates && s->accum == 1 && !s->vel;
+  // Plain Eq. 2 is applied in the epilogues that produce the gradient (the weight-gradient
+  // products, the column reductions), on an MLP stage the momentum form as well; the rest takes the
+  // separate update kernels.
+  s->fused = updates && s->accum == 1 && (s->kind == RV_MLP || !s->vel);
   s->upd_dst = dst;
   rv_status rc;
   if (s->kind == RV_MLP) {
     rc = rv_mlp_backward(s, sl, grad_out, grad_in);
-    if (rc == RV_OK) rc = rv_stage_update_range(s, 0, s->P, s->st);
+    if (rc == RV_OK && !s->fused) rc = rv_stage_update_range(s, 0, s->P, s->st);
   } else {
     rc = rv_dec_backward(s, sl, grad_out, grad_in);   // updates block by block
   }
   if (rc != RV_OK) return rc;   // (a failed launch leaves the stage unusable)
-  s->grad_valid = !s->fused || s->keep_grad;
+  s->grad_valid = s->kind == RV_MLP || !s->fused || s->keep_grad;
   sl.live = false;
   s->ver_ref[sl.ver] -= 1;
   sl.ver = -1;

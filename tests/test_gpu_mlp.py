@@ -182,3 +182,56 @@ def test_stage_with_gradient_accumulation(A, momentum):
     close(host64(g.get_params()) - w0, o.w - w0, 1e-4, "t", group="MLP stage, bar 1e-4")
     with pytest.raises(rv.RvError):
         g.set_accumulation(0)
+
+
+@pytest.mark.parametrize("dims,mb,momentum", [
+    # one launch per direction: 16 / 32 / 64 rows, one to four layers, widest rows, contractions of one piece,
+    # of exactly one request and of more than one
+    ([1, 1], 1, 0.0), ([16, 128, 16], 16, 0.9), ([17, 129, 15], 17, 0.0), ([256, 13, 256], 33, 0.0),
+    ([250, 40, 31, 7], 64, 0.9), ([120, 256, 20], 16, 0.0), ([40, 64, 3, 33, 128], 48, 0.0),
+    # a 32 x 32 tile per workgroup: just past the widths / rows / layers of the form above
+    ([257, 64, 31], 8, 0.9), ([64, 100, 64], 65, 0.0), ([8, 9, 10, 11, 12, 13], 5, 0.9), ([520, 40], 33, 0.0),
+    # LDS tiles of 64 and of 128 with ragged edges (one layer: no gate, so no gate can fall the other
+    # way); contractions of less than a tile, of one, of two and a bit
+    ([1030, 2052], 2051, 0.0), ([2052, 2060], 2049, 0.9), ([31, 4100], 600, 0.0), ([32, 1037], 1030, 0.9), ([65, 2048], 2048, 0.0),
+])
+def test_product_forms_at_their_edges(dims, mb, momentum):
+    """Two microbatches against the oracle.  Bar: sums of K <= 2060 fp32 products with random signs, in any order,
+    stay within about sqrt(K) * 2^-24 = 2.7e-6 normwise; 1e-5 leaves a factor of four."""
+    import paper_2401_01728_amd as rv
+    eta, wd = 1e-3, 1e-3 if momentum else 0.0
+    w0 = kaiming_uniform_flat(61, dims)
+    g = rv.Stage.mlp(dims, mb, 1, eta); g.set_params(dev(w0))
+    if momentum:
+        g.set_optimizer(momentum, wd)
+    o = ostage.Stage("mlp", 1, eta, w0, dims=dims, momentum=momentum, weight_decay=wd)
+    x = [gen.normal_f32(61, 10 + t, mb * dims[0]).reshape(mb, dims[0]) for t in range(2)]
+    dy = [gen.normal_f32(61, 50 + t, mb * dims[-1], std=0.1).reshape(mb, dims[-1]) for t in range(2)]
+    grp = "MLP product forms, bar 1e-5"
+    for t in range(2):
+        close(host64(g.forward(t, dev(x[t]))), o.forward(t, x[t]), 1e-5, "t", group=grp)
+    for t in range(2):
+        close(host64(g.backward(t, dev(dy[t]))), o.backward(t, dy[t]), 1e-5, "t", group=grp)
+        close(host64(g.last_grad()), o.last_grad, 1e-5, "t", group=grp)
+    # two updates: each rounds the weight once (2^-24 of it), and eta times a gradient off by 1e-5 is less than 1e-7 of
+    # the weights' norm
+    close(host64(g.get_params()), o.w, 1e-6, "t", group="MLP product forms: parameters, bar 1e-6")
+
+
+def test_output_may_share_the_input_buffer():
+    import paper_2401_01728_amd as rv
+    for dims in ([24, 24], [24, 40, 24], [300, 40, 300]):
+        w0 = kaiming_uniform_flat(62, dims)
+        mb = 9
+        g = rv.Stage.mlp(dims, mb, 0, 0.05); g.set_params(dev(w0))
+        o = ostage.Stage("mlp", 0, 0.05, w0, dims=dims)
+        x = gen.normal_f32(62, 1, mb * dims[0]).reshape(mb, dims[0])
+        b = dev(x)
+        g.forward(0, b, b)
+        close(host64(b), o.forward(0, x), 1e-5, "t", group="MLP stage, bar 1e-5")
+        dy = dev(x)
+        g.backward(0, dy, dy if len(dims) > 2 else None)
+        dxo = o.backward(0, x)
+        if len(dims) > 2:
+            close(host64(dy), dxo, 1e-5, "t", group="MLP stage, bar 1e-5")
+        close(host64(g.last_grad()), o.last_grad, 1e-5, "t", group="MLP stage, bar 1e-5")
