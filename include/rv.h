@@ -237,8 +237,7 @@ rv_status rv_block_update_momentum(float* w, const float* g, float* v, size_t n,
  *                enters the average as x - eta*grad (Alg. 2, the all-reduce
  *                branch), so the mean moves by -(eta/C) grad (Eq. 17).  The
  *                product and the subtraction are rounded separately.
- * RV_E_INVAL on bad arguments.  Pointers that are not 16-byte aligned are
- * accepted (slower path).
+ * RV_E_INVAL on bad arguments.  Pointers need no more than a float's alignment.
  */
 rv_status rv_cluster_average(float* const* replicas, int C, size_t n, int R, float* mean_out,
                              int write_back, const float* grad, int grad_replica, float eta,

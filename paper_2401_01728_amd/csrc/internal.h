@@ -10,7 +10,13 @@ rv_status rv_launch_update(float* w, const float* g, size_t n, float eta, void* 
 rv_status rv_launch_update_momentum(float* w, const float* g, float* v, size_t n, float eta, float mu, float wd,
                                     void* copy, int copy_kind, hipStream_t st);
 rv_status rv_launch_accumulate(float* acc, const float* g, size_t n, bool first, hipStream_t st);
-rv_status rv_launch_publish(const float* w, size_t n, void* copy, int copy_kind, hipStream_t st);
+// master <- w and copy <- w in the version's type
+rv_status rv_launch_set(const float* w, size_t n, float* master, void* copy, int copy_kind, hipStream_t st);
+
+// ---- average.hip -----------------------------------------------------------------
+// rv_cluster_average with write-back, and the mean also stored to C weight versions (copy_kind)
+rv_status rv_average_publish(float* const* masters, void* const* versions, int copy_kind, int C, size_t n, int R, const float* grad,
+                             int grad_replica, float eta, hipStream_t st);
 
 // ---- gemm_bf16.hip ----------------------------------------------------------------
 #include "../../include/rv_kernels.h"

@@ -120,8 +120,7 @@ extern "C" int rv_stage_in_flight(const rv_stage* s) {
 extern "C" rv_status rv_stage_set_params(rv_stage* s, const float* flat, size_t n) {
   if (!s || !flat || n != s->P || s->sync_dst >= 0) return RV_E_INVAL;
   if (rv_stage_in_flight(s) != 0) return RV_E_INVAL;
-  RV_HIP_TRY(hipMemcpyAsync(s->master, flat, n * 4, hipMemcpyDeviceToDevice, s->st));
-  return rv_launch_publish(s->master, s->P, s->ver[s->cur], copy_kind(s), s->st);
+  return rv_launch_set(flat, s->P, s->master, s->ver[s->cur], copy_kind(s), s->st);
 }
 
 extern "C" rv_status rv_stage_set_optimizer(rv_stage* s, float momentum, float weight_decay) {
@@ -160,6 +159,7 @@ extern "C" rv_status rv_cluster_sync_fork(rv_stage* const* stages, int C, int R,
   if (state && pending >= 0) return RV_E_INVAL;   // the folded step is the plain one of Alg. 2
   float* masters[64];
   float* vels[64];
+  void* versions[64];
   for (int c = 0; c < C; ++c) {
     rv_stage* s = stages[c];
     if (!s || s->P != stages[0]->P || s->dtype != stages[0]->dtype || s->st != stages[0]->st) return RV_E_INVAL;
@@ -192,13 +192,10 @@ extern "C" rv_status rv_cluster_sync_fork(rv_stage* const* stages, int C, int R,
     RV_HIP_TRY(hipEventRecord(owner->ev_sync_ready, st));
     RV_HIP_TRY(hipStreamWaitEvent(ss, owner->ev_sync_ready, 0));
   }
-  RV_TRY(rv_cluster_average(masters, C, owner->P, R, nullptr, 1, p ? p->grad : nullptr, pending >= 0 ? pending : 0,
+  for (int c = 0; c < C; ++c) versions[c] = stages[c]->ver[dst[c]];
+  RV_TRY(rv_average_publish(masters, versions, copy_kind(owner), C, owner->P, R, p ? p->grad : nullptr, pending >= 0 ? pending : 0,
                             p ? p->eta : 0.f, ss));
   if (state) RV_TRY(rv_cluster_average(vels, C, owner->P, R, nullptr, 1, nullptr, 0, 0.f, ss));
-  for (int c = 0; c < C; ++c) {
-    rv_stage* s = stages[c];
-    RV_TRY(rv_launch_publish(s->master, s->P, s->ver[dst[c]], copy_kind(s), ss));
-  }
   if (forked) RV_HIP_TRY(hipEventRecord(owner->ev_sync_done, ss));
   for (int c = 0; c < C; ++c) {
     stages[c]->sync_dst = dst[c];

@@ -149,14 +149,29 @@ __global__ __launch_bounds__(kThreads) void accumulate_kernel(float* __restrict_
   }
 }
 
-// plain conversion of the master vector into a version slot (set_params)
+// set_params: a flat vector becomes the master and, converted, a weight version, in one pass
 template <int COPY>
-__global__ __launch_bounds__(kThreads) void publish_kernel(const float* __restrict__ w, uint64_t n,
-                                                           void* __restrict__ copy) {
-  uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= n) return;
-  if (COPY == 1) reinterpret_cast<uint16_t*>(copy)[i] = rv_f32_to_bf16(w[i]);
-  if (COPY == 2) reinterpret_cast<float*>(copy)[i] = w[i];
+__global__ __launch_bounds__(kThreads) void set_kernel(const float* w, uint64_t n, float* master, void* __restrict__ copy) {
+  const uint64_t e = ((uint64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
+  if (e + 4 <= n) {
+    typedef f4 f4_u __attribute__((aligned(4)));           // the caller's vector may start anywhere
+    const f4 v = *reinterpret_cast<const f4_u*>(w + e);
+    *reinterpret_cast<f4*>(master + e) = v;
+    if (COPY == 1) {
+      u2 pk;
+      pk.x = rv_pack_bf16x2(v.x, v.y); pk.y = rv_pack_bf16x2(v.z, v.w);
+      *reinterpret_cast<u2*>(reinterpret_cast<uint16_t*>(copy) + e) = pk;
+    } else {
+      *reinterpret_cast<f4*>(reinterpret_cast<float*>(copy) + e) = v;
+    }
+    return;
+  }
+  for (uint64_t i = e; i < n; ++i) {
+    const float v = w[i];
+    master[i] = v;
+    if (COPY == 1) reinterpret_cast<uint16_t*>(copy)[i] = rv_f32_to_bf16(v);
+    else reinterpret_cast<float*>(copy)[i] = v;
+  }
 }
 
 }  // namespace
@@ -200,13 +215,13 @@ rv_status rv_launch_accumulate(float* acc, const float* g, size_t n, bool first,
   return rv_launch_status();
 }
 
-rv_status rv_launch_publish(const float* w, size_t n, void* copy, int copy_kind, hipStream_t st) {
+rv_status rv_launch_set(const float* w, size_t n, float* master, void* copy, int copy_kind, hipStream_t st) {
   if (n == 0) return RV_OK;
-  unsigned blocks = (unsigned)((n + kThreads - 1) / kThreads);
+  const unsigned blocks = (unsigned)((n + kThreads * 4 - 1) / (kThreads * 4));
   if (copy_kind == 1)
-    hipLaunchKernelGGL(publish_kernel<1>, dim3(blocks), dim3(kThreads), 0, st, w, n, copy);
+    hipLaunchKernelGGL(set_kernel<1>, dim3(blocks), dim3(kThreads), 0, st, w, n, master, copy);
   else
-    hipLaunchKernelGGL(publish_kernel<2>, dim3(blocks), dim3(kThreads), 0, st, w, n, copy);
+    hipLaunchKernelGGL(set_kernel<2>, dim3(blocks), dim3(kThreads), 0, st, w, n, master, copy);
   return rv_launch_status();
 }
 

@@ -57,6 +57,16 @@ def test_average_matches_oracle(C, R, n, fused):
     _check(xs, R, g, (C - 1) if fused else 0, 1e-3 * 37, write_back=False)
 
 
+@pytest.mark.parametrize("C", [5, 6, 9, 12, 15, 16, 17, 24, 33, 64])
+def test_average_whole_tiles_for_any_replica_count(C):
+    """Chunks of several tiles of 1024 elements: C at compile time up to 16, in batches of eight loads beyond
+    (two whole ones and a rest, whole ones only, a rest of one)."""
+    xs = _replicas(70 + C, C, C * 2 * 5000 + 7)
+    g = gen.normal_f32(70 + C, 99, xs[0].size, std=1e-3)
+    _check(xs, 2, g, C // 2, 0.25, write_back=False)
+    _check(xs, 2, None, 0, 0.0, write_back=True)
+
+
 @pytest.mark.parametrize("C,R,n", [(4, 4, 50003), (16, 2, 9000), (3, 3, 100)])
 def test_average_write_back(C, R, n):
     xs = _replicas(7, C, n)
