@@ -80,9 +80,9 @@ rv_status rv_dec_plan(rv_stage* s) {
   for (auto& pair : p->w_part_ln)
     for (size_t& o : pair) { o = w; w += align_up(part_ln * 4); }
   // partial rows of the bias gradients: of the arriving gradient (32-row blocks), of dz (one per tile
-  // row of the product that makes it, at least 128 rows) and of dqkv (32-token blocks)
+  // row of the product that makes it, at least 32 rows) and of dqkv (32-token blocks)
   p->w_part_dy = w; w += align_up((size_t)rv_widen_parts(p->T) * d * 4);
-  for (size_t& o : p->w_part_dz) { o = w; w += align_up((size_t)((T + 127) / 128) * f * 4); }
+  for (size_t& o : p->w_part_dz) { o = w; w += align_up((size_t)((T + 31) / 32) * f * 4); }
   for (size_t& o : p->w_part_qkv) { o = w; w += align_up((size_t)rv_attn_colsum_parts(p->mb, p->S) * 3 * d * 4); }
   p->w_ytmp = w; w += align_up(T * d * 4);
   s->work_bytes = w;

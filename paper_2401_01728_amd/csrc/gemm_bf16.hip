@@ -338,13 +338,17 @@ __device__ __forceinline__ void write_tile_staged(const f32x16 (&acc)[TM][TN], c
 // index instead; because a lane's LDS slot is fixed, the swizzle is applied to the GLOBAL
 // address a lane fetches.
 //   k-contiguous tile [rows][BK]: physical chunk = c ^ ((row / rows_per_256B) % chunks_per_row)
-//   k-major tile [BK][cols]     : physical chunk = c ^ ((k & 3) << 2)   (64-byte granules)
+//   k-major tile [BK][cols]     : physical chunk = c ^ ((k & 3) << 2)   (64-byte granules); with 64
+//                                 columns, two rows to a 256-byte bank line, c ^ ((k & 2) << 1)
 // NS stages form a ring.  Plain form (four-wave tiles): the loads of tile t+NS-1 are issued
 // right after the barrier that opens tile t.  Pipelined form (the eight-wave 256x256 tile): see
 // gemm_dtl_body - the products are bound by how fast operand tiles arrive, inside a stage step
 // even more than alone (with seven of eight MFMAs taken out the step is 3 % shorter, without
 // the loads 24 %), so that tile keeps three 32-deep tiles in flight instead of one 64-deep one.
 __host__ __device__ constexpr int dtl_tile_bytes(int rows, int bk) { return rows * bk * 2; }
+
+template <int ROWS>
+__device__ __forceinline__ int km_swizzle(int k) { return ROWS == 64 ? (k & 2) << 1 : (k & 3) << 2; }
 
 template <bool KM, int ROWS, int BK, int NW>
 struct Dtl {
@@ -366,7 +370,7 @@ __device__ __forceinline__ void dtl_init(Dtl<KM, ROWS, BK, NW>& s, int64_t ld, i
       s.off[i] = gr * (int)ld + c * 8;
     } else {
       constexpr int CPR = ROWS / 8;
-      const int kr = slot / CPR, c = (slot % CPR) ^ ((kr & 3) << 2);
+      const int kr = slot / CPR, c = (slot % CPR) ^ km_swizzle<ROWS>(kr);
       int col = r0 + c * 8;
       col = col < rows ? col : rows - 8;
       s.off[i] = kr * (int)ld + col;
@@ -405,7 +409,7 @@ __device__ __forceinline__ bf16x8 dtl_frag(const char* lds, int row0, int kk) {
     const int q = l >> 4, i = l & 15;
     const int kr = kk * 16 + 8 * (q >> 1) + (i >> 2);
     const int col = row0 + 16 * (q & 1) + 4 * (i & 3);
-    const int c = (col >> 3) ^ ((kr & 3) << 2);
+    const int c = (col >> 3) ^ km_swizzle<ROWS>(kr);
     const char* p = lds + kr * (ROWS * 2) + c * 16 + (col & 7) * 2;
     s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p));
     s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
@@ -769,6 +773,228 @@ __global__ __launch_bounds__(64 * NW, WPE) void gemm_dtl_kernel(const uint16_t* 
   gemm_dtl_body<BM, BN, BK, NS, NW, AKM, BKM, EPI>(A, lda, B, ldb, M, N, K, bm, bn, e);
 }
 
+// ---- few tiles: the contraction split inside a workgroup ------------------------------------
+// A product whose 128x128 or 256x256 tiles do not cover the chip lasts as long as ONE workgroup's
+// walk along K: each 32-deep step costs a barrier and what is left of a memory round trip, and most
+// CUs have no tile at all.  Here a workgroup of G groups of four waves takes a smaller tile and group
+// g the k-tiles g, g + G, ... of it, each group with its own ring of NS slots - the walk is G times
+// shorter and a CU keeps G (NS - 1) k-tiles on the way.  (Interleaved k-tiles, so that the two
+// halves of a 128-byte line of a k-contiguous operand are asked for together.)  The G partial
+// tiles meet in LDS as fp32 images and are added in group order; the epilogue runs on rows of the image,
+// eight columns per lane, with what it reads from memory requested before the partial tiles are parked.
+__host__ __device__ constexpr int split_pitch(int bn) { return bn + 4; }   // floats
+template <int BM, int BN, int G, int NS> constexpr int split_lds() {
+  constexpr int ring = G * NS * (dtl_tile_bytes(BM, 32) + dtl_tile_bytes(BN, 32)), image = G * BM * split_pitch(BN) * 4;
+  return ring > image ? ring : image;
+}
+__device__ __forceinline__ void bf16x8_to_f32(f32x4 (&v)[2], u32x4 b) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    v[h].x = __uint_as_float(b[2 * h] << 16); v[h].y = __uint_as_float(b[2 * h] & 0xFFFF0000u);
+    v[h].z = __uint_as_float(b[2 * h + 1] << 16); v[h].w = __uint_as_float(b[2 * h + 1] & 0xFFFF0000u);
+  }
+}
+// eight bf16 at an 8-byte boundary (biases, weight versions, the rounded copy of an fp32 result)
+__device__ __forceinline__ u32x4 load8(const uint16_t* p) {
+  const u32x2 a = reinterpret_cast<const u32x2*>(p)[0], b = reinterpret_cast<const u32x2*>(p)[1];
+  return u32x4{a.x, a.y, b.x, b.y};
+}
+__device__ __forceinline__ void store8(void* base, int64_t at, u32x4 v) {
+  u32x2* p = reinterpret_cast<u32x2*>((uint16_t*)base + at);
+  p[0] = u32x2{v.x, v.y}; p[1] = u32x2{v.z, v.w};
+}
+__device__ __forceinline__ u32x4 f32_to_bf16x8(const f32x4 (&v)[2]) {
+  u32x4 o;
+  o.x = rv_pack_bf16x2(v[0].x, v[0].y); o.y = rv_pack_bf16x2(v[0].z, v[0].w);
+  o.z = rv_pack_bf16x2(v[1].x, v[1].y); o.w = rv_pack_bf16x2(v[1].z, v[1].w);
+  return o;
+}
+
+template <int BM, int BN, int G, int NW, int NS, bool AKM, bool BKM, int EPI>
+__device__ __forceinline__ void gemm_split_body(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ B,
+                                                int64_t ldb, int M, int N, int K, int bm, int bn, const Epi& e) {
+  constexpr int BK = 32, NT = 64 * NW * G;               // a group's NW waves: NW / 2 (m) x 2 (n)
+  constexpr int WM = BM / (NW / 2), WN = BN / 2, TM = WM / 32, TN = WN / 32;
+  constexpr int A_BYTES = dtl_tile_bytes(BM, BK), BUF = A_BYTES + dtl_tile_bytes(BN, BK);
+  constexpr int NA = Dtl<AKM, BM, BK, NW>::N, NB = Dtl<BKM, BN, BK, NW>::N, LPT = NA + NB;
+  static_assert(NS >= 3 && NS <= 5 && LPT * (NS - 2) < 64, "ring");
+  const int m0 = bm * BM, n0 = bn * BN;
+  const int group = __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * NW)), wave = (threadIdx.x >> 6) % NW, l = threadIdx.x & 63;
+  const int wm0 = wave / 2 * WM, wn0 = wave % 2 * WN;
+  char* ring = dtl_smem + group * (NS * BUF);
+
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  Dtl<AKM, BM, BK, NW> da;
+  Dtl<BKM, BN, BK, NW> db;
+  dtl_init<AKM, BM, BK, NW>(da, lda, m0, M, wave);
+  dtl_init<BKM, BN, BK, NW>(db, ldb, n0, N, wave);
+  const int nk = K / BK, turns = (nk + G - 1) / G;
+  const int mine = (nk - group + G - 1) / G;               // k-tiles of this group: group, group + G, ...
+  auto issue = [&](int i) {                                // its i-th k-tile into slot i % NS
+    const int t = i * G + group;
+    const int lb = __builtin_amdgcn_readfirstlane((int)(size_t)(ring + (i % NS) * BUF) + wave * 1024);
+    const uint16_t* pa = AKM ? A + (int64_t)t * BK * lda : A + (int64_t)t * BK;
+    const uint16_t* pb = BKM ? B + (int64_t)t * BK * ldb : B + (int64_t)t * BK;
+#pragma unroll
+    for (int q = 0; q < NA; ++q) dtl_load_s(pa, (unsigned)da.off[q] * 2u, lb + q * NW * 1024);
+#pragma unroll
+    for (int q = 0; q < NB; ++q) dtl_load_s(pb, (unsigned)db.off[q] * 2u, lb + A_BYTES + q * NW * 1024);
+  };
+#pragma unroll
+  for (int i = 0; i < NS - 1; ++i)
+    if (i < mine) issue(i);
+  for (int i = 0; i < turns; ++i) {
+    // this group's k-tile i has landed once at most its newer ones are outstanding
+    const int newer = mine - 1 - i;
+    if (NS >= 5 && newer >= 3) RV_WAIT_VMCNT(LPT * (NS >= 5 ? 3 : 0));
+    else if (NS >= 4 && newer >= 2) RV_WAIT_VMCNT(LPT * (NS >= 4 ? 2 : 0));
+    else if (newer >= 1) RV_WAIT_VMCNT(LPT);
+    else RV_WAIT_VMCNT(0);
+    __syncthreads();                                       // every wave's part of it has; everyone left k-tile i - 1
+    if (i + NS - 1 < mine) issue(i + NS - 1);
+    if (i < mine) {                                        // (wave-uniform)
+      const char* curA = ring + (i % NS) * BUF;
+      const char* curB = curA + A_BYTES;
+      bf16x8 fa[2][TM], fb[2][TN];
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+        for (int a = 0; a < TM; ++a) fa[kk][a] = dtl_frag<AKM, BM, BK>(curA, wm0 + a * 32, kk);
+#pragma unroll
+        for (int b = 0; b < TN; ++b) fb[kk][b] = dtl_frag<BKM, BN, BK>(curB, wn0 + b * 32, kk);
+      }
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+          for (int b = 0; b < TN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kk][b], fa[kk][a], acc[a][b], 0, 0, 0);
+    }
+  }
+  // rows of the tile, eight columns per lane: this lane's pieces and what their epilogue reads
+  constexpr int CPR = BN / 8, PIECES = (BM * CPR + NT - 1) / NT, PITCH = split_pitch(BN);
+  constexpr bool RESID = epi_has_resid(EPI), BIAS = epi_has_bias(EPI), ZIN = EPI == EPI_BF16_DGELU, UPD = EPI == EPI_F32_UPD;
+  f32x4 in[PIECES][2];
+  u32x4 bias[PIECES], zin[PIECES];
+  int64_t at[PIECES];
+  bool ok[PIECES];
+#pragma unroll
+  for (int p = 0; p < PIECES; ++p) {
+    const int idx = threadIdx.x + p * NT, row = idx / CPR, gm = m0 + row, gn = n0 + idx % CPR * 8;
+    ok[p] = row < BM && gm < M && gn < N;
+    const int mc = gm < M ? gm : M - 1, nc = gn < N ? gn : N - 8;
+    at[p] = (int64_t)mc * e.ldo + nc;
+    if (BIAS) bias[p] = load8(e.bias + nc);
+    if (ZIN) zin[p] = *reinterpret_cast<const u32x4*>(e.zin + at[p]);
+    if (RESID || (UPD && e.upd_w)) {
+      const f32x4* src = reinterpret_cast<const f32x4*>(RESID ? e.resid + (int64_t)mc * e.ldr + nc : e.upd_w + at[p]);
+      in[p][0] = src[0]; in[p][1] = src[1];
+    }
+  }
+  __syncthreads();                                         // the rings are free
+  float* image = reinterpret_cast<float*>(dtl_smem);
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int rg = 0; rg < 4; ++rg)
+        *reinterpret_cast<f32x4*>(image + (group * BM + wm0 + i * 32 + (l & 31)) * PITCH + wn0 + j * 32 + 8 * rg + 4 * (l >> 5)) =
+            f32x4{acc[i][j][4 * rg], acc[i][j][4 * rg + 1], acc[i][j][4 * rg + 2], acc[i][j][4 * rg + 3]};
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < PIECES; ++p) {
+    const int idx = threadIdx.x + p * NT, row = idx / CPR, c = idx % CPR * 8;
+    if (BM * CPR % NT != 0 && row >= BM) break;
+    f32x4 v[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      v[h] = *reinterpret_cast<const f32x4*>(image + row * PITCH + c + 4 * h);
+#pragma unroll
+      for (int g = 1; g < G; ++g) v[h] += *reinterpret_cast<const f32x4*>(image + (g * BM + row) * PITCH + c + 4 * h);
+    }
+    if (BIAS) {
+      f32x4 b[2];
+      bf16x8_to_f32(b, bias[p]);
+      v[0] += b[0]; v[1] += b[1];
+    }
+    if (ZIN) {
+      f32x4 z[2];
+      bf16x8_to_f32(z, zin[p]);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[h][k] = ok[p] ? v[h][k] * dgelu_f(z[h][k]) : 0.f;
+      if (e.colpart) {                                     // for the column sums below
+        *reinterpret_cast<f32x4*>(image + row * PITCH + c) = v[0];
+        *reinterpret_cast<f32x4*>(image + row * PITCH + c + 4) = v[1];
+      }
+    }
+    if (!ok[p]) continue;
+    if (EPI == EPI_BF16 || EPI == EPI_BF16_BIAS || EPI == EPI_BF16_BIAS_GELU || EPI == EPI_BF16_DGELU)
+      *reinterpret_cast<u32x4*>((uint16_t*)e.out + at[p]) = f32_to_bf16x8(v);
+    if (EPI == EPI_BF16_BIAS_GELU) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[h][k] = gelu_f(v[h][k]);
+      *reinterpret_cast<u32x4*>((uint16_t*)e.out2 + at[p]) = f32_to_bf16x8(v);
+    }
+    if (RESID) {
+      v[0] += in[p][0]; v[1] += in[p][1];
+      if (EPI == EPI_F32_BIAS_RESID_BF16) store8(e.out2, at[p], f32_to_bf16x8(v));
+    }
+    if ((RESID || EPI == EPI_F32 || UPD) && e.out) {
+      f32x4* dst = reinterpret_cast<f32x4*>((float*)e.out + at[p]);
+      dst[0] = v[0]; dst[1] = v[1];
+    }
+    if (UPD && e.upd_w) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[h][k] = __fmaf_rn(-e.eta, v[h][k], in[p][h][k]);
+      f32x4* dst = reinterpret_cast<f32x4*>(e.upd_w + at[p]);
+      dst[0] = v[0]; dst[1] = v[1];
+      store8(e.out2, at[p], f32_to_bf16x8(v));
+    }
+  }
+  if (ZIN && e.colpart) {                                  // (uniform) NT / BN row lanes per column, added in order
+    constexpr int RL = NT / BN < 4 ? NT / BN : 4;
+    __syncthreads();
+    float* part = image + BM * PITCH;
+    const int c = threadIdx.x % BN, rl = threadIdx.x / BN;
+    if (rl < RL) {
+      float s = 0.f;
+#pragma unroll 8
+      for (int r = rl; r < BM; r += RL) s += image[r * PITCH + c];
+      part[rl * BN + c] = s;
+    }
+    __syncthreads();
+    if (rl == 0 && n0 + c < N) {
+      float s = part[c];
+#pragma unroll
+      for (int q = 1; q < RL; ++q) s += part[q * BN + c];
+      e.colpart[(int64_t)(m0 / BM) * e.ldo + n0 + c] = s;
+    }
+  }
+}
+
+template <int BM, int BN, int G, int NW, int NS, bool AKM, bool BKM, int EPI>
+__global__ __launch_bounds__(64 * NW * G, NW * G / 4) void gemm_split_kernel(const uint16_t* __restrict__ A, int64_t lda,
+                                                                const uint16_t* __restrict__ B, int64_t ldb, int M, int N, int K,
+                                                                int tiles_m, int tiles_n, Epi e) {
+  int bm, bn;
+  tile_of_block(-tiles_m, tiles_n, 8, bm, bn);
+  gemm_split_body<BM, BN, G, NW, NS, AKM, BKM, EPI>(A, lda, B, ldb, M, N, K, bm, bn, e);
+}
+
 // Several independent products of one kind in a single launch (the four weight-gradient
 // products of a decoder block): a workgroup finds its problem from the running tile count.
 // One launch fills the chip where four small grids would each leave most CUs idle.
@@ -782,8 +1008,8 @@ struct GroupedArgs {
   int count;
 };
 
-template <int BM, int BN, int BK, int NS, int NW, int WPE>
-__global__ __launch_bounds__(64 * NW, WPE) void gemm_dtl_grouped_wgrad_kernel(GroupedArgs ga) {
+// the problem, tile row and tile column of a workgroup
+__device__ __forceinline__ const GroupedProblem& grouped_tile(const GroupedArgs& ga, int& bm, int& bn) {
   // Workgroup ids are dealt to the 8 XCDs in turn, and each XCD pulls its operand panels
   // through its own L2.  Give XCD g a CONTIGUOUS range of the tile numbering (so it works on
   // one problem at a time, not on a slice of all of them) and number a problem's tiles in bands
@@ -801,9 +1027,25 @@ __global__ __launch_bounds__(64 * NW, WPE) void gemm_dtl_grouped_wgrad_kernel(Gr
   const int band = local / (GB * q.tiles_n), first_row = band * GB;
   const int rows = q.tiles_m - first_row < GB ? q.tiles_m - first_row : GB;
   const int in = local - band * GB * q.tiles_n;
-  Epi e{q.out, q.ldo, q.upd_ver, nullptr, nullptr, 0, nullptr, q.upd_w, q.eta, nullptr};
-  gemm_dtl_body<BM, BN, BK, NS, NW, true, true, EPI_F32_UPD>(q.A, q.lda, q.B, q.ldb, q.M, q.N, q.K, first_row + in % rows,
-                                                      in / rows, e);
+  bm = first_row + in % rows;
+  bn = in / rows;
+  return q;
+}
+__device__ __forceinline__ Epi grouped_epi(const GroupedProblem& q) {
+  return Epi{q.out, q.ldo, q.upd_ver, nullptr, nullptr, 0, nullptr, q.upd_w, q.eta, nullptr};
+}
+
+template <int BM, int BN, int BK, int NS, int NW, int WPE>
+__global__ __launch_bounds__(64 * NW, WPE) void gemm_dtl_grouped_wgrad_kernel(GroupedArgs ga) {
+  int bm, bn;
+  const GroupedProblem& q = grouped_tile(ga, bm, bn);
+  gemm_dtl_body<BM, BN, BK, NS, NW, true, true, EPI_F32_UPD>(q.A, q.lda, q.B, q.ldb, q.M, q.N, q.K, bm, bn, grouped_epi(q));
+}
+template <int BM, int BN, int G, int NW, int NS>
+__global__ __launch_bounds__(64 * NW * G, NW * G / 4) void gemm_split_grouped_wgrad_kernel(GroupedArgs ga) {
+  int bm, bn;
+  const GroupedProblem& q = grouped_tile(ga, bm, bn);
+  gemm_split_body<BM, BN, G, NW, NS, true, true, EPI_F32_UPD>(q.A, q.lda, q.B, q.ldb, q.M, q.N, q.K, bm, bn, grouped_epi(q));
 }
 
 template <int BM, int BN, int BK, int NS, int NW, int WPE, bool AKM, bool BKM, int EPI>
@@ -834,33 +1076,75 @@ rv_status launch_dtl(const rv_gemm_args& g, hipStream_t st) {
   return rv_launch_status();
 }
 
-// Tile choice (codes: 5256, 2256, 2192, 2128).
+template <int BM, int BN, int G, int NW, int NS, bool AKM, bool BKM, int EPI>
+rv_status launch_split(const rv_gemm_args& g, hipStream_t st) {
+  constexpr int smem = split_lds<BM, BN, G, NS>();
+  static_assert(smem <= 160 * 1024, "LDS of one CU");
+  auto kern = gemm_split_kernel<BM, BN, G, NW, NS, AKM, BKM, EPI>;
+  static const hipError_t configured =
+      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+  if (configured != hipSuccess) return RV_E_DEVICE;
+  const int tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN;
+  Epi e{g.out, g.ldo, g.out2, g.bias, g.resid, g.ldr, g.zin, nullptr, 0.f, g.epi == EPI_BF16_DGELU ? g.colpart : nullptr};
+  g.colpart_rows = tm;
+  hipLaunchKernelGGL(kern, dim3(tm * tn), dim3(64 * NW * G), smem, st, g.A, g.lda, g.B, g.ldb, g.M, g.N, g.K, tm, tn, e);
+  return rv_launch_status();
+}
+
+// Tile choice (codes: 5256, 2256, 2192, 2128, 1128, 1065, 1064, 1032).
 //   5256  256x256, eight waves of 128x64, BK 32, ring of four slots run in the pipelined form
 //         (three tiles in flight, loads dealt out behind the MFMAs), one workgroup per CU:
 //         lowest LDS traffic per MFMA, two waves per SIMD cover each other's stalls;
 //   2192  128x256, four waves of 64x128, BK 32, three stages, two workgroups per CU;
-//   2128  128x128, four waves of 64x64, BK 64, two stages, two workgroups per CU: fills the
-//         chip on small outputs.
-// The automatic choice minimises  rounds * tile_area * workgroups_per_CU / efficiency  with
-// rounds = ceil(tiles / (256 CUs * workgroups_per_CU)); efficiencies are measured ratios.
+//   2128  128x128, four waves of 64x64, BK 64, two stages, two workgroups per CU;
+//   1128  128x128, 1065 / 1064 64x64, 1032 32x64: the contraction split inside the workgroup over
+//         2, 2 / 4 and 8 groups of waves.
+// The automatic choice minimises the modelled time
+//   rounds * (f + turns * t),  rounds = ceil(tiles / (256 CUs * workgroups per CU)), turns = k-tiles per group,
+// f and t in us, t between t0 (a launch that leaves most CUs idle) and t1 (one that fills them), fitted to
+// launches of 64 .. 8192 rows alone.  A product of few tiles is one walk along K: 256x448x1792 takes 36 us
+// with 5256, 20 with 2128 and 7 with 1032; 128x1024x4096 75 / 44 / 15; 1152x768x3072 59 / 34 / 16
+// (1064); 4096x1024x4096 77 / 48 / 36 (1128); 8192x6400x1600 183 / 204 / 261.
+struct TileForm { int code, bm, bn, k, per_cu; float f, t0, t1; };
+constexpr TileForm kForms[] = {
+    {5256, 256, 256, 32, 1, 4.9f, 0.53f, 0.86f}, {2192, 128, 256, 32, 2, 3.5f, 0.42f, 1.05f}, {2128, 128, 128, 64, 2, 2.8f, 0.58f, 1.10f},
+    {1128, 128, 128, 64, 1, 3.9f, 0.43f, 0.56f}, {1065, 64, 64, 64, 2, 2.3f, 0.265f, 0.47f}, {1064, 64, 64, 128, 1, 2.7f, 0.44f, 0.64f},
+    {1032, 32, 64, 256, 1, 2.4f, 0.72f, 0.82f}};
+int best_form(int M, int N, int K, int codes_from, int codes_to, float& least) {
+  int best = 0;
+  for (const TileForm& c : kForms) {
+    if (c.code < codes_from || c.code >= codes_to) continue;
+    const float tiles = (float)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn), slots = 256.f * c.per_cu;
+    const float fill = tiles < slots ? tiles / slots : 1.f;
+    const float time = ceilf(tiles / slots) * (c.f + ceilf((float)K / c.k) * (c.t0 + (c.t1 - c.t0) * fill * fill));
+    if (!best || time < least) { best = c.code; least = time; }
+  }
+  return best;
+}
+
 template <bool AKM, bool BKM, int EPI>
 rv_status pick_tile(const rv_gemm_args& g, hipStream_t st) {
-  auto cost = [&](int bm, int bn, int bpc, double eff) {
-    const long tiles = (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
-    const long rounds = (tiles + 256 * bpc - 1) / (256 * bpc);
-    return (double)rounds * bm * bn * bpc / eff;
-  };
   int tile = g.tile;
-  if (tile == 0 && g.sharing) {
-    // Measured inside the stage step (configs 2, 3, 5): what a launch leaves of the chip is
-    // used by the other streams, so CU time per flop counts for more than its own duration.
-    const long t256 = (long)((g.M + 255) / 256) * ((g.N + 255) / 256);
-    if (g.sharing == 2 || t256 >= 128) tile = 5256;
-  }
   if (tile == 0) {
-    const double c256 = cost(256, 256, 1, 1.0), c192 = cost(128, 256, 2, 0.92), c128 = cost(128, 128, 2, 0.85);
-    tile = c256 <= c192 && c256 <= c128 ? 5256 : (c192 <= c128 ? 2192 : 2128);
+    // Whether the contraction is split depends on the shape alone, so that a product has the same
+    // bits beside other streams as by itself; and it has to gain a quarter of the launch's time: a split
+    // tile takes more CU time per flop, which the other streams of a step could have used (with
+    // 4096x1024x4096 split, 49 against 61 us alone, the step of the 1024-wide stage is 6 % longer).
+    float in_order = 0.f, split = 0.f;
+    tile = best_form(g.M, g.N, g.K, 2000, 10000, in_order);
+    const int s = best_form(g.M, g.N, g.K, AKM ? 1033 : 0, 2000, split);
+    const long t256 = (long)((g.M + 255) / 256) * ((g.N + 255) / 256);
+    if (split < 0.75f * in_order) tile = s;
+    // Measured inside the stage step (d = 1024, 1600, 2048): what a launch leaves of the chip is
+    // used by the other streams, so CU time per flop counts for more than its own duration.
+    else if (g.sharing == 2 || (g.sharing && t256 >= 128)) tile = 5256;
   }
+  if constexpr (!AKM) {
+    if (tile == 1032) return launch_split<32, 64, 8, 2, 3, AKM, BKM, EPI>(g, st);
+  }
+  if (tile == 1064) return launch_split<64, 64, 4, 4, 4, AKM, BKM, EPI>(g, st);
+  if (tile == 1065) return launch_split<64, 64, 2, 4, 4, AKM, BKM, EPI>(g, st);
+  if (tile == 1128) return launch_split<128, 128, 2, 4, 4, AKM, BKM, EPI>(g, st);
   if (tile == 2256) return launch_dtl<256, 256, 32, 4, 4, 1, AKM, BKM, EPI>(g, st);
   if (tile == 2192) return launch_dtl<128, 256, 32, 3, 4, 2, AKM, BKM, EPI>(g, st);
   if (tile == 2128) return launch_dtl<128, 128, 64, 2, 4, 2, AKM, BKM, EPI>(g, st);
@@ -909,8 +1193,8 @@ rv_status rv_gemm_bf16(const rv_gemm_args& g, hipStream_t st) {
 }
 
 namespace {
-template <int BM, int BN, int BK, int NS, int NW>
-rv_status launch_grouped(const rv_gemm_args* gs, int count, hipStream_t st) {
+rv_status launch_grouped(void (*kern)(GroupedArgs), int BM, int BN, int threads, int smem, const rv_gemm_args* gs, int count,
+                         hipStream_t st) {
   GroupedArgs ga;
   int tiles = 0;
   for (int k = 0; k < count; ++k) {
@@ -926,6 +1210,11 @@ rv_status launch_grouped(const rv_gemm_args* gs, int count, hipStream_t st) {
   }
   for (int k = count; k < RV_GEMM_GROUP_MAX; ++k) ga.p[k] = ga.p[0];
   ga.count = count;
+  hipLaunchKernelGGL(kern, dim3(tiles), dim3(threads), smem, st, ga);
+  return rv_launch_status();
+}
+template <int BM, int BN, int BK, int NS, int NW>
+rv_status launch_grouped_dtl(const rv_gemm_args* gs, int count, hipStream_t st) {
   constexpr int ring = NS * (dtl_tile_bytes(BM, BK) + dtl_tile_bytes(BN, BK));
   constexpr int smem = ring > upd_image_bytes(BM, BN) ? ring : upd_image_bytes(BM, BN);
   static_assert(smem <= 160 * 1024, "LDS of one CU");
@@ -933,12 +1222,21 @@ rv_status launch_grouped(const rv_gemm_args* gs, int count, hipStream_t st) {
   static const hipError_t configured =
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   if (configured != hipSuccess) return RV_E_DEVICE;
-  hipLaunchKernelGGL(kern, dim3(tiles), dim3(64 * NW), smem, st, ga);
-  return rv_launch_status();
+  return launch_grouped(kern, BM, BN, 64 * NW, smem, gs, count, st);
+}
+template <int BM, int BN, int G, int NW, int NS>
+rv_status launch_grouped_split(const rv_gemm_args* gs, int count, hipStream_t st) {
+  constexpr int smem = split_lds<BM, BN, G, NS>();
+  static_assert(smem <= 160 * 1024, "LDS of one CU");
+  auto kern = gemm_split_grouped_wgrad_kernel<BM, BN, G, NW, NS>;
+  static const hipError_t configured =
+      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+  if (configured != hipSuccess) return RV_E_DEVICE;
+  return launch_grouped(kern, BM, BN, 64 * NW * G, smem, gs, count, st);
 }
 }  // namespace
 
-rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t st) {
+rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t st, bool in_order) {
   if (!gs || count < 1 || count > RV_GEMM_GROUP_MAX) return RV_E_INVAL;
   for (int k = 0; k < count; ++k) {
     const rv_gemm_args& g = gs[k];
@@ -954,7 +1252,16 @@ rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t s
   // 256x256 tiles, eight waves (measured against 128x128 and 128x256 tiles, alone and inside the
   // stage step of configs 2, 3 and 5: fewest LDS bytes per MFMA, so it takes the least CU time
   // from the kernels that run beside it, and the step is 3-4 % shorter)
-  return launch_grouped<256, 256, 32, 4, 8>(gs, count, st);
+  // A block whose 256x256 tiles do not cover the chip and whose walk along the tokens is short takes
+  // 128x128 tiles with the walk split in two, four times as many: 24 -> 12 us (d 448, ffn 1792, 256
+  // tokens, 44 tiles), 37 -> 34 us (768, 3072, 1152 tokens, 108); even at 30 us with 128 tokens of a
+  // 1024-wide block, where the update's 126 MB bound it.  Longer walks keep the CU time per flop down.
+  if (!in_order) {
+    int tiles = 0;
+    for (int k = 0; k < count; ++k) tiles += ((gs[k].M + 255) / 256) * ((gs[k].N + 255) / 256);
+    if (tiles < 256 && gs[0].K < 2048) return launch_grouped_split<128, 128, 2, 4, 4>(gs, count, st);
+  }
+  return launch_grouped_dtl<256, 256, 32, 4, 8>(gs, count, st);
 }
 
 extern "C" rv_status rv_k_gemm_bf16(const void* A, int64_t lda, int a_kmajor, const void* B, int64_t ldb,
@@ -979,5 +1286,5 @@ extern "C" rv_status rv_k_gemm_wgrad_grouped(int count, const void* const* X, co
     g[k].B = (const uint16_t*)dY[k]; g[k].ldb = ldb[k]; g[k].b_kmajor = 1;
     g[k].M = M[k]; g[k].N = N[k]; g[k].K = K; g[k].epi = EPI_F32; g[k].out = dW[k]; g[k].ldo = N[k];
   }
-  return rv_gemm_wgrad_grouped(g, count, (hipStream_t)stream);
+  return rv_gemm_wgrad_grouped(g, count, (hipStream_t)stream, true);
 }

@@ -30,7 +30,7 @@ struct rv_gemm_args {
   const uint16_t* bias = nullptr;         // bf16 [N]
   const float* resid = nullptr; int64_t ldr = 0;
   const uint16_t* zin = nullptr;          // bf16 [M, ldo] pre-activations for GELU'
-  int tile = 0;                           // 0 = choose, 128 or 256 = force
+  int tile = 0;                           // 0 = choose, else the code of a tile form
   // who else is on the chip while this product runs (automatic tile choice only):
   //   0  nobody: shortest time of this launch alone
   //   1  the other streams of a stage step, and the launch is on the step's critical chain:
@@ -40,7 +40,7 @@ struct rv_gemm_args {
   // weight-gradient products of the grouped launch only: the delayed update of Eq. 2 applied in
   // the epilogue.  upd_w = fp32 master tile base (same [M, ldo] layout as out), upd_ver = bf16
   // weight-version tile base; the gradient itself is stored to `out` only if store_out.
-  // GELU' epilogue only: if given, fp32 [ceil(M / tile rows), ldo] partial column sums of the
+  // GELU' epilogue only: if given, fp32 [ceil(M / tile rows), ldo] (tile rows >= 32) partial column sums of the
   // output (the bias gradient of the Linear whose pre-activation gradient this is), one row per
   // tile row; the number of rows written comes back in colpart_rows
   float* colpart = nullptr;
@@ -54,7 +54,9 @@ rv_status rv_gemm_bf16(const rv_gemm_args& g, hipStream_t st);
 // up to RV_GEMM_GROUP_MAX weight-gradient products (both operands k-major, fp32 output) in one launch
 #define RV_GEMM_GROUP_MAX 4
 rv_status rv_stage_update_range(rv_stage* s, size_t off, size_t n, hipStream_t st);
-rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t st);
+// in_order: every product summed in order of k, as rv_gemm_bf16 with tile 5256 does; otherwise small
+// blocks take tiles whose contraction is split
+rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t st, bool in_order = false);
 
 // ---- norm.hip ---------------------------------------------------------------------
 rv_status rv_ln_fwd(const void* x, int x_is_bf16, float* xcopy, const uint16_t* gamma, const uint16_t* beta,

@@ -143,3 +143,15 @@ def test_grouped_weight_gradient_products():
     import paper_2401_01728_amd as rv
     with pytest.raises(rv.RvError):
         k.gemm_wgrad_grouped(xs * 2, dys * 2, outs * 2)      # more than four
+
+
+# an eighth of a tile, one tile exactly, a ragged second tile; K = 2, 4, 10 and 34 tiles of 32 (fewer than a
+# workgroup's groups, as many, a partly filled turn, several turns of every ring)
+@pytest.mark.parametrize("M,N,K", [(8, 8, 64), (64, 64, 128), (136, 200, 320), (40, 136, 1088), (264, 72, 64)])
+@pytest.mark.parametrize("tile", [1032, 1064, 1065, 1128])
+def test_split_contraction(M, N, K, tile):
+    """Tiles whose contraction is split over groups of waves: every layout and epilogue (bars as above)."""
+    test_forward_product_and_epilogues(M, N, K, tile)
+    test_input_gradient_product(M, N, K, tile)
+    if tile != 1032:
+        test_weight_gradient_product(M, N, K, tile)
