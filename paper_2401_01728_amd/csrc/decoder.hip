@@ -167,15 +167,18 @@ rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
   // fused update (plain Eq. 2): every kernel that completes a parameter gradient applies it at once
   // to the fp32 master and writes the bf16 rounding into the new weight version `vdst`
   uint16_t* vdst = s->fused ? (uint16_t*)s->ver[s->upd_dst] : nullptr;
-  rv_reduce_update ru;
-  ru.eta = s->eta; ru.store = s->keep_grad;
-  auto upd = [&](float* const* dst, int n) -> const rv_reduce_update* {
-    if (!s->fused) return nullptr;
-    for (int k = 0; k < n; ++k) {
-      const size_t off = (size_t)(dst[k] - s->grad);
-      ru.w[k] = s->master + off; ru.ver[k] = vdst + off;
-    }
-    return &ru;
+  // The column sums of a block (bias and LayerNorm-affine gradients) are listed here as their partial
+  // rows come into being.  They go out in one launch at the block's end: with four launches per block,
+  // each behind an event pair of its own, the host was what bounded small stages (12 blocks of d 448 on
+  // 256 tokens, stage step 1.53 -> 1.26 ms; 6 blocks of d 768, 1152 tokens, four microbatches
+  // 6.06 -> 5.84 ms).  A stage whose weight-gradient products leave early (below) sends them along with
+  // those: one launch at the end made the stage step 0.8 % longer at 12 blocks of d 1600, 8192 tokens.
+  rv_reduce_job sums[RV_REDUCE_MAX];
+  int n_sums = 0;
+  auto colsum = [&](const float* part, int rows, int64_t pitch, int n, float* dst) {
+    const size_t off = (size_t)(dst - s->grad);
+    sums[n_sums++] = rv_reduce_job{part, !s->fused || s->keep_grad ? dst : nullptr, s->fused ? s->master + off : nullptr,
+                                   s->fused ? vdst + off : nullptr, pitch, rows, n};
   };
 
   // Everything that only feeds the parameter gradient - the four weight-gradient products of a
@@ -192,16 +195,18 @@ rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
     return RV_OK;
   };
 
+  auto send_sums = [&]() -> rv_status {
+    const int n = n_sums;
+    n_sums = 0;
+    return rv_reduce_rows(sums, n, s->eta, ws);
+  };
+
   // gradient of the last block's output: fp32 copy for the residual path, bf16 as operand
   // (summed over tokens it is also the gradient of the last block's b2: partial sums on the way)
   float* part_dy = (float*)(s->work + p.w_part_dy);
   RV_TRY(rv_widen_colsum((const uint16_t*)grad_out, dres, part_dy, T, d, st));
   const uint16_t* dres16 = (const uint16_t*)grad_out;
-  {
-    float* out = s->grad + (size_t)(p.L - 1) * p.per_block + p.b2;
-    RV_TRY(side_begin());
-    RV_TRY(rv_reduce_rows(part_dy, rv_widen_parts(T), d, d, out, ws, upd(&out, 1)));
-  }
+  colsum(part_dy, rv_widen_parts(T), d, d, s->grad + (size_t)(p.L - 1) * p.per_block + p.b2);
   // When the four weight-gradient products of a block go to the side stream.  Launch points:
   // 0 behind the GELU' product (dz exists: dW2 and dW1 can run), 1 behind the second LayerNorm's
   // backward (dx1 exists: dWo), 2 behind the attention backward (dqkv exists: all four).  One
@@ -213,12 +218,15 @@ rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
   //   (d 1024, ffn 4096);
   //   dWo on its own at point 1 as well:  -2.8 %, -1.2 %, +7 % in the same order.
   // So: the feed-forward pair goes out early when it fills the chip at least once, and dWo leaves
-  // dWqkv only when the two together are not a whole number of rounds anyway.
+  // dWqkv only when the two together are not a whole number of rounds anyway.  (All four behind the
+  // first LayerNorm's backward, one event pair less per block: +4 % at d 2048, d 1024 and 6 blocks of
+  // d 768 on 1152 tokens, -5 % only at 12 blocks of d 448 on 256 tokens, where the host is the limit.)
   const int kCUs = 256;
   auto tiles = [](int M, int N) { return ((M + 255) / 256) * ((N + 255) / 256); };
   const int n_ffn = 2 * tiles(d, f), n_o = tiles(d, d), n_qkv = tiles(d, 3 * d);
   int wg_pos[4] = {2, 2, 2, 2};   // dW2, dW1, dWo, dWqkv
-  if (n_ffn >= kCUs) {
+  const bool early = n_ffn >= kCUs;
+  if (early) {
     wg_pos[0] = wg_pos[1] = 0;
     if ((n_o + n_qkv) % kCUs != 0) wg_pos[2] = 1;
   }
@@ -251,6 +259,7 @@ rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
       for (int k = 0; k < 4; ++k)
         if (wg_pos[k] == pos) grp[n++] = wg[k];
       if (!n) return RV_OK;
+      if (pos != 1) RV_TRY(side_begin());   // (at 1 the side stream already waits for the LayerNorm backward)
       if (s->prof_on) {   // measurement aid: bracket the launch with events on its own stream
         hipEvent_t e0 = nullptr, e1 = nullptr;
         RV_HIP_TRY(hipEventCreate(&e0));
@@ -281,46 +290,40 @@ rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
     RV_TRY(gemm(sh, st, dres16, d, 0, w + p.w2, d, 0, T, f, d, RV_EPI_BF16_DGELU, dz, f, nullptr, nullptr, nullptr, z,
                 part_dz, &dz_parts));
     wgrad(1, v2, d, dz, f, d, f, gl + p.w1);                                                         // dW1 = v2^T dz
-    RV_TRY(side_begin());
     RV_TRY(side_launch(0));
-    {
-      float* out = gl + p.b1;
-      RV_TRY(rv_reduce_rows(part_dz, dz_parts, f, f, out, ws, upd(&out, 1)));
-    }
+    colsum(part_dz, dz_parts, f, f, gl + p.b1);
+    if (early) RV_TRY(send_sums());
     RV_TRY(gemm(sh, st, dz, f, 0, w + p.w1, f, 0, T, d, f, RV_EPI_BF16, dtmp, d));                       // dv2 = dz W1^T
     RV_TRY(rv_ln_bwd(dtmp, x1, (const float*)(sb + p.s_m2), (const float*)(sb + p.s_r2), w + p.ln2g, dres, dres,
                      dx1_16, part2, T, d, st));
-    {
-      const float* src[3] = {part2, part2 + d, part2 + 2 * d};
-      float* dst[3] = {gl + p.ln2g, gl + p.ln2b, gl + p.bo};                                         // dbo = sum dx1
+    colsum(part2, ln_parts, 3 * (int64_t)d, d, gl + p.ln2g);
+    colsum(part2 + d, ln_parts, 3 * (int64_t)d, d, gl + p.ln2b);
+    colsum(part2 + 2 * d, ln_parts, 3 * (int64_t)d, d, gl + p.bo);                                     // dbo = sum dx1
+    if (early) {
       RV_TRY(side_begin());
-      RV_TRY(rv_reduce_rows_multi(src, dst, 3, ln_parts, 3 * (int64_t)d, d, ws, upd(dst, 3)));
+      RV_TRY(send_sums());
     }
     // attention half
     wgrad(2, a, d, dx1_16, d, d, d, gl + p.wo);                                                      // dWo = a^T dx1
-    RV_TRY(side_launch(1));   // (the side stream already waits for the LayerNorm backward above)
+    RV_TRY(side_launch(1));
     RV_TRY(gemm(sh, st, dx1_16, d, 0, w + p.wo, d, 0, T, d, d, RV_EPI_BF16, dtmp, d));                   // da = dx1 Wo^T
     // (the attention backward also leaves partial column sums of dqkv: the qkv bias gradient)
     float* part_qkv = (float*)(s->work + p.w_part_qkv[par]);
     RV_TRY(rv_attn_bwd(qkv, a, dtmp, (const float*)(sb + p.s_lse), Dbuf, dqkv, p.mb, p.S, d, p.H, st, part_qkv));
     wgrad(3, u, d, dqkv, 3 * d, d, 3 * d, gl + p.wqkv);                                              // dWqkv = u^T dqkv
-    RV_TRY(side_begin());
     RV_TRY(side_launch(2));
-    {
-      float* out = gl + p.bqkv;
-      RV_TRY(rv_reduce_rows(part_qkv, rv_attn_colsum_parts(p.mb, p.S), 3 * d, 3 * d, out, ws, upd(&out, 1)));
-    }
+    colsum(part_qkv, rv_attn_colsum_parts(p.mb, p.S), 3 * d, 3 * d, gl + p.bqkv);
+    if (early) RV_TRY(send_sums());
     RV_TRY(gemm(sh, st, dqkv, 3 * d, 0, w + p.wqkv, 3 * d, 0, T, d, 3 * d, RV_EPI_BF16, dtmp, d));       // du
     uint16_t* dx16 = l == 0 ? (uint16_t*)grad_in : dy_below;
     RV_TRY(rv_ln_bwd(dtmp, x, (const float*)(sb + p.s_m1), (const float*)(sb + p.s_r1), w + p.ln1g, dres, dres, dx16,
                      part1, T, d, st));
-    {
-      // the residual gradient leaving this block is dy of the block below: its b2 gradient
-      const float* src[3] = {part1, part1 + d, part1 + 2 * d};
-      float* dst[3] = {gl + p.ln1g, gl + p.ln1b, l > 0 ? s->grad + (size_t)(l - 1) * p.per_block + p.b2 : nullptr};
-      RV_TRY(side_begin());
-      RV_TRY(rv_reduce_rows_multi(src, dst, l > 0 ? 3 : 2, ln_parts, 3 * (int64_t)d, d, ws, upd(dst, l > 0 ? 3 : 2)));
-    }
+    colsum(part1, ln_parts, 3 * (int64_t)d, d, gl + p.ln1g);
+    colsum(part1 + d, ln_parts, 3 * (int64_t)d, d, gl + p.ln1b);
+    // the residual gradient leaving this block is dy of the block below: its b2 gradient
+    if (l > 0) colsum(part1 + 2 * d, ln_parts, 3 * (int64_t)d, d, s->grad + (size_t)(l - 1) * p.per_block + p.b2);
+    RV_TRY(side_begin());
+    RV_TRY(send_sums());
     // every gradient of block l is complete behind this point of `ws` (its b2 gradient came
     // from the block above); unless the epilogues above have applied it already, the delayed
     // update of the block follows at once

@@ -69,19 +69,19 @@ rv_status rv_ln_bwd(const uint16_t* dy, const float* x, const float* mean, const
 // blocks of 32 rows
 int rv_widen_parts(int T);
 rv_status rv_widen_colsum(const uint16_t* a, float* o, float* part, int T, int d, hipStream_t st);
-// out_k[c] = sum_r src_k[r * pitch + c].  upd (may be null): per job the fp32 master vector and the
-// bf16 weight-version vector the column sums update in place, w <- w - eta * sum (Eq. 2); with
-// store = false the sums themselves are not written.
-struct rv_reduce_update {
-  float* w[4];
-  uint16_t* ver[4];
-  float eta;
-  bool store;
+// out[c] = sum_r src[r * pitch + c] for r < R, c < N, each job of a list in the same launch.  w (may be
+// null) with ver: the fp32 master vector and the bf16 weight-version vector the column sums update,
+// w <- w - eta * sum (Eq. 2); out null: the sums themselves are not written.
+#define RV_REDUCE_MAX 9
+struct rv_reduce_job {
+  const float* src;
+  float* out;
+  float* w;
+  uint16_t* ver;
+  int64_t pitch;
+  int R, N;
 };
-rv_status rv_reduce_rows_multi(const float* const* src, float* const* out, int njobs, int R, int64_t pitch,
-                               int N, hipStream_t st, const rv_reduce_update* upd = nullptr);
-rv_status rv_reduce_rows(const float* part, int R, int64_t pitch, int N, float* out, hipStream_t st,
-                         const rv_reduce_update* upd = nullptr);
+rv_status rv_reduce_rows(const rv_reduce_job* jobs, int njobs, float eta, hipStream_t st);
 
 // ---- attention.hip ----------------------------------------------------------------
 rv_status rv_attn_fwd(const uint16_t* qkv, uint16_t* out, float* lse2, int mb, int S, int d, int H,

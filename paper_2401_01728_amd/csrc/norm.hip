@@ -460,21 +460,27 @@ __global__ __launch_bounds__(kThreads) void widen_colsum_kernel(const uint16_t* 
   *reinterpret_cast<f32x4*>(part + (int64_t)blockIdx.y * d + c) = acc;
 }
 
-// out_k[c] = sum_r src_k[r * pitch + c] for up to four (src, out) pairs in one launch
-// (blockIdx.y picks the pair).  32 columns x 8 row lanes per workgroup; every row lane adds
-// its rows in order, the eight partial sums are combined in a fixed order.
+// out_k[c] = sum_r src_k[r * pitch_k + c] for a list of jobs in one launch.  32 columns x 8 row lanes
+// per workgroup, a job's workgroups next to each other; every row lane adds its rows in order, the
+// eight partial sums are combined in a fixed order.  A launch is a few microseconds however small, so
+// what counts is how many there are: all the sums of a decoder block go out together (see rv_dec_backward).
 struct ReduceJobs {
-  const float* src[4];
-  float* out[4];      // null: the sums are not stored
-  float* w[4];        // fp32 parameters updated in place with the sums (null: none), and
-  uint16_t* ver[4];   // their bf16 weight version
+  rv_reduce_job j[RV_REDUCE_MAX];
+  int first[RV_REDUCE_MAX];   // first workgroup of the job; beyond the last job: past the grid
   float eta;
 };
-__global__ __launch_bounds__(kThreads) void reduce_rows_kernel(ReduceJobs jobs, int R, int64_t pitch, int N) {
+__global__ __launch_bounds__(kThreads) void reduce_rows_kernel(ReduceJobs jobs) {
   __shared__ float red[8][33];
-  const float* __restrict__ src = jobs.src[blockIdx.y];
+  int ji = 0;
+#pragma unroll
+  for (int k = 1; k < RV_REDUCE_MAX; ++k)
+    if ((int)blockIdx.x >= jobs.first[k]) ji = k;
+  const rv_reduce_job& job = jobs.j[ji];
+  const float* __restrict__ src = job.src;
+  const int R = job.R, N = job.N;
+  const int64_t pitch = job.pitch;
   const int cl = threadIdx.x & 31, rl = threadIdx.x >> 5;
-  const int c = blockIdx.x * 32 + cl;
+  const int c = ((int)blockIdx.x - jobs.first[ji]) * 32 + cl;
   float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // eight loads in flight per lane
   if (c < N) {
     int r = rl;
@@ -497,11 +503,11 @@ __global__ __launch_bounds__(kThreads) void reduce_rows_kernel(ReduceJobs jobs, 
     float t = red[0][cl];
 #pragma unroll
     for (int w = 1; w < 8; ++w) t += red[w][cl];
-    if (jobs.out[blockIdx.y]) jobs.out[blockIdx.y][c] = t;
-    if (jobs.w[blockIdx.y]) {   // delayed update of this small parameter vector (Eq. 2), where its gradient is born
-      const float r = __fmaf_rn(-jobs.eta, t, jobs.w[blockIdx.y][c]);
-      jobs.w[blockIdx.y][c] = r;
-      jobs.ver[blockIdx.y][c] = rv_f32_to_bf16(r);
+    if (job.out) job.out[c] = t;
+    if (job.w) {   // delayed update of this small parameter vector (Eq. 2), where its gradient is born
+      const float r = __fmaf_rn(-jobs.eta, t, job.w[c]);
+      job.w[c] = r;
+      job.ver[c] = rv_f32_to_bf16(r);
     }
   }
 }
@@ -577,25 +583,21 @@ rv_status rv_widen_colsum(const uint16_t* a, float* o, float* part, int T, int d
   return rv_launch_status();
 }
 
-rv_status rv_reduce_rows_multi(const float* const* src, float* const* out, int njobs, int R, int64_t pitch,
-                               int N, hipStream_t st, const rv_reduce_update* upd) {
-  if (njobs < 1 || njobs > 4 || R < 1 || N < 1) return RV_E_INVAL;
-  ReduceJobs j;
-  j.eta = upd ? upd->eta : 0.f;
-  for (int k = 0; k < 4; ++k) {
-    j.src[k] = k < njobs ? src[k] : nullptr;
-    j.out[k] = k < njobs && (!upd || upd->store) ? out[k] : nullptr;
-    j.w[k] = k < njobs && upd ? upd->w[k] : nullptr;
-    j.ver[k] = k < njobs && upd ? upd->ver[k] : nullptr;
-    if (k < njobs && (!src[k] || !out[k] || (upd && (!upd->w[k] || !upd->ver[k])))) return RV_E_INVAL;
+rv_status rv_reduce_rows(const rv_reduce_job* jobs, int njobs, float eta, hipStream_t st) {
+  if (!jobs || njobs < 1 || njobs > RV_REDUCE_MAX) return RV_E_INVAL;
+  ReduceJobs a = {};
+  a.eta = eta;
+  int groups = 0;
+  for (int k = 0; k < njobs; ++k) {
+    const rv_reduce_job& j = jobs[k];
+    if (!j.src || j.R < 1 || j.N < 1 || (!j.out && !j.w) || (j.w != nullptr) != (j.ver != nullptr)) return RV_E_INVAL;
+    a.j[k] = j;
+    a.first[k] = groups;
+    groups += (j.N + 31) / 32;
   }
-  hipLaunchKernelGGL(reduce_rows_kernel, dim3((N + 31) / 32, njobs), dim3(kThreads), 0, st, j, R, pitch, N);
+  for (int k = njobs; k < RV_REDUCE_MAX; ++k) a.first[k] = groups;
+  hipLaunchKernelGGL(reduce_rows_kernel, dim3(groups), dim3(kThreads), 0, st, a);
   return rv_launch_status();
-}
-
-rv_status rv_reduce_rows(const float* part, int R, int64_t pitch, int N, float* out, hipStream_t st,
-                         const rv_reduce_update* upd) {
-  return rv_reduce_rows_multi(&part, &out, 1, R, pitch, N, st, upd);
 }
 
 extern "C" rv_status rv_k_layernorm_fwd(const void* x, int x_is_bf16, float* xcopy, const void* gamma,
@@ -613,9 +615,10 @@ extern "C" rv_status rv_k_layernorm_bwd(const void* dy, const float* x, const fl
   RV_TRY(rv_ln_bwd((const uint16_t*)dy, x, mean, rstd, (const uint16_t*)gamma, dres, dx, (uint16_t*)dx_bf16,
                    part, T, d, st));
   const int R = rv_ln_bwd_parts(T, d);
-  const float* src[3]; float* out[3]; int n = 0;
-  if (dgamma) { src[n] = part; out[n++] = dgamma; }
-  if (dbeta) { src[n] = part + d; out[n++] = dbeta; }
-  if (dbias) { src[n] = part + 2 * d; out[n++] = dbias; }
-  return n ? rv_reduce_rows_multi(src, out, n, R, 3 * (int64_t)d, d, st) : RV_OK;
+  rv_reduce_job job[3];
+  float* const out[3] = {dgamma, dbeta, dbias};
+  int n = 0;
+  for (int k = 0; k < 3; ++k)
+    if (out[k]) job[n++] = rv_reduce_job{part + (int64_t)k * d, out[k], nullptr, nullptr, 3 * (int64_t)d, R, d};
+  return n ? rv_reduce_rows(job, n, 0.f, st) : RV_OK;
 }
