@@ -18,9 +18,10 @@
 //
 // Softmax runs in base 2: s2 = s * (log2(e)/sqrt(dh)), p = exp2(s2 - m).  The forward
 // stores lse2 = m + log2(sum); the backward recomputes p = exp2(s2 - lse2).
-// Backward is split in two deterministic kernels (no atomics): one accumulates dQ per query
-// tile (and leaves D = rowsum(dO * O) behind), one accumulates dK and dV per key tile over the
-// queries that see it.
+// Backward has two deterministic parts (no atomics): one accumulates dQ per query tile, one
+// accumulates dK and dV per key tile over the queries that see it.  Both need D = rowsum(dO * O):
+// as two launches the first part leaves it behind for the second, in one launch (see rv_attn_bwd)
+// the second forms its own.
 #include <mutex>
 #include "internal.h"
 
@@ -120,6 +121,16 @@ __device__ __forceinline__ void load_owned(bf16x8* f, const uint16_t* __restrict
     f[kk] = *reinterpret_cast<const bf16x8*>(g + (int64_t)(l & 31) * ld + kk * 16 + (l >> 5) * 8);
 }
 
+// acc + the product sum of two chunks of eight bf16
+__device__ __forceinline__ float dot8(u32x4 a, u32x4 b, float acc) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    acc = __fmaf_rn(__uint_as_float(a[e] << 16), __uint_as_float(b[e] << 16), acc);
+    acc = __fmaf_rn(__uint_as_float(a[e] & 0xFFFF0000u), __uint_as_float(b[e] & 0xFFFF0000u), acc);
+  }
+  return acc;
+}
+
 // write a transposed accumulator (lane = row, registers = 4-column groups) as bf16
 template <int DH>
 __device__ __forceinline__ void store_owned(const f32x16* acc, float mul, uint16_t* __restrict__ g, int64_t ld) {
@@ -157,10 +168,10 @@ __device__ __forceinline__ void colsum_owned(const f32x16* acc, float mul, float
 // digit of the id, or whole XCDs get only long (or only short) blocks and the kernel lasts as
 // long as the unluckiest XCD (measured: 1.2x - 1.7x).  rank 0 is the heaviest block, so the
 // long blocks also start first.
-__device__ __forceinline__ void attn_block(int H, int nseq, int& rank, int& h, int& b) {
+__device__ __forceinline__ void attn_block(int block, int H, int nseq, int& rank, int& h, int& b) {
   const int per = H * nseq;
-  rank = blockIdx.x / per;
-  const int rest = blockIdx.x % per;
+  rank = block / per;
+  const int rest = block % per;
   h = rest % H; b = rest / H;
 }
 
@@ -176,7 +187,7 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_kernel(const uint16_t* __re
   constexpr int BUF = L<DH>::KC_BYTES + L<DH>::KM_BYTES;   // K tile (k-contiguous) + V tile (transpose-read)
   const int nblk = (S + BROWS - 1) / BROWS;
   int rank, h, b;
-  attn_block(H, nseq, rank, h, b);
+  attn_block(blockIdx.x, H, nseq, rank, h, b);
   const int qb = nblk - 1 - rank;                          // long rows first
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, grp = l >> 5;
   const int q0 = qb * BROWS + wave * WROWS;
@@ -277,18 +288,28 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_kernel(const uint16_t* __re
 }
 
 // ----------------------------------------------------------------------------------------
-// backward, part 2 (launched second: it reads the D the dQ kernel stores): dK and dV.
-// A wave owns 32 keys (lane = key); queries stream.
+// backward, part 2: dK and dV.  A wave owns 32 keys (lane = key); queries stream.
+// OWN_D: D is formed from the streamed rows of dO and O; else it is read where part 1, launched
+// before, has stored it.
 // ----------------------------------------------------------------------------------------
-template <int DH>
-__global__ __launch_bounds__(kThreads) void attn_bwd_kv_kernel(const uint16_t* __restrict__ qkv, int64_t ld,
-                                                               const uint16_t* __restrict__ dout, int64_t ldo,
-                                                               const float* __restrict__ lse2,
-                                                               const float* __restrict__ Dv,
-                                                               uint16_t* __restrict__ dqkv, int S, int d, int H,
-                                                               int nseq, float c2, float scale,
-                                                               float* __restrict__ colpart) {
-  extern __shared__ __align__(16) char smem[];
+struct BwdArgs {
+  const uint16_t* qkv; int64_t ld;
+  const uint16_t* dout; const uint16_t* out; int64_t ldo;
+  const float* lse2;
+  float* D;
+  uint16_t* dqkv;
+  int S, d, H, nseq;
+  float c2, scale;
+  float* colpart;
+};
+template <int DH, bool OWN_D>
+__device__ __forceinline__ void bwd_kv_body(const BwdArgs& a, int block, char* smem) {
+  const uint16_t* __restrict__ qkv = a.qkv;
+  const uint16_t* __restrict__ dout = a.dout;
+  uint16_t* __restrict__ dqkv = a.dqkv;
+  const int64_t ld = a.ld, ldo = a.ldo;
+  const int S = a.S, d = a.d, H = a.H;
+  const float c2 = a.c2, scale = a.scale;
   char* Qkc = smem;                         // Q tile, k-contiguous (for S = Q K^T)
   char* Qkm = Qkc + L<DH>::KC_BYTES;        // Q tile, transpose-read (for dK^T = Q^T dS)
   char* Okc = Qkm + L<DH>::KM_BYTES;        // dO tile, k-contiguous (for dP = dO V^T)
@@ -296,15 +317,16 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_kv_kernel(const uint16_t* _
   float* stat = reinterpret_cast<float*>(Okm + L<DH>::KM_BYTES);   // lse2[64], D[64]
 
   int jb, h, b;                             // the first key block sees every query: heaviest
-  attn_block(H, nseq, jb, h, b);
+  attn_block(block, H, a.nseq, jb, h, b);
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, grp = l >> 5;
   const int j0 = jb * BROWS + wave * WROWS;
   const bool active = j0 < S;
   const int64_t tok0 = (int64_t)b * S;
   const uint16_t* Qg = qkv + tok0 * ld + h * DH;
   const uint16_t* Og = dout + tok0 * ldo + h * DH;
-  const float* lse_g = lse2 + ((int64_t)b * H + h) * S;
-  const float* D_g = Dv + ((int64_t)b * H + h) * S;
+  const uint16_t* Pg = a.out + tok0 * ldo + h * DH;
+  const float* lse_g = a.lse2 + ((int64_t)b * H + h) * S;
+  const float* D_g = a.D + ((int64_t)b * H + h) * S;
 
   bf16x8 kf[DH / 16], vf[DH / 16];
   if (active) {
@@ -320,19 +342,30 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_kv_kernel(const uint16_t* _
   // parked in LDS after the barrier that ends the compute phase.
   const int nit = S / TILE;
   const int it0 = jb * (BROWS / TILE);
-  u32x4 rq[L<DH>::CHUNKS], ro[L<DH>::CHUNKS];
+  u32x4 rq[L<DH>::CHUNKS], ro[L<DH>::CHUNKS], rp[L<DH>::CHUNKS];
   float rstat = 0.f;
   auto fetch = [&](int it) {
     const int i0 = it * TILE;
     g2r<DH>(rq, Qg + (int64_t)i0 * ld, ld);
     g2r<DH>(ro, Og + (int64_t)i0 * ldo, ldo);
+    if (OWN_D) g2r<DH>(rp, Pg + (int64_t)i0 * ldo, ldo);
     if (threadIdx.x < TILE) rstat = lse_g[i0 + threadIdx.x];
-    else if (threadIdx.x < 2 * TILE) rstat = D_g[i0 + threadIdx.x - TILE];
+    else if (!OWN_D && threadIdx.x < 2 * TILE) rstat = D_g[i0 + threadIdx.x - TILE];
   };
   auto park = [&]() {
     r2s<DH, L<DH>::PKC>(rq, Qkc); r2s<DH, L<DH>::PKM>(rq, Qkm);
     r2s<DH, L<DH>::PKC>(ro, Okc); r2s<DH, L<DH>::PKM>(ro, Okm);
-    if (threadIdx.x < 2 * TILE) stat[threadIdx.x] = rstat;
+    if (threadIdx.x < (OWN_D ? TILE : 2 * TILE)) stat[threadIdx.x] = rstat;
+    if (OWN_D) {   // a row's DH / 8 chunks lie in neighbouring lanes
+#pragma unroll
+      for (int i = 0; i < L<DH>::CHUNKS; ++i) {
+        float t = dot8(rp[i], ro[i], 0.f);
+#pragma unroll
+        for (int x = 1; x < DH / 8; x *= 2) t += __shfl_xor(t, x, 64);
+        const int idx = threadIdx.x + kThreads * i;
+        if (idx % (DH / 8) == 0) stat[TILE + idx / (DH / 8)] = t;
+      }
+    }
   };
   if (it0 < nit) { fetch(it0); park(); }
   __syncthreads();
@@ -389,33 +422,32 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_kv_kernel(const uint16_t* _
   if (!active) return;
   store_owned<DH>(dk, scale, dqkv + (tok0 + j0) * ld + d + h * DH, ld);
   store_owned<DH>(dv, 1.0f, dqkv + (tok0 + j0) * ld + 2 * d + h * DH, ld);
-  if (colpart) {   // partial row (sequence, 32-key block) of the k and v thirds of the qkv bias gradient
-    float* prow = colpart + ((tok0 + j0) / WROWS) * ld;
+  if (a.colpart) {   // partial row (sequence, 32-key block) of the k and v thirds of the qkv bias gradient
+    float* prow = a.colpart + ((tok0 + j0) / WROWS) * ld;
     colsum_owned<DH>(dk, scale, prow + d + h * DH);
     colsum_owned<DH>(dv, 1.0f, prow + 2 * d + h * DH);
   }
 }
 
 // ----------------------------------------------------------------------------------------
-// backward, part 1: dQ, and D = rowsum(dO * O).  A wave owns 32 queries (lane = query); keys stream.
+// backward, part 1: dQ, and D = rowsum(dO * O), stored where part 2 follows in a launch of its own.
+// A wave owns 32 queries (lane = query); keys stream.
 // ----------------------------------------------------------------------------------------
-template <int DH>
-__global__ __launch_bounds__(kThreads) void attn_bwd_q_kernel(const uint16_t* __restrict__ qkv, int64_t ld,
-                                                              const uint16_t* __restrict__ dout, int64_t ldo,
-                                                              const uint16_t* __restrict__ outp,
-                                                              const float* __restrict__ lse2,
-                                                              float* __restrict__ Dv,
-                                                              uint16_t* __restrict__ dqkv, int S, int d, int H,
-                                                              int nseq, float c2, float scale,
-                                                              float* __restrict__ colpart) {
-  extern __shared__ __align__(16) char smem[];
+template <int DH, bool STORE_D>
+__device__ __forceinline__ void bwd_q_body(const BwdArgs& a, int block, char* smem) {
+  const uint16_t* __restrict__ qkv = a.qkv;
+  const uint16_t* __restrict__ dout = a.dout;
+  uint16_t* __restrict__ dqkv = a.dqkv;
+  const int64_t ld = a.ld, ldo = a.ldo;
+  const int S = a.S, d = a.d, H = a.H;
+  const float c2 = a.c2, scale = a.scale;
   char* Kkc = smem;                         // K tile, k-contiguous (S^T = K Q^T)
   char* Kkm = Kkc + L<DH>::KC_BYTES;        // K tile, transpose-read (dQ^T = K^T dS^T)
   char* Vkc = Kkm + L<DH>::KM_BYTES;        // V tile, k-contiguous (dP^T = V dO^T)
 
   const int nblk = (S + BROWS - 1) / BROWS;
   int rank, h, b;
-  attn_block(H, nseq, rank, h, b);
+  attn_block(block, H, a.nseq, rank, h, b);
   const int qb = nblk - 1 - rank;
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, grp = l >> 5;
   const int q0 = qb * BROWS + wave * WROWS;
@@ -430,22 +462,15 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_q_kernel(const uint16_t* __
   if (active) {
     load_owned<DH>(qf, qkv + (tok0 + q0) * ld + h * DH, ld);
     load_owned<DH>(of, dout + (tok0 + q0) * ldo + h * DH, ldo);
-    lse_i = lse2[((int64_t)b * H + h) * S + qi];
+    lse_i = a.lse2[((int64_t)b * H + h) * S + qi];
     // D_i = sum_dh dO[i,dh] * O[i,dh]: the wave holds its rows of dO as fragments already; the
-    // rows of O come in the same layout.  Stored for the dK/dV kernel, which runs after this one.
+    // rows of O come in the same layout.
     bf16x8 oo[DH / 16];
-    load_owned<DH>(oo, outp + (tok0 + q0) * ldo + h * DH, ldo);
+    load_owned<DH>(oo, a.out + (tok0 + q0) * ldo + h * DH, ldo);
 #pragma unroll
-    for (int kk = 0; kk < DH / 16; ++kk) {
-      const u32x4 a = __builtin_bit_cast(u32x4, oo[kk]), g = __builtin_bit_cast(u32x4, of[kk]);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        D_i = __fmaf_rn(__uint_as_float(a[e] << 16), __uint_as_float(g[e] << 16), D_i);
-        D_i = __fmaf_rn(__uint_as_float(a[e] & 0xFFFF0000u), __uint_as_float(g[e] & 0xFFFF0000u), D_i);
-      }
-    }
+    for (int kk = 0; kk < DH / 16; ++kk) D_i = dot8(__builtin_bit_cast(u32x4, oo[kk]), __builtin_bit_cast(u32x4, of[kk]), D_i);
     D_i += __shfl_xor(D_i, 32, 64);
-    if (grp == 0) Dv[((int64_t)b * H + h) * S + qi] = D_i;
+    if (STORE_D && grp == 0) a.D[((int64_t)b * H + h) * S + qi] = D_i;
   }
   f32x16 dq[DH / 32];
 #pragma unroll
@@ -506,7 +531,26 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_q_kernel(const uint16_t* __
   }
   if (!active) return;
   store_owned<DH>(dq, scale, dqkv + (tok0 + q0) * ld + h * DH, ld);
-  if (colpart) colsum_owned<DH>(dq, scale, colpart + ((tok0 + q0) / WROWS) * ld + h * DH);   // the q third
+  if (a.colpart) colsum_owned<DH>(dq, scale, a.colpart + ((tok0 + q0) / WROWS) * ld + h * DH);   // the q third
+}
+
+template <int DH>
+__global__ __launch_bounds__(kThreads) void attn_bwd_kv_kernel(BwdArgs a) {
+  extern __shared__ __align__(16) char smem[];
+  bwd_kv_body<DH, false>(a, blockIdx.x, smem);
+}
+template <int DH>
+__global__ __launch_bounds__(kThreads) void attn_bwd_q_kernel(BwdArgs a) {
+  extern __shared__ __align__(16) char smem[];
+  bwd_q_body<DH, true>(a, blockIdx.x, smem);
+}
+// both parts: the row blocks of part 2 and part 1 in turn, heaviest first
+template <int DH>
+__global__ __launch_bounds__(kThreads) void attn_bwd_kernel(BwdArgs a) {
+  extern __shared__ __align__(16) char smem[];
+  const int per = a.H * a.nseq, slab = blockIdx.x / per, block = (slab >> 1) * per + blockIdx.x % per;
+  if (slab & 1) bwd_q_body<DH, false>(a, block, smem);
+  else bwd_kv_body<DH, true>(a, block, smem);
 }
 
 template <typename K>
@@ -546,32 +590,42 @@ rv_status rv_attn_fwd(const uint16_t* qkv, uint16_t* out, float* lse2, int mb, i
 
 int rv_attn_colsum_parts(int mb, int S) { return mb * (S / WROWS); }
 
+namespace {
+// Both parts in one launch, or one after the other?  Together they fill each other's gaps and the walk of
+// the longest key block runs beside that of the longest query block; in return part 2 reads O again and
+// part 1 takes part 2's registers (two waves per SIMD at head size 64, one at 128).  Alone, two launches /
+// one, us, at nwg row blocks per part:
+//   head size 64    nwg 14 14.4 / 8.9    108 25.6 / 17.3    256 31.8 / 24.0 (S 512), 93.3 / 71.3 (S 2048)
+//                   512 38.8 / 35.4      1024 99.9 / 99.2   1600 146.9 / 152.3
+//   head size 128   nwg 4 23.2 / 15.5    128 89.4 / 70.4 (S 1024)    256 92.2 / 71.5    512 116.0 / 134.9
+// Stage steps: 12 blocks of d 448 on 256 tokens 1.27 -> 1.21 ms, 6 of d 768 on 1152 tokens with four
+// microbatches 5.84 -> 5.56 ms, four of d 1024 on 4096 tokens (nwg 512) 1.91 -> 1.88 ms.
+bool one_launch(int dh, int nwg) { return nwg <= (dh == 64 ? 512 : 256); }
+template <int DH>
+rv_status launch_bwd(const BwdArgs& a, hipStream_t st) {
+  constexpr int s1 = 2 * (L<DH>::KC_BYTES + L<DH>::KM_BYTES) + 2 * TILE * 4;
+  constexpr int s2 = 2 * L<DH>::KC_BYTES + L<DH>::KM_BYTES;
+  const int nwg = (a.S + BROWS - 1) / BROWS * a.H * a.nseq;
+  if (one_launch(DH, nwg)) {
+    RV_TRY(set_smem(attn_bwd_kernel<DH>, s1));
+    hipLaunchKernelGGL(attn_bwd_kernel<DH>, dim3(2 * nwg), dim3(kThreads), s1, st, a);
+    return rv_launch_status();
+  }
+  RV_TRY(set_smem(attn_bwd_kv_kernel<DH>, s1)); RV_TRY(set_smem(attn_bwd_q_kernel<DH>, s2));
+  hipLaunchKernelGGL(attn_bwd_q_kernel<DH>, dim3(nwg), dim3(kThreads), s2, st, a);
+  hipLaunchKernelGGL(attn_bwd_kv_kernel<DH>, dim3(nwg), dim3(kThreads), s1, st, a);
+  return rv_launch_status();
+}
+}  // namespace
+
 rv_status rv_attn_bwd(const uint16_t* qkv, const uint16_t* out, const uint16_t* dout, const float* lse2,
                       float* Dbuf, uint16_t* dqkv, int mb, int S, int d, int H, hipStream_t st, float* colpart) {
   if (!qkv || !out || !dout || !lse2 || !Dbuf || !dqkv || !shape_ok(mb, S, d, H)) return RV_E_INVAL;
   const int dh = d / H;
   const float scale = 1.0f / sqrtf((float)dh);
-  const float c2 = 1.4426950408889634f * scale;
-  const int nwg = ((S + BROWS - 1) / BROWS) * H * mb;
-  dim3 grid(nwg);
-  if (dh == 64) {
-    constexpr int s1 = 2 * (L<64>::KC_BYTES + L<64>::KM_BYTES) + 2 * TILE * 4;
-    constexpr int s2 = 2 * L<64>::KC_BYTES + L<64>::KM_BYTES;
-    RV_TRY(set_smem(attn_bwd_kv_kernel<64>, s1)); RV_TRY(set_smem(attn_bwd_q_kernel<64>, s2));
-    hipLaunchKernelGGL(attn_bwd_q_kernel<64>, grid, dim3(kThreads), s2, st, qkv, (int64_t)3 * d, dout, (int64_t)d,
-                       out, lse2, Dbuf, dqkv, S, d, H, mb, c2, scale, colpart);
-    hipLaunchKernelGGL(attn_bwd_kv_kernel<64>, grid, dim3(kThreads), s1, st, qkv, (int64_t)3 * d, dout, (int64_t)d,
-                       lse2, Dbuf, dqkv, S, d, H, mb, c2, scale, colpart);
-  } else {
-    constexpr int s1 = 2 * (L<128>::KC_BYTES + L<128>::KM_BYTES) + 2 * TILE * 4;
-    constexpr int s2 = 2 * L<128>::KC_BYTES + L<128>::KM_BYTES;
-    RV_TRY(set_smem(attn_bwd_kv_kernel<128>, s1)); RV_TRY(set_smem(attn_bwd_q_kernel<128>, s2));
-    hipLaunchKernelGGL(attn_bwd_q_kernel<128>, grid, dim3(kThreads), s2, st, qkv, (int64_t)3 * d, dout, (int64_t)d,
-                       out, lse2, Dbuf, dqkv, S, d, H, mb, c2, scale, colpart);
-    hipLaunchKernelGGL(attn_bwd_kv_kernel<128>, grid, dim3(kThreads), s1, st, qkv, (int64_t)3 * d, dout, (int64_t)d,
-                       lse2, Dbuf, dqkv, S, d, H, mb, c2, scale, colpart);
-  }
-  return rv_launch_status();
+  const BwdArgs a = {qkv, (int64_t)3 * d, dout, out, (int64_t)d, lse2, Dbuf, dqkv, S, d, H, mb,
+                     1.4426950408889634f * scale, scale, colpart};
+  return dh == 64 ? launch_bwd<64>(a, st) : launch_bwd<128>(a, st);
 }
 
 extern "C" rv_status rv_k_attention_fwd(const void* qkv, void* out, float* lse2, int microbatch, int seq,
@@ -588,7 +642,7 @@ extern "C" rv_status rv_k_attention_bwd(const void* qkv, const void* out, const 
 }
 
 // ---- the backward for callers that cannot allocate ---------------------------------------
-// The per-row term D = rowsum(dO * O) that the two backward kernels exchange lives in a
+// The per-row term D = rowsum(dO * O) that the backward's two launches exchange lives in a
 // file-scope device array instead of a caller workspace.  Every GPU holds its own copy of
 // the array; its address on a device is looked up once, with that device current.
 namespace {

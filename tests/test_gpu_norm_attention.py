@@ -81,6 +81,14 @@ def test_attention_forward_backward(mb, S, H, dh):
     close(dqkv[:, 2 * d:], _unheads(dv), 8e-3, "k", group="LayerNorm / column sum / attention kernels, bar 8e-3")
 
 
+# row blocks at and beyond the number up to which both parts of the backward share a launch, sequences whose
+# last row block is half empty
+@pytest.mark.parametrize("mb,S,H,dh", [(32, 64, 16, 64), (33, 64, 16, 64), (9, 192, 30, 64), (16, 64, 16, 128),
+                                        (17, 64, 16, 128), (5, 192, 26, 128)])
+def test_attention_many_row_blocks(mb, S, H, dh):
+    test_attention_forward_backward(mb, S, H, dh)
+
+
 def test_attention_rejects_unsupported_shapes():
     from paper_2401_01728_amd import kernels as k
     import paper_2401_01728_amd as rv
