@@ -163,7 +163,7 @@ rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
   float* dres = (float*)(s->work + p.w_dres);
   uint16_t* dtmp = (uint16_t*)(s->work + p.w_dtmp);
   float* Dbuf = (float*)(s->work + p.w_D);
-  const int ln_parts = rv_ln_bwd_parts(T, d);
+  const int ln_rows = rv_ln_bwd_rows(T, d), ln_parts = rv_ln_bwd_parts(T, d);
   // fused update (plain Eq. 2): every kernel that completes a parameter gradient applies it at once
   // to the fp32 master and writes the bf16 rounding into the new weight version `vdst`
   uint16_t* vdst = s->fused ? (uint16_t*)s->ver[s->upd_dst] : nullptr;
@@ -295,7 +295,7 @@ rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
     if (early) RV_TRY(send_sums());
     RV_TRY(gemm(sh, st, dz, f, 0, w + p.w1, f, 0, T, d, f, RV_EPI_BF16, dtmp, d));                       // dv2 = dz W1^T
     RV_TRY(rv_ln_bwd(dtmp, x1, (const float*)(sb + p.s_m2), (const float*)(sb + p.s_r2), w + p.ln2g, dres, dres,
-                     dx1_16, part2, T, d, st));
+                     dx1_16, part2, T, d, st, ln_rows));
     colsum(part2, ln_parts, 3 * (int64_t)d, d, gl + p.ln2g);
     colsum(part2 + d, ln_parts, 3 * (int64_t)d, d, gl + p.ln2b);
     colsum(part2 + 2 * d, ln_parts, 3 * (int64_t)d, d, gl + p.bo);                                     // dbo = sum dx1
@@ -317,7 +317,7 @@ rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
     RV_TRY(gemm(sh, st, dqkv, 3 * d, 0, w + p.wqkv, 3 * d, 0, T, d, 3 * d, RV_EPI_BF16, dtmp, d));       // du
     uint16_t* dx16 = l == 0 ? (uint16_t*)grad_in : dy_below;
     RV_TRY(rv_ln_bwd(dtmp, x, (const float*)(sb + p.s_m1), (const float*)(sb + p.s_r1), w + p.ln1g, dres, dres, dx16,
-                     part1, T, d, st));
+                     part1, T, d, st, ln_rows));
     colsum(part1, ln_parts, 3 * (int64_t)d, d, gl + p.ln1g);
     colsum(part1 + d, ln_parts, 3 * (int64_t)d, d, gl + p.ln1b);
     // the residual gradient leaving this block is dy of the block below: its b2 gradient

@@ -190,7 +190,6 @@ __global__ __launch_bounds__(kThreads, 5) void ln_fwd_pipe_kernel(const float* _
 // column sums over the workgroup's rows into part[blk][0..2][d]:
 //   0: sum dy * xh (d gamma)   1: sum dy (d beta)   2: sum dx (bias gradient of the Linear
 //   whose output fed this residual stream).
-constexpr int kRowsPerBlock = 16;
 constexpr int kBwdWaves = 4;
 
 // Four waves per workgroup, all on the same rows: wave cs owns columns [cs * NV * 256, +NV * 256)
@@ -203,7 +202,7 @@ constexpr int kBwdWaves = 4;
 // RF = 1 up to 2048; NV = 4 beyond (no such stage is benchmarked); d <= 1024 takes
 // ln_bwd_pipe_kernel below, which keeps twice the rows in flight.  Row statistics are combined
 // through LDS in a fixed order, one barrier per RF rows, two alternating slots.  The column sums
-// stay in registers for the workgroup's 16 rows and leave as one partial row per workgroup.
+// stay in registers for the workgroup's rows and leave as one partial row per workgroup.
 template <int NV, int RF>
 __global__ __launch_bounds__(64 * kBwdWaves, NV <= 2 ? 6 : 1) void ln_bwd_kernel(const uint16_t* __restrict__ dy,
                                                                 const float* __restrict__ x,
@@ -212,7 +211,7 @@ __global__ __launch_bounds__(64 * kBwdWaves, NV <= 2 ? 6 : 1) void ln_bwd_kernel
                                                                 const uint16_t* __restrict__ gamma,
                                                                 const float* dres, float* dx,
                                                                 uint16_t* __restrict__ dx_bf16,
-                                                                float* __restrict__ part, int T, int d) {
+                                                                float* __restrict__ part, int T, int d, int rows) {
   constexpr int CS = kBwdWaves;
   __shared__ float stat[2][RF][CS][2];
   const int cs = threadIdx.x >> 6, l = threadIdx.x & 63;
@@ -226,8 +225,8 @@ __global__ __launch_bounds__(64 * kBwdWaves, NV <= 2 ? 6 : 1) void ln_bwd_kernel
     if (c >= d) gam[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 #pragma unroll 1
-  for (int k = 0; k < kRowsPerBlock / RF; ++k) {
-    const int row0 = blockIdx.x * kRowsPerBlock + k * RF;
+  for (int k = 0; k < rows / RF; ++k) {
+    const int row0 = blockIdx.x * rows + k * RF;
     // every operand of the RF rows is requested here: one memory round trip per RF rows
     f32x4 xh[RF][NV], rs[RF][NV];
     u32x2 dyr[RF][NV];
@@ -548,28 +547,39 @@ rv_status rv_ln_fwd(const void* x, int x_is_bf16, float* xcopy, const uint16_t* 
   return rv_launch_status();
 }
 
-// Rows per workgroup: 8 for d <= 1024 (twice the workgroups: the stage step of the 1024-wide stage
-// measured 0.4 % shorter than with 16, and 0.9 % shorter than with 4), 16 beyond (8 measured
-// -0.2 % at d = 1600 and +0.2 % at d = 2048).
-constexpr int kPipeRows = 8;
+// Rows per workgroup.  Many tokens: 8 for d <= 1024 (twice the workgroups: the stage step of the
+// 1024-wide stage measured 0.4 % shorter than with 16, and 0.9 % shorter than with 4), 16 beyond (8 measured
+// -0.2 % at d = 1600 and +0.2 % at d = 2048).  Fewer than 256 workgroups of those leave CUs without one
+// while the others walk through their rows one memory round trip after another: then a workgroup
+// takes fewer, down to 2.  (Against 8 / 16 rows for every token count: an averaging iteration over four
+// stages of d 1024 on 128 tokens 3.27 -> 3.19 ms; six blocks of d 768 on 1152 tokens, four microbatches,
+// 5.550 -> 5.535 ms.)
+int rv_ln_bwd_rows(int T, int d) {
+  int rows = d <= 1024 ? 8 : 16;
+  while (rows > 2 && (T + rows - 1) / rows < 256) rows /= 2;
+  return rows;
+}
 int rv_ln_bwd_parts(int T, int d) {
-  const int rows = d <= 1024 ? kPipeRows : kRowsPerBlock;
+  const int rows = rv_ln_bwd_rows(T, d);
   return (T + rows - 1) / rows;
 }
 
 rv_status rv_ln_bwd(const uint16_t* dy, const float* x, const float* mean, const float* rstd,
                     const uint16_t* gamma, const float* dres, float* dx, uint16_t* dx_bf16, float* part,
-                    int T, int d, hipStream_t st) {
+                    int T, int d, hipStream_t st, int rows) {
   if (!dy || !x || !mean || !rstd || !gamma || !dres || !dx || !part || T < 1 || d < 4 || d % 4 || d > 4096)
     return RV_E_INVAL;
-  dim3 grid(rv_ln_bwd_parts(T, d)), blk(64 * kBwdWaves);
+  dim3 grid((T + rows - 1) / rows), blk(64 * kBwdWaves);
 #define RV_LN_BWD(NV, RF) \
-  hipLaunchKernelGGL((ln_bwd_kernel<NV, RF>), grid, blk, 0, st, dy, x, mean, rstd, gamma, dres, dx, dx_bf16, part, T, d);
+  hipLaunchKernelGGL((ln_bwd_kernel<NV, RF>), grid, blk, 0, st, dy, x, mean, rstd, gamma, dres, dx, dx_bf16, part, T, d, rows);
+#define RV_LN_PIPE(RF, ROWS) \
+  hipLaunchKernelGGL((ln_bwd_pipe_kernel<1, RF, ROWS>), grid, blk, 0, st, dy, x, mean, rstd, gamma, dres, dx, dx_bf16, part, T, d);
   if (d <= 1024) {
-    hipLaunchKernelGGL((ln_bwd_pipe_kernel<1, 2, kPipeRows>), grid, blk, 0, st, dy, x, mean, rstd, gamma, dres, dx, dx_bf16, part, T, d);
+    if (rows == 8) { RV_LN_PIPE(2, 8) } else if (rows == 4) { RV_LN_PIPE(2, 4) } else { RV_LN_PIPE(1, 2) }
   }
   else if (d <= 2048) { RV_LN_BWD(2, 1) }
   else { RV_LN_BWD(4, 1) }
+#undef RV_LN_PIPE
 #undef RV_LN_BWD
   return rv_launch_status();
 }
@@ -612,9 +622,10 @@ extern "C" rv_status rv_k_layernorm_bwd(const void* dy, const float* x, const fl
                                         float* part, float* dgamma, float* dbeta, float* dbias, int T, int d,
                                         void* stream) {
   hipStream_t st = (hipStream_t)stream;
+  const int rows = std::max(8, rv_ln_bwd_rows(T, d));   // the caller's workspace holds ceil(T / 8) partial rows
   RV_TRY(rv_ln_bwd((const uint16_t*)dy, x, mean, rstd, (const uint16_t*)gamma, dres, dx, (uint16_t*)dx_bf16,
-                   part, T, d, st));
-  const int R = rv_ln_bwd_parts(T, d);
+                   part, T, d, st, rows));
+  const int R = (T + rows - 1) / rows;
   rv_reduce_job job[3];
   float* const out[3] = {dgamma, dbeta, dbias};
   int n = 0;

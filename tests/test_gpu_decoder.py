@@ -96,6 +96,13 @@ def test_small_stage_schedules(L, d, H, f, S, mb, tau):
     run_schedule(L, d, H, f, S, mb, tau, n_mb=2 * tau + 2, seed=20 + L)
 
 
+# LayerNorm backward by 2, 4 and 8 rows per workgroup for widths up to 1024 and beyond (16: the full-size stages)
+@pytest.mark.parametrize("d,H,S,mb", [(128, 2, 512, 1), (128, 2, 512, 2), (128, 2, 512, 4),
+                                      (1088, 17, 64, 1), (1088, 17, 512, 2), (1088, 17, 512, 4), (2304, 18, 64, 1)])
+def test_stage_of_few_or_many_tokens(d, H, S, mb):
+    run_schedule(1, d, H, 64, S, mb, 0, n_mb=1, seed=60 + mb)
+
+
 @pytest.mark.parametrize("L,d,H,f,S,mb,tau", [(2, 128, 2, 256, 128, 2, 2), (2, 256, 2, 512, 128, 1, 0),
                                                (3, 192, 3, 320, 64, 3, 1)])
 def test_fused_step_equals_forward_then_backward(L, d, H, f, S, mb, tau):
