@@ -102,6 +102,8 @@ struct rv_slot {
   char* base = nullptr;  // activation stash of this microbatch
 };
 
+#define RV_VER_PAD 16   // zero bytes behind the parameters of every weight version
+
 struct rv_stage {
   int kind = 0, dtype = 0, n_layers = 0, microbatch = 0, tau = 0;
   float eta = 0.f, ln_eps = 1e-5f;

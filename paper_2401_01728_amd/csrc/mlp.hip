@@ -452,7 +452,7 @@ rv_status launch_bwd(hipStream_t st, const Prod& dx, const Out& ox, const Prod& 
 // ---- tiny ----------------------------------------------------------------------------------
 struct Tiny {
   int n, mb, dim[kTinyLayers + 1];
-  unsigned offW[kTinyLayers], offB[kTinyLayers], offA[kTinyLayers];
+  unsigned offW[kTinyLayers], offB[kTinyLayers], offA[kTinyLayers], zero;   // zero: the number of parameters
 };
 constexpr int kTinyDepth = 128;   // contraction a wave requests at a time
 constexpr int kTinyThreads = 512, kTinyWaves = kTinyThreads / 64;
@@ -462,7 +462,11 @@ __host__ __device__ constexpr int tiny_pitch(int w) { return (w + 15) / 16 * 16 
 // written by other launches, which leaves every XCD's L2 without them) and the number of lines a
 // load instruction touches.  So a wave requests everything its first tiles of a layer read one
 // layer ahead, the rows of a transposed weight tile come in 16-byte pieces, and no load waits behind
-// a branch: indexes past an end are clamped, their values unused.
+// a branch: an index past an end is clamped where its result is not stored, and points at a zero behind the
+// parameters where it enters a sum (the zero on the other side would not do: zero times an infinity is no zero).
+// These kernels run through their code once, so its length is time too: device time of 64-128-64 on 8 rows, forward /
+// backward, 5.4 / 8.1 us like this; with that index chosen in every group 6.2 / 8.5, clamped values zeroed in registers
+// 6.0 / 8.1, the range check of a buffer descriptor 5.7 / 8.6 (clamped and left as they are: 5.5 / 8.0).
 template <int N>
 __device__ __forceinline__ void pin(float (&v)[N]) {   // the values have arrived here
 #pragma unroll
@@ -470,48 +474,63 @@ __device__ __forceinline__ void pin(float (&v)[N]) {   // the values have arrive
 }
 
 // One 16-column tile of a product over the activations in LDS: acc[t] = rows 16 t .. of
-// act[., 0..K) x B, kTinyDepth deep at a time.  A lane takes k = 16 u + 4 (lane / 16) + e; columns K .. of
-// act are zero.   BT = false: B(k, c) = W[k * ldw + c];   true: B(k, c) = W[c * ldw + k]
+// act[., 0..K) x B.  A lane takes k = 16 u + 4 (lane / 16) + e of group u; kTinyDepth of whole groups are requested
+// at a time, what is left of K past them (`rest`) with the first: there act is zero from column K on, and so is
+// W[zero].   BT = false: B(k, c) = W[k * ldw + c];   true: B(k, c) = W[c * ldw + k]
+struct TinyB { float b[kTinyDepth / 4], rest[4]; };
 template <bool BT>
-__device__ __forceinline__ void tiny_request(float (&b)[kTinyDepth / 4], const float* __restrict__ W, unsigned ldw, int K, int k0, int c) {
-  const int q = (threadIdx.x & 63) >> 4;
+__device__ __forceinline__ void tiny_request(TinyB& r, const float* __restrict__ W, unsigned ldw, int K, int k0, int c) {
+  const unsigned q = (threadIdx.x & 63) >> 4, lane = (BT ? c * ldw + 4u * q : 4u * q * ldw + c) * 4u;   // bytes
+  const float* g = W + (BT ? (unsigned)k0 : (unsigned)k0 * ldw);   // uniform
 #pragma unroll
   for (int u = 0; u < kTinyDepth / 16; ++u) {
-    const int k = k0 + 16 * u + 4 * q;
-    if (BT && k0 + 16 * u + 16 <= K) {                     // (uniform)
-      const f32x4 v = *reinterpret_cast<const f32x4_u*>(W + c * ldw + (unsigned)k);
+    if (k0 + 16 * u + 16 <= K) {
+      if (BT) {
+        const f32x4 v = *reinterpret_cast<const f32x4_u*>(reinterpret_cast<const char*>(g) + lane);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) b[4 * u + e] = v[e];
-    } else if (k0 + 16 * u < K) {
+        for (int e = 0; e < 4; ++e) r.b[4 * u + e] = v[e];
+      } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const unsigned kc = k + e < K ? k + e : K - 1;
-        b[4 * u + e] = BT ? W[c * ldw + kc] : W[kc * ldw + c];
+        for (int e = 0; e < 4; ++e) r.b[4 * u + e] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(g + (unsigned)e * ldw) + lane);
       }
     }
+    g += BT ? 16u : 16u * ldw;
+  }
+}
+template <bool BT>
+__device__ __forceinline__ void tiny_request_rest(TinyB& r, const float* __restrict__ W, unsigned zero, unsigned ldw, int K, int c) {
+  const int k = K / 16 * 16 + 4 * ((threadIdx.x & 63) >> 4);
+  if (K % 16 != 0) {                                       // (uniform)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r.rest[e] = W[k + e < K ? (BT ? c * ldw + (unsigned)(k + e) : (unsigned)(k + e) * ldw + c) : zero];
   }
 }
 template <int MT, bool BT>
-__device__ __forceinline__ void tiny_tile(f32x4 (&acc)[MT], float (&b)[kTinyDepth / 4], const float* act, int pitch,
-                                          const float* __restrict__ W, unsigned ldw, int K, int c) {
+__device__ __forceinline__ void tiny_tile(f32x4 (&acc)[MT], TinyB& r, const float* act, int pitch, const float* __restrict__ W,
+                                          unsigned ldw, int K, int c) {
   const int l = threadIdx.x & 63, q = l >> 4;
 #pragma unroll
   for (int t = 0; t < MT; ++t) acc[t] = 0.f;
+  auto group = [&](const float* b, int kg) {
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const f32x4 a = *reinterpret_cast<const f32x4*>(act + (t * 16 + (l & 15)) * pitch + kg + 4 * q);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], acc[t], 0, 0, 0);
+    }
+  };
   for (int k0 = 0;;) {
-    pin(b);
+    pin(r.b);
 #pragma unroll
     for (int u = 0; u < kTinyDepth / 16; ++u)
-      if (k0 + 16 * u < K) {
-#pragma unroll
-        for (int t = 0; t < MT; ++t) {
-          const f32x4 a = *reinterpret_cast<const f32x4*>(act + (t * 16 + (l & 15)) * pitch + k0 + 16 * u + 4 * q);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[4 * u + e], acc[t], 0, 0, 0);
-        }
-      }
+      if (k0 + 16 * u + 16 <= K) group(r.b + 4 * u, k0 + 16 * u);
     k0 += kTinyDepth;
-    if (k0 >= K) break;
-    tiny_request<BT>(b, W, ldw, K, k0, c);
+    if (k0 + 16 > K) break;
+    tiny_request<BT>(r, W, ldw, K, k0, c);
+  }
+  if (K % 16 != 0) {
+    pin(r.rest);
+    group(r.rest, K / 16 * 16);
   }
 }
 
@@ -526,7 +545,7 @@ __device__ __forceinline__ void tiny_rows(float* s, const float* __restrict__ g,
     }
 }
 
-struct TinyFwdReq { float b[kTinyDepth / 4], bias[1]; };
+struct TinyFwdReq { TinyB b; float bias[1]; };
 template <int NL, int MT>
 __global__ __launch_bounds__(kTinyThreads) void tiny_fwd_kernel(Tiny p, const float* __restrict__ w, const float* __restrict__ in,
                                                                 float* __restrict__ stash, float* __restrict__ out, int half) {
@@ -537,6 +556,7 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_fwd_kernel(Tiny p, const fl
   auto request = [&](TinyFwdReq& r, int i, int t) {
     const int N = p.dim[i + 1], c = t * 16 + (l & 15), cc = c < N ? c : N - 1;
     tiny_request<false>(r.b, w + p.offW[i], N, p.dim[i], 0, cc);
+    tiny_request_rest<false>(r.b, w + p.offW[i], p.zero - p.offW[i], N, p.dim[i], cc);
     r.bias[0] = w[p.offB[i] + cc];
   };
   TinyFwdReq cur, nxt;
@@ -579,7 +599,7 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_fwd_kernel(Tiny p, const fl
   }
 }
 
-template <int MT> struct TinyBwdReq { float b[kTinyDepth / 4], gate[4 * MT], a[4 * MT], w[4], v[4]; };
+template <int MT> struct TinyBwdReq { TinyB b; float gate[4 * MT], a[4 * MT], w[4], v[4]; };
 template <int NL, int MT>
 __global__ __launch_bounds__(kTinyThreads) void tiny_bwd_kernel(Tiny p, const float* __restrict__ w, const float* __restrict__ stash,
                                                                 const float* __restrict__ dout, float* __restrict__ din, Upd u,
@@ -591,6 +611,7 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_bwd_kernel(Tiny p, const fl
   auto request_chain = [&](TinyBwdReq<MT>& r, int i, int t) {
     const int K = p.dim[i], N = p.dim[i + 1], c = t * 16 + (l & 15), cc = c < K ? c : K - 1;
     tiny_request<true>(r.b, w + p.offW[i], N, N, 0, cc);
+    tiny_request_rest<true>(r.b, w + p.offW[i], p.zero - p.offW[i], N, N, cc);
 #pragma unroll
     for (int k = 0; k < 4 * MT; ++k) {
       const int m = k / 4 * 16 + 4 * q + k % 4;
@@ -667,8 +688,10 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_bwd_kernel(Tiny p, const fl
       f32x4 acc = 0.f;
       pin(cur.a); pin(cur.w); pin(cur.v);
 #pragma unroll
-      for (int k = 0; k < 4 * MT; ++k)                     // four rows of the microbatch at a time; past its end d is zero
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kr < K ? cur.a[k] : 1.f, d[(4 * k + q) * dp + c], acc, 0, 0, 0);
+      for (int k = 0; k < 4 * MT; ++k) {                   // four rows of the microbatch at a time; past its end both are zero
+        const float a = 4 * k + q < p.mb ? kr < K ? cur.a[k] : 1.f : 0.f;
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, d[(4 * k + q) * dp + c], acc, 0, 0, 0);
+      }
 #pragma unroll
       for (int r = 0; r < 4; ++r)
         if (c < N && t / tn * 16 + 4 * q + r <= K) {
@@ -701,7 +724,7 @@ int tiny_half(const rv_stage* s) {   // floats of one LDS activation buffer
 Tiny tiny_desc(const rv_stage* s) {
   const MlpPlan* p = (const MlpPlan*)s->impl;
   Tiny t = {};
-  t.n = p->n; t.mb = s->microbatch;
+  t.n = p->n; t.mb = s->microbatch; t.zero = (unsigned)s->P;
   for (int i = 0; i <= p->n; ++i) t.dim[i] = (int)s->dims[i];
   for (int i = 0; i < p->n; ++i) { t.offW[i] = (unsigned)p->offW[i]; t.offB[i] = (unsigned)p->offB[i]; t.offA[i] = (unsigned)p->offA[i]; }
   return t;

@@ -73,7 +73,7 @@ extern "C" rv_status rv_stage_create(const rv_stage_desc* d, rv_stage** out) {
   s->slots.assign(ns, rv_slot());
   bool ok = hipMalloc((void**)&s->master, s->P * 4) == hipSuccess &&
             hipMalloc((void**)&s->grad, s->P * 4) == hipSuccess;
-  for (int i = 0; ok && i < nv; ++i) ok = hipMalloc((void**)&s->ver[i], s->P * s->ver_elem) == hipSuccess;
+  for (int i = 0; ok && i < nv; ++i) ok = hipMalloc((void**)&s->ver[i], s->P * s->ver_elem + RV_VER_PAD) == hipSuccess;
   if (ok && s->slot_bytes) ok = hipMalloc((void**)&s->stash, s->slot_bytes * ns) == hipSuccess;
   if (ok && s->work_bytes) ok = hipMalloc((void**)&s->work, s->work_bytes) == hipSuccess;
   if (!ok) { (void)hipGetLastError(); free_all(s); return RV_E_NOMEM; }
@@ -83,6 +83,8 @@ extern "C" rv_status rv_stage_create(const rv_stage_desc* d, rv_stage** out) {
       hipMemsetAsync(s->ver[0], 0, s->P * s->ver_elem, s->st) != hipSuccess) {
     free_all(s); return RV_E_DEVICE;
   }
+  for (char* v : s->ver)
+    if (hipMemsetAsync(v + s->P * s->ver_elem, 0, RV_VER_PAD, s->st) != hipSuccess) { free_all(s); return RV_E_DEVICE; }
   if (hipStreamCreateWithFlags(&s->aux, hipStreamNonBlocking) != hipSuccess ||
       hipEventCreateWithFlags(&s->ev_fork, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&s->ev_join, hipEventDisableTiming) != hipSuccess ||

@@ -235,3 +235,46 @@ def test_output_may_share_the_input_buffer():
         if len(dims) > 2:
             close(host64(dy), dxo, 1e-5, "t", group="MLP stage, bar 1e-5")
         close(host64(g.last_grad()), o.last_grad, 1e-5, "t", group="MLP stage, bar 1e-5")
+
+
+def _same(got, ref, tol, grp):
+    """Infinities and NaN in the same places, the rest within the bar."""
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref))
+    assert np.array_equal(np.isneginf(got), np.isneginf(ref))
+    ok = np.isfinite(ref)
+    close(got[ok], ref[ok], tol, "t", group=grp)
+
+
+# one launch per direction (16, 32 and 64 rows), split contraction, LDS tiles; widths and row counts that are no
+# multiple of a piece, so that the last weight row and the last activation row are what clamped indexes read
+_ODD = [([20, 7], 5), ([20, 24, 7], 13), ([17, 33, 9], 29), ([131, 30, 33], 45), ([300, 21, 9], 13), ([301, 1030], 1030)]
+
+
+@pytest.mark.parametrize("where,dims,mb", [("first weight row",) + c for c in _ODD + [([18, 21, 19, 5], 50)]] +
+                         [("last weight row",) + c for c in _ODD if len(c[0]) == 3] + [("activation",) + c for c in _ODD])
+@pytest.mark.filterwarnings("ignore::RuntimeWarning")
+def test_an_infinity_stays_where_it_belongs(where, dims, mb):
+    """One infinite weight in the last row of the first or last layer, or one infinite activation in the last row
+    of the microbatch, against the oracle.  (Two layers for the last two: the unit in front of the last layer's
+    infinity has its gate open, and no hidden unit sums infinities of both signs - there the oracle's product with
+    the gate and its maximum give NaN.)"""
+    import paper_2401_01728_amd as rv
+    w0 = kaiming_uniform_flat(63, dims)
+    x = gen.normal_f32(63, 1, mb * dims[0]).reshape(mb, dims[0])
+    dy = gen.normal_f32(63, 2, mb * dims[-1], std=0.1).reshape(mb, dims[-1])
+    if where == "activation":
+        x[mb - 1, dims[0] - 1] = np.inf
+    elif where == "first weight row":
+        w0[(dims[0] - 1) * dims[1] + dims[1] // 2] = np.inf
+    else:
+        last = dims[0] * dims[1] + dims[1]
+        w0[last - 1] = 100.0
+        w0[last + (dims[1] - 1) * dims[2] + dims[2] // 2] = np.inf
+    g = rv.Stage.mlp(dims, mb, 0, 0.05); g.set_params(dev(w0))
+    o = ostage.Stage("mlp", 0, 0.05, w0, dims=dims)
+    grp = "MLP stage, bar 1e-5"
+    _same(host64(g.forward(0, dev(x))), o.forward(0, x), 1e-5, grp)
+    dx, dxo = g.backward(0, dev(dy)), o.backward(0, dy)
+    _same(host64(dx), dxo, 1e-5, grp)
+    _same(host64(g.last_grad()), o.last_grad, 1e-5, grp)
+    _same(host64(g.get_params()), o.w, 1e-6, "MLP stage, bar 1e-6")
