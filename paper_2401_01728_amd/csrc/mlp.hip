@@ -841,6 +841,11 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
   float* ping = (float*)s->work;
   float* pong = ping + (size_t)mb * p->maxw;
   const float* d = (const float*)grad_out;   // dL/dz_i, already gated
+  if (p->n == 1 && overlap(grad_out, (size_t)mb * s->dims[1], grad_in, (size_t)mb * s->dims[0])) {
+    // the one launch reads the gradient for all its parts while the input gradient is written over it
+    RV_HIP_TRY(hipMemcpyAsync(ping, grad_out, (size_t)mb * s->dims[1] * 4, hipMemcpyDeviceToDevice, s->st));
+    d = ping;
+  }
   for (int i = p->n - 1; i >= 0; --i) {
     const int K = (int)s->dims[i], N = (int)s->dims[i + 1];
     const float* a = stash + p->offA[i];

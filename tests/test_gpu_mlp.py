@@ -218,23 +218,26 @@ def test_product_forms_at_their_edges(dims, mb, momentum):
     close(host64(g.get_params()), o.w, 1e-6, "t", group="MLP product forms: parameters, bar 1e-6")
 
 
-def test_output_may_share_the_input_buffer():
+@pytest.mark.parametrize("momentum", [0.0, 0.9])
+@pytest.mark.parametrize("dims,mb", [([24, 24], 9), ([24, 40, 24], 9), ([300, 40, 300], 9), ([300, 300], 40), ([64, 64], 2000),
+                                     ([1100, 1100], 1030)])
+def test_output_may_share_the_input_buffer(dims, mb, momentum):
     import paper_2401_01728_amd as rv
-    for dims in ([24, 24], [24, 40, 24], [300, 40, 300]):
-        w0 = kaiming_uniform_flat(62, dims)
-        mb = 9
-        g = rv.Stage.mlp(dims, mb, 0, 0.05); g.set_params(dev(w0))
-        o = ostage.Stage("mlp", 0, 0.05, w0, dims=dims)
-        x = gen.normal_f32(62, 1, mb * dims[0]).reshape(mb, dims[0])
-        b = dev(x)
-        g.forward(0, b, b)
-        close(host64(b), o.forward(0, x), 1e-5, "t", group="MLP stage, bar 1e-5")
-        dy = dev(x)
-        g.backward(0, dy, dy if len(dims) > 2 else None)
-        dxo = o.backward(0, x)
-        if len(dims) > 2:
-            close(host64(dy), dxo, 1e-5, "t", group="MLP stage, bar 1e-5")
-        close(host64(g.last_grad()), o.last_grad, 1e-5, "t", group="MLP stage, bar 1e-5")
+    w0 = kaiming_uniform_flat(62, dims)
+    g = rv.Stage.mlp(dims, mb, 0, 0.05); g.set_params(dev(w0))
+    if momentum:
+        g.set_optimizer(momentum, 1e-3)
+    o = ostage.Stage("mlp", 0, 0.05, w0, dims=dims, momentum=momentum, weight_decay=1e-3 if momentum else 0.0)
+    x = gen.normal_f32(62, 1, mb * dims[0]).reshape(mb, dims[0])
+    b = dev(x)
+    g.forward(0, b, b)
+    close(host64(b), o.forward(0, x), 1e-5, "t", group="MLP stage, bar 1e-5")
+    dy = dev(x)
+    g.backward(0, dy, dy)
+    dxo = o.backward(0, x)
+    close(host64(dy), dxo, 1e-5, "t", group="MLP stage, bar 1e-5")
+    close(host64(g.last_grad()), o.last_grad, 1e-5, "t", group="MLP stage, bar 1e-5")
+    close(host64(g.get_params()) - w0, o.w - w0, 1e-4, "t", group="MLP stage, bar 1e-4")
 
 
 def _same(got, ref, tol, grp):
