@@ -194,10 +194,12 @@ def test_stage_with_gradient_accumulation(A, momentum):
     # LDS tiles of 64 and of 128 with ragged edges (one layer: no gate, so no gate can fall the other
     # way); contractions of less than a tile, of one, of two and a bit
     ([1030, 2052], 2051, 0.0), ([2052, 2060], 2049, 0.9), ([31, 4100], 600, 0.0), ([32, 1037], 1030, 0.9), ([65, 2048], 2048, 0.0),
+    # an input of several turns of the workgroups that copy it, with a piece and a float left over
+    ([4099, 9], 2051, 0.0),
 ])
 def test_product_forms_at_their_edges(dims, mb, momentum):
-    """Two microbatches against the oracle.  Bar: sums of K <= 2060 fp32 products with random signs, in any order,
-    stay within about sqrt(K) * 2^-24 = 2.7e-6 normwise; 1e-5 leaves a factor of four."""
+    """Two microbatches against the oracle.  Bar: sums of K <= 4100 fp32 products with random signs, in any order,
+    stay within about sqrt(K) * 2^-24 = 3.8e-6 normwise; 1e-5 leaves a factor of 2.6."""
     import paper_2401_01728_amd as rv
     eta, wd = 1e-3, 1e-3 if momentum else 0.0
     w0 = kaiming_uniform_flat(61, dims)
