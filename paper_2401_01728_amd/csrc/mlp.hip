@@ -6,14 +6,15 @@
 //
 // Every product runs on the fp32 matrix instructions (v_mfma_f32_32x32x2_f32 and
 // v_mfma_f32_16x16x4_f32: full fp32 products and sums at twice the rate of plain vector FMAs,
-// which may not be packed here), in a fixed order (deterministic).  Three forms:
+// which may not be packed here), in a fixed order (deterministic).  Four forms:
 //   tiny   a whole forward, or a whole backward with its update, in ONE launch: workgroups
 //          repeat the small chain of activations (or of gradients) each for itself in LDS and
 //          share out the results, so that no layer waits for a launch of its own;
 //   split  a 32x32 result tile per workgroup, the contraction dealt out over its four or eight waves,
 //          operands straight from memory to registers;
+//   wave   a 32x32 result tile per wave, for thin results of short contractions;
 //   tiled  LDS tiles of 128x128 or 64x64 results, 32 deep, double buffered.
-// In split and tiled form one launch per layer and direction: the forward product; or the input
+// In all but the tiny form one launch per layer and direction: the forward product; or the input
 // gradient, the weight gradient with the update in its epilogue, and the bias gradient together
 // (they read the same gradient and do not depend on one another).
 #include <new>
@@ -348,6 +349,51 @@ __device__ __forceinline__ void split_body(const Prod& p, const Out& o, int tile
   finish<OP, R>(o, m, n0 + nl, p.M, p.N, v);
 }
 
+// ---- one wave per tile ---------------------------------------------------------------------
+// A short contraction behind a thin result (see pick): a 32x32 tile per wave straight from its accumulators,
+// nothing to add up between waves, no LDS, no barrier.  What bounds it is the results' own memory traffic.
+template <int NT, bool AKM, bool BKM, int OP>
+__device__ __forceinline__ void wave_body(const Prod& p, const Out& o, int group) {
+  const int tile = __builtin_amdgcn_readfirstlane(group * (NT / 64) + (threadIdx.x >> 6));
+  const int m0 = tile / p.tiles_n * 32, n0 = tile % p.tiles_n * 32;
+  if (m0 >= p.M) return;
+  const int l = threadIdx.x & 63, h = l >> 5;
+  const int ra = m0 + (l & 31) < p.M ? m0 + (l & 31) : p.M - 1, rb = n0 + (l & 31) < p.N ? n0 + (l & 31) : p.N - 1;
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  constexpr int U = 4;
+  const int ng = (p.K + 7) / 8, whole = p.K / 8;
+  for (int g0 = 0; g0 < ng; g0 += U) {
+    f32x4 fa[U], fb[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int g = g0 + u;
+      fa[u] = 0.f; fb[u] = 0.f;
+      if (g < ng) {
+        fa[u] = direct_frag<AKM>(p.A, p.lda, ra, 8 * g + 4 * h, p.K, g < whole);
+        fb[u] = direct_frag<BKM>(p.B, p.ldb, rb, 8 * g + 4 * h, p.K, g < whole);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u][e], fb[u][e], acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int rb = 0; rb < 16; rb += 8) {
+    if (m0 + 2 * rb >= p.M) break;                         // (uniform) rows 2 rb .. 2 rb + 15 of the tile
+    int m[8];
+    float v[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      m[r] = m0 + 8 * ((rb + r) >> 2) + 4 * h + (r & 3);
+      v[r] = acc[rb + r];
+    }
+    finish<OP, 8>(o, m, n0 + (l & 31), p.M, p.N, v);
+  }
+}
+
 // column sums of D[M,N] (the bias gradient): 32 columns per workgroup, NT / 32 row lanes whose
 // sums are added in order
 template <int NT>
@@ -377,13 +423,17 @@ __device__ __forceinline__ void bias_body(const float* __restrict__ D, int M, in
   }
 }
 
-// BT: 128 or 64 (tiled), 32 (split over NT / 64 waves)
+// BT: 128 or 64 (tiled), 32 (split over NT / 64 waves), kWave (a 32x32 tile per wave)
+constexpr int kWave = 1;
 template <int BT, int NT, bool AKM, bool BKM> constexpr int mlp_lds_bytes() {
-  return 4 * (BT == 32 ? NT / 64 * 32 * 33 : 2 * (Lds<AKM, BT>::FLOATS + Lds<BKM, BT>::FLOATS));
+  // (kWave: the bias sums beside it)
+  return 4 * (BT == kWave ? NT / 32 * 33 : BT == 32 ? NT / 64 * 32 * 33 : 2 * (Lds<AKM, BT>::FLOATS + Lds<BKM, BT>::FLOATS));
 }
 template <int BT, int NT, bool AKM, bool BKM, int OP>
 __device__ __forceinline__ void mlp_body(const Prod& p, const Out& o, int tile, float* smem) {
-  if constexpr (BT == 32) {
+  if constexpr (BT == kWave) {
+    wave_body<NT, AKM, BKM, OP>(p, o, tile);
+  } else if constexpr (BT == 32) {
     split_body<NT / 64, AKM, BKM, OP>(p, o, tile, smem);
   } else {
     static_assert(NT == 256, "four waves");
@@ -426,9 +476,9 @@ __global__ __launch_bounds__(NT) void mlp_bwd_kernel(Prod dx, Out ox, Prod dw, O
   bias_body<NT>(d, M, N, ow.u, offb, b - dw.tiles, mlp_smem);
 }
 
-Prod product(const float* A, int lda, const float* B, int ldb, int M, int N, int K, int bt) {
-  const int tn = (N + bt - 1) / bt;
-  return Prod{A, B, lda, ldb, M, N, K, tn, (M + bt - 1) / bt * tn};
+Prod product(const float* A, int lda, const float* B, int ldb, int M, int N, int K, int bt, int nt) {
+  const int edge = bt == kWave ? 32 : bt, tn = (N + edge - 1) / edge, tiles = (M + edge - 1) / edge * tn, waves = nt / 64;
+  return Prod{A, B, lda, ldb, M, N, K, tn, bt == kWave ? (tiles + waves - 1) / waves : tiles};   // (tiles: workgroups)
 }
 int tile_count(int M, int N, int bt) { return (M + bt - 1) / bt * ((N + bt - 1) / bt); }
 constexpr int kCUs = 256;
@@ -438,7 +488,19 @@ constexpr int kCUs = 256;
 // tiles with separate bias and update launches (108 of 157 TFLOP/s; 4096^3 alone 128 / 140 / 133
 // TFLOP/s forward / input / weight gradient), 300-1000-1000-77 on 100 rows with momentum
 // 304 -> 74 us, where 64x64 tiles for the 100-row products would take 120.
-int pick(int M, int N) { return tile_count(M, N, 128) >= kCUs ? 128 : tile_count(M, N, 64) >= kCUs / 2 ? 64 : 32; }
+// A result of at most 32 rows or columns fills at best half of such a tile's matrix instructions, so there the tile
+// count says nothing about the chip: it takes 32x32 tiles, one per wave where the contraction is short (the work is the
+// results' memory traffic), split where it is long.  Times in us against the tiles that the count alone would take:
+//   4 -> 1e5 on 8 rows, forward 20 -> 7 (32x32 split 35)        1e5 -> 4 on 8 rows, backward 40 -> 13 (61)
+//   64 -> 10 on 65536 rows, forward 29 -> 13 (42)               16384 -> 100 on 16 rows, backward 13.5 -> 12.6 (16)
+//   8192 -> 8192 on 8 rows, forward / backward 307 / 408 -> 74 / 303
+//   slower: 8 -> 2048 on 8192 rows, backward 83 -> 87; 32 -> 32768 on 128 rows, backward 285 -> 310
+int pick(int M, int N, int K) {
+  const int thin = std::min(M, N);
+  if (thin <= 32 && tile_count(M, N, 64) >= kCUs / 2) return K <= 128 ? kWave : 32;
+  return thin > 64 && tile_count(M, N, 128) >= kCUs ? 128 : tile_count(M, N, 64) >= kCUs / 2 ? 64 : 32;
+}
+int threads(int bt) { return bt == 32 ? 64 * kSplitWaves : 256; }
 
 template <typename K>
 rv_status allow_lds(K kern, int bytes) {
@@ -816,13 +878,14 @@ rv_status rv_mlp_forward(rv_stage* s, rv_slot& slot, const void* in, void* out) 
   for (int i = 0; i < p->n; ++i) {
     const bool last = i == p->n - 1, first = i == 0 && !copy_first;
     const int K = (int)s->dims[i], N = (int)s->dims[i + 1];
-    const int bt = pick(mb, N);
-    const Prod pr = product(first ? (const float*)in : stash + p->offA[i], K, w + p->offW[i], N, mb, N, K, bt);
+    const int bt = pick(mb, N, K);
+    const Prod pr = product(first ? (const float*)in : stash + p->offA[i], K, w + p->offW[i], N, mb, N, K, bt, threads(bt));
     Out o = {};
     o.C = last ? (float*)out : stash + p->offA[i + 1]; o.bias = w + p->offB[i]; o.relu = !last;
     float* copy = first ? stash : nullptr;
     const rv_status rc = bt == 128  ? launch_fwd<128, 256>(s->st, pr, o, copy)
                          : bt == 64 ? launch_fwd<64, 256>(s->st, pr, o, copy)
+                         : bt == kWave ? launch_fwd<kWave, 256>(s->st, pr, o, copy)
                                     : launch_fwd<32, 64 * kSplitWaves>(s->st, pr, o, copy);
     RV_TRY(rc);
   }
@@ -867,18 +930,20 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
     const float* a = stash + p->offA[i];
     const bool want_dx = i > 0 || grad_in;
     float* dst = i == 0 ? (float*)grad_in : (d == ping ? pong : ping);
-    const int bx = pick(mb, K), bw = pick(K, N);
-    Prod px = product(d, N, w + p->offW[i], N, mb, K, N, bx);
-    const Prod pw = product(a, K, d, N, K, N, mb, bw);
+    const int bx = pick(mb, K, N), bw = pick(K, N, mb), nt = std::max(bx, bw) == 32 ? threads(32) : 256;
+    Prod px = product(d, N, w + p->offW[i], N, mb, K, N, bx, nt);
+    const Prod pw = product(a, K, d, N, K, N, mb, bw, nt);
     if (!want_dx) px.tiles = 0;
     Out ox = {}, ow = {};
     ox.C = dst; ox.gate = i > 0 ? a : nullptr;
     ow.u = u; ow.off = p->offW[i];
     auto go = [&](auto launch) { return launch(s->st, px, ox, pw, ow, d, mb, N, p->offB[i]); };
-    rv_status rc;
-    if (bx == 128) rc = bw == 128 ? go(launch_bwd<128, 128, 256>) : bw == 64 ? go(launch_bwd<128, 64, 256>) : go(launch_bwd<128, 32, 256>);
-    else if (bx == 64) rc = bw == 128 ? go(launch_bwd<64, 128, 256>) : bw == 64 ? go(launch_bwd<64, 64, 256>) : go(launch_bwd<64, 32, 256>);
-    else rc = bw == 128 ? go(launch_bwd<32, 128, 256>) : bw == 64 ? go(launch_bwd<32, 64, 256>) : go(launch_bwd<32, 32, 64 * kSplitWaves>);
+    auto by_bw = [&](auto x) {
+      constexpr int BX = decltype(x)::value, NT = BX <= 32 ? 64 * kSplitWaves : 256;
+      return bw == 128 ? go(launch_bwd<BX, 128, 256>) : bw == 64 ? go(launch_bwd<BX, 64, 256>)
+             : bw == 32 ? go(launch_bwd<BX, 32, NT>) : go(launch_bwd<BX, kWave, BX == 32 ? NT : 256>);
+    };
+    const rv_status rc = bx == 128 ? by_bw(Int<128>()) : bx == 64 ? by_bw(Int<64>()) : bx == 32 ? by_bw(Int<32>()) : by_bw(Int<kWave>());
     RV_TRY(rc);
     if (want_dx) d = dst;
   }

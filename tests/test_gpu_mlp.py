@@ -283,3 +283,28 @@ def test_an_infinity_stays_where_it_belongs(where, dims, mb):
     _same(host64(dx), dxo, 1e-5, grp)
     _same(host64(g.last_grad()), o.last_grad, 1e-5, grp)
     _same(host64(g.get_params()), o.w, 1e-6, "MLP stage, bar 1e-6")
+
+
+@pytest.mark.parametrize("dims,mb,momentum", [
+    # results of at most 32 rows or columns and thousands the other way: a tile per wave up to a contraction of 128,
+    # split beyond, in both gradients at once and each beside the other forms; one row more takes LDS tiles
+    ([128, 8200], 8, 0.0), ([129, 8200], 8, 0.9), ([8, 33000], 32, 0.9), ([33000, 7], 8, 0.0), ([8, 5], 33000, 0.9), ([5, 8200], 33, 0.0),
+    ([3, 33000], 64, 0.0), ([3, 33000], 65, 0.0), ([8200, 200], 16, 0.9), ([130, 40], 8200, 0.0),
+])
+def test_thin_products(dims, mb, momentum):
+    """As above.  Bar: contractions up to K = 33000, sqrt(K) * 2^-24 = 1.1e-5 in the worst order of additions; 3e-5
+    leaves a factor of 2.8.  (One layer: no gate.)"""
+    import paper_2401_01728_amd as rv
+    eta, wd = 1e-3, 1e-3 if momentum else 0.0
+    w0 = kaiming_uniform_flat(64, dims)
+    g = rv.Stage.mlp(dims, mb, 0, eta); g.set_params(dev(w0))
+    if momentum:
+        g.set_optimizer(momentum, wd)
+    o = ostage.Stage("mlp", 0, eta, w0, dims=dims, momentum=momentum, weight_decay=wd)
+    x = gen.normal_f32(64, 10, mb * dims[0]).reshape(mb, dims[0])
+    dy = gen.normal_f32(64, 50, mb * dims[-1], std=0.1).reshape(mb, dims[-1])
+    grp = "MLP thin products, bar 3e-5"
+    close(host64(g.forward(0, dev(x))), o.forward(0, x), 3e-5, "t", group=grp)
+    close(host64(g.backward(0, dev(dy))), o.backward(0, dy), 3e-5, "t", group=grp)
+    close(host64(g.last_grad()), o.last_grad, 3e-5, "t", group=grp)
+    close(host64(g.get_params()), o.w, 1e-6, "t", group="MLP product forms: parameters, bar 1e-6")
