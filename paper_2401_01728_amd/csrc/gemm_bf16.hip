@@ -1099,8 +1099,14 @@ rv_status launch_split(const rv_gemm_args& g, hipStream_t st) {
 //   2128  128x128, four waves of 64x64, BK 64, two stages, two workgroups per CU;
 //   1128  128x128, 1065 / 1064 64x64, 1032 32x64: the contraction split inside the workgroup over
 //         2, 2 / 4 and 8 groups of waves.
-// The automatic choice minimises the modelled time
-//   rounds * (f + turns * t),  rounds = ceil(tiles / (256 CUs * workgroups per CU)), turns = k-tiles per group,
+// The automatic choice among the first three minimises  rounds * tile area * workgroups per CU / efficiency,
+// rounds = ceil(tiles / (256 CUs * workgroups per CU)), efficiencies measured ratios.  By the time model below
+// instead (as it stood for a while), launches that fill between half a round and a round of 2192 took that tile and up
+// to 39 % longer: 8192x1280x3840 106 us against 76, 8192x1280x5120 146 against 111, 2048x4608x1536 47 against 37, 4096x2560x1280
+// 46 against 40.  Over 309 launches of 256 .. 8192 rows alone the rule is on average 0.3 % above the best of the three,
+// the model was 1.5 %; with 0.85 for 2128 the rule takes 132 us for 8192x4800x1600 instead of 121.
+// Whether the contraction is split is decided by the modelled time
+//   rounds * (f + turns * t),  turns = k-tiles per group,
 // f and t in us, t between t0 (a launch that leaves most CUs idle) and t1 (one that fills them), fitted to
 // launches of 64 .. 8192 rows alone.  A product of few tiles is one walk along K: 256x448x1792 takes 36 us
 // with 5256, 20 with 2128 and 7 with 1032; 128x1024x4096 75 / 44 / 15; 1152x768x3072 59 / 34 / 16
@@ -1122,6 +1128,15 @@ int best_form(int M, int N, int K, int codes_from, int codes_to, float& least) {
   return best;
 }
 
+int in_order_form(int M, int N) {
+  auto cost = [&](int bm, int bn, int bpc, double eff) {
+    const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+    return (double)((tiles + 256 * bpc - 1) / (256 * bpc)) * bm * bn * bpc / eff;
+  };
+  const double c256 = cost(256, 256, 1, 1.0), c192 = cost(128, 256, 2, 0.92), c128 = cost(128, 128, 2, 0.83);
+  return c256 <= c192 && c256 <= c128 ? 5256 : c192 <= c128 ? 2192 : 2128;
+}
+
 template <bool AKM, bool BKM, int EPI>
 rv_status pick_tile(const rv_gemm_args& g, hipStream_t st) {
   int tile = g.tile;
@@ -1131,7 +1146,8 @@ rv_status pick_tile(const rv_gemm_args& g, hipStream_t st) {
     // tile takes more CU time per flop, which the other streams of a step could have used (with
     // 4096x1024x4096 split, 49 against 61 us alone, the step of the 1024-wide stage is 6 % longer).
     float in_order = 0.f, split = 0.f;
-    tile = best_form(g.M, g.N, g.K, 2000, 10000, in_order);
+    best_form(g.M, g.N, g.K, 2000, 10000, in_order);
+    tile = in_order_form(g.M, g.N);
     const int s = best_form(g.M, g.N, g.K, AKM ? 1033 : 0, 2000, split);
     const long t256 = (long)((g.M + 255) / 256) * ((g.N + 255) / 256);
     if (split < 0.75f * in_order) tile = s;
