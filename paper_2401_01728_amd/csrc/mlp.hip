@@ -529,7 +529,7 @@ rv_status launch_bwd(hipStream_t st, const Prod& dx, const Out& ox, const Prod& 
 
 // ---- tiny ----------------------------------------------------------------------------------
 struct Tiny {
-  int n, mb, dim[kTinyLayers + 1];
+  int mb, dim[kTinyLayers + 1];
   unsigned offW[kTinyLayers], offB[kTinyLayers], offA[kTinyLayers], zero;   // zero: the number of parameters
 };
 constexpr int kTinyDepth = 128;   // contraction a wave requests at a time
@@ -802,15 +802,15 @@ int tiny_half(const rv_stage* s) {   // floats of one LDS activation buffer
 Tiny tiny_desc(const rv_stage* s) {
   const MlpPlan* p = (const MlpPlan*)s->impl;
   Tiny t = {};
-  t.n = p->n; t.mb = s->microbatch; t.zero = (unsigned)s->P;
+  t.mb = s->microbatch; t.zero = (unsigned)s->P;
   for (int i = 0; i <= p->n; ++i) t.dim[i] = (int)s->dims[i];
   for (int i = 0; i < p->n; ++i) { t.offW[i] = (unsigned)p->offW[i]; t.offB[i] = (unsigned)p->offB[i]; t.offA[i] = (unsigned)p->offA[i]; }
   return t;
 }
 template <typename F>
-rv_status tiny_by_shape(int n, int mt, F f) {   // layers and 16-row groups as constants
+rv_status tiny_by_shape(int n, int mt, F f) {   // layers (2, 3, 4) and 16-row groups as constants
   auto rows = [&](auto nl) { return mt == 1 ? f(nl, Int<1>()) : mt == 2 ? f(nl, Int<2>()) : f(nl, Int<4>()); };
-  return n == 1 ? rows(Int<1>()) : n == 2 ? rows(Int<2>()) : n == 3 ? rows(Int<3>()) : rows(Int<4>());
+  return n == 2 ? rows(Int<2>()) : n == 3 ? rows(Int<3>()) : rows(Int<4>());
 }
 bool overlap(const void* a, size_t na, const void* b, size_t nb) {
   return a && b && (const char*)a < (const char*)b + nb * 4 && (const char*)b < (const char*)a + na * 4;
@@ -837,13 +837,13 @@ rv_status rv_mlp_plan(rv_stage* s) {
   s->work_bytes = 2 * (size_t)s->microbatch * p->maxw * 4;
   // One launch per direction, or one per layer and direction?  Forward + backward of one microbatch
   // back to back, us (one per direction / one per layer):
-  //   64-128-64       8 rows 13.6 / 19.0   64 rows 27.9 / 19.9     64-64-64-64      8 rows 15.4 / 27.3
-  //   128-256-128     8 rows 27.5 / 20.5                           200-200-200-200 16 rows 46.3 / 31.8
-  //   16-16-16        4 rows  9.1 / 14.9   256-256-256 8 / 64 rows 37.0 / 21.6, 87.6 / 23.4
+  //   8 rows    16-16-16 11.9 / 18.7   64-128-64 14.9 / 22.0   64-64-64-64 15.2 / 29.8   64-64-64-64-64 18.0 / 42.0
+  //   16 rows   128-128-128-128 24.4 / 33.0   20-60-200-60-20 23.7 / 38     32 rows  64-64-64-64 19.6 / 31.6
+  //   one layer, 16 rows   32-32 11.7 / 11.3   16-256 12.8 / 11.8
   // A launch costs about 5 us whatever it does; the repeated chain about 8 + 2.5 (g - 1) us and
   // (0.2 + 0.11 g) ns per parameter, g = 1, 2, 4 groups of 16 rows.
   const int g = s->microbatch <= 16 ? 1 : s->microbatch <= 32 ? 2 : 4;
-  p->tiny = p->n <= kTinyLayers && s->microbatch <= kTinyRows && p->maxw <= 256 &&
+  p->tiny = p->n >= 2 && p->n <= kTinyLayers && s->microbatch <= kTinyRows && p->maxw <= 256 &&
             (20.0 + 11.0 * g) * (double)off < 1e5 * (10.0 * p->n - 5.5 - 2.5 * g);
   return RV_OK;
 }
