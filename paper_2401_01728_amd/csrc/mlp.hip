@@ -839,11 +839,14 @@ rv_status rv_mlp_plan(rv_stage* s) {
   // back to back, us (one per direction / one per layer):
   //   8 rows    16-16-16 11.9 / 18.7   64-128-64 14.9 / 22.0   64-64-64-64 15.2 / 29.8   64-64-64-64-64 18.0 / 42.0
   //   16 rows   128-128-128-128 24.4 / 33.0   20-60-200-60-20 23.7 / 38     32 rows  64-64-64-64 19.6 / 31.6
+  //   64 rows   16-16-16 19.9 / 20.0   48-48-48-48 29.3 / 32.4   64-64-64-64-64 42.7 / 43.6
+  //             10-200-10 30.3 / 22.4   72-72-72-72 43.5 / 33.0   96-96-96-96-96 61.2 / 44.2
   //   one layer, 16 rows   32-32 11.7 / 11.3   16-256 12.8 / 11.8
   // A launch costs about 5 us whatever it does; the repeated chain about 8 + 2.5 (g - 1) us and
-  // (0.2 + 0.11 g) ns per parameter, g = 1, 2, 4 groups of 16 rows.
+  // (0.2 + 0.11 g) ns per parameter, g = 1, 2, 4 groups of 16 rows.  With four groups the registers no longer hold
+  // what is requested ahead, and rows wider than 64 lose whatever the other widths.
   const int g = s->microbatch <= 16 ? 1 : s->microbatch <= 32 ? 2 : 4;
-  p->tiny = p->n >= 2 && p->n <= kTinyLayers && s->microbatch <= kTinyRows && p->maxw <= 256 &&
+  p->tiny = p->n >= 2 && p->n <= kTinyLayers && s->microbatch <= kTinyRows && p->maxw <= (g == 4 ? 64 : 256) &&
             (20.0 + 11.0 * g) * (double)off < 1e5 * (10.0 * p->n - 5.5 - 2.5 * g);
   return RV_OK;
 }

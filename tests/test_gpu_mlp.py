@@ -189,6 +189,8 @@ def test_stage_with_gradient_accumulation(A, momentum):
     # of exactly one request and of more than one
     ([1, 1], 1, 0.0), ([16, 128, 16], 16, 0.9), ([17, 129, 15], 17, 0.0), ([256, 13, 256], 33, 0.0),
     ([250, 40, 31, 7], 64, 0.9), ([120, 256, 20], 16, 0.0), ([40, 64, 3, 33, 128], 48, 0.0),
+    # the same with more than 32 rows: up to 64 wide
+    ([64, 13, 64], 33, 0.0), ([60, 40, 31, 7], 64, 0.9), ([40, 64, 3, 33, 64], 48, 0.0),
     # a 32 x 32 tile per workgroup: just past the widths / rows / layers of the form above
     ([257, 64, 31], 8, 0.9), ([64, 100, 64], 65, 0.0), ([8, 9, 10, 11, 12, 13], 5, 0.9), ([520, 40], 33, 0.0),
     # LDS tiles of 64 and of 128 with ragged edges (one layer: no gate, so no gate can fall the other
@@ -252,7 +254,7 @@ def _same(got, ref, tol, grp):
 
 # one launch per direction (16, 32 and 64 rows), split contraction, LDS tiles; widths and row counts that are no
 # multiple of a piece, so that the last weight row and the last activation row are what clamped indexes read
-_ODD = [([20, 7], 5), ([20, 24, 7], 13), ([17, 33, 9], 29), ([131, 30, 33], 45), ([300, 21, 9], 13), ([301, 1030], 1030)]
+_ODD = [([20, 7], 5), ([20, 24, 7], 13), ([17, 33, 9], 29), ([131, 30, 33], 45), ([61, 30, 33], 45), ([300, 21, 9], 13), ([301, 1030], 1030)]
 
 
 @pytest.mark.parametrize("where,dims,mb", [("first weight row",) + c for c in _ODD + [([18, 21, 19, 5], 50)]] +
