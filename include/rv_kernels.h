@@ -33,7 +33,8 @@ enum {
  *   Supported (a_kmajor, b_kmajor, epilogue): (0,1,{1,2,3,6}), (0,0,{0,4}), (1,1,{5}).
  *   K % 64 == 0; M, N, lda, ldb % 8 == 0; ldo % 8 == 0 for bf16 outputs and % 4 for fp32 ones;
  *   ldr % 4 == 0.  tile: 0 = automatic; 2128 (128x128), 2192 (128x256), 2256 (256x256, four
- *   waves), 5256 (256x256, eight waves) force a tile.
+ *   waves), 5256 (256x256, eight waves) force a tile; 1128 (128x128), 1065, 1064 (64x64) and 1032
+ *   (32x64; not with a_kmajor) one whose contraction is split over 2, 2, 4 and 8 groups of waves.
  */
 rv_status rv_k_gemm_bf16(const void* A, int64_t lda, int a_kmajor, const void* B, int64_t ldb,
                          int b_kmajor, int M, int N, int K, int epilogue, void* out, int64_t ldo,
@@ -51,6 +52,18 @@ rv_status rv_k_gemm_bf16(const void* A, int64_t lda, int a_kmajor, const void* B
 rv_status rv_k_gemm_wgrad_grouped(int count, const void* const* X, const int64_t* lda, const void* const* dY,
                                   const int64_t* ldb, const int* M, const int* N, int K, float* const* dW,
                                   void* stream);
+
+/*
+ * The same products as a decoder stage launches them.  The tile form is chosen by size: fewer than 256 tiles of
+ * 256x256 over fewer than 2048 tokens take 128x128 tiles with the contraction split (results equal
+ * rv_k_gemm_bf16(..., epilogue 5, tile 1128) bit for bit), the rest the form above.  w (with ver; both NULL: no
+ * update): host arrays of fp32 master matrices [M_i, N_i], updated in place, w <- w - eta * dW (Eq. 2, one fused
+ * multiply-add), and of bf16 weight versions that receive their rounding.  dW may be NULL with w: the gradients are
+ * then not stored.
+ */
+rv_status rv_k_gemm_wgrad_update(int count, const void* const* X, const int64_t* lda, const void* const* dY,
+                                 const int64_t* ldb, const int* M, const int* N, int K, float* const* dW,
+                                 float* const* w, void* const* ver, float eta, void* stream);
 
 /*
  * LayerNorm over the last dimension (biased variance, eps inside the root), affine in

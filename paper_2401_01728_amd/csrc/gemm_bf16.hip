@@ -1304,3 +1304,19 @@ extern "C" rv_status rv_k_gemm_wgrad_grouped(int count, const void* const* X, co
   }
   return rv_gemm_wgrad_grouped(g, count, (hipStream_t)stream, true);
 }
+
+extern "C" rv_status rv_k_gemm_wgrad_update(int count, const void* const* X, const int64_t* lda, const void* const* dY,
+                                            const int64_t* ldb, const int* M, const int* N, int K, float* const* dW,
+                                            float* const* w, void* const* ver, float eta, void* stream) {
+  if (count < 1 || count > RV_GEMM_GROUP_MAX || !X || !lda || !dY || !ldb || !M || !N || (!dW && !w) || !w != !ver) return RV_E_INVAL;
+  rv_gemm_args g[RV_GEMM_GROUP_MAX];
+  for (int k = 0; k < count; ++k) {
+    g[k].A = (const uint16_t*)X[k]; g[k].lda = lda[k]; g[k].a_kmajor = 1;
+    g[k].B = (const uint16_t*)dY[k]; g[k].ldb = ldb[k]; g[k].b_kmajor = 1;
+    g[k].M = M[k]; g[k].N = N[k]; g[k].K = K; g[k].epi = EPI_F32; g[k].ldo = N[k];
+    g[k].out = dW ? dW[k] : w[k];   // (not written without dW)
+    g[k].store_out = dW != nullptr;
+    if (w) { g[k].upd_w = w[k]; g[k].upd_ver = (uint16_t*)ver[k]; g[k].upd_eta = eta; }
+  }
+  return rv_gemm_wgrad_grouped(g, count, (hipStream_t)stream);
+}

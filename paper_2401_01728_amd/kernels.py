@@ -31,6 +31,19 @@ def gemm_wgrad_grouped(xs, dys, outs, stream=None):
     return outs
 
 
+def gemm_wgrad_update(xs, dys, outs=None, w=None, ver=None, eta=0.0, stream=None):
+    """rv_k_gemm_wgrad_update: the products of gemm_wgrad_grouped in the form a decoder stage launches, with the
+    update of the fp32 masters w[i] and bf16 versions ver[i] where given."""
+    n = len(xs)
+    vp = (ctypes.c_void_p * n); i64 = (ctypes.c_int64 * n); i32 = (ctypes.c_int * n)
+    arr = lambda ts: vp(*[_ptr(t) for t in ts]) if ts is not None else None
+    _check(_lib.lib().rv_k_gemm_wgrad_update(n, arr(xs), i64(*[x.stride(0) for x in xs]), arr(dys),
+                                             i64(*[y.stride(0) for y in dys]), i32(*[x.shape[1] for x in xs]),
+                                             i32(*[y.shape[1] for y in dys]), xs[0].shape[0], arr(outs), arr(w), arr(ver),
+                                             eta, _stream_handle(stream)))
+    return outs
+
+
 def layernorm_fwd(x, gamma, beta, eps, xcopy=None, stream=None):
     T, d = x.shape
     y = torch.empty(T, d, dtype=torch.bfloat16, device="cuda")

@@ -145,6 +145,43 @@ def test_grouped_weight_gradient_products():
         k.gemm_wgrad_grouped(xs * 2, dys * 2, outs * 2)      # more than four
 
 
+# K / 32 = 2, 8, 10, 62 k-tiles (fewer than the split form's eight ring slots, as many, two more, several turns);
+# 64 k-tiles are 2048 tokens, where the in-order form takes over
+@pytest.mark.parametrize("K,tile", [(64, 1128), (256, 1128), (320, 1128), (1984, 1128), (2048, 5256)])
+def test_grouped_weight_gradients_with_their_update(K, tile):
+    """The launch of a decoder stage: gradients against fp64 and bit for bit against single launches of the same tile,
+    the updated masters and versions bit for bit against rv_block_update with that gradient, with and without the
+    gradient stored."""
+    from paper_2401_01728_amd import kernels as k
+    import paper_2401_01728_amd as rv
+    eta = 0.05
+    dims = [(192, 256), (64, 64), (136, 512), (512, 72)]
+    xs, dys, ws, refs = [], [], [], []
+    for i, (M, N) in enumerate(dims):
+        x, x64 = bf16_normal(12, 3 * i, (K, M)); dy, dy64 = bf16_normal(12, 3 * i + 1, (K, N), std=1e-2)
+        xs.append(x); dys.append(dy); refs.append(x64.T @ dy64)
+        ws.append(torch.randn(M, N, device="cuda"))
+    single = [_out(s, torch.float32) for s in dims]
+    for i, (M, N) in enumerate(dims):
+        k.gemm_bf16(xs[i], 1, dys[i], 1, M, N, K, k.EPI_F32, single[i], tile=tile)
+        close(host64(single[i]), refs[i], 1e-5, "gemm", group=GROUP[1e-5])
+    outs = [_out(s, torch.float32) for s in dims]
+    k.gemm_wgrad_update(xs, dys, outs)
+    assert all(torch.equal(a, b) for a, b in zip(outs, single))
+    new, ver = [w.clone() for w in ws], [_out(s, torch.bfloat16) for s in dims]
+    for i in range(4):
+        rv.block_update(new[i].view(-1), single[i].view(-1), eta, bf16_out=ver[i].view(-1))
+    for store in (True, False):
+        w, v, outs = [w.clone() for w in ws], [_out(s, torch.bfloat16) for s in dims], [_out(s, torch.float32) for s in dims]
+        k.gemm_wgrad_update(xs, dys, outs if store else None, w, v, eta)
+        assert all(torch.equal(a, b) for a, b in zip(w, new)) and all(torch.equal(a, b) for a, b in zip(v, ver))
+        assert not store or all(torch.equal(a, b) for a, b in zip(outs, single))
+    with pytest.raises(rv.RvError):
+        k.gemm_wgrad_update(xs, dys, None, None, None, eta)      # nothing to write
+    with pytest.raises(rv.RvError):
+        k.gemm_wgrad_update(xs, dys, outs, ws, None, eta)        # masters without versions
+
+
 # an eighth of a tile, one tile exactly, a ragged second tile; K = 2, 4, 10 and 34 tiles of 32 (fewer than a
 # workgroup's groups, as many, a partly filled turn, several turns of every ring)
 @pytest.mark.parametrize("M,N,K", [(8, 8, 64), (64, 64, 128), (136, 200, 320), (40, 136, 1088), (264, 72, 64)])
