@@ -13,6 +13,9 @@ rv_status rv_launch_accumulate(float* acc, const float* g, size_t n, bool first,
 // master <- w and copy <- w in the version's type
 rv_status rv_launch_set(const float* w, size_t n, float* master, void* copy, int copy_kind, hipStream_t st);
 
+// the RV_VER_PAD bytes at offset `at` of each of n version slots <- 0 (at: a multiple of 4)
+rv_status rv_launch_clear_pads(char* const* ver, int n, size_t at, hipStream_t st);
+
 // ---- average.hip -----------------------------------------------------------------
 // rv_cluster_average with write-back, and the mean also stored to C weight versions (copy_kind)
 rv_status rv_average_publish(float* const* masters, void* const* versions, int copy_kind, int C, size_t n, int R, const float* grad,
@@ -102,7 +105,7 @@ struct rv_slot {
   char* base = nullptr;  // activation stash of this microbatch
 };
 
-#define RV_VER_PAD 16   // zero bytes behind the parameters of every weight version
+#define RV_VER_PAD 16   // bytes behind the parameters of every weight version; zero on an MLP stage (tiny_request_rest)
 
 struct rv_stage {
   int kind = 0, dtype = 0, n_layers = 0, microbatch = 0, tau = 0;

@@ -83,8 +83,7 @@ extern "C" rv_status rv_stage_create(const rv_stage_desc* d, rv_stage** out) {
       hipMemsetAsync(s->ver[0], 0, s->P * s->ver_elem, s->st) != hipSuccess) {
     free_all(s); return RV_E_DEVICE;
   }
-  for (char* v : s->ver)
-    if (hipMemsetAsync(v + s->P * s->ver_elem, 0, RV_VER_PAD, s->st) != hipSuccess) { free_all(s); return RV_E_DEVICE; }
+  if (s->kind == RV_MLP && rv_launch_clear_pads(s->ver.data(), nv, s->P * s->ver_elem, s->st) != RV_OK) { free_all(s); return RV_E_DEVICE; }
   if (hipStreamCreateWithFlags(&s->aux, hipStreamNonBlocking) != hipSuccess ||
       hipEventCreateWithFlags(&s->ev_fork, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&s->ev_join, hipEventDisableTiming) != hipSuccess ||

@@ -174,6 +174,15 @@ __global__ __launch_bounds__(kThreads) void set_kernel(const float* w, uint64_t 
   }
 }
 
+// One launch for 64 version slots: with a 16-byte hipMemsetAsync each, creating an MLP stage of tau = 4 / 100 took
+// 79 / 408 us instead of 62 / 170 (60 / 159 without the pads).
+constexpr int kPadSlots = 64;
+struct PadSlots { uint32_t* p[kPadSlots]; };
+__global__ __launch_bounds__(kPadSlots * RV_VER_PAD / 4) void clear_pads_kernel(PadSlots a, int n) {
+  const int slot = threadIdx.x / (RV_VER_PAD / 4);
+  if (slot < n) a.p[slot][threadIdx.x % (RV_VER_PAD / 4)] = 0;
+}
+
 }  // namespace
 
 rv_status rv_launch_update(float* w, const float* g, size_t n, float eta, void* copy, int copy_kind,
@@ -212,6 +221,16 @@ rv_status rv_launch_accumulate(float* acc, const float* g, size_t n, bool first,
   const unsigned blocks = (unsigned)((n + kTile - 1) / kTile);
   if (first) hipLaunchKernelGGL(accumulate_kernel<true>, dim3(blocks), dim3(kThreads), 0, st, acc, g, n, aligned);
   else hipLaunchKernelGGL(accumulate_kernel<false>, dim3(blocks), dim3(kThreads), 0, st, acc, g, n, aligned);
+  return rv_launch_status();
+}
+
+rv_status rv_launch_clear_pads(char* const* ver, int n, size_t at, hipStream_t st) {
+  for (int k = 0; k < n; k += kPadSlots) {
+    PadSlots a = {};
+    const int m = n - k < kPadSlots ? n - k : kPadSlots;
+    for (int i = 0; i < m; ++i) a.p[i] = reinterpret_cast<uint32_t*>(ver[k + i] + at);
+    hipLaunchKernelGGL(clear_pads_kernel, dim3(1), dim3(kPadSlots * RV_VER_PAD / 4), 0, st, a, m);
+  }
   return rv_launch_status();
 }
 

@@ -310,3 +310,22 @@ def test_thin_products(dims, mb, momentum):
     close(host64(g.backward(0, dev(dy))), o.backward(0, dy), 3e-5, "t", group=grp)
     close(host64(g.last_grad()), o.last_grad, 3e-5, "t", group=grp)
     close(host64(g.get_params()), o.w, 1e-6, "t", group="MLP product forms: parameters, bar 1e-6")
+
+
+def test_more_version_slots_than_one_launch_clears():
+    """tau = 70: 72 version slots, each bound to a microbatch in turn.  Contractions are no multiple of 16, so the
+    kernels read the zero behind every slot's parameters; the memory the slots may get held NaN before."""
+    import paper_2401_01728_amd as rv
+    dims, mb, tau, eta = [20, 24, 7], 5, 70, 1e-3
+    junk = [torch.full((1 << 19,), float("nan"), device="cuda") for _ in range(64)]
+    torch.cuda.synchronize(); del junk; torch.cuda.empty_cache()
+    w0 = kaiming_uniform_flat(65, dims)
+    g = rv.Stage.mlp(dims, mb, tau, eta); g.set_params(dev(w0))
+    o = ostage.Stage("mlp", tau, eta, w0, dims=dims)
+    for t in range(2 * tau + 10):
+        x = gen.normal_f32(65, 10 + t, mb * dims[0]).reshape(mb, dims[0])
+        close(host64(g.forward(t, dev(x))), o.forward(t, x), 1e-5, "t", group="MLP stage, bar 1e-5")
+        if t >= tau:
+            dy = gen.normal_f32(65, 500 + t, mb * dims[-1], std=0.1).reshape(mb, dims[-1])
+            close(host64(g.backward(t - tau, dev(dy))), o.backward(t - tau, dy), 1e-5, "t", group="MLP stage, bar 1e-5")
+    close(host64(g.get_params()), o.w, 1e-6, "t", group="MLP stage, bar 1e-6")
