@@ -642,9 +642,10 @@ extern "C" rv_status rv_k_attention_bwd(const void* qkv, const void* out, const 
 }
 
 // ---- the backward for callers that cannot allocate ---------------------------------------
-// The per-row term D = rowsum(dO * O) that the backward's two launches exchange lives in a
-// file-scope device array instead of a caller workspace.  Every GPU holds its own copy of
-// the array; its address on a device is looked up once, with that device current.
+// The per-row term D = rowsum(dO * O) that the backward's two launches exchange (one launch
+// keeps it to itself and leaves the array alone) lives in a file-scope device array instead of a
+// caller workspace.  Every GPU holds its own copy of the array; its address on a device is looked
+// up once, with that device current.
 namespace {
 constexpr int kStaticRows = 262144;   // 1 MiB: microbatch * n_heads * seq may not exceed this
 static __device__ __align__(256) float scratch[kStaticRows];
@@ -676,7 +677,7 @@ extern "C" rv_status rv_k_attention_bwd_static(const void* qkv, const void* out,
     return RV_E_INVAL;   // beyond the fixed scratch
   float* D = nullptr;
   RV_TRY(static_scratch(&D));
-  // every row of D that the second kernel reads is written by the first one in this call:
+  // every row of D that a second launch reads is written by the first one in this call:
   // nothing of the previous call's contents is used, so nothing has to be cleared
   return rv_attn_bwd((const uint16_t*)qkv, (const uint16_t*)out, (const uint16_t*)dout, lse2, D,
                      (uint16_t*)dqkv, microbatch, seq, d_model, n_heads, (hipStream_t)stream);

@@ -185,7 +185,7 @@ rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
   // block, the reductions behind the bias and LayerNorm gradients, the block's delayed update -
   // is side work: nothing in the chain dy -> dx that the block below waits for reads it.  It
   // goes to a stream of its own and runs beside the next block's chain (measured step time
-  // against issuing it in line: config 2 -7 %, config 3 -1 %, config 5 -5 %).  Buffers that
+  // against issuing it in line: d 1024 -7 %, d 2048 -1 %, d 1600 -5 %).  Buffers that
   // side work reads alternate between blocks (dy: in threes, since block l-1 writes the dy of
   // block l-2 while the side work of block l still reads its own).
   hipStream_t ws = s->wgs;

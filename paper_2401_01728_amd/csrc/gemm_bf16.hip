@@ -776,7 +776,7 @@ __global__ __launch_bounds__(64 * NW, WPE) void gemm_dtl_kernel(const uint16_t* 
 // ---- few tiles: the contraction split inside a workgroup ------------------------------------
 // A product whose 128x128 or 256x256 tiles do not cover the chip lasts as long as ONE workgroup's
 // walk along K: each 32-deep step costs a barrier and what is left of a memory round trip, and most
-// CUs have no tile at all.  Here a workgroup of G groups of four waves takes a smaller tile and group
+// CUs have no tile at all.  Here a workgroup of G groups of NW waves takes a smaller tile and group
 // g the k-tiles g, g + G, ... of it, each group with its own ring of NS slots - the walk is G times
 // shorter and a CU keeps G (NS - 1) k-tiles on the way.  (Interleaved k-tiles, so that the two
 // halves of a 128-byte line of a k-contiguous operand are asked for together.)  The G partial
@@ -1067,7 +1067,7 @@ rv_status launch_dtl(const rv_gemm_args& g, hipStream_t st) {
   // Measured: alone, the XCD-banded map pays only for the small tile.  Inside a stage step a
   // launch holds about a third of every XCD's CUs, and what an XCD runs of it at one time should
   // share operand panels: bands of 8 tile rows (2 for 32 or more tile rows, either tile size)
-  // against the natural order: stage steps -1.3 % / -0.6 % / -1.9 % (configs 5 / 3 / 2).
+  // against the natural order: stage steps -1.3 % / -0.6 % / -1.9 % (d 1600 / 2048 / 1024).
   int band = 8;
   if (g.sharing != 0) band = tm >= 32 ? 2 : 8;
   else if (!(BM == 128 && BN == 128)) tm = -tm;
@@ -1266,12 +1266,17 @@ rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t s
     if ((((uintptr_t)g.upd_w) & 15) || (((uintptr_t)g.upd_ver) & 7)) return RV_E_INVAL;
   }
   // 256x256 tiles, eight waves (measured against 128x128 and 128x256 tiles, alone and inside the
-  // stage step of configs 2, 3 and 5: fewest LDS bytes per MFMA, so it takes the least CU time
+  // stage step of d 1024, 2048 and 1600: fewest LDS bytes per MFMA, so it takes the least CU time
   // from the kernels that run beside it, and the step is 3-4 % shorter)
   // A block whose 256x256 tiles do not cover the chip and whose walk along the tokens is short takes
   // 128x128 tiles with the walk split in two, four times as many: 24 -> 12 us (d 448, ffn 1792, 256
   // tokens, 44 tiles), 37 -> 34 us (768, 3072, 1152 tokens, 108); even at 30 us with 128 tokens of a
-  // 1024-wide block, where the update's 126 MB bound it.  Longer walks keep the CU time per flop down.
+  // 1024-wide block, where the update's 126 MB bound it.  Longer walks keep the CU time per flop down: stage steps of
+  // four blocks, ms, split / in order (the separate calls differ the same way):
+  //   tokens           512          1024         1536         2048         3072         4096
+  //   d 1024   0.710/0.732  0.870/0.876  1.090/1.074  1.240/1.220  1.584/1.535  1.979/1.881
+  //   d 768    0.514/0.520  0.656/0.651  0.772/0.786  0.917/0.904  1.156/1.095  1.377/1.357
+  //   d 448    0.390/0.410  0.425/0.443  0.486/0.496  0.531/0.568  0.669/0.690  0.786/0.818
   if (!in_order) {
     int tiles = 0;
     for (int k = 0; k < count; ++k) tiles += ((gs[k].M + 255) / 256) * ((gs[k].N + 255) / 256);

@@ -38,7 +38,8 @@ struct rv_gemm_args {
   //   0  nobody: shortest time of this launch alone
   //   1  the other streams of a stage step, and the launch is on the step's critical chain:
   //      the 256x256 tile as soon as it covers half the chip
-  //   2  the same, off the critical chain: always the 256x256 tile (least CU time per flop)
+  //   2  the same, off the critical chain: the 256x256 tile (least CU time per flop)
+  // in every case a split form instead where it takes a quarter off the launch's time alone
   int sharing = 0;
   // weight-gradient products of the grouped launch only: the delayed update of Eq. 2 applied in
   // the epilogue.  upd_w = fp32 master tile base (same [M, ldo] layout as out), upd_ver = bf16
@@ -130,7 +131,8 @@ struct rv_stage {
   bool defer = false;       // backward leaves its update pending (folded into the next cluster sync)
   bool keep_grad = false;   // decoder: also store the parameter gradient when the update is applied in the
                             // epilogues that produce it (rv_stage_keep_grad)
-  bool fused = false;       // the running backward applies Eq. 2 in those epilogues
+  bool fused = false;       // the running backward applies the update where the gradient is produced: plain Eq. 2,
+                            // on an MLP stage the momentum form as well
   bool grad_valid = false;  // `grad` holds the whole gradient of the last backward
   size_t ver_elem = 0;      // bytes per parameter in a version slot (2 or 4)
   std::vector<char*> ver;   // tau+2 version slots: one is always free of readers, so an update can be

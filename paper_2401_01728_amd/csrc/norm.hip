@@ -551,9 +551,11 @@ rv_status rv_ln_fwd(const void* x, int x_is_bf16, float* xcopy, const uint16_t* 
 // 1024-wide stage measured 0.4 % shorter than with 16, and 0.9 % shorter than with 4), 16 beyond (8 measured
 // -0.2 % at d = 1600 and +0.2 % at d = 2048).  Fewer than 256 workgroups of those leave CUs without one
 // while the others walk through their rows one memory round trip after another: then a workgroup
-// takes fewer, down to 2.  (Against 8 / 16 rows for every token count: an averaging iteration over four
-// stages of d 1024 on 128 tokens 3.27 -> 3.19 ms; six blocks of d 768 on 1152 tokens, four microbatches,
-// 5.550 -> 5.535 ms.)
+// takes fewer, down to 2.  Three blocks, stage step / separate calls, ms, against 8 / 16 rows for every token count:
+//   d 448    256 tokens  - / 0.354 -> 0.318        d 1024   256 tokens  0.429 / 0.560 -> 0.416 / 0.545
+//   d 768    512 tokens  0.433 / 0.549 -> 0.414 / 0.534     d 1280   256 tokens  0.617 / 0.745 -> 0.470 / 0.589
+//   d 1600    64 tokens  0.711 / 0.883 -> 0.552 / 0.728              768 tokens  1.248 / 1.578 -> 1.093 / 1.403
+//   d 2048  2048 tokens  1.821 / 2.098 -> 1.740 / 2.130 (the one size seen to lose, in separate calls)
 int rv_ln_bwd_rows(int T, int d) {
   int rows = d <= 1024 ? 8 : 16;
   while (rows > 2 && (T + rows - 1) / rows < 256) rows /= 2;
