@@ -137,7 +137,7 @@ rv_status rv_stage_set_accumulation(rv_stage* s, int microbatches);
 
 /*
  * Forward branch of Alg. 1: out = forward_pass(x_{c,p}, in) at the CURRENT
- * parameters.  Binds mb_id to a stash slot and to the current weight version.
+ * parameters.  Binds mb_id to a stash slot and to the current weight version.  out may share in's buffer.
  * in/out: device, MLP fp32 [microbatch, dims[0]] -> [microbatch, dims[n_layers]];
  * decoder bf16 [microbatch, seq, d_model] -> same shape.
  * RV_E_STASH_FULL when tau+1 microbatches are in flight; RV_E_DUP_MB.
@@ -148,7 +148,7 @@ rv_status rv_stage_forward(rv_stage* s, int64_t mb_id, const void* in, void* out
  * Backward branch of Alg. 1 with the update of Eq. 2: computes the exact
  * gradient of the block at the weights and activations of mb_id's forward
  * (the stale gradient g^{k - tau_k}), writes the gradient for the preceding
- * peer to grad_in (may be NULL), applies x <- x - eta * g to this stage's
+ * peer to grad_in (may be NULL; may share grad_out's buffer), applies x <- x - eta * g to this stage's
  * block only (Eq. 4) and publishes the result as the newest weight version.
  * Any in-flight id is legal.  RV_E_UNKNOWN_MB.
  */

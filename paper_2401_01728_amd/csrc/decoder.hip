@@ -204,8 +204,15 @@ rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
   // gradient of the last block's output: fp32 copy for the residual path, bf16 as operand
   // (summed over tokens it is also the gradient of the last block's b2: partial sums on the way)
   float* part_dy = (float*)(s->work + p.w_part_dy);
-  RV_TRY(rv_widen_colsum((const uint16_t*)grad_out, dres, part_dy, T, d, st));
   const uint16_t* dres16 = (const uint16_t*)grad_out;
+  if (rv_overlap(grad_out, (size_t)T * d * 2, grad_in, (size_t)T * d * 2)) {
+    // the first block's backward writes grad_in without waiting for the side stream, where the last block's dW2
+    // still reads the arriving gradient: that goes to its place among the gradients of the other blocks first
+    uint16_t* dy = (uint16_t*)(s->work + p.w_dy[(p.L - 1) % 3]);
+    RV_HIP_TRY(hipMemcpyAsync(dy, grad_out, (size_t)T * d * 2, hipMemcpyDeviceToDevice, st));
+    dres16 = dy;
+  }
+  RV_TRY(rv_widen_colsum(dres16, dres, part_dy, T, d, st));
   colsum(part_dy, rv_widen_parts(T), d, d, s->grad + (size_t)(p.L - 1) * p.per_block + p.b2);
   // When the four weight-gradient products of a block go to the side stream.  Launch points:
   // 0 behind the GELU' product (dz exists: dW2 and dW1 can run), 1 behind the second LayerNorm's

@@ -106,6 +106,11 @@ struct rv_slot {
   char* base = nullptr;  // activation stash of this microbatch
 };
 
+// do [a, a + na) and [b, b + nb) bytes meet (null: no)
+inline bool rv_overlap(const void* a, size_t na, const void* b, size_t nb) {
+  return a && b && (const char*)a < (const char*)b + nb && (const char*)b < (const char*)a + na;
+}
+
 #define RV_VER_PAD 16   // bytes behind the parameters of every weight version; zero on an MLP stage (tiny_request_rest)
 
 struct rv_stage {

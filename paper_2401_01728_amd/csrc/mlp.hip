@@ -812,8 +812,10 @@ rv_status tiny_by_shape(int n, int mt, F f) {   // layers (2, 3, 4) and 16-row g
   auto rows = [&](auto nl) { return mt == 1 ? f(nl, Int<1>()) : mt == 2 ? f(nl, Int<2>()) : f(nl, Int<4>()); };
   return n == 2 ? rows(Int<2>()) : n == 3 ? rows(Int<3>()) : rows(Int<4>());
 }
-bool overlap(const void* a, size_t na, const void* b, size_t nb) {
-  return a && b && (const char*)a < (const char*)b + nb * 4 && (const char*)b < (const char*)a + na * 4;
+// [mb, wa] and [mb, wb] floats
+bool overlap(const rv_stage* s, const void* a, int64_t wa, const void* b, int64_t wb) {
+  const size_t row = (size_t)s->microbatch * 4;
+  return rv_overlap(a, row * wa, b, row * wb);
 }
 }  // namespace
 
@@ -862,7 +864,7 @@ rv_status rv_mlp_forward(rv_stage* s, rv_slot& slot, const void* in, void* out) 
   float* stash = (float*)slot.base;
   const int mb = s->microbatch;
   // a caller may hand the same buffer in and out: then nothing may be written before all of it is read
-  const bool in_place = overlap(in, (size_t)mb * s->dims[0], out, (size_t)mb * s->dims[p->n]);
+  const bool in_place = overlap(s, in, s->dims[0], out, s->dims[p->n]);
   if (p->tiny && !in_place) {
     const Tiny t = tiny_desc(s);
     const int half = tiny_half(s), mt = (mb + 15) / 16;
@@ -904,7 +906,7 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
   const int mb = s->microbatch;
   Upd u = {s->grad, nullptr, nullptr, nullptr, s->eta, s->momentum, s->weight_decay};
   if (s->fused) { u.w = s->master; u.vel = s->vel; u.ver = (float*)s->ver[s->upd_dst]; }
-  if (p->tiny && !overlap(grad_out, (size_t)mb * s->dims[p->n], grad_in, (size_t)mb * s->dims[0])) {
+  if (p->tiny && !overlap(s, grad_out, s->dims[p->n], grad_in, s->dims[0])) {
     const Tiny t = tiny_desc(s);
     const int half = tiny_half(s), mt = (mb + 15) / 16;
     int tiles = 0;
@@ -923,7 +925,7 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
   float* ping = (float*)s->work;
   float* pong = ping + (size_t)mb * p->maxw;
   const float* d = (const float*)grad_out;   // dL/dz_i, already gated
-  if (p->n == 1 && overlap(grad_out, (size_t)mb * s->dims[1], grad_in, (size_t)mb * s->dims[0])) {
+  if (p->n == 1 && overlap(s, grad_out, s->dims[1], grad_in, s->dims[0])) {
     // the one launch reads the gradient for all its parts while the input gradient is written over it
     RV_HIP_TRY(hipMemcpyAsync(ping, grad_out, (size_t)mb * s->dims[1] * 4, hipMemcpyDeviceToDevice, s->st));
     d = ping;

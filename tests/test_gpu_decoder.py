@@ -254,3 +254,31 @@ def test_decoder_stage_with_accumulation_in_fused_steps(A, momentum, wd):
             check_tensors(host64(g.last_grad()), o.last_grad, shapes, what="grad step %d" % j, group=tag + " param grads")
     assert o.k == n // A
     assert rel_l2(host64(g.get_params()) - w0, o.w - w0) < TOL
+
+
+@pytest.mark.parametrize("L,d,H,f,S,mb,tau,step", [(1, 128, 2, 2048, 256, 4, 0, False), (2, 256, 2, 1024, 128, 3, 1, True),
+                                                   (4, 128, 2, 512, 64, 2, 2, True), (1, 2048, 16, 8192, 64, 1, 0, False)])
+def test_grad_in_may_share_the_buffer_of_grad_out(L, d, H, f, S, mb, tau, step):
+    """Bit for bit as with two buffers: one block (whose dW2 reads the gradient that its own input gradient replaces) and
+    more, the weight-gradient products leaving early (d 2048, ffn 8192) and not, alone and inside a stage step."""
+    import paper_2401_01728_amd as rv
+    w0 = dev(decoder_params_host(71, L, d, f))
+    res = []
+    for shared in (False, True):
+        g = rv.Stage.decoder(L, d, H, f, S, mb, tau, 1e-2, keep_grad=True)
+        g.set_params(w0)
+        outs = []
+        for t in range(tau + 3):
+            x, _ = bf16_normal(71, 10 + t, (mb, S, d))
+            dy, _ = bf16_normal(71, 50 + t, (mb, S, d), std=1e-2)
+            dx = dy if shared else torch.empty_like(dy)
+            y = torch.empty_like(x)
+            if t < tau:
+                g.forward(t, x, y)
+            elif step:
+                g.step(t, x, t - tau, dy, y, dx)
+            else:
+                g.forward(t, x, y); g.backward(t - tau, dy, dx)
+            outs += [y] + ([dx, g.last_grad()] if t >= tau else [])
+        res.append(outs + [g.get_params()])
+    assert all(torch.equal(a, b) for a, b in zip(*res))
