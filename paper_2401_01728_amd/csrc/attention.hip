@@ -598,6 +598,8 @@ namespace {
 //   head size 64    nwg 14 14.4 / 8.9    108 25.6 / 17.3    256 31.8 / 24.0 (S 512), 93.3 / 71.3 (S 2048)
 //                   512 38.8 / 35.4      1024 99.9 / 99.2   1600 146.9 / 152.3
 //   head size 128   nwg 4 23.2 / 15.5    128 89.4 / 70.4 (S 1024)    256 92.2 / 71.5    512 116.0 / 134.9
+// Over S 64 .. 8192 at nwg 8 .. 512 (256) one launch takes 0.64 .. 0.99 of the two, but for two sizes at the limit: head
+// size 64, S 256, nwg 512 30.0 / 30.7 and 128, S 128, nwg 256 29.4 / 30.4.
 // Stage steps: 12 blocks of d 448 on 256 tokens 1.27 -> 1.21 ms, 6 of d 768 on 1152 tokens with four
 // microbatches 5.84 -> 5.56 ms, four of d 1024 on 4096 tokens (nwg 512) 1.91 -> 1.88 ms.
 bool one_launch(int dh, int nwg) { return nwg <= (dh == 64 ? 512 : 256); }
