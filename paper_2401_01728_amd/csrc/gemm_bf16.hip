@@ -1147,13 +1147,13 @@ rv_status pick_tile(const rv_gemm_args& g, hipStream_t st) {
     // 4096x1024x4096 split, 49 against 61 us alone, the step of the 1024-wide stage is 6 % longer).
     float in_order = 0.f, split = 0.f;
     best_form(g.M, g.N, g.K, 2000, 10000, in_order);
-    tile = in_order_form(g.M, g.N);
     const int s = best_form(g.M, g.N, g.K, AKM ? 1033 : 0, 2000, split);
     const long t256 = (long)((g.M + 255) / 256) * ((g.N + 255) / 256);
     if (split < 0.75f * in_order) tile = s;
     // Measured inside the stage step (d = 1024, 1600, 2048): what a launch leaves of the chip is
     // used by the other streams, so CU time per flop counts for more than its own duration.
     else if (g.sharing == 2 || (g.sharing && t256 >= 128)) tile = 5256;
+    else tile = in_order_form(g.M, g.N);
   }
   if constexpr (!AKM) {
     if (tile == 1032) return launch_split<32, 64, 8, 2, 3, AKM, BKM, EPI>(g, st);
