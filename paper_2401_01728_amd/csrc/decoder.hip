@@ -22,12 +22,22 @@ struct DecPlan {
   size_t ln1g, ln1b, wqkv, bqkv, wo, bo, ln2g, ln2b, w1, b1, w2, b2, per_block;
   // byte offsets inside one block's stash
   size_t s_x, s_m1, s_r1, s_u, s_qkv, s_a, s_lse, s_x1, s_m2, s_r2, s_v2, s_z, s_g, blk_bytes;
-  // byte offsets inside the work buffer
-  // (dy: three buffers, dx1 / dz / dqkv: two, so a block's weight-gradient products can run
-  // beside the next block)
-  size_t w_dres, w_dy[3], w_dx1_16[2], w_dtmp, w_dz[2], w_dqkv[2], w_D, w_part_ln[2][2], w_part_dy, w_part_dz[2],
-      w_part_qkv[2], w_ytmp;
+  // byte offsets inside the work buffer.  What a block's side work reads (dy, dx1, dz, dqkv and the partial rows of the
+  // column sums) alternates between `sets` sets, so that it can run beside the blocks below: block l uses set l % sets,
+  // its dy buffer l % (sets + 1) (block l - 1 writes the dy of block l - 2 while the side work of block l still reads
+  // its own).  deep: a set for every block, nothing is overwritten within a backward.
+  bool deep;
+  int sets, dy_sets, group;   // group: blocks whose side work goes out together (deep only)
+  size_t w_dres, w_dtmp, w_D, w_part_dy, w_ytmp;
+  size_t w_dy, dy_bytes;                                                   // dy buffers: w_dy + i * dy_bytes
+  size_t w_set, set_bytes;                                                 // sets: w_set + i * set_bytes, and in a set
+  size_t o_dx1_16, o_dz, o_dqkv, o_part_ln[2], o_part_dz, o_part_qkv;
 };
+
+// A stage whose sets for every block fit in this many bytes gets them (deep).
+constexpr size_t kDeepBytes = 512u << 20;
+constexpr int kGroupBlocks = RV_GEMM_GROUP_MAX / 4;
+static_assert(9 * kGroupBlocks <= RV_REDUCE_MAX, "the column sums of a group fit in one launch");
 
 }  // namespace
 
@@ -68,23 +78,38 @@ rv_status rv_dec_plan(rv_stage* s) {
   p->s_g = b; b += align_up(T * f * 2);
   p->blk_bytes = b;
   s->slot_bytes = b * p->L;
+  // one set; partial rows of the bias gradients: of dz (one per tile row of the product that makes it, at least 32 rows)
+  // and of dqkv (32-token blocks)
+  const size_t part_ln = (size_t)rv_ln_bwd_parts(p->T, d) * 3 * d;
+  size_t q = 0;
+  p->o_dx1_16 = q; q += align_up(T * d * 2);
+  p->o_dz = q; q += align_up(T * f * 2);
+  p->o_dqkv = q; q += align_up(T * 3 * d * 2);
+  for (size_t& o : p->o_part_ln) { o = q; q += align_up(part_ln * 4); }
+  p->o_part_dz = q; q += align_up((size_t)((T + 31) / 32) * f * 4);
+  p->o_part_qkv = q; q += align_up((size_t)rv_attn_colsum_parts(p->mb, p->S) * 3 * d * 4);
+  p->set_bytes = q;
+  p->dy_bytes = align_up(T * d * 2);
+  p->deep = (size_t)p->L * (p->set_bytes + p->dy_bytes) <= kDeepBytes;
+  p->sets = p->deep ? p->L : 2;
+  p->dy_sets = p->deep ? p->L : 3;
+  p->group = 1;
+  if (p->deep && p->T < RV_WGRAD_SPLIT_K) {
+    // as many blocks as give the split weight-gradient launch a tile for every CU (a launch is a few microseconds, and the
+    // event pair in front of it 11 of host time, however small it is)
+    auto tiles = [](int64_t M, int64_t N) { return ((M + 127) / 128) * ((N + 127) / 128); };
+    const int64_t n = 2 * tiles(d, f) + tiles(d, d) + tiles(d, 3 * d);
+    p->group = (int)((256 + n - 1) / n);
+    if (p->group > kGroupBlocks) p->group = kGroupBlocks;
+  }
   size_t w = 0;
   p->w_dres = w; w += align_up(T * d * 4);
-  for (size_t& o : p->w_dy) { o = w; w += align_up(T * d * 2); }
-  for (size_t& o : p->w_dx1_16) { o = w; w += align_up(T * d * 2); }
   p->w_dtmp = w; w += align_up(T * d * 2);
-  for (size_t& o : p->w_dz) { o = w; w += align_up(T * f * 2); }
-  for (size_t& o : p->w_dqkv) { o = w; w += align_up(T * 3 * d * 2); }
   p->w_D = w; w += align_up(T * H * 4);
-  const size_t part_ln = (size_t)rv_ln_bwd_parts(p->T, d) * 3 * d;
-  for (auto& pair : p->w_part_ln)
-    for (size_t& o : pair) { o = w; w += align_up(part_ln * 4); }
-  // partial rows of the bias gradients: of the arriving gradient (32-row blocks), of dz (one per tile
-  // row of the product that makes it, at least 32 rows) and of dqkv (32-token blocks)
-  p->w_part_dy = w; w += align_up((size_t)rv_widen_parts(p->T) * d * 4);
-  for (size_t& o : p->w_part_dz) { o = w; w += align_up((size_t)((T + 31) / 32) * f * 4); }
-  for (size_t& o : p->w_part_qkv) { o = w; w += align_up((size_t)rv_attn_colsum_parts(p->mb, p->S) * 3 * d * 4); }
+  p->w_part_dy = w; w += align_up((size_t)rv_widen_parts(p->T) * d * 4);   // of the arriving gradient (32-row blocks)
   p->w_ytmp = w; w += align_up(T * d * 4);
+  p->w_dy = w; w += p->dy_bytes * p->dy_sets;
+  p->w_set = w; w += p->set_bytes * p->sets;
   s->work_bytes = w;
   return RV_OK;
 }
@@ -112,142 +137,178 @@ rv_status gemm(int sharing, hipStream_t st, const void* A, int64_t lda, int akm,
   return rc;
 }
 
-}  // namespace
-
-rv_status rv_dec_forward(rv_stage* s, rv_slot& slot, const void* in, void* out) {
+// the forward of block l of one microbatch, on st
+rv_status forward_block(const rv_stage* s, const rv_slot& slot, const void* in, void* out, int l, hipStream_t st) {
   const DecPlan& p = *(const DecPlan*)s->impl;
-  const uint16_t* wv = (const uint16_t*)s->ver[slot.ver];
-  hipStream_t st = s->st;
   const int T = p.T, d = p.d, f = p.f;
   const int sh = s->in_step ? 2 : 0;   // in a step the backward chain is the longer one
-  for (int l = 0; l < p.L; ++l) {
-    const uint16_t* w = wv + (size_t)l * p.per_block;
-    char* sb = slot.base + (size_t)l * p.blk_bytes;
-    float* x = (float*)(sb + p.s_x);
-    float* x1 = (float*)(sb + p.s_x1);
-    uint16_t* u = (uint16_t*)(sb + p.s_u);
-    uint16_t* qkv = (uint16_t*)(sb + p.s_qkv);
-    uint16_t* a = (uint16_t*)(sb + p.s_a);
-    uint16_t* v2 = (uint16_t*)(sb + p.s_v2);
-    uint16_t* z = (uint16_t*)(sb + p.s_z);
-    uint16_t* g = (uint16_t*)(sb + p.s_g);
-    if (l == 0)
-      RV_TRY(rv_ln_fwd(in, 1, x, w + p.ln1g, w + p.ln1b, u, (float*)(sb + p.s_m1), (float*)(sb + p.s_r1), T, d,
-                       s->ln_eps, st));
-    else
-      RV_TRY(rv_ln_fwd(x, 0, nullptr, w + p.ln1g, w + p.ln1b, u, (float*)(sb + p.s_m1), (float*)(sb + p.s_r1), T,
-                       d, s->ln_eps, st));
-    RV_TRY(gemm(sh, st, u, d, 0, w + p.wqkv, 3 * d, 1, T, 3 * d, d, RV_EPI_BF16_BIAS, qkv, 3 * d, nullptr, w + p.bqkv));
-    RV_TRY(rv_attn_fwd(qkv, a, (float*)(sb + p.s_lse), p.mb, p.S, d, p.H, st));
-    RV_TRY(gemm(sh, st, a, d, 0, w + p.wo, d, 1, T, d, d, RV_EPI_F32_BIAS_RESID, x1, d, nullptr, w + p.bo, x));
-    RV_TRY(rv_ln_fwd(x1, 0, nullptr, w + p.ln2g, w + p.ln2b, v2, (float*)(sb + p.s_m2), (float*)(sb + p.s_r2), T, d,
+  const uint16_t* w = (const uint16_t*)s->ver[slot.ver] + (size_t)l * p.per_block;
+  char* sb = slot.base + (size_t)l * p.blk_bytes;
+  float* x = (float*)(sb + p.s_x);
+  float* x1 = (float*)(sb + p.s_x1);
+  uint16_t* u = (uint16_t*)(sb + p.s_u);
+  uint16_t* qkv = (uint16_t*)(sb + p.s_qkv);
+  uint16_t* a = (uint16_t*)(sb + p.s_a);
+  uint16_t* v2 = (uint16_t*)(sb + p.s_v2);
+  uint16_t* z = (uint16_t*)(sb + p.s_z);
+  uint16_t* g = (uint16_t*)(sb + p.s_g);
+  if (l == 0)
+    RV_TRY(rv_ln_fwd(in, 1, x, w + p.ln1g, w + p.ln1b, u, (float*)(sb + p.s_m1), (float*)(sb + p.s_r1), T, d, s->ln_eps, st));
+  else
+    RV_TRY(rv_ln_fwd(x, 0, nullptr, w + p.ln1g, w + p.ln1b, u, (float*)(sb + p.s_m1), (float*)(sb + p.s_r1), T, d,
                      s->ln_eps, st));
-    RV_TRY(gemm(sh, st, v2, d, 0, w + p.w1, f, 1, T, f, d, RV_EPI_BF16_BIAS_GELU, z, f, g, w + p.b1));
-    if (l + 1 < p.L) {
-      float* xn = (float*)(slot.base + (size_t)(l + 1) * p.blk_bytes + p.s_x);
-      RV_TRY(gemm(sh, st, g, f, 0, w + p.w2, d, 1, T, d, f, RV_EPI_F32_BIAS_RESID, xn, d, nullptr, w + p.b2, x1));
-    } else {
-      RV_TRY(gemm(sh, st, g, f, 0, w + p.w2, d, 1, T, d, f, RV_EPI_F32_BIAS_RESID_BF16, s->work + p.w_ytmp, d, out,
-                  w + p.b2, x1));
-    }
+  RV_TRY(gemm(sh, st, u, d, 0, w + p.wqkv, 3 * d, 1, T, 3 * d, d, RV_EPI_BF16_BIAS, qkv, 3 * d, nullptr, w + p.bqkv));
+  RV_TRY(rv_attn_fwd(qkv, a, (float*)(sb + p.s_lse), p.mb, p.S, d, p.H, st));
+  RV_TRY(gemm(sh, st, a, d, 0, w + p.wo, d, 1, T, d, d, RV_EPI_F32_BIAS_RESID, x1, d, nullptr, w + p.bo, x));
+  RV_TRY(rv_ln_fwd(x1, 0, nullptr, w + p.ln2g, w + p.ln2b, v2, (float*)(sb + p.s_m2), (float*)(sb + p.s_r2), T, d,
+                   s->ln_eps, st));
+  RV_TRY(gemm(sh, st, v2, d, 0, w + p.w1, f, 1, T, f, d, RV_EPI_BF16_BIAS_GELU, z, f, g, w + p.b1));
+  if (l + 1 < p.L) {
+    float* xn = (float*)(slot.base + (size_t)(l + 1) * p.blk_bytes + p.s_x);
+    return gemm(sh, st, g, f, 0, w + p.w2, d, 1, T, d, f, RV_EPI_F32_BIAS_RESID, xn, d, nullptr, w + p.b2, x1);
   }
-  return RV_OK;
+  return gemm(sh, st, g, f, 0, w + p.w2, d, 1, T, d, f, RV_EPI_F32_BIAS_RESID_BF16, s->work + p.w_ytmp, d, out, w + p.b2, x1);
 }
 
-rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void* grad_in) {
-  const DecPlan& p = *(const DecPlan*)s->impl;
-  const uint16_t* wv = (const uint16_t*)s->ver[slot.ver];
-  hipStream_t st = s->st;
-  const int T = p.T, d = p.d, f = p.f;
-  const int sh = s->in_step ? 1 : 0;
-  float* dres = (float*)(s->work + p.w_dres);
-  uint16_t* dtmp = (uint16_t*)(s->work + p.w_dtmp);
-  float* Dbuf = (float*)(s->work + p.w_D);
-  const int ln_rows = rv_ln_bwd_rows(T, d), ln_parts = rv_ln_bwd_parts(T, d);
-  // fused update (plain Eq. 2): every kernel that completes a parameter gradient applies it at once
-  // to the fp32 master and writes the bf16 rounding into the new weight version `vdst`
-  uint16_t* vdst = s->fused ? (uint16_t*)s->ver[s->upd_dst] : nullptr;
-  // The column sums of a block (bias and LayerNorm-affine gradients) are listed here as their partial
-  // rows come into being.  They go out in one launch at the block's end: with four launches per block,
-  // each behind an event pair of its own, the host was what bounded small stages (12 blocks of d 448 on
-  // 256 tokens, stage step 1.53 -> 1.26 ms; 6 blocks of d 768, 1152 tokens, four microbatches
-  // 6.06 -> 5.84 ms).  A stage whose weight-gradient products leave early (below) sends them along with
-  // those: one launch at the end made the stage step 0.8 % longer at 12 blocks of d 1600, 8192 tokens.
+// The backward of one microbatch, issued block by block from the last: begin, block(L-1) .. block(0), end.
+//
+// Everything that only feeds the parameter gradient - the four weight-gradient products of a
+// block, the reductions behind the bias and LayerNorm gradients, the block's delayed update -
+// is side work: nothing in the chain dy -> dx that the block below waits for reads it.  It
+// goes to a stream of its own and runs beside the next block's chain (measured step time
+// against issuing it in line: d 1024 -7 %, d 2048 -1 %, d 1600 -5 %).
+//
+// The host's part in this: a launch takes 2.7 us to issue, making the side stream wait for the chain 11 us (record 1.5,
+// wait 9 .. 10).  A small stage is bounded by that, so where every block has buffers of its own (deep) the side stream is
+// made to wait once per launch of products, the column sums behind the last LayerNorm of a block ride with those
+// of the next, and no wait guards the reuse of a buffer.  Stage step of 12 blocks of d 448 on 256 tokens 1193 -> 924 us
+// (with forward and backward issued in turn, see rv_dec_step); bounded by the device, 4 blocks of d 1024 on 128 tokens
+// forward and backward 0.70 -> 0.69 ms, on 4096 tokens the same.
+struct Backward {
+  rv_stage* s;
+  const DecPlan& p;
+  const rv_slot& slot;
+  const void* grad_out;
+  void* grad_in;
+  hipStream_t st, ws;          // the chain's stream, the side stream
+  int sh;
+  uint16_t* vdst = nullptr;
+  const uint16_t* dres16 = nullptr;   // bf16 gradient of the current block's output
+  // the side work that has come into being and not left yet
   rv_reduce_job sums[RV_REDUCE_MAX];
-  int n_sums = 0;
-  auto colsum = [&](const float* part, int rows, int64_t pitch, int n, float* dst) {
-    const size_t off = (size_t)(dst - s->grad);
-    sums[n_sums++] = rv_reduce_job{part, !s->fused || s->keep_grad ? dst : nullptr, s->fused ? s->master + off : nullptr,
-                                   s->fused ? vdst + off : nullptr, pitch, rows, n};
-  };
+  rv_gemm_args prods[RV_GEMM_GROUP_MAX];
+  int n_sums = 0, n_prods = 0;
+  bool early = false;
+  int wg_pos[4] = {2, 2, 2, 2};   // dW2, dW1, dWo, dWqkv
+  int whole = 0;                  // blocks below this one (and it) still lack part of their gradient: updates done down to it
 
-  // Everything that only feeds the parameter gradient - the four weight-gradient products of a
-  // block, the reductions behind the bias and LayerNorm gradients, the block's delayed update -
-  // is side work: nothing in the chain dy -> dx that the block below waits for reads it.  It
-  // goes to a stream of its own and runs beside the next block's chain (measured step time
-  // against issuing it in line: d 1024 -7 %, d 2048 -1 %, d 1600 -5 %).  Buffers that
-  // side work reads alternate between blocks (dy: in threes, since block l-1 writes the dy of
-  // block l-2 while the side work of block l still reads its own).
-  hipStream_t ws = s->wgs;
-  auto side_begin = [&]() -> rv_status {
+  Backward(rv_stage* s_, const rv_slot& slot_, const void* go, void* gi, hipStream_t st_)
+      : s(s_), p(*(const DecPlan*)s_->impl), slot(slot_), grad_out(go), grad_in(gi), st(st_), ws(s_->wgs),
+        sh(s_->in_step ? 1 : 0) {}
+
+  uint16_t* dy_buf(int l) const { return (uint16_t*)(s->work + p.w_dy + (size_t)(l % p.dy_sets) * p.dy_bytes); }
+  char* set(int l) const { return s->work + p.w_set + (size_t)(l % p.sets) * p.set_bytes; }
+
+  rv_status side_begin() {
     RV_HIP_TRY(hipEventRecord(s->ev_wg_ready, st));
     RV_HIP_TRY(hipStreamWaitEvent(ws, s->ev_wg_ready, 0));
     return RV_OK;
-  };
-
-  auto send_sums = [&]() -> rv_status {
+  }
+  // The column sums of a block (bias and LayerNorm-affine gradients) are listed as their partial
+  // rows come into being.  fused update (plain Eq. 2): every kernel that completes a parameter gradient applies it at
+  // once to the fp32 master and writes the bf16 rounding into the new weight version `vdst`
+  void colsum(const float* part, int rows, int64_t pitch, int n, float* dst) {
+    const size_t off = (size_t)(dst - s->grad);
+    sums[n_sums++] = rv_reduce_job{part, !s->fused || s->keep_grad ? dst : nullptr, s->fused ? s->master + off : nullptr,
+                                   s->fused ? vdst + off : nullptr, pitch, rows, n};
+  }
+  rv_status send_sums() {
     const int n = n_sums;
     n_sums = 0;
-    return rv_reduce_rows(sums, n, s->eta, ws);
-  };
+    return n ? rv_reduce_rows(sums, n, s->eta, ws) : RV_OK;
+  }
+  rv_status send_prods() {
+    const int n = n_prods;
+    n_prods = 0;
+    if (!n) return RV_OK;
+    if (s->prof_on) {   // measurement aid: bracket the launch with events on its own stream
+      hipEvent_t e0 = nullptr, e1 = nullptr;
+      RV_HIP_TRY(hipEventCreate(&e0));
+      s->prof_ev.push_back(e0);
+      RV_HIP_TRY(hipEventCreate(&e1));
+      s->prof_ev.push_back(e1);
+      RV_HIP_TRY(hipEventRecord(e0, ws));
+      RV_TRY(rv_gemm_wgrad_grouped(prods, n, ws));
+      RV_HIP_TRY(hipEventRecord(e1, ws));
+      return RV_OK;
+    }
+    return rv_gemm_wgrad_grouped(prods, n, ws);
+  }
+  // blocks l .. whole - 1 have their whole gradient: unless the epilogues have applied it already, their delayed update
+  rv_status update_from(int l) {
+    const int n = whole - l;
+    whole = l;
+    if (s->fused || n <= 0) return RV_OK;
+    return rv_stage_update_range(s, (size_t)l * p.per_block, (size_t)n * p.per_block, ws);
+  }
 
-  // gradient of the last block's output: fp32 copy for the residual path, bf16 as operand
-  // (summed over tokens it is also the gradient of the last block's b2: partial sums on the way)
-  float* part_dy = (float*)(s->work + p.w_part_dy);
-  const uint16_t* dres16 = (const uint16_t*)grad_out;
-  if (rv_overlap(grad_out, (size_t)T * d * 2, grad_in, (size_t)T * d * 2)) {
-    // the first block's backward writes grad_in without waiting for the side stream, where the last block's dW2
-    // still reads the arriving gradient: that goes to its place among the gradients of the other blocks first
-    uint16_t* dy = (uint16_t*)(s->work + p.w_dy[(p.L - 1) % 3]);
-    RV_HIP_TRY(hipMemcpyAsync(dy, grad_out, (size_t)T * d * 2, hipMemcpyDeviceToDevice, st));
-    dres16 = dy;
+  rv_status begin() {
+    vdst = s->fused ? (uint16_t*)s->ver[s->upd_dst] : nullptr;
+    whole = p.L;
+    const int T = p.T, d = p.d;
+    // gradient of the last block's output: fp32 copy for the residual path, bf16 as operand
+    // (summed over tokens it is also the gradient of the last block's b2: partial sums on the way)
+    float* part_dy = (float*)(s->work + p.w_part_dy);
+    dres16 = (const uint16_t*)grad_out;
+    if (rv_overlap(grad_out, (size_t)T * d * 2, grad_in, (size_t)T * d * 2)) {
+      // the first block's backward writes grad_in without waiting for the side stream, where the last block's dW2
+      // still reads the arriving gradient: that goes to its place among the gradients of the other blocks first
+      uint16_t* dy = dy_buf(p.L - 1);
+      RV_HIP_TRY(hipMemcpyAsync(dy, grad_out, (size_t)T * d * 2, hipMemcpyDeviceToDevice, st));
+      dres16 = dy;
+    }
+    RV_TRY(rv_widen_colsum(dres16, (float*)(s->work + p.w_dres), part_dy, T, d, st));
+    colsum(part_dy, rv_widen_parts(T), d, d, s->grad + (size_t)(p.L - 1) * p.per_block + p.b2);
+    // When the four weight-gradient products of a block go to the side stream.  Launch points:
+    // 0 behind the GELU' product (dz exists: dW2 and dW1 can run), 1 behind the second LayerNorm's
+    // backward (dx1 exists: dWo), 2 behind the attention backward (dqkv exists: all four).  One
+    // launch of all four at point 2 is the least launch work; going out earlier puts the products
+    // beside the chain's LayerNorm and attention kernels instead of beside its next products.
+    // Measured step time against the single launch, tiles of 256 x 256 on 256 CUs:
+    //   dW2 + dW1 at point 0, dWo + dWqkv at point 2:  -4.7 % where they are 512 and 256 tiles
+    //   (d 2048, ffn 8192), 0 % at 350 and 182 tiles (d 1600, ffn 6400), +1.3 % at 128 and 64 tiles
+    //   (d 1024, ffn 4096);
+    //   dWo on its own at point 1 as well:  -2.8 %, -1.2 %, +7 % in the same order.
+    // So: the feed-forward pair goes out early when it fills the chip at least once, and dWo leaves
+    // dWqkv only when the two together are not a whole number of rounds anyway.  (All four behind the
+    // first LayerNorm's backward, one event pair less per block: +4 % at d 2048, d 1024 and 6 blocks of
+    // d 768 on 1152 tokens.)
+    const int kCUs = 256;
+    auto tiles = [](int M, int N) { return ((M + 255) / 256) * ((N + 255) / 256); };
+    const int n_ffn = 2 * tiles(p.d, p.f), n_o = tiles(p.d, p.d), n_qkv = tiles(p.d, 3 * p.d);
+    early = n_ffn >= kCUs;
+    if (early) {
+      wg_pos[0] = wg_pos[1] = 0;
+      if (!p.deep && (n_o + n_qkv) % kCUs != 0) wg_pos[2] = 1;
+    }
+    return RV_OK;
   }
-  RV_TRY(rv_widen_colsum(dres16, dres, part_dy, T, d, st));
-  colsum(part_dy, rv_widen_parts(T), d, d, s->grad + (size_t)(p.L - 1) * p.per_block + p.b2);
-  // When the four weight-gradient products of a block go to the side stream.  Launch points:
-  // 0 behind the GELU' product (dz exists: dW2 and dW1 can run), 1 behind the second LayerNorm's
-  // backward (dx1 exists: dWo), 2 behind the attention backward (dqkv exists: all four).  One
-  // launch of all four at point 2 is the least launch work; going out earlier puts the products
-  // beside the chain's LayerNorm and attention kernels instead of beside its next products.
-  // Measured step time against the single launch, tiles of 256 x 256 on 256 CUs:
-  //   dW2 + dW1 at point 0, dWo + dWqkv at point 2:  -4.7 % where they are 512 and 256 tiles
-  //   (d 2048, ffn 8192), 0 % at 350 and 182 tiles (d 1600, ffn 6400), +1.3 % at 128 and 64 tiles
-  //   (d 1024, ffn 4096);
-  //   dWo on its own at point 1 as well:  -2.8 %, -1.2 %, +7 % in the same order.
-  // So: the feed-forward pair goes out early when it fills the chip at least once, and dWo leaves
-  // dWqkv only when the two together are not a whole number of rounds anyway.  (All four behind the
-  // first LayerNorm's backward, one event pair less per block: +4 % at d 2048, d 1024 and 6 blocks of
-  // d 768 on 1152 tokens, -5 % only at 12 blocks of d 448 on 256 tokens, where the host is the limit.)
-  const int kCUs = 256;
-  auto tiles = [](int M, int N) { return ((M + 255) / 256) * ((N + 255) / 256); };
-  const int n_ffn = 2 * tiles(d, f), n_o = tiles(d, d), n_qkv = tiles(d, 3 * d);
-  int wg_pos[4] = {2, 2, 2, 2};   // dW2, dW1, dWo, dWqkv
-  const bool early = n_ffn >= kCUs;
-  if (early) {
-    wg_pos[0] = wg_pos[1] = 0;
-    if ((n_o + n_qkv) % kCUs != 0) wg_pos[2] = 1;
-  }
-  for (int l = p.L - 1; l >= 0; --l) {
-    const int par = l & 1;
+
+  rv_status block(int l) {
+    const int T = p.T, d = p.d, f = p.f, par = l & 1;
+    float* dres = (float*)(s->work + p.w_dres);
+    uint16_t* dtmp = (uint16_t*)(s->work + p.w_dtmp);
+    float* Dbuf = (float*)(s->work + p.w_D);
+    const int ln_rows = rv_ln_bwd_rows(T, d), ln_parts = rv_ln_bwd_parts(T, d);
     // block l may overwrite what the side work of block l+2 read only after that is done
-    if (l + 2 < p.L) RV_HIP_TRY(hipStreamWaitEvent(st, s->ev_wg_done[par], 0));
-    uint16_t* dx1_16 = (uint16_t*)(s->work + p.w_dx1_16[par]);   // bf16 dx1 of this block
-    uint16_t* dz = (uint16_t*)(s->work + p.w_dz[par]);
-    uint16_t* dqkv = (uint16_t*)(s->work + p.w_dqkv[par]);
-    uint16_t* dy_below = (uint16_t*)(s->work + p.w_dy[(l + 2) % 3]);   // = slot (l-1) mod 3
-    float* part2 = (float*)(s->work + p.w_part_ln[par][0]);      // LayerNorm 2 / 1 partial sums
-    float* part1 = (float*)(s->work + p.w_part_ln[par][1]);
-    const uint16_t* w = wv + (size_t)l * p.per_block;
+    if (!p.deep && l + 2 < p.L) RV_HIP_TRY(hipStreamWaitEvent(st, s->ev_wg_done[par], 0));
+    char* set_l = set(l);
+    uint16_t* dx1_16 = (uint16_t*)(set_l + p.o_dx1_16);          // bf16 dx1 of this block
+    uint16_t* dz = (uint16_t*)(set_l + p.o_dz);
+    uint16_t* dqkv = (uint16_t*)(set_l + p.o_dqkv);
+    float* part2 = (float*)(set_l + p.o_part_ln[0]);             // LayerNorm 2 / 1 partial sums
+    float* part1 = (float*)(set_l + p.o_part_ln[1]);
+    const uint16_t* w = (const uint16_t*)s->ver[slot.ver] + (size_t)l * p.per_block;
     float* gl = s->grad + (size_t)l * p.per_block;
     const char* sb = slot.base + (size_t)l * p.blk_bytes;
     const float* x = (const float*)(sb + p.s_x);
@@ -259,27 +320,6 @@ rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
     const uint16_t* z = (const uint16_t*)(sb + p.s_z);
     const uint16_t* g = (const uint16_t*)(sb + p.s_g);
     rv_gemm_args wg[4];
-    // the weight-gradient products whose launch point is `pos` go out as one grouped launch
-    auto side_launch = [&](int pos) -> rv_status {
-      rv_gemm_args grp[4];
-      int n = 0;
-      for (int k = 0; k < 4; ++k)
-        if (wg_pos[k] == pos) grp[n++] = wg[k];
-      if (!n) return RV_OK;
-      if (pos != 1) RV_TRY(side_begin());   // (at 1 the side stream already waits for the LayerNorm backward)
-      if (s->prof_on) {   // measurement aid: bracket the launch with events on its own stream
-        hipEvent_t e0 = nullptr, e1 = nullptr;
-        RV_HIP_TRY(hipEventCreate(&e0));
-        s->prof_ev.push_back(e0);
-        RV_HIP_TRY(hipEventCreate(&e1));
-        s->prof_ev.push_back(e1);
-        RV_HIP_TRY(hipEventRecord(e0, ws));
-        RV_TRY(rv_gemm_wgrad_grouped(grp, n, ws));
-        RV_HIP_TRY(hipEventRecord(e1, ws));
-        return RV_OK;
-      }
-      return rv_gemm_wgrad_grouped(grp, n, ws);
-    };
     auto wgrad = [&](int k, const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, int M, int N, float* out) {
       wg[k].A = A; wg[k].lda = lda; wg[k].a_kmajor = 1; wg[k].B = B; wg[k].ldb = ldb; wg[k].b_kmajor = 1;
       wg[k].M = M; wg[k].N = N; wg[k].K = T; wg[k].epi = RV_EPI_F32; wg[k].out = out; wg[k].ldo = N;
@@ -289,57 +329,110 @@ rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
         wg[k].store_out = s->keep_grad;
       }
     };
+    // the weight-gradient products whose launch point is `pos` join the list
+    auto take = [&](int pos) {
+      for (int k = 0; k < 4; ++k)
+        if (wg_pos[k] == pos) prods[n_prods++] = wg[k];
+    };
+    // Where the listed side work leaves.  One buffer set per block: the products at points 0 and 2 (2 of every group-th
+    // block where the group has several), each time with the sums listed so far - a block's last sums with the
+    // next launch.  Alternating sets: the products as above, the sums of a block in one launch at its end (with four
+    // launches per block, each behind an event pair of its own, the host bounded small stages), or along with the
+    // products where those leave early (one launch at the end made the stage step 0.8 % longer at 12 blocks of
+    // d 1600, 8192 tokens).
+    const bool leaves = !p.deep || l % p.group == 0;
     // feed-forward half
     wgrad(0, g, f, dres16, d, f, d, gl + p.w2);                                                      // dW2 = g^T dy
     // dz = (dy W2^T) * GELU'(z); its column sums (the b1 gradient) leave the same epilogue as partial rows
-    float* part_dz = (float*)(s->work + p.w_part_dz[par]);
+    float* part_dz = (float*)(set_l + p.o_part_dz);
     int dz_parts = 0;
     RV_TRY(gemm(sh, st, dres16, d, 0, w + p.w2, d, 0, T, f, d, RV_EPI_BF16_DGELU, dz, f, nullptr, nullptr, nullptr, z,
                 part_dz, &dz_parts));
     wgrad(1, v2, d, dz, f, d, f, gl + p.w1);                                                         // dW1 = v2^T dz
-    RV_TRY(side_launch(0));
     colsum(part_dz, dz_parts, f, f, gl + p.b1);
-    if (early) RV_TRY(send_sums());
+    take(0);
+    if (early && leaves) {
+      RV_TRY(side_begin());
+      RV_TRY(send_prods());
+      RV_TRY(send_sums());
+      if (p.deep) RV_TRY(update_from(l + 1));
+    }
     RV_TRY(gemm(sh, st, dz, f, 0, w + p.w1, f, 0, T, d, f, RV_EPI_BF16, dtmp, d));                       // dv2 = dz W1^T
     RV_TRY(rv_ln_bwd(dtmp, x1, (const float*)(sb + p.s_m2), (const float*)(sb + p.s_r2), w + p.ln2g, dres, dres,
                      dx1_16, part2, T, d, st, ln_rows));
     colsum(part2, ln_parts, 3 * (int64_t)d, d, gl + p.ln2g);
     colsum(part2 + d, ln_parts, 3 * (int64_t)d, d, gl + p.ln2b);
     colsum(part2 + 2 * d, ln_parts, 3 * (int64_t)d, d, gl + p.bo);                                     // dbo = sum dx1
-    if (early) {
-      RV_TRY(side_begin());
-      RV_TRY(send_sums());
-    }
     // attention half
     wgrad(2, a, d, dx1_16, d, d, d, gl + p.wo);                                                      // dWo = a^T dx1
-    RV_TRY(side_launch(1));
+    take(1);
+    if (early && !p.deep) {
+      RV_TRY(side_begin());
+      RV_TRY(send_sums());
+      RV_TRY(send_prods());
+    }
     RV_TRY(gemm(sh, st, dx1_16, d, 0, w + p.wo, d, 0, T, d, d, RV_EPI_BF16, dtmp, d));                   // da = dx1 Wo^T
     // (the attention backward also leaves partial column sums of dqkv: the qkv bias gradient)
-    float* part_qkv = (float*)(s->work + p.w_part_qkv[par]);
+    float* part_qkv = (float*)(set_l + p.o_part_qkv);
     RV_TRY(rv_attn_bwd(qkv, a, dtmp, (const float*)(sb + p.s_lse), Dbuf, dqkv, p.mb, p.S, d, p.H, st, part_qkv));
     wgrad(3, u, d, dqkv, 3 * d, d, 3 * d, gl + p.wqkv);                                              // dWqkv = u^T dqkv
-    RV_TRY(side_launch(2));
     colsum(part_qkv, rv_attn_colsum_parts(p.mb, p.S), 3 * d, 3 * d, gl + p.bqkv);
-    if (early) RV_TRY(send_sums());
+    take(2);
+    if (leaves) {
+      RV_TRY(side_begin());
+      RV_TRY(send_prods());
+      if (early || p.deep) RV_TRY(send_sums());
+      if (p.deep) RV_TRY(update_from(l + 1));   // (block l lacks what its last LayerNorm gives)
+    }
     RV_TRY(gemm(sh, st, dqkv, 3 * d, 0, w + p.wqkv, 3 * d, 0, T, d, 3 * d, RV_EPI_BF16, dtmp, d));       // du
-    uint16_t* dx16 = l == 0 ? (uint16_t*)grad_in : dy_below;
-    RV_TRY(rv_ln_bwd(dtmp, x, (const float*)(sb + p.s_m1), (const float*)(sb + p.s_r1), w + p.ln1g, dres, dres, dx16,
-                     part1, T, d, st, ln_rows));
+    uint16_t* dy_below = l > 0 ? dy_buf(l - 1) : nullptr;
+    RV_TRY(rv_ln_bwd(dtmp, x, (const float*)(sb + p.s_m1), (const float*)(sb + p.s_r1), w + p.ln1g, dres, dres,
+                     l == 0 ? (uint16_t*)grad_in : dy_below, part1, T, d, st, ln_rows));
     colsum(part1, ln_parts, 3 * (int64_t)d, d, gl + p.ln1g);
     colsum(part1 + d, ln_parts, 3 * (int64_t)d, d, gl + p.ln1b);
     // the residual gradient leaving this block is dy of the block below: its b2 gradient
     if (l > 0) colsum(part1 + 2 * d, ln_parts, 3 * (int64_t)d, d, s->grad + (size_t)(l - 1) * p.per_block + p.b2);
+    dres16 = dy_below;
+    if (p.deep && l > 0) return RV_OK;
     RV_TRY(side_begin());
     RV_TRY(send_sums());
-    // every gradient of block l is complete behind this point of `ws` (its b2 gradient came
-    // from the block above); unless the epilogues above have applied it already, the delayed
-    // update of the block follows at once
-    if (!s->fused) RV_TRY(rv_stage_update_range(s, (size_t)l * p.per_block, p.per_block, ws));
+    // every gradient of block l is complete behind this point of `ws` (its b2 gradient came from the block above)
+    RV_TRY(update_from(l));
     RV_HIP_TRY(hipEventRecord(s->ev_wg_done[par], ws));
-    dres16 = dy_below;               // dy of the block below
+    return RV_OK;
   }
-  // the caller's stream (and with it the update) continues behind the last side work
-  RV_HIP_TRY(hipStreamWaitEvent(st, s->ev_wg_done[0], 0));
-  if (p.L > 1) RV_HIP_TRY(hipStreamWaitEvent(st, s->ev_wg_done[1], 0));
+
+  // the chain's stream (and with it the caller's) continues behind the last side work
+  rv_status end() {
+    RV_HIP_TRY(hipStreamWaitEvent(st, s->ev_wg_done[0], 0));
+    if (!p.deep && p.L > 1) RV_HIP_TRY(hipStreamWaitEvent(st, s->ev_wg_done[1], 0));
+    return RV_OK;
+  }
+};
+
+}  // namespace
+
+rv_status rv_dec_forward(rv_stage* s, rv_slot& slot, const void* in, void* out) {
+  const int L = ((const DecPlan*)s->impl)->L;
+  for (int l = 0; l < L; ++l) RV_TRY(forward_block(s, slot, in, out, l, s->st));
   return RV_OK;
+}
+
+rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void* grad_in) {
+  Backward b(s, slot, grad_out, grad_in, s->st);
+  RV_TRY(b.begin());
+  for (int l = b.p.L - 1; l >= 0; --l) RV_TRY(b.block(l));
+  return b.end();
+}
+
+// A forward on the stage's stream beside a backward on the auxiliary one, issued in turn block by block: the backward is
+// the longer chain, and behind a whole forward its first launch would wait for as long as that takes to issue.
+rv_status rv_dec_step(rv_stage* s, rv_slot& fwd, const void* in, void* out, rv_slot& bwd, const void* grad_out, void* grad_in) {
+  Backward b(s, bwd, grad_out, grad_in, s->aux);
+  RV_TRY(b.begin());
+  for (int l = 0; l < b.p.L; ++l) {
+    RV_TRY(b.block(b.p.L - 1 - l));
+    RV_TRY(forward_block(s, fwd, in, out, l, s->st));
+  }
+  return b.end();
 }

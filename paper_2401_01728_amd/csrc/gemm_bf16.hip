@@ -1003,13 +1003,15 @@ struct GroupedProblem {
   float* upd_w; uint16_t* upd_ver; float eta;
   int lda, ldb, ldo, M, N, K, tiles_m, tiles_n, first_tile;
 };
+template <int MAX>
 struct GroupedArgs {
-  GroupedProblem p[RV_GEMM_GROUP_MAX];
+  GroupedProblem p[MAX];
   int count;
 };
 
 // the problem, tile row and tile column of a workgroup
-__device__ __forceinline__ const GroupedProblem& grouped_tile(const GroupedArgs& ga, int& bm, int& bn) {
+template <int MAX>
+__device__ __forceinline__ const GroupedProblem& grouped_tile(const GroupedArgs<MAX>& ga, int& bm, int& bn) {
   // Workgroup ids are dealt to the 8 XCDs in turn, and each XCD pulls its operand panels
   // through its own L2.  Give XCD g a CONTIGUOUS range of the tile numbering (so it works on
   // one problem at a time, not on a slice of all of them) and number a problem's tiles in bands
@@ -1019,7 +1021,7 @@ __device__ __forceinline__ const GroupedProblem& grouped_tile(const GroupedArgs&
   const int v = g * base + (g < rem ? g : rem) + i;
   int pi = 0;
 #pragma unroll
-  for (int k = 1; k < RV_GEMM_GROUP_MAX; ++k)
+  for (int k = 1; k < MAX; ++k)
     if (k < ga.count && v >= ga.p[k].first_tile) pi = k;
   const GroupedProblem& q = ga.p[pi];
   const int local = v - q.first_tile;
@@ -1036,13 +1038,13 @@ __device__ __forceinline__ Epi grouped_epi(const GroupedProblem& q) {
 }
 
 template <int BM, int BN, int BK, int NS, int NW, int WPE>
-__global__ __launch_bounds__(64 * NW, WPE) void gemm_dtl_grouped_wgrad_kernel(GroupedArgs ga) {
+__global__ __launch_bounds__(64 * NW, WPE) void gemm_dtl_grouped_wgrad_kernel(GroupedArgs<RV_GEMM_GROUP_BLOCK> ga) {
   int bm, bn;
   const GroupedProblem& q = grouped_tile(ga, bm, bn);
   gemm_dtl_body<BM, BN, BK, NS, NW, true, true, EPI_F32_UPD>(q.A, q.lda, q.B, q.ldb, q.M, q.N, q.K, bm, bn, grouped_epi(q));
 }
-template <int BM, int BN, int G, int NW, int NS>
-__global__ __launch_bounds__(64 * NW * G, NW * G / 4) void gemm_split_grouped_wgrad_kernel(GroupedArgs ga) {
+template <int BM, int BN, int G, int NW, int NS, int MAX>
+__global__ __launch_bounds__(64 * NW * G, NW * G / 4) void gemm_split_grouped_wgrad_kernel(GroupedArgs<MAX> ga) {
   int bm, bn;
   const GroupedProblem& q = grouped_tile(ga, bm, bn);
   gemm_split_body<BM, BN, G, NW, NS, true, true, EPI_F32_UPD>(q.A, q.lda, q.B, q.ldb, q.M, q.N, q.K, bm, bn, grouped_epi(q));
@@ -1209,9 +1211,10 @@ rv_status rv_gemm_bf16(const rv_gemm_args& g, hipStream_t st) {
 }
 
 namespace {
-rv_status launch_grouped(void (*kern)(GroupedArgs), int BM, int BN, int threads, int smem, const rv_gemm_args* gs, int count,
+template <int MAX>
+rv_status launch_grouped(void (*kern)(GroupedArgs<MAX>), int BM, int BN, int threads, int smem, const rv_gemm_args* gs, int count,
                          hipStream_t st) {
-  GroupedArgs ga;
+  GroupedArgs<MAX> ga;
   int tiles = 0;
   for (int k = 0; k < count; ++k) {
     const rv_gemm_args& g = gs[k];
@@ -1224,7 +1227,7 @@ rv_status launch_grouped(void (*kern)(GroupedArgs), int BM, int BN, int threads,
     q.first_tile = tiles;
     tiles += q.tiles_m * q.tiles_n;
   }
-  for (int k = count; k < RV_GEMM_GROUP_MAX; ++k) ga.p[k] = ga.p[0];
+  for (int k = count; k < MAX; ++k) ga.p[k] = ga.p[0];
   ga.count = count;
   hipLaunchKernelGGL(kern, dim3(tiles), dim3(threads), smem, st, ga);
   return rv_launch_status();
@@ -1240,11 +1243,11 @@ rv_status launch_grouped_dtl(const rv_gemm_args* gs, int count, hipStream_t st) 
   if (configured != hipSuccess) return RV_E_DEVICE;
   return launch_grouped(kern, BM, BN, 64 * NW, smem, gs, count, st);
 }
-template <int BM, int BN, int G, int NW, int NS>
+template <int BM, int BN, int G, int NW, int NS, int MAX>
 rv_status launch_grouped_split(const rv_gemm_args* gs, int count, hipStream_t st) {
   constexpr int smem = split_lds<BM, BN, G, NS>();
   static_assert(smem <= 160 * 1024, "LDS of one CU");
-  auto kern = gemm_split_grouped_wgrad_kernel<BM, BN, G, NW, NS>;
+  auto kern = gemm_split_grouped_wgrad_kernel<BM, BN, G, NW, NS, MAX>;
   static const hipError_t configured =
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   if (configured != hipSuccess) return RV_E_DEVICE;
@@ -1253,7 +1256,8 @@ rv_status launch_grouped_split(const rv_gemm_args* gs, int count, hipStream_t st
 }  // namespace
 
 rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t st, bool in_order) {
-  if (!gs || count < 1 || count > RV_GEMM_GROUP_MAX) return RV_E_INVAL;
+  if (!gs || count < 1 || count > (in_order ? RV_GEMM_GROUP_BLOCK : RV_GEMM_GROUP_MAX)) return RV_E_INVAL;
+  if (count > RV_GEMM_GROUP_BLOCK && gs[0].K >= RV_WGRAD_SPLIT_K) return RV_E_INVAL;
   for (int k = 0; k < count; ++k) {
     const rv_gemm_args& g = gs[k];
     if (!g.A || !g.B || !g.out || !g.a_kmajor || !g.b_kmajor || g.epi != EPI_F32) return RV_E_INVAL;
@@ -1280,7 +1284,8 @@ rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t s
   if (!in_order) {
     int tiles = 0;
     for (int k = 0; k < count; ++k) tiles += ((gs[k].M + 255) / 256) * ((gs[k].N + 255) / 256);
-    if (tiles < 256 && gs[0].K < 2048) return launch_grouped_split<128, 128, 2, 4, 4>(gs, count, st);
+    if (count > RV_GEMM_GROUP_BLOCK) return launch_grouped_split<128, 128, 2, 4, 4, RV_GEMM_GROUP_MAX>(gs, count, st);
+    if (tiles < 256 && gs[0].K < RV_WGRAD_SPLIT_K) return launch_grouped_split<128, 128, 2, 4, 4, RV_GEMM_GROUP_BLOCK>(gs, count, st);
   }
   return launch_grouped_dtl<256, 256, 32, 4, 8>(gs, count, st);
 }
@@ -1300,8 +1305,8 @@ extern "C" rv_status rv_k_gemm_bf16(const void* A, int64_t lda, int a_kmajor, co
 extern "C" rv_status rv_k_gemm_wgrad_grouped(int count, const void* const* X, const int64_t* lda,
                                              const void* const* dY, const int64_t* ldb, const int* M, const int* N,
                                              int K, float* const* dW, void* stream) {
-  if (count < 1 || count > RV_GEMM_GROUP_MAX || !X || !lda || !dY || !ldb || !M || !N || !dW) return RV_E_INVAL;
-  rv_gemm_args g[RV_GEMM_GROUP_MAX];
+  if (count < 1 || count > RV_GEMM_GROUP_BLOCK || !X || !lda || !dY || !ldb || !M || !N || !dW) return RV_E_INVAL;
+  rv_gemm_args g[RV_GEMM_GROUP_BLOCK];
   for (int k = 0; k < count; ++k) {
     g[k].A = (const uint16_t*)X[k]; g[k].lda = lda[k]; g[k].a_kmajor = 1;
     g[k].B = (const uint16_t*)dY[k]; g[k].ldb = ldb[k]; g[k].b_kmajor = 1;
@@ -1313,8 +1318,8 @@ extern "C" rv_status rv_k_gemm_wgrad_grouped(int count, const void* const* X, co
 extern "C" rv_status rv_k_gemm_wgrad_update(int count, const void* const* X, const int64_t* lda, const void* const* dY,
                                             const int64_t* ldb, const int* M, const int* N, int K, float* const* dW,
                                             float* const* w, void* const* ver, float eta, void* stream) {
-  if (count < 1 || count > RV_GEMM_GROUP_MAX || !X || !lda || !dY || !ldb || !M || !N || (!dW && !w) || !w != !ver) return RV_E_INVAL;
-  rv_gemm_args g[RV_GEMM_GROUP_MAX];
+  if (count < 1 || count > RV_GEMM_GROUP_BLOCK || !X || !lda || !dY || !ldb || !M || !N || (!dW && !w) || !w != !ver) return RV_E_INVAL;
+  rv_gemm_args g[RV_GEMM_GROUP_BLOCK];
   for (int k = 0; k < count; ++k) {
     g[k].A = (const uint16_t*)X[k]; g[k].lda = lda[k]; g[k].a_kmajor = 1;
     g[k].B = (const uint16_t*)dY[k]; g[k].ldb = ldb[k]; g[k].b_kmajor = 1;

@@ -55,8 +55,11 @@ struct rv_gemm_args {
   bool store_out = true;
 };
 rv_status rv_gemm_bf16(const rv_gemm_args& g, hipStream_t st);
-// up to RV_GEMM_GROUP_MAX weight-gradient products (both operands k-major, fp32 output) in one launch
-#define RV_GEMM_GROUP_MAX 4
+// up to RV_GEMM_GROUP_MAX weight-gradient products (both operands k-major, fp32 output) in one launch; more than the four
+// of one block only with contractions shorter than RV_WGRAD_SPLIT_K (the tiles whose contraction is split)
+#define RV_GEMM_GROUP_BLOCK 4
+#define RV_GEMM_GROUP_MAX 16
+#define RV_WGRAD_SPLIT_K 2048
 rv_status rv_stage_update_range(rv_stage* s, size_t off, size_t n, hipStream_t st);
 // in_order: every product summed in order of k, as rv_gemm_bf16 with tile 5256 does; otherwise small
 // blocks take tiles whose contraction is split
@@ -77,7 +80,7 @@ rv_status rv_widen_colsum(const uint16_t* a, float* o, float* part, int T, int d
 // out[c] = sum_r src[r * pitch + c] for r < R, c < N, each job of a list in the same launch.  w (may be
 // null) with ver: the fp32 master vector and the bf16 weight-version vector the column sums update,
 // w <- w - eta * sum (Eq. 2); out null: the sums themselves are not written.
-#define RV_REDUCE_MAX 9
+#define RV_REDUCE_MAX 36
 struct rv_reduce_job {
   const float* src;
   float* out;
@@ -172,3 +175,4 @@ rv_status rv_dec_plan(rv_stage* s);
 void rv_dec_free(rv_stage* s);
 rv_status rv_dec_forward(rv_stage* s, rv_slot& slot, const void* in, void* out);
 rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void* grad_in);
+rv_status rv_dec_step(rv_stage* s, rv_slot& fwd, const void* in, void* out, rv_slot& bwd, const void* grad_out, void* grad_in);

@@ -462,17 +462,20 @@ __global__ __launch_bounds__(kThreads) void widen_colsum_kernel(const uint16_t* 
 // out_k[c] = sum_r src_k[r * pitch_k + c] for a list of jobs in one launch.  32 columns x 8 row lanes
 // per workgroup, a job's workgroups next to each other; every row lane adds its rows in order, the
 // eight partial sums are combined in a fixed order.  A launch is a few microseconds however small, so
-// what counts is how many there are: all the sums of a decoder block go out together (see rv_dec_backward).
+// what counts is how many there are: all the sums of a decoder block, or of a few, go out together (decoder.hip).
+constexpr int kReduceBlock = 9;   // a block's worth
+template <int MAX>
 struct ReduceJobs {
-  rv_reduce_job j[RV_REDUCE_MAX];
-  int first[RV_REDUCE_MAX];   // first workgroup of the job; beyond the last job: past the grid
+  rv_reduce_job j[MAX];
+  int first[MAX];   // first workgroup of the job; beyond the last job: past the grid
   float eta;
 };
-__global__ __launch_bounds__(kThreads) void reduce_rows_kernel(ReduceJobs jobs) {
+template <int MAX>
+__global__ __launch_bounds__(kThreads) void reduce_rows_kernel(ReduceJobs<MAX> jobs) {
   __shared__ float red[8][33];
   int ji = 0;
 #pragma unroll
-  for (int k = 1; k < RV_REDUCE_MAX; ++k)
+  for (int k = 1; k < MAX; ++k)
     if ((int)blockIdx.x >= jobs.first[k]) ji = k;
   const rv_reduce_job& job = jobs.j[ji];
   const float* __restrict__ src = job.src;
@@ -595,9 +598,10 @@ rv_status rv_widen_colsum(const uint16_t* a, float* o, float* part, int T, int d
   return rv_launch_status();
 }
 
-rv_status rv_reduce_rows(const rv_reduce_job* jobs, int njobs, float eta, hipStream_t st) {
-  if (!jobs || njobs < 1 || njobs > RV_REDUCE_MAX) return RV_E_INVAL;
-  ReduceJobs a = {};
+namespace {
+template <int MAX>
+rv_status launch_reduce(const rv_reduce_job* jobs, int njobs, float eta, hipStream_t st) {
+  ReduceJobs<MAX> a = {};
   a.eta = eta;
   int groups = 0;
   for (int k = 0; k < njobs; ++k) {
@@ -607,9 +611,15 @@ rv_status rv_reduce_rows(const rv_reduce_job* jobs, int njobs, float eta, hipStr
     a.first[k] = groups;
     groups += (j.N + 31) / 32;
   }
-  for (int k = njobs; k < RV_REDUCE_MAX; ++k) a.first[k] = groups;
-  hipLaunchKernelGGL(reduce_rows_kernel, dim3(groups), dim3(kThreads), 0, st, a);
+  for (int k = njobs; k < MAX; ++k) a.first[k] = groups;
+  hipLaunchKernelGGL(reduce_rows_kernel<MAX>, dim3(groups), dim3(kThreads), 0, st, a);
   return rv_launch_status();
+}
+}  // namespace
+
+rv_status rv_reduce_rows(const rv_reduce_job* jobs, int njobs, float eta, hipStream_t st) {
+  if (!jobs || njobs < 1 || njobs > RV_REDUCE_MAX) return RV_E_INVAL;
+  return njobs <= kReduceBlock ? launch_reduce<kReduceBlock>(jobs, njobs, eta, st) : launch_reduce<RV_REDUCE_MAX>(jobs, njobs, eta, st);
 }
 
 extern "C" rv_status rv_k_layernorm_fwd(const void* x, int x_is_bf16, float* xcopy, const void* gamma,

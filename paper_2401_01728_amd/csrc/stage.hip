@@ -290,31 +290,41 @@ rv_status rv_stage_update_range(rv_stage* s, size_t off, size_t n, hipStream_t s
 
 namespace {
 
-// forward branch: bind to a free slot and the newest version, enqueue on s->st
-rv_status do_forward(rv_stage* s, int64_t mb_id, const void* in, void* out) {
+// forward branch: bind to a free slot and the newest version
+rv_status admit_forward(rv_stage* s, int64_t mb_id, rv_slot** slot) {
   int free_i = -1;
   for (size_t i = 0; i < s->slots.size(); ++i)
     if (!s->slots[i].live) { free_i = (int)i; break; }
   if (free_i < 0) return RV_E_STASH_FULL;
   rv_slot& sl = s->slots[free_i];
   sl.ver = s->cur;
-  rv_status rc = s->kind == RV_MLP ? rv_mlp_forward(s, sl, in, out) : rv_dec_forward(s, sl, in, out);
-  if (rc != RV_OK) { sl.ver = -1; return rc; }
   sl.live = true; sl.mb = mb_id;
   s->ver_ref[s->cur] += 1;
+  *slot = &sl;
   return RV_OK;
 }
+void release(rv_stage* s, rv_slot& sl) {
+  s->ver_ref[sl.ver] -= 1;
+  sl.live = false; sl.ver = -1;
+}
 
-// backward branch + update, enqueued on s->st
-rv_status do_backward(rv_stage* s, int slot_i, const void* grad_out, void* grad_in) {
-  rv_slot& sl = s->slots[slot_i];
-  // The updated block is published as a new version in a slot that no in-flight microbatch is
-  // bound to - not even this one, whose version the backward is still reading while the first
-  // pieces of the new one are written (tau+2 slots, at most tau+1 of them referenced).  The slot
-  // is chosen before the backward so that a stage kind may update layer by layer as the
-  // gradients complete.  With gradient accumulation only the last microbatch of a group
-  // updates; the others leave the current version in force.
-  const bool updates = !s->defer && s->acc_count + 1 >= s->accum;
+rv_status do_forward(rv_stage* s, int64_t mb_id, const void* in, void* out) {
+  rv_slot* sl = nullptr;
+  RV_TRY(admit_forward(s, mb_id, &sl));
+  const rv_status rc = s->kind == RV_MLP ? rv_mlp_forward(s, *sl, in, out) : rv_dec_forward(s, *sl, in, out);
+  if (rc != RV_OK) release(s, *sl);
+  return rc;
+}
+
+// The updated block is published as a new version in a slot that no in-flight microbatch is
+// bound to - not even the one whose backward runs, which reads its version while the first
+// pieces of the new one are written (tau+2 slots, at most tau+1 of them referenced).  The slot
+// is chosen before the backward so that a stage kind may update layer by layer as the
+// gradients complete.  With gradient accumulation only the last microbatch of a group
+// updates; the others leave the current version in force.
+bool backward_updates(const rv_stage* s) { return !s->defer && s->acc_count + 1 >= s->accum; }
+rv_status admit_backward(rv_stage* s) {
+  const bool updates = backward_updates(s);
   int dst = -1;
   if (updates) {
     for (size_t v = 0; dst < 0 && v < s->ver.size(); ++v)
@@ -326,6 +336,20 @@ rv_status do_backward(rv_stage* s, int slot_i, const void* grad_out, void* grad_
   // separate update kernels.
   s->fused = updates && s->accum == 1 && (s->kind == RV_MLP || !s->vel);
   s->upd_dst = dst;
+  return RV_OK;
+}
+void finish_backward(rv_stage* s, rv_slot& sl) {
+  const bool updates = backward_updates(s);
+  s->grad_valid = s->kind == RV_MLP || !s->fused || s->keep_grad;
+  release(s, sl);
+  if (updates) { s->cur = s->upd_dst; s->acc_count = 0; }
+  else if (!s->defer) s->acc_count += 1;
+}
+
+// backward branch + update, enqueued on s->st
+rv_status do_backward(rv_stage* s, int slot_i, const void* grad_out, void* grad_in) {
+  rv_slot& sl = s->slots[slot_i];
+  RV_TRY(admit_backward(s));
   rv_status rc;
   if (s->kind == RV_MLP) {
     rc = rv_mlp_backward(s, sl, grad_out, grad_in);
@@ -334,12 +358,26 @@ rv_status do_backward(rv_stage* s, int slot_i, const void* grad_out, void* grad_
     rc = rv_dec_backward(s, sl, grad_out, grad_in);   // updates block by block
   }
   if (rc != RV_OK) return rc;   // (a failed launch leaves the stage unusable)
-  s->grad_valid = s->kind == RV_MLP || !s->fused || s->keep_grad;
-  sl.live = false;
-  s->ver_ref[sl.ver] -= 1;
-  sl.ver = -1;
-  if (updates) { s->cur = dst; s->acc_count = 0; }
-  else if (!s->defer) s->acc_count += 1;
+  finish_backward(s, sl);
+  return RV_OK;
+}
+
+// the two of a step: the forward on s->st, the backward on the auxiliary stream
+rv_status do_both(rv_stage* s, int64_t fwd_mb, const void* in, void* out, int bwd_slot, const void* grad_out, void* grad_in) {
+  if (s->kind == RV_MLP) {
+    RV_TRY(do_forward(s, fwd_mb, in, out));
+    const hipStream_t main_st = s->st;
+    s->st = s->aux;
+    const rv_status rc = do_backward(s, bwd_slot, grad_out, grad_in);
+    s->st = main_st;
+    return rc;
+  }
+  rv_slot* fwd = nullptr;
+  RV_TRY(admit_forward(s, fwd_mb, &fwd));
+  RV_TRY(admit_backward(s));
+  rv_slot& bwd = s->slots[bwd_slot];
+  RV_TRY(rv_dec_step(s, *fwd, in, out, bwd, grad_out, grad_in));   // (a failed launch leaves the stage unusable)
+  finish_backward(s, bwd);
   return RV_OK;
 }
 
@@ -376,12 +414,7 @@ extern "C" rv_status rv_stage_step(rv_stage* s, int64_t fwd_mb, const void* in, 
   RV_HIP_TRY(hipEventRecord(s->ev_fork, main_st));
   RV_HIP_TRY(hipStreamWaitEvent(s->aux, s->ev_fork, 0));
   s->in_step = true;
-  rv_status rc = do_forward(s, fwd_mb, in, out);
-  if (rc == RV_OK) {
-    s->st = s->aux;
-    rc = do_backward(s, bi, grad_out, grad_in);
-    s->st = main_st;
-  }
+  const rv_status rc = do_both(s, fwd_mb, in, out, bi, grad_out, grad_in);
   s->in_step = false;
   // join even after a failure so the caller's stream stays ordered behind the aux work
   hipError_t e1 = hipEventRecord(s->ev_join, s->aux);

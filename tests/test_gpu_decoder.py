@@ -282,3 +282,48 @@ def test_grad_in_may_share_the_buffer_of_grad_out(L, d, H, f, S, mb, tau, step):
             outs += [y] + ([dx, g.last_grad()] if t >= tau else [])
         res.append(outs + [g.get_params()])
     assert all(torch.equal(a, b) for a, b in zip(*res))
+
+
+def torch_block_grads(w0, L, d, H, f, x, dy):
+    """out, grad_in and parameter gradient of the stage in fp32 torch on the GPU, from the bf16-rounded parameters."""
+    import torch.nn.functional as F
+    p = dev(w0).to(torch.bfloat16).float().requires_grad_(True)
+    xin = x.float().requires_grad_(True)
+    dh, h, S = d // H, xin, x.shape[1]
+    mask = torch.full((S, S), float("-inf"), device="cuda").triu(1)
+    for l in range(L):
+        q = {n: t.reshape(s) for (n, s), t in zip(blocks.decoder_param_shapes(1, d, f), p.view(L, -1)[l].split(
+            [int(np.prod(s)) for _, s in blocks.decoder_param_shapes(1, d, f)]))}
+        g1, b1, wqkv, bqkv, wo, bo, g2, b2, w1, c1, w2, c2 = q.values()
+        qkv = F.layer_norm(h, (d,), g1, b1) @ wqkv + bqkv
+        qh, kh, vh = (t.reshape(-1, S, H, dh).transpose(1, 2).contiguous() for t in qkv.split(d, dim=-1))
+        a = torch.softmax(torch.matmul(qh, kh.transpose(2, 3).contiguous()) * dh ** -0.5 + mask, -1)
+        h = h + torch.matmul(a, vh).transpose(1, 2).reshape(h.shape) @ wo + bo
+        h = h + F.gelu(F.layer_norm(h, (d,), g2, b2) @ w1 + c1) @ w2 + c2
+    gx, gp = torch.autograd.grad(h, (xin, p), dy.float())
+    return h.detach(), gx, gp
+
+
+# How the side work of a backward leaves: every block with buffers of its own and four, two or one block to a launch
+# (with a remainder, and with the feed-forward products ahead of the rest), or two alternating sets of buffers
+# (more than 512 MiB for all blocks).
+@pytest.mark.parametrize("L,d,H,f,S,mb", [(6, 128, 2, 256, 64, 2), (5, 320, 5, 1280, 64, 3), (2, 768, 12, 3072, 128, 1),
+                                          (2, 2048, 16, 8192, 64, 1), (8, 128, 2, 256, 64, 512)])
+def test_side_work_schedules(L, d, H, f, S, mb):
+    import paper_2401_01728_amd as rv
+    shapes = blocks.decoder_param_shapes(L, d, f)
+    w0 = decoder_params_host(70 + L, L, d, f)
+    g = rv.Stage.decoder(L, d, H, f, S, mb, 1, 1e-3, keep_grad=True)
+    g.set_params(dev(w0))
+    (x, _), (dy, _) = bf16_normal(71, 0, (mb, S, d)), bf16_normal(71, 1, (mb, S, d), std=1e-3)
+    ref = torch_block_grads(w0, L, d, H, f, x, dy)
+    y = g.forward(0, x)
+    y1, dx = g.step(1, x, 0, dy)                 # both halves at once, at the same weights
+    tag = "side work, %d blocks of d %d on %d tokens" % (L, d, mb * S)
+    for what, a, b in (("out", y, ref[0]), ("out of the step", y1, ref[0]), ("grad_in", dx, ref[1])):
+        close(host64(a), host64(b), TOL, what, group=tag)
+    gg = host64(g.last_grad())
+    check_tensors(gg, host64(ref[2]), shapes, what="grad", group=tag)
+    check_update(host64(g.get_params()), w0, gg, 1e-3)
+    g.backward(1, dy)                            # and the halves apart (fp32 column sums per tile row, whose height may differ)
+    close(host64(g.last_grad()), gg, 1e-5, "grad, apart", group=tag + ", apart")
