@@ -42,6 +42,14 @@ rv_status rv_k_gemm_bf16(const void* A, int64_t lda, int a_kmajor, const void* B
                          const void* zin, int tile, void* stream);
 
 /*
+ * The same product cut into `parts` stretches of the contraction (1 .. 8, at most K / 32), for shapes of few tiles:
+ * part fp32 [parts][M][N] = the sums over each (stretch i: k from 32 * (i * (K/32) / parts) on), to be added by the kernel that reads
+ * the result.  a_kmajor is 0; tile is 1128, 1065, 1064 or 1032.  The divisibility rules are those above.
+ */
+rv_status rv_k_gemm_part(const void* A, int64_t lda, const void* B, int64_t ldb, int b_kmajor, int M, int N, int K,
+                         int tile, int parts, float* part, void* stream);
+
+/*
  * Up to 4 weight-gradient products dW_i[M_i,N_i] = X_i^T dY_i (both operands k-major: X_i is
  * [K, M_i] with pitch lda_i, dY_i is [K, N_i] with pitch ldb_i; fp32 outputs with pitch N_i)
  * over the same K tokens, in ONE launch: the four products of a decoder block together fill
@@ -76,6 +84,15 @@ rv_status rv_k_layernorm_fwd(const void* x, int x_is_bf16, float* xcopy, const v
                              float eps, void* stream);
 
 /*
+ * LayerNorm forward of x = part[0] + ... + part[parts-1] + bias + resid (added in that order), parts in {2, 4, 8}: part fp32
+ * [parts][T][d], bias bf16 [d], resid fp32 [T,d]; x goes to xsum.  y NULL: no LayerNorm, x rounded to bf16 goes to out16 (and to
+ * xsum if given).  d <= 4096.
+ */
+rv_status rv_k_layernorm_fwd_parts(const float* part, int parts, const void* bias, const float* resid, float* xsum,
+                                   const void* gamma, const void* beta, void* y, float* mean, float* rstd, void* out16,
+                                   int T, int d, float eps, void* stream);
+
+/*
  * Backward of the LayerNorm joined with the residual branch it hangs off:
  *   dx = dres + rstd * (dxh - mean(dxh) - xh * mean(dxh * xh)),  dxh = dy * gamma
  * dy bf16 [T,d]; x, dres, dx fp32 [T,d] (dx may alias dres); dx_bf16 optional bf16 copy.
@@ -86,6 +103,14 @@ rv_status rv_k_layernorm_bwd(const void* dy, const float* x, const float* mean, 
                              const void* gamma, const float* dres, float* dx, void* dx_bf16,
                              float* part, float* dgamma, float* dbeta, float* dbias, int T, int d,
                              void* stream);
+
+/*
+ * The same with dy = dy_part[0] + ... + dy_part[parts-1] (fp32 [parts][T][d], parts in {2, 4, 8}); the column sums stay partial rows
+ * of `rows` (2, 4, 8 or 16) tokens each: part fp32 [ceil(T/rows)][3][d].
+ */
+rv_status rv_k_layernorm_bwd_parts(const float* dy_part, int parts, const float* x, const float* mean, const float* rstd,
+                                   const void* gamma, const float* dres, float* dx, void* dx_bf16, float* part,
+                                   int rows, int T, int d, void* stream);
 
 /*
  * Causal self-attention.  qkv bf16 [microbatch*seq, 3*d_model] (column thirds q|k|v, heads

@@ -29,6 +29,10 @@ struct DecPlan {
   bool deep;
   int sets, dy_sets, group;   // group: blocks whose side work goes out together (deep only)
   size_t w_dres, w_dtmp, w_D, w_part_dy, w_ytmp;
+  // products whose contraction is cut over workgroups, the LayerNorm behind them adding the pieces (S 1: none), and where
+  // the pieces go: those of the forward and of the backward apart, a step runs both at once
+  rv_part_form f_wo, f_w2, b_w1, b_wqkv;
+  size_t w_pf, w_pb;
   size_t w_dy, dy_bytes;                                                   // dy buffers: w_dy + i * dy_bytes
   size_t w_set, set_bytes;                                                 // sets: w_set + i * set_bytes, and in a set
   size_t o_dx1_16, o_dz, o_dqkv, o_part_ln[2], o_part_dz, o_part_qkv;
@@ -108,6 +112,11 @@ rv_status rv_dec_plan(rv_stage* s) {
   p->w_D = w; w += align_up(T * H * 4);
   p->w_part_dy = w; w += align_up((size_t)rv_widen_parts(p->T) * d * 4);   // of the arriving gradient (32-row blocks)
   p->w_ytmp = w; w += align_up(T * d * 4);
+  p->f_wo = rv_gemm_part_form(p->T, p->d, p->d); p->f_w2 = rv_gemm_part_form(p->T, p->d, p->f);
+  p->b_w1 = rv_gemm_part_form(p->T, p->d, p->f); p->b_wqkv = rv_gemm_part_form(p->T, p->d, 3 * p->d);
+  auto most = [](const rv_part_form& a, const rv_part_form& b) { const int S = a.S > b.S ? a.S : b.S; return (size_t)(S > 1 ? S : 0); };
+  p->w_pf = w; w += align_up(most(p->f_wo, p->f_w2) * T * d * 4);
+  p->w_pb = w; w += align_up(most(p->b_w1, p->b_wqkv) * T * d * 4);
   p->w_dy = w; w += p->dy_bytes * p->dy_sets;
   p->w_set = w; w += p->set_bytes * p->sets;
   s->work_bytes = w;
@@ -137,6 +146,14 @@ rv_status gemm(int sharing, hipStream_t st, const void* A, int64_t lda, int akm,
   return rc;
 }
 
+rv_status gemm_part(const rv_part_form& form, hipStream_t st, const void* A, int64_t lda, const void* B, int64_t ldb, int bkm, int M,
+                    int N, int K, float* part) {
+  rv_gemm_args g;
+  g.A = (const uint16_t*)A; g.lda = lda; g.B = (const uint16_t*)B; g.ldb = ldb; g.b_kmajor = bkm;
+  g.M = M; g.N = N; g.K = K; g.tile = form.tile;
+  return rv_gemm_part(g, form.S, part, st);
+}
+
 // the forward of block l of one microbatch, on st
 rv_status forward_block(const rv_stage* s, const rv_slot& slot, const void* in, void* out, int l, hipStream_t st) {
   const DecPlan& p = *(const DecPlan*)s->impl;
@@ -152,17 +169,33 @@ rv_status forward_block(const rv_stage* s, const rv_slot& slot, const void* in, 
   uint16_t* v2 = (uint16_t*)(sb + p.s_v2);
   uint16_t* z = (uint16_t*)(sb + p.s_z);
   uint16_t* g = (uint16_t*)(sb + p.s_g);
+  float* pf = (float*)(s->work + p.w_pf);
   if (l == 0)
     RV_TRY(rv_ln_fwd(in, 1, x, w + p.ln1g, w + p.ln1b, u, (float*)(sb + p.s_m1), (float*)(sb + p.s_r1), T, d, s->ln_eps, st));
+  else if (p.f_w2.S > 1)   // (x is what it adds up)
+    RV_TRY(rv_ln_fwd_parts(pf, p.f_w2.S, w - p.per_block + p.b2, (const float*)(sb - p.blk_bytes + p.s_x1), x, w + p.ln1g, w + p.ln1b, u,
+                           (float*)(sb + p.s_m1), (float*)(sb + p.s_r1), nullptr, T, d, s->ln_eps, st));
   else
     RV_TRY(rv_ln_fwd(x, 0, nullptr, w + p.ln1g, w + p.ln1b, u, (float*)(sb + p.s_m1), (float*)(sb + p.s_r1), T, d,
                      s->ln_eps, st));
   RV_TRY(gemm(sh, st, u, d, 0, w + p.wqkv, 3 * d, 1, T, 3 * d, d, RV_EPI_BF16_BIAS, qkv, 3 * d, nullptr, w + p.bqkv));
   RV_TRY(rv_attn_fwd(qkv, a, (float*)(sb + p.s_lse), p.mb, p.S, d, p.H, st));
-  RV_TRY(gemm(sh, st, a, d, 0, w + p.wo, d, 1, T, d, d, RV_EPI_F32_BIAS_RESID, x1, d, nullptr, w + p.bo, x));
-  RV_TRY(rv_ln_fwd(x1, 0, nullptr, w + p.ln2g, w + p.ln2b, v2, (float*)(sb + p.s_m2), (float*)(sb + p.s_r2), T, d,
-                   s->ln_eps, st));
+  if (p.f_wo.S > 1) {
+    RV_TRY(gemm_part(p.f_wo, st, a, d, w + p.wo, d, 1, T, d, d, pf));
+    RV_TRY(rv_ln_fwd_parts(pf, p.f_wo.S, w + p.bo, x, x1, w + p.ln2g, w + p.ln2b, v2, (float*)(sb + p.s_m2), (float*)(sb + p.s_r2),
+                           nullptr, T, d, s->ln_eps, st));
+  } else {
+    RV_TRY(gemm(sh, st, a, d, 0, w + p.wo, d, 1, T, d, d, RV_EPI_F32_BIAS_RESID, x1, d, nullptr, w + p.bo, x));
+    RV_TRY(rv_ln_fwd(x1, 0, nullptr, w + p.ln2g, w + p.ln2b, v2, (float*)(sb + p.s_m2), (float*)(sb + p.s_r2), T, d,
+                     s->ln_eps, st));
+  }
   RV_TRY(gemm(sh, st, v2, d, 0, w + p.w1, f, 1, T, f, d, RV_EPI_BF16_BIAS_GELU, z, f, g, w + p.b1));
+  if (p.f_w2.S > 1) {
+    RV_TRY(gemm_part(p.f_w2, st, g, f, w + p.w2, d, 1, T, d, f, pf));
+    if (l + 1 < p.L) return RV_OK;   // the next block's LayerNorm adds the pieces
+    return rv_ln_fwd_parts(pf, p.f_w2.S, w + p.b2, x1, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, (uint16_t*)out, T, d,
+                           s->ln_eps, st);
+  }
   if (l + 1 < p.L) {
     float* xn = (float*)(slot.base + (size_t)(l + 1) * p.blk_bytes + p.s_x);
     return gemm(sh, st, g, f, 0, w + p.w2, d, 1, T, d, f, RV_EPI_F32_BIAS_RESID, xn, d, nullptr, w + p.b2, x1);
@@ -252,6 +285,21 @@ struct Backward {
     return rv_stage_update_range(s, (size_t)l * p.per_block, (size_t)n * p.per_block, ws);
   }
 
+  // dy = A W^T (A [T,K], W [d,K]) and the backward of the LayerNorm in front of that Linear, joined with the residual branch
+  rv_status product_and_norm(const rv_part_form& form, const uint16_t* A, const uint16_t* W, int K, const float* x, const float* mean,
+                             const float* rstd, const uint16_t* gamma, uint16_t* dx16, float* part) {
+    const int T = p.T, d = p.d, rows = rv_ln_bwd_rows(T, d);
+    float* dres = (float*)(s->work + p.w_dres);
+    if (form.S > 1) {
+      float* pb = (float*)(s->work + p.w_pb);
+      RV_TRY(gemm_part(form, st, A, K, W, K, 0, T, d, K, pb));
+      return rv_ln_bwd_parts_in(pb, form.S, x, mean, rstd, gamma, dres, dres, dx16, part, T, d, st, rows);
+    }
+    uint16_t* dtmp = (uint16_t*)(s->work + p.w_dtmp);
+    RV_TRY(gemm(sh, st, A, K, 0, W, K, 0, T, d, K, RV_EPI_BF16, dtmp, d));
+    return rv_ln_bwd(dtmp, x, mean, rstd, gamma, dres, dres, dx16, part, T, d, st, rows);
+  }
+
   rv_status begin() {
     vdst = s->fused ? (uint16_t*)s->ver[s->upd_dst] : nullptr;
     whole = p.L;
@@ -296,10 +344,9 @@ struct Backward {
 
   rv_status block(int l) {
     const int T = p.T, d = p.d, f = p.f, par = l & 1;
-    float* dres = (float*)(s->work + p.w_dres);
     uint16_t* dtmp = (uint16_t*)(s->work + p.w_dtmp);
     float* Dbuf = (float*)(s->work + p.w_D);
-    const int ln_rows = rv_ln_bwd_rows(T, d), ln_parts = rv_ln_bwd_parts(T, d);
+    const int ln_parts = rv_ln_bwd_parts(T, d);
     // block l may overwrite what the side work of block l+2 read only after that is done
     if (!p.deep && l + 2 < p.L) RV_HIP_TRY(hipStreamWaitEvent(st, s->ev_wg_done[par], 0));
     char* set_l = set(l);
@@ -357,9 +404,9 @@ struct Backward {
       RV_TRY(send_sums());
       if (p.deep) RV_TRY(update_from(l + 1));
     }
-    RV_TRY(gemm(sh, st, dz, f, 0, w + p.w1, f, 0, T, d, f, RV_EPI_BF16, dtmp, d));                       // dv2 = dz W1^T
-    RV_TRY(rv_ln_bwd(dtmp, x1, (const float*)(sb + p.s_m2), (const float*)(sb + p.s_r2), w + p.ln2g, dres, dres,
-                     dx1_16, part2, T, d, st, ln_rows));
+    // dv2 = dz W1^T
+    RV_TRY(product_and_norm(p.b_w1, dz, w + p.w1, f, x1, (const float*)(sb + p.s_m2), (const float*)(sb + p.s_r2), w + p.ln2g, dx1_16,
+                            part2));
     colsum(part2, ln_parts, 3 * (int64_t)d, d, gl + p.ln2g);
     colsum(part2 + d, ln_parts, 3 * (int64_t)d, d, gl + p.ln2b);
     colsum(part2 + 2 * d, ln_parts, 3 * (int64_t)d, d, gl + p.bo);                                     // dbo = sum dx1
@@ -384,10 +431,10 @@ struct Backward {
       if (early || p.deep) RV_TRY(send_sums());
       if (p.deep) RV_TRY(update_from(l + 1));   // (block l lacks what its last LayerNorm gives)
     }
-    RV_TRY(gemm(sh, st, dqkv, 3 * d, 0, w + p.wqkv, 3 * d, 0, T, d, 3 * d, RV_EPI_BF16, dtmp, d));       // du
     uint16_t* dy_below = l > 0 ? dy_buf(l - 1) : nullptr;
-    RV_TRY(rv_ln_bwd(dtmp, x, (const float*)(sb + p.s_m1), (const float*)(sb + p.s_r1), w + p.ln1g, dres, dres,
-                     l == 0 ? (uint16_t*)grad_in : dy_below, part1, T, d, st, ln_rows));
+    // du
+    RV_TRY(product_and_norm(p.b_wqkv, dqkv, w + p.wqkv, 3 * d, x, (const float*)(sb + p.s_m1), (const float*)(sb + p.s_r1), w + p.ln1g,
+                            l == 0 ? (uint16_t*)grad_in : dy_below, part1));
     colsum(part1, ln_parts, 3 * (int64_t)d, d, gl + p.ln1g);
     colsum(part1 + d, ln_parts, 3 * (int64_t)d, d, gl + p.ln1b);
     // the residual gradient leaving this block is dy of the block below: its b2 gradient

@@ -847,6 +847,27 @@ __device__ __forceinline__ void gemm_split_body(const uint16_t* __restrict__ A, 
 #pragma unroll
     for (int q = 0; q < NB; ++q) dtl_load_s(pb, (unsigned)db.off[q] * 2u, lb + A_BYTES + q * NW * 1024);
   };
+  // The epilogue works on rows of the tile, eight columns per lane.  What it reads from memory is requested here, ahead of
+  // the operand tiles: asked for behind the walk along K it was a memory round trip of its own.
+  constexpr int CPR = BN / 8, PIECES = (BM * CPR + NT - 1) / NT, PITCH = split_pitch(BN);
+  constexpr bool RESID = epi_has_resid(EPI), BIAS = epi_has_bias(EPI), ZIN = EPI == EPI_BF16_DGELU, UPD = EPI == EPI_F32_UPD;
+  f32x4 in[PIECES][2];
+  u32x4 bias[PIECES], zin[PIECES];
+  int64_t at[PIECES];
+  bool ok[PIECES];
+#pragma unroll
+  for (int p = 0; p < PIECES; ++p) {
+    const int idx = threadIdx.x + p * NT, row = idx / CPR, gm = m0 + row, gn = n0 + idx % CPR * 8;
+    ok[p] = row < BM && gm < M && gn < N;
+    const int mc = gm < M ? gm : M - 1, nc = gn < N ? gn : N - 8;
+    at[p] = (int64_t)mc * e.ldo + nc;
+    if (BIAS) bias[p] = load8(e.bias + nc);
+    if (ZIN) zin[p] = *reinterpret_cast<const u32x4*>(e.zin + at[p]);
+    if (RESID || (UPD && e.upd_w)) {
+      const f32x4* src = reinterpret_cast<const f32x4*>(RESID ? e.resid + (int64_t)mc * e.ldr + nc : e.upd_w + at[p]);
+      in[p][0] = src[0]; in[p][1] = src[1];
+    }
+  }
 #pragma unroll
   for (int i = 0; i < NS - 1; ++i)
     if (i < mine) issue(i);
@@ -876,26 +897,6 @@ __device__ __forceinline__ void gemm_split_body(const uint16_t* __restrict__ A, 
         for (int a = 0; a < TM; ++a)
 #pragma unroll
           for (int b = 0; b < TN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kk][b], fa[kk][a], acc[a][b], 0, 0, 0);
-    }
-  }
-  // rows of the tile, eight columns per lane: this lane's pieces and what their epilogue reads
-  constexpr int CPR = BN / 8, PIECES = (BM * CPR + NT - 1) / NT, PITCH = split_pitch(BN);
-  constexpr bool RESID = epi_has_resid(EPI), BIAS = epi_has_bias(EPI), ZIN = EPI == EPI_BF16_DGELU, UPD = EPI == EPI_F32_UPD;
-  f32x4 in[PIECES][2];
-  u32x4 bias[PIECES], zin[PIECES];
-  int64_t at[PIECES];
-  bool ok[PIECES];
-#pragma unroll
-  for (int p = 0; p < PIECES; ++p) {
-    const int idx = threadIdx.x + p * NT, row = idx / CPR, gm = m0 + row, gn = n0 + idx % CPR * 8;
-    ok[p] = row < BM && gm < M && gn < N;
-    const int mc = gm < M ? gm : M - 1, nc = gn < N ? gn : N - 8;
-    at[p] = (int64_t)mc * e.ldo + nc;
-    if (BIAS) bias[p] = load8(e.bias + nc);
-    if (ZIN) zin[p] = *reinterpret_cast<const u32x4*>(e.zin + at[p]);
-    if (RESID || (UPD && e.upd_w)) {
-      const f32x4* src = reinterpret_cast<const f32x4*>(RESID ? e.resid + (int64_t)mc * e.ldr + nc : e.upd_w + at[p]);
-      in[p][0] = src[0]; in[p][1] = src[1];
     }
   }
   __syncthreads();                                         // the rings are free
@@ -986,13 +987,42 @@ __device__ __forceinline__ void gemm_split_body(const uint16_t* __restrict__ A, 
   }
 }
 
+// Workgroup -> stretch of the contraction and tile: every XCD (workgroup ids go to the 8 of them in turn) takes a contiguous
+// range of a stretch's tiles, column by column in bands of up to 8 tile rows, so that a panel of the weights - cold, in HBM -
+// is fetched into one or two of the L2s and not into all that hold a tile row.
+__device__ __forceinline__ void split_tile(int tiles_m, int tiles_n, int S, int& ks, int& bm, int& bn) {
+  const int tiles = tiles_m * tiles_n, total = tiles * S, base = total / 8, rem = total % 8;
+  const int g = blockIdx.x % 8, v = g * base + (g < rem ? g : rem) + blockIdx.x / 8;
+  ks = v / tiles;
+  const int t = v - ks * tiles, band = t / (8 * tiles_n), first = band * 8;
+  const int rows = tiles_m - first < 8 ? tiles_m - first : 8, in = t - band * 8 * tiles_n;
+  bm = first + in % rows;
+  bn = in / rows;
+}
+
 template <int BM, int BN, int G, int NW, int NS, bool AKM, bool BKM, int EPI>
 __global__ __launch_bounds__(64 * NW * G, NW * G / 4) void gemm_split_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                                 const uint16_t* __restrict__ B, int64_t ldb, int M, int N, int K,
                                                                 int tiles_m, int tiles_n, Epi e) {
-  int bm, bn;
-  tile_of_block(-tiles_m, tiles_n, 8, bm, bn);
+  int ks, bm, bn;
+  split_tile(tiles_m, tiles_n, 1, ks, bm, bn);
   gemm_split_body<BM, BN, G, NW, NS, AKM, BKM, EPI>(A, lda, B, ldb, M, N, K, bm, bn, e);
+}
+
+// ---- few tiles and a long contraction: split over workgroups as well ------------------------
+// A product of so few tiles that most CUs have none is cut into S stretches of k-tiles, a workgroup to each tile of each: every
+// one stores its sum as fp32 to part[stretch][M][N], and the kernel that reads the result - a LayerNorm, which passes over
+// whole rows anyway - adds the S of them in order (norm.hip): no exchange between workgroups, no launch of its own.
+template <int BM, int BN, int G, int NW, int NS, bool BKM>
+__global__ __launch_bounds__(64 * NW * G, NW * G / 4) void gemm_part_kernel(const uint16_t* __restrict__ A, int64_t lda,
+                                                               const uint16_t* __restrict__ B, int64_t ldb, int M, int N, int K,
+                                                               int tiles_m, int tiles_n, int S, float* part) {
+  int ks, bm, bn;
+  split_tile(tiles_m, tiles_n, S, ks, bm, bn);
+  const int nk = K / 32, t0 = nk * ks / S, t1 = nk * (ks + 1) / S;
+  Epi e{part + (int64_t)ks * M * N, N, nullptr, nullptr, nullptr, 0, nullptr, nullptr, 0.f, nullptr};
+  gemm_split_body<BM, BN, G, NW, NS, false, BKM, EPI_F32>(A + t0 * 32, lda, BKM ? B + (int64_t)t0 * 32 * ldb : B + t0 * 32, ldb,
+                                                          M, N, (t1 - t0) * 32, bm, bn, e);
 }
 
 // Several independent products of one kind in a single launch (the four weight-gradient
@@ -1093,6 +1123,29 @@ rv_status launch_split(const rv_gemm_args& g, hipStream_t st) {
   return rv_launch_status();
 }
 
+template <int BM, int BN, int G, int NW, int NS, bool BKM>
+rv_status launch_part(const rv_gemm_args& g, int S, float* part, hipStream_t st) {
+  constexpr int smem = split_lds<BM, BN, G, NS>();
+  static_assert(smem <= 160 * 1024, "LDS of one CU");
+  auto kern = gemm_part_kernel<BM, BN, G, NW, NS, BKM>;
+  static const hipError_t configured =
+      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+  if (configured != hipSuccess) return RV_E_DEVICE;
+  const int tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN;
+  hipLaunchKernelGGL(kern, dim3(tm * tn * S), dim3(64 * NW * G), smem, st, g.A, g.lda, g.B, g.ldb, g.M, g.N, g.K, tm, tn, S, part);
+  return rv_launch_status();
+}
+template <bool BKM>
+rv_status pick_part(const rv_gemm_args& g, int S, float* part, hipStream_t st) {
+  switch (g.tile) {
+    case 1032: return launch_part<32, 64, 8, 2, 3, BKM>(g, S, part, st);
+    case 1064: return launch_part<64, 64, 4, 4, 4, BKM>(g, S, part, st);
+    case 1065: return launch_part<64, 64, 2, 4, 4, BKM>(g, S, part, st);
+    case 1128: return launch_part<128, 128, 2, 4, 4, BKM>(g, S, part, st);
+  }
+  return RV_E_INVAL;
+}
+
 // Tile choice (codes: 5256, 2256, 2192, 2128, 1128, 1065, 1064, 1032).
 //   5256  256x256, eight waves of 128x64, BK 32, ring of four slots run in the pipelined form
 //         (three tiles in flight, loads dealt out behind the MFMAs), one workgroup per CU:
@@ -1118,13 +1171,17 @@ constexpr TileForm kForms[] = {
     {5256, 256, 256, 32, 1, 4.9f, 0.53f, 0.86f}, {2192, 128, 256, 32, 2, 3.5f, 0.42f, 1.05f}, {2128, 128, 128, 64, 2, 2.8f, 0.58f, 1.10f},
     {1128, 128, 128, 64, 1, 3.9f, 0.43f, 0.56f}, {1065, 64, 64, 64, 2, 2.3f, 0.265f, 0.47f}, {1064, 64, 64, 128, 1, 2.7f, 0.44f, 0.64f},
     {1032, 32, 64, 256, 1, 2.4f, 0.72f, 0.82f}};
+// the modelled time of a form whose contraction is cut into S stretches
+float form_time(const TileForm& c, int M, int N, int K, int S) {
+  const float tiles = (float)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * S, slots = 256.f * c.per_cu;
+  const float fill = tiles < slots ? tiles / slots : 1.f;
+  return ceilf(tiles / slots) * (c.f + ceilf((float)K / S / c.k) * (c.t0 + (c.t1 - c.t0) * fill * fill));
+}
 int best_form(int M, int N, int K, int codes_from, int codes_to, float& least) {
   int best = 0;
   for (const TileForm& c : kForms) {
     if (c.code < codes_from || c.code >= codes_to) continue;
-    const float tiles = (float)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn), slots = 256.f * c.per_cu;
-    const float fill = tiles < slots ? tiles / slots : 1.f;
-    const float time = ceilf(tiles / slots) * (c.f + ceilf((float)K / c.k) * (c.t0 + (c.t1 - c.t0) * fill * fill));
+    const float time = form_time(c, M, N, K, 1);
     if (!best || time < least) { best = c.code; least = time; }
   }
   return best;
@@ -1208,6 +1265,39 @@ rv_status rv_gemm_bf16(const rv_gemm_args& g, hipStream_t st) {
     if (g.epi == EPI_F32) return pick_tile<true, true, EPI_F32>(g, st);
   }
   return RV_E_INVAL;
+}
+
+// The form and the number of stretches of a product whose partial sums the next kernel can add: the least modelled time,
+// 8 bytes per partial sum (written and read back) at 5 TB/s, if that takes a fifth off the best whole product; S = 1: none does.
+// Weights not in any cache, whole / cut, us: 128x1024x4096 21.0 / 7.3 (64x64 tiles, S 8) and, k-contiguous weights, 16.9 / 7.1;
+// 128x1024x3072 13.7 / 6.7; 256x448x1792 7.1 / 5.4 (32x64, 4); 128x1024x1024 6.0 / 5.0; 2048x1024x4096 44.7 / 28.1 (128x128, 2).  Not
+// taken, as the pieces' traffic eats the gain: 512x1024x4096 19.9 / 15.3, 1152x768x3072 16.1 / 14.0, 2048x1024x1024 11.7 / 13.0.
+// Four stages of 4 blocks of d 1024 on 128 tokens, forward and backward, with their average 3137 -> 2761 us, stage step of 12
+// blocks of d 448 on 256 tokens 924 -> 852 us (with what split_tile and the early requests give).
+rv_part_form rv_gemm_part_form(int M, int N, int K) {
+  float whole = 0.f, in_order = 0.f;
+  best_form(M, N, K, 2000, 10000, in_order);
+  best_form(M, N, K, 0, 2000, whole);
+  if (!(whole < 0.75f * in_order)) whole = in_order;   // (what pick_tile takes)
+  rv_part_form best = {0, 1};
+  float least = 0.8f * whole;
+  for (const TileForm& c : kForms) {
+    if (c.code >= 2000) continue;
+    for (int S = 2; S <= RV_GEMM_PARTS_MAX && S * c.k <= K; S *= 2) {
+      const float time = form_time(c, M, N, K, S) + (float)M * N * S * 8.f / 5e6f;
+      if (time < least) { least = time; best = {c.code, S}; }
+    }
+  }
+  return best;
+}
+
+// the product's operands as in g (a_kmajor 0), its sums over S stretches of the contraction to part[S][M][N]
+rv_status rv_gemm_part(const rv_gemm_args& g, int S, float* part, hipStream_t st) {
+  if (!g.A || !g.B || !part || g.a_kmajor || g.M < 8 || g.N < 8 || g.K < 64 || S < 1 || S > RV_GEMM_PARTS_MAX || S > g.K / 32) return RV_E_INVAL;
+  if (g.K % 64 || g.N % 8 || g.M % 8 || g.lda % 8 || g.ldb % 8) return RV_E_INVAL;
+  if ((((uintptr_t)g.A) | ((uintptr_t)g.B) | ((uintptr_t)part)) & 15) return RV_E_INVAL;
+  if ((int64_t)g.M * g.lda >= (1ll << 31) || (int64_t)(g.b_kmajor ? g.K : g.N) * g.ldb >= (1ll << 31)) return RV_E_INVAL;
+  return g.b_kmajor ? pick_part<true>(g, S, part, st) : pick_part<false>(g, S, part, st);
 }
 
 namespace {
@@ -1300,6 +1390,14 @@ extern "C" rv_status rv_k_gemm_bf16(const void* A, int64_t lda, int a_kmajor, co
   g.M = M; g.N = N; g.K = K; g.epi = epilogue; g.out = out; g.ldo = ldo; g.out2 = out2;
   g.bias = (const uint16_t*)bias; g.resid = resid; g.ldr = ldr; g.zin = (const uint16_t*)zin; g.tile = tile;
   return rv_gemm_bf16(g, (hipStream_t)stream);
+}
+
+extern "C" rv_status rv_k_gemm_part(const void* A, int64_t lda, const void* B, int64_t ldb, int b_kmajor, int M, int N, int K,
+                                    int tile, int parts, float* part, void* stream) {
+  rv_gemm_args g;
+  g.A = (const uint16_t*)A; g.lda = lda; g.B = (const uint16_t*)B; g.ldb = ldb; g.b_kmajor = b_kmajor;
+  g.M = M; g.N = N; g.K = K; g.tile = tile;
+  return rv_gemm_part(g, parts, part, (hipStream_t)stream);
 }
 
 extern "C" rv_status rv_k_gemm_wgrad_grouped(int count, const void* const* X, const int64_t* lda,

@@ -55,6 +55,11 @@ struct rv_gemm_args {
   bool store_out = true;
 };
 rv_status rv_gemm_bf16(const rv_gemm_args& g, hipStream_t st);
+// the product cut into S stretches along K: part[S][M][N] = their sums, for a kernel that adds them
+#define RV_GEMM_PARTS_MAX 8
+rv_status rv_gemm_part(const rv_gemm_args& g, int S, float* part, hipStream_t st);
+struct rv_part_form { int tile, S; };   // S 1: the whole product is as good
+rv_part_form rv_gemm_part_form(int M, int N, int K);
 // up to RV_GEMM_GROUP_MAX weight-gradient products (both operands k-major, fp32 output) in one launch; more than the four
 // of one block only with contractions shorter than RV_WGRAD_SPLIT_K (the tiles whose contraction is split)
 #define RV_GEMM_GROUP_BLOCK 4
@@ -68,11 +73,19 @@ rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t s
 // ---- norm.hip ---------------------------------------------------------------------
 rv_status rv_ln_fwd(const void* x, int x_is_bf16, float* xcopy, const uint16_t* gamma, const uint16_t* beta,
                     uint16_t* y, float* mean, float* rstd, int T, int d, float eps, hipStream_t st);
+// the same of x = part[0] + .. + part[S-1] + bias + resid, which it also writes to xsum (S in {2, 4, 8}); y null: only xsum, and
+// its bf16 rounding to out16
+rv_status rv_ln_fwd_parts(const float* part, int S, const uint16_t* bias, const float* resid, float* xsum, const uint16_t* gamma,
+                          const uint16_t* beta, uint16_t* y, float* mean, float* rstd, uint16_t* out16, int T, int d, float eps,
+                          hipStream_t st);
 int rv_ln_bwd_rows(int T, int d);    // rows per workgroup of the backward: 2, 4, 8 or (d > 1024) 16
 int rv_ln_bwd_parts(int T, int d);   // partial rows it writes with them (each 3*d floats)
 rv_status rv_ln_bwd(const uint16_t* dy, const float* x, const float* mean, const float* rstd,
                     const uint16_t* gamma, const float* dres, float* dx, uint16_t* dx_bf16, float* part,
                     int T, int d, hipStream_t st, int rows);
+// the same with dy = part[0] + .. + part[S-1] (S in {2, 4, 8}, fp32 [T,d] each), not rounded
+rv_status rv_ln_bwd_parts_in(const float* dy_part, int S, const float* x, const float* mean, const float* rstd, const uint16_t* gamma,
+                             const float* dres, float* dx, uint16_t* dx_bf16, float* part, int T, int d, hipStream_t st, int rows);
 // o fp32 [T,d] = a bf16 [T,d] widened, and part fp32 [rv_widen_parts(T), d] = column sums of a over
 // blocks of 32 rows
 int rv_widen_parts(int T);

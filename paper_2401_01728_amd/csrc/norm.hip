@@ -184,6 +184,76 @@ __global__ __launch_bounds__(kThreads, 5) void ln_fwd_pipe_kernel(const float* _
   finish(vb, row0 + RPW - 1);
 }
 
+// x = part[0] + .. + part[S-1] + bias + resid, then as above: the end of a product whose contraction was cut into S stretches
+// (gemm_part_kernel) and the LayerNorm behind it in one pass.  One wave to a workgroup and a row, all of a row's operands
+// requested before the first is added: few rows (that is when products are cut) leave CUs idle, and what bounds the launch is
+// one memory round trip.  WITH_LN false: only x, and its bf16 rounding (the stage's output).
+template <int NV, int S, bool WITH_LN>
+__global__ __launch_bounds__(64) void ln_fwd_parts_kernel(const float* __restrict__ part, const uint16_t* __restrict__ bias,
+                                                          const float* __restrict__ resid, float* __restrict__ xsum,
+                                                          const uint16_t* __restrict__ gamma, const uint16_t* __restrict__ beta,
+                                                          uint16_t* __restrict__ y, float* __restrict__ mean,
+                                                          float* __restrict__ rstd, uint16_t* __restrict__ out16, int T, int d,
+                                                          float eps) {
+  const int l = threadIdx.x, row = blockIdx.x;
+  const int64_t at = (int64_t)row * d, step = (int64_t)T * d;
+  f32x4 v[NV];
+  u32x2 g[NV], b[NV];
+  constexpr int NB = NV > 4 ? 4 : NV;   // column groups per batch of requests
+#pragma unroll
+  for (int i0 = 0; i0 < NV; i0 += NB) {
+    f32x4 p[NB][S], r[NB];
+    u32x2 bb[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int c = l * 4 + 256 * (i0 + i), cc = c < d ? c : d - 4;
+#pragma unroll
+      for (int k = 0; k < S; ++k) p[i][k] = *reinterpret_cast<const f32x4*>(part + k * step + at + cc);
+      r[i] = *reinterpret_cast<const f32x4*>(resid + at + cc);
+      bb[i] = *reinterpret_cast<const u32x2*>(bias + cc);
+      if (WITH_LN) {
+        g[i0 + i] = *reinterpret_cast<const u32x2*>(gamma + cc);
+        b[i0 + i] = *reinterpret_cast<const u32x2*>(beta + cc);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      f32x4 t = p[i][0];
+#pragma unroll
+      for (int k = 1; k < S; ++k) t += p[i][k];
+      t += bf16x4_to_f32(bb[i]);
+      v[i0 + i] = t + r[i];
+    }
+  }
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int c = l * 4 + 256 * i;
+    if (c < d) {
+      if (xsum) *reinterpret_cast<f32x4*>(xsum + at + c) = v[i];
+      if (!WITH_LN) *reinterpret_cast<u32x2*>(out16 + at + c) = f32_to_bf16x4(v[i]);
+      s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+    }
+  }
+  if (!WITH_LN) return;
+  const float mu = wave_sum_imm(s) / (float)d;
+  float q = 0.f;
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+    if (l * 4 + 256 * i < d) {
+      const f32x4 t = v[i] - mu;
+      q += (t.x * t.x + t.y * t.y) + (t.z * t.z + t.w * t.w);
+    }
+  const float r = rsqrtf(wave_sum_imm(q) / (float)d + eps);
+  if (l == 0) { mean[row] = mu; rstd[row] = r; }
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int c = l * 4 + 256 * i;
+    const f32x4 o = (v[i] - mu) * r * bf16x4_to_f32(g[i]) + bf16x4_to_f32(b[i]);
+    if (c < d) *reinterpret_cast<u32x2*>(y + at + c) = f32_to_bf16x4(o);
+  }
+}
+
 // Backward of y = LN(x)*gamma + beta joined with the residual branch:
 //   dx = dres + rstd * (dxh - mean(dxh) - xh * mean(dxh * xh)),  dxh = dy * gamma
 // Writes dx (fp32, may alias dres) and optionally its bf16 rounding; accumulates three
@@ -203,8 +273,10 @@ constexpr int kBwdWaves = 4;
 // ln_bwd_pipe_kernel below, which keeps twice the rows in flight.  Row statistics are combined
 // through LDS in a fixed order, one barrier per RF rows, two alternating slots.  The column sums
 // stay in registers for the workgroup's rows and leave as one partial row per workgroup.
-template <int NV, int RF>
-__global__ __launch_bounds__(64 * kBwdWaves, NV <= 2 ? 6 : 1) void ln_bwd_kernel(const uint16_t* __restrict__ dy,
+// S > 0: dy arrives as S partial sums (fp32 [S][T][d], of a product whose contraction was cut into S stretches), added in order
+// as they come; such launches are of few rows, and all rows of a workgroup are in flight at once (RF).
+template <int NV, int RF, int S>
+__global__ __launch_bounds__(64 * kBwdWaves, S == 0 && NV <= 2 ? 6 : 1) void ln_bwd_kernel(const void* __restrict__ dy,
                                                                 const float* __restrict__ x,
                                                                 const float* __restrict__ mean,
                                                                 const float* __restrict__ rstd,
@@ -228,7 +300,7 @@ __global__ __launch_bounds__(64 * kBwdWaves, NV <= 2 ? 6 : 1) void ln_bwd_kernel
   for (int k = 0; k < rows / RF; ++k) {
     const int row0 = blockIdx.x * rows + k * RF;
     // every operand of the RF rows is requested here: one memory round trip per RF rows
-    f32x4 xh[RF][NV], rs[RF][NV];
+    f32x4 xh[RF][NV], rs[RF][NV], dyp[RF][NV][S > 0 ? S : 1];
     u32x2 dyr[RF][NV];
     float mu[RF], r[RF];
 #pragma unroll
@@ -240,15 +312,30 @@ __global__ __launch_bounds__(64 * kBwdWaves, NV <= 2 ? 6 : 1) void ln_bwd_kernel
       for (int i = 0; i < NV; ++i) {
         const int c = cbase + 256 * i;
         xh[q][i] = 0.f; rs[q][i] = 0.f; dyr[q][i] = u32x2{0u, 0u};
-        if (valid && c < d) {
+        if (S > 0) {   // (clamped: no branch around the loads)
+          const int64_t at = (int64_t)(valid ? row : T - 1) * d + (c < d ? c : d - 4);
+#pragma unroll
+          for (int k = 0; k < S; ++k) dyp[q][i][k] = *reinterpret_cast<const f32x4*>((const float*)dy + (int64_t)k * T * d + at);
+          xh[q][i] = *reinterpret_cast<const f32x4*>(x + at);
+          rs[q][i] = *reinterpret_cast<const f32x4*>(dres + at);
+        } else if (valid && c < d) {
           // read once, written once: the non-temporal hint keeps these rows from pushing the
           // operand panels of the matrix products on the other streams out of L2
           xh[q][i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(x + (int64_t)row * d + c));
           rs[q][i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(dres + (int64_t)row * d + c));
-          dyr[q][i] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(dy + (int64_t)row * d + c));
+          dyr[q][i] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>((const uint16_t*)dy + (int64_t)row * d + c));
         }
       }
     }
+    if (S > 0) {
+#pragma unroll
+      for (int q = 0; q < RF; ++q)
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+          for (int k = 1; k < S; ++k) dyp[q][i][0] += dyp[q][i][k];
+    }
+    auto dy_of = [&](int q, int i) { return S > 0 ? dyp[q][i][0] : bf16x4_to_f32(dyr[q][i]); };
 #pragma unroll
     for (int q = 0; q < RF; ++q) {
       float s1 = 0.f, s2 = 0.f;
@@ -257,7 +344,7 @@ __global__ __launch_bounds__(64 * kBwdWaves, NV <= 2 ? 6 : 1) void ln_bwd_kernel
         const int c = cbase + 256 * i;
         if (c < d) {
           xh[q][i] = (xh[q][i] - mu[q]) * r[q];
-          const f32x4 dxh = bf16x4_to_f32(dyr[q][i]) * gam[i];
+          const f32x4 dxh = dy_of(q, i) * gam[i];
           const f32x4 t = dxh * xh[q][i];
           s1 += (dxh.x + dxh.y) + (dxh.z + dxh.w);
           s2 += (t.x + t.y) + (t.z + t.w);
@@ -279,7 +366,7 @@ __global__ __launch_bounds__(64 * kBwdWaves, NV <= 2 ? 6 : 1) void ln_bwd_kernel
         for (int i = 0; i < NV; ++i) {
           const int c = cbase + 256 * i;
           if (c < d) {
-            const f32x4 dyv = bf16x4_to_f32(dyr[q][i]);
+            const f32x4 dyv = dy_of(q, i);
             const f32x4 dxh = dyv * gam[i];
             const f32x4 o = (dxh - c1 - xh[q][i] * c2) * r[q] + rs[q][i];
             __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(dx + (int64_t)row * d + c));
@@ -550,6 +637,32 @@ rv_status rv_ln_fwd(const void* x, int x_is_bf16, float* xcopy, const uint16_t* 
   return rv_launch_status();
 }
 
+rv_status rv_ln_fwd_parts(const float* part, int S, const uint16_t* bias, const float* resid, float* xsum, const uint16_t* gamma,
+                          const uint16_t* beta, uint16_t* y, float* mean, float* rstd, uint16_t* out16, int T, int d, float eps,
+                          hipStream_t st) {
+  if (!part || !bias || !resid || T < 1 || d < 4 || d % 4 || d > 4096) return RV_E_INVAL;
+  if (y ? !xsum || !gamma || !beta || !mean || !rstd : !out16) return RV_E_INVAL;
+#define RV_LN_FP(NV, S)                                                                                                        \
+  if (y) hipLaunchKernelGGL((ln_fwd_parts_kernel<NV, S, true>), dim3(T), dim3(64), 0, st, part, bias, resid, xsum, gamma, beta, y, \
+                            mean, rstd, out16, T, d, eps);                                                                     \
+  else hipLaunchKernelGGL((ln_fwd_parts_kernel<NV, S, false>), dim3(T), dim3(64), 0, st, part, bias, resid, xsum, gamma, beta, y,  \
+                          mean, rstd, out16, T, d, eps);
+#define RV_LN_FP_S(S)                    \
+  if (d <= 1024) { RV_LN_FP(4, S) }      \
+  else if (d <= 2048) { RV_LN_FP(8, S) } \
+  else { RV_LN_FP(16, S) }               \
+  break;
+  switch (S) {
+    case 2: RV_LN_FP_S(2)
+    case 4: RV_LN_FP_S(4)
+    case 8: RV_LN_FP_S(8)
+    default: return RV_E_INVAL;
+  }
+#undef RV_LN_FP_S
+#undef RV_LN_FP
+  return rv_launch_status();
+}
+
 // Rows per workgroup.  Many tokens: 8 for d <= 1024 (twice the workgroups: the stage step of the
 // 1024-wide stage measured 0.4 % shorter than with 16, and 0.9 % shorter than with 4), 16 beyond (8 measured
 // -0.2 % at d = 1600 and +0.2 % at d = 2048).  Fewer than 256 workgroups of those leave CUs without one
@@ -576,7 +689,7 @@ rv_status rv_ln_bwd(const uint16_t* dy, const float* x, const float* mean, const
     return RV_E_INVAL;
   dim3 grid((T + rows - 1) / rows), blk(64 * kBwdWaves);
 #define RV_LN_BWD(NV, RF) \
-  hipLaunchKernelGGL((ln_bwd_kernel<NV, RF>), grid, blk, 0, st, dy, x, mean, rstd, gamma, dres, dx, dx_bf16, part, T, d, rows);
+  hipLaunchKernelGGL((ln_bwd_kernel<NV, RF, 0>), grid, blk, 0, st, dy, x, mean, rstd, gamma, dres, dx, dx_bf16, part, T, d, rows);
 #define RV_LN_PIPE(RF, ROWS) \
   hipLaunchKernelGGL((ln_bwd_pipe_kernel<1, RF, ROWS>), grid, blk, 0, st, dy, x, mean, rstd, gamma, dres, dx, dx_bf16, part, T, d);
   if (d <= 1024) {
@@ -586,6 +699,30 @@ rv_status rv_ln_bwd(const uint16_t* dy, const float* x, const float* mean, const
   else { RV_LN_BWD(4, 1) }
 #undef RV_LN_PIPE
 #undef RV_LN_BWD
+  return rv_launch_status();
+}
+
+rv_status rv_ln_bwd_parts_in(const float* dy_part, int S, const float* x, const float* mean, const float* rstd, const uint16_t* gamma,
+                             const float* dres, float* dx, uint16_t* dx_bf16, float* part, int T, int d, hipStream_t st, int rows) {
+  if (!dy_part || !x || !mean || !rstd || !gamma || !dres || !dx || !part || T < 1 || d < 4 || d % 4 || d > 4096 || rows % 2)
+    return RV_E_INVAL;
+  dim3 grid((T + rows - 1) / rows), blk(64 * kBwdWaves);
+  const void* dy = dy_part;
+#define RV_LN_BWDP(NV, RF, S) \
+  hipLaunchKernelGGL((ln_bwd_kernel<NV, RF, S>), grid, blk, 0, st, dy, x, mean, rstd, gamma, dres, dx, dx_bf16, part, T, d, rows)
+#define RV_LN_BWDP_S(S)                        \
+  if (d <= 1024) RV_LN_BWDP(1, 2, S);          \
+  else if (d <= 2048) RV_LN_BWDP(2, 2, S);     \
+  else RV_LN_BWDP(4, 1, S);                    \
+  break;
+  switch (S) {
+    case 2: RV_LN_BWDP_S(2)
+    case 4: RV_LN_BWDP_S(4)
+    case 8: RV_LN_BWDP_S(8)
+    default: return RV_E_INVAL;
+  }
+#undef RV_LN_BWDP_S
+#undef RV_LN_BWDP
   return rv_launch_status();
 }
 
@@ -627,6 +764,21 @@ extern "C" rv_status rv_k_layernorm_fwd(const void* x, int x_is_bf16, float* xco
                                         float eps, void* stream) {
   return rv_ln_fwd(x, x_is_bf16, xcopy, (const uint16_t*)gamma, (const uint16_t*)beta, (uint16_t*)y, mean, rstd,
                    T, d, eps, (hipStream_t)stream);
+}
+
+extern "C" rv_status rv_k_layernorm_fwd_parts(const float* part, int parts, const void* bias, const float* resid, float* xsum,
+                                              const void* gamma, const void* beta, void* y, float* mean, float* rstd, void* out16,
+                                              int T, int d, float eps, void* stream) {
+  return rv_ln_fwd_parts(part, parts, (const uint16_t*)bias, resid, xsum, (const uint16_t*)gamma, (const uint16_t*)beta, (uint16_t*)y,
+                         mean, rstd, (uint16_t*)out16, T, d, eps, (hipStream_t)stream);
+}
+
+extern "C" rv_status rv_k_layernorm_bwd_parts(const float* dy_part, int parts, const float* x, const float* mean, const float* rstd,
+                                              const void* gamma, const float* dres, float* dx, void* dx_bf16, float* part,
+                                              int rows, int T, int d, void* stream) {
+  if (rows != 2 && rows != 4 && rows != 8 && rows != 16) return RV_E_INVAL;
+  return rv_ln_bwd_parts_in(dy_part, parts, x, mean, rstd, (const uint16_t*)gamma, dres, dx, (uint16_t*)dx_bf16, part, T, d,
+                            (hipStream_t)stream, rows);
 }
 
 extern "C" rv_status rv_k_layernorm_bwd(const void* dy, const float* x, const float* mean, const float* rstd,

@@ -19,6 +19,14 @@ def gemm_bf16(A, a_kmajor, B, b_kmajor, M, N, K, epilogue, out, out2=None, bias=
     return out
 
 
+def gemm_part(A, B, b_kmajor, M, N, K, tile, parts, stream=None):
+    """rv_k_gemm_part: fp32 [parts, M, N], the product's sums over `parts` stretches of the contraction."""
+    part = torch.full((parts, M, N), float("nan"), dtype=torch.float32, device="cuda")
+    _check(_lib.lib().rv_k_gemm_part(_ptr(A), A.stride(0), _ptr(B), B.stride(0), int(b_kmajor), M, N, K, tile, parts, _ptr(part),
+                                     _stream_handle(stream)))
+    return part
+
+
 def gemm_wgrad_grouped(xs, dys, outs, stream=None):
     """rv_k_gemm_wgrad_grouped: outs[i] (fp32 [M_i, N_i]) = xs[i]^T @ dys[i]; xs[i] is [K, M_i], dys[i] is [K, N_i]."""
     n = len(xs)
@@ -52,6 +60,28 @@ def layernorm_fwd(x, gamma, beta, eps, xcopy=None, stream=None):
                                          _ptr(beta), _ptr(y), _ptr(mean), _ptr(rstd), T, d, eps,
                                          _stream_handle(stream)))
     return y, mean, rstd
+
+
+def layernorm_fwd_parts(part, bias, resid, gamma, beta, eps, stream=None):
+    """(xsum, y, mean, rstd); without gamma: (xsum, xsum rounded to bf16)."""
+    S, T, d = part.shape
+    xsum, y = torch.empty(T, d, dtype=torch.float32, device="cuda"), torch.empty(T, d, dtype=torch.bfloat16, device="cuda")
+    ln = gamma is not None
+    mean, rstd = (torch.empty(T, dtype=torch.float32, device="cuda") if ln else None for _ in range(2))
+    _check(_lib.lib().rv_k_layernorm_fwd_parts(_ptr(part), S, _ptr(bias), _ptr(resid), _ptr(xsum), _ptr(gamma), _ptr(beta),
+                                               _ptr(y if ln else None), _ptr(mean), _ptr(rstd), _ptr(None if ln else y), T, d, eps,
+                                               _stream_handle(stream)))
+    return (xsum, y, mean, rstd) if ln else (xsum, y)
+
+
+def layernorm_bwd_parts(dy_part, x, mean, rstd, gamma, dres, rows, stream=None):
+    """(dx, its bf16 rounding, column sums fp32 [ceil(T / rows), 3, d])."""
+    S, T, d = dy_part.shape
+    dx, dx16 = torch.empty(T, d, dtype=torch.float32, device="cuda"), torch.empty(T, d, dtype=torch.bfloat16, device="cuda")
+    part = torch.empty((T + rows - 1) // rows, 3, d, dtype=torch.float32, device="cuda")
+    _check(_lib.lib().rv_k_layernorm_bwd_parts(_ptr(dy_part), S, _ptr(x), _ptr(mean), _ptr(rstd), _ptr(gamma), _ptr(dres), _ptr(dx),
+                                               _ptr(dx16), _ptr(part), rows, T, d, _stream_handle(stream)))
+    return dx, dx16, part
 
 
 def layernorm_bwd(dy, x, mean, rstd, gamma, dres, want_bf16=True, stream=None):

@@ -224,3 +224,29 @@ def test_automatic_tile_is_among_the_fast_ones(kind, M, N, K):
             e1.record(); torch.cuda.synchronize()
             times[tile] = min(times.get(tile, 1e9), e0.elapsed_time(e1))
     assert times[0] <= 1.15 * min(v for t, v in times.items() if t), times
+
+
+# Products cut into stretches of the contraction: more stretches than a form has groups of waves get k-tiles (K = 64 in two), uneven
+# stretches (K/32 = 10 in 3, 4 and 8), ragged tiles, fewer tiles than XCDs and more than one band of tile rows
+@pytest.mark.parametrize("M,N,K,parts", [(8, 8, 64, 2), (40, 72, 320, 4), (128, 200, 320, 3), (648, 136, 1024, 8), (256, 448, 1792, 8)])
+@pytest.mark.parametrize("tile", [1032, 1064, 1065, 1128])
+def test_product_in_stretches(M, N, K, parts, tile):
+    from paper_2401_01728_amd import kernels as k
+    x, x64 = bf16_normal(9, 0, (M, K))
+    edges = [32 * (K // 32 * i // parts) for i in range(parts + 1)]
+    for b_kmajor in (0, 1):
+        w, w64 = bf16_normal(9, 1 + b_kmajor, (K, N) if b_kmajor else (N, K), std=0.05)
+        got = host64(k.gemm_part(x, w, b_kmajor, M, N, K, tile, parts))
+        w64 = w64 if b_kmajor else w64.T
+        for i in range(parts):
+            lo, hi = edges[i], edges[i + 1]
+            close(got[i], x64[:, lo:hi] @ w64[lo:hi], 1e-5, "part %d" % i, group=GROUP[1e-5])
+
+
+def test_product_in_stretches_refuses():
+    import paper_2401_01728_amd as rv
+    from paper_2401_01728_amd import kernels as k
+    x = torch.zeros(64, 64, dtype=torch.bfloat16, device="cuda")
+    for tile, parts in ((1032, 3), (1032, 0), (5256, 2), (0, 2)):      # K / 32 = 2 stretches at most; the split forms only
+        with pytest.raises(rv.RvError):
+            k.gemm_part(x, x, 0, 64, 64, 64, tile, parts)

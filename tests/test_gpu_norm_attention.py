@@ -47,6 +47,31 @@ def test_layernorm_forward_backward(T, d):
     close(host64(dbias), rdx.sum(0), 1e-5, "k", group="LayerNorm / column sum / attention kernels, bar 1e-5")
 
 
+# the LayerNorm that adds a product's pieces: every register layout (up to 1024, 2048, 4096 columns), odd rows and widths
+@pytest.mark.parametrize("T,d,S,rows", [(5, 64, 2, 2), (37, 1024, 4, 4), (16, 1028, 8, 2), (9, 2048, 2, 8), (3, 2052, 4, 2), (6, 4096, 8, 16)])
+def test_layernorm_of_parts(T, d, S, rows):
+    from paper_2401_01728_amd import kernels as k
+    eps, grp = 1e-5, "LayerNorm / column sum / attention kernels, bar "
+    part32 = gen.normal_f32(4, 0, S * T * d, std=0.7).reshape(S, T, d)
+    res32 = gen.normal_f32(4, 1, T * d, mean=0.3, std=2.0).reshape(T, d)
+    (bias, bias64), (g, g64), (b, b64) = bf16_normal(4, 2, (d,)), bf16_normal(4, 3, (d,), mean=1.0, std=0.1), bf16_normal(4, 4, (d,))
+    x64 = part32.astype(np.float64).sum(0) + bias64 + res32
+    xsum, y, mean, rstd = k.layernorm_fwd_parts(dev(part32), bias, dev(res32), g, b, eps)
+    ref, (xh, r) = blocks.layernorm_fwd(x64, g64, b64, eps)
+    for got, want, tol in ((xsum, x64, 1e-5), (mean, x64.mean(-1), 1e-5), (rstd, r[:, 0], 1e-5), (y, ref, 4e-3)):
+        close(host64(got), want, tol, "k", group=grp + "%.0e" % tol)
+    x2, out16 = k.layernorm_fwd_parts(dev(part32), bias, dev(res32), None, None, eps)
+    assert torch.equal(x2, xsum) and torch.equal(out16, xsum.to(torch.bfloat16))
+    dyp32 = gen.normal_f32(4, 5, S * T * d, std=1e-2).reshape(S, T, d)
+    dres32 = gen.normal_f32(4, 6, T * d, std=1e-2).reshape(T, d)
+    dx, dx16, part = k.layernorm_bwd_parts(dev(dyp32), xsum, mean, rstd, g, dev(dres32), rows)
+    dx64, dg, db = blocks.layernorm_bwd(dyp32.astype(np.float64).sum(0), g64, (xh, r))
+    dx64 = dx64 + dres32
+    assert torch.equal(dx16, dx.to(torch.bfloat16))
+    for got, want in zip((host64(dx), *host64(part).sum(0)), (dx64, dg, db, dx64.sum(0))):
+        close(got, want, 1e-5, "k", group=grp + "1e-05")
+
+
 def _heads(t64, mb, S, H, dh):
     return t64.reshape(mb, S, H, dh).transpose(0, 2, 1, 3)
 
