@@ -10,6 +10,7 @@ rv_status rv_launch_update(float* w, const float* g, size_t n, float eta, void* 
 rv_status rv_launch_update_momentum(float* w, const float* g, float* v, size_t n, float eta, float mu, float wd,
                                     void* copy, int copy_kind, hipStream_t st);
 rv_status rv_launch_accumulate(float* acc, const float* g, size_t n, bool first, hipStream_t st);
+rv_status rv_launch_copy(float* dst, const float* src, size_t n, hipStream_t st);
 // master <- w and copy <- w in the version's type
 rv_status rv_launch_set(const float* w, size_t n, float* master, void* copy, int copy_kind, hipStream_t st);
 

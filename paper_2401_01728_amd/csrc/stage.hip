@@ -253,8 +253,7 @@ extern "C" rv_status rv_stage_profile_read(rv_stage* s, int* launches, float* me
 
 extern "C" rv_status rv_stage_get_params(const rv_stage* s, float* flat_out, size_t n) {
   if (!s || !flat_out || n != s->P || s->sync_dst >= 0) return RV_E_INVAL;
-  RV_HIP_TRY(hipMemcpyAsync(flat_out, s->master, n * 4, hipMemcpyDeviceToDevice, s->st));
-  return RV_OK;
+  return rv_launch_copy(flat_out, s->master, n, s->st);
 }
 
 extern "C" rv_status rv_stage_keep_grad(rv_stage* s, int on) {
@@ -266,8 +265,7 @@ extern "C" rv_status rv_stage_keep_grad(rv_stage* s, int on) {
 extern "C" rv_status rv_stage_last_grad(const rv_stage* s, float* flat_out, size_t n) {
   if (!s || !flat_out || n != s->P) return RV_E_INVAL;
   if (!s->grad_valid) return RV_E_INVAL;   // no backward yet, or its gradient was consumed where it was produced
-  RV_HIP_TRY(hipMemcpyAsync(flat_out, s->grad, n * 4, hipMemcpyDeviceToDevice, s->st));
-  return RV_OK;
+  return rv_launch_copy(flat_out, s->grad, n, s->st);
 }
 
 // delayed update (Eq. 2, or its momentum / weight-decay variant) of parameters [off, off+n)

@@ -61,3 +61,18 @@ def test_momentum_update(n):
     a, b = dev(w), dev(w); z = torch.zeros(n, device="cuda")
     rv.block_update_momentum(a, dg, z, eta, 0.0, 0.0); rv.block_update(b, dg, eta)
     assert torch.equal(a, b)
+
+
+# what the stage hands out: beyond 32 MB by a kernel of its own (a whole number of its tiles, and a tail that is no vector), into
+# memory at 16 bytes or not
+@pytest.mark.parametrize("d", [4096, 2896, 2895])
+@pytest.mark.parametrize("off", [0, 1])
+def test_parameters_handed_out(d, off):
+    import paper_2401_01728_amd as rv
+    st = rv.Stage.mlp([d, d], 1, 0, 0.1)
+    w = torch.randn(st.num_params, device="cuda")
+    st.set_params(w)
+    buf = torch.full((st.num_params + 8,), -3.0, device="cuda")
+    st.get_params(buf[off:off + st.num_params])
+    assert torch.equal(buf[off:off + st.num_params], w)
+    assert bool((buf[:off] == -3.0).all()) and bool((buf[off + st.num_params:] == -3.0).all())
