@@ -48,14 +48,14 @@ template <int DH> struct L {
   static constexpr int CHUNKS = TILE * DH / 8 / kThreads;  // 16-byte chunks per lane per tile
 };
 
-// global [TILE rows][DH] (row pitch ld elements) -> registers
+// global [TILE rows][DH] (rows ld elements apart, blocks of 32 columns bs: internal.h, rv_mat) -> registers
 template <int DH>
-__device__ __forceinline__ void g2r(u32x4* v, const uint16_t* __restrict__ g, int64_t ld) {
+__device__ __forceinline__ void g2r(u32x4* v, const uint16_t* __restrict__ g, int64_t ld, int64_t bs = 32) {
 #pragma unroll
   for (int i = 0; i < L<DH>::CHUNKS; ++i) {
     const int idx = threadIdx.x + kThreads * i;
     const int row = idx / (DH / 8), c = idx % (DH / 8);
-    v[i] = *reinterpret_cast<const u32x4*>(g + (int64_t)row * ld + c * 8);
+    v[i] = *reinterpret_cast<const u32x4*>(g + (int64_t)row * ld + (c >> 2) * bs + (c & 3) * 8);
   }
 }
 template <int DH, int PITCH>
@@ -114,11 +114,11 @@ __device__ __forceinline__ f32x16 zero16() {
 
 // owned-side fragments straight from global: rows tok0 + lane%32, all of DH
 template <int DH>
-__device__ __forceinline__ void load_owned(bf16x8* f, const uint16_t* __restrict__ g, int64_t ld) {
+__device__ __forceinline__ void load_owned(bf16x8* f, const uint16_t* __restrict__ g, int64_t ld, int64_t bs = 32) {
   const int l = threadIdx.x & 63;
 #pragma unroll
   for (int kk = 0; kk < DH / 16; ++kk)
-    f[kk] = *reinterpret_cast<const bf16x8*>(g + (int64_t)(l & 31) * ld + kk * 16 + (l >> 5) * 8);
+    f[kk] = *reinterpret_cast<const bf16x8*>(g + (int64_t)(l & 31) * ld + (kk >> 1) * bs + (kk & 1) * 16 + (l >> 5) * 8);
 }
 
 // acc + the product sum of two chunks of eight bf16
@@ -133,7 +133,7 @@ __device__ __forceinline__ float dot8(u32x4 a, u32x4 b, float acc) {
 
 // write a transposed accumulator (lane = row, registers = 4-column groups) as bf16
 template <int DH>
-__device__ __forceinline__ void store_owned(const f32x16* acc, float mul, uint16_t* __restrict__ g, int64_t ld) {
+__device__ __forceinline__ void store_owned(const f32x16* acc, float mul, uint16_t* __restrict__ g, int64_t ld, int64_t bs) {
   const int l = threadIdx.x & 63, grp = l >> 5;
 #pragma unroll
   for (int dt = 0; dt < DH / 32; ++dt)
@@ -142,7 +142,7 @@ __device__ __forceinline__ void store_owned(const f32x16* acc, float mul, uint16
       u32x2 o;
       o.x = rv_pack_bf16x2(acc[dt][4 * rg] * mul, acc[dt][4 * rg + 1] * mul);
       o.y = rv_pack_bf16x2(acc[dt][4 * rg + 2] * mul, acc[dt][4 * rg + 3] * mul);
-      *reinterpret_cast<u32x2*>(g + (int64_t)(l & 31) * ld + dt * 32 + 8 * rg + 4 * grp) = o;
+      *reinterpret_cast<u32x2*>(g + (int64_t)(l & 31) * ld + dt * bs + 8 * rg + 4 * grp) = o;
     }
 }
 
@@ -180,8 +180,7 @@ __device__ __forceinline__ void attn_block(int block, int H, int nseq, int& rank
 // ----------------------------------------------------------------------------------------
 template <int DH>
 __global__ __launch_bounds__(kThreads) void attn_fwd_kernel(const uint16_t* __restrict__ qkv, int64_t ld,
-                                                            uint16_t* __restrict__ out, int64_t ldo,
-                                                            float* __restrict__ lse2, int S, int d, int H,
+                                                            rv_mat out, float* __restrict__ lse2, int S, int d, int H,
                                                             int nseq, float c2) {
   extern __shared__ __align__(16) char smem[];
   constexpr int BUF = L<DH>::KC_BYTES + L<DH>::KM_BYTES;   // K tile (k-contiguous) + V tile (transpose-read)
@@ -283,7 +282,7 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_kernel(const uint16_t* __re
   }
   if (!active) return;
   const float tot = lsum + __shfl_xor(lsum, 32, 64);
-  store_owned<DH>(o, 1.0f / tot, out + (tok0 + q0) * ldo + h * DH, ldo);
+  store_owned<DH>(o, 1.0f / tot, out.p + rv_at(out, tok0 + q0, h * DH), out.ld, out.bs);
   if (grp == 0) lse2[((int64_t)b * H + h) * S + qi] = m + __builtin_amdgcn_logf(tot);   // v_log_f32 is log2
 }
 
@@ -294,10 +293,11 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_kernel(const uint16_t* __re
 // ----------------------------------------------------------------------------------------
 struct BwdArgs {
   const uint16_t* qkv; int64_t ld;
-  const uint16_t* dout; const uint16_t* out; int64_t ldo;
+  const uint16_t* dout; int64_t ldo;
+  rv_mat out;
   const float* lse2;
   float* D;
-  uint16_t* dqkv;
+  rv_mat dqkv;
   int S, d, H, nseq;
   float c2, scale;
   float* colpart;
@@ -306,7 +306,7 @@ template <int DH, bool OWN_D>
 __device__ __forceinline__ void bwd_kv_body(const BwdArgs& a, int block, char* smem) {
   const uint16_t* __restrict__ qkv = a.qkv;
   const uint16_t* __restrict__ dout = a.dout;
-  uint16_t* __restrict__ dqkv = a.dqkv;
+  const rv_mat dqkv = a.dqkv;
   const int64_t ld = a.ld, ldo = a.ldo;
   const int S = a.S, d = a.d, H = a.H;
   const float c2 = a.c2, scale = a.scale;
@@ -324,7 +324,7 @@ __device__ __forceinline__ void bwd_kv_body(const BwdArgs& a, int block, char* s
   const int64_t tok0 = (int64_t)b * S;
   const uint16_t* Qg = qkv + tok0 * ld + h * DH;
   const uint16_t* Og = dout + tok0 * ldo + h * DH;
-  const uint16_t* Pg = a.out + tok0 * ldo + h * DH;
+  const uint16_t* Pg = a.out.p + rv_at(a.out, tok0, h * DH);
   const float* lse_g = a.lse2 + ((int64_t)b * H + h) * S;
   const float* D_g = a.D + ((int64_t)b * H + h) * S;
 
@@ -348,7 +348,7 @@ __device__ __forceinline__ void bwd_kv_body(const BwdArgs& a, int block, char* s
     const int i0 = it * TILE;
     g2r<DH>(rq, Qg + (int64_t)i0 * ld, ld);
     g2r<DH>(ro, Og + (int64_t)i0 * ldo, ldo);
-    if (OWN_D) g2r<DH>(rp, Pg + (int64_t)i0 * ldo, ldo);
+    if (OWN_D) g2r<DH>(rp, Pg + (int64_t)i0 * a.out.ld, a.out.ld, a.out.bs);
     if (threadIdx.x < TILE) rstat = lse_g[i0 + threadIdx.x];
     else if (!OWN_D && threadIdx.x < 2 * TILE) rstat = D_g[i0 + threadIdx.x - TILE];
   };
@@ -420,8 +420,8 @@ __device__ __forceinline__ void bwd_kv_body(const BwdArgs& a, int block, char* s
     __syncthreads();
   }
   if (!active) return;
-  store_owned<DH>(dk, scale, dqkv + (tok0 + j0) * ld + d + h * DH, ld);
-  store_owned<DH>(dv, 1.0f, dqkv + (tok0 + j0) * ld + 2 * d + h * DH, ld);
+  store_owned<DH>(dk, scale, dqkv.p + rv_at(dqkv, tok0 + j0, d + h * DH), dqkv.ld, dqkv.bs);
+  store_owned<DH>(dv, 1.0f, dqkv.p + rv_at(dqkv, tok0 + j0, 2 * d + h * DH), dqkv.ld, dqkv.bs);
   if (a.colpart) {   // partial row (sequence, 32-key block) of the k and v thirds of the qkv bias gradient
     float* prow = a.colpart + ((tok0 + j0) / WROWS) * ld;
     colsum_owned<DH>(dk, scale, prow + d + h * DH);
@@ -437,7 +437,7 @@ template <int DH, bool STORE_D>
 __device__ __forceinline__ void bwd_q_body(const BwdArgs& a, int block, char* smem) {
   const uint16_t* __restrict__ qkv = a.qkv;
   const uint16_t* __restrict__ dout = a.dout;
-  uint16_t* __restrict__ dqkv = a.dqkv;
+  const rv_mat dqkv = a.dqkv;
   const int64_t ld = a.ld, ldo = a.ldo;
   const int S = a.S, d = a.d, H = a.H;
   const float c2 = a.c2, scale = a.scale;
@@ -466,7 +466,7 @@ __device__ __forceinline__ void bwd_q_body(const BwdArgs& a, int block, char* sm
     // D_i = sum_dh dO[i,dh] * O[i,dh]: the wave holds its rows of dO as fragments already; the
     // rows of O come in the same layout.
     bf16x8 oo[DH / 16];
-    load_owned<DH>(oo, a.out + (tok0 + q0) * ldo + h * DH, ldo);
+    load_owned<DH>(oo, a.out.p + rv_at(a.out, tok0 + q0, h * DH), a.out.ld, a.out.bs);
 #pragma unroll
     for (int kk = 0; kk < DH / 16; ++kk) D_i = dot8(__builtin_bit_cast(u32x4, oo[kk]), __builtin_bit_cast(u32x4, of[kk]), D_i);
     D_i += __shfl_xor(D_i, 32, 64);
@@ -530,7 +530,7 @@ __device__ __forceinline__ void bwd_q_body(const BwdArgs& a, int block, char* sm
     __syncthreads();
   }
   if (!active) return;
-  store_owned<DH>(dq, scale, dqkv + (tok0 + q0) * ld + h * DH, ld);
+  store_owned<DH>(dq, scale, dqkv.p + rv_at(dqkv, tok0 + q0, h * DH), dqkv.ld, dqkv.bs);
   if (a.colpart) colsum_owned<DH>(dq, scale, a.colpart + ((tok0 + q0) / WROWS) * ld + h * DH);   // the q third
 }
 
@@ -567,9 +567,9 @@ bool shape_ok(int mb, int S, int d, int H) {
 
 }  // namespace
 
-rv_status rv_attn_fwd(const uint16_t* qkv, uint16_t* out, float* lse2, int mb, int S, int d, int H,
+rv_status rv_attn_fwd(const uint16_t* qkv, rv_mat out, float* lse2, int mb, int S, int d, int H,
                       hipStream_t st) {
-  if (!qkv || !out || !lse2 || !shape_ok(mb, S, d, H)) return RV_E_INVAL;
+  if (!qkv || !out.p || !lse2 || !shape_ok(mb, S, d, H)) return RV_E_INVAL;
   const int dh = d / H;
   const float c2 = 1.4426950408889634f / sqrtf((float)dh);
   const int nwg = ((S + BROWS - 1) / BROWS) * H * mb;
@@ -577,13 +577,13 @@ rv_status rv_attn_fwd(const uint16_t* qkv, uint16_t* out, float* lse2, int mb, i
   if (dh == 64) {
     constexpr int smem = 2 * (L<64>::KC_BYTES + L<64>::KM_BYTES);
     RV_TRY(set_smem(attn_fwd_kernel<64>, smem));
-    hipLaunchKernelGGL(attn_fwd_kernel<64>, grid, dim3(kThreads), smem, st, qkv, (int64_t)3 * d, out, (int64_t)d,
+    hipLaunchKernelGGL(attn_fwd_kernel<64>, grid, dim3(kThreads), smem, st, qkv, (int64_t)3 * d, out,
                        lse2, S, d, H, mb, c2);
   } else {
     constexpr int smem = 2 * (L<128>::KC_BYTES + L<128>::KM_BYTES);
     RV_TRY(set_smem(attn_fwd_kernel<128>, smem));
     hipLaunchKernelGGL(attn_fwd_kernel<128>, grid, dim3(kThreads), smem, st, qkv, (int64_t)3 * d, out,
-                       (int64_t)d, lse2, S, d, H, mb, c2);
+                       lse2, S, d, H, mb, c2);
   }
   return rv_launch_status();
 }
@@ -620,27 +620,27 @@ rv_status launch_bwd(const BwdArgs& a, hipStream_t st) {
 }
 }  // namespace
 
-rv_status rv_attn_bwd(const uint16_t* qkv, const uint16_t* out, const uint16_t* dout, const float* lse2,
-                      float* Dbuf, uint16_t* dqkv, int mb, int S, int d, int H, hipStream_t st, float* colpart) {
-  if (!qkv || !out || !dout || !lse2 || !Dbuf || !dqkv || !shape_ok(mb, S, d, H)) return RV_E_INVAL;
+rv_status rv_attn_bwd(const uint16_t* qkv, rv_mat out, const uint16_t* dout, const float* lse2,
+                      float* Dbuf, rv_mat dqkv, int mb, int S, int d, int H, hipStream_t st, float* colpart) {
+  if (!qkv || !out.p || !dout || !lse2 || !Dbuf || !dqkv.p || !shape_ok(mb, S, d, H)) return RV_E_INVAL;
   const int dh = d / H;
   const float scale = 1.0f / sqrtf((float)dh);
-  const BwdArgs a = {qkv, (int64_t)3 * d, dout, out, (int64_t)d, lse2, Dbuf, dqkv, S, d, H, mb,
+  const BwdArgs a = {qkv, (int64_t)3 * d, dout, (int64_t)d, out, lse2, Dbuf, dqkv, S, d, H, mb,
                      1.4426950408889634f * scale, scale, colpart};
   return dh == 64 ? launch_bwd<64>(a, st) : launch_bwd<128>(a, st);
 }
 
 extern "C" rv_status rv_k_attention_fwd(const void* qkv, void* out, float* lse2, int microbatch, int seq,
                                         int d_model, int n_heads, void* stream) {
-  return rv_attn_fwd((const uint16_t*)qkv, (uint16_t*)out, lse2, microbatch, seq, d_model, n_heads,
+  return rv_attn_fwd((const uint16_t*)qkv, rv_rows(out, d_model), lse2, microbatch, seq, d_model, n_heads,
                      (hipStream_t)stream);
 }
 
 extern "C" rv_status rv_k_attention_bwd(const void* qkv, const void* out, const void* dout, const float* lse2,
                                         float* dscratch, void* dqkv, int microbatch, int seq, int d_model,
                                         int n_heads, void* stream) {
-  return rv_attn_bwd((const uint16_t*)qkv, (const uint16_t*)out, (const uint16_t*)dout, lse2, dscratch,
-                     (uint16_t*)dqkv, microbatch, seq, d_model, n_heads, (hipStream_t)stream);
+  return rv_attn_bwd((const uint16_t*)qkv, rv_rows(out, d_model), (const uint16_t*)dout, lse2, dscratch,
+                     rv_rows(dqkv, 3 * d_model), microbatch, seq, d_model, n_heads, (hipStream_t)stream);
 }
 
 // ---- the backward for callers that cannot allocate ---------------------------------------
@@ -681,6 +681,6 @@ extern "C" rv_status rv_k_attention_bwd_static(const void* qkv, const void* out,
   RV_TRY(static_scratch(&D));
   // every row of D that a second launch reads is written by the first one in this call:
   // nothing of the previous call's contents is used, so nothing has to be cleared
-  return rv_attn_bwd((const uint16_t*)qkv, (const uint16_t*)out, (const uint16_t*)dout, lse2, D,
-                     (uint16_t*)dqkv, microbatch, seq, d_model, n_heads, (hipStream_t)stream);
+  return rv_attn_bwd((const uint16_t*)qkv, rv_rows(out, d_model), (const uint16_t*)dout, lse2, D,
+                     rv_rows(dqkv, 3 * d_model), microbatch, seq, d_model, n_heads, (hipStream_t)stream);
 }

@@ -34,10 +34,11 @@ struct RepTable {
   float* p[RV_MAX_C];
 };
 
-// where the mean goes as a weight version: kind 0 nowhere, 1 bf16, 2 fp32
+// where the mean goes as a weight version: kind 0 nowhere, 2 fp32, 3 bf16 through the map
 struct Versions {
   void* p[RV_MAX_C];
   int kind;
+  rv_ver_map map;
 };
 
 constexpr int kThreads = 256;
@@ -153,11 +154,12 @@ __device__ __forceinline__ void tile_fast(const RepTable& tab, const Versions& v
     for (int c = 0; c < C; ++c)
       __builtin_nontemporal_store(a, reinterpret_cast<f4_u*>(tab.p[c] + e));
   }
-  if (ver.kind == 1) {
+  if (ver.kind == 3) {
     u2 h;
     h.x = rv_pack_bf16x2(a.x, a.y); h.y = rv_pack_bf16x2(a.z, a.w);
+    const uint64_t at = rv_ver_at(ver.map, base, e);
 #pragma unroll
-    for (int c = 0; c < C; ++c) *reinterpret_cast<u2*>((uint16_t*)ver.p[c] + e) = h;
+    for (int c = 0; c < C; ++c) *reinterpret_cast<u2*>((uint16_t*)ver.p[c] + at) = h;
   } else if (ver.kind == 2) {
 #pragma unroll
     for (int c = 0; c < C; ++c) __builtin_nontemporal_store(a, reinterpret_cast<f4*>((float*)ver.p[c] + e));
@@ -195,7 +197,7 @@ __global__ __launch_bounds__(kThreads) void average_kernel(RepTable tab, Version
                                                            const float* grad, int gr, float eta,
                                                            DivConsts dc, RingOffsets ro) {
   const int C = CT > 0 ? CT : Crt;
-  const uint64_t base = (uint64_t)blockIdx.x * kTile, last = base + kTile - 1;
+  const uint64_t base = (uint64_t)(ver.kind == 3 ? rv_ver_tile(blockIdx.x, gridDim.x) : blockIdx.x) * kTile, last = base + kTile - 1;
   int j;
   uint64_t chunk_end;
   if (EXPL) {
@@ -220,7 +222,7 @@ __global__ __launch_bounds__(kThreads) void average_kernel(RepTable tab, Version
     if (write_back)
       for (int c = 0; c < C; ++c) tab.p[c][i] = m;
     for (int c = 0; ver.kind && c < C; ++c) {
-      if (ver.kind == 1) ((uint16_t*)ver.p[c])[i] = rv_f32_to_bf16(m);
+      if (ver.kind == 3) ((uint16_t*)ver.p[c])[rv_ver_at(ver.map, base, i)] = rv_f32_to_bf16(m);
       else ((float*)ver.p[c])[i] = m;
     }
   }
@@ -253,7 +255,7 @@ void launch_for(int C, const A&... a) {   // CT = C up to 16
 
 static rv_status average_impl(float* const* replicas, int C, size_t n, int R, const RingOffsets* ro,
                               float* mean_out, int write_back, const float* grad, int grad_replica, float eta,
-                              void* const* versions, int ver_kind, void* stream) {
+                              void* const* versions, int ver_kind, const rv_ver_map& map, void* stream) {
   if (replicas == nullptr || C < 1 || C > RV_MAX_C || R < 1 || R > RV_MAX_R || n == 0)
     return RV_E_INVAL;
   if (mean_out == nullptr && !write_back) return RV_E_INVAL;
@@ -262,6 +264,7 @@ static rv_status average_impl(float* const* replicas, int C, size_t n, int R, co
   RepTable tab = {};
   Versions ver = {};
   ver.kind = ver_kind;
+  ver.map = map;
   for (int c = 0; c < C; ++c) {
     if (replicas[c] == nullptr) return RV_E_INVAL;
     for (int k = 0; k < c; ++k)
@@ -274,15 +277,15 @@ static rv_status average_impl(float* const* replicas, int C, size_t n, int R, co
   return rv_launch_status();
 }
 
-rv_status rv_average_publish(float* const* masters, void* const* versions, int ver_kind, int C, size_t n, int R, const float* grad,
-                             int grad_replica, float eta, hipStream_t st) {
-  return average_impl(masters, C, n, R, nullptr, nullptr, 1, grad, grad_replica, eta, versions, ver_kind, st);
+rv_status rv_average_publish(float* const* masters, void* const* versions, int ver_kind, const rv_ver_map& map, int C, size_t n, int R,
+                             const float* grad, int grad_replica, float eta, hipStream_t st) {
+  return average_impl(masters, C, n, R, nullptr, nullptr, 1, grad, grad_replica, eta, versions, ver_kind, map, st);
 }
 
 extern "C" rv_status rv_cluster_average(float* const* replicas, int C, size_t n, int R,
                                         float* mean_out, int write_back, const float* grad,
                                         int grad_replica, float eta, void* stream) {
-  return average_impl(replicas, C, n, R, nullptr, mean_out, write_back, grad, grad_replica, eta, nullptr, 0, stream);
+  return average_impl(replicas, C, n, R, nullptr, mean_out, write_back, grad, grad_replica, eta, nullptr, 0, rv_ver_map(), stream);
 }
 
 extern "C" rv_status rv_cluster_average_v(float* const* replicas, int C, size_t n, const int64_t* ring_offsets,
@@ -295,5 +298,5 @@ extern "C" rv_status rv_cluster_average_v(float* const* replicas, int C, size_t 
     if (r > 0 && ring_offsets[r] < ring_offsets[r - 1]) return RV_E_INVAL;
     ro.off[r] = (uint64_t)ring_offsets[r];
   }
-  return average_impl(replicas, C, n, R, &ro, mean_out, write_back, grad, grad_replica, eta, nullptr, 0, stream);
+  return average_impl(replicas, C, n, R, &ro, mean_out, write_back, grad, grad_replica, eta, nullptr, 0, rv_ver_map(), stream);
 }

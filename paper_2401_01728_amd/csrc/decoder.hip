@@ -67,6 +67,11 @@ rv_status rv_dec_plan(rv_stage* s) {
   p->w2 = o; o += (size_t)f * d; p->b2 = o; o += d;
   p->per_block = o;
   s->P = o * p->L;
+  // the matrices of a weight version lie in blocks of 32 columns
+  const size_t at[4] = {p->wqkv, p->wo, p->w1, p->w2};
+  const int64_t rows[4] = {d, d, d, f}, cols[4] = {3 * d, d, f, d};
+  s->ver_map.per_block = (uint32_t)o;
+  for (int k = 0; k < 4; ++k) { s->ver_map.at[k] = (uint32_t)at[k]; s->ver_map.rows[k] = (uint32_t)rows[k]; s->ver_map.cols[k] = (uint32_t)cols[k]; }
   const size_t T = p->T;
   size_t b = 0;
   p->s_x = b; b += align_up(T * d * 4);
@@ -130,26 +135,30 @@ void rv_dec_free(rv_stage* s) {
 
 namespace {
 
-rv_status gemm(int sharing, hipStream_t st, const void* A, int64_t lda, int akm, const void* B, int64_t ldb, int bkm, int M,
-               int N, int K, int epi, void* out, int64_t ldo, void* out2 = nullptr, const void* bias = nullptr,
-               const float* resid = nullptr, const void* zin = nullptr, float* colpart = nullptr,
-               int* colpart_rows = nullptr) {
+// out = A B: A [M,K], B a weight [K,N] (wt 0) or its transpose, W [N,K] (wt 1); the outputs that are operands
+// later, GELU(z) and dz, leave in blocks of columns
+rv_status gemm(int sharing, hipStream_t st, rv_mat A, const void* W, int wt, int M, int N, int K, int epi, void* out, int64_t ldo,
+               void* out2 = nullptr, const void* bias = nullptr, const float* resid = nullptr, const void* zin = nullptr,
+               float* colpart = nullptr, int* colpart_rows = nullptr) {
   rv_gemm_args g;
   g.colpart = colpart;
   g.sharing = sharing;
-  g.A = (const uint16_t*)A; g.lda = lda; g.a_kmajor = akm;
-  g.B = (const uint16_t*)B; g.ldb = ldb; g.b_kmajor = bkm;
+  g.A = A.p; g.lda = A.ld; g.a_bs = A.bs;
+  const rv_mat B = rv_blocks(W, wt ? N : K);
+  g.B = B.p; g.ldb = B.ld; g.b_bs = B.bs; g.b_kmajor = !wt;
   g.M = M; g.N = N; g.K = K; g.epi = epi; g.out = out; g.ldo = ldo; g.out2 = out2;
+  if (epi == RV_EPI_BF16_BIAS_GELU || epi == RV_EPI_BF16_DGELU) g.bsv = (int64_t)M * 32;
   g.bias = (const uint16_t*)bias; g.resid = resid; g.ldr = ldo; g.zin = (const uint16_t*)zin;
   const rv_status rc = rv_gemm_bf16(g, st);
   if (colpart_rows) *colpart_rows = g.colpart_rows;
   return rc;
 }
 
-rv_status gemm_part(const rv_part_form& form, hipStream_t st, const void* A, int64_t lda, const void* B, int64_t ldb, int bkm, int M,
-                    int N, int K, float* part) {
+rv_status gemm_part(const rv_part_form& form, hipStream_t st, rv_mat A, const void* W, int wt, int M, int N, int K, float* part) {
   rv_gemm_args g;
-  g.A = (const uint16_t*)A; g.lda = lda; g.B = (const uint16_t*)B; g.ldb = ldb; g.b_kmajor = bkm;
+  g.A = A.p; g.lda = A.ld; g.a_bs = A.bs;
+  const rv_mat B = rv_blocks(W, wt ? N : K);
+  g.B = B.p; g.ldb = B.ld; g.b_bs = B.bs; g.b_kmajor = !wt;
   g.M = M; g.N = N; g.K = K; g.tile = form.tile;
   return rv_gemm_part(g, form.S, part, st);
 }
@@ -163,12 +172,12 @@ rv_status forward_block(const rv_stage* s, const rv_slot& slot, const void* in, 
   char* sb = slot.base + (size_t)l * p.blk_bytes;
   float* x = (float*)(sb + p.s_x);
   float* x1 = (float*)(sb + p.s_x1);
-  uint16_t* u = (uint16_t*)(sb + p.s_u);
+  const rv_mat u = rv_blocks(sb + p.s_u, T);
   uint16_t* qkv = (uint16_t*)(sb + p.s_qkv);
-  uint16_t* a = (uint16_t*)(sb + p.s_a);
-  uint16_t* v2 = (uint16_t*)(sb + p.s_v2);
+  const rv_mat a = rv_blocks(sb + p.s_a, T);
+  const rv_mat v2 = rv_blocks(sb + p.s_v2, T);
   uint16_t* z = (uint16_t*)(sb + p.s_z);
-  uint16_t* g = (uint16_t*)(sb + p.s_g);
+  const rv_mat g = rv_blocks(sb + p.s_g, T);
   float* pf = (float*)(s->work + p.w_pf);
   if (l == 0)
     RV_TRY(rv_ln_fwd(in, 1, x, w + p.ln1g, w + p.ln1b, u, (float*)(sb + p.s_m1), (float*)(sb + p.s_r1), T, d, s->ln_eps, st));
@@ -178,29 +187,29 @@ rv_status forward_block(const rv_stage* s, const rv_slot& slot, const void* in, 
   else
     RV_TRY(rv_ln_fwd(x, 0, nullptr, w + p.ln1g, w + p.ln1b, u, (float*)(sb + p.s_m1), (float*)(sb + p.s_r1), T, d,
                      s->ln_eps, st));
-  RV_TRY(gemm(sh, st, u, d, 0, w + p.wqkv, 3 * d, 1, T, 3 * d, d, RV_EPI_BF16_BIAS, qkv, 3 * d, nullptr, w + p.bqkv));
+  RV_TRY(gemm(sh, st, u, w + p.wqkv, 0, T, 3 * d, d, RV_EPI_BF16_BIAS, qkv, 3 * d, nullptr, w + p.bqkv));
   RV_TRY(rv_attn_fwd(qkv, a, (float*)(sb + p.s_lse), p.mb, p.S, d, p.H, st));
   if (p.f_wo.S > 1) {
-    RV_TRY(gemm_part(p.f_wo, st, a, d, w + p.wo, d, 1, T, d, d, pf));
+    RV_TRY(gemm_part(p.f_wo, st, a, w + p.wo, 0, T, d, d, pf));
     RV_TRY(rv_ln_fwd_parts(pf, p.f_wo.S, w + p.bo, x, x1, w + p.ln2g, w + p.ln2b, v2, (float*)(sb + p.s_m2), (float*)(sb + p.s_r2),
                            nullptr, T, d, s->ln_eps, st));
   } else {
-    RV_TRY(gemm(sh, st, a, d, 0, w + p.wo, d, 1, T, d, d, RV_EPI_F32_BIAS_RESID, x1, d, nullptr, w + p.bo, x));
+    RV_TRY(gemm(sh, st, a, w + p.wo, 0, T, d, d, RV_EPI_F32_BIAS_RESID, x1, d, nullptr, w + p.bo, x));
     RV_TRY(rv_ln_fwd(x1, 0, nullptr, w + p.ln2g, w + p.ln2b, v2, (float*)(sb + p.s_m2), (float*)(sb + p.s_r2), T, d,
                      s->ln_eps, st));
   }
-  RV_TRY(gemm(sh, st, v2, d, 0, w + p.w1, f, 1, T, f, d, RV_EPI_BF16_BIAS_GELU, z, f, g, w + p.b1));
+  RV_TRY(gemm(sh, st, v2, w + p.w1, 0, T, f, d, RV_EPI_BF16_BIAS_GELU, z, f, g.p, w + p.b1));
   if (p.f_w2.S > 1) {
-    RV_TRY(gemm_part(p.f_w2, st, g, f, w + p.w2, d, 1, T, d, f, pf));
+    RV_TRY(gemm_part(p.f_w2, st, g, w + p.w2, 0, T, d, f, pf));
     if (l + 1 < p.L) return RV_OK;   // the next block's LayerNorm adds the pieces
-    return rv_ln_fwd_parts(pf, p.f_w2.S, w + p.b2, x1, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, (uint16_t*)out, T, d,
+    return rv_ln_fwd_parts(pf, p.f_w2.S, w + p.b2, x1, nullptr, nullptr, nullptr, rv_mat{}, nullptr, nullptr, (uint16_t*)out, T, d,
                            s->ln_eps, st);
   }
   if (l + 1 < p.L) {
     float* xn = (float*)(slot.base + (size_t)(l + 1) * p.blk_bytes + p.s_x);
-    return gemm(sh, st, g, f, 0, w + p.w2, d, 1, T, d, f, RV_EPI_F32_BIAS_RESID, xn, d, nullptr, w + p.b2, x1);
+    return gemm(sh, st, g, w + p.w2, 0, T, d, f, RV_EPI_F32_BIAS_RESID, xn, d, nullptr, w + p.b2, x1);
   }
-  return gemm(sh, st, g, f, 0, w + p.w2, d, 1, T, d, f, RV_EPI_F32_BIAS_RESID_BF16, s->work + p.w_ytmp, d, out, w + p.b2, x1);
+  return gemm(sh, st, g, w + p.w2, 0, T, d, f, RV_EPI_F32_BIAS_RESID_BF16, s->work + p.w_ytmp, d, out, w + p.b2, x1);
 }
 
 // The backward of one microbatch, issued block by block from the last: begin, block(L-1) .. block(0), end.
@@ -226,7 +235,7 @@ struct Backward {
   hipStream_t st, ws;          // the chain's stream, the side stream
   int sh;
   uint16_t* vdst = nullptr;
-  const uint16_t* dres16 = nullptr;   // bf16 gradient of the current block's output
+  rv_mat dres16 = {};   // bf16 gradient of the current block's output
   // the side work that has come into being and not left yet
   rv_reduce_job sums[RV_REDUCE_MAX];
   rv_gemm_args prods[RV_GEMM_GROUP_MAX];
@@ -286,17 +295,17 @@ struct Backward {
   }
 
   // dy = A W^T (A [T,K], W [d,K]) and the backward of the LayerNorm in front of that Linear, joined with the residual branch
-  rv_status product_and_norm(const rv_part_form& form, const uint16_t* A, const uint16_t* W, int K, const float* x, const float* mean,
-                             const float* rstd, const uint16_t* gamma, uint16_t* dx16, float* part) {
+  rv_status product_and_norm(const rv_part_form& form, rv_mat A, const uint16_t* W, int K, const float* x, const float* mean,
+                             const float* rstd, const uint16_t* gamma, rv_mat dx16, float* part) {
     const int T = p.T, d = p.d, rows = rv_ln_bwd_rows(T, d);
     float* dres = (float*)(s->work + p.w_dres);
     if (form.S > 1) {
       float* pb = (float*)(s->work + p.w_pb);
-      RV_TRY(gemm_part(form, st, A, K, W, K, 0, T, d, K, pb));
+      RV_TRY(gemm_part(form, st, A, W, 1, T, d, K, pb));
       return rv_ln_bwd_parts_in(pb, form.S, x, mean, rstd, gamma, dres, dres, dx16, part, T, d, st, rows);
     }
     uint16_t* dtmp = (uint16_t*)(s->work + p.w_dtmp);
-    RV_TRY(gemm(sh, st, A, K, 0, W, K, 0, T, d, K, RV_EPI_BF16, dtmp, d));
+    RV_TRY(gemm(sh, st, A, W, 1, T, d, K, RV_EPI_BF16, dtmp, d));
     return rv_ln_bwd(dtmp, x, mean, rstd, gamma, dres, dres, dx16, part, T, d, st, rows);
   }
 
@@ -307,15 +316,15 @@ struct Backward {
     // gradient of the last block's output: fp32 copy for the residual path, bf16 as operand
     // (summed over tokens it is also the gradient of the last block's b2: partial sums on the way)
     float* part_dy = (float*)(s->work + p.w_part_dy);
-    dres16 = (const uint16_t*)grad_out;
+    dres16 = rv_rows(grad_out, d);
     if (rv_overlap(grad_out, (size_t)T * d * 2, grad_in, (size_t)T * d * 2)) {
       // the first block's backward writes grad_in without waiting for the side stream, where the last block's dW2
       // still reads the arriving gradient: that goes to its place among the gradients of the other blocks first
       uint16_t* dy = dy_buf(p.L - 1);
       RV_HIP_TRY(hipMemcpyAsync(dy, grad_out, (size_t)T * d * 2, hipMemcpyDeviceToDevice, st));
-      dres16 = dy;
+      dres16 = rv_rows(dy, d);
     }
-    RV_TRY(rv_widen_colsum(dres16, (float*)(s->work + p.w_dres), part_dy, T, d, st));
+    RV_TRY(rv_widen_colsum(dres16.p, (float*)(s->work + p.w_dres), part_dy, T, d, st));
     colsum(part_dy, rv_widen_parts(T), d, d, s->grad + (size_t)(p.L - 1) * p.per_block + p.b2);
     // When the four weight-gradient products of a block go to the side stream.  Launch points:
     // 0 behind the GELU' product (dz exists: dW2 and dW1 can run), 1 behind the second LayerNorm's
@@ -350,9 +359,9 @@ struct Backward {
     // block l may overwrite what the side work of block l+2 read only after that is done
     if (!p.deep && l + 2 < p.L) RV_HIP_TRY(hipStreamWaitEvent(st, s->ev_wg_done[par], 0));
     char* set_l = set(l);
-    uint16_t* dx1_16 = (uint16_t*)(set_l + p.o_dx1_16);          // bf16 dx1 of this block
-    uint16_t* dz = (uint16_t*)(set_l + p.o_dz);
-    uint16_t* dqkv = (uint16_t*)(set_l + p.o_dqkv);
+    const rv_mat dx1_16 = rv_blocks(set_l + p.o_dx1_16, T);      // bf16 dx1 of this block
+    const rv_mat dz = rv_blocks(set_l + p.o_dz, T);
+    const rv_mat dqkv = rv_blocks(set_l + p.o_dqkv, T);
     float* part2 = (float*)(set_l + p.o_part_ln[0]);             // LayerNorm 2 / 1 partial sums
     float* part1 = (float*)(set_l + p.o_part_ln[1]);
     const uint16_t* w = (const uint16_t*)s->ver[slot.ver] + (size_t)l * p.per_block;
@@ -360,19 +369,20 @@ struct Backward {
     const char* sb = slot.base + (size_t)l * p.blk_bytes;
     const float* x = (const float*)(sb + p.s_x);
     const float* x1 = (const float*)(sb + p.s_x1);
-    const uint16_t* u = (const uint16_t*)(sb + p.s_u);
+    const rv_mat u = rv_blocks(sb + p.s_u, T);
     const uint16_t* qkv = (const uint16_t*)(sb + p.s_qkv);
-    const uint16_t* a = (const uint16_t*)(sb + p.s_a);
-    const uint16_t* v2 = (const uint16_t*)(sb + p.s_v2);
+    const rv_mat a = rv_blocks(sb + p.s_a, T);
+    const rv_mat v2 = rv_blocks(sb + p.s_v2, T);
     const uint16_t* z = (const uint16_t*)(sb + p.s_z);
-    const uint16_t* g = (const uint16_t*)(sb + p.s_g);
+    const rv_mat g = rv_blocks(sb + p.s_g, T);
     rv_gemm_args wg[4];
-    auto wgrad = [&](int k, const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, int M, int N, float* out) {
-      wg[k].A = A; wg[k].lda = lda; wg[k].a_kmajor = 1; wg[k].B = B; wg[k].ldb = ldb; wg[k].b_kmajor = 1;
+    auto wgrad = [&](int k, rv_mat A, rv_mat B, int M, int N, float* out) {
+      wg[k].A = A.p; wg[k].lda = A.ld; wg[k].a_bs = A.bs; wg[k].a_kmajor = 1;
+      wg[k].B = B.p; wg[k].ldb = B.ld; wg[k].b_bs = B.bs; wg[k].b_kmajor = 1;
       wg[k].M = M; wg[k].N = N; wg[k].K = T; wg[k].epi = RV_EPI_F32; wg[k].out = out; wg[k].ldo = N;
       if (s->fused) {   // Eq. 2 in the product's epilogue: master and new weight version at the same offset
         const size_t off = (size_t)(out - s->grad);
-        wg[k].upd_w = s->master + off; wg[k].upd_ver = vdst + off; wg[k].upd_eta = s->eta;
+        wg[k].upd_w = s->master + off; wg[k].upd_ver = vdst + off; wg[k].bsv = (int64_t)M * 32; wg[k].upd_eta = s->eta;
         wg[k].store_out = s->keep_grad;
       }
     };
@@ -393,13 +403,13 @@ struct Backward {
     // d 1600, 8192 tokens).
     const bool leaves = !p.deep || l % p.group == 0;
     // feed-forward half
-    wgrad(0, g, f, dres16, d, f, d, gl + p.w2);                                                      // dW2 = g^T dy
+    wgrad(0, g, dres16, f, d, gl + p.w2);                                                      // dW2 = g^T dy
     // dz = (dy W2^T) * GELU'(z); its column sums (the b1 gradient) leave the same epilogue as partial rows
     float* part_dz = (float*)(set_l + p.o_part_dz);
     int dz_parts = 0;
-    RV_TRY(gemm(sh, st, dres16, d, 0, w + p.w2, d, 0, T, f, d, RV_EPI_BF16_DGELU, dz, f, nullptr, nullptr, nullptr, z,
+    RV_TRY(gemm(sh, st, dres16, w + p.w2, 1, T, f, d, RV_EPI_BF16_DGELU, dz.p, f, nullptr, nullptr, nullptr, z,
                 part_dz, &dz_parts));
-    wgrad(1, v2, d, dz, f, d, f, gl + p.w1);                                                         // dW1 = v2^T dz
+    wgrad(1, v2, dz, d, f, gl + p.w1);                                                         // dW1 = v2^T dz
     colsum(part_dz, dz_parts, f, f, gl + p.b1);
     take(0);
     if (pair_first && leaves) {
@@ -415,18 +425,18 @@ struct Backward {
     colsum(part2 + d, ln_parts, 3 * (int64_t)d, d, gl + p.ln2b);
     colsum(part2 + 2 * d, ln_parts, 3 * (int64_t)d, d, gl + p.bo);                                     // dbo = sum dx1
     // attention half
-    wgrad(2, a, d, dx1_16, d, d, d, gl + p.wo);                                                      // dWo = a^T dx1
+    wgrad(2, a, dx1_16, d, d, gl + p.wo);                                                      // dWo = a^T dx1
     take(1);
     if (early && !p.deep) {
       RV_TRY(side_begin());
       RV_TRY(send_sums(ws));
       RV_TRY(send_prods());
     }
-    RV_TRY(gemm(sh, st, dx1_16, d, 0, w + p.wo, d, 0, T, d, d, RV_EPI_BF16, dtmp, d));                   // da = dx1 Wo^T
+    RV_TRY(gemm(sh, st, dx1_16, w + p.wo, 1, T, d, d, RV_EPI_BF16, dtmp, d));                   // da = dx1 Wo^T
     // (the attention backward also leaves partial column sums of dqkv: the qkv bias gradient)
     float* part_qkv = (float*)(set_l + p.o_part_qkv);
     RV_TRY(rv_attn_bwd(qkv, a, dtmp, (const float*)(sb + p.s_lse), Dbuf, dqkv, p.mb, p.S, d, p.H, st, part_qkv));
-    wgrad(3, u, d, dqkv, 3 * d, d, 3 * d, gl + p.wqkv);                                              // dWqkv = u^T dqkv
+    wgrad(3, u, dqkv, d, 3 * d, gl + p.wqkv);                                              // dWqkv = u^T dqkv
     colsum(part_qkv, rv_attn_colsum_parts(p.mb, p.S), 3 * d, 3 * d, gl + p.bqkv);
     take(2);
     if (leaves) {
@@ -435,10 +445,10 @@ struct Backward {
       if (early || p.deep) RV_TRY(send_sums(ws));
       if (p.deep) RV_TRY(update_from(l + 1, ws));   // (block l lacks what its last LayerNorm gives)
     }
-    uint16_t* dy_below = l > 0 ? dy_buf(l - 1) : nullptr;
+    const rv_mat dy_below = l > 0 ? rv_blocks(dy_buf(l - 1), T) : rv_rows(grad_in, d);
     // du
     RV_TRY(product_and_norm(p.b_wqkv, dqkv, w + p.wqkv, 3 * d, x, (const float*)(sb + p.s_m1), (const float*)(sb + p.s_r1), w + p.ln1g,
-                            l == 0 ? (uint16_t*)grad_in : dy_below, part1));
+                            dy_below, part1));
     colsum(part1, ln_parts, 3 * (int64_t)d, d, gl + p.ln1g);
     colsum(part1 + d, ln_parts, 3 * (int64_t)d, d, gl + p.ln1b);
     // the residual gradient leaving this block is dy of the block below: its b2 gradient

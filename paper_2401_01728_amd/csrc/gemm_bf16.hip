@@ -4,7 +4,15 @@
 //   C[M,N] = sum_k A(m,k) B(k,n)        K % 64 == 0, N % 8 == 0, M % 8 == 0
 //
 // Each operand is either "k-contiguous" (A[m*lda+k], B[n*ldb+k]) or "k-major"
-// (A[k*lda+m], B[k*ldb+n]).  The three products of a Linear y = x W, W stored [in,out]:
+// (A[k*lda+m], B[k*ldb+n]) - in rows, or in blocks of 32 columns: element (r, c) of a matrix of R rows at
+// (c / 32) * 32 R + 32 r + c % 32, so that the 32-deep tile of a k-contiguous operand is ONE run of rows x 64 bytes (as rows: so many
+// pieces of 64, each half a line) and that of a k-major one BN / 32 runs of 2 KiB.  Both are one address form,
+// r * ld + (c / 32) * bs + c % 32, rows being bs = 32.  Blocks against rows, alone,
+// us: 4096x2048x8192 (k-contiguous W) 172 -> 147, 8192x6400x1600 with GELU' 242 -> 216, 4096x8192x2048 with GELU 142 -> 137, weight
+// gradients the same; weights cold, 128x1024x4096 21.1 -> 16.0 (32x64 split), 2048x1024x3072 32.0 -> 24.3 (64x64 split).  Stage steps:
+// d 2048, 4096 tokens 11.49 -> 10.87 ms, d 1024 1.773 -> 1.714, d 1600, 8192 tokens 22.5 -> 21.9; 6 blocks of d 768 on 1152
+// tokens, four microbatches 5345 -> 5095 us.  What it costs: the average that publishes versions 353 -> 372 us over four of 50 M
+// parameters (a row of a blocked version is pieces of 64 bytes).  The three products of a Linear y = x W, W stored [in,out]:
 //   forward  y  = x W      : A = x  k-contiguous, B = W  k-major
 //   dX       dx = dy W^T   : A = dy k-contiguous, B = W  k-contiguous (its rows are the n's)
 //   dW       dW = x^T dy   : A = x  k-major,      B = dy k-major      (contraction over tokens)
@@ -71,6 +79,10 @@ struct Epi {
   float* upd_w;   // EPI_F32_UPD: fp32 master tile updated in place (out2 = its bf16 weight version)
   float eta;
   float* colpart; // EPI_BF16_DGELU: partial column sums of the output, one row (pitch ldo) per tile row
+  // where (m, n) lies in the output that may be in blocks of 32 columns: `out` of EPI_BF16_DGELU, `out2` of
+  // EPI_BF16_BIAS_GELU and of EPI_F32_UPD (rows: ldb = ldo, bsb = 32)
+  int64_t ldb, bsb;
+  __device__ __forceinline__ int64_t blocked(int m, int n) const { return (int64_t)m * ldb + (n >> 5) * bsb + (n & 31); }
 };
 
 enum { EPI_BF16 = RV_EPI_BF16, EPI_BF16_BIAS = RV_EPI_BF16_BIAS, EPI_F32_BIAS_RESID = RV_EPI_F32_BIAS_RESID,
@@ -111,13 +123,13 @@ __device__ __forceinline__ void epilogue4(const Epi& e, int m, int n, f32x4 a, u
     u32x2 g;
     g.x = rv_pack_bf16x2(gelu_f(a.x), gelu_f(a.y));
     g.y = rv_pack_bf16x2(gelu_f(a.z), gelu_f(a.w));
-    *reinterpret_cast<u32x2*>((uint16_t*)e.out2 + (int64_t)m * e.ldo + n) = g;
+    *reinterpret_cast<u32x2*>((uint16_t*)e.out2 + e.blocked(m, n)) = g;
   } else if (EPI == EPI_BF16_DGELU) {
     u32x2 z = *reinterpret_cast<const u32x2*>(e.zin + (int64_t)m * e.ldo + n);
     a.x *= dgelu_f(__uint_as_float(z.x << 16)); a.y *= dgelu_f(__uint_as_float(z.x & 0xFFFF0000u));
     a.z *= dgelu_f(__uint_as_float(z.y << 16)); a.w *= dgelu_f(__uint_as_float(z.y & 0xFFFF0000u));
     u32x2 o; o.x = rv_pack_bf16x2(a.x, a.y); o.y = rv_pack_bf16x2(a.z, a.w);
-    *reinterpret_cast<u32x2*>((uint16_t*)e.out + (int64_t)m * e.ldo + n) = o;
+    *reinterpret_cast<u32x2*>((uint16_t*)e.out + e.blocked(m, n)) = o;
   } else if (EPI == EPI_F32) {
     *reinterpret_cast<f32x4*>((float*)e.out + (int64_t)m * e.ldo + n) = a;
   } else if (EPI == EPI_F32_UPD) {
@@ -324,7 +336,8 @@ __device__ __forceinline__ void write_tile_staged(const f32x16 (&acc)[TM][TN], c
       for (int u = 0; u < BATCH; ++u) {
         const int idx = threadIdx.x + (p0 + u) * NT, row = idx / CPR, c = idx % CPR;
         const int gm = m0 + row, gn = n0 + c * 8;
-        if (gm < M && gn < N) *reinterpret_cast<u32x4*>(dst + (int64_t)gm * e.ldo + gn) = v[u];
+        const bool blk = EPI == EPI_BF16_DGELU || (EPI == EPI_BF16_BIAS_GELU && pass == 1);
+        if (gm < M && gn < N) *reinterpret_cast<u32x4*>(dst + (blk ? e.blocked(gm, gn) : (int64_t)gm * e.ldo + gn)) = v[u];
       }
     }
     if (pass + 1 < PASSES) __syncthreads();
@@ -357,7 +370,7 @@ struct Dtl {
 };
 
 template <bool KM, int ROWS, int BK, int NW>
-__device__ __forceinline__ void dtl_init(Dtl<KM, ROWS, BK, NW>& s, int64_t ld, int r0, int rows, int wave) {
+__device__ __forceinline__ void dtl_init(Dtl<KM, ROWS, BK, NW>& s, int64_t ld, int64_t bs, int r0, int rows, int wave) {
   const int l = threadIdx.x & 63;
 #pragma unroll
   for (int i = 0; i < Dtl<KM, ROWS, BK, NW>::N; ++i) {
@@ -367,21 +380,21 @@ __device__ __forceinline__ void dtl_init(Dtl<KM, ROWS, BK, NW>& s, int64_t ld, i
       const int row = slot / CPR, c = (slot % CPR) ^ ((row / R256) % CPR);
       int gr = r0 + row;
       gr = gr < rows ? gr : rows - 1;
-      s.off[i] = gr * (int)ld + c * 8;
+      s.off[i] = gr * (int)ld + (c * 8 / 32) * (int)bs + c * 8 % 32;
     } else {
       constexpr int CPR = ROWS / 8;
       const int kr = slot / CPR, c = (slot % CPR) ^ km_swizzle<ROWS>(kr);
       int col = r0 + c * 8;
       col = col < rows ? col : rows - 8;
-      s.off[i] = kr * (int)ld + col;
+      s.off[i] = kr * (int)ld + (col >> 5) * (int)bs + (col & 31);
     }
   }
 }
 
 template <bool KM, int ROWS, int BK, int NW>
 __device__ __forceinline__ void dtl_issue(const Dtl<KM, ROWS, BK, NW>& s, const uint16_t* __restrict__ g,
-                                          int64_t ld, int k0, char* lds, int wave) {
-  const uint16_t* base = KM ? g + (int64_t)k0 * ld : g + k0;
+                                          int64_t ld, int64_t bs, int k0, char* lds, int wave) {
+  const uint16_t* base = KM ? g + (int64_t)k0 * ld : g + (k0 >> 5) * bs;
 #pragma unroll
   for (int i = 0; i < Dtl<KM, ROWS, BK, NW>::N; ++i) {
     // LDS byte address of this wave's 1 KiB block (wave-uniform, goes to M0; the hardware
@@ -528,7 +541,7 @@ __device__ __forceinline__ void f32_tile_through_lds(const f32x16 (&acc)[TM][TN]
           *reinterpret_cast<f32x4*>(dst32 + o) = v[u];
           if (BF16OUT) {
             u32x2 q; q.x = rv_pack_bf16x2(v[u].x, v[u].y); q.y = rv_pack_bf16x2(v[u].z, v[u].w);
-            *reinterpret_cast<u32x2*>((uint16_t*)e.out2 + o) = q;
+            *reinterpret_cast<u32x2*>((uint16_t*)e.out2 + (MODE == 0 ? e.blocked(gm, gn) : o)) = q;
           }
         }
       }
@@ -537,8 +550,8 @@ __device__ __forceinline__ void f32_tile_through_lds(const f32x16 (&acc)[TM][TN]
 }
 
 template <int BM, int BN, int BK, int NS, int NW, bool AKM, bool BKM, int EPI>
-__device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, int64_t lda,
-                                              const uint16_t* __restrict__ B, int64_t ldb, int M, int N,
+__device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, int64_t lda, int64_t a_bs,
+                                              const uint16_t* __restrict__ B, int64_t ldb, int64_t b_bs, int M, int N,
                                               int K, int bm, int bn, const Epi& e) {
   // NW waves laid out 2 (m) x NW/2 (n)
   constexpr int WM = BM / 2, WN = BN / (NW / 2), TM = WM / 32, TN = WN / 32, KSTEPS = BK / 16;
@@ -567,8 +580,8 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
   const int lw = wave;                 // this wave's share of a tile's loads
   Dtl<AKM, BM, BK, NL> da;
   Dtl<BKM, BN, BK, NL> db;
-  dtl_init<AKM, BM, BK, NL>(da, lda, m0, M, lw);
-  dtl_init<BKM, BN, BK, NL>(db, ldb, n0, N, lw);
+  dtl_init<AKM, BM, BK, NL>(da, lda, a_bs, m0, M, lw);
+  dtl_init<BKM, BN, BK, NL>(db, ldb, b_bs, n0, N, lw);
   const int nk = K / BK;
   if constexpr (PIPELINED) {
     // Ring of NS slots, the slot hand-over INSIDE a k-tile.  Before the last k-step of tile s
@@ -586,8 +599,8 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
     for (int i = 0; i < NA; ++i) oa[i] = (unsigned)da.off[i] * 2u;
 #pragma unroll
     for (int i = 0; i < NB; ++i) ob[i] = (unsigned)db.off[i] * 2u;
-    auto baseA = [&](int t) { return AKM ? A + (int64_t)t * BK * lda : A + (int64_t)t * BK; };
-    auto baseB = [&](int t) { return BKM ? B + (int64_t)t * BK * ldb : B + (int64_t)t * BK; };
+    auto baseA = [&](int t) { return AKM ? A + (int64_t)t * BK * lda : A + (int64_t)t * (BK / 32) * a_bs; };
+    auto baseB = [&](int t) { return BKM ? B + (int64_t)t * BK * ldb : B + (int64_t)t * (BK / 32) * b_bs; };
     // wait until at most `tiles` of this wave's newest tile loads are still in flight
     auto wait_tiles = [&](int tiles) {
       if (NS >= 5 && tiles >= 4) RV_WAIT_VMCNT(4 * LPS);
@@ -700,8 +713,8 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
 #pragma unroll
     for (int t = 0; t < NS - 1; ++t)
       if (t < nk) {
-        dtl_issue<AKM, BM, BK, NL>(da, A, lda, t * BK, smem + t * BUF, lw);
-        dtl_issue<BKM, BN, BK, NL>(db, B, ldb, t * BK, smem + t * BUF + A_BYTES, lw);
+        dtl_issue<AKM, BM, BK, NL>(da, A, lda, a_bs, t * BK, smem + t * BUF, lw);
+        dtl_issue<BKM, BN, BK, NL>(db, B, ldb, b_bs, t * BK, smem + t * BUF + A_BYTES, lw);
       }
     int stage = 0;               // ring slot of tile `it`
     int fill = NS - 1;           // ring slot the next issued tile goes to
@@ -713,8 +726,8 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
       else RV_WAIT_VMCNT(0);
       __syncthreads();           // everyone's part of tile `it` is in LDS; everyone left tile it-1
       if (it + NS - 1 < nk) {
-        dtl_issue<AKM, BM, BK, NL>(da, A, lda, (it + NS - 1) * BK, smem + fill * BUF, lw);
-        dtl_issue<BKM, BN, BK, NL>(db, B, ldb, (it + NS - 1) * BK, smem + fill * BUF + A_BYTES, lw);
+        dtl_issue<AKM, BM, BK, NL>(da, A, lda, a_bs, (it + NS - 1) * BK, smem + fill * BUF, lw);
+        dtl_issue<BKM, BN, BK, NL>(db, B, ldb, b_bs, (it + NS - 1) * BK, smem + fill * BUF + A_BYTES, lw);
       }
       const char* curA = smem + stage * BUF;
       const char* curB = curA + A_BYTES;
@@ -764,13 +777,13 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
 }
 
 template <int BM, int BN, int BK, int NS, int NW, int WPE, bool AKM, bool BKM, int EPI>
-__global__ __launch_bounds__(64 * NW, WPE) void gemm_dtl_kernel(const uint16_t* __restrict__ A, int64_t lda,
-                                                                 const uint16_t* __restrict__ B, int64_t ldb,
+__global__ __launch_bounds__(64 * NW, WPE) void gemm_dtl_kernel(const uint16_t* __restrict__ A, int64_t lda, int64_t a_bs,
+                                                                 const uint16_t* __restrict__ B, int64_t ldb, int64_t b_bs,
                                                                  int M, int N, int K, int tiles_m, int tiles_n,
                                                                  int band_rows, Epi e) {
   int bm, bn;
   tile_of_block(tiles_m, tiles_n, band_rows, bm, bn);
-  gemm_dtl_body<BM, BN, BK, NS, NW, AKM, BKM, EPI>(A, lda, B, ldb, M, N, K, bm, bn, e);
+  gemm_dtl_body<BM, BN, BK, NS, NW, AKM, BKM, EPI>(A, lda, a_bs, B, ldb, b_bs, M, N, K, bm, bn, e);
 }
 
 // ---- few tiles: the contraction split inside a workgroup ------------------------------------
@@ -811,8 +824,8 @@ __device__ __forceinline__ u32x4 f32_to_bf16x8(const f32x4 (&v)[2]) {
 }
 
 template <int BM, int BN, int G, int NW, int NS, bool AKM, bool BKM, int EPI>
-__device__ __forceinline__ void gemm_split_body(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ B,
-                                                int64_t ldb, int M, int N, int K, int bm, int bn, const Epi& e) {
+__device__ __forceinline__ void gemm_split_body(const uint16_t* __restrict__ A, int64_t lda, int64_t a_bs,
+                                                const uint16_t* __restrict__ B, int64_t ldb, int64_t b_bs, int M, int N, int K, int bm, int bn, const Epi& e) {
   constexpr int BK = 32, NT = 64 * NW * G;               // a group's NW waves: NW / 2 (m) x 2 (n)
   constexpr int WM = BM / (NW / 2), WN = BN / 2, TM = WM / 32, TN = WN / 32;
   constexpr int A_BYTES = dtl_tile_bytes(BM, BK), BUF = A_BYTES + dtl_tile_bytes(BN, BK);
@@ -833,15 +846,15 @@ __device__ __forceinline__ void gemm_split_body(const uint16_t* __restrict__ A, 
 
   Dtl<AKM, BM, BK, NW> da;
   Dtl<BKM, BN, BK, NW> db;
-  dtl_init<AKM, BM, BK, NW>(da, lda, m0, M, wave);
-  dtl_init<BKM, BN, BK, NW>(db, ldb, n0, N, wave);
+  dtl_init<AKM, BM, BK, NW>(da, lda, a_bs, m0, M, wave);
+  dtl_init<BKM, BN, BK, NW>(db, ldb, b_bs, n0, N, wave);
   const int nk = K / BK, turns = (nk + G - 1) / G;
   const int mine = (nk - group + G - 1) / G;               // k-tiles of this group: group, group + G, ...
   auto issue = [&](int i) {                                // its i-th k-tile into slot i % NS
     const int t = i * G + group;
     const int lb = __builtin_amdgcn_readfirstlane((int)(size_t)(ring + (i % NS) * BUF) + wave * 1024);
-    const uint16_t* pa = AKM ? A + (int64_t)t * BK * lda : A + (int64_t)t * BK;
-    const uint16_t* pb = BKM ? B + (int64_t)t * BK * ldb : B + (int64_t)t * BK;
+    const uint16_t* pa = AKM ? A + (int64_t)t * BK * lda : A + (int64_t)t * a_bs;
+    const uint16_t* pb = BKM ? B + (int64_t)t * BK * ldb : B + (int64_t)t * b_bs;
 #pragma unroll
     for (int q = 0; q < NA; ++q) dtl_load_s(pa, (unsigned)da.off[q] * 2u, lb + q * NW * 1024);
 #pragma unroll
@@ -939,14 +952,16 @@ __device__ __forceinline__ void gemm_split_body(const uint16_t* __restrict__ A, 
       }
     }
     if (!ok[p]) continue;
-    if (EPI == EPI_BF16 || EPI == EPI_BF16_BIAS || EPI == EPI_BF16_BIAS_GELU || EPI == EPI_BF16_DGELU)
+    const int gm = m0 + row, gn = n0 + c;
+    if (EPI == EPI_BF16 || EPI == EPI_BF16_BIAS || EPI == EPI_BF16_BIAS_GELU)
       *reinterpret_cast<u32x4*>((uint16_t*)e.out + at[p]) = f32_to_bf16x8(v);
+    if (EPI == EPI_BF16_DGELU) *reinterpret_cast<u32x4*>((uint16_t*)e.out + e.blocked(gm, gn)) = f32_to_bf16x8(v);
     if (EPI == EPI_BF16_BIAS_GELU) {
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[h][k] = gelu_f(v[h][k]);
-      *reinterpret_cast<u32x4*>((uint16_t*)e.out2 + at[p]) = f32_to_bf16x8(v);
+      *reinterpret_cast<u32x4*>((uint16_t*)e.out2 + e.blocked(gm, gn)) = f32_to_bf16x8(v);
     }
     if (RESID) {
       v[0] += in[p][0]; v[1] += in[p][1];
@@ -963,7 +978,7 @@ __device__ __forceinline__ void gemm_split_body(const uint16_t* __restrict__ A, 
         for (int k = 0; k < 4; ++k) v[h][k] = __fmaf_rn(-e.eta, v[h][k], in[p][h][k]);
       f32x4* dst = reinterpret_cast<f32x4*>(e.upd_w + at[p]);
       dst[0] = v[0]; dst[1] = v[1];
-      store8(e.out2, at[p], f32_to_bf16x8(v));
+      store8(e.out2, e.blocked(gm, gn), f32_to_bf16x8(v));
     }
   }
   if (ZIN && e.colpart) {                                  // (uniform) NT / BN row lanes per column, added in order
@@ -1001,12 +1016,12 @@ __device__ __forceinline__ void split_tile(int tiles_m, int tiles_n, int S, int&
 }
 
 template <int BM, int BN, int G, int NW, int NS, bool AKM, bool BKM, int EPI>
-__global__ __launch_bounds__(64 * NW * G, NW * G / 4) void gemm_split_kernel(const uint16_t* __restrict__ A, int64_t lda,
-                                                                const uint16_t* __restrict__ B, int64_t ldb, int M, int N, int K,
+__global__ __launch_bounds__(64 * NW * G, NW * G / 4) void gemm_split_kernel(const uint16_t* __restrict__ A, int64_t lda, int64_t a_bs,
+                                                                const uint16_t* __restrict__ B, int64_t ldb, int64_t b_bs, int M, int N, int K,
                                                                 int tiles_m, int tiles_n, Epi e) {
   int ks, bm, bn;
   split_tile(tiles_m, tiles_n, 1, ks, bm, bn);
-  gemm_split_body<BM, BN, G, NW, NS, AKM, BKM, EPI>(A, lda, B, ldb, M, N, K, bm, bn, e);
+  gemm_split_body<BM, BN, G, NW, NS, AKM, BKM, EPI>(A, lda, a_bs, B, ldb, b_bs, M, N, K, bm, bn, e);
 }
 
 // ---- few tiles and a long contraction: split over workgroups as well ------------------------
@@ -1014,14 +1029,14 @@ __global__ __launch_bounds__(64 * NW * G, NW * G / 4) void gemm_split_kernel(con
 // one stores its sum as fp32 to part[stretch][M][N], and the kernel that reads the result - a LayerNorm, which passes over
 // whole rows anyway - adds the S of them in order (norm.hip): no exchange between workgroups, no launch of its own.
 template <int BM, int BN, int G, int NW, int NS, bool BKM>
-__global__ __launch_bounds__(64 * NW * G, NW * G / 4) void gemm_part_kernel(const uint16_t* __restrict__ A, int64_t lda,
-                                                               const uint16_t* __restrict__ B, int64_t ldb, int M, int N, int K,
+__global__ __launch_bounds__(64 * NW * G, NW * G / 4) void gemm_part_kernel(const uint16_t* __restrict__ A, int64_t lda, int64_t a_bs,
+                                                               const uint16_t* __restrict__ B, int64_t ldb, int64_t b_bs, int M, int N, int K,
                                                                int tiles_m, int tiles_n, int S, float* part) {
   int ks, bm, bn;
   split_tile(tiles_m, tiles_n, S, ks, bm, bn);
   const int nk = K / 32, t0 = nk * ks / S, t1 = nk * (ks + 1) / S;
-  Epi e{part + (int64_t)ks * M * N, N, nullptr, nullptr, nullptr, 0, nullptr, nullptr, 0.f, nullptr};
-  gemm_split_body<BM, BN, G, NW, NS, false, BKM, EPI_F32>(A + t0 * 32, lda, BKM ? B + (int64_t)t0 * 32 * ldb : B + t0 * 32, ldb,
+  Epi e{part + (int64_t)ks * M * N, N, nullptr, nullptr, nullptr, 0, nullptr, nullptr, 0.f, nullptr, 0, 0};
+  gemm_split_body<BM, BN, G, NW, NS, false, BKM, EPI_F32>(A + t0 * a_bs, lda, a_bs, B + t0 * (BKM ? 32 * ldb : b_bs), ldb, b_bs,
                                                           M, N, (t1 - t0) * 32, bm, bn, e);
 }
 
@@ -1031,7 +1046,7 @@ __global__ __launch_bounds__(64 * NW * G, NW * G / 4) void gemm_part_kernel(cons
 struct GroupedProblem {
   const uint16_t* A; const uint16_t* B; float* out;
   float* upd_w; uint16_t* upd_ver; float eta;
-  int lda, ldb, ldo, M, N, K, tiles_m, tiles_n, first_tile;
+  int lda, a_bs, ldb, b_bs, ldo, ldv, bsv, M, N, K, tiles_m, tiles_n, first_tile;   // ldv, bsv: of the weight version
 };
 template <int MAX>
 struct GroupedArgs {
@@ -1064,20 +1079,20 @@ __device__ __forceinline__ const GroupedProblem& grouped_tile(const GroupedArgs<
   return q;
 }
 __device__ __forceinline__ Epi grouped_epi(const GroupedProblem& q) {
-  return Epi{q.out, q.ldo, q.upd_ver, nullptr, nullptr, 0, nullptr, q.upd_w, q.eta, nullptr};
+  return Epi{q.out, q.ldo, q.upd_ver, nullptr, nullptr, 0, nullptr, q.upd_w, q.eta, nullptr, q.ldv, q.bsv};
 }
 
 template <int BM, int BN, int BK, int NS, int NW, int WPE>
 __global__ __launch_bounds__(64 * NW, WPE) void gemm_dtl_grouped_wgrad_kernel(GroupedArgs<RV_GEMM_GROUP_BLOCK> ga) {
   int bm, bn;
   const GroupedProblem& q = grouped_tile(ga, bm, bn);
-  gemm_dtl_body<BM, BN, BK, NS, NW, true, true, EPI_F32_UPD>(q.A, q.lda, q.B, q.ldb, q.M, q.N, q.K, bm, bn, grouped_epi(q));
+  gemm_dtl_body<BM, BN, BK, NS, NW, true, true, EPI_F32_UPD>(q.A, q.lda, q.a_bs, q.B, q.ldb, q.b_bs, q.M, q.N, q.K, bm, bn, grouped_epi(q));
 }
 template <int BM, int BN, int G, int NW, int NS, int MAX>
 __global__ __launch_bounds__(64 * NW * G, NW * G / 4) void gemm_split_grouped_wgrad_kernel(GroupedArgs<MAX> ga) {
   int bm, bn;
   const GroupedProblem& q = grouped_tile(ga, bm, bn);
-  gemm_split_body<BM, BN, G, NW, NS, true, true, EPI_F32_UPD>(q.A, q.lda, q.B, q.ldb, q.M, q.N, q.K, bm, bn, grouped_epi(q));
+  gemm_split_body<BM, BN, G, NW, NS, true, true, EPI_F32_UPD>(q.A, q.lda, q.a_bs, q.B, q.ldb, q.b_bs, q.M, q.N, q.K, bm, bn, grouped_epi(q));
 }
 
 template <int BM, int BN, int BK, int NS, int NW, int WPE, bool AKM, bool BKM, int EPI>
@@ -1093,7 +1108,8 @@ rv_status launch_dtl(const rv_gemm_args& g, hipStream_t st) {
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   if (configured != hipSuccess) return RV_E_DEVICE;
   int tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN;
-  Epi e{g.out, g.ldo, g.out2, g.bias, g.resid, g.ldr, g.zin, nullptr, 0.f, g.epi == EPI_BF16_DGELU ? g.colpart : nullptr};
+  Epi e{g.out, g.ldo, g.out2, g.bias, g.resid, g.ldr, g.zin, nullptr, 0.f, g.epi == EPI_BF16_DGELU ? g.colpart : nullptr,
+        g.bsv ? 32 : g.ldo, g.bsv ? g.bsv : 32};
   g.colpart_rows = (g.M + BM - 1) / BM;
   const int ntiles = tm * tn;
   // Measured: alone, the XCD-banded map pays only for the small tile.  Inside a stage step a
@@ -1103,7 +1119,7 @@ rv_status launch_dtl(const rv_gemm_args& g, hipStream_t st) {
   int band = 8;
   if (g.sharing != 0) band = tm >= 32 ? 2 : 8;
   else if (!(BM == 128 && BN == 128)) tm = -tm;
-  hipLaunchKernelGGL(kern, dim3(ntiles), dim3(64 * NW), smem, st, g.A, g.lda, g.B, g.ldb, g.M, g.N, g.K,
+  hipLaunchKernelGGL(kern, dim3(ntiles), dim3(64 * NW), smem, st, g.A, g.lda, g.a_bs, g.B, g.ldb, g.b_bs, g.M, g.N, g.K,
                      tm, tn, band, e);
   return rv_launch_status();
 }
@@ -1117,9 +1133,10 @@ rv_status launch_split(const rv_gemm_args& g, hipStream_t st) {
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   if (configured != hipSuccess) return RV_E_DEVICE;
   const int tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN;
-  Epi e{g.out, g.ldo, g.out2, g.bias, g.resid, g.ldr, g.zin, nullptr, 0.f, g.epi == EPI_BF16_DGELU ? g.colpart : nullptr};
+  Epi e{g.out, g.ldo, g.out2, g.bias, g.resid, g.ldr, g.zin, nullptr, 0.f, g.epi == EPI_BF16_DGELU ? g.colpart : nullptr,
+        g.bsv ? 32 : g.ldo, g.bsv ? g.bsv : 32};
   g.colpart_rows = tm;
-  hipLaunchKernelGGL(kern, dim3(tm * tn), dim3(64 * NW * G), smem, st, g.A, g.lda, g.B, g.ldb, g.M, g.N, g.K, tm, tn, e);
+  hipLaunchKernelGGL(kern, dim3(tm * tn), dim3(64 * NW * G), smem, st, g.A, g.lda, g.a_bs, g.B, g.ldb, g.b_bs, g.M, g.N, g.K, tm, tn, e);
   return rv_launch_status();
 }
 
@@ -1132,7 +1149,7 @@ rv_status launch_part(const rv_gemm_args& g, int S, float* part, hipStream_t st)
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   if (configured != hipSuccess) return RV_E_DEVICE;
   const int tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN;
-  hipLaunchKernelGGL(kern, dim3(tm * tn * S), dim3(64 * NW * G), smem, st, g.A, g.lda, g.B, g.ldb, g.M, g.N, g.K, tm, tn, S, part);
+  hipLaunchKernelGGL(kern, dim3(tm * tn * S), dim3(64 * NW * G), smem, st, g.A, g.lda, g.a_bs, g.B, g.ldb, g.b_bs, g.M, g.N, g.K, tm, tn, S, part);
   return rv_launch_status();
 }
 template <bool BKM>
@@ -1229,6 +1246,19 @@ rv_status pick_tile(const rv_gemm_args& g, hipStream_t st) {
 
 }  // namespace
 
+namespace {
+// tile offsets are kept in 32 bits, and a matrix in blocks of columns is whole blocks
+bool operand_fits(const rv_gemm_args& g) {
+  auto fits = [](int64_t rows, int64_t cols, int64_t ld, int64_t bs) {
+    if (bs == 32) return rows * ld < (1ll << 31);
+    return ld == 32 && bs == rows * 32 && cols % 32 == 0 && rows * cols < (1ll << 31);
+  };
+  return (g.a_kmajor ? fits(g.K, g.M, g.lda, g.a_bs) : fits(g.M, g.K, g.lda, g.a_bs)) &&
+         (g.b_kmajor ? fits(g.K, g.N, g.ldb, g.b_bs) : fits(g.N, g.K, g.ldb, g.b_bs)) &&
+         (!g.bsv || (g.bsv == (int64_t)g.M * 32 && g.N % 32 == 0 && (int64_t)g.M * g.N < (1ll << 31)));
+}
+}  // namespace
+
 rv_status rv_gemm_bf16(const rv_gemm_args& g, hipStream_t st) {
   if (!g.A || !g.B || !g.out || g.M < 8 || g.N < 8 || g.K < 64) return RV_E_INVAL;
   if (g.K % 64 || g.N % 8 || g.M % 8 || g.lda % 8 || g.ldb % 8 || g.ldo % 4) return RV_E_INVAL;
@@ -1237,9 +1267,7 @@ rv_status rv_gemm_bf16(const rv_gemm_args& g, hipStream_t st) {
   if ((staged_epi(g.epi) || g.epi == EPI_F32_BIAS_RESID_BF16) && g.ldo % 8) return RV_E_INVAL;
   if (staged_epi(g.epi) && g.epi == EPI_BF16_BIAS_GELU && (((uintptr_t)g.out2) & 15)) return RV_E_INVAL;
   if (g.epi == EPI_BF16_DGELU && (((uintptr_t)g.zin) & 15)) return RV_E_INVAL;
-  // tile offsets are kept in 32 bits
-  if ((int64_t)(g.a_kmajor ? g.K : g.M) * g.lda >= (1ll << 31) || (int64_t)(g.b_kmajor ? g.K : g.N) * g.ldb >= (1ll << 31))
-    return RV_E_INVAL;
+  if (!operand_fits(g)) return RV_E_INVAL;
   const bool need_bias = g.epi == EPI_BF16_BIAS || g.epi == EPI_F32_BIAS_RESID ||
                          g.epi == EPI_BF16_BIAS_GELU || g.epi == EPI_F32_BIAS_RESID_BF16;
   if (need_bias && (!g.bias || (((uintptr_t)g.bias) & 7))) return RV_E_INVAL;
@@ -1296,7 +1324,7 @@ rv_status rv_gemm_part(const rv_gemm_args& g, int S, float* part, hipStream_t st
   if (!g.A || !g.B || !part || g.a_kmajor || g.M < 8 || g.N < 8 || g.K < 64 || S < 1 || S > RV_GEMM_PARTS_MAX || S > g.K / 32) return RV_E_INVAL;
   if (g.K % 64 || g.N % 8 || g.M % 8 || g.lda % 8 || g.ldb % 8) return RV_E_INVAL;
   if ((((uintptr_t)g.A) | ((uintptr_t)g.B) | ((uintptr_t)part)) & 15) return RV_E_INVAL;
-  if ((int64_t)g.M * g.lda >= (1ll << 31) || (int64_t)(g.b_kmajor ? g.K : g.N) * g.ldb >= (1ll << 31)) return RV_E_INVAL;
+  if (!operand_fits(g)) return RV_E_INVAL;
   return g.b_kmajor ? pick_part<true>(g, S, part, st) : pick_part<false>(g, S, part, st);
 }
 
@@ -1311,7 +1339,9 @@ rv_status launch_grouped(void (*kern)(GroupedArgs<MAX>), int BM, int BN, int thr
     GroupedProblem& q = ga.p[k];
     q.A = g.A; q.B = g.B; q.out = g.store_out ? (float*)g.out : nullptr;
     q.upd_w = g.upd_w; q.upd_ver = g.upd_ver; q.eta = g.upd_eta;
-    q.lda = (int)g.lda; q.ldb = (int)g.ldb; q.ldo = (int)g.ldo; q.M = g.M; q.N = g.N; q.K = g.K;
+    q.lda = (int)g.lda; q.a_bs = (int)g.a_bs; q.ldb = (int)g.ldb; q.b_bs = (int)g.b_bs; q.ldo = (int)g.ldo;
+    q.ldv = (int)(g.bsv ? 32 : g.ldo); q.bsv = (int)(g.bsv ? g.bsv : 32);
+    q.M = g.M; q.N = g.N; q.K = g.K;
     q.tiles_m = (g.M + BM - 1) / BM;
     q.tiles_n = (g.N + BN - 1) / BN;
     q.first_tile = tiles;
@@ -1354,7 +1384,7 @@ rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t s
     if (g.M < 8 || g.N < 8 || g.K < 64 || g.K % 64 || g.N % 8 || g.M % 8 || g.lda % 8 || g.ldb % 8 || g.ldo % 4)
       return RV_E_INVAL;
     if ((((uintptr_t)g.A) | ((uintptr_t)g.B) | ((uintptr_t)g.out)) & 15) return RV_E_INVAL;
-    if ((int64_t)g.K * g.lda >= (1ll << 31) || (int64_t)g.K * g.ldb >= (1ll << 31)) return RV_E_INVAL;
+    if (!operand_fits(g)) return RV_E_INVAL;
     if ((g.upd_w != nullptr) != (g.upd_ver != nullptr)) return RV_E_INVAL;
     if (!g.upd_w && !g.store_out) return RV_E_INVAL;
     if ((((uintptr_t)g.upd_w) & 15) || (((uintptr_t)g.upd_ver) & 7)) return RV_E_INVAL;

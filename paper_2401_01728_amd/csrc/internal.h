@@ -4,33 +4,78 @@
 #include "common.h"
 
 // ---- update.hip ------------------------------------------------------------------
-// copy_kind: 0 none, 1 bf16 bits, 2 fp32
+// Where a weight version keeps the parameters of a flat vector: as they come, or with the four matrices of every `per_block`
+// parameters in blocks of 32 columns (rv_mat).  [0, n) of a call is whole blocks then; all numbers are multiples of 64.
+struct rv_ver_map {
+  uint32_t per_block = 0;      // 0: as they come
+  uint32_t at[4] = {0, 0, 0, 0}, rows[4] = {0, 0, 0, 0}, cols[4] = {1, 1, 1, 1};
+};
+// position in the version of the parameter at e = base + (less than per_block); base is the same in all lanes of a wave
+__device__ __forceinline__ uint64_t rv_ver_at(const rv_ver_map& m, uint64_t base, uint64_t e) {
+  uint64_t first = base / m.per_block * m.per_block;
+  if (e - first >= m.per_block) first += m.per_block;
+  const uint32_t r = (uint32_t)(e - first);
+  uint32_t at = r;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t i = r - m.at[k];
+    if (r >= m.at[k] && i < m.rows[k] * m.cols[k]) {
+      const uint32_t row = i / m.cols[k], c = i - row * m.cols[k];
+      at = m.at[k] + (c >> 5) * (m.rows[k] * 32) + row * 32 + (c & 31);
+    }
+  }
+  return first + at;
+}
+// Workgroup -> tile of a kernel that writes versions through the map: an XCD (workgroup ids go to the 8 of them in turn) takes 32
+// consecutive tiles at a time, so that the 64-byte pieces two neighbouring rows leave in one line meet in one L2.
+__device__ __forceinline__ unsigned rv_ver_tile(unsigned block, unsigned blocks) {
+  const unsigned whole = blocks / 256 * 256;
+  return block < whole ? block / 256 * 256 + block % 8 * 32 + block % 256 / 8 : block;
+}
+// copy_kind: 0 none, 1 bf16 bits, 2 fp32, 3 bf16 bits through `map`
 rv_status rv_launch_update(float* w, const float* g, size_t n, float eta, void* copy, int copy_kind,
-                           hipStream_t st);
+                           hipStream_t st, const rv_ver_map& map = rv_ver_map());
 rv_status rv_launch_update_momentum(float* w, const float* g, float* v, size_t n, float eta, float mu, float wd,
-                                    void* copy, int copy_kind, hipStream_t st);
+                                    void* copy, int copy_kind, hipStream_t st, const rv_ver_map& map = rv_ver_map());
 rv_status rv_launch_accumulate(float* acc, const float* g, size_t n, bool first, hipStream_t st);
 rv_status rv_launch_copy(float* dst, const float* src, size_t n, hipStream_t st);
 // master <- w and copy <- w in the version's type
-rv_status rv_launch_set(const float* w, size_t n, float* master, void* copy, int copy_kind, hipStream_t st);
+rv_status rv_launch_set(const float* w, size_t n, float* master, void* copy, int copy_kind, hipStream_t st,
+                        const rv_ver_map& map);
 
 // the RV_VER_PAD bytes at offset `at` of each of n version slots <- 0 (at: a multiple of 4)
 rv_status rv_launch_clear_pads(char* const* ver, int n, size_t at, hipStream_t st);
 
 // ---- average.hip -----------------------------------------------------------------
 // rv_cluster_average with write-back, and the mean also stored to C weight versions (copy_kind)
-rv_status rv_average_publish(float* const* masters, void* const* versions, int copy_kind, int C, size_t n, int R, const float* grad,
-                             int grad_replica, float eta, hipStream_t st);
+rv_status rv_average_publish(float* const* masters, void* const* versions, int copy_kind, const rv_ver_map& map, int C, size_t n, int R,
+                             const float* grad, int grad_replica, float eta, hipStream_t st);
+
+// A bf16 matrix as the decoder keeps its own ones: element (r, c) at r * ld + (c / 32) * bs + c % 32.  Rows of pitch ld are
+// bs = 32; "blocked" is ld = 32, bs = 32 * (number of rows): blocks of 32 columns, each a contiguous run of 64-byte rows, which is
+// what a 32-deep tile of a matrix product reads (gemm_bf16.hip).  The matrices a product reads - the weight versions and
+// the activations and gradients that are operands - are blocked; what only other kernels read, and what callers hand in or
+// get, is in rows.
+struct rv_mat {
+  uint16_t* p;
+  int64_t ld, bs;
+};
+__host__ __device__ inline int64_t rv_at(const rv_mat& m, int64_t r, int c) { return r * m.ld + (int64_t)(c >> 5) * m.bs + (c & 31); }
+inline rv_mat rv_rows(const void* p, int64_t ld) { return {(uint16_t*)p, ld, 32}; }
+inline rv_mat rv_blocks(const void* p, int64_t rows) { return {(uint16_t*)p, 32, 32 * rows}; }
 
 // ---- gemm_bf16.hip ----------------------------------------------------------------
 #include "../../include/rv_kernels.h"
 struct rv_gemm_args {
-  const uint16_t* A = nullptr; int64_t lda = 0; int a_kmajor = 0;
-  const uint16_t* B = nullptr; int64_t ldb = 0; int b_kmajor = 0;
+  // a_bs, b_bs 32: the operand lies in rows of pitch lda, ldb; else in blocks of 32 columns (rv_mat): 32 and 32 * its rows
+  const uint16_t* A = nullptr; int64_t lda = 0, a_bs = 32; int a_kmajor = 0;
+  const uint16_t* B = nullptr; int64_t ldb = 0, b_bs = 32; int b_kmajor = 0;
   int M = 0, N = 0, K = 0;
   int epi = 0;
   void* out = nullptr; int64_t ldo = 0;   // primary output [M, ldo]
   void* out2 = nullptr;                   // second output, same pitch (GELU value / bf16 copy)
+  // != 0 (32 M): `out` of the GELU' product, `out2` of the GELU product, upd_ver of a weight gradient in blocks of 32 columns
+  int64_t bsv = 0;
   const uint16_t* bias = nullptr;         // bf16 [N]
   const float* resid = nullptr; int64_t ldr = 0;
   const uint16_t* zin = nullptr;          // bf16 [M, ldo] pre-activations for GELU'
@@ -73,20 +118,20 @@ rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t s
 
 // ---- norm.hip ---------------------------------------------------------------------
 rv_status rv_ln_fwd(const void* x, int x_is_bf16, float* xcopy, const uint16_t* gamma, const uint16_t* beta,
-                    uint16_t* y, float* mean, float* rstd, int T, int d, float eps, hipStream_t st);
-// the same of x = part[0] + .. + part[S-1] + bias + resid, which it also writes to xsum (S in {2, 4, 8}); y null: only xsum, and
+                    rv_mat y, float* mean, float* rstd, int T, int d, float eps, hipStream_t st);
+// the same of x = part[0] + .. + part[S-1] + bias + resid, which it also writes to xsum (S in {2, 4, 8}); y.p null: only xsum, and
 // its bf16 rounding to out16
 rv_status rv_ln_fwd_parts(const float* part, int S, const uint16_t* bias, const float* resid, float* xsum, const uint16_t* gamma,
-                          const uint16_t* beta, uint16_t* y, float* mean, float* rstd, uint16_t* out16, int T, int d, float eps,
+                          const uint16_t* beta, rv_mat y, float* mean, float* rstd, uint16_t* out16, int T, int d, float eps,
                           hipStream_t st);
 int rv_ln_bwd_rows(int T, int d);    // rows per workgroup of the backward: 2, 4, 8 or (d > 1024) 16
 int rv_ln_bwd_parts(int T, int d);   // partial rows it writes with them (each 3*d floats)
 rv_status rv_ln_bwd(const uint16_t* dy, const float* x, const float* mean, const float* rstd,
-                    const uint16_t* gamma, const float* dres, float* dx, uint16_t* dx_bf16, float* part,
-                    int T, int d, hipStream_t st, int rows);
+                    const uint16_t* gamma, const float* dres, float* dx, rv_mat dx_bf16, float* part,
+                    int T, int d, hipStream_t st, int rows);   // (dx_bf16.p may be null)
 // the same with dy = part[0] + .. + part[S-1] (S in {2, 4, 8}, fp32 [T,d] each), not rounded
 rv_status rv_ln_bwd_parts_in(const float* dy_part, int S, const float* x, const float* mean, const float* rstd, const uint16_t* gamma,
-                             const float* dres, float* dx, uint16_t* dx_bf16, float* part, int T, int d, hipStream_t st, int rows);
+                             const float* dres, float* dx, rv_mat dx_bf16, float* part, int T, int d, hipStream_t st, int rows);
 // o fp32 [T,d] = a bf16 [T,d] widened, and part fp32 [rv_widen_parts(T), d] = column sums of a over
 // blocks of 32 rows
 int rv_widen_parts(int T);
@@ -106,13 +151,13 @@ struct rv_reduce_job {
 rv_status rv_reduce_rows(const rv_reduce_job* jobs, int njobs, float eta, hipStream_t st);
 
 // ---- attention.hip ----------------------------------------------------------------
-rv_status rv_attn_fwd(const uint16_t* qkv, uint16_t* out, float* lse2, int mb, int S, int d, int H,
+rv_status rv_attn_fwd(const uint16_t* qkv, rv_mat out, float* lse2, int mb, int S, int d, int H,
                       hipStream_t st);
 // colpart (may be null): fp32 [mb*S/32, 3d] partial rows of the column sums of dqkv (the qkv
 // bias gradient), one per (sequence, 32-token block); reduce with rv_reduce_rows
 int rv_attn_colsum_parts(int mb, int S);
-rv_status rv_attn_bwd(const uint16_t* qkv, const uint16_t* out, const uint16_t* dout, const float* lse2,
-                      float* Dbuf, uint16_t* dqkv, int mb, int S, int d, int H, hipStream_t st,
+rv_status rv_attn_bwd(const uint16_t* qkv, rv_mat out, const uint16_t* dout, const float* lse2,
+                      float* Dbuf, rv_mat dqkv, int mb, int S, int d, int H, hipStream_t st,
                       float* colpart = nullptr);
 
 // ---- stage bookkeeping -------------------------------------------------------------
@@ -157,6 +202,7 @@ struct rv_stage {
                             // on an MLP stage the momentum form as well
   bool grad_valid = false;  // `grad` holds the whole gradient of the last backward
   size_t ver_elem = 0;      // bytes per parameter in a version slot (2 or 4)
+  rv_ver_map ver_map;       // decoder: the matrices of a version lie in blocks of columns
   std::vector<char*> ver;   // tau+2 version slots: one is always free of readers, so an update can be
                             // written piece by piece while the backward still reads its own version
   std::vector<int> ver_ref; // in-flight microbatches bound to each slot

@@ -60,7 +60,7 @@ __global__ __launch_bounds__(kThreads, NV <= 8 ? 6 : 1) void ln_fwd_kernel(const
                                                           float* __restrict__ xcopy,
                                                           const uint16_t* __restrict__ gamma,
                                                           const uint16_t* __restrict__ beta,
-                                                          uint16_t* __restrict__ y,
+                                                          rv_mat y,
                                                           float* __restrict__ mean,
                                                           float* __restrict__ rstd, int T, int d,
                                                           float eps) {
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kThreads, NV <= 8 ? 6 : 1) void ln_fwd_kernel(const
     const f32x4 g = bf16x4_to_f32(*reinterpret_cast<const u32x2*>(gamma + cc));
     const f32x4 b = bf16x4_to_f32(*reinterpret_cast<const u32x2*>(beta + cc));
     const f32x4 o = (v[i] - mu) * r * g + b;
-    if (c < d) *reinterpret_cast<u32x2*>(y + (int64_t)row * d + c) = f32_to_bf16x4(o);
+    if (c < d) *reinterpret_cast<u32x2*>(y.p + rv_at(y, row, c)) = f32_to_bf16x4(o);
   }
 }
 
@@ -117,7 +117,7 @@ template <int NV, int RPW>
 __global__ __launch_bounds__(kThreads, 5) void ln_fwd_pipe_kernel(const float* __restrict__ xin,
                                                                   const uint16_t* __restrict__ gamma,
                                                                   const uint16_t* __restrict__ beta,
-                                                                  uint16_t* __restrict__ y,
+                                                                  rv_mat y,
                                                                   float* __restrict__ mean,
                                                                   float* __restrict__ rstd, int T, int d,
                                                                   float eps) {
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(kThreads, 5) void ln_fwd_pipe_kernel(const float* _
     const float r = rsqrtf(wave_sum_imm(q) / (float)d + eps);
     if (row >= T) return;
     if (l == 0) { mean[row] = mu; rstd[row] = r; }
-    char* yr = reinterpret_cast<char*>(y + (int64_t)row * d);
+    uint16_t* yr = y.p + (int64_t)row * y.ld;
     // gamma and beta are fetched again for every row (they stay in cache) rather than held in
     // 4 * NV registers across rows
     const char* gp = reinterpret_cast<const char*>(gamma);
@@ -166,7 +166,10 @@ __global__ __launch_bounds__(kThreads, 5) void ln_fwd_pipe_kernel(const float* _
       const f32x4 g = bf16x4_to_f32(*reinterpret_cast<const u32x2*>(gp + (cbo(i) >> 1)));
       const f32x4 b = bf16x4_to_f32(*reinterpret_cast<const u32x2*>(bp + (cbo(i) >> 1)));
       const f32x4 o = (v[i] - mu) * r * g + b;
-      if (l * 4 + 256 * i < d) *reinterpret_cast<u32x2*>(yr + (cbo(i) >> 1)) = f32_to_bf16x4(o);
+      if (l * 4 + 256 * i < d) {
+        const int c = (int)(cbo(i) >> 2);
+        *reinterpret_cast<u32x2*>(yr + (c >> 5) * y.bs + (c & 31)) = f32_to_bf16x4(o);
+      }
       if (NV > 4 && i % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // gamma/beta of four column groups at a time
     }
   };
@@ -192,7 +195,7 @@ template <int NV, int S, bool WITH_LN>
 __global__ __launch_bounds__(64) void ln_fwd_parts_kernel(const float* __restrict__ part, const uint16_t* __restrict__ bias,
                                                           const float* __restrict__ resid, float* __restrict__ xsum,
                                                           const uint16_t* __restrict__ gamma, const uint16_t* __restrict__ beta,
-                                                          uint16_t* __restrict__ y, float* __restrict__ mean,
+                                                          rv_mat y, float* __restrict__ mean,
                                                           float* __restrict__ rstd, uint16_t* __restrict__ out16, int T, int d,
                                                           float eps) {
   const int l = threadIdx.x, row = blockIdx.x;
@@ -250,7 +253,7 @@ __global__ __launch_bounds__(64) void ln_fwd_parts_kernel(const float* __restric
   for (int i = 0; i < NV; ++i) {
     const int c = l * 4 + 256 * i;
     const f32x4 o = (v[i] - mu) * r * bf16x4_to_f32(g[i]) + bf16x4_to_f32(b[i]);
-    if (c < d) *reinterpret_cast<u32x2*>(y + at + c) = f32_to_bf16x4(o);
+    if (c < d) *reinterpret_cast<u32x2*>(y.p + rv_at(y, row, c)) = f32_to_bf16x4(o);
   }
 }
 
@@ -282,7 +285,7 @@ __global__ __launch_bounds__(64 * kBwdWaves, S == 0 && NV <= 2 ? 6 : 1) void ln_
                                                                 const float* __restrict__ rstd,
                                                                 const uint16_t* __restrict__ gamma,
                                                                 const float* dres, float* dx,
-                                                                uint16_t* __restrict__ dx_bf16,
+                                                                rv_mat dx_bf16,
                                                                 float* __restrict__ part, int T, int d, int rows) {
   constexpr int CS = kBwdWaves;
   __shared__ float stat[2][RF][CS][2];
@@ -370,7 +373,7 @@ __global__ __launch_bounds__(64 * kBwdWaves, S == 0 && NV <= 2 ? 6 : 1) void ln_
             const f32x4 dxh = dyv * gam[i];
             const f32x4 o = (dxh - c1 - xh[q][i] * c2) * r[q] + rs[q][i];
             __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(dx + (int64_t)row * d + c));
-            if (dx_bf16) __builtin_nontemporal_store(f32_to_bf16x4(o), reinterpret_cast<u32x2*>(dx_bf16 + (int64_t)row * d + c));
+            if (dx_bf16.p) __builtin_nontemporal_store(f32_to_bf16x4(o), reinterpret_cast<u32x2*>(dx_bf16.p + rv_at(dx_bf16, row, c)));
             ag[i] += dyv * xh[q][i];
             ab[i] += dyv;
             ax[i] += o;
@@ -412,7 +415,7 @@ __global__ __launch_bounds__(64 * kBwdWaves, 5) void ln_bwd_pipe_kernel(const ui
                                                                 const float* __restrict__ rstd,
                                                                 const uint16_t* __restrict__ gamma,
                                                                 const float* dres, float* dx,
-                                                                uint16_t* __restrict__ dx_bf16,
+                                                                rv_mat dx_bf16,
                                                                 float* __restrict__ part, int T, int d) {
   constexpr int CS = kBwdWaves;
   constexpr int G = ROWS / RF;
@@ -484,8 +487,8 @@ __global__ __launch_bounds__(64 * kBwdWaves, 5) void ln_bwd_pipe_kernel(const ui
             const f32x4 dxh = dyv * gam[i];
             const f32x4 o = (dxh - c1 - w.xh[q][i] * c2) * w.r[q] + w.rs[q][i];
             __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(reinterpret_cast<char*>(dx + (int64_t)row * d) + cb[i]));
-            if (dx_bf16)
-              __builtin_nontemporal_store(f32_to_bf16x4(o), reinterpret_cast<u32x2*>(reinterpret_cast<char*>(dx_bf16 + (int64_t)row * d) + (cb[i] >> 1)));
+            if (dx_bf16.p)
+              __builtin_nontemporal_store(f32_to_bf16x4(o), reinterpret_cast<u32x2*>(dx_bf16.p + rv_at(dx_bf16, row, c)));
             ag[i] += dyv * w.xh[q][i];
             ab[i] += dyv;
             ax[i] += o;
@@ -604,8 +607,8 @@ int nv_for(int d) { return d <= 1024 ? 4 : d <= 2048 ? 8 : d <= 4096 ? 16 : d <=
 }  // namespace
 
 rv_status rv_ln_fwd(const void* x, int x_is_bf16, float* xcopy, const uint16_t* gamma, const uint16_t* beta,
-                    uint16_t* y, float* mean, float* rstd, int T, int d, float eps, hipStream_t st) {
-  if (!x || !gamma || !beta || !y || !mean || !rstd || T < 1 || d < 4 || d % 4 || (x_is_bf16 && !xcopy))
+                    rv_mat y, float* mean, float* rstd, int T, int d, float eps, hipStream_t st) {
+  if (!x || !gamma || !beta || !y.p || !mean || !rstd || T < 1 || d < 4 || d % 4 || (x_is_bf16 && !xcopy))
     return RV_E_INVAL;
   const int nv = nv_for(d);
   if (!nv) return RV_E_INVAL;
@@ -636,12 +639,12 @@ rv_status rv_ln_fwd(const void* x, int x_is_bf16, float* xcopy, const uint16_t* 
 }
 
 rv_status rv_ln_fwd_parts(const float* part, int S, const uint16_t* bias, const float* resid, float* xsum, const uint16_t* gamma,
-                          const uint16_t* beta, uint16_t* y, float* mean, float* rstd, uint16_t* out16, int T, int d, float eps,
+                          const uint16_t* beta, rv_mat y, float* mean, float* rstd, uint16_t* out16, int T, int d, float eps,
                           hipStream_t st) {
   if (!part || !bias || !resid || T < 1 || d < 4 || d % 4 || d > 4096) return RV_E_INVAL;
-  if (y ? !xsum || !gamma || !beta || !mean || !rstd : !out16) return RV_E_INVAL;
+  if (y.p ? !xsum || !gamma || !beta || !mean || !rstd : !out16) return RV_E_INVAL;
 #define RV_LN_FP(NV, S)                                                                                                        \
-  if (y) hipLaunchKernelGGL((ln_fwd_parts_kernel<NV, S, true>), dim3(T), dim3(64), 0, st, part, bias, resid, xsum, gamma, beta, y, \
+  if (y.p) hipLaunchKernelGGL((ln_fwd_parts_kernel<NV, S, true>), dim3(T), dim3(64), 0, st, part, bias, resid, xsum, gamma, beta, y, \
                             mean, rstd, out16, T, d, eps);                                                                     \
   else hipLaunchKernelGGL((ln_fwd_parts_kernel<NV, S, false>), dim3(T), dim3(64), 0, st, part, bias, resid, xsum, gamma, beta, y,  \
                           mean, rstd, out16, T, d, eps);
@@ -681,7 +684,7 @@ int rv_ln_bwd_parts(int T, int d) {
 }
 
 rv_status rv_ln_bwd(const uint16_t* dy, const float* x, const float* mean, const float* rstd,
-                    const uint16_t* gamma, const float* dres, float* dx, uint16_t* dx_bf16, float* part,
+                    const uint16_t* gamma, const float* dres, float* dx, rv_mat dx_bf16, float* part,
                     int T, int d, hipStream_t st, int rows) {
   if (!dy || !x || !mean || !rstd || !gamma || !dres || !dx || !part || T < 1 || d < 4 || d % 4 || d > 4096)
     return RV_E_INVAL;
@@ -701,7 +704,7 @@ rv_status rv_ln_bwd(const uint16_t* dy, const float* x, const float* mean, const
 }
 
 rv_status rv_ln_bwd_parts_in(const float* dy_part, int S, const float* x, const float* mean, const float* rstd, const uint16_t* gamma,
-                             const float* dres, float* dx, uint16_t* dx_bf16, float* part, int T, int d, hipStream_t st, int rows) {
+                             const float* dres, float* dx, rv_mat dx_bf16, float* part, int T, int d, hipStream_t st, int rows) {
   if (!dy_part || !x || !mean || !rstd || !gamma || !dres || !dx || !part || T < 1 || d < 4 || d % 4 || d > 4096 || rows % 2)
     return RV_E_INVAL;
   dim3 grid((T + rows - 1) / rows), blk(64 * kBwdWaves);
@@ -760,14 +763,14 @@ rv_status rv_reduce_rows(const rv_reduce_job* jobs, int njobs, float eta, hipStr
 extern "C" rv_status rv_k_layernorm_fwd(const void* x, int x_is_bf16, float* xcopy, const void* gamma,
                                         const void* beta, void* y, float* mean, float* rstd, int T, int d,
                                         float eps, void* stream) {
-  return rv_ln_fwd(x, x_is_bf16, xcopy, (const uint16_t*)gamma, (const uint16_t*)beta, (uint16_t*)y, mean, rstd,
+  return rv_ln_fwd(x, x_is_bf16, xcopy, (const uint16_t*)gamma, (const uint16_t*)beta, rv_rows(y, d), mean, rstd,
                    T, d, eps, (hipStream_t)stream);
 }
 
 extern "C" rv_status rv_k_layernorm_fwd_parts(const float* part, int parts, const void* bias, const float* resid, float* xsum,
                                               const void* gamma, const void* beta, void* y, float* mean, float* rstd, void* out16,
                                               int T, int d, float eps, void* stream) {
-  return rv_ln_fwd_parts(part, parts, (const uint16_t*)bias, resid, xsum, (const uint16_t*)gamma, (const uint16_t*)beta, (uint16_t*)y,
+  return rv_ln_fwd_parts(part, parts, (const uint16_t*)bias, resid, xsum, (const uint16_t*)gamma, (const uint16_t*)beta, rv_rows(y, d),
                          mean, rstd, (uint16_t*)out16, T, d, eps, (hipStream_t)stream);
 }
 
@@ -775,7 +778,7 @@ extern "C" rv_status rv_k_layernorm_bwd_parts(const float* dy_part, int parts, c
                                               const void* gamma, const float* dres, float* dx, void* dx_bf16, float* part,
                                               int rows, int T, int d, void* stream) {
   if (rows != 2 && rows != 4 && rows != 8 && rows != 16) return RV_E_INVAL;
-  return rv_ln_bwd_parts_in(dy_part, parts, x, mean, rstd, (const uint16_t*)gamma, dres, dx, (uint16_t*)dx_bf16, part, T, d,
+  return rv_ln_bwd_parts_in(dy_part, parts, x, mean, rstd, (const uint16_t*)gamma, dres, dx, rv_rows(dx_bf16, d), part, T, d,
                             (hipStream_t)stream, rows);
 }
 
@@ -785,7 +788,7 @@ extern "C" rv_status rv_k_layernorm_bwd(const void* dy, const float* x, const fl
                                         void* stream) {
   hipStream_t st = (hipStream_t)stream;
   const int rows = std::max(8, rv_ln_bwd_rows(T, d));   // the caller's workspace holds ceil(T / 8) partial rows
-  RV_TRY(rv_ln_bwd((const uint16_t*)dy, x, mean, rstd, (const uint16_t*)gamma, dres, dx, (uint16_t*)dx_bf16,
+  RV_TRY(rv_ln_bwd((const uint16_t*)dy, x, mean, rstd, (const uint16_t*)gamma, dres, dx, rv_rows(dx_bf16, d),
                    part, T, d, st, rows));
   const int R = (T + rows - 1) / rows;
   rv_reduce_job job[3];

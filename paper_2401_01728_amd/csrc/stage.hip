@@ -8,6 +8,7 @@
 //     its own, so tau+2 slots are kept: the new version can then be written piece by piece, by
 //     the kernels that produce the gradient, while the backward still reads its own.
 // All device work is enqueued on the stage's stream by mlp.hip / decoder.hip / update.hip.
+#include <cstring>
 #include <new>
 #include "internal.h"
 
@@ -19,7 +20,7 @@ int find_slot(const rv_stage* s, int64_t mb) {
   return -1;
 }
 
-int copy_kind(const rv_stage* s) { return s->dtype == RV_BF16 ? 1 : 2; }
+int copy_kind(const rv_stage* s) { return s->dtype == RV_BF16 ? 3 : 2; }
 
 void free_all(rv_stage* s) {
   if (!s) return;
@@ -121,7 +122,7 @@ extern "C" int rv_stage_in_flight(const rv_stage* s) {
 extern "C" rv_status rv_stage_set_params(rv_stage* s, const float* flat, size_t n) {
   if (!s || !flat || n != s->P || s->sync_dst >= 0) return RV_E_INVAL;
   if (rv_stage_in_flight(s) != 0) return RV_E_INVAL;
-  return rv_launch_set(flat, s->P, s->master, s->ver[s->cur], copy_kind(s), s->st);
+  return rv_launch_set(flat, s->P, s->master, s->ver[s->cur], copy_kind(s), s->st, s->ver_map);
 }
 
 extern "C" rv_status rv_stage_set_optimizer(rv_stage* s, float momentum, float weight_decay) {
@@ -194,8 +195,18 @@ extern "C" rv_status rv_cluster_sync_fork(rv_stage* const* stages, int C, int R,
     RV_HIP_TRY(hipStreamWaitEvent(ss, owner->ev_sync_ready, 0));
   }
   for (int c = 0; c < C; ++c) versions[c] = stages[c]->ver[dst[c]];
-  RV_TRY(rv_average_publish(masters, versions, copy_kind(owner), C, owner->P, R, p ? p->grad : nullptr, pending >= 0 ? pending : 0,
-                            p ? p->eta : 0.f, ss));
+  const float* pend = p ? p->grad : nullptr;
+  const int at = p ? pending : 0;
+  const float eta = p ? p->eta : 0.f;
+  bool one_map = true;           // stages of as many parameters may still be of different widths
+  for (int c = 1; c < C; ++c) one_map = one_map && memcmp(&stages[c]->ver_map, &owner->ver_map, sizeof(rv_ver_map)) == 0;
+  if (one_map) {
+    RV_TRY(rv_average_publish(masters, versions, copy_kind(owner), owner->ver_map, C, owner->P, R, pend, at, eta, ss));
+  } else {
+    RV_TRY(rv_cluster_average(masters, C, owner->P, R, nullptr, 1, pend, at, eta, ss));
+    for (int c = 0; c < C; ++c)
+      RV_TRY(rv_launch_set(masters[c], owner->P, masters[c], versions[c], copy_kind(owner), ss, stages[c]->ver_map));
+  }
   if (state) RV_TRY(rv_cluster_average(vels, C, owner->P, R, nullptr, 1, nullptr, 0, 0.f, ss));
   if (forked) RV_HIP_TRY(hipEventRecord(owner->ev_sync_done, ss));
   for (int c = 0; c < C; ++c) {
@@ -271,7 +282,7 @@ extern "C" rv_status rv_stage_last_grad(const rv_stage* s, float* flat_out, size
 // delayed update (Eq. 2, or its momentum / weight-decay variant) of parameters [off, off+n)
 // into the version slot chosen for this backward
 rv_status rv_stage_update_range(rv_stage* s, size_t off, size_t n, hipStream_t st) {
-  const int kind = s->dtype == RV_BF16 ? 1 : 2;
+  const int kind = copy_kind(s);
   const float* g = s->grad + off;
   if (s->defer) return RV_OK;   // the update stays pending
   if (s->accum > 1) {   // sum the group's gradients; only its last microbatch updates
@@ -282,8 +293,8 @@ rv_status rv_stage_update_range(rv_stage* s, size_t off, size_t n, hipStream_t s
   void* copy = (char*)s->ver[s->upd_dst] + off * s->ver_elem;
   if (s->vel)
     return rv_launch_update_momentum(s->master + off, g, s->vel + off, n, s->eta, s->momentum, s->weight_decay,
-                                     copy, kind, st);
-  return rv_launch_update(s->master + off, g, n, s->eta, copy, kind, st);
+                                     copy, kind, st, s->ver_map);
+  return rv_launch_update(s->master + off, g, n, s->eta, copy, kind, st, s->ver_map);   // (decoder: a range of whole blocks)
 }
 
 namespace {

@@ -19,7 +19,7 @@ constexpr int kThreads = 256;
 constexpr int kVec = 1;
 constexpr int kTile = kThreads * kVec * 4;
 
-// COPY: 0 none, 1 bf16, 2 fp32.  Without the bf16 version w and g stream through with non-temporal
+// COPY: 0 none, 1 bf16, 2 fp32, 3 bf16 where the map puts it.  Without the bf16 version w and g stream through with non-temporal
 // accesses (nothing is read twice; measured 76 % -> 81 % of HBM peak).  With it, only g does: every
 // non-temporal access to w or to the version measured 3-5 % slower there (73 % -> 69-70 %), and so
 // did 8 consecutive parameters per lane for a 16-byte bf16 store (the lanes of a wave must stay
@@ -28,14 +28,14 @@ template <int COPY>
 __global__ __launch_bounds__(kThreads) void update_kernel(float* __restrict__ w,
                                                           const float* __restrict__ g, uint64_t n,
                                                           float eta, void* __restrict__ copy,
-                                                          int aligned) {
-  const uint64_t base = (uint64_t)blockIdx.x * kTile;
+                                                          int aligned, rv_ver_map map) {
+  const uint64_t base = (uint64_t)(COPY == 3 ? rv_ver_tile(blockIdx.x, gridDim.x) : blockIdx.x) * kTile;
   if (aligned && base + kTile <= n) {
     f4 wv[kVec], gv[kVec];
 #pragma unroll
     for (int u = 0; u < kVec; ++u) {
       uint64_t e = base + (uint64_t)(u * kThreads + threadIdx.x) * 4;
-      if (COPY == 1) wv[u] = *reinterpret_cast<const f4*>(w + e);
+      if (COPY == 1 || COPY == 3) wv[u] = *reinterpret_cast<const f4*>(w + e);
       else wv[u] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(w + e));
       gv[u] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(g + e));
     }
@@ -47,13 +47,13 @@ __global__ __launch_bounds__(kThreads) void update_kernel(float* __restrict__ w,
       r.y = __fmaf_rn(-eta, gv[u].y, wv[u].y);
       r.z = __fmaf_rn(-eta, gv[u].z, wv[u].z);
       r.w = __fmaf_rn(-eta, gv[u].w, wv[u].w);
-      if (COPY == 1) *reinterpret_cast<f4*>(w + e) = r;
+      if (COPY == 1 || COPY == 3) *reinterpret_cast<f4*>(w + e) = r;
       else __builtin_nontemporal_store(r, reinterpret_cast<f4*>(w + e));
-      if (COPY == 1) {
+      if (COPY == 1 || COPY == 3) {
         u2 pk;
         pk.x = rv_pack_bf16x2(r.x, r.y);
         pk.y = rv_pack_bf16x2(r.z, r.w);
-        *reinterpret_cast<u2*>(reinterpret_cast<uint16_t*>(copy) + e) = pk;
+        *reinterpret_cast<u2*>(reinterpret_cast<uint16_t*>(copy) + (COPY == 3 ? rv_ver_at(map, base, e) : e)) = pk;
       } else if (COPY == 2) {
         __builtin_nontemporal_store(r, reinterpret_cast<f4*>(reinterpret_cast<float*>(copy) + e));
       }
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kThreads) void update_kernel(float* __restrict__ w,
     if (i >= n) break;
     float r = __fmaf_rn(-eta, g[i], w[i]);
     w[i] = r;
-    if (COPY == 1) reinterpret_cast<uint16_t*>(copy)[i] = rv_f32_to_bf16(r);
+    if (COPY == 1 || COPY == 3) reinterpret_cast<uint16_t*>(copy)[COPY == 3 ? rv_ver_at(map, base, i) : i] = rv_f32_to_bf16(r);
     if (COPY == 2) reinterpret_cast<float*>(copy)[i] = r;
   }
 }
@@ -80,8 +80,8 @@ __global__ __launch_bounds__(kThreads) void update_momentum_kernel(float* __rest
                                                                    const float* __restrict__ g,
                                                                    float* __restrict__ v, uint64_t n,
                                                                    float eta, float mu, float wd,
-                                                                   void* __restrict__ copy, int aligned) {
-  const uint64_t base = (uint64_t)blockIdx.x * kTile;
+                                                                   void* __restrict__ copy, int aligned, rv_ver_map map) {
+  const uint64_t base = (uint64_t)(COPY == 3 ? rv_ver_tile(blockIdx.x, gridDim.x) : blockIdx.x) * kTile;
   auto step = [&](float wi, float gi, float& vi) {
     const float d = __fmaf_rn(wd, wi, gi);
     vi = __fmaf_rn(mu, vi, d);
@@ -103,11 +103,11 @@ __global__ __launch_bounds__(kThreads) void update_momentum_kernel(float* __rest
       }
       *reinterpret_cast<f4*>(w + e) = r;
       *reinterpret_cast<f4*>(v + e) = vv;
-      if (COPY == 1) {
+      if (COPY == 1 || COPY == 3) {
         u2 pk;
         pk.x = rv_pack_bf16x2(r.x, r.y);
         pk.y = rv_pack_bf16x2(r.z, r.w);
-        *reinterpret_cast<u2*>(reinterpret_cast<uint16_t*>(copy) + e) = pk;
+        *reinterpret_cast<u2*>(reinterpret_cast<uint16_t*>(copy) + (COPY == 3 ? rv_ver_at(map, base, e) : e)) = pk;
       } else if (COPY == 2) {
         *reinterpret_cast<f4*>(reinterpret_cast<float*>(copy) + e) = r;
       }
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(kThreads) void update_momentum_kernel(float* __rest
     float vi = v[i];
     const float r = step(w[i], g[i], vi);
     w[i] = r; v[i] = vi;
-    if (COPY == 1) reinterpret_cast<uint16_t*>(copy)[i] = rv_f32_to_bf16(r);
+    if (COPY == 1 || COPY == 3) reinterpret_cast<uint16_t*>(copy)[COPY == 3 ? rv_ver_at(map, base, i) : i] = rv_f32_to_bf16(r);
     if (COPY == 2) reinterpret_cast<float*>(copy)[i] = r;
   }
 }
@@ -151,16 +151,17 @@ __global__ __launch_bounds__(kThreads) void accumulate_kernel(float* __restrict_
 
 // set_params: a flat vector becomes the master and, converted, a weight version, in one pass
 template <int COPY>
-__global__ __launch_bounds__(kThreads) void set_kernel(const float* w, uint64_t n, float* master, void* __restrict__ copy) {
-  const uint64_t e = ((uint64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
+__global__ __launch_bounds__(kThreads) void set_kernel(const float* w, uint64_t n, float* master, void* __restrict__ copy, rv_ver_map map) {
+  const uint64_t base = (uint64_t)(COPY == 3 ? rv_ver_tile(blockIdx.x, gridDim.x) : blockIdx.x) * (kThreads * 4);
+  const uint64_t e = base + threadIdx.x * 4;
   if (e + 4 <= n) {
     typedef f4 f4_u __attribute__((aligned(4)));           // the caller's vector may start anywhere
     const f4 v = *reinterpret_cast<const f4_u*>(w + e);
     *reinterpret_cast<f4*>(master + e) = v;
-    if (COPY == 1) {
+    if (COPY == 3) {
       u2 pk;
       pk.x = rv_pack_bf16x2(v.x, v.y); pk.y = rv_pack_bf16x2(v.z, v.w);
-      *reinterpret_cast<u2*>(reinterpret_cast<uint16_t*>(copy) + e) = pk;
+      *reinterpret_cast<u2*>(reinterpret_cast<uint16_t*>(copy) + rv_ver_at(map, base, e)) = pk;
     } else {
       *reinterpret_cast<f4*>(reinterpret_cast<float*>(copy) + e) = v;
     }
@@ -169,7 +170,7 @@ __global__ __launch_bounds__(kThreads) void set_kernel(const float* w, uint64_t 
   for (uint64_t i = e; i < n; ++i) {
     const float v = w[i];
     master[i] = v;
-    if (COPY == 1) reinterpret_cast<uint16_t*>(copy)[i] = rv_f32_to_bf16(v);
+    if (COPY == 3) reinterpret_cast<uint16_t*>(copy)[rv_ver_at(map, base, i)] = rv_f32_to_bf16(v);
     else reinterpret_cast<float*>(copy)[i] = v;
   }
 }
@@ -204,32 +205,36 @@ __global__ __launch_bounds__(kPadSlots * RV_VER_PAD / 4) void clear_pads_kernel(
 }  // namespace
 
 rv_status rv_launch_update(float* w, const float* g, size_t n, float eta, void* copy, int copy_kind,
-                           hipStream_t st) {
+                           hipStream_t st, const rv_ver_map& map) {
   if (n == 0) return RV_OK;
   int aligned = ((((uintptr_t)w) | ((uintptr_t)g)) & 15) == 0;
   if (copy && (((uintptr_t)copy) & 15)) aligned = 0;
   unsigned blocks = (unsigned)((n + kTile - 1) / kTile);
   if (!copy || copy_kind == 0)
-    hipLaunchKernelGGL(update_kernel<0>, dim3(blocks), dim3(kThreads), 0, st, w, g, n, eta, nullptr, aligned);
+    hipLaunchKernelGGL(update_kernel<0>, dim3(blocks), dim3(kThreads), 0, st, w, g, n, eta, nullptr, aligned, map);
   else if (copy_kind == 1)
-    hipLaunchKernelGGL(update_kernel<1>, dim3(blocks), dim3(kThreads), 0, st, w, g, n, eta, copy, aligned);
+    hipLaunchKernelGGL(update_kernel<1>, dim3(blocks), dim3(kThreads), 0, st, w, g, n, eta, copy, aligned, map);
+  else if (copy_kind == 3)
+    hipLaunchKernelGGL(update_kernel<3>, dim3(blocks), dim3(kThreads), 0, st, w, g, n, eta, copy, aligned, map);
   else
-    hipLaunchKernelGGL(update_kernel<2>, dim3(blocks), dim3(kThreads), 0, st, w, g, n, eta, copy, aligned);
+    hipLaunchKernelGGL(update_kernel<2>, dim3(blocks), dim3(kThreads), 0, st, w, g, n, eta, copy, aligned, map);
   return rv_launch_status();
 }
 
 rv_status rv_launch_update_momentum(float* w, const float* g, float* v, size_t n, float eta, float mu, float wd,
-                                    void* copy, int copy_kind, hipStream_t st) {
+                                    void* copy, int copy_kind, hipStream_t st, const rv_ver_map& map) {
   if (n == 0) return RV_OK;
   int aligned = ((((uintptr_t)w) | ((uintptr_t)g) | ((uintptr_t)v)) & 15) == 0;
   if (copy && (((uintptr_t)copy) & 15)) aligned = 0;
   unsigned blocks = (unsigned)((n + kTile - 1) / kTile);
   if (!copy || copy_kind == 0)
-    hipLaunchKernelGGL(update_momentum_kernel<0>, dim3(blocks), dim3(kThreads), 0, st, w, g, v, n, eta, mu, wd, nullptr, aligned);
+    hipLaunchKernelGGL(update_momentum_kernel<0>, dim3(blocks), dim3(kThreads), 0, st, w, g, v, n, eta, mu, wd, nullptr, aligned, map);
   else if (copy_kind == 1)
-    hipLaunchKernelGGL(update_momentum_kernel<1>, dim3(blocks), dim3(kThreads), 0, st, w, g, v, n, eta, mu, wd, copy, aligned);
+    hipLaunchKernelGGL(update_momentum_kernel<1>, dim3(blocks), dim3(kThreads), 0, st, w, g, v, n, eta, mu, wd, copy, aligned, map);
+  else if (copy_kind == 3)
+    hipLaunchKernelGGL(update_momentum_kernel<3>, dim3(blocks), dim3(kThreads), 0, st, w, g, v, n, eta, mu, wd, copy, aligned, map);
   else
-    hipLaunchKernelGGL(update_momentum_kernel<2>, dim3(blocks), dim3(kThreads), 0, st, w, g, v, n, eta, mu, wd, copy, aligned);
+    hipLaunchKernelGGL(update_momentum_kernel<2>, dim3(blocks), dim3(kThreads), 0, st, w, g, v, n, eta, mu, wd, copy, aligned, map);
   return rv_launch_status();
 }
 
@@ -263,13 +268,13 @@ rv_status rv_launch_copy(float* dst, const float* src, size_t n, hipStream_t st)
   return rv_launch_status();
 }
 
-rv_status rv_launch_set(const float* w, size_t n, float* master, void* copy, int copy_kind, hipStream_t st) {
+rv_status rv_launch_set(const float* w, size_t n, float* master, void* copy, int copy_kind, hipStream_t st, const rv_ver_map& map) {
   if (n == 0) return RV_OK;
   const unsigned blocks = (unsigned)((n + kThreads * 4 - 1) / (kThreads * 4));
-  if (copy_kind == 1)
-    hipLaunchKernelGGL(set_kernel<1>, dim3(blocks), dim3(kThreads), 0, st, w, n, master, copy);
+  if (copy_kind == 3)
+    hipLaunchKernelGGL(set_kernel<3>, dim3(blocks), dim3(kThreads), 0, st, w, n, master, copy, map);
   else
-    hipLaunchKernelGGL(set_kernel<2>, dim3(blocks), dim3(kThreads), 0, st, w, n, master, copy);
+    hipLaunchKernelGGL(set_kernel<2>, dim3(blocks), dim3(kThreads), 0, st, w, n, master, copy, map);
   return rv_launch_status();
 }
 

@@ -327,3 +327,36 @@ def test_side_work_schedules(L, d, H, f, S, mb):
     check_update(host64(g.get_params()), w0, gg, 1e-3)
     g.backward(1, dy)                            # and the halves apart (fp32 column sums per tile row, whose height may differ)
     close(host64(g.last_grad()), gg, 1e-5, "grad, apart", group=tag + ", apart")
+
+
+# Whichever kernel published a version - the gradient products' epilogue, the update with its momentum form, an averaging over
+# stages of one shape or of two - holds the bf16 rounding of the masters: a fresh stage given those masters answers bit for bit alike
+@pytest.mark.parametrize("how", ["fused", "split tiles", "accumulate", "momentum", "average", "average of two shapes"])
+def test_versions_hold_the_masters(how):
+    import paper_2401_01728_amd as rv
+    d, f, mb, S = (2048, 4096, 1, 64) if how == "fused" else (192, 320, 3, 64)
+    make = lambda L, d, f: rv.Stage.decoder(L, d, d // 64, f, S, mb, 0, 1e-2)
+    st = [make(2, d, f)]
+    if how == "accumulate":
+        st[0].set_accumulation(2)
+    if how == "momentum":
+        st[0].set_optimizer(0.9, 5e-4)
+    if how == "average":
+        st.append(make(2, d, f))
+    if how == "average of two shapes":     # of as many parameters each
+        st = [make(1, 64, 768), make(1, 128, 192)]
+        assert st[0].num_params == st[1].num_params
+    for k, s in enumerate(st):
+        s.set_params(dev(decoder_params_host(80 + k, 2, d, f)[:s.num_params]) if "two" not in how else
+                     torch.randn(s.num_params, device="cuda") * 0.02)
+        for t in range(2):
+            x, dy = bf16_normal(81, 2 * t, s.in_shape)[0], bf16_normal(81, 2 * t + 1, s.in_shape, std=1e-2)[0]
+            s.forward(t, x)
+            s.backward(t, dy)
+    if len(st) > 1:
+        rv.api.cluster_sync(st, 3)
+    for s in st:
+        fresh = make(1 if "two" in how else 2, s.dims[0], s.dims[2])
+        fresh.set_params(s.get_params())
+        x = bf16_normal(82, 0, s.in_shape)[0]
+        assert torch.equal(s.forward(9, x), fresh.forward(9, x))
