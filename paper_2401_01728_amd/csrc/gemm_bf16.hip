@@ -1172,38 +1172,32 @@ rv_status pick_part(const rv_gemm_args& g, int S, float* part, hipStream_t st) {
 //   1128  128x128, 1065 / 1064 64x64, 1032 32x64: the contraction split inside the workgroup over
 //         2, 2 / 4 and 8 groups of waves.
 // The automatic choice among the first three minimises  rounds * tile area * workgroups per CU / efficiency,
-// rounds = ceil(tiles / (256 CUs * workgroups per CU)), efficiencies measured ratios.  By the time model below
-// instead (as it stood for a while), launches that fill between half a round and a round of 2192 took that tile and up
-// to 39 % longer: 8192x1280x3840 106 us against 76, 8192x1280x5120 146 against 111, 2048x4608x1536 47 against 37, 4096x2560x1280
-// 46 against 40.  Over 309 launches of 256 .. 8192 rows alone the rule is on average 0.3 % above the best of the three,
-// the model was 1.5 %; with 0.85 for 2128 the rule takes 132 us for 8192x4800x1600 instead of 121.
-// Whether the contraction is split is decided by the modelled time
-//   rounds * (f + turns * t),  turns = k-tiles per group,
-// f and t in us, t between t0 (a launch that leaves most CUs idle) and t1 (one that fills them), fitted to
-// launches of 64 .. 8192 rows alone.  A product of few tiles is one walk along K: 256x448x1792 takes 36 us
-// with 5256, 20 with 2128 and 7 with 1032; 128x1024x4096 75 / 44 / 15; 1152x768x3072 59 / 34 / 16
-// (1064); 4096x1024x4096 77 / 48 / 36 (1128); 8192x6400x1600 183 / 204 / 261.
-struct TileForm { int code, bm, bn, k, per_cu; float f, t0, t1; };
+// rounds = ceil(tiles / (256 CUs * workgroups per CU)), efficiencies measured ratios: over 309 launches of 256 .. 8192 rows
+// alone on average 0.3 % above the best of the three; with 0.85 for 2128 the rule takes 132 us for 8192x4800x1600 instead of 121.
+// Whether the contraction is split is decided by the modelled time, us,
+//   rounds * (f + turns * t) + out * M N / 1e6,  turns = k-tiles per group,
+// t between t0 (a launch that leaves most CUs idle) and t1 (one that fills them), fitted to 488 launches of 64 .. 8192 rows
+// alone, operands in blocks of columns, weights cold.  A product of few tiles is one walk along K: 256x448x1792 takes 43 us
+// with 5256, 22 with 2128 and 7 with 1032; 512x4096x1024 with GELU' 32 / 17 / 11 (1065); 1152x768x3072 65 / 36 / 14 (1064);
+// 1152x2048x8192 152 / 108 / 72 (1128); 2048x1024x4096 82 / 44 / 29 (1065); 8192x6400x1600 183 / 204 / 261.
+// A split form is taken where the model has it a tenth faster, on the shape alone, so that a product has the same bits beside
+// other streams as by itself; and not from 64 tiles of 256x256 on: it takes more CU time per flop, which the other streams
+// of a step could have used.  Stage steps, split where a tenth faster / not from 64 tiles on / nowhere, us:
+//   4 blocks d 1024, 4096 tokens 1762 / 1718 / 1714    6 blocks d 768, 1152 tokens, 4 microbatches 4847 / 4850 / 5260
+//   8 blocks d 832, 2048 tokens  1535 / 1443           9 blocks d 896, 4032 tokens (64 tiles)     3382 / 3520
+//   12 blocks d 640, 2880 tokens 2230 / - / 2400       7 blocks d 1536, 1536 tokens, 2 microbatches 5890 / - / 6230
+struct TileForm { int code, bm, bn, k, per_cu; float f, t0, t1, out; };
 constexpr TileForm kForms[] = {
-    {5256, 256, 256, 32, 1, 4.9f, 0.53f, 0.86f}, {2192, 128, 256, 32, 2, 3.5f, 0.42f, 1.05f}, {2128, 128, 128, 64, 2, 2.8f, 0.58f, 1.10f},
-    {1128, 128, 128, 64, 1, 3.9f, 0.43f, 0.56f}, {1065, 64, 64, 64, 2, 2.3f, 0.265f, 0.47f}, {1064, 64, 64, 128, 1, 2.7f, 0.44f, 0.64f},
-    {1032, 32, 64, 256, 1, 2.4f, 0.72f, 0.82f}};
+    {5256, 256, 256, 32, 1, 8.9f, 0.51f, 0.64f, 0.63f}, {2192, 128, 256, 32, 2, 6.1f, 0.45f, 0.77f, 0.66f},
+    {2128, 128, 128, 64, 2, 3.1f, 0.65f, 0.91f, 0.77f}, {1128, 128, 128, 64, 1, 4.3f, 0.47f, 0.48f, 0.68f},
+    {1065, 64, 64, 64, 2, 3.1f, 0.27f, 0.37f, 0.50f},   {1064, 64, 64, 128, 1, 3.9f, 0.43f, 0.40f, 0.11f},
+    {1032, 32, 64, 256, 1, 3.3f, 0.66f, 0.57f, 0.f}};
 // the modelled time of a form whose contraction is cut into S stretches
 float form_time(const TileForm& c, int M, int N, int K, int S) {
   const float tiles = (float)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * S, slots = 256.f * c.per_cu;
   const float fill = tiles < slots ? tiles / slots : 1.f;
-  return ceilf(tiles / slots) * (c.f + ceilf((float)K / S / c.k) * (c.t0 + (c.t1 - c.t0) * fill * fill));
+  return ceilf(tiles / slots) * (c.f + ceilf((float)K / S / c.k) * (c.t0 + (c.t1 - c.t0) * fill * fill)) + c.out * 1e-6f * M * N * S;
 }
-int best_form(int M, int N, int K, int codes_from, int codes_to, float& least) {
-  int best = 0;
-  for (const TileForm& c : kForms) {
-    if (c.code < codes_from || c.code >= codes_to) continue;
-    const float time = form_time(c, M, N, K, 1);
-    if (!best || time < least) { best = c.code; least = time; }
-  }
-  return best;
-}
-
 int in_order_form(int M, int N) {
   auto cost = [&](int bm, int bn, int bpc, double eff) {
     const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
@@ -1212,24 +1206,31 @@ int in_order_form(int M, int N) {
   const double c256 = cost(256, 256, 1, 1.0), c192 = cost(128, 256, 2, 0.92), c128 = cost(128, 128, 2, 0.83);
   return c256 <= c192 && c256 <= c128 ? 5256 : c192 <= c128 ? 2192 : 2128;
 }
+// the form of a whole product where nobody shares the chip, and its modelled time (k32: form 1032 is there)
+int whole_form(int M, int N, int K, bool k32, float& time) {
+  int best = in_order_form(M, N);
+  for (const TileForm& c : kForms)
+    if (c.code == best) time = form_time(c, M, N, K, 1);
+  if (((M + 255) / 256) * ((N + 255) / 256) >= 64) return best;
+  float least = 0.9f * time;
+  for (const TileForm& c : kForms) {
+    if (c.code >= 2000 || (c.code == 1032 && !k32)) continue;
+    const float t = form_time(c, M, N, K, 1);
+    if (t < least) { best = c.code; least = time = t; }
+  }
+  return best;
+}
 
 template <bool AKM, bool BKM, int EPI>
 rv_status pick_tile(const rv_gemm_args& g, hipStream_t st) {
   int tile = g.tile;
   if (tile == 0) {
-    // Whether the contraction is split depends on the shape alone, so that a product has the same
-    // bits beside other streams as by itself; and it has to gain a quarter of the launch's time: a split
-    // tile takes more CU time per flop, which the other streams of a step could have used (with
-    // 4096x1024x4096 split, 49 against 61 us alone, the step of the 1024-wide stage is 6 % longer).
-    float in_order = 0.f, split = 0.f;
-    best_form(g.M, g.N, g.K, 2000, 10000, in_order);
-    const int s = best_form(g.M, g.N, g.K, AKM ? 1033 : 0, 2000, split);
+    float time;   // (whether the contraction is split: by the shape alone)
+    tile = whole_form(g.M, g.N, g.K, !AKM, time);
     const long t256 = (long)((g.M + 255) / 256) * ((g.N + 255) / 256);
-    if (split < 0.75f * in_order) tile = s;
     // Measured inside the stage step (d = 1024, 1600, 2048): what a launch leaves of the chip is
     // used by the other streams, so CU time per flop counts for more than its own duration.
-    else if (g.sharing == 2 || (g.sharing && t256 >= 128)) tile = 5256;
-    else tile = in_order_form(g.M, g.N);
+    if (tile >= 2000 && (g.sharing == 2 || (g.sharing && t256 >= 128))) tile = 5256;
   }
   if constexpr (!AKM) {
     if (tile == 1032) return launch_split<32, 64, 8, 2, 3, AKM, BKM, EPI>(g, st);
@@ -1296,23 +1297,22 @@ rv_status rv_gemm_bf16(const rv_gemm_args& g, hipStream_t st) {
 }
 
 // The form and the number of stretches of a product whose partial sums the next kernel can add: the least modelled time,
-// 8 bytes per partial sum (written and read back) at 5 TB/s, if that takes a fifth off the best whole product; S = 1: none does.
-// Weights not in any cache, whole / cut, us: 128x1024x4096 21.0 / 7.3 (64x64 tiles, S 8) and, k-contiguous weights, 16.9 / 7.1;
-// 128x1024x3072 13.7 / 6.7; 256x448x1792 7.1 / 5.4 (32x64, 4); 128x1024x1024 6.0 / 5.0; 2048x1024x4096 44.7 / 28.1 (128x128, 2).  Not
-// taken, as the pieces' traffic eats the gain: 512x1024x4096 19.9 / 15.3, 1152x768x3072 16.1 / 14.0, 2048x1024x1024 11.7 / 13.0.
+// with 4 bytes per partial sum read back at 5 TB/s, if that takes a tenth off the best whole product; S = 1: none does.
+// Weights cold, best whole form / cut (with the reading back), us: 64x2048x8192 30.1 / 11.3 (64x64 tiles, S 8), 128x1024x4096
+// 11.6 / 7.1 (32x64, 4), 256x2048x8192 29.7 / 23.0 (64x64, 4), 1024x2048x8192 66.9 / 46.0 (128x128, 2), 1152x1600x6400 50.2 / 35.7,
+// 256x448x1792 7.2 / 5.9.  Over 130 products of 64 .. 2048 rows the modelled ratio is below the measured one by 0.1 .. 0.2 on the
+// short walks and above it by as much on the long ones; a modelled tenth was 0 .. 30 % measured.
 // Four stages of 4 blocks of d 1024 on 128 tokens, forward and backward, with their average 3137 -> 2761 us, stage step of 12
 // blocks of d 448 on 256 tokens 924 -> 852 us (with what split_tile and the early requests give).
 rv_part_form rv_gemm_part_form(int M, int N, int K) {
-  float whole = 0.f, in_order = 0.f;
-  best_form(M, N, K, 2000, 10000, in_order);
-  best_form(M, N, K, 0, 2000, whole);
-  if (!(whole < 0.75f * in_order)) whole = in_order;   // (what pick_tile takes)
+  float whole;
+  whole_form(M, N, K, true, whole);
   rv_part_form best = {0, 1};
-  float least = 0.8f * whole;
+  float least = 0.9f * whole;
   for (const TileForm& c : kForms) {
     if (c.code >= 2000) continue;
     for (int S = 2; S <= RV_GEMM_PARTS_MAX && S * c.k <= K; S *= 2) {
-      const float time = form_time(c, M, N, K, S) + (float)M * N * S * 8.f / 5e6f;
+      const float time = form_time(c, M, N, K, S) + (float)M * N * S * 4.f / 5e6f;   // (written: in the form's own time)
       if (time < least) { least = time; best = {c.code, S}; }
     }
   }

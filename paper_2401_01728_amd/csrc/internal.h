@@ -85,7 +85,7 @@ struct rv_gemm_args {
   //   1  the other streams of a stage step, and the launch is on the step's critical chain:
   //      the 256x256 tile as soon as it covers half the chip
   //   2  the same, off the critical chain: the 256x256 tile (least CU time per flop)
-  // in every case a split form instead where it takes a quarter off the launch's time alone
+  // in every case a split form instead where the rule for the shape takes one (whole_form)
   int sharing = 0;
   // weight-gradient products of the grouped launch only: the delayed update of Eq. 2 applied in
   // the epilogue.  upd_w = fp32 master tile base (same [M, ldo] layout as out), upd_ver = bf16
