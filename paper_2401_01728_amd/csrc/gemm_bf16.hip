@@ -1375,7 +1375,8 @@ rv_status launch_grouped_split(const rv_gemm_args* gs, int count, hipStream_t st
 }
 }  // namespace
 
-rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t st, bool in_order) {
+rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t st, rv_wgrad_form form) {
+  const bool in_order = form == RV_WGRAD_IN_ORDER;
   if (!gs || count < 1 || count > (in_order ? RV_GEMM_GROUP_BLOCK : RV_GEMM_GROUP_MAX)) return RV_E_INVAL;
   if (count > RV_GEMM_GROUP_BLOCK && gs[0].K >= RV_WGRAD_SPLIT_K) return RV_E_INVAL;
   for (int k = 0; k < count; ++k) {
@@ -1405,7 +1406,15 @@ rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t s
     int tiles = 0;
     for (int k = 0; k < count; ++k) tiles += ((gs[k].M + 255) / 256) * ((gs[k].N + 255) / 256);
     if (count > RV_GEMM_GROUP_BLOCK) return launch_grouped_split<128, 128, 2, 4, 4, RV_GEMM_GROUP_MAX>(gs, count, st);
-    if (tiles < 256 && gs[0].K < RV_WGRAD_SPLIT_K) return launch_grouped_split<128, 128, 2, 4, 4, RV_GEMM_GROUP_BLOCK>(gs, count, st);
+    // On more tokens the split form where the model of the forms has it a quarter faster: that is a narrow block, whose 256x256 tiles
+    // are a tenth of the chip.  Stage steps, in order / split, us: d 128, 4032 tokens 726 / 539; d 320, 6272 tokens 2266 /
+    // 2000; d 256, 2688 tokens 1226 / 1164; d 448, 4160 tokens, four microbatches in separate calls 4340 / 3915; the one
+    // seen to lose, d 384 on 3584 tokens in separate calls, 2443 / 2500.
+    int small = 0;
+    for (int k = 0; k < count; ++k) small += ((gs[k].M + 127) / 128) * ((gs[k].N + 127) / 128);
+    const int K = gs[0].K;
+    const float whole = ceilf(tiles / 256.f) * (8.9f + K / 32 * 0.55f), split = ceilf(small / 256.f) * (4.3f + K / 64 * 0.48f);
+    if (tiles < 256 && (K < RV_WGRAD_SPLIT_K || (form == RV_WGRAD_STAGE && split < 0.75f * whole))) return launch_grouped_split<128, 128, 2, 4, 4, RV_GEMM_GROUP_BLOCK>(gs, count, st);
   }
   return launch_grouped_dtl<256, 256, 32, 4, 8>(gs, count, st);
 }
@@ -1440,7 +1449,7 @@ extern "C" rv_status rv_k_gemm_wgrad_grouped(int count, const void* const* X, co
     g[k].B = (const uint16_t*)dY[k]; g[k].ldb = ldb[k]; g[k].b_kmajor = 1;
     g[k].M = M[k]; g[k].N = N[k]; g[k].K = K; g[k].epi = EPI_F32; g[k].out = dW[k]; g[k].ldo = N[k];
   }
-  return rv_gemm_wgrad_grouped(g, count, (hipStream_t)stream, true);
+  return rv_gemm_wgrad_grouped(g, count, (hipStream_t)stream, RV_WGRAD_IN_ORDER);
 }
 
 extern "C" rv_status rv_k_gemm_wgrad_update(int count, const void* const* X, const int64_t* lda, const void* const* dY,
@@ -1456,5 +1465,5 @@ extern "C" rv_status rv_k_gemm_wgrad_update(int count, const void* const* X, con
     g[k].store_out = dW != nullptr;
     if (w) { g[k].upd_w = w[k]; g[k].upd_ver = (uint16_t*)ver[k]; g[k].upd_eta = eta; }
   }
-  return rv_gemm_wgrad_grouped(g, count, (hipStream_t)stream);
+  return rv_gemm_wgrad_grouped(g, count, (hipStream_t)stream, RV_WGRAD_BY_TOKENS);
 }

@@ -112,9 +112,10 @@ rv_part_form rv_gemm_part_form(int M, int N, int K);
 #define RV_GEMM_GROUP_MAX 16
 #define RV_WGRAD_SPLIT_K 2048
 rv_status rv_stage_update_range(rv_stage* s, size_t off, size_t n, hipStream_t st);
-// in_order: every product summed in order of k, as rv_gemm_bf16 with tile 5256 does; otherwise small
-// blocks take tiles whose contraction is split
-rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t st, bool in_order = false);
+// RV_WGRAD_IN_ORDER: every product summed in order of k, as rv_gemm_bf16 with tile 5256 does; BY_TOKENS: small blocks on fewer than
+// RV_WGRAD_SPLIT_K tokens take tiles whose contraction is split; STAGE: narrow ones on more tokens as well
+enum rv_wgrad_form { RV_WGRAD_IN_ORDER, RV_WGRAD_BY_TOKENS, RV_WGRAD_STAGE };
+rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t st, rv_wgrad_form form = RV_WGRAD_STAGE);
 
 // ---- norm.hip ---------------------------------------------------------------------
 rv_status rv_ln_fwd(const void* x, int x_is_bf16, float* xcopy, const uint16_t* gamma, const uint16_t* beta,
