@@ -54,32 +54,40 @@ __device__ __forceinline__ float next_velocity(const Upd& u, float w, float v, f
 // store between two loads keeps the second one waiting for a round trip of its own); ok[k] = false: no
 // such parameter (o[k] is a valid offset all the same).
 template <int N>
-__device__ __forceinline__ void apply(const Upd& u, const size_t (&o)[N], const float (&g)[N], const bool (&ok)[N]) {
+struct Apply {
   float w[N], v[N];
-  if (u.w) {
+  __device__ __forceinline__ void request(const Upd& u, const size_t (&o)[N]) {
+    if (u.w) {
 #pragma unroll
-    for (int k = 0; k < N; ++k) w[k] = u.w[o[k]];
-    if (u.vel) {
+      for (int k = 0; k < N; ++k) w[k] = u.w[o[k]];
+      if (u.vel) {
 #pragma unroll
-      for (int k = 0; k < N; ++k) v[k] = u.vel[o[k]];
-#pragma unroll
-      for (int k = 0; k < N; ++k) {
-        v[k] = next_velocity(u, w[k], v[k], g[k]);
-        w[k] = __fmaf_rn(-u.eta, v[k], w[k]);
-        if (ok[k]) u.vel[o[k]] = v[k];
+        for (int k = 0; k < N; ++k) v[k] = u.vel[o[k]];
       }
-    } else {
+    }
+  }
+  __device__ __forceinline__ void complete(const Upd& u, const size_t (&o)[N], const float (&g)[N], const bool (&ok)[N]) {
+    if (u.w) {
+      if (u.vel) {
 #pragma unroll
-      for (int k = 0; k < N; ++k) w[k] = __fmaf_rn(-u.eta, g[k], w[k]);
+        for (int k = 0; k < N; ++k) {
+          v[k] = next_velocity(u, w[k], v[k], g[k]);
+          w[k] = __fmaf_rn(-u.eta, v[k], w[k]);
+          if (ok[k]) u.vel[o[k]] = v[k];
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < N; ++k) w[k] = __fmaf_rn(-u.eta, g[k], w[k]);
+      }
+#pragma unroll
+      for (int k = 0; k < N; ++k)
+        if (ok[k]) { u.w[o[k]] = w[k]; u.ver[o[k]] = w[k]; }
     }
 #pragma unroll
     for (int k = 0; k < N; ++k)
-      if (ok[k]) { u.w[o[k]] = w[k]; u.ver[o[k]] = w[k]; }
+      if (ok[k]) u.grad[o[k]] = g[k];
   }
-#pragma unroll
-  for (int k = 0; k < N; ++k)
-    if (ok[k]) u.grad[o[k]] = g[k];
-}
+};
 
 // One product C[M,N] = sum_k A(m,k) B(k,n).  An operand is k-contiguous (A[m*lda + k],
 // B[n*ldb + k]) or k-major (A[k*lda + m], B[k*ldb + n]).
@@ -95,31 +103,42 @@ struct Out {
   int relu;            // FWD
   Upd u; size_t off;   // DW: parameter offset of the tile's matrix
 };
-// R results of a lane, rows m[] of column n
+// R results of a lane, rows m[] of column n: what they read is requested, then they are completed
 template <int OP, int R>
-__device__ __forceinline__ void finish(const Out& o, const int (&m)[R], int n, int M, int N, const float (&v)[R]) {
-  const int nc = n < N ? n : N - 1;
+struct Finish {
   size_t i[R];
   bool ok[R];
+  float b, gate[R];
+  Apply<R> a;
+  __device__ __forceinline__ void request(const Out& o, const int (&m)[R], int n, int M, int N) {
+    const int nc = n < N ? n : N - 1;
 #pragma unroll
-  for (int r = 0; r < R; ++r) { ok[r] = m[r] < M && n < N; i[r] = (size_t)(m[r] < M ? m[r] : M - 1) * N + nc; }
-  if (OP == FWD) {
-    const float b = o.bias[nc];
+    for (int r = 0; r < R; ++r) {
+      ok[r] = m[r] < M && n < N;
+      i[r] = (size_t)(m[r] < M ? m[r] : M - 1) * N + nc;
+      if (OP == DW) i[r] += o.off;
+    }
+    if (OP == FWD) b = o.bias[nc];
+    if (OP == DX) {
 #pragma unroll
-    for (int r = 0; r < R; ++r)
-      if (ok[r]) o.C[i[r]] = o.relu ? fmaxf(v[r] + b, 0.f) : v[r] + b;
-  } else if (OP == DX) {
-    float g[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) g[r] = o.gate ? o.gate[i[r]] : 1.f;
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-      if (ok[r]) o.C[i[r]] = g[r] > 0.f ? v[r] : 0.f;
-  } else {
-#pragma unroll
-    for (int r = 0; r < R; ++r) i[r] += o.off;
-    apply<R>(o.u, i, v, ok);
+      for (int r = 0; r < R; ++r) gate[r] = o.gate ? o.gate[i[r]] : 1.f;
+    }
+    if (OP == DW) a.request(o.u, i);
   }
+  __device__ __forceinline__ void complete(const Out& o, const float (&v)[R]) {
+    if (OP == DW) { a.complete(o.u, i, v, ok); return; }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const float x = OP == DX ? (gate[r] > 0.f ? v[r] : 0.f) : o.relu ? fmaxf(v[r] + b, 0.f) : v[r] + b;
+      if (ok[r]) o.C[i[r]] = x;
+    }
+  }
+};
+template <int OP, int R>
+__device__ __forceinline__ void finish(const Out& o, const int (&m)[R], int n, int M, int N, const float (&v)[R]) {
+  Finish<OP, R> f;
+  f.request(o, m, n, M, N);
+  f.complete(o, v);
 }
 
 // ---- tiled ---------------------------------------------------------------------------------
@@ -144,7 +163,7 @@ __device__ __forceinline__ void tile_load(f32x4* v, const float* __restrict__ g,
   const float* base = KM ? g + (int64_t)k0 * ld + r0 : g + (int64_t)r0 * ld + k0;
 #pragma unroll
   for (int i = 0; i < Lds<KM, ROWS>::PIECES; ++i) {
-    const int p = threadIdx.x + 256 * i;
+    const int p = threadIdx.x % 256 + 256 * i;
     const int k = KM ? p / (ROWS / 4) : p % (BK / 4) * 4, r = KM ? p % (ROWS / 4) * 4 : p / (BK / 4);
     if (INSIDE) {
       v[i] = *reinterpret_cast<const f32x4_u*>(base + (unsigned)(KM ? k * ld + r : r * ld + k));
@@ -162,7 +181,7 @@ template <bool KM, int ROWS>
 __device__ __forceinline__ void tile_park(const f32x4* v, float* s, int left) {   // left: K - k0
 #pragma unroll
   for (int i = 0; i < Lds<KM, ROWS>::PIECES; ++i) {
-    const int p = threadIdx.x + 256 * i;
+    const int p = threadIdx.x % 256 + 256 * i;
     const int row = KM ? p / (ROWS / 4) : p / (BK / 4), c = KM ? p % (ROWS / 4) : p % (BK / 4);
     f32x4 x = v[i];
     if (left < BK) {                                       // (uniform)
@@ -180,12 +199,17 @@ __device__ __forceinline__ f32x4 tile_frag(const float* s, int row0, int g) {
   return f32x4{s[k * P + row], s[(k + 1) * P + row], s[(k + 2) * P + row], s[(k + 3) * P + row]};
 }
 
+// A workgroup of 512 threads takes two tiles, side by side: both have the same number of steps and so of barriers; the last
+// one's second tile may be past the end (it walks along on the last tile and keeps nothing).
 template <int BT, bool AKM, bool BKM, int OP>
 __device__ __forceinline__ void tiled_body(const Prod& p, const Out& o, int tile, float* smem) {
   constexpr int W = BT / 2, T = W / 32;                    // four waves, 2 x 2, each W x W
   constexpr int AF = Lds<AKM, BT>::FLOATS, BUF = AF + Lds<BKM, BT>::FLOATS;
+  const int all = (p.M + BT - 1) / BT * p.tiles_n;
+  const bool live = tile < all;        // (uniform in 256 threads)
+  tile = live ? tile : all - 1;
   const int m0 = tile / p.tiles_n * BT, n0 = tile % p.tiles_n * BT;
-  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int wave = threadIdx.x % 256 >> 6, l = threadIdx.x & 63;
   const int wm = (wave & 1) * W, wn = (wave >> 1) * W;
   f32x16 acc[T][T];
 #pragma unroll
@@ -267,6 +291,7 @@ __device__ __forceinline__ void tiled_body(const Prod& p, const Out& o, int tile
   if (inside)
     for (; (t + 3) * BK <= p.K; ++t) step(t, Int<1>());
   for (; t < nk; ++t) step(t, Int<0>());
+  if (!live) return;
 #pragma unroll
   for (int i = 0; i < T; ++i)
 #pragma unroll
@@ -285,8 +310,8 @@ __device__ __forceinline__ void tiled_body(const Prod& p, const Out& o, int tile
 }
 
 // ---- split ---------------------------------------------------------------------------------
-// NW waves on one 32x32 tile; wave w takes the 8-deep groups w, w + NW, ... of the contraction, eight of
-// them requested at a time; the partial tiles are added in wave order.
+// NW waves on one 32x32 tile; wave w takes the 8-deep groups w, w + NW, ... of the contraction, up to eight of
+// them on the way; the partial tiles are added in wave order.
 constexpr int kSplitWaves = 8;
 template <bool KM>
 __device__ __forceinline__ f32x4 direct_frag(const float* __restrict__ g, int ld, int row, int k, int K, bool whole) {
@@ -310,43 +335,60 @@ __device__ __forceinline__ void split_body(const Prod& p, const Out& o, int tile
   const int m0 = tile / p.tiles_n * 32, n0 = tile % p.tiles_n * 32;
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, h = l >> 5;
   const int ra = m0 + (l & 31) < p.M ? m0 + (l & 31) : p.M - 1, rb = n0 + (l & 31) < p.N ? n0 + (l & 31) : p.N - 1;
-  f32x16 acc;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  constexpr int U = 8;                                     // groups requested before the first is used
+  constexpr int U = 4;                                     // two sets of so many groups are on the way
   const int ng = (p.K + 7) / 8, whole = p.K / 8;
-  for (int g0 = wave; g0 < ng; g0 += U * NW) {
-    f32x4 fa[U], fb[U];
+  f32x4 fa[2][U], fb[2][U];
+  auto request = [&](int set, int g0) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int g = g0 + u * NW;                  // wave-uniform
-      fa[u] = 0.f; fb[u] = 0.f;
+      fa[set][u] = 0.f; fb[set][u] = 0.f;
       if (g < ng) {
-        fa[u] = direct_frag<AKM>(p.A, p.lda, ra, 8 * g + 4 * h, p.K, g < whole);
-        fb[u] = direct_frag<BKM>(p.B, p.ldb, rb, 8 * g + 4 * h, p.K, g < whole);
+        fa[set][u] = direct_frag<AKM>(p.A, p.lda, ra, 8 * g + 4 * h, p.K, g < whole);
+        fb[set][u] = direct_frag<BKM>(p.B, p.ldb, rb, 8 * g + 4 * h, p.K, g < whole);
       }
     }
+  };
+  // what the results read comes with the first operands, and the next operands while the present ones are multiplied:
+  // behind one another these were a memory round trip each (two sets of eight groups instead hold registers that a
+  // second workgroup of the CU would use: 442-461-220-2087-99 on 450 rows 272 -> 291 us)
+  constexpr int R = 32 * 32 / (64 * NW);
+  int m[R];
+  const int nl = threadIdx.x & 31;
+#pragma unroll
+  for (int i = 0; i < R; ++i) m[i] = m0 + (threadIdx.x >> 5) + 2 * NW * i;
+  Finish<OP, R> f;
+  request(0, wave);
+  if (wave + U * NW < ng) request(1, wave + U * NW);
+  f.request(o, m, n0 + nl, p.M, p.N);
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  auto products = [&](int set) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u][e], fb[u][e], acc, 0, 0, 0);
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[set][u][e], fb[set][u][e], acc, 0, 0, 0);
+  };
+  for (int g0 = wave; g0 < ng; g0 += 2 * U * NW) {
+    products(0);
+    if (g0 + 2 * U * NW < ng) request(0, g0 + 2 * U * NW);
+    if (g0 + U * NW >= ng) break;
+    products(1);
+    if (g0 + 3 * U * NW < ng) request(1, g0 + 3 * U * NW);
   }
 #pragma unroll
   for (int r = 0; r < 16; ++r) smem[(wave * 32 + 8 * (r >> 2) + 4 * h + (r & 3)) * 33 + (l & 31)] = acc[r];
   __syncthreads();
-  constexpr int R = 32 * 32 / (64 * NW);
-  int m[R];
   float v[R];
-  const int nl = threadIdx.x & 31;
 #pragma unroll
   for (int i = 0; i < R; ++i) {
-    const int ml = (threadIdx.x >> 5) + 2 * NW * i;
+    const int ml = m[i] - m0;
     v[i] = smem[ml * 33 + nl];
 #pragma unroll
     for (int w = 1; w < NW; ++w) v[i] += smem[(w * 32 + ml) * 33 + nl];
-    m[i] = m0 + ml;
   }
-  finish<OP, R>(o, m, n0 + nl, p.M, p.N, v);
+  f.complete(o, v);
 }
 
 // ---- one wave per tile ---------------------------------------------------------------------
@@ -419,7 +461,9 @@ __device__ __forceinline__ void bias_body(const float* __restrict__ D, int M, in
     const size_t i[1] = {off + c};
     const float g[1] = {t};
     const bool ok[1] = {true};
-    apply<1>(u, i, g, ok);
+    Apply<1> a;
+    a.request(u, i);
+    a.complete(u, i, g, ok);
   }
 }
 
@@ -427,7 +471,8 @@ __device__ __forceinline__ void bias_body(const float* __restrict__ D, int M, in
 constexpr int kWave = 1;
 template <int BT, int NT, bool AKM, bool BKM> constexpr int mlp_lds_bytes() {
   // (kWave: the bias sums beside it)
-  return 4 * (BT == kWave ? NT / 32 * 33 : BT == 32 ? NT / 64 * 32 * 33 : 2 * (Lds<AKM, BT>::FLOATS + Lds<BKM, BT>::FLOATS));
+  return 4 * (BT == kWave ? NT / 32 * 33 : BT == 32 ? NT / 64 * 32 * 33
+              : NT / 256 * 2 * (Lds<AKM, BT>::FLOATS + Lds<BKM, BT>::FLOATS));
 }
 template <int BT, int NT, bool AKM, bool BKM, int OP>
 __device__ __forceinline__ void mlp_body(const Prod& p, const Out& o, int tile, float* smem) {
@@ -436,8 +481,9 @@ __device__ __forceinline__ void mlp_body(const Prod& p, const Out& o, int tile, 
   } else if constexpr (BT == 32) {
     split_body<NT / 64, AKM, BKM, OP>(p, o, tile, smem);
   } else {
-    static_assert(NT == 256, "four waves");
-    tiled_body<BT, AKM, BKM, OP>(p, o, tile, smem);
+    static_assert(NT == 256 || NT == 512, "four waves a tile");
+    const int part = NT == 256 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / 256);
+    tiled_body<BT, AKM, BKM, OP>(p, o, tile * (NT / 256) + part, smem + part * (mlp_lds_bytes<BT, 256, AKM, BKM>() / 4));
   }
 }
 extern __shared__ __align__(16) float mlp_smem[];
@@ -478,7 +524,8 @@ __global__ __launch_bounds__(NT) void mlp_bwd_kernel(Prod dx, Out ox, Prod dw, O
 
 Prod product(const float* A, int lda, const float* B, int ldb, int M, int N, int K, int bt, int nt) {
   const int edge = bt == kWave ? 32 : bt, tn = (N + edge - 1) / edge, tiles = (M + edge - 1) / edge * tn, waves = nt / 64;
-  return Prod{A, B, lda, ldb, M, N, K, tn, bt == kWave ? (tiles + waves - 1) / waves : tiles};   // (tiles: workgroups)
+  const int per = bt == kWave ? waves : bt > 32 ? nt / 256 : 1;   // tiles a workgroup
+  return Prod{A, B, lda, ldb, M, N, K, tn, (tiles + per - 1) / per};   // (tiles: workgroups)
 }
 int tile_count(int M, int N, int bt) { return (M + bt - 1) / bt * ((N + bt - 1) / bt); }
 constexpr int kCUs = 256;
@@ -487,7 +534,7 @@ constexpr int kCUs = 256;
 // + backward + update of 1024-4096-4096-1024 on 1024 rows 11.0 -> 1.43 ms against plain 16x16 vector
 // tiles with separate bias and update launches (108 of 157 TFLOP/s; 4096^3 alone 128 / 140 / 133
 // TFLOP/s forward / input / weight gradient), 300-1000-1000-77 on 100 rows with momentum
-// 304 -> 74 us, where 64x64 tiles for the 100-row products would take 120.
+// 304 -> 68 us, where 64x64 tiles for the 100-row products would take 120.
 // A result of at most 32 rows or columns fills at best half of such a tile's matrix instructions, so there the tile
 // count says nothing about the chip: it takes 32x32 tiles, one per wave where the contraction is short (the work is the
 // results' memory traffic), split where it is long.  Times in us against the tiles that the count alone would take:
@@ -935,7 +982,9 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
     const float* a = stash + p->offA[i];
     const bool want_dx = i > 0 || grad_in;
     float* dst = i == 0 ? (float*)grad_in : (d == ping ? pong : ping);
-    const int bx = pick(mb, K, N), bw = pick(K, N, mb), nt = std::max(bx, bw) == 32 ? threads(32) : 256;
+    // 64x64 weight-gradient tiles beside an input gradient whose walk is dealt out over eight waves: two to a workgroup
+    const int bx = pick(mb, K, N), bw = pick(K, N, mb);
+    const int nt = std::max(bx, bw) == 32 || (bx == 32 && bw == 64) ? threads(32) : 256;
     Prod px = product(d, N, w + p->offW[i], N, mb, K, N, bx, nt);
     const Prod pw = product(a, K, d, N, K, N, mb, bw, nt);
     if (!want_dx) px.tiles = 0;
@@ -943,13 +992,12 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
     ox.C = dst; ox.gate = i > 0 ? a : nullptr;
     ow.u = u; ow.off = p->offW[i];
     auto go = [&](auto launch) { return launch(s->st, px, ox, pw, ow, d, mb, N, p->offB[i]); };
-    // Beside LDS tiles, which are made for four waves, a split form has four instead of eight, also where the input
+    // Beside 128x128 tiles, which are made for four waves, a split form has four instead of eight, also where the input
     // gradient's walk is the longer one: 32x32 weight-gradient tiles with eight waves for both took (one layer, backward, us)
-    // 25 instead of 17.6 at 1000 -> 1000 on 100 rows, 49 / 23 at 4096 -> 1024 on 8, 188 / 87 at 4096 -> 4096 on 16,
-    // 273 / 98 on 64, 24 / 24 at 2048 -> 512 on 200.
+    // 49 instead of 23 at 4096 -> 1024 on 8 rows, 188 / 87 at 4096 -> 4096 on 16, 273 / 98 on 64.
     auto by_bw = [&](auto x) {
       constexpr int BX = decltype(x)::value, NT = BX <= 32 ? 64 * kSplitWaves : 256;
-      return bw == 128 ? go(launch_bwd<BX, 128, 256>) : bw == 64 ? go(launch_bwd<BX, 64, 256>)
+      return bw == 128 ? go(launch_bwd<BX, 128, 256>) : bw == 64 ? go(launch_bwd<BX, 64, BX == 32 ? NT : 256>)
              : bw == 32 ? go(launch_bwd<BX, 32, NT>) : go(launch_bwd<BX, kWave, BX == 32 ? NT : 256>);
     };
     const rv_status rc = bx == 128 ? by_bw(Int<128>()) : bx == 64 ? by_bw(Int<64>()) : bx == 32 ? by_bw(Int<32>()) : by_bw(Int<kWave>());

@@ -329,3 +329,11 @@ def test_more_version_slots_than_one_launch_clears():
             dy = gen.normal_f32(65, 500 + t, mb * dims[-1], std=0.1).reshape(mb, dims[-1])
             close(host64(g.backward(t - tau, dev(dy))), o.backward(t - tau, dy), 1e-5, "t", group="MLP stage, bar 1e-5")
     close(host64(g.get_params()), o.w, 1e-6, "t", group="MLP stage, bar 1e-6")
+
+
+# 64x64 weight-gradient tiles two to a workgroup: an odd number of them, ragged or whole, contractions of one and two tile depths
+@pytest.mark.parametrize("dims,mb,momentum", [([700, 830], 40, 0.9), ([704, 832], 32, 0.0), ([704, 832], 64, 0.9)] +
+                         # the split walk: one set of requests exactly, a second one begun, full, a third and a fourth begun
+                         [([K, 40], 9, 0.0) for K in (256, 264, 512, 513, 769, 1030)])
+def test_two_tiles_a_workgroup_and_the_split_walk(dims, mb, momentum):
+    test_product_forms_at_their_edges(dims, mb, momentum)
