@@ -104,12 +104,12 @@ rv_status rv_dec_plan(rv_stage* s) {
   p->dy_sets = p->deep ? p->L : 3;
   p->group = 1;
   if (p->deep && p->T < RV_WGRAD_SPLIT_K) {
-    // as many blocks as give the split weight-gradient launch a tile for every CU (a launch is a few microseconds, and the
-    // event pair in front of it 11 of host time, however small it is)
+    // A block whose products do not give every CU a tile leaves with three others: a launch is a few microseconds, and the
+    // event pair in front of it 11 of host time, however small it is.  Stage step of 12 blocks of d 448 (172 tiles) on
+    // 256 tokens, two / three / four blocks at a time, 815 / 785 / 745 us.  Blocks that fill the chip lose by waiting for each other:
+    // d 896 (448 tiles), 256 tokens, one / three at a time 400 / 407, d 832 in separate calls 1398 / 1422.
     auto tiles = [](int64_t M, int64_t N) { return ((M + 127) / 128) * ((N + 127) / 128); };
-    const int64_t n = 2 * tiles(d, f) + tiles(d, d) + tiles(d, 3 * d);
-    p->group = (int)((256 + n - 1) / n);
-    if (p->group > kGroupBlocks) p->group = kGroupBlocks;
+    if (2 * tiles(d, f) + tiles(d, d) + tiles(d, 3 * d) < 256) p->group = kGroupBlocks;
   }
   size_t w = 0;
   p->w_dres = w; w += align_up(T * d * 4);
