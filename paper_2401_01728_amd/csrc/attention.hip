@@ -39,6 +39,7 @@ constexpr int kThreads = 256;
 constexpr int TILE = 64;    // streamed rows per LDS tile
 constexpr int WROWS = 32;   // rows a wave owns
 constexpr int BROWS = 128;  // rows a workgroup owns
+constexpr int kTwoGroups = 6 * TILE;   // sequences from here on may take two groups of waves
 
 template <int DH> struct L {
   static constexpr int PKC = DH * 2 + 16;          // k-contiguous pitch (bytes)
@@ -53,7 +54,7 @@ template <int DH>
 __device__ __forceinline__ void g2r(u32x4* v, const uint16_t* __restrict__ g, int64_t ld, int64_t bs = 32) {
 #pragma unroll
   for (int i = 0; i < L<DH>::CHUNKS; ++i) {
-    const int idx = threadIdx.x + kThreads * i;
+    const int idx = threadIdx.x % kThreads + kThreads * i;
     const int row = idx / (DH / 8), c = idx % (DH / 8);
     v[i] = *reinterpret_cast<const u32x4*>(g + (int64_t)row * ld + (c >> 2) * bs + (c & 3) * 8);
   }
@@ -62,7 +63,7 @@ template <int DH, int PITCH>
 __device__ __forceinline__ void r2s(const u32x4* v, char* lds) {
 #pragma unroll
   for (int i = 0; i < L<DH>::CHUNKS; ++i) {
-    const int idx = threadIdx.x + kThreads * i;
+    const int idx = threadIdx.x % kThreads + kThreads * i;
     const int row = idx / (DH / 8), c = idx % (DH / 8);
     *reinterpret_cast<u32x4*>(lds + row * PITCH + c * 16) = v[i];
   }
@@ -163,6 +164,27 @@ __device__ __forceinline__ void colsum_owned(const f32x16* acc, float mul, float
     }
 }
 
+// Few row blocks: two groups of four waves to a workgroup (G = 2), which take the streamed tiles in turn, each with tiles of its
+// own in LDS; the second group's sums go through LDS to the first (lane by lane, n registers each), which completes them.  With as
+// many workgroups as CUs or fewer there is one wave to a SIMD otherwise and the walk along the streamed side is a chain of
+// LDS reads, matrix products and exponentials, each waiting for the one before.
+template <int N>
+__device__ __forceinline__ void give_regs(const f32x16 (&v)[N], float* lds) {
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) lds[(i * 16 + r) * 64] = v[i][r];
+}
+template <int N>
+__device__ __forceinline__ void add_regs(f32x16 (&v)[N], const float* lds, float mine, float theirs) {
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[i][r] = v[i][r] * mine + lds[(i * 16 + r) * 64] * theirs;
+}
+// LDS of the exchange: four waves of n registers
+constexpr int give_bytes(int n) { return 4 * n * 64 * 4; }
+
 // Workgroup -> (row block, head, sequence).  Causal work per row block is a ramp, and
 // consecutive workgroup ids go to the 8 XCDs in turn: the block index must be the SLOWEST
 // digit of the id, or whole XCDs get only long (or only short) blocks and the kernel lasts as
@@ -178,17 +200,19 @@ __device__ __forceinline__ void attn_block(int block, int H, int nseq, int& rank
 // ----------------------------------------------------------------------------------------
 // forward
 // ----------------------------------------------------------------------------------------
-template <int DH>
-__global__ __launch_bounds__(kThreads) void attn_fwd_kernel(const uint16_t* __restrict__ qkv, int64_t ld,
-                                                            rv_mat out, float* __restrict__ lse2, int S, int d, int H,
-                                                            int nseq, float c2) {
-  extern __shared__ __align__(16) char smem[];
+template <int DH, int G>
+__global__ __launch_bounds__(kThreads * G) void attn_fwd_kernel(const uint16_t* __restrict__ qkv, int64_t ld,
+                                                                rv_mat out, float* __restrict__ lse2, int S, int d, int H,
+                                                                int nseq, float c2) {
+  extern __shared__ __align__(16) char all_smem[];
   constexpr int BUF = L<DH>::KC_BYTES + L<DH>::KM_BYTES;   // K tile (k-contiguous) + V tile (transpose-read)
+  const int group = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads);
+  char* smem = all_smem + group * 2 * BUF;
   const int nblk = (S + BROWS - 1) / BROWS;
   int rank, h, b;
   attn_block(blockIdx.x, H, nseq, rank, h, b);
   const int qb = nblk - 1 - rank;                          // long rows first
-  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, grp = l >> 5;
+  const int wave = threadIdx.x / 64 % 4, l = threadIdx.x & 63, grp = l >> 5;
   const int q0 = qb * BROWS + wave * WROWS;
   const bool active = q0 < S;
   const int64_t tok0 = (int64_t)b * S;
@@ -205,18 +229,21 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_kernel(const uint16_t* __re
 
   const int nkt = min(S, (qb + 1) * BROWS) / TILE;
   u32x4 kr[L<DH>::CHUNKS], vr[L<DH>::CHUNKS];
-  g2r<DH>(kr, Kg, ld); g2r<DH>(vr, Vg, ld);
-  r2s<DH, L<DH>::PKC>(kr, smem); r2s<DH, L<DH>::PKM>(vr, smem + L<DH>::KC_BYTES);
+  if (group < nkt) {
+    g2r<DH>(kr, Kg + (int64_t)group * TILE * ld, ld); g2r<DH>(vr, Vg + (int64_t)group * TILE * ld, ld);
+    r2s<DH, L<DH>::PKC>(kr, smem); r2s<DH, L<DH>::PKM>(vr, smem + L<DH>::KC_BYTES);
+  }
   __syncthreads();
-  for (int kt = 0; kt < nkt; ++kt) {
-    const char* Ks = smem + (kt & 1) * BUF;
+  for (int turn = 0; turn * G < nkt; ++turn) {
+    const int kt = turn * G + group;                       // this group's tile
+    const char* Ks = smem + (turn & 1) * BUF;
     const char* Vs = Ks + L<DH>::KC_BYTES;
-    if (kt + 1 < nkt) {
-      g2r<DH>(kr, Kg + (int64_t)(kt + 1) * TILE * ld, ld);
-      g2r<DH>(vr, Vg + (int64_t)(kt + 1) * TILE * ld, ld);
+    if (kt + G < nkt) {
+      g2r<DH>(kr, Kg + (int64_t)(kt + G) * TILE * ld, ld);
+      g2r<DH>(vr, Vg + (int64_t)(kt + G) * TILE * ld, ld);
     }
     const int k0 = kt * TILE;
-    if (active && k0 <= q0 + WROWS - 1) {
+    if (active && kt < nkt && k0 <= q0 + WROWS - 1) {
       f32x16 s[2] = {zero16(), zero16()};
 #pragma unroll
       for (int kk = 0; kk < DH / 16; ++kk)
@@ -274,11 +301,26 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_kernel(const uint16_t* __re
                                                             o[dt], 0, 0, 0);
         }
     }
-    if (kt + 1 < nkt) {
-      char* nb = smem + ((kt + 1) & 1) * BUF;
+    if (kt + G < nkt) {
+      char* nb = smem + ((turn + 1) & 1) * BUF;
       r2s<DH, L<DH>::PKC>(kr, nb); r2s<DH, L<DH>::PKM>(vr, nb + L<DH>::KC_BYTES);
     }
     __syncthreads();
+  }
+  if constexpr (G > 1) {   // (the last barrier of the walk has freed the tiles)
+    float* x = reinterpret_cast<float*>(all_smem) + wave * (DH / 2 + 2) * 64 + l;
+    if (group == 1) {
+      give_regs(o, x);
+      x[DH / 2 * 64] = m; x[(DH / 2 + 1) * 64] = lsum;
+    }
+    __syncthreads();
+    if (group == 1) return;
+    // the second group may have had no tile of these rows: its maximum is -inf then and counts as zero
+    const float m1 = x[DH / 2 * 64], mn = fmaxf(m, m1);
+    const float mine = __builtin_amdgcn_exp2f(m - mn), theirs = __builtin_amdgcn_exp2f(m1 - mn);
+    add_regs(o, x, mine, theirs);
+    lsum = lsum * mine + x[(DH / 2 + 1) * 64] * theirs;
+    m = mn;
   }
   if (!active) return;
   const float tot = lsum + __shfl_xor(lsum, 32, 64);
@@ -302,8 +344,12 @@ struct BwdArgs {
   float c2, scale;
   float* colpart;
 };
-template <int DH, bool OWN_D>
-__device__ __forceinline__ void bwd_kv_body(const BwdArgs& a, int block, char* smem) {
+template <int DH> constexpr int kv_bytes() { return 2 * (L<DH>::KC_BYTES + L<DH>::KM_BYTES) + 2 * TILE * 4; }   // of one group
+template <int DH> constexpr int q_bytes() { return 2 * L<DH>::KC_BYTES + L<DH>::KM_BYTES; }
+template <int DH, int G, bool OWN_D>
+__device__ __forceinline__ void bwd_kv_body(const BwdArgs& a, int block, char* all_smem) {
+  const int group = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tid = threadIdx.x % kThreads;
+  char* smem = all_smem + group * kv_bytes<DH>();
   const uint16_t* __restrict__ qkv = a.qkv;
   const uint16_t* __restrict__ dout = a.dout;
   const rv_mat dqkv = a.dqkv;
@@ -318,7 +364,7 @@ __device__ __forceinline__ void bwd_kv_body(const BwdArgs& a, int block, char* s
 
   int jb, h, b;                             // the first key block sees every query: heaviest
   attn_block(block, H, a.nseq, jb, h, b);
-  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, grp = l >> 5;
+  const int wave = tid >> 6, l = threadIdx.x & 63, grp = l >> 5;
   const int j0 = jb * BROWS + wave * WROWS;
   const bool active = j0 < S;
   const int64_t tok0 = (int64_t)b * S;
@@ -349,30 +395,30 @@ __device__ __forceinline__ void bwd_kv_body(const BwdArgs& a, int block, char* s
     g2r<DH>(rq, Qg + (int64_t)i0 * ld, ld);
     g2r<DH>(ro, Og + (int64_t)i0 * ldo, ldo);
     if (OWN_D) g2r<DH>(rp, Pg + (int64_t)i0 * a.out.ld, a.out.ld, a.out.bs);
-    if (threadIdx.x < TILE) rstat = lse_g[i0 + threadIdx.x];
-    else if (!OWN_D && threadIdx.x < 2 * TILE) rstat = D_g[i0 + threadIdx.x - TILE];
+    if (tid < TILE) rstat = lse_g[i0 + tid];
+    else if (!OWN_D && tid < 2 * TILE) rstat = D_g[i0 + tid - TILE];
   };
   auto park = [&]() {
     r2s<DH, L<DH>::PKC>(rq, Qkc); r2s<DH, L<DH>::PKM>(rq, Qkm);
     r2s<DH, L<DH>::PKC>(ro, Okc); r2s<DH, L<DH>::PKM>(ro, Okm);
-    if (threadIdx.x < (OWN_D ? TILE : 2 * TILE)) stat[threadIdx.x] = rstat;
+    if (tid < (OWN_D ? TILE : 2 * TILE)) stat[tid] = rstat;
     if (OWN_D) {   // a row's DH / 8 chunks lie in neighbouring lanes
 #pragma unroll
       for (int i = 0; i < L<DH>::CHUNKS; ++i) {
         float t = dot8(rp[i], ro[i], 0.f);
 #pragma unroll
         for (int x = 1; x < DH / 8; x *= 2) t += __shfl_xor(t, x, 64);
-        const int idx = threadIdx.x + kThreads * i;
+        const int idx = tid + kThreads * i;
         if (idx % (DH / 8) == 0) stat[TILE + idx / (DH / 8)] = t;
       }
     }
   };
-  if (it0 < nit) { fetch(it0); park(); }
+  if (it0 + group < nit) { fetch(it0 + group); park(); }
   __syncthreads();
-  for (int it = it0; it < nit; ++it) {
-    const int i0 = it * TILE;
-    if (it + 1 < nit) fetch(it + 1);
-    if (active) {
+  for (int first = it0; first < nit; first += G) {
+    const int it = first + group, i0 = it * TILE;          // this group's tile
+    if (it + G < nit) fetch(it + G);
+    if (active && it < nit) {
 #pragma unroll
       for (int sub = 0; sub < 2; ++sub) {
         const int is = i0 + sub * 32;
@@ -416,8 +462,15 @@ __device__ __forceinline__ void bwd_kv_body(const BwdArgs& a, int block, char* s
       }
     }
     __syncthreads();           // everyone is done reading this tile
-    if (it + 1 < nit) park();
+    if (it + G < nit) park();
     __syncthreads();
+  }
+  if constexpr (G > 1) {
+    float* x = reinterpret_cast<float*>(all_smem) + wave * DH * 64 + l;
+    if (group == 1) { give_regs(dk, x); give_regs(dv, x + DH / 2 * 64); }
+    __syncthreads();
+    if (group == 1) return;
+    add_regs(dk, x, 1.f, 1.f); add_regs(dv, x + DH / 2 * 64, 1.f, 1.f);
   }
   if (!active) return;
   store_owned<DH>(dk, scale, dqkv.p + rv_at(dqkv, tok0 + j0, d + h * DH), dqkv.ld, dqkv.bs);
@@ -433,8 +486,10 @@ __device__ __forceinline__ void bwd_kv_body(const BwdArgs& a, int block, char* s
 // backward, part 1: dQ, and D = rowsum(dO * O), stored where part 2 follows in a launch of its own.
 // A wave owns 32 queries (lane = query); keys stream.
 // ----------------------------------------------------------------------------------------
-template <int DH, bool STORE_D>
-__device__ __forceinline__ void bwd_q_body(const BwdArgs& a, int block, char* smem) {
+template <int DH, int G, bool STORE_D>
+__device__ __forceinline__ void bwd_q_body(const BwdArgs& a, int block, char* all_smem) {
+  const int group = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads);
+  char* smem = all_smem + group * q_bytes<DH>();
   const uint16_t* __restrict__ qkv = a.qkv;
   const uint16_t* __restrict__ dout = a.dout;
   const rv_mat dqkv = a.dqkv;
@@ -449,7 +504,7 @@ __device__ __forceinline__ void bwd_q_body(const BwdArgs& a, int block, char* sm
   int rank, h, b;
   attn_block(block, H, a.nseq, rank, h, b);
   const int qb = nblk - 1 - rank;
-  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, grp = l >> 5;
+  const int wave = threadIdx.x / 64 % 4, l = threadIdx.x & 63, grp = l >> 5;
   const int q0 = qb * BROWS + wave * WROWS;
   const bool active = q0 < S;
   const int64_t tok0 = (int64_t)b * S;
@@ -486,12 +541,12 @@ __device__ __forceinline__ void bwd_q_body(const BwdArgs& a, int block, char* sm
     r2s<DH, L<DH>::PKC>(rk, Kkc); r2s<DH, L<DH>::PKM>(rk, Kkm);
     r2s<DH, L<DH>::PKC>(rv, Vkc);
   };
-  fetch(0); park();
+  if (group < nkt) { fetch(group); park(); }
   __syncthreads();
-  for (int kt = 0; kt < nkt; ++kt) {
-    const int k0 = kt * TILE;
-    if (kt + 1 < nkt) fetch(kt + 1);
-    if (active && k0 <= q0 + WROWS - 1) {
+  for (int first = 0; first < nkt; first += G) {
+    const int kt = first + group, k0 = kt * TILE;          // this group's tile
+    if (kt + G < nkt) fetch(kt + G);
+    if (active && kt < nkt && k0 <= q0 + WROWS - 1) {
 #pragma unroll
       for (int sub = 0; sub < 2; ++sub) {
         const int ks0 = k0 + sub * 32;
@@ -526,8 +581,15 @@ __device__ __forceinline__ void bwd_q_body(const BwdArgs& a, int block, char* sm
       }
     }
     __syncthreads();           // everyone is done reading this tile
-    if (kt + 1 < nkt) park();
+    if (kt + G < nkt) park();
     __syncthreads();
+  }
+  if constexpr (G > 1) {
+    float* x = reinterpret_cast<float*>(all_smem) + wave * (DH / 2) * 64 + l;
+    if (group == 1) give_regs(dq, x);
+    __syncthreads();
+    if (group == 1) return;
+    add_regs(dq, x, 1.f, 1.f);
   }
   if (!active) return;
   store_owned<DH>(dq, scale, dqkv.p + rv_at(dqkv, tok0 + q0, h * DH), dqkv.ld, dqkv.bs);
@@ -537,20 +599,20 @@ __device__ __forceinline__ void bwd_q_body(const BwdArgs& a, int block, char* sm
 template <int DH>
 __global__ __launch_bounds__(kThreads) void attn_bwd_kv_kernel(BwdArgs a) {
   extern __shared__ __align__(16) char smem[];
-  bwd_kv_body<DH, false>(a, blockIdx.x, smem);
+  bwd_kv_body<DH, 1, false>(a, blockIdx.x, smem);
 }
 template <int DH>
 __global__ __launch_bounds__(kThreads) void attn_bwd_q_kernel(BwdArgs a) {
   extern __shared__ __align__(16) char smem[];
-  bwd_q_body<DH, true>(a, blockIdx.x, smem);
+  bwd_q_body<DH, 1, true>(a, blockIdx.x, smem);
 }
 // both parts: the row blocks of part 2 and part 1 in turn, heaviest first
-template <int DH>
-__global__ __launch_bounds__(kThreads) void attn_bwd_kernel(BwdArgs a) {
+template <int DH, int G>
+__global__ __launch_bounds__(kThreads * G) void attn_bwd_kernel(BwdArgs a) {
   extern __shared__ __align__(16) char smem[];
   const int per = a.H * a.nseq, slab = blockIdx.x / per, block = (slab >> 1) * per + blockIdx.x % per;
-  if (slab & 1) bwd_q_body<DH, false>(a, block, smem);
-  else bwd_kv_body<DH, true>(a, block, smem);
+  if (slab & 1) bwd_q_body<DH, G, false>(a, block, smem);
+  else bwd_kv_body<DH, G, true>(a, block, smem);
 }
 
 template <typename K>
@@ -573,19 +635,20 @@ rv_status rv_attn_fwd(const uint16_t* qkv, rv_mat out, float* lse2, int mb, int 
   const int dh = d / H;
   const float c2 = 1.4426950408889634f / sqrtf((float)dh);
   const int nwg = ((S + BROWS - 1) / BROWS) * H * mb;
-  dim3 grid(nwg);
-  if (dh == 64) {
-    constexpr int smem = 2 * (L<64>::KC_BYTES + L<64>::KM_BYTES);
-    RV_TRY(set_smem(attn_fwd_kernel<64>, smem));
-    hipLaunchKernelGGL(attn_fwd_kernel<64>, grid, dim3(kThreads), smem, st, qkv, (int64_t)3 * d, out,
-                       lse2, S, d, H, mb, c2);
-  } else {
-    constexpr int smem = 2 * (L<128>::KC_BYTES + L<128>::KM_BYTES);
-    RV_TRY(set_smem(attn_fwd_kernel<128>, smem));
-    hipLaunchKernelGGL(attn_fwd_kernel<128>, grid, dim3(kThreads), smem, st, qkv, (int64_t)3 * d, out,
-                       lse2, S, d, H, mb, c2);
-  }
-  return rv_launch_status();
+  auto launch = [&](auto kern, int groups, int one) -> rv_status {
+    const int smem = groups * one;
+    RV_TRY(set_smem(kern, smem));
+    hipLaunchKernelGGL(kern, dim3(nwg), dim3(kThreads * groups), smem, st, qkv, (int64_t)3 * d, out, lse2, S, d, H, mb, c2);
+    return rv_launch_status();
+  };
+  // Two groups where there are no more workgroups than CUs and the walk is six tiles or longer.  One / two, us: 12 heads of 64, 3
+  // sequences of 384 9.4 / 8.9; 4 heads, one of 640 12.8 / 11.0; 8, one of 1024 18.5 / 15.4, of size 128 26.8 / 23.4; 4, one of
+  // 2048 32.6 / 25.7.  On shorter sequences the stages measured within 1 % either way.
+  const bool two = nwg <= 256 && S >= kTwoGroups;
+  constexpr int b64 = 2 * (L<64>::KC_BYTES + L<64>::KM_BYTES), b128 = 2 * (L<128>::KC_BYTES + L<128>::KM_BYTES);
+  static_assert(2 * b64 >= give_bytes(34) && 2 * b128 >= give_bytes(66) && 2 * b128 <= 160 * 1024, "the exchange lies in the tiles");
+  if (dh == 64) return two ? launch(attn_fwd_kernel<64, 2>, 2, b64) : launch(attn_fwd_kernel<64, 1>, 1, b64);
+  return two ? launch(attn_fwd_kernel<128, 2>, 2, b128) : launch(attn_fwd_kernel<128, 1>, 1, b128);
 }
 
 int rv_attn_colsum_parts(int mb, int S) { return mb * (S / WROWS); }
@@ -605,12 +668,19 @@ namespace {
 bool one_launch(int dh, int nwg) { return nwg <= (dh == 64 ? 512 : 256); }
 template <int DH>
 rv_status launch_bwd(const BwdArgs& a, hipStream_t st) {
-  constexpr int s1 = 2 * (L<DH>::KC_BYTES + L<DH>::KM_BYTES) + 2 * TILE * 4;
-  constexpr int s2 = 2 * L<DH>::KC_BYTES + L<DH>::KM_BYTES;
+  constexpr int s1 = kv_bytes<DH>(), s2 = q_bytes<DH>();
   const int nwg = (a.S + BROWS - 1) / BROWS * a.H * a.nseq;
+  if constexpr (DH == 64) {   // (head size 128 has no registers for eight waves)
+    static_assert(2 * s1 >= give_bytes(DH), "the exchange lies in the tiles");
+    if (2 * nwg <= 256 && a.S >= kTwoGroups) {   // two groups, as in the forward: 17.4 / 15.4, 24.0 / 19.6, 35.6 / 27.8, 65.9 / 49.0 us
+      RV_TRY(set_smem(attn_bwd_kernel<DH, 2>, 2 * s1));
+      hipLaunchKernelGGL((attn_bwd_kernel<DH, 2>), dim3(2 * nwg), dim3(2 * kThreads), 2 * s1, st, a);
+      return rv_launch_status();
+    }
+  }
   if (one_launch(DH, nwg)) {
-    RV_TRY(set_smem(attn_bwd_kernel<DH>, s1));
-    hipLaunchKernelGGL(attn_bwd_kernel<DH>, dim3(2 * nwg), dim3(kThreads), s1, st, a);
+    RV_TRY(set_smem(attn_bwd_kernel<DH, 1>, s1));
+    hipLaunchKernelGGL((attn_bwd_kernel<DH, 1>), dim3(2 * nwg), dim3(kThreads), s1, st, a);
     return rv_launch_status();
   }
   RV_TRY(set_smem(attn_bwd_kv_kernel<DH>, s1)); RV_TRY(set_smem(attn_bwd_q_kernel<DH>, s2));

@@ -114,6 +114,20 @@ def test_attention_many_row_blocks(mb, S, H, dh):
     test_attention_forward_backward(mb, S, H, dh)
 
 
+# two groups of waves to a workgroup, sequences of 384 and more: odd numbers of tiles, a half-empty last row block, the most row
+# blocks the rules take (256 forward, 128 backward) and a few more
+@pytest.mark.parametrize("mb,S,H,dh", [(1, 384, 1, 64), (2, 448, 3, 64), (1, 576, 2, 128), (8, 512, 4, 64), (16, 512, 4, 64), (13, 576, 4, 64),
+                                        (8, 448, 8, 128)])
+def test_attention_of_few_row_blocks(mb, S, H, dh):
+    test_attention_forward_backward(mb, S, H, dh)
+
+
+# 2048 rows and more: two rows to a wave; one row less: a workgroup to each row
+@pytest.mark.parametrize("T,d", [(2051, 1024), (2049, 1792), (2047, 64)])
+def test_layernorm_around_two_rows_a_wave(T, d):
+    test_layernorm_forward_backward(T, d)
+
+
 def test_attention_rejects_unsupported_shapes():
     from paper_2401_01728_amd import kernels as k
     import paper_2401_01728_amd as rv
