@@ -622,6 +622,26 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
     }
     wait_tiles(pre - 1);
     __syncthreads();
+    // A wave whose part of a ragged tile lies past the end of the result only takes its share of the loads (a width of 1600 is
+    // six tiles and a quarter: of the last one's eight waves two have something to multiply).
+    if (__builtin_amdgcn_readfirstlane(m0 + wm0 >= M || n0 + wn0 >= N)) {
+      int slot = 0;
+      for (int s = 0; s + 1 < nk; ++s) {
+        if (s + NS < nk) RV_WAIT_VMCNT((NS - 2) * LPS);
+        else wait_tiles(nk - 2 - s);
+        __syncthreads();
+        if (s + NS < nk) {
+          const int lb = __builtin_amdgcn_readfirstlane((int)(size_t)(smem + slot * BUF) + lw * 1024);
+          const uint16_t* pa = baseA(s + NS);
+          const uint16_t* pb = baseB(s + NS);
+#pragma unroll
+          for (int q = 0; q < NA; ++q) dtl_load_s(pa, oa[q], lb + q * NL * 1024);
+#pragma unroll
+          for (int q = 0; q < NB; ++q) dtl_load_s(pb, ob[q], lb + A_BYTES + q * NL * 1024);
+        }
+        slot = slot + 1 == NS ? 0 : slot + 1;
+      }
+    } else {
     bf16x8 fa[2][TM], fb[2][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i) fa[0][i] = dtl_frag<AKM, BM, BK>(smem, wm0 + i * 32, 0);
@@ -708,6 +728,7 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
 #pragma unroll
         for (int j = 0; j < TN; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[L][j], fa[L][i], acc[i][j], 0, 0, 0);
+    }
     }
   } else {
 #pragma unroll
