@@ -43,6 +43,37 @@ constexpr size_t kDeepBytes = 512u << 20;
 constexpr int kGroupBlocks = RV_GEMM_GROUP_MAX / 4;
 static_assert(9 * kGroupBlocks <= RV_REDUCE_MAX, "the column sums of a group fit in one launch");
 
+// the work buffer, with a set of buffers for every block or with alternating ones
+void plan_work(rv_stage* s, DecPlan* p, bool deep) {
+  const size_t T = p->T, d = p->d;
+  p->deep = deep;
+  p->sets = deep ? p->L : 2;
+  p->dy_sets = deep ? p->L : 3;
+  p->group = 1;
+  if (p->deep && p->T < RV_WGRAD_SPLIT_K) {
+    // A block whose products do not give every CU a tile leaves with three others: a launch is a few microseconds, and the
+    // event pair in front of it 11 of host time, however small it is.  Stage step of 12 blocks of d 448 (172 tiles) on
+    // 256 tokens, two / three / four blocks at a time, 815 / 785 / 745 us.  Blocks that fill the chip lose by waiting for each other:
+    // d 896 (448 tiles), 256 tokens, one / three at a time 400 / 407, d 832 in separate calls 1398 / 1422.
+    auto tiles = [](int64_t M, int64_t N) { return ((M + 127) / 128) * ((N + 127) / 128); };
+    if (2 * tiles(p->d, p->f) + tiles(p->d, p->d) + tiles(p->d, 3 * p->d) < 256) p->group = kGroupBlocks;
+  }
+  size_t w = 0;
+  p->w_dres = w; w += align_up(T * d * 4);
+  p->w_dtmp = w; w += align_up(T * d * 2);
+  p->w_D = w; w += align_up(T * p->H * 4);
+  p->w_part_dy = w; w += align_up((size_t)rv_widen_parts(p->T) * d * 4);   // of the arriving gradient (32-row blocks)
+  p->w_ytmp = w; w += align_up(T * d * 4);
+  p->f_wo = rv_gemm_part_form(p->T, p->d, p->d); p->f_w2 = rv_gemm_part_form(p->T, p->d, p->f);
+  p->b_w1 = rv_gemm_part_form(p->T, p->d, p->f); p->b_wqkv = rv_gemm_part_form(p->T, p->d, 3 * p->d);
+  auto most = [](const rv_part_form& a, const rv_part_form& b) { const int S = a.S > b.S ? a.S : b.S; return (size_t)(S > 1 ? S : 0); };
+  p->w_pf = w; w += align_up(most(p->f_wo, p->f_w2) * T * d * 4);
+  p->w_pb = w; w += align_up(most(p->b_w1, p->b_wqkv) * T * d * 4);
+  p->w_dy = w; w += p->dy_bytes * p->dy_sets;
+  p->w_set = w; w += p->set_bytes * p->sets;
+  s->work_bytes = w;
+}
+
 }  // namespace
 
 rv_status rv_dec_plan(rv_stage* s) {
@@ -99,33 +130,15 @@ rv_status rv_dec_plan(rv_stage* s) {
   p->o_part_qkv = q; q += align_up((size_t)rv_attn_colsum_parts(p->mb, p->S) * 3 * d * 4);
   p->set_bytes = q;
   p->dy_bytes = align_up(T * d * 2);
-  p->deep = (size_t)p->L * (p->set_bytes + p->dy_bytes) <= kDeepBytes;
-  p->sets = p->deep ? p->L : 2;
-  p->dy_sets = p->deep ? p->L : 3;
-  p->group = 1;
-  if (p->deep && p->T < RV_WGRAD_SPLIT_K) {
-    // A block whose products do not give every CU a tile leaves with three others: a launch is a few microseconds, and the
-    // event pair in front of it 11 of host time, however small it is.  Stage step of 12 blocks of d 448 (172 tiles) on
-    // 256 tokens, two / three / four blocks at a time, 815 / 785 / 745 us.  Blocks that fill the chip lose by waiting for each other:
-    // d 896 (448 tiles), 256 tokens, one / three at a time 400 / 407, d 832 in separate calls 1398 / 1422.
-    auto tiles = [](int64_t M, int64_t N) { return ((M + 127) / 128) * ((N + 127) / 128); };
-    if (2 * tiles(d, f) + tiles(d, d) + tiles(d, 3 * d) < 256) p->group = kGroupBlocks;
-  }
-  size_t w = 0;
-  p->w_dres = w; w += align_up(T * d * 4);
-  p->w_dtmp = w; w += align_up(T * d * 2);
-  p->w_D = w; w += align_up(T * H * 4);
-  p->w_part_dy = w; w += align_up((size_t)rv_widen_parts(p->T) * d * 4);   // of the arriving gradient (32-row blocks)
-  p->w_ytmp = w; w += align_up(T * d * 4);
-  p->f_wo = rv_gemm_part_form(p->T, p->d, p->d); p->f_w2 = rv_gemm_part_form(p->T, p->d, p->f);
-  p->b_w1 = rv_gemm_part_form(p->T, p->d, p->f); p->b_wqkv = rv_gemm_part_form(p->T, p->d, 3 * p->d);
-  auto most = [](const rv_part_form& a, const rv_part_form& b) { const int S = a.S > b.S ? a.S : b.S; return (size_t)(S > 1 ? S : 0); };
-  p->w_pf = w; w += align_up(most(p->f_wo, p->f_w2) * T * d * 4);
-  p->w_pb = w; w += align_up(most(p->b_w1, p->b_wqkv) * T * d * 4);
-  p->w_dy = w; w += p->dy_bytes * p->dy_sets;
-  p->w_set = w; w += p->set_bytes * p->sets;
-  s->work_bytes = w;
+  plan_work(s, p, (size_t)p->L * (p->set_bytes + p->dy_bytes) <= kDeepBytes);
   return RV_OK;
+}
+
+bool rv_dec_less_work(rv_stage* s) {
+  DecPlan* p = (DecPlan*)s->impl;
+  if (!p->deep) return false;
+  plan_work(s, p, false);
+  return true;
 }
 
 void rv_dec_free(rv_stage* s) {

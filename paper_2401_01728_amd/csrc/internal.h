@@ -233,6 +233,7 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
 
 // ---- decoder.hip -------------------------------------------------------------------
 rv_status rv_dec_plan(rv_stage* s);
+bool rv_dec_less_work(rv_stage* s);   // after a failed allocation: a smaller work buffer, if there is one (work_bytes)
 void rv_dec_free(rv_stage* s);
 rv_status rv_dec_forward(rv_stage* s, rv_slot& slot, const void* in, void* out);
 rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void* grad_in);

@@ -76,7 +76,13 @@ extern "C" rv_status rv_stage_create(const rv_stage_desc* d, rv_stage** out) {
             hipMalloc((void**)&s->grad, s->P * 4) == hipSuccess;
   for (int i = 0; ok && i < nv; ++i) ok = hipMalloc((void**)&s->ver[i], s->P * s->ver_elem + RV_VER_PAD) == hipSuccess;
   if (ok && s->slot_bytes) ok = hipMalloc((void**)&s->stash, s->slot_bytes * ns) == hipSuccess;
-  if (ok && s->work_bytes) ok = hipMalloc((void**)&s->work, s->work_bytes) == hipSuccess;
+  if (ok && s->work_bytes) {
+    ok = hipMalloc((void**)&s->work, s->work_bytes) == hipSuccess;
+    if (!ok && s->kind == RV_DECODER && rv_dec_less_work(s)) {
+      (void)hipGetLastError();
+      ok = hipMalloc((void**)&s->work, s->work_bytes) == hipSuccess;
+    }
+  }
   if (!ok) { (void)hipGetLastError(); free_all(s); return RV_E_NOMEM; }
   for (int i = 0; i < ns; ++i) s->slots[i].base = s->stash + (size_t)i * s->slot_bytes;
   if (hipMemsetAsync(s->master, 0, s->P * 4, s->st) != hipSuccess ||
