@@ -28,6 +28,8 @@ struct DecPlan {
   // its own).  deep: a set for every block, nothing is overwritten within a backward.
   bool deep;
   int sets, dy_sets, group;   // group: blocks whose side work goes out together (deep only)
+  bool early;                 // the feed-forward pair of the weight-gradient products leaves ahead of the other two (begin)
+  rv_wgrad_form wgrad, wgrad_last;   // of a block's products; of the two that leave last by themselves, of the first block
   size_t w_dres, w_dtmp, w_D, w_part_dy, w_ytmp;
   // products whose contraction is cut over workgroups, the LayerNorm behind them adding the pieces (S 1: none), and where
   // the pieces go: those of the forward and of the backward apart, a step runs both at once
@@ -40,6 +42,8 @@ struct DecPlan {
 
 // A stage whose sets for every block fit in this many bytes gets them (deep).
 constexpr size_t kDeepBytes = 512u << 20;
+constexpr int kCUs = 256;
+int tiles256(int M, int N) { return ((M + 255) / 256) * ((N + 255) / 256); }
 constexpr int kGroupBlocks = RV_GEMM_GROUP_MAX / 4;
 static_assert(9 * kGroupBlocks <= RV_REDUCE_MAX, "the column sums of a group fit in one launch");
 
@@ -50,7 +54,7 @@ void plan_work(rv_stage* s, DecPlan* p, bool deep) {
   p->sets = deep ? p->L : 2;
   p->dy_sets = deep ? p->L : 3;
   p->group = 1;
-  if (p->deep && p->T < RV_WGRAD_SPLIT_K) {
+  if (p->deep && p->wgrad == RV_WGRAD_SPLIT && p->T < RV_WGRAD_SPLIT_K) {
     // A block whose products do not give every CU a tile leaves with three others: a launch is a few microseconds, and the
     // event pair in front of it 11 of host time, however small it is.  Stage step of 12 blocks of d 448 (172 tiles) on
     // 256 tokens, two / three / four blocks at a time, 815 / 785 / 745 us.  Blocks that fill the chip lose by waiting for each other:
@@ -97,6 +101,12 @@ rv_status rv_dec_plan(rv_stage* s) {
   p->w1 = o; o += (size_t)d * f; p->b1 = o; o += f;
   p->w2 = o; o += (size_t)f * d; p->b2 = o; o += d;
   p->per_block = o;
+  const int pm[4] = {p->f, p->d, p->d, p->d}, pn[4] = {p->d, p->f, p->d, 3 * p->d};   // dW2, dW1, dWo, dWqkv
+  p->early = 2 * tiles256(p->d, p->f) >= kCUs;
+  // (a launch of an early block that does not fill the chip is split on few tokens by itself)
+  p->wgrad = p->early ? RV_WGRAD_BY_TOKENS : rv_gemm_wgrad_form(4, pm, pn, p->T);
+  // (stage step of 4 blocks of d 1024, 4096 tokens, these 64 tiles split / in order 1789 / 1817 us)
+  p->wgrad_last = rv_gemm_wgrad_form(2, pm + 2, pn + 2, p->T);
   s->P = o * p->L;
   // the matrices of a weight version lie in blocks of 32 columns
   const size_t at[4] = {p->wqkv, p->wo, p->w1, p->w2};
@@ -253,13 +263,13 @@ struct Backward {
   rv_reduce_job sums[RV_REDUCE_MAX];
   rv_gemm_args prods[RV_GEMM_GROUP_MAX];
   int n_sums = 0, n_prods = 0;
-  bool early = false;
+  bool early;
   int wg_pos[4] = {2, 2, 2, 2};   // launch points (see begin) of dW2, dW1, dWo, dWqkv
   int whole = 0;                  // blocks below this one (and it) still lack part of their gradient: updates done down to it
 
   Backward(rv_stage* s_, const rv_slot& slot_, const void* go, void* gi, hipStream_t st_)
       : s(s_), p(*(const DecPlan*)s_->impl), slot(slot_), grad_out(go), grad_in(gi), st(st_), ws(s_->wgs),
-        sh(s_->in_step ? 1 : 0) {}
+        sh(s_->in_step ? 1 : 0), early(p.early) {}
 
   uint16_t* dy_buf(int l) const { return (uint16_t*)(s->work + p.w_dy + (size_t)(l % p.dy_sets) * p.dy_bytes); }
   char* set(int l) const { return s->work + p.w_set + (size_t)(l % p.sets) * p.set_bytes; }
@@ -282,7 +292,7 @@ struct Backward {
     n_sums = 0;
     return n ? rv_reduce_rows(sums, n, s->eta, to) : RV_OK;
   }
-  rv_status send_prods() {
+  rv_status send_prods(rv_wgrad_form form) {
     const int n = n_prods;
     n_prods = 0;
     if (!n) return RV_OK;
@@ -293,11 +303,11 @@ struct Backward {
       RV_HIP_TRY(hipEventCreate(&e1));
       s->prof_ev.push_back(e1);
       RV_HIP_TRY(hipEventRecord(e0, ws));
-      RV_TRY(rv_gemm_wgrad_grouped(prods, n, ws));
+      RV_TRY(rv_gemm_wgrad_grouped(prods, n, ws, form));
       RV_HIP_TRY(hipEventRecord(e1, ws));
       return RV_OK;
     }
-    return rv_gemm_wgrad_grouped(prods, n, ws);
+    return rv_gemm_wgrad_grouped(prods, n, ws, form);
   }
   // blocks l .. whole - 1 have their whole gradient: unless the epilogues have applied it already, their delayed update
   rv_status update_from(int l, hipStream_t to) {
@@ -353,13 +363,9 @@ struct Backward {
     // dWqkv only when the two together are not a whole number of rounds anyway.  (All four behind the
     // first LayerNorm's backward, one event pair less per block: +4 % at d 2048, d 1024 and 6 blocks of
     // d 768 on 1152 tokens.)
-    const int kCUs = 256;
-    auto tiles = [](int M, int N) { return ((M + 255) / 256) * ((N + 255) / 256); };
-    const int n_ffn = 2 * tiles(p.d, p.f), n_o = tiles(p.d, p.d), n_qkv = tiles(p.d, 3 * p.d);
-    early = n_ffn >= kCUs;
     if (early) {
       wg_pos[0] = wg_pos[1] = 0;
-      if (!p.deep && (n_o + n_qkv) % kCUs != 0) wg_pos[2] = 1;
+      if (!p.deep && (tiles256(p.d, p.d) + tiles256(p.d, 3 * p.d)) % kCUs != 0) wg_pos[2] = 1;
     }
     return RV_OK;
   }
@@ -427,7 +433,7 @@ struct Backward {
     take(0);
     if (pair_first && leaves) {
       RV_TRY(side_begin());
-      RV_TRY(send_prods());
+      RV_TRY(send_prods(p.wgrad));
       RV_TRY(send_sums(ws));
       if (p.deep) RV_TRY(update_from(l + 1, ws));
     }
@@ -443,7 +449,7 @@ struct Backward {
     if (early && !p.deep) {
       RV_TRY(side_begin());
       RV_TRY(send_sums(ws));
-      RV_TRY(send_prods());
+      RV_TRY(send_prods(p.wgrad));
     }
     RV_TRY(gemm(sh, st, dx1_16, w + p.wo, 1, T, d, d, RV_EPI_BF16, dtmp, d));                   // da = dx1 Wo^T
     // (the attention backward also leaves partial column sums of dqkv: the qkv bias gradient)
@@ -454,7 +460,7 @@ struct Backward {
     take(2);
     if (leaves) {
       RV_TRY(side_begin());
-      RV_TRY(send_prods());
+      RV_TRY(send_prods(l == 0 && pair_first && !early ? p.wgrad_last : p.wgrad));
       if (early || p.deep) RV_TRY(send_sums(ws));
       if (p.deep) RV_TRY(update_from(l + 1, ws));   // (block l lacks what its last LayerNorm gives)
     }

@@ -1396,10 +1396,42 @@ rv_status launch_grouped_split(const rv_gemm_args* gs, int count, hipStream_t st
 }
 }  // namespace
 
+namespace {
+int tiles_of(int count, const int* M, const int* N, int edge) {
+  int tiles = 0;
+  for (int k = 0; k < count; ++k) tiles += ((M[k] + edge - 1) / edge) * ((N[k] + edge - 1) / edge);
+  return tiles;
+}
+}  // namespace
+
+// 256x256 tiles, eight waves (measured against 128x128 and 128x256 tiles, alone and inside the
+// stage step of d 1024, 2048 and 1600: fewest LDS bytes per MFMA, so it takes the least CU time
+// from the kernels that run beside it, and the step is 3-4 % shorter)
+// A block whose 256x256 tiles do not cover the chip and whose walk along the tokens is short takes
+// 128x128 tiles with the walk split in two, four times as many: 24 -> 12 us (d 448, ffn 1792, 256
+// tokens, 44 tiles), 37 -> 34 us (768, 3072, 1152 tokens, 108); even at 30 us with 128 tokens of a
+// 1024-wide block, where the update's 126 MB bound it.  Longer walks keep the CU time per flop down: stage steps of
+// four blocks, ms, split / in order (the separate calls differ the same way):
+//   tokens           512          1024         1536         2048         3072         4096
+//   d 1024   0.710/0.732  0.870/0.876  1.090/1.074  1.240/1.220  1.584/1.535  1.979/1.881
+//   d 768    0.514/0.520  0.656/0.651  0.772/0.786  0.917/0.904  1.156/1.095  1.377/1.357
+//   d 448    0.390/0.410  0.425/0.443  0.486/0.496  0.531/0.568  0.669/0.690  0.786/0.818
+// From RV_WGRAD_SPLIT_K tokens on the split form where the model of the forms has the whole block a quarter faster: that is a narrow
+// one, whose 256x256 tiles are a tenth of the chip.  Stage steps, in order / split, us: d 128, 4032 tokens 726 / 539; d 320, 6272 tokens 2266 /
+// 2000; d 256, 2688 tokens 1226 / 1164; d 448, 4160 tokens, four microbatches in separate calls 4340 / 3915; the one
+// seen to lose, d 384 on 3584 tokens in separate calls, 2443 / 2500.
+// Asked for the four products of a block together, however many launches they leave in (the few tiles that a wide block sends by
+// themselves share the chip with the others: dWo of d 1600, 8192 tokens, 49 tiles, split 11 ms of CU time, in order 7; stage step
+// 21.53 / 21.43 and, another run, 21.39 / 21.37 ms),
+// and for what leaves last by itself, with nothing behind it to share the chip (decoder.hip).
+rv_wgrad_form rv_gemm_wgrad_form(int count, const int* M, const int* N, int K) {
+  const int tiles = tiles_of(count, M, N, 256), small = tiles_of(count, M, N, 128);
+  const float whole = ceilf(tiles / 256.f) * (8.9f + K / 32 * 0.55f), split = ceilf(small / 256.f) * (4.3f + K / 64 * 0.48f);
+  return tiles < 256 && (K < RV_WGRAD_SPLIT_K || split < 0.75f * whole) ? RV_WGRAD_SPLIT : RV_WGRAD_IN_ORDER;
+}
+
 rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t st, rv_wgrad_form form) {
-  const bool in_order = form == RV_WGRAD_IN_ORDER;
-  if (!gs || count < 1 || count > (in_order ? RV_GEMM_GROUP_BLOCK : RV_GEMM_GROUP_MAX)) return RV_E_INVAL;
-  if (count > RV_GEMM_GROUP_BLOCK && gs[0].K >= RV_WGRAD_SPLIT_K) return RV_E_INVAL;
+  if (!gs || count < 1 || count > (form == RV_WGRAD_SPLIT ? RV_GEMM_GROUP_MAX : RV_GEMM_GROUP_BLOCK)) return RV_E_INVAL;
   for (int k = 0; k < count; ++k) {
     const rv_gemm_args& g = gs[k];
     if (!g.A || !g.B || !g.out || !g.a_kmajor || !g.b_kmajor || g.epi != EPI_F32) return RV_E_INVAL;
@@ -1411,33 +1443,14 @@ rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t s
     if (!g.upd_w && !g.store_out) return RV_E_INVAL;
     if ((((uintptr_t)g.upd_w) & 15) || (((uintptr_t)g.upd_ver) & 7)) return RV_E_INVAL;
   }
-  // 256x256 tiles, eight waves (measured against 128x128 and 128x256 tiles, alone and inside the
-  // stage step of d 1024, 2048 and 1600: fewest LDS bytes per MFMA, so it takes the least CU time
-  // from the kernels that run beside it, and the step is 3-4 % shorter)
-  // A block whose 256x256 tiles do not cover the chip and whose walk along the tokens is short takes
-  // 128x128 tiles with the walk split in two, four times as many: 24 -> 12 us (d 448, ffn 1792, 256
-  // tokens, 44 tiles), 37 -> 34 us (768, 3072, 1152 tokens, 108); even at 30 us with 128 tokens of a
-  // 1024-wide block, where the update's 126 MB bound it.  Longer walks keep the CU time per flop down: stage steps of
-  // four blocks, ms, split / in order (the separate calls differ the same way):
-  //   tokens           512          1024         1536         2048         3072         4096
-  //   d 1024   0.710/0.732  0.870/0.876  1.090/1.074  1.240/1.220  1.584/1.535  1.979/1.881
-  //   d 768    0.514/0.520  0.656/0.651  0.772/0.786  0.917/0.904  1.156/1.095  1.377/1.357
-  //   d 448    0.390/0.410  0.425/0.443  0.486/0.496  0.531/0.568  0.669/0.690  0.786/0.818
-  if (!in_order) {
-    int tiles = 0;
-    for (int k = 0; k < count; ++k) tiles += ((gs[k].M + 255) / 256) * ((gs[k].N + 255) / 256);
-    if (count > RV_GEMM_GROUP_BLOCK) return launch_grouped_split<128, 128, 2, 4, 4, RV_GEMM_GROUP_MAX>(gs, count, st);
-    // On more tokens the split form where the model of the forms has it a quarter faster: that is a narrow block, whose 256x256 tiles
-    // are a tenth of the chip.  Stage steps, in order / split, us: d 128, 4032 tokens 726 / 539; d 320, 6272 tokens 2266 /
-    // 2000; d 256, 2688 tokens 1226 / 1164; d 448, 4160 tokens, four microbatches in separate calls 4340 / 3915; the one
-    // seen to lose, d 384 on 3584 tokens in separate calls, 2443 / 2500.
-    int small = 0;
-    for (int k = 0; k < count; ++k) small += ((gs[k].M + 127) / 128) * ((gs[k].N + 127) / 128);
-    const int K = gs[0].K;
-    const float whole = ceilf(tiles / 256.f) * (8.9f + K / 32 * 0.55f), split = ceilf(small / 256.f) * (4.3f + K / 64 * 0.48f);
-    if (tiles < 256 && (K < RV_WGRAD_SPLIT_K || (form == RV_WGRAD_STAGE && split < 0.75f * whole))) return launch_grouped_split<128, 128, 2, 4, 4, RV_GEMM_GROUP_BLOCK>(gs, count, st);
+  if (form == RV_WGRAD_BY_TOKENS) {
+    int M[RV_GEMM_GROUP_BLOCK], N[RV_GEMM_GROUP_BLOCK];
+    for (int k = 0; k < count; ++k) { M[k] = gs[k].M; N[k] = gs[k].N; }
+    form = gs[0].K < RV_WGRAD_SPLIT_K && tiles_of(count, M, N, 256) < 256 ? RV_WGRAD_SPLIT : RV_WGRAD_IN_ORDER;
   }
-  return launch_grouped_dtl<256, 256, 32, 4, 8>(gs, count, st);
+  if (form == RV_WGRAD_IN_ORDER) return launch_grouped_dtl<256, 256, 32, 4, 8>(gs, count, st);
+  return count > RV_GEMM_GROUP_BLOCK ? launch_grouped_split<128, 128, 2, 4, 4, RV_GEMM_GROUP_MAX>(gs, count, st)
+                                     : launch_grouped_split<128, 128, 2, 4, 4, RV_GEMM_GROUP_BLOCK>(gs, count, st);
 }
 
 extern "C" rv_status rv_k_gemm_bf16(const void* A, int64_t lda, int a_kmajor, const void* B, int64_t ldb,

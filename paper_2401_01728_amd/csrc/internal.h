@@ -107,15 +107,17 @@ rv_status rv_gemm_part(const rv_gemm_args& g, int S, float* part, hipStream_t st
 struct rv_part_form { int tile, S; };   // S 1: the whole product is as good
 rv_part_form rv_gemm_part_form(int M, int N, int K);
 // up to RV_GEMM_GROUP_MAX weight-gradient products (both operands k-major, fp32 output) in one launch; more than the four
-// of one block only with contractions shorter than RV_WGRAD_SPLIT_K (the tiles whose contraction is split)
+// of one block only in the split form
 #define RV_GEMM_GROUP_BLOCK 4
 #define RV_GEMM_GROUP_MAX 16
 #define RV_WGRAD_SPLIT_K 2048
 rv_status rv_stage_update_range(rv_stage* s, size_t off, size_t n, hipStream_t st);
-// RV_WGRAD_IN_ORDER: every product summed in order of k, as rv_gemm_bf16 with tile 5256 does; BY_TOKENS: small blocks on fewer than
-// RV_WGRAD_SPLIT_K tokens take tiles whose contraction is split; STAGE: narrow ones on more tokens as well
-enum rv_wgrad_form { RV_WGRAD_IN_ORDER, RV_WGRAD_BY_TOKENS, RV_WGRAD_STAGE };
-rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t st, rv_wgrad_form form = RV_WGRAD_STAGE);
+// RV_WGRAD_IN_ORDER: every product summed in order of k, as rv_gemm_bf16 with tile 5256 does; SPLIT: in tiles whose contraction
+// is split, as with tile 1128; BY_TOKENS: the latter where the products of the launch are small and of fewer than RV_WGRAD_SPLIT_K tokens
+enum rv_wgrad_form { RV_WGRAD_IN_ORDER, RV_WGRAD_SPLIT, RV_WGRAD_BY_TOKENS };
+rv_status rv_gemm_wgrad_grouped(const rv_gemm_args* gs, int count, hipStream_t st, rv_wgrad_form form);
+// IN_ORDER or SPLIT for count products [M[k], N[k]] over K tokens
+rv_wgrad_form rv_gemm_wgrad_form(int count, const int* M, const int* N, int K);
 
 // ---- norm.hip ---------------------------------------------------------------------
 rv_status rv_ln_fwd(const void* x, int x_is_bf16, float* xcopy, const uint16_t* gamma, const uint16_t* beta,

@@ -360,3 +360,26 @@ def test_versions_hold_the_masters(how):
         fresh.set_params(s.get_params())
         x = bf16_normal(82, 0, s.in_shape)[0]
         assert torch.equal(s.forward(9, x), fresh.forward(9, x))
+
+
+# The feed-forward pair of a block's gradient products leaves in a launch of its own where the block is the stage's first one; there
+# as elsewhere the block decides how they are summed.  Blocks of which the pair alone would be split: on 2048 tokens, and on few
+@pytest.mark.parametrize("d,H,f,S,mb", [(512, 8, 3328, 64, 32), (1536, 24, 5376, 64, 2)])
+def test_gradients_do_not_depend_on_the_launch_they_leave_in(d, H, f, S, mb):
+    import paper_2401_01728_amd as rv
+    block = decoder_params_host(73, 1, d, f)
+    passing = block.copy()              # a block whose two branches add nothing: Wo, bo, W2, b2 zero
+    shapes = blocks.decoder_param_shapes(1, d, f)
+    for name, v in blocks.unflatten(passing, shapes).items():
+        if name.split(".")[1] in ("Wo", "bo", "W2", "b2"):
+            v[...] = 0.0
+    (x, _), (dy, _) = bf16_normal(73, 0, (mb, S, d)), bf16_normal(73, 1, (mb, S, d), std=1e-2)
+    res = []
+    for w in ([block], [passing, block]):
+        g = rv.Stage.decoder(len(w), d, H, f, S, mb, 0, 1e-2, keep_grad=True)
+        g.set_params(dev(np.concatenate(w)))
+        y = g.forward(0, x)
+        g.backward(0, dy)
+        gb = blocks.unflatten(g.last_grad()[-block.size:].cpu().numpy(), shapes)
+        res.append((y.float().cpu().numpy(), gb["blk0.W1"], gb["blk0.W2"]))
+    assert all(np.array_equal(a, b) for a, b in zip(*res))
