@@ -151,6 +151,8 @@ rv_status rv_stage_forward(rv_stage* s, int64_t mb_id, const void* in, void* out
  * peer to grad_in (may be NULL; may share grad_out's buffer), applies x <- x - eta * g to this stage's
  * block only (Eq. 4) and publishes the result as the newest weight version.
  * Any in-flight id is legal.  RV_E_UNKNOWN_MB.
+ * Decoder stages: RV_E_INVAL if grad_out does not begin at 16 bytes (unless it shares memory with grad_in) or if
+ * microbatch * seq * max(3 d_model, d_ffn) reaches 2^31 (a forward: max(d_model, d_ffn)).
  */
 rv_status rv_stage_backward(rv_stage* s, int64_t mb_id, const void* grad_out, void* grad_in);
 

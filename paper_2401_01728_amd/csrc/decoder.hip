@@ -9,6 +9,7 @@
 // product operands are bf16.  Per microbatch and block the stash keeps x, x1 (fp32), the
 // LN statistics, u, qkv, a, v2, z, g (bf16) and the softmax log-sums: everything the
 // backward reads, so nothing is recomputed except the attention probabilities.
+#include <algorithm>
 #include <new>
 #include "internal.h"
 
@@ -499,6 +500,20 @@ struct Backward {
 };
 
 }  // namespace
+
+// Matrix products address an operand in 32 bits (T * f: also GELU(z) and dz).
+bool rv_dec_takes_forward(const rv_stage* s) {
+  const DecPlan& p = *(const DecPlan*)s->impl;
+  return (int64_t)p.T * std::max(p.d, p.f) < (1ll << 31);
+}
+// The arriving gradient is such an operand where it lies, and begins at 16 bytes then; one that shares memory with grad_in is
+// copied first.
+bool rv_dec_takes_backward(const rv_stage* s, const void* grad_out, const void* grad_in) {
+  const DecPlan& p = *(const DecPlan*)s->impl;
+  const size_t bytes = (size_t)p.T * p.d * 2;
+  return (int64_t)p.T * std::max(3 * p.d, p.f) < (1ll << 31) &&
+         (((uintptr_t)grad_out & 15) == 0 || rv_overlap(grad_out, bytes, grad_in, bytes));
+}
 
 rv_status rv_dec_forward(rv_stage* s, rv_slot& slot, const void* in, void* out) {
   const int L = ((const DecPlan*)s->impl)->L;

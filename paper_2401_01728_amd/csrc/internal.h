@@ -237,6 +237,9 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
 rv_status rv_dec_plan(rv_stage* s);
 bool rv_dec_less_work(rv_stage* s);   // after a failed allocation: a smaller work buffer, if there is one (work_bytes)
 void rv_dec_free(rv_stage* s);
+// what the kernels of a forward, of a backward would refuse, to be asked before a microbatch is admitted or anything is enqueued
+bool rv_dec_takes_forward(const rv_stage* s);
+bool rv_dec_takes_backward(const rv_stage* s, const void* grad_out, const void* grad_in);
 rv_status rv_dec_forward(rv_stage* s, rv_slot& slot, const void* in, void* out);
 rv_status rv_dec_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void* grad_in);
 rv_status rv_dec_step(rv_stage* s, rv_slot& fwd, const void* in, void* out, rv_slot& bwd, const void* grad_out, void* grad_in);

@@ -389,11 +389,17 @@ rv_status do_both(rv_stage* s, int64_t fwd_mb, const void* in, void* out, int bw
   }
   rv_slot* fwd = nullptr;
   RV_TRY(admit_forward(s, fwd_mb, &fwd));
-  RV_TRY(admit_backward(s));
   rv_slot& bwd = s->slots[bwd_slot];
-  RV_TRY(rv_dec_step(s, *fwd, in, out, bwd, grad_out, grad_in));   // (a failed launch leaves the stage unusable)
+  rv_status rc = admit_backward(s);
+  if (rc == RV_OK) rc = rv_dec_step(s, *fwd, in, out, bwd, grad_out, grad_in);
+  if (rc != RV_OK) { release(s, *fwd); return rc; }   // (a failed launch leaves the stage unusable)
   finish_backward(s, bwd);
   return RV_OK;
+}
+
+bool takes_forward(const rv_stage* s) { return s->kind == RV_MLP || rv_dec_takes_forward(s); }
+bool takes_backward(const rv_stage* s, const void* grad_out, const void* grad_in) {
+  return s->kind == RV_MLP || rv_dec_takes_backward(s, grad_out, grad_in);
 }
 
 }  // namespace
@@ -401,6 +407,8 @@ rv_status do_both(rv_stage* s, int64_t fwd_mb, const void* in, void* out, int bw
 extern "C" rv_status rv_stage_forward(rv_stage* s, int64_t mb_id, const void* in, void* out) {
   if (!s || !in || !out) return RV_E_INVAL;
   if (find_slot(s, mb_id) >= 0) return RV_E_DUP_MB;
+  if (rv_stage_in_flight(s) > s->tau) return RV_E_STASH_FULL;
+  if (!takes_forward(s)) return RV_E_INVAL;
   return do_forward(s, mb_id, in, out);
 }
 
@@ -409,6 +417,7 @@ extern "C" rv_status rv_stage_backward(rv_stage* s, int64_t mb_id, const void* g
   if (s->sync_dst >= 0) return RV_E_INVAL;   // the parameters are being averaged on another stream
   int i = find_slot(s, mb_id);
   if (i < 0) return RV_E_UNKNOWN_MB;
+  if (!takes_backward(s, grad_out, grad_in)) return RV_E_INVAL;
   return do_backward(s, i, grad_out, grad_in);
 }
 
@@ -416,13 +425,14 @@ extern "C" rv_status rv_stage_step(rv_stage* s, int64_t fwd_mb, const void* in, 
                                    const void* grad_out, void* grad_in) {
   if (!s || !in || !out || !grad_out || s->sync_dst >= 0) return RV_E_INVAL;
   if (find_slot(s, fwd_mb) >= 0) return RV_E_DUP_MB;
+  const int bi = find_slot(s, bwd_mb);
+  if (bi < 0 && fwd_mb != bwd_mb) return RV_E_UNKNOWN_MB;
+  if (rv_stage_in_flight(s) > s->tau) return RV_E_STASH_FULL;   // no free slot for the forward
+  if (!takes_forward(s) || !takes_backward(s, grad_out, grad_in)) return RV_E_INVAL;
   if (fwd_mb == bwd_mb) {  // tau = 0: the backward needs this very forward; nothing to overlap
     RV_TRY(do_forward(s, fwd_mb, in, out));
     return do_backward(s, find_slot(s, bwd_mb), grad_out, grad_in);
   }
-  const int bi = find_slot(s, bwd_mb);
-  if (bi < 0) return RV_E_UNKNOWN_MB;
-  if (rv_stage_in_flight(s) > s->tau) return RV_E_STASH_FULL;   // no free slot for the forward
   // fork: the backward of the old microbatch runs on the auxiliary stream beside the
   // forward of the new one; both see the weights as they are before this step's update.
   hipStream_t main_st = s->st;

@@ -383,3 +383,37 @@ def test_gradients_do_not_depend_on_the_launch_they_leave_in(d, H, f, S, mb):
         gb = blocks.unflatten(g.last_grad()[-block.size:].cpu().numpy(), shapes)
         res.append((y.float().cpu().numpy(), gb["blk0.W1"], gb["blk0.W2"]))
     assert all(np.array_equal(a, b) for a, b in zip(*res))
+
+
+@pytest.mark.parametrize("tau", [0, 2])
+def test_refused_backward_changes_nothing(tau):
+    """An arriving gradient that does not begin at 16 bytes is refused before anything is admitted or enqueued, by the step
+    and by the backward alone: microbatches in flight, results and parameters are those of a stage that never saw it."""
+    import paper_2401_01728_amd as rv
+    L, d, H, f, S, mb = 2, 128, 2, 256, 64, 2
+    w0 = dev(decoder_params_host(72, L, d, f))
+    res = []
+    for disturbed in (False, True):
+        g = rv.Stage.decoder(L, d, H, f, S, mb, tau, 1e-2, keep_grad=True)
+        g.set_params(w0)
+        outs = []
+        for t in range(tau + 3):
+            x, _ = bf16_normal(72, 10 + t, (mb, S, d))
+            dy, _ = bf16_normal(72, 50 + t, (mb, S, d), std=1e-2)
+            if t < tau:
+                g.forward(t, x)
+                continue
+            if disturbed:
+                odd = torch.empty(dy.numel() + 1, dtype=dy.dtype, device="cuda")[1:].view(dy.shape)
+                odd.copy_(dy)
+                calls = [lambda: g.step(t, x, t - tau, odd)] + ([lambda: g.backward(t - tau, odd)] if tau else [])
+                for call in calls:
+                    with pytest.raises(rv.RvError) as e:
+                        call()
+                    assert e.value.status == rv.api.RV_E_INVAL and g.in_flight == tau
+                with pytest.raises(rv.RvError) as e:
+                    g.backward(t, dy)              # the refused step's forward is not in flight
+                assert e.value.status == rv.api.RV_E_UNKNOWN_MB
+            outs += [*g.step(t, x, t - tau, dy), g.last_grad()]
+        res.append(outs + [g.get_params()])
+    assert all(torch.equal(a, b) for a, b in zip(*res))
