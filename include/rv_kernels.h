@@ -48,6 +48,9 @@ rv_status rv_k_gemm_bf16(const void* A, int64_t lda, int a_kmajor, const void* B
  */
 rv_status rv_k_gemm_part(const void* A, int64_t lda, const void* B, int64_t ldb, int b_kmajor, int M, int N, int K,
                          int tile, int parts, float* part, void* stream);
+/* The tile and the number of stretches that a decoder stage takes for a product in front of a LayerNorm; parts 1 (tile 0): the
+ * whole product by rv_k_gemm_bf16.  Needs no device. */
+rv_status rv_k_gemm_part_form(int M, int N, int K, int* tile, int* parts);
 
 /*
  * Up to 4 weight-gradient products dW_i[M_i,N_i] = X_i^T dY_i (both operands k-major: X_i is

@@ -1320,15 +1320,20 @@ rv_status rv_gemm_bf16(const rv_gemm_args& g, hipStream_t st) {
 // The form and the number of stretches of a product whose partial sums the next kernel can add: the least modelled time,
 // with 4 bytes per partial sum read back at 5 TB/s, if that takes a tenth off the best whole product; S = 1: none does.
 // Weights cold, best whole form / cut (with the reading back), us: 64x2048x8192 30.1 / 11.3 (64x64 tiles, S 8), 128x1024x4096
-// 11.6 / 7.1 (32x64, 4), 256x2048x8192 29.7 / 23.0 (64x64, 4), 1024x2048x8192 66.9 / 46.0 (128x128, 2), 1152x1600x6400 50.2 / 35.7,
+// 11.6 / 7.1 (32x64, 4), 1024x2048x8192 66.9 / 46.0 (128x128, 2), 1152x1600x6400 50.2 / 35.7,
 // 256x448x1792 7.2 / 5.9.  Over 130 products of 64 .. 2048 rows the modelled ratio is below the measured one by 0.1 .. 0.2 on the
 // short walks and above it by as much on the long ones; a modelled tenth was 0 .. 30 % measured.
 // Four stages of 4 blocks of d 1024 on 128 tokens, forward and backward, with their average 3137 -> 2761 us, stage step of 12
 // blocks of d 448 on 256 tokens 924 -> 852 us (with what split_tile and the early requests give).
+// Not from 64 tiles of 256x256 on, as with the split forms of whole products.  Stage steps, cut / whole, us: 4 blocks d 2048, 2048 tokens
+// 3367 / 3069, 2 of d 4096, 4608 tokens 11080 / 9200 (separate calls 11530 / 10910), 3 of d 4096, 1024 tokens 4537 / 4262 (separate
+// calls 4853 / 5017: the one form that loses).  Below, cut against the forms without: 4 of d 2048, 1024 tokens 2100 / 2550, of
+// d 1600, 2048 tokens (56 tiles) 2170 / 2344, of d 1024, 3072 tokens (48) 1390 / 1513.
 rv_part_form rv_gemm_part_form(int M, int N, int K) {
   float whole;
   whole_form(M, N, K, true, whole);
   rv_part_form best = {0, 1};
+  if (((M + 255) / 256) * ((N + 255) / 256) >= 64) return best;
   float least = 0.9f * whole;
   for (const TileForm& c : kForms) {
     if (c.code >= 2000) continue;
@@ -1463,6 +1468,14 @@ extern "C" rv_status rv_k_gemm_bf16(const void* A, int64_t lda, int a_kmajor, co
   g.M = M; g.N = N; g.K = K; g.epi = epilogue; g.out = out; g.ldo = ldo; g.out2 = out2;
   g.bias = (const uint16_t*)bias; g.resid = resid; g.ldr = ldr; g.zin = (const uint16_t*)zin; g.tile = tile;
   return rv_gemm_bf16(g, (hipStream_t)stream);
+}
+
+extern "C" rv_status rv_k_gemm_part_form(int M, int N, int K, int* tile, int* parts) {
+  if (!tile || !parts || M < 8 || N < 8 || K < 64) return RV_E_INVAL;
+  const rv_part_form form = rv_gemm_part_form(M, N, K);
+  *tile = form.tile;
+  *parts = form.S;
+  return RV_OK;
 }
 
 extern "C" rv_status rv_k_gemm_part(const void* A, int64_t lda, const void* B, int64_t ldb, int b_kmajor, int M, int N, int K,

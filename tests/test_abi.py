@@ -49,3 +49,21 @@ def test_argument_validation_needs_no_device():
     assert lib.rv_stage_create(ctypes.byref(d), ctypes.byref(h)) == INVAL                 # tau < 0
     assert lib.rv_stage_num_params(None) == 0
     assert lib.rv_strerror(-2).decode().startswith("tau+1")
+
+
+def test_large_products_are_not_cut():
+    """From 64 tiles of 256x256 on no product is cut into stretches (a step needs the CU time for its other streams); at the
+    sizes that the rule's comment quotes the forms are those."""
+    def form(M, N, K):
+        tile, parts = ctypes.c_int(), ctypes.c_int()
+        assert _lib.lib().rv_k_gemm_part_form(M, N, K, ctypes.byref(tile), ctypes.byref(parts)) == 0
+        return tile.value, parts.value
+    for tm, tn in ((8, 8), (4, 16), (5, 13), (16, 4), (11, 6), (18, 16), (64, 16)):
+        for M in (256 * tm - 192, 256 * tm):
+            for N in (256 * tn - 192, 256 * tn):
+                for K in (N, 2 * N, 3 * N, 4 * N):
+                    assert form(M, N, K) == (0, 1), (M, N, K)
+    for shape, want in (((64, 2048, 8192), (1064, 8)), ((128, 1024, 4096), (1032, 4)), ((1024, 2048, 8192), (1128, 2)),
+                        ((1152, 1600, 6400), (1128, 2)), ((256, 448, 1792), (1032, 4))):
+        assert form(*shape) == want
+    assert _lib.lib().rv_k_gemm_part_form(64, 64, 64, None, None) == -1
