@@ -48,6 +48,12 @@ rv_status rv_k_gemm_bf16(const void* A, int64_t lda, int a_kmajor, const void* B
  */
 rv_status rv_k_gemm_part(const void* A, int64_t lda, const void* B, int64_t ldb, int b_kmajor, int M, int N, int K,
                          int tile, int parts, float* part, void* stream);
+/*
+ * An idle decoder stage whose blocks have a set of work buffers each takes the alternating sets instead, as creation does when
+ * the larger buffer cannot be allocated.  Waits for the stage's stream.  RV_E_INVAL where there is no smaller buffer, with a
+ * microbatch in flight or an averaging not joined.
+ */
+rv_status rv_k_stage_less_work(rv_stage* s);
 /* The tile and the number of stretches that a decoder stage takes for a product in front of a LayerNorm; parts 1 (tile 0): the
  * whole product by rv_k_gemm_bf16.  Needs no device. */
 rv_status rv_k_gemm_part_form(int M, int N, int K, int* tile, int* parts);

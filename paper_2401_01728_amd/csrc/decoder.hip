@@ -148,8 +148,11 @@ rv_status rv_dec_plan(rv_stage* s) {
 bool rv_dec_less_work(rv_stage* s) {
   DecPlan* p = (DecPlan*)s->impl;
   if (!p->deep) return false;
+  const size_t had = s->work_bytes;
   plan_work(s, p, false);
-  return true;
+  if (s->work_bytes < had) return true;
+  plan_work(s, p, true);   // (one or two blocks: the alternating sets are more)
+  return false;
 }
 
 void rv_dec_free(rv_stage* s) {

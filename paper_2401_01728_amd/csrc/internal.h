@@ -235,7 +235,7 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
 
 // ---- decoder.hip -------------------------------------------------------------------
 rv_status rv_dec_plan(rv_stage* s);
-bool rv_dec_less_work(rv_stage* s);   // after a failed allocation: a smaller work buffer, if there is one (work_bytes)
+bool rv_dec_less_work(rv_stage* s);   // plan a smaller work buffer (work_bytes), if there is one; nothing may be on the way
 void rv_dec_free(rv_stage* s);
 // what the kernels of a forward, of a backward would refuse, to be asked before a microbatch is admitted or anything is enqueued
 bool rv_dec_takes_forward(const rv_stage* s);

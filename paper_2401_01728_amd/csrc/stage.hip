@@ -116,6 +116,16 @@ extern "C" rv_status rv_stage_destroy(rv_stage* s) {
   return RV_OK;
 }
 
+extern "C" rv_status rv_k_stage_less_work(rv_stage* s) {
+  if (!s || s->kind != RV_DECODER || rv_stage_in_flight(s) != 0 || s->sync_dst >= 0) return RV_E_INVAL;
+  RV_HIP_TRY(hipStreamSynchronize(s->st));   // (the internal streams join it in every call)
+  if (!rv_dec_less_work(s)) return RV_E_INVAL;
+  (void)hipFree(s->work);
+  s->work = nullptr;
+  RV_HIP_TRY(hipMalloc((void**)&s->work, s->work_bytes));
+  return RV_OK;
+}
+
 extern "C" size_t rv_stage_num_params(const rv_stage* s) { return s ? s->P : 0; }
 
 extern "C" int rv_stage_in_flight(const rv_stage* s) {

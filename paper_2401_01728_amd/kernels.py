@@ -19,6 +19,11 @@ def gemm_bf16(A, a_kmajor, B, b_kmajor, M, N, K, epilogue, out, out2=None, bias=
     return out
 
 
+def stage_less_work(stage):
+    """rv_k_stage_less_work: the stage's smaller work buffer."""
+    _check(_lib.lib().rv_k_stage_less_work(stage._h))
+
+
 def gemm_part(A, B, b_kmajor, M, N, K, tile, parts, stream=None):
     """rv_k_gemm_part: fp32 [parts, M, N], the product's sums over `parts` stretches of the contraction."""
     part = torch.full((parts, M, N), float("nan"), dtype=torch.float32, device="cuda")

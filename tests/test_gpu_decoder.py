@@ -417,3 +417,44 @@ def test_refused_backward_changes_nothing(tau):
             outs += [*g.step(t, x, t - tau, dy), g.last_grad()]
         res.append(outs + [g.get_params()])
     assert all(torch.equal(a, b) for a, b in zip(*res))
+
+
+# The work buffer that creation falls back to: two alternating sets where every block had one of its own (four, two or one block to
+# a launch; the feed-forward products ahead of the rest), all results bit for bit the same
+@pytest.mark.parametrize("L,d,H,f,mb,A,momentum", [(6, 128, 2, 256, 2, 1, 0.0), (5, 320, 5, 1280, 3, 1, 0.9), (3, 2048, 16, 8192, 1, 1, 0.0),
+                                                   (4, 512, 8, 3328, 4, 2, 0.0)])
+def test_smaller_work_buffer(L, d, H, f, mb, A, momentum):
+    import paper_2401_01728_amd as rv
+    from paper_2401_01728_amd import kernels as k
+    w0 = dev(decoder_params_host(85, L, d, f))
+    res = []
+    for less in (False, True):
+        g = rv.Stage.decoder(L, d, H, f, 64, mb, 1, 1e-2, keep_grad=True)
+        g.set_accumulation(A)
+        if momentum:
+            g.set_optimizer(momentum)
+        g.set_params(w0)
+        outs = []
+        for t in range(4):
+            if less and t == 2:                        # between two uses of the stage; once only, and only when idle
+                with pytest.raises(rv.RvError):
+                    k.stage_less_work(g)
+                outs += [g.backward(1, dy), g.last_grad()]
+                k.stage_less_work(g)
+                with pytest.raises(rv.RvError):
+                    k.stage_less_work(g)
+            elif t == 2:
+                outs += [g.backward(1, dy), g.last_grad()]
+            x, dy = bf16_normal(85, 2 * t, g.in_shape)[0], bf16_normal(85, 2 * t + 1, g.in_shape, std=1e-2)[0]
+            outs += [g.forward(t, x)] if t % 2 == 0 else [*g.step(t, x, t - 1, dy), g.last_grad()]
+        res.append(outs + [g.backward(3, dy), g.last_grad(), g.get_params()])
+    assert all(torch.equal(a, b) for a, b in zip(*res))
+
+
+def test_smaller_work_buffer_is_refused():
+    import paper_2401_01728_amd as rv
+    from paper_2401_01728_amd import kernels as k
+    for g in (rv.Stage.decoder(2, 128, 2, 256, 64, 2, 0, 1e-2), rv.Stage.mlp([8, 8], 4, 0, 0.1)):   # two sets are more than two blocks need
+        with pytest.raises(rv.RvError) as e:
+            k.stage_less_work(g)
+        assert e.value.status == rv.api.RV_E_INVAL
