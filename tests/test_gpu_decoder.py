@@ -220,12 +220,12 @@ def test_decoder_error_paths():
 
 
 @pytest.mark.parametrize("A,momentum,wd", [(2, 0.0, 0.0), (1, 0.9, 5e-4), (2, 0.9, 5e-4)])
-def test_decoder_stage_with_accumulation_in_fused_steps(A, momentum, wd):
+def test_decoder_stage_with_accumulation_in_fused_steps(A, momentum, wd, L=2):
     """Gradient accumulation (section 4.2) and the momentum / weight-decay optimiser (section 4.1)
     through rv_stage_step: block-wise accumulate / update on the side stream, forwards bound to
     a version that only every A-th backward replaces."""
     import paper_2401_01728_amd as rv
-    L, d, H, f, S, mb, tau, eta = 2, 128, 2, 256, 128, 2, 2, 1e-2
+    d, H, f, S, mb, tau, eta = 128, 2, 256, 128, 2, 2, 1e-2
     shapes = blocks.decoder_param_shapes(L, d, f)
     w0 = decoder_params_host(31, L, d, f)
     g = rv.Stage.decoder(L, d, H, f, S, mb, tau, eta); g.set_params(dev(w0)); g.set_accumulation(A)
@@ -254,6 +254,29 @@ def test_decoder_stage_with_accumulation_in_fused_steps(A, momentum, wd):
             check_tensors(host64(g.last_grad()), o.last_grad, shapes, what="grad step %d" % j, group=tag + " param grads")
     assert o.k == n // A
     assert rel_l2(host64(g.get_params()) - w0, o.w - w0) < TOL
+
+
+# Six blocks, whose gradients leave four and two at a time, and with them the ranges the update kernels are given; a block's 132480
+# parameters are no multiple of the 1024 of a workgroup, which then holds the end of one block and the beginning of the next
+@pytest.mark.parametrize("A,momentum,wd", [(2, 0.0, 0.0), (1, 0.9, 5e-4), (2, 0.9, 5e-4)])
+def test_updates_of_several_blocks_at_once(A, momentum, wd):
+    test_decoder_stage_with_accumulation_in_fused_steps(A, momentum, wd, 6)
+
+
+@pytest.mark.parametrize("A,momentum", [(2, 0.0), (1, 0.9)])
+def test_versions_after_updates_of_several_blocks(A, momentum):
+    """As test_versions_hold_the_masters, for blocks that share an update's workgroup."""
+    import paper_2401_01728_amd as rv
+    st = [rv.Stage.decoder(6, 128, 2, 256, 64, 2, 0, 1e-2) for _ in range(2)]
+    st[0].set_accumulation(A)
+    st[0].set_optimizer(momentum)
+    st[0].set_params(dev(decoder_params_host(83, 6, 128, 256)))
+    for t in range(2):
+        st[0].forward(t, bf16_normal(84, 2 * t, st[0].in_shape)[0])
+        st[0].backward(t, bf16_normal(84, 2 * t + 1, st[0].in_shape, std=1e-2)[0])
+    st[1].set_params(st[0].get_params())
+    x = bf16_normal(84, 9, st[0].in_shape)[0]
+    assert torch.equal(st[0].forward(9, x), st[1].forward(9, x))
 
 
 @pytest.mark.parametrize("L,d,H,f,S,mb,tau,step", [(1, 128, 2, 2048, 256, 4, 0, False), (2, 256, 2, 1024, 128, 3, 1, True),
