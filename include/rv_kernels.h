@@ -49,6 +49,15 @@ rv_status rv_k_gemm_bf16(const void* A, int64_t lda, int a_kmajor, const void* B
 rv_status rv_k_gemm_part(const void* A, int64_t lda, const void* B, int64_t ldb, int b_kmajor, int M, int N, int K,
                          int tile, int parts, float* part, void* stream);
 /*
+ * rv_k_gemm_bf16 (parts 0) or rv_k_gemm_part (out: its pieces) on operands without gaps between the rows, each in rows or,
+ * a_blocks / b_blocks nonzero, in blocks of 32 columns as a decoder stage keeps them: element (r, c) of R rows at
+ * (c / 32) * 32 R + 32 r + c % 32 (the number of columns a multiple of 32).  out_blocks: so is the result of epilogue 4 (out) and the
+ * second result of epilogue 3 (out2).  Results are those of rows, bit for bit.
+ */
+rv_status rv_k_gemm_bf16_blocks(const void* A, int a_blocks, int a_kmajor, const void* B, int b_blocks, int b_kmajor, int M,
+                                int N, int K, int epilogue, void* out, void* out2, int out_blocks, const void* bias,
+                                const float* resid, const void* zin, int tile, int parts, void* stream);
+/*
  * An idle decoder stage whose blocks have a set of work buffers each takes the alternating sets instead, as creation does when
  * the larger buffer cannot be allocated.  Waits for the stage's stream.  RV_E_INVAL where there is no smaller buffer, with a
  * microbatch in flight or an averaging not joined.

@@ -58,6 +58,8 @@ KERNEL_SYMBOLS = {
                                c_void_p, c_int64, c_void_p, c_void_p, c_void_p, c_int64, c_void_p, c_int,
                                c_void_p]),
     "rv_k_gemm_part": (c_int, [c_void_p, c_int64, c_void_p, c_int64, c_int, c_int, c_int, c_int, c_int, c_int, c_void_p, c_void_p]),
+    "rv_k_gemm_bf16_blocks": (c_int, [c_void_p, c_int, c_int, c_void_p, c_int, c_int, c_int, c_int, c_int, c_int, c_void_p, c_void_p, c_int,
+                                      c_void_p, c_void_p, c_void_p, c_int, c_int, c_void_p]),
     "rv_k_stage_less_work": (c_int, [c_void_p]),
     "rv_k_gemm_part_form": (c_int, [c_int, c_int, c_int, c_void_p, c_void_p]),
     "rv_k_layernorm_fwd_parts": (c_int, [c_void_p, c_int, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p,

@@ -1470,6 +1470,21 @@ extern "C" rv_status rv_k_gemm_bf16(const void* A, int64_t lda, int a_kmajor, co
   return rv_gemm_bf16(g, (hipStream_t)stream);
 }
 
+extern "C" rv_status rv_k_gemm_bf16_blocks(const void* A, int a_blocks, int a_kmajor, const void* B, int b_blocks, int b_kmajor, int M,
+                                           int N, int K, int epilogue, void* out, void* out2, int out_blocks, const void* bias,
+                                           const float* resid, const void* zin, int tile, int parts, void* stream) {
+  if (M < 1 || N < 1 || K < 1 || (out_blocks && epilogue != EPI_BF16_BIAS_GELU && epilogue != EPI_BF16_DGELU)) return RV_E_INVAL;
+  auto operand = [](const void* p, int blocks, int64_t rows, int64_t cols) { return blocks ? rv_blocks(p, rows) : rv_rows(p, cols); };
+  const rv_mat a = a_kmajor ? operand(A, a_blocks, K, M) : operand(A, a_blocks, M, K);
+  const rv_mat b = b_kmajor ? operand(B, b_blocks, K, N) : operand(B, b_blocks, N, K);
+  rv_gemm_args g;
+  g.A = a.p; g.lda = a.ld; g.a_bs = a.bs; g.a_kmajor = a_kmajor;
+  g.B = b.p; g.ldb = b.ld; g.b_bs = b.bs; g.b_kmajor = b_kmajor;
+  g.M = M; g.N = N; g.K = K; g.epi = epilogue; g.out = out; g.ldo = N; g.out2 = out2; g.bsv = out_blocks ? (int64_t)M * 32 : 0;
+  g.bias = (const uint16_t*)bias; g.resid = resid; g.ldr = N; g.zin = (const uint16_t*)zin; g.tile = tile;
+  return parts ? rv_gemm_part(g, parts, (float*)out, (hipStream_t)stream) : rv_gemm_bf16(g, (hipStream_t)stream);
+}
+
 extern "C" rv_status rv_k_gemm_part_form(int M, int N, int K, int* tile, int* parts) {
   if (!tile || !parts || M < 8 || N < 8 || K < 64) return RV_E_INVAL;
   const rv_part_form form = rv_gemm_part_form(M, N, K);

@@ -19,6 +19,15 @@ def gemm_bf16(A, a_kmajor, B, b_kmajor, M, N, K, epilogue, out, out2=None, bias=
     return out
 
 
+def gemm_bf16_blocks(A, a_blocks, a_kmajor, B, b_blocks, b_kmajor, M, N, K, epilogue, out, out2=None, out_blocks=0, bias=None, resid=None,
+                     zin=None, tile=0, parts=0, stream=None):
+    """rv_k_gemm_bf16_blocks: operands and results in rows or in blocks of 32 columns."""
+    _check(_lib.lib().rv_k_gemm_bf16_blocks(_ptr(A), int(a_blocks), int(a_kmajor), _ptr(B), int(b_blocks), int(b_kmajor), M, N, K, epilogue,
+                                            _ptr(out), _ptr(out2), int(out_blocks), _ptr(bias), _ptr(resid), _ptr(zin), tile, parts,
+                                            _stream_handle(stream)))
+    return out
+
+
 def stage_less_work(stage):
     """rv_k_stage_less_work: the stage's smaller work buffer."""
     _check(_lib.lib().rv_k_stage_less_work(stage._h))

@@ -250,3 +250,62 @@ def test_product_in_stretches_refuses():
     for tile, parts in ((1032, 3), (1032, 0), (5256, 2), (0, 2)):      # K / 32 = 2 stretches at most; the split forms only
         with pytest.raises(rv.RvError):
             k.gemm_part(x, x, 0, 64, 64, 64, tile, parts)
+
+
+def _blocks(t):
+    """[R, C] -> the same memory size, blocks of 32 columns, each a run of R rows of 32."""
+    return t.view(t.shape[0], -1, 32).transpose(0, 1).contiguous()
+
+
+# Operands and results in blocks of 32 columns, the layout of a stage's versions and operand activations: bit for bit what rows
+# give, in every tile form, ragged in both directions (a last tile of one block of columns, of eight rows), one k-tile and more
+@pytest.mark.parametrize("M,N,K", [(40, 96, 64), (200, 352, 256), (264, 288, 128), (776, 1600, 320)])
+@pytest.mark.parametrize("tile", [2128, 2192, 2256, 5256, 1128, 1065, 1064, 1032])
+def test_operands_in_blocks_of_columns(M, N, K, tile):
+    from paper_2401_01728_amd import kernels as k
+    x, _ = bf16_normal(10, 0, (M, K))
+    w, _ = bf16_normal(10, 1, (K, N), std=0.05)
+    wt, z = w.t().contiguous(), bf16_normal(10, 2, (M, N))[0]
+    b, r = bf16_normal(10, 3, (N,), std=0.5)[0], torch.randn(M, N, device="cuda")
+    bf, f32 = torch.bfloat16, torch.float32
+    for xb, wb in ((0, 1), (1, 0), (1, 1)):
+        X, W, WT = _blocks(x) if xb else x, _blocks(w) if wb else w, _blocks(wt) if wb else wt
+        for epi, dt, kw in ((k.EPI_BF16_BIAS, bf, dict(bias=b)), (k.EPI_F32_BIAS_RESID, f32, dict(bias=b, resid=r)),
+                            (k.EPI_F32_BIAS_RESID_BF16, f32, dict(bias=b, resid=r)), (k.EPI_BF16_BIAS_GELU, bf, dict(bias=b))):
+            want, got = _out((M, N), dt), _out((M, N), dt)
+            two = epi in (k.EPI_F32_BIAS_RESID_BF16, k.EPI_BF16_BIAS_GELU)
+            want2, got2 = (_out((M, N), bf) if two else None for _ in range(2))
+            k.gemm_bf16(x, 0, w, 1, M, N, K, epi, want, out2=want2, tile=tile, **kw)
+            gb = epi == k.EPI_BF16_BIAS_GELU
+            k.gemm_bf16_blocks(X, xb, 0, W, wb, 1, M, N, K, epi, got, got2, gb, tile=tile, **kw)
+            assert torch.equal(got, want) and (not two or torch.equal(got2.flatten(), (_blocks(want2) if gb else want2).flatten()))
+        for epi, zin in ((k.EPI_BF16, None), (k.EPI_BF16_DGELU, z)):
+            want, got = _out((M, N), bf), _out((M, N), bf)
+            k.gemm_bf16(x, 0, wt, 0, M, N, K, epi, want, zin=zin, tile=tile)
+            k.gemm_bf16_blocks(X, xb, 0, WT, wb, 0, M, N, K, epi, got, None, zin is not None, zin=zin, tile=tile)
+            assert torch.equal(got.flatten(), (want if zin is None else _blocks(want)).flatten())
+        if tile < 2000:
+            for parts in (2, min(8, K // 32)):
+                for km, w_rows, w_form in ((1, w, W), (0, wt, WT)):
+                    got = torch.full((parts, M, N), float("nan"), device="cuda")
+                    k.gemm_bf16_blocks(X, xb, 0, w_form, wb, km, M, N, K, 0, got, tile=tile, parts=parts)
+                    assert torch.equal(got, k.gemm_part(x, w_rows, km, M, N, K, tile, parts))
+    if tile != 1032:                       # both operands k-major: their columns in blocks
+        Mw = (M + 31) // 32 * 32
+        xt, _ = bf16_normal(10, 4, (K, Mw))
+        want, got = _out((Mw, N), f32), _out((Mw, N), f32)
+        k.gemm_bf16(xt, 1, w, 1, Mw, N, K, k.EPI_F32, want, tile=tile)
+        k.gemm_bf16_blocks(_blocks(xt), 1, 1, _blocks(w), 1, 1, Mw, N, K, k.EPI_F32, got, tile=tile)
+        assert torch.equal(got, want)
+
+
+def test_blocks_of_columns_are_whole():
+    import paper_2401_01728_amd as rv
+    from paper_2401_01728_amd import kernels as k
+    x = torch.zeros(64, 72, dtype=torch.bfloat16, device="cuda")
+    o = torch.zeros(72, 72, dtype=torch.float32, device="cuda")
+    for args in ((x, 1, 1, x, 0, 1, 72, 72, 64, k.EPI_F32), (x, 0, 1, x, 1, 1, 72, 72, 64, k.EPI_F32)):      # 72 columns
+        with pytest.raises(rv.RvError):
+            k.gemm_bf16_blocks(*args, o)
+    with pytest.raises(rv.RvError):        # a result that is never in blocks
+        k.gemm_bf16_blocks(x, 0, 1, x, 0, 1, 72, 72, 64, k.EPI_F32, o, None, 1)
