@@ -185,7 +185,8 @@ def bench_stage(args, name, cpu_seconds=20.0):
             break
     # The dominant kernel of the step (largest share of its rocprofv3 trace) is the grouped
     # weight-gradient kernel: dW2 | dW1 | dWo | dWqkv of one block over the microbatch's tokens, in
-    # one to three launches per block (the library decides when each product goes out).  The
+    # one to three launches per block (the library decides when each product goes out; where a step's
+    # last one is small it takes gemm_split_grouped_wgrad_kernel and is counted with the rest).  The
     # library brackets each of its launches with HIP events on the stream it goes to, here,
     # inside the timed steps, beside everything else the step has running.
     st.profile(True)

@@ -82,8 +82,8 @@ rv_status rv_k_gemm_wgrad_grouped(int count, const void* const* X, const int64_t
 /*
  * The same products as a decoder stage launches them.  The tile form is chosen by size: fewer than 256 tiles of
  * 256x256 over fewer than 2048 tokens take 128x128 tiles with the contraction split (results equal
- * rv_k_gemm_bf16(..., epilogue 5, tile 1128) bit for bit), the rest the form above (a stage whose blocks are narrow takes the
- * split tiles on more tokens too).  w (with ver; both NULL: no
+ * rv_k_gemm_bf16(..., epilogue 5, tile 1128) bit for bit), the rest the form above (a stage chooses for the four
+ * products of a block together, and takes the split tiles on more tokens too where its blocks are narrow).  w (with ver; both NULL: no
  * update): host arrays of fp32 master matrices [M_i, N_i], updated in place, w <- w - eta * dW (Eq. 2, one fused
  * multiply-add), and of bf16 weight versions that receive their rounding.  dW may be NULL with w: the gradients are
  * then not stored.

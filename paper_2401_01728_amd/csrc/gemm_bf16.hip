@@ -623,7 +623,9 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
     wait_tiles(pre - 1);
     __syncthreads();
     // A wave whose part of a ragged tile lies past the end of the result only takes its share of the loads (a width of 1600 is
-    // six tiles and a quarter: of the last one's eight waves two have something to multiply).
+    // six tiles and a quarter: of the last one's eight waves two have something to multiply).  8192x1600x6400 alone 152 -> 146 us,
+    // 8192x1600x1600 48 -> 46; 12 blocks of d 1600 on 8192 tokens in separate calls 20.47 -> 20.24 ms, as a stage step, where the other
+    // streams take what a wave leaves, the same; widths of 832, 1088 and 2112 within 0.5 % either way.
     if (__builtin_amdgcn_readfirstlane(m0 + wm0 >= M || n0 + wn0 >= N)) {
       int slot = 0;
       for (int s = 0; s + 1 < nk; ++s) {
