@@ -46,10 +46,13 @@ template <int CTRL>
 __device__ __forceinline__ float rv_dpp_add(float v) {
   return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
 }
-__device__ __forceinline__ float rv_half_wave_sum(float v) {
+__device__ __forceinline__ float rv_row_sum(float v) {   // over the 16 lanes of each row alone
   v = rv_dpp_add<0xB1>(v);    // quad_perm [1,0,3,2]
   v = rv_dpp_add<0x4E>(v);    // quad_perm [2,3,0,1]
   v = rv_dpp_add<0x141>(v);   // row_half_mirror: the other quad of each 8
-  v = rv_dpp_add<0x140>(v);   // row_mirror: the other 8 of each 16
+  return rv_dpp_add<0x140>(v);   // row_mirror: the other 8 of each 16
+}
+__device__ __forceinline__ float rv_half_wave_sum(float v) {
+  v = rv_row_sum(v);
   return v + __shfl_xor(v, 16, 64);
 }

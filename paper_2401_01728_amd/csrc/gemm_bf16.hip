@@ -18,7 +18,7 @@
 //   dW       dW = x^T dy   : A = x  k-major,      B = dy k-major      (contraction over tokens)
 //
 // Tiling: a workgroup of 4 or 8 waves owns a BM x BN tile and walks K in steps of BK (32 or
-// 64); a wave owns a block of 32x32 MFMA tiles (v_mfma_f32_32x32x16_bf16).  Operand tiles go
+// 64); a wave owns a block of MFMA products (v_mfma_f32_32x32x16_bf16 or _16x16x32_bf16).  Operand tiles go
 // global -> LDS directly (global_load_lds_dwordx4) through a ring of NS stages, unpadded, bank
 // conflicts removed by an XOR swizzle (see "direct-to-LDS pipeline" below);
 //   k-contiguous operands sit in LDS as [row][BK k], read as one 16-byte fragment per lane;
@@ -27,6 +27,7 @@
 //   transposes, no transposed copies of activations in HBM.
 // The MFMA is issued with the B fragment as its first operand, so a lane ends up with
 // four CONSECUTIVE n of one row m: epilogues store 8 (bf16) or 16 (fp32) bytes per lane.
+#include <type_traits>
 #include "internal.h"
 
 namespace {
@@ -138,55 +139,66 @@ __device__ __forceinline__ void epilogue4(const Epi& e, int m, int n, f32x4 a, u
   }
 }
 
-// lane holds row m = l%32 of the wave tile and, per group rg of 4 registers,
-// columns 8*rg + 4*(l/32) .. +3
+// A wave's part of a tile is accumulated in products of 32x32 (V = f32x16) or 16x16 (V = f32x4), [TM][TN] of them.  Either
+// way a lane holds of each of its TM rows - row l % 32 or l % 16 of a product - runs of four consecutive columns: "quads", four
+// to a product of 32x32 (columns 8 r + 4 (l / 32)), one to a product of 16x16 (columns 4 (l / 16)).
+template <typename V> constexpr int kEdge = sizeof(V) == 64 ? 32 : 16;       // of a product
+template <typename V, int TN> constexpr int kQuads = sizeof(V) == 64 ? 4 * TN : TN;
+template <typename V>
+__device__ __forceinline__ int quad_row(int i) { return i * kEdge<V> + (threadIdx.x & (kEdge<V> - 1)); }
+template <typename V>
+__device__ __forceinline__ int quad_col(int c) {
+  const int l = threadIdx.x & 63;
+  return sizeof(V) == 64 ? (c >> 2) * 32 + 8 * (c & 3) + 4 * (l >> 5) : c * 16 + 4 * (l >> 4);
+}
+template <int TM, int TN>
+__device__ __forceinline__ f32x4 quad(const f32x4 (&acc)[TM][TN], int i, int c) { return acc[i][c]; }
+template <int TM, int TN>
+__device__ __forceinline__ f32x4 quad(const f32x16 (&acc)[TM][TN], int i, int c) {
+  const int r = 4 * (c & 3);
+  return f32x4{acc[i][c >> 2][r], acc[i][c >> 2][r + 1], acc[i][c >> 2][r + 2], acc[i][c >> 2][r + 3]};
+}
+
 // What an epilogue reads (bias, residual) is requested for a whole batch of column groups, at
 // addresses clamped into the matrix, before the first result is formed: a batch costs one
 // memory round trip, not one per group of four columns.
-template <int TM, int TN, int EPI>
-__device__ __forceinline__ void write_tile(const f32x16 (&acc)[TM][TN], const Epi& e, int mw, int nw, int M, int N) {
-  const int l = threadIdx.x & 63;
-  constexpr int JB = TN > 2 ? 2 : TN;          // tile columns per batch of residual loads
-  u32x2 bias4[TN][4];
+template <typename V, int TM, int TN, int EPI>
+__device__ __forceinline__ void write_tile(const V (&acc)[TM][TN], const Epi& e, int mw, int nw, int M, int N) {
+  constexpr int Q = kQuads<V, TN>, QB = Q < 8 ? Q : 8, IB = 8 / QB < TM ? 8 / QB : TM;   // quads, rows per batch of residual loads
+  static_assert(Q % QB == 0 && TM % IB == 0, "whole batches");
+  u32x2 bias4[Q];
 #pragma unroll
-  for (int j = 0; j < TN; ++j)
-#pragma unroll
-    for (int rg = 0; rg < 4; ++rg) {
-      bias4[j][rg] = u32x2{0u, 0u};
-      if (epi_has_bias(EPI)) {
-        const int n = nw + j * 32 + 8 * rg + 4 * (l >> 5);
-        bias4[j][rg] = *reinterpret_cast<const u32x2*>(e.bias + (n < N ? n : N - 4));
-      }
+  for (int c = 0; c < Q; ++c) {
+    bias4[c] = u32x2{0u, 0u};
+    if (epi_has_bias(EPI)) {
+      const int n = nw + quad_col<V>(c);
+      bias4[c] = *reinterpret_cast<const u32x2*>(e.bias + (n < N ? n : N - 4));
     }
+  }
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int m = mw + i * 32 + (l & 31);
-    const int mc = m < M ? m : M - 1;
+  for (int i0 = 0; i0 < TM; i0 += IB)
 #pragma unroll
-    for (int j0 = 0; j0 < TN; j0 += JB) {
-      f32x4 res[JB][4];
+    for (int c0 = 0; c0 < Q; c0 += QB) {
+      f32x4 res[IB][QB];
 #pragma unroll
-      for (int jj = 0; jj < JB; ++jj)
+      for (int i = 0; i < IB; ++i)
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          res[jj][rg] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < QB; ++c) {
+          res[i][c] = f32x4{0.f, 0.f, 0.f, 0.f};
           if (epi_has_resid(EPI)) {
-            const int n = nw + (j0 + jj) * 32 + 8 * rg + 4 * (l >> 5);
-            res[jj][rg] = *reinterpret_cast<const f32x4*>(e.resid + (int64_t)mc * e.ldr + (n < N ? n : N - 4));
+            const int m = mw + quad_row<V>(i0 + i), n = nw + quad_col<V>(c0 + c);
+            res[i][c] = *reinterpret_cast<const f32x4*>(e.resid + (int64_t)(m < M ? m : M - 1) * e.ldr + (n < N ? n : N - 4));
           }
         }
 #pragma unroll
-      for (int jj = 0; jj < JB; ++jj)
+      for (int i = 0; i < IB; ++i)
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          const int j = j0 + jj;
-          const int n = nw + j * 32 + 8 * rg + 4 * (l >> 5);
+        for (int c = 0; c < QB; ++c) {
+          const int m = mw + quad_row<V>(i0 + i), n = nw + quad_col<V>(c0 + c);
           if (m >= M || n >= N) continue;
-          f32x4 a = {acc[i][j][4 * rg], acc[i][j][4 * rg + 1], acc[i][j][4 * rg + 2], acc[i][j][4 * rg + 3]};
-          epilogue4<EPI>(e, m, n, a, bias4[j][rg], res[jj][rg]);
+          epilogue4<EPI>(e, m, n, quad(acc, i0 + i, c0 + c), bias4[c0 + c], res[i][c]);
         }
     }
-  }
 }
 
 // Workgroup -> tile map (tiles_m > 0; a negative tiles_m selects the natural order).
@@ -221,8 +233,8 @@ __host__ __device__ constexpr bool staged_epi(int epi) {
   return epi == EPI_BF16 || epi == EPI_BF16_BIAS || epi == EPI_BF16_BIAS_GELU || epi == EPI_BF16_DGELU;
 }
 
-template <int BM, int BN, int NT, int TM, int TN, int EPI>
-__device__ __forceinline__ void write_tile_staged(const f32x16 (&acc)[TM][TN], const Epi& e, int m0, int n0,
+template <int BM, int BN, int NT, typename V, int TM, int TN, int EPI>
+__device__ __forceinline__ void write_tile_staged(const V (&acc)[TM][TN], const Epi& e, int m0, int n0,
                                                   int wm0, int wn0, int M, int N, char* smem) {
   constexpr int PITCH = stage_pitch(BN);
   constexpr int PASSES = EPI == EPI_BF16_BIAS_GELU ? 2 : 1;
@@ -255,66 +267,58 @@ __device__ __forceinline__ void write_tile_staged(const f32x16 (&acc)[TM][TN], c
   }
   // GELU' epilogue: column sums of the results over this wave's rows, kept per lane while the tile
   // is packed (the bias gradient of the Linear below the GELU, one partial row per tile row)
-  f32x4 cs[TN][4];
+  constexpr int Q = kQuads<V, TN>;
+  f32x4 cs[Q];
   const bool want_cs = EPI == EPI_BF16_DGELU && e.colpart != nullptr;
   float* red = reinterpret_cast<float*>(smem + BM * PITCH);   // [2 wave rows][BN], behind the image
   if (EPI == EPI_BF16_DGELU) {
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int rg = 0; rg < 4; ++rg) cs[j][rg] = 0.f;
+    for (int c = 0; c < Q; ++c) cs[c] = 0.f;
   }
-  u32x2 bias4[TN][4];                            // this lane's bias values, loaded once
+  u32x2 bias4[Q];                                // this lane's bias values, loaded once
 #pragma unroll
-  for (int j = 0; j < TN; ++j)
-#pragma unroll
-    for (int rg = 0; rg < 4; ++rg) {
-      bias4[j][rg] = u32x2{0u, 0u};
-      if (EPI == EPI_BF16_BIAS || EPI == EPI_BF16_BIAS_GELU) {
-        const int gn = n0 + wn0 + j * 32 + 8 * rg + 4 * (l >> 5);
-        bias4[j][rg] = *reinterpret_cast<const u32x2*>(e.bias + (gn < N ? gn : N - 4));
-      }
+  for (int c = 0; c < Q; ++c) {
+    bias4[c] = u32x2{0u, 0u};
+    if (EPI == EPI_BF16_BIAS || EPI == EPI_BF16_BIAS_GELU) {
+      const int gn = n0 + wn0 + quad_col<V>(c);
+      bias4[c] = *reinterpret_cast<const u32x2*>(e.bias + (gn < N ? gn : N - 4));
     }
+  }
 #pragma unroll
   for (int pass = 0; pass < PASSES; ++pass) {
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      const int ml = wm0 + i * 32 + (l & 31);
+      const int ml = wm0 + quad_row<V>(i);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-#pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          const int nl = wn0 + j * 32 + 8 * rg + 4 * (l >> 5);
-          const int gm = m0 + ml, gn = n0 + nl;
-          f32x4 a = {acc[i][j][4 * rg], acc[i][j][4 * rg + 1], acc[i][j][4 * rg + 2], acc[i][j][4 * rg + 3]};
-          if (EPI == EPI_BF16_BIAS || EPI == EPI_BF16_BIAS_GELU) {
-            add_bias4(a, bias4[j][rg]);
-            if (pass == 1) { a.x = gelu_f(a.x); a.y = gelu_f(a.y); a.z = gelu_f(a.z); a.w = gelu_f(a.w); }
-          }
-          if (EPI == EPI_BF16_DGELU) {
-            if (gm < M && gn < N) {
-              const u32x2 z = *reinterpret_cast<const u32x2*>(smem + ml * PITCH + nl * 2);
-              a.x *= dgelu_f(__uint_as_float(z.x << 16)); a.y *= dgelu_f(__uint_as_float(z.x & 0xFFFF0000u));
-              a.z *= dgelu_f(__uint_as_float(z.y << 16)); a.w *= dgelu_f(__uint_as_float(z.y & 0xFFFF0000u));
-              cs[j][rg] += a;
-            }
-          }
-          u32x2 o; o.x = rv_pack_bf16x2(a.x, a.y); o.y = rv_pack_bf16x2(a.z, a.w);
-          *reinterpret_cast<u32x2*>(smem + ml * PITCH + nl * 2) = o;
+      for (int c = 0; c < Q; ++c) {
+        const int nl = wn0 + quad_col<V>(c);
+        const int gm = m0 + ml, gn = n0 + nl;
+        f32x4 a = quad(acc, i, c);
+        if (EPI == EPI_BF16_BIAS || EPI == EPI_BF16_BIAS_GELU) {
+          add_bias4(a, bias4[c]);
+          if (pass == 1) { a.x = gelu_f(a.x); a.y = gelu_f(a.y); a.z = gelu_f(a.z); a.w = gelu_f(a.w); }
         }
+        if (EPI == EPI_BF16_DGELU) {
+          const u32x2 z = *reinterpret_cast<const u32x2*>(smem + ml * PITCH + nl * 2);
+          a.x *= dgelu_f(__uint_as_float(z.x << 16)); a.y *= dgelu_f(__uint_as_float(z.x & 0xFFFF0000u));
+          a.z *= dgelu_f(__uint_as_float(z.y << 16)); a.w *= dgelu_f(__uint_as_float(z.y & 0xFFFF0000u));
+          const bool ok = gm < M && gn < N;   // (a select and no branch: what is past the end is not summed)
+#pragma unroll
+          for (int k = 0; k < 4; ++k) cs[c][k] += ok ? a[k] : 0.f;
+        }
+        u32x2 o; o.x = rv_pack_bf16x2(a.x, a.y); o.y = rv_pack_bf16x2(a.z, a.w);
+        *reinterpret_cast<u32x2*>(smem + ml * PITCH + nl * 2) = o;
+        if (EPI == EPI_BF16_DGELU && c % 2 == 1) __builtin_amdgcn_sched_barrier(0);   // (all quads' pre-activations at once spill)
       }
     }
     if (EPI == EPI_BF16_DGELU && want_cs) {   // (workgroup-uniform)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int c = 0; c < Q; ++c) {
+        f32x4 v;
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          f32x4 v;
-          v.x = rv_half_wave_sum(cs[j][rg].x); v.y = rv_half_wave_sum(cs[j][rg].y);
-          v.z = rv_half_wave_sum(cs[j][rg].z); v.w = rv_half_wave_sum(cs[j][rg].w);
-          if ((l & 31) == 0)
-            *reinterpret_cast<f32x4*>(red + (wm0 ? BN : 0) + wn0 + j * 32 + 8 * rg + 4 * (l >> 5)) = v;
-        }
+        for (int k = 0; k < 4; ++k) v[k] = kEdge<V> == 32 ? rv_half_wave_sum(cs[c][k]) : rv_row_sum(cs[c][k]);
+        if ((l & (kEdge<V> - 1)) == 0) *reinterpret_cast<f32x4*>(red + (wm0 ? BN : 0) + wn0 + quad_col<V>(c)) = v;
+      }
     }
     __syncthreads();
     if (EPI == EPI_BF16_DGELU && want_cs) {
@@ -351,8 +355,10 @@ __device__ __forceinline__ void write_tile_staged(const f32x16 (&acc)[TM][TN], c
 // index instead; because a lane's LDS slot is fixed, the swizzle is applied to the GLOBAL
 // address a lane fetches.
 //   k-contiguous tile [rows][BK]: physical chunk = c ^ ((row / rows_per_256B) % chunks_per_row)
-//   k-major tile [BK][cols]     : physical chunk = c ^ ((k & 3) << 2)   (64-byte granules); with 64
-//                                 columns, two rows to a 256-byte bank line, c ^ ((k & 2) << 1)
+//   k-major tile [BK][cols]     : half a wave's transposing read takes 32 bytes of rows k .. k + 3 and k + 8 .. k + 11
+//                                 (fragments of 16 rows) or 64 bytes of rows k .. k + 3 (of 32): physical chunk =
+//                                 c ^ ((k & 3) << 2) ^ ((k & 8) >> 2); split forms with 64 columns (fragments of 32 rows),
+//                                 two rows to a 256-byte bank line, c ^ ((k & 2) << 1)
 // NS stages form a ring.  Plain form (four-wave tiles): the loads of tile t+NS-1 are issued
 // right after the barrier that opens tile t.  Pipelined form (the eight-wave 256x256 tile): see
 // gemm_dtl_body - the products are bound by how fast operand tiles arrive, inside a stage step
@@ -361,7 +367,7 @@ __device__ __forceinline__ void write_tile_staged(const f32x16 (&acc)[TM][TN], c
 __host__ __device__ constexpr int dtl_tile_bytes(int rows, int bk) { return rows * bk * 2; }
 
 template <int ROWS>
-__device__ __forceinline__ int km_swizzle(int k) { return ROWS == 64 ? (k & 2) << 1 : (k & 3) << 2; }
+__device__ __forceinline__ int km_swizzle(int k) { return ROWS == 64 ? (k & 2) << 1 : ((k & 3) << 2) ^ ((k & 8) >> 2); }
 
 template <bool KM, int ROWS, int BK, int NW>
 struct Dtl {
@@ -410,8 +416,39 @@ __device__ __forceinline__ void dtl_issue(const Dtl<KM, ROWS, BK, NW>& s, const 
   }
 }
 
+// rows kr .. + 3 and kr + 4 .. + 7 of a k-major tile, transposed: a lane gets eight consecutive k of one column
+template <int ROWS>
+__device__ __forceinline__ bf16x8 dtl_read_tr(const char* lds, int kr, int col) {
+  const int c = (col >> 3) ^ km_swizzle<ROWS>(kr);
+  const char* p = lds + kr * (ROWS * 2) + c * 16 + (col & 7) * 2;
+  s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p));
+  s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (s16x4 __attribute__((address_space(3)))*)(p + 4 * (ROWS * 2)));
+  s16x8 r = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  return __builtin_bit_cast(bf16x8, r);
+}
+
+// Fragment of one v_mfma_f32_16x16x32_bf16 (the pipelined 256x256 tile): rows row0 .. + 15, k-step kk of 32.  Lane l holds row l % 16, k = 8 (l / 16) .. + 7.
 template <bool KM, int ROWS, int BK>
 __device__ __forceinline__ bf16x8 dtl_frag(const char* lds, int row0, int kk) {
+  const int l = threadIdx.x & 63;
+  if (!KM) {
+    constexpr int CPR = BK / 8, R256 = 256 / (BK * 2);
+    const int row = row0 + (l & 15);
+    const int c = (kk * 4 + (l >> 4)) ^ ((row / R256) % CPR);
+    return *reinterpret_cast<const bf16x8*>(lds + row * (BK * 2) + c * 16);
+  } else {
+    static_assert(!KM || ROWS > 64, "the swizzle of narrower tiles is that of 32-row fragments");
+    const int q = l >> 4, i = l & 15;
+    const int kr = kk * 32 + 8 * q + (i >> 2);
+    const int col = row0 + 4 * (i & 3);
+    return dtl_read_tr<ROWS>(lds, kr, col);
+  }
+}
+
+// Fragment of one v_mfma_f32_32x32x16_bf16: rows row0 .. + 31, k-step kk of 16.  Lane l holds row l % 32, k = 8 (l / 32) .. + 7.
+template <bool KM, int ROWS, int BK>
+__device__ __forceinline__ bf16x8 dtl_frag32(const char* lds, int row0, int kk) {
   const int l = threadIdx.x & 63;
   if (!KM) {
     constexpr int CPR = BK / 8, R256 = 256 / (BK * 2);
@@ -422,13 +459,7 @@ __device__ __forceinline__ bf16x8 dtl_frag(const char* lds, int row0, int kk) {
     const int q = l >> 4, i = l & 15;
     const int kr = kk * 16 + 8 * (q >> 1) + (i >> 2);
     const int col = row0 + 16 * (q & 1) + 4 * (i & 3);
-    const int c = (col >> 3) ^ km_swizzle<ROWS>(kr);
-    const char* p = lds + kr * (ROWS * 2) + c * 16 + (col & 7) * 2;
-    s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p));
-    s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (s16x4 __attribute__((address_space(3)))*)(p + 4 * (ROWS * 2)));
-    s16x8 r = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8, r);
+    return dtl_read_tr<ROWS>(lds, kr, col);
   }
 }
 
@@ -460,8 +491,8 @@ __host__ __device__ constexpr int upd_image_bytes(int bm, int bn) { return (bm /
 //         more L2 requests than a short product's whole main loop.
 // The results go back into the LDS rows they came from and leave the way the rows came in: whole rows, 16 bytes
 // per lane, one 128-byte line per 8 lanes, instead of 32-byte pieces of 32 different rows per store instruction.
-template <int BM, int BN, int NW, int TM, int TN, int MODE, bool BF16OUT>
-__device__ __forceinline__ void f32_tile_through_lds(const f32x16 (&acc)[TM][TN], const Epi& e, int m0, int n0,
+template <int BM, int BN, int NW, typename V, int TM, int TN, int MODE, bool BF16OUT>
+__device__ __forceinline__ void f32_tile_through_lds(const V (&acc)[TM][TN], const Epi& e, int m0, int n0,
                                                      int wm0, int wn0, int M, int N, char* smem) {
   static_assert(BN == 256, "one direct-to-LDS instruction moves one 256-column fp32 row");
   constexpr int HALF = BM / 2, PITCH = BN * 4 + 16, RPW = HALF / NW;   // rows per wave in the row-wise phases
@@ -470,17 +501,16 @@ __device__ __forceinline__ void f32_tile_through_lds(const f32x16 (&acc)[TM][TN]
   const float* srcm = MODE == 0 ? e.upd_w : e.resid;
   const int64_t lds_src = MODE == 0 ? e.ldo : e.ldr;
   float* dst32 = MODE == 0 ? e.upd_w : (float*)e.out;
-  u32x2 bias4[TN][4];
+  constexpr int Q = kQuads<V, TN>;
+  u32x2 bias4[Q];
 #pragma unroll
-  for (int j = 0; j < TN; ++j)
-#pragma unroll
-    for (int rg = 0; rg < 4; ++rg) {
-      bias4[j][rg] = u32x2{0u, 0u};
-      if (MODE == 1) {
-        const int n = n0 + wn0 + j * 32 + 8 * rg + 4 * (l >> 5);
-        bias4[j][rg] = *reinterpret_cast<const u32x2*>(e.bias + (n < N ? n : N - 4));
-      }
+  for (int c = 0; c < Q; ++c) {
+    bias4[c] = u32x2{0u, 0u};
+    if (MODE == 1) {
+      const int n = n0 + wn0 + quad_col<V>(c);
+      bias4[c] = *reinterpret_cast<const u32x2*>(e.bias + (n < N ? n : N - 4));
     }
+  }
   int gn = n0 + l * 4;
   const bool col_ok = gn < N;
   gn = col_ok ? gn : N - 4;                    // ragged tiles fetch valid memory and ignore it below
@@ -502,28 +532,25 @@ __device__ __forceinline__ void f32_tile_through_lds(const f32x16 (&acc)[TM][TN]
     if (wm0 == h * HALF) {
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        const int ml = i * 32 + (l & 31);
+        const int ml = quad_row<V>(i);
         const int gm = m0 + wm0 + ml;
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-#pragma unroll
-          for (int rg = 0; rg < 4; ++rg) {
-            const int nl = wn0 + j * 32 + 8 * rg + 4 * (l >> 5);
-            f32x4* p = reinterpret_cast<f32x4*>(smem + ml * PITCH + nl * 4);
-            const f32x4 w = *p;
-            f32x4 a = {acc[i][j][4 * rg], acc[i][j][4 * rg + 1], acc[i][j][4 * rg + 2], acc[i][j][4 * rg + 3]};
-            f32x4 r;
-            if (MODE == 0) {
-              r.x = __fmaf_rn(-e.eta, a.x, w.x); r.y = __fmaf_rn(-e.eta, a.y, w.y);
-              r.z = __fmaf_rn(-e.eta, a.z, w.z); r.w = __fmaf_rn(-e.eta, a.w, w.w);
-              if (e.out && gm < M && n0 + nl < N)
-                *reinterpret_cast<f32x4*>((float*)e.out + (int64_t)gm * e.ldo + n0 + nl) = a;
-            } else {
-              add_bias4(a, bias4[j][rg]);
-              r = a + w;
-            }
-            *p = r;
+        for (int c = 0; c < Q; ++c) {
+          const int nl = wn0 + quad_col<V>(c);
+          f32x4* p = reinterpret_cast<f32x4*>(smem + ml * PITCH + nl * 4);
+          const f32x4 w = *p;
+          f32x4 a = quad(acc, i, c);
+          f32x4 r;
+          if (MODE == 0) {
+            r.x = __fmaf_rn(-e.eta, a.x, w.x); r.y = __fmaf_rn(-e.eta, a.y, w.y);
+            r.z = __fmaf_rn(-e.eta, a.z, w.z); r.w = __fmaf_rn(-e.eta, a.w, w.w);
+            if (e.out && gm < M && n0 + nl < N)
+              *reinterpret_cast<f32x4*>((float*)e.out + (int64_t)gm * e.ldo + n0 + nl) = a;
+          } else {
+            add_bias4(a, bias4[c]);
+            r = a + w;
           }
+          *p = r;
         }
       }
     }
@@ -553,13 +580,16 @@ template <int BM, int BN, int BK, int NS, int NW, bool AKM, bool BKM, int EPI>
 __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, int64_t lda, int64_t a_bs,
                                               const uint16_t* __restrict__ B, int64_t ldb, int64_t b_bs, int M, int N,
                                               int K, int bm, int bn, const Epi& e) {
+  // The eight-wave 256x256 tile runs the pipelined ring below, on products of 16x16: with those the matrix cores do 1717
+  // TFLOP/s out of LDS at the board's power cap, with 32x32 ones 1586 (registers alone 2028 / 1807; half the accumulator
+  // traffic per flop).  The four-wave tiles keep the plain ring (loads of tile t+NS-1 right after the barrier that
+  // opens tile t) and 32x32, of which they need half as many instructions: 4096x1024x4096 on 128x128 tiles 43.7 against 46.0 us.
+  constexpr bool PIPELINED = NW == 8 && BM == 256 && BN == 256;
+  typedef std::conditional_t<PIPELINED, f32x4, f32x16> V;
   // NW waves laid out 2 (m) x NW/2 (n)
-  constexpr int WM = BM / 2, WN = BN / (NW / 2), TM = WM / 32, TN = WN / 32, KSTEPS = BK / 16;
+  constexpr int WM = BM / 2, WN = BN / (NW / 2), TM = WM / kEdge<V>, TN = WN / kEdge<V>, KSTEPS = PIPELINED ? BK / 32 : BK / 16;
   constexpr int A_BYTES = dtl_tile_bytes(BM, BK), B_BYTES = dtl_tile_bytes(BN, BK);
   constexpr int BUF = A_BYTES + B_BYTES;
-  // The eight-wave 256x256 tile runs the pipelined ring below; the four-wave tiles keep the
-  // plain ring (loads of tile t+NS-1 right after the barrier that opens tile t).
-  constexpr bool PIPELINED = NW == 8 && BM == 256 && BN == 256;
   constexpr int NL = NW;                                                    // loader waves per tile
   constexpr int LPT = Dtl<AKM, BM, BK, NL>::N + Dtl<BKM, BN, BK, NL>::N;   // loads per lane per tile
   static_assert(LPT * (NS - 2) < 64, "vmcnt range");
@@ -569,13 +599,11 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
   const int wave = threadIdx.x >> 6;
   const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
 
-  f32x16 acc[TM][TN];
+  V acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int j = 0; j < TN; ++j) acc[i][j] = 0.f;
 
   const int lw = wave;                 // this wave's share of a tile's loads
   Dtl<AKM, BM, BK, NL> da;
@@ -584,15 +612,16 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
   dtl_init<BKM, BN, BK, NL>(db, ldb, b_bs, n0, N, lw);
   const int nk = K / BK;
   if constexpr (PIPELINED) {
-    // Ring of NS slots, the slot hand-over INSIDE a k-tile.  Before the last k-step of tile s
-    // (its fragments are already in registers) the workgroup meets once: tile s+1 has landed
-    // and nobody reads tile s's slot any more.  Behind that barrier the first fragments of tile
-    // s+1 are read and the loads of tile s+NS go into the slot just left, one behind every
-    // few MFMAs of the last k-step - so NS-1 tiles are in flight while one is being used, and
-    // the matrix core does not wait at a tile boundary.
+    // Ring of NS slots, the slot hand-over INSIDE a k-tile.  A tile is one step of 32 in k, multiplied in two halves: the upper
+    // TM / 2 rows of fragments, column by column, then the lower ones.  Between the halves (all fragments of the tile are
+    // in registers) the workgroup meets once: tile s+1 has landed and nobody reads tile s's slot any more.  Behind
+    // that barrier, among the multiplications of the lower half, the upper fragments of tile s+1 are read, each column's B fragment
+    // as soon as its last multiplication is out (no second set of registers), and the loads of tile s+NS go into
+    // the slot just left - so NS-1 tiles are in flight while one is being used, and the matrix core does not wait at a
+    // tile boundary.
     constexpr int NA = Dtl<AKM, BM, BK, NL>::N, NB = Dtl<BKM, BN, BK, NL>::N, LPS = NA + NB;
-    constexpr int STRIDE = (TM * TN) / LPS;            // MFMAs per load in the last k-step
-    static_assert(STRIDE >= 1 && STRIDE * LPS == TM * TN, "loads are dealt out evenly behind the MFMAs of the last k-step");
+    constexpr int HM = TM / 2, STRIDE = HM * TN / LPS; // MFMAs per load in the lower half
+    static_assert(KSTEPS == 1 && TM % 2 == 0 && STRIDE >= 1 && STRIDE * LPS == HM * TN, "loads are dealt out evenly behind the MFMAs of the lower half");
     static_assert((NS - 1) * LPS < 64, "vmcnt range");
     unsigned oa[NA], ob[NB];               // per-lane byte offsets of this wave's loads inside a tile
 #pragma unroll
@@ -644,93 +673,68 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
         slot = slot + 1 == NS ? 0 : slot + 1;
       }
     } else {
-    bf16x8 fa[2][TM], fb[2][TN];
+    bf16x8 fa[TM], fb[TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) fa[0][i] = dtl_frag<AKM, BM, BK>(smem, wm0 + i * 32, 0);
+    for (int i = 0; i < HM; ++i) fa[i] = dtl_frag<AKM, BM, BK>(smem, wm0 + i * 16, 0);
 #pragma unroll
-    for (int j = 0; j < TN; ++j) fb[0][j] = dtl_frag<BKM, BN, BK>(smem + A_BYTES, wn0 + j * 32, 0);
-    // k-steps 0 .. KSTEPS-2 of the tile in `cur` (fragments of k-step 0 already in fa[0], fb[0])
-    auto head_steps = [&](const char* curA, const char* curB) {
+    for (int j = 0; j < TN; ++j) fb[j] = dtl_frag<BKM, BN, BK>(smem + A_BYTES, wn0 + j * 16, 0);
+    // the upper half of the tile at `cur`, and the reads of its lower fragments, one behind each of the first MFMAs
+    auto upper_half = [&](const char* cur) {
 #pragma unroll
-      for (int kk = 0; kk + 1 < KSTEPS; ++kk) {
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int i = 0; i < TM; ++i) fa[(kk + 1) & 1][i] = dtl_frag<AKM, BM, BK>(curA, wm0 + i * 32, kk + 1);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) fb[(kk + 1) & 1][j] = dtl_frag<BKM, BN, BK>(curB, wn0 + j * 32, kk + 1);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kk & 1][j], fa[kk & 1][i], acc[i][j], 0, 0, 0);
-        constexpr int NREAD = (AKM ? 2 : 1) * TM + (BKM ? 2 : 1) * TN;
-        constexpr int NMFMA = TM * TN;
-        constexpr int PER = NMFMA / NREAD > 0 ? NMFMA / NREAD : 1;
-#pragma unroll
-        for (int g = 0; g < NREAD; ++g) {
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, PER, 0);
-        }
-      }
-    };
-    auto next_frags = [&](const char* nxtA) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i) fa[0][i] = dtl_frag<AKM, BM, BK>(nxtA, wm0 + i * 32, 0);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) fb[0][j] = dtl_frag<BKM, BN, BK>(nxtA + A_BYTES, wn0 + j * 32, 0);
-    };
-    static_assert((KSTEPS & 1) == 0, "the next tile's first fragments go to buffer 0");
-    constexpr int L = (KSTEPS - 1) & 1;      // the last k-step's fragments are in fa[L], fb[L]
-    int slot = 0;                            // ring slot of tile s
-    int s = 0;
-    for (; s + NS < nk; ++s) {               // passes that still have a tile s+NS to fetch
-      const char* curA = smem + slot * BUF;
-      const int nslot = slot + 1 == NS ? 0 : slot + 1;
-      head_steps(curA, curA + A_BYTES);
-      RV_WAIT_VMCNT((NS - 2) * LPS);         // tile s+1 (tiles s+2 .. s+NS-1 may still fly)
-      __syncthreads();                       // all of tile s+1 is in LDS; all fragment reads of tile s are done
-      next_frags(smem + nslot * BUF);
-      const int lb = __builtin_amdgcn_readfirstlane((int)(size_t)(smem + slot * BUF) + lw * 1024);
-      const uint16_t* pa = baseA(s + NS);
-      const uint16_t* pb = baseB(s + NS);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int m = i * TN + j;
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[L][j], fa[L][i], acc[i][j], 0, 0, 0);
-          if (m % STRIDE == 0) {
-            const int q = m / STRIDE;
+        for (int i = 0; i < HM; ++i) {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+          if (j == 0) {
             __builtin_amdgcn_sched_barrier(0);
-            if (q < NA) dtl_load_s(pa, oa[q], lb + q * NL * 1024);
-            else dtl_load_s(pb, ob[q - NA], lb + A_BYTES + (q - NA) * NL * 1024);
+            fa[HM + i] = dtl_frag<AKM, BM, BK>(cur, wm0 + (HM + i) * 16, 0);
             __builtin_amdgcn_sched_barrier(0);
           }
         }
+    };
+    // the lower half; with `nxt` the first fragments of the tile there, with `pa` the loads of a tile into the block at `lb`
+    auto lower_half = [&](auto has_next, const char* nxt, auto has_load, const uint16_t* pa, const uint16_t* pb, int lb) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+#pragma unroll
+        for (int i = 0; i < HM; ++i) {
+          acc[HM + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[HM + i], acc[HM + i][j], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          if (has_next && j == 0) fa[i] = dtl_frag<AKM, BM, BK>(nxt, wm0 + i * 16, 0);
+          const int m = j * HM + i;
+          if (has_load && m % STRIDE == STRIDE - 1) {
+            const int q = m / STRIDE;
+            if (q < NA) dtl_load_s(pa, oa[q], lb + q * NL * 1024);
+            else dtl_load_s(pb, ob[q - NA], lb + A_BYTES + (q - NA) * NL * 1024);
+          }
+          if (has_next && i == HM - 1) fb[j] = dtl_frag<BKM, BN, BK>(nxt + A_BYTES, wn0 + j * 16, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    };
+    constexpr std::true_type yes;
+    constexpr std::false_type no;
+    int slot = 0;                            // ring slot of tile s
+    int s = 0;
+    for (; s + NS < nk; ++s) {               // passes that still have a tile s+NS to fetch
+      const int nslot = slot + 1 == NS ? 0 : slot + 1;
+      upper_half(smem + slot * BUF);
+      RV_WAIT_VMCNT((NS - 2) * LPS);         // tile s+1 (tiles s+2 .. s+NS-1 may still fly)
+      __syncthreads();                       // all of tile s+1 is in LDS; all fragment reads of tile s are done
+      const int lb = __builtin_amdgcn_readfirstlane((int)(size_t)(smem + slot * BUF) + lw * 1024);
+      lower_half(yes, smem + nslot * BUF, yes, baseA(s + NS), baseB(s + NS), lb);
       slot = nslot;
     }
     for (; s + 1 < nk; ++s) {                // the last NS-1 hand-overs: nothing left to fetch
-      const char* curA = smem + slot * BUF;
       const int nslot = slot + 1 == NS ? 0 : slot + 1;
-      head_steps(curA, curA + A_BYTES);
+      upper_half(smem + slot * BUF);
       wait_tiles(nk - 2 - s);                // tiles s+2 .. nk-1 may still fly
       __syncthreads();
-      next_frags(smem + nslot * BUF);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[L][j], fa[L][i], acc[i][j], 0, 0, 0);
+      lower_half(yes, smem + nslot * BUF, no, nullptr, nullptr, 0);
       slot = nslot;
     }
-    {
-      const char* curA = smem + slot * BUF;
-      head_steps(curA, curA + A_BYTES);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[L][j], fa[L][i], acc[i][j], 0, 0, 0);
-    }
+    upper_half(smem + slot * BUF);
+    lower_half(no, nullptr, no, nullptr, nullptr, 0);
     }
   } else {
 #pragma unroll
@@ -756,16 +760,16 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
       const char* curB = curA + A_BYTES;
       bf16x8 fa[2][TM], fb[2][TN];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) fa[0][i] = dtl_frag<AKM, BM, BK>(curA, wm0 + i * 32, 0);
+      for (int i = 0; i < TM; ++i) fa[0][i] = dtl_frag32<AKM, BM, BK>(curA, wm0 + i * 32, 0);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) fb[0][j] = dtl_frag<BKM, BN, BK>(curB, wn0 + j * 32, 0);
+      for (int j = 0; j < TN; ++j) fb[0][j] = dtl_frag32<BKM, BN, BK>(curB, wn0 + j * 32, 0);
 #pragma unroll
       for (int kk = 0; kk < KSTEPS; ++kk) {
         if (kk + 1 < KSTEPS) {
 #pragma unroll
-          for (int i = 0; i < TM; ++i) fa[(kk + 1) & 1][i] = dtl_frag<AKM, BM, BK>(curA, wm0 + i * 32, kk + 1);
+          for (int i = 0; i < TM; ++i) fa[(kk + 1) & 1][i] = dtl_frag32<AKM, BM, BK>(curA, wm0 + i * 32, kk + 1);
 #pragma unroll
-          for (int j = 0; j < TN; ++j) fb[(kk + 1) & 1][j] = dtl_frag<BKM, BN, BK>(curB, wn0 + j * 32, kk + 1);
+          for (int j = 0; j < TN; ++j) fb[(kk + 1) & 1][j] = dtl_frag32<BKM, BN, BK>(curB, wn0 + j * 32, kk + 1);
         }
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -788,14 +792,14 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
     }
   }
   if constexpr (staged_epi(EPI)) {
-    write_tile_staged<BM, BN, 64 * NW, TM, TN, EPI>(acc, e, m0, n0, wm0, wn0, M, N, smem);
+    write_tile_staged<BM, BN, 64 * NW, V, TM, TN, EPI>(acc, e, m0, n0, wm0, wn0, M, N, smem);
   } else if constexpr (EPI == EPI_F32_UPD) {
-    if (e.upd_w) f32_tile_through_lds<BM, BN, NW, TM, TN, 0, true>(acc, e, m0, n0, wm0, wn0, M, N, smem);   // workgroup-uniform
-    else write_tile<TM, TN, EPI>(acc, e, m0 + wm0, n0 + wn0, M, N);
+    if (e.upd_w) f32_tile_through_lds<BM, BN, NW, V, TM, TN, 0, true>(acc, e, m0, n0, wm0, wn0, M, N, smem);   // workgroup-uniform
+    else write_tile<V, TM, TN, EPI>(acc, e, m0 + wm0, n0 + wn0, M, N);
   } else if constexpr (epi_has_resid(EPI) && PIPELINED && RV_RESID_LDS) {
-    f32_tile_through_lds<BM, BN, NW, TM, TN, 1, EPI == EPI_F32_BIAS_RESID_BF16>(acc, e, m0, n0, wm0, wn0, M, N, smem);
+    f32_tile_through_lds<BM, BN, NW, V, TM, TN, 1, EPI == EPI_F32_BIAS_RESID_BF16>(acc, e, m0, n0, wm0, wn0, M, N, smem);
   } else {
-    write_tile<TM, TN, EPI>(acc, e, m0 + wm0, n0 + wn0, M, N);
+    write_tile<V, TM, TN, EPI>(acc, e, m0 + wm0, n0 + wn0, M, N);
   }
 }
 
@@ -863,9 +867,7 @@ __device__ __forceinline__ void gemm_split_body(const uint16_t* __restrict__ A, 
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int j = 0; j < TN; ++j) acc[i][j] = 0.f;
 
   Dtl<AKM, BM, BK, NW> da;
   Dtl<BKM, BN, BK, NW> db;
@@ -923,9 +925,9 @@ __device__ __forceinline__ void gemm_split_body(const uint16_t* __restrict__ A, 
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
-        for (int a = 0; a < TM; ++a) fa[kk][a] = dtl_frag<AKM, BM, BK>(curA, wm0 + a * 32, kk);
+        for (int a = 0; a < TM; ++a) fa[kk][a] = dtl_frag32<AKM, BM, BK>(curA, wm0 + a * 32, kk);
 #pragma unroll
-        for (int b = 0; b < TN; ++b) fb[kk][b] = dtl_frag<BKM, BN, BK>(curB, wn0 + b * 32, kk);
+        for (int b = 0; b < TN; ++b) fb[kk][b] = dtl_frag32<BKM, BN, BK>(curB, wn0 + b * 32, kk);
       }
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk)
@@ -940,11 +942,8 @@ __device__ __forceinline__ void gemm_split_body(const uint16_t* __restrict__ A, 
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int rg = 0; rg < 4; ++rg)
-        *reinterpret_cast<f32x4*>(image + (group * BM + wm0 + i * 32 + (l & 31)) * PITCH + wn0 + j * 32 + 8 * rg + 4 * (l >> 5)) =
-            f32x4{acc[i][j][4 * rg], acc[i][j][4 * rg + 1], acc[i][j][4 * rg + 2], acc[i][j][4 * rg + 3]};
+    for (int c = 0; c < 4 * TN; ++c)
+      *reinterpret_cast<f32x4*>(image + (group * BM + wm0 + quad_row<f32x16>(i)) * PITCH + wn0 + quad_col<f32x16>(c)) = quad(acc, i, c);
   __syncthreads();
 #pragma unroll
   for (int p = 0; p < PIECES; ++p) {
