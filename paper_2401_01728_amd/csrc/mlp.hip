@@ -4,16 +4,16 @@
 // Stash per microbatch: the input of every Linear (a_0 .. a_{n-1}).  Because a_{i+1} =
 // ReLU(z_i), "a_{i+1} > 0" is the ReLU gate of layer i, so pre-activations are not kept.
 //
-// Every product runs on the fp32 matrix instructions (v_mfma_f32_32x32x2_f32 and
-// v_mfma_f32_16x16x4_f32: full fp32 products and sums at twice the rate of plain vector FMAs,
-// which may not be packed here), in a fixed order (deterministic).  Four forms:
+// Every product has fp32 precision and a fixed order of additions (deterministic).  It runs on the fp32 matrix instructions
+// (v_mfma_f32_32x32x2_f32 and v_mfma_f32_16x16x4_f32: full fp32 products and sums at twice the rate of plain vector FMAs,
+// which may not be packed here), the large ones on the bf16 instructions with each operand in three pieces.  Four forms:
 //   tiny   a whole forward, or a whole backward with its update, in ONE launch: workgroups
 //          repeat the small chain of activations (or of gradients) each for itself in LDS and
 //          share out the results, so that no layer waits for a launch of its own;
 //   split  a 32x32 result tile per workgroup, the contraction dealt out over its four or eight waves,
 //          operands straight from memory to registers;
 //   wave   a 32x32 result tile per wave, for thin results of short contractions;
-//   tiled  LDS tiles of 128x128 or 64x64 results, 32 deep, double buffered.
+//   tiled  LDS tiles of 128x128 or 64x64 results, the operands in three bf16 planes.
 // In all but the tiny form one launch per layer and direction: the forward product; or the input
 // gradient, the weight gradient with the update in its epilogue, and the bias gradient together
 // (they read the same gradient and do not depend on one another).
@@ -27,6 +27,10 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef f32x4 f32x4_u __attribute__((aligned(4)));   // four floats at any float's address
 
 template <int V> struct Int { static constexpr int value = V; };   // a constant as an argument
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void each(F f) {                // f(0), .. f(N - 1)
+  if constexpr (I < N) { f(Int<I>()); each<N, I + 1>(f); }
+}
 
 constexpr int kTinyLayers = 4, kTinyRows = 64;
 
@@ -142,11 +146,10 @@ __device__ __forceinline__ void finish(const Out& o, const int (&m)[R], int n, i
 }
 
 // ---- tiled ---------------------------------------------------------------------------------
-// LDS keeps an operand the way memory has it: k-contiguous rows of 32 (pitch 36 floats: sixteen
-// rows of 16-byte reads fall on all 64 banks), k-major rows of the tile's width (pitch + 8: rows
-// k and k + 4, read together, are 32 banks apart).  A lane takes k = 8 g + 4 (lane / 32) + e,
-// e = 0..3, for the four matrix instructions of group g: one 16-byte read of a k-contiguous tile,
-// four 4-byte reads of a k-major one (transposing it on the way into LDS instead measured 3 - 8 % slower).
+// The fp32 walk, for the tiles that three planes do not do for.  LDS keeps an operand the way memory has it: k-contiguous rows of
+// 32 (pitch 36 floats: sixteen rows of 16-byte reads fall on all 64 banks), k-major rows of the tile's width (pitch + 8:
+// rows k and k + 4, read together, are 32 banks apart).  A lane takes k = 8 g + 4 (lane / 32) + e, e = 0..3, for the four
+// matrix instructions of group g: one 16-byte read of a k-contiguous tile, four 4-byte reads of a k-major one.
 constexpr int BK = 32;
 template <bool KM, int ROWS> struct Lds {
   static constexpr int PITCH = KM ? ROWS + 8 : BK + 4;
@@ -154,26 +157,20 @@ template <bool KM, int ROWS> struct Lds {
   static constexpr int PIECES = ROWS * BK / 4 / 256;       // 16-byte pieces per thread and tile
 };
 
-// A thread's share of a tile.  INSIDE: the whole tile lies in the matrix - one load per piece at a
-// lane offset from a uniform base.  Otherwise element by element at clamped indexes, and what lies
-// past the end of k is zeroed when the piece is parked (results of rows past the other end are not
-// stored).
-template <bool INSIDE, bool KM, int ROWS>
+// A thread's share of a tile D deep, element by element at clamped indexes: what lies past the end of k is zeroed when the piece
+// is parked (results of rows past the other end are not stored).
+template <bool KM, int ROWS, int D>
 __device__ __forceinline__ void tile_load(f32x4* v, const float* __restrict__ g, int ld, int r0, int rows, int k0, int K) {
   const float* base = KM ? g + (int64_t)k0 * ld + r0 : g + (int64_t)r0 * ld + k0;
 #pragma unroll
-  for (int i = 0; i < Lds<KM, ROWS>::PIECES; ++i) {
+  for (int i = 0; i < ROWS * D / 4 / 256; ++i) {
     const int p = threadIdx.x % 256 + 256 * i;
-    const int k = KM ? p / (ROWS / 4) : p % (BK / 4) * 4, r = KM ? p % (ROWS / 4) * 4 : p / (BK / 4);
-    if (INSIDE) {
-      v[i] = *reinterpret_cast<const f32x4_u*>(base + (unsigned)(KM ? k * ld + r : r * ld + k));
-    } else {
+    const int k = KM ? p / (ROWS / 4) : p % (D / 4) * 4, r = KM ? p % (ROWS / 4) * 4 : p / (D / 4);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        int ke = KM ? k : k + e, re = KM ? r + e : r;
-        ke = k0 + ke < K ? ke : K - 1 - k0; re = r0 + re < rows ? re : rows - 1 - r0;
-        v[i][e] = base[KM ? (int64_t)ke * ld + re : (int64_t)re * ld + ke];
-      }
+    for (int e = 0; e < 4; ++e) {
+      int ke = KM ? k : k + e, re = KM ? r + e : r;
+      ke = k0 + ke < K ? ke : K - 1 - k0; re = r0 + re < rows ? re : rows - 1 - r0;
+      v[i][e] = base[KM ? (int64_t)ke * ld + re : (int64_t)re * ld + ke];
     }
   }
 }
@@ -199,99 +196,322 @@ __device__ __forceinline__ f32x4 tile_frag(const float* s, int row0, int g) {
   return f32x4{s[k * P + row], s[(k + 1) * P + row], s[(k + 2) * P + row], s[(k + 3) * P + row]};
 }
 
-// A workgroup of 512 threads takes two tiles, side by side: both have the same number of steps and so of barriers; the last
-// one's second tile may be past the end (it walks along on the last tile and keeps nothing).
-template <int BT, bool AKM, bool BKM, int OP>
-__device__ __forceinline__ void tiled_body(const Prod& p, const Out& o, int tile, float* smem) {
-  constexpr int W = BT / 2, T = W / 32;                    // four waves, 2 x 2, each W x W
-  constexpr int AF = Lds<AKM, BT>::FLOATS, BUF = AF + Lds<BKM, BT>::FLOATS;
-  const int all = (p.M + BT - 1) / BT * p.tiles_n;
-  const bool live = tile < all;        // (uniform in 256 threads)
-  tile = live ? tile : all - 1;
-  const int m0 = tile / p.tiles_n * BT, n0 = tile % p.tiles_n * BT;
-  const int wave = threadIdx.x % 256 >> 6, l = threadIdx.x & 63;
-  const int wm = (wave & 1) * W, wn = (wave >> 1) * W;
-  f32x16 acc[T][T];
+// A tile of BT x BT results is formed by four waves, 2 x 2, in products of 32x32.  Walks along K: on the bf16 matrix
+// instructions (planes_walk), and where that does not do on the fp32 ones.
+template <int BT> constexpr int kTileEdge = BT / 64;      // products to a wave's side
+template <int BT> using TileAcc = f32x16[kTileEdge<BT>][kTileEdge<BT>];
+
+template <int BT, bool AKM, bool BKM>
+__device__ __forceinline__ void fp32_walk(TileAcc<BT>& acc, const Prod& p, int m0, int n0, float* s) {
+  constexpr int T = kTileEdge<BT>, AF = Lds<AKM, BT>::FLOATS;
+  const int wave = threadIdx.x % 256 >> 6, wm = (wave & 1) * 32 * T, wn = (wave >> 1) * 32 * T;
 #pragma unroll
   for (int i = 0; i < T; ++i)
 #pragma unroll
-    for (int j = 0; j < T; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  f32x4 va[Lds<AKM, BT>::PIECES], vb[Lds<BKM, BT>::PIECES];
-  const bool inside = m0 + BT <= p.M && n0 + BT <= p.N;
-  auto fetch = [&](int k0) {
-    if (inside && k0 + BK <= p.K) {                        // (uniform)
-      tile_load<true, AKM, BT>(va, p.A, p.lda, m0, p.M, k0, p.K);
-      tile_load<true, BKM, BT>(vb, p.B, p.ldb, n0, p.N, k0, p.K);
-    } else {
-      tile_load<false, AKM, BT>(va, p.A, p.lda, m0, p.M, k0, p.K);
-      tile_load<false, BKM, BT>(vb, p.B, p.ldb, n0, p.N, k0, p.K);
-    }
-  };
-  auto park = [&](float* s, int k0) { tile_park<AKM, BT>(va, s, p.K - k0); tile_park<BKM, BT>(vb, s + AF, p.K - k0); };
-  // While tile t is used, tile t + 1 is parked (group 1) and tile t + 2 requested (group 2): a load has
-  // nearly a whole tile's products to arrive in, and the barrier at the tile's end finds the writes done.
-  // With one or two waves per SIMD whatever is not issued in the shadow of a matrix instruction leaves
-  // the matrix core idle, so tiles with whole successors run without branches and every other
-  // instruction is dealt out behind the products.
-  const int nk = (p.K + BK - 1) / BK;
-  fetch(0);
-  park(smem, 0);
-  if (nk > 1) fetch(BK);
-  __syncthreads();
-  auto step = [&](int t, auto whole) {
-    constexpr bool WHOLE = decltype(whole)::value != 0;
-    const float* sa = smem + (t & 1) * BUF;
-    const float* sb = sa + AF;
-    f32x4 fa[2][T], fb[2][T];                              // fragments of group g + 1 are read behind the products of group g
-    auto frags = [&](int g) {
-#pragma unroll
-      for (int i = 0; i < T; ++i) fa[g & 1][i] = tile_frag<AKM, BT>(sa, wm + i * 32, g);
-#pragma unroll
-      for (int j = 0; j < T; ++j) fb[g & 1][j] = tile_frag<BKM, BT>(sb, wn + j * 32, g);
-    };
-    frags(0);
+    for (int j = 0; j < T; ++j) acc[i][j] = 0.f;
+  for (int k0 = 0; k0 < p.K; k0 += BK) {
+    f32x4 va[Lds<AKM, BT>::PIECES], vb[Lds<BKM, BT>::PIECES];
+    tile_load<AKM, BT, BK>(va, p.A, p.lda, m0, p.M, k0, p.K);
+    tile_load<BKM, BT, BK>(vb, p.B, p.ldb, n0, p.N, k0, p.K);
+    __syncthreads();
+    tile_park<AKM, BT>(va, s, p.K - k0);
+    tile_park<BKM, BT>(vb, s + AF, p.K - k0);
+    __syncthreads();
 #pragma unroll
     for (int g = 0; g < BK / 8; ++g) {
-      if (g + 1 < BK / 8) frags(g + 1);
-      if (WHOLE) {
-        if (g == 1) {
-          float* nb = smem + ((t + 1) & 1) * BUF;
-          tile_park<AKM, BT>(va, nb, BK); tile_park<BKM, BT>(vb, nb + AF, BK);
-        }
-        if (g == 2) {
-          tile_load<true, AKM, BT>(va, p.A, p.lda, m0, p.M, (t + 2) * BK, p.K);
-          tile_load<true, BKM, BT>(vb, p.B, p.ldb, n0, p.N, (t + 2) * BK, p.K);
-        }
-      }
+      f32x4 fa[T], fb[T];
+#pragma unroll
+      for (int i = 0; i < T; ++i) fa[i] = tile_frag<AKM, BT>(s, wm + i * 32, g);
+#pragma unroll
+      for (int j = 0; j < T; ++j) fb[j] = tile_frag<BKM, BT>(s + AF, wn + j * 32, g);
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
         for (int i = 0; i < T; ++i)
 #pragma unroll
-          for (int j = 0; j < T; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[g & 1][i][e], fb[g & 1][j][e], acc[i][j], 0, 0, 0);
-      if (WHOLE) {
+          for (int j = 0; j < T; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][e], fb[j][e], acc[i][j], 0, 0, 0);
+    }
+  }
+}
+
+// A float is the sum of three bf16 numbers, exactly: the nearest one (a0), the one nearest to what is left, and what is left
+// then.  Of the nine products of pieces six are formed; the three left out are below 2^-25 of the product, of either sign.
+// Six bf16 instructions of 32 cycles stand against eight fp32 ones of 64.  a0 b0 is summed by itself: the instruction drops what
+// lies below its sum towards minus infinity several times in 16 k, and with all six in one sum 1024-4096-4096-1024 on
+// 1024 rows is 1.43e-6 from 64 bits and 4096 in k low by 2e-7 in the mean (fp32 instructions 1.28e-6 and 0).
+// LDS keeps the planes of an operand as memory has it: k-contiguous rows of 32 bytes, read as one 16-byte fragment per
+// lane, k-major rows of the tile's width, read by the transposing LDS read; 16-byte chunks are exchanged so that neither way
+// of reading nor the 8-byte writes have bank conflicts.
+// What bounds it: with two workgroups to a CU the matrix cores (1024 rows, 4096 -> 8192 forward 328 us = 209 TFLOP/s, 1255 of
+// bf16), with one the LDS and barrier latency of a wave alone on its SIMD (4096 -> 4096 forward 188 us, 183 TFLOP/s).  Against the
+// fp32 walk that ran here before, 1024 rows, forward / backward with the update, us: 4096 -> 4096 303 / 538 -> 188 / 349,
+// 1024 -> 4096 90 / 157 -> 61 / 115; 2051 rows, 1030 -> 2052 174 / 240 -> 85 / 160; distance from 64 bits 0.31 - 0.36 times.
+constexpr int SK = 16, kSlots = 3;                         // of k to a step
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+template <bool KM, int ROWS> struct Planes {
+  static constexpr int BYTES = ROWS * SK * 2;              // of one plane
+  static constexpr int PIECES = ROWS * SK / 4 / 256;       // 16-byte pieces of memory per thread and step
+};
+// The pieces of a step that is whole in k, one load each at a lane offset from a uniform base: rows past the end are clamped, and
+// of a k-major operand whole pieces - the last may reach into the row behind (so not in the last row of all: see planes_walk).
+template <bool KM, int ROWS>
+__device__ __forceinline__ void plane_offsets(int ld, int r0, int rows, unsigned (&off)[Planes<KM, ROWS>::PIECES]) {
 #pragma unroll
-        for (int q = 0; q < 4 * T * T; ++q) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // a matrix instruction
-          __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);   // then vector arithmetic,
-          __builtin_amdgcn_sched_group_barrier(0x080, 1, 0);   // an LDS access
-          __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // and a load
-        }
-      } else if (g == 1) {
-        if (t + 1 < nk) park(smem + ((t + 1) & 1) * BUF, (t + 1) * BK);
-        if (t + 2 < nk) fetch((t + 2) * BK);
+  for (int i = 0; i < Planes<KM, ROWS>::PIECES; ++i) {
+    const int p = threadIdx.x % 256 + 256 * i;
+    const int k = KM ? p / (ROWS / 4) : p % (SK / 4) * 4, r = KM ? p % (ROWS / 4) * 4 : p / (SK / 4);
+    const int last = (KM ? (rows - 1) / 4 * 4 : rows - 1) - r0, rc = r < last ? r : last;
+    off[i] = KM ? k * ld + rc : rc * ld + k;
+  }
+}
+template <bool KM, int ROWS>
+__device__ __forceinline__ void planes_load(f32x4* v, const unsigned (&off)[Planes<KM, ROWS>::PIECES], const float* __restrict__ g, int ld,
+                                            int r0, int k0) {
+  const float* base = KM ? g + (int64_t)k0 * ld + r0 : g + (int64_t)r0 * ld + k0;
+#pragma unroll
+  for (int i = 0; i < Planes<KM, ROWS>::PIECES; ++i) v[i] = *reinterpret_cast<const f32x4_u*>(base + off[i]);
+}
+template <bool KM, int ROWS>
+__device__ __forceinline__ int plane_chunk(int row, int c) {   // byte of 16-byte chunk c of a row
+  return KM ? row * (ROWS * 2) + (c ^ (ROWS == 64 ? (row & 2) << 1 : (row & 3) << 2)) * 16 : row * 32 + (c ^ (row >> 3 & 1)) * 16;
+}
+template <bool KM, int ROWS>
+__device__ __forceinline__ void planes_park(const f32x4* v, char* s, int left) {   // left: K - k0
+#pragma unroll
+  for (int i = 0; i < Planes<KM, ROWS>::PIECES; ++i) {
+    const int p = threadIdx.x % 256 + 256 * i;
+    const int row = KM ? p / (ROWS / 4) : p / (SK / 4), c = KM ? p % (ROWS / 4) : p % (SK / 4);
+    f32x4 x = v[i];
+    if (left < SK) {                                       // (uniform)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = (KM ? row : c * 4 + e) < left ? x[e] : 0.f;
+    }
+    char* d = s + plane_chunk<KM, ROWS>(row, c >> 1) + (c & 1) * 8;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const u32x2 h = {rv_pack_bf16x2(x[0], x[1]), rv_pack_bf16x2(x[2], x[3])};
+      *reinterpret_cast<u32x2*>(d + q * Planes<KM, ROWS>::BYTES) = h;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] -= __uint_as_float(e & 1 ? h[e >> 1] & 0xFFFF0000u : h[e >> 1] << 16);
+    }
+  }
+}
+// rows row0 .. + 31 of plane q for v_mfma_f32_32x32x16_bf16: lane l holds row l % 32, k = 8 (l / 32) .. + 7
+template <bool KM, int ROWS>
+__device__ __forceinline__ bf16x8 plane_frag(const char* s, int row0, int plane) {
+  const int l = threadIdx.x & 63;
+  s += plane * Planes<KM, ROWS>::BYTES;
+  if (!KM) return *reinterpret_cast<const bf16x8*>(s + plane_chunk<KM, ROWS>(row0 + (l & 31), l >> 5));
+  typedef s16x4 __attribute__((address_space(3)))* lds4;
+  const int q = l >> 4, i = l & 15, k = 8 * (q >> 1) + (i >> 2), col = row0 + 16 * (q & 1) + 4 * (i & 3);
+  const char* at = s + plane_chunk<KM, ROWS>(k, col >> 3) + (col & 7) * 2;
+  const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(at));
+  const s16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(at + 4 * (ROWS * 2)));
+  return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+template <int BT, bool AKM, bool BKM> constexpr int kSlotBytes = 3 * (Planes<AKM, BT>::BYTES + Planes<BKM, BT>::BYTES);
+
+// While step s is multiplied, step s + 2 goes into the slot that step s - 1 was read from and step s + 2 + D is requested (D steps
+// are on the way, what the registers hold): one barrier a step.  Fragments have one set of registers: the order of the products lets those of pieces 1 and 2 be read anew behind
+// the last products of the step before, those of piece 0 behind the first of their own.  Two workgroups share a CU.
+template <int BT, bool AKM, bool BKM>
+__device__ __forceinline__ void planes_walk(TileAcc<BT>& acc, const Prod& p, int m0, int n0, char* smem) {
+  constexpr int T = kTileEdge<BT>, PA = Planes<AKM, BT>::BYTES, SLOT = kSlotBytes<BT, AKM, BKM>;
+  const int wave = threadIdx.x % 256 >> 6, wm = (wave & 1) * 32 * T, wn = (wave >> 1) * 32 * T;
+  TileAcc<BT> low;
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int j = 0; j < T; ++j) { acc[i][j] = 0.f; low[i][j] = 0.f; }
+  constexpr int D = T == 2 ? 2 : 8;
+  f32x4 va[D][Planes<AKM, BT>::PIECES], vb[D][Planes<BKM, BT>::PIECES];   // step s in set s % D
+  unsigned oa[Planes<AKM, BT>::PIECES], ob[Planes<BKM, BT>::PIECES];
+  plane_offsets<AKM, BT>(p.lda, m0, p.M, oa);
+  plane_offsets<BKM, BT>(p.ldb, n0, p.N, ob);
+  bf16x8 a[3][T], b[3][T];
+  const int ns = (p.K + SK - 1) / SK;
+  const int Kw = p.K - ((AKM && p.M % 4) || (BKM && p.N % 4) ? 1 : 0);   // steps that end here at the latest are loaded by pieces
+  auto fetch = [&](auto set, int s) {
+    constexpr int S = decltype(set)::value;
+    if (s >= ns) return;
+    if ((s + 1) * SK <= Kw) {                              // (uniform)
+      planes_load<AKM, BT>(va[S], oa, p.A, p.lda, m0, s * SK);
+      planes_load<BKM, BT>(vb[S], ob, p.B, p.ldb, n0, s * SK);
+    } else {
+      tile_load<AKM, BT, SK>(va[S], p.A, p.lda, m0, p.M, s * SK, p.K);
+      tile_load<BKM, BT, SK>(vb[S], p.B, p.ldb, n0, p.N, s * SK, p.K);
+    }
+  };
+  auto park = [&](auto set, int s, char* to) {
+    constexpr int S = decltype(set)::value;
+    if (s >= ns) return;
+    planes_park<AKM, BT>(va[S], to, p.K - s * SK);
+    planes_park<BKM, BT>(vb[S], to + 3 * PA, p.K - s * SK);
+  };
+  auto frags = [&](int piece, const char* from) {
+#pragma unroll
+    for (int i = 0; i < T; ++i) a[piece][i] = plane_frag<AKM, BT>(from, wm + i * 32, piece);
+#pragma unroll
+    for (int j = 0; j < T; ++j) b[piece][j] = plane_frag<BKM, BT>(from + 3 * PA, wn + j * 32, piece);
+  };
+  auto products = [&](TileAcc<BT>& to, int pa, int pb) {
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+      for (int j = 0; j < T; ++j) to[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pa][i], b[pb][j], to[i][j], 0, 0, 0);
+  };
+  char *cur = smem, *nxt = smem + SLOT, *free = smem + 2 * SLOT;
+  // steps 0 and 1 in their slots, 2 .. D + 1 on the way, the first fragments read.  (Both kinds of loop have a start of their own:
+  // behind loads that may not have been issued the compiler waits for all there are, in every turn of the loop.)
+  auto begin = [&](auto load, auto store) {
+    each<D>([&](auto set) { load(set, decltype(set)::value); });
+    store(Int<0>(), 0, cur);
+    load(Int<0>(), D);
+    store(Int<1>(), 1, nxt);
+    load(Int<1>(), D + 1);
+    __syncthreads();
+    frags(1, cur);
+    frags(2, cur);
+  };
+  auto step = [&](int s, auto set, auto whole) {
+    constexpr int S = (decltype(set)::value + 2) % D;      // of step s + 2
+    constexpr bool WHOLE = decltype(whole)::value != 0;    // step s + 2 + D is loaded by pieces
+    const bool next = WHOLE || s + 1 < ns;
+    // the order in which a stretch's instructions are issued: behind each matrix instruction some of the others
+    auto deal = [&](auto matrix, auto lds) {
+#pragma unroll
+      for (int q = 0; q < decltype(matrix)::value * T * T; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, T == 2 ? 5 : 10, 0);
+        __builtin_amdgcn_sched_group_barrier(0x080, decltype(lds)::value, 0);
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
       }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    if (!WHOLE) {
+      park(Int<S>(), s + 2, free);
+      fetch(Int<S>(), s + 2 + D);
+    }
+    frags(0, cur);
+    products(low, 1, 1);
+    if (WHOLE) deal(Int<1>(), Int<T == 2 ? 2 : 4>());
+    if (WHOLE) {
+      planes_park<AKM, BT>(va[S], free, SK);
+      planes_load<AKM, BT>(va[S], oa, p.A, p.lda, m0, (s + 2 + D) * SK);
+    }
+    products(low, 1, 0);
+    products(low, 0, 1);
+    if (WHOLE) deal(Int<2>(), Int<T == 2 ? 1 : 2>());
+    if (next) frags(1, nxt);
+    if (WHOLE) {
+      planes_park<BKM, BT>(vb[S], free + 3 * PA, SK);
+      planes_load<BKM, BT>(vb[S], ob, p.B, p.ldb, n0, (s + 2 + D) * SK);
+    }
+    products(low, 2, 0);
+    products(low, 0, 2);
+    if (WHOLE) deal(Int<2>(), Int<T == 2 ? 2 : 4>());
+    if (next) frags(2, nxt);
+    products(acc, 0, 0);
+    if (WHOLE) deal(Int<1>(), Int<T == 2 ? 2 : 4>());
+    __syncthreads();
+    char* t = cur; cur = nxt; nxt = free; free = t;
+  };
+  int s = 0;
+  if ((2 * D + 2) * SK <= Kw) {
+    begin(
+        [&](auto set, int s) {
+          planes_load<AKM, BT>(va[decltype(set)::value], oa, p.A, p.lda, m0, s * SK);
+          planes_load<BKM, BT>(vb[decltype(set)::value], ob, p.B, p.ldb, n0, s * SK);
+        },
+        [&](auto set, int s, char* to) {
+          planes_park<AKM, BT>(va[decltype(set)::value], to, SK);
+          planes_park<BKM, BT>(vb[decltype(set)::value], to + 3 * PA, SK);
+        });
+    do {
+      each<D>([&](auto set) { step(s + decltype(set)::value, set, Int<1>()); });
+      s += D;
+    } while ((s + 2 * D + 2) * SK <= Kw);
+  } else {
+    begin(fetch, park);
+  }
+  for (; s < ns; s += D)
+    each<D>([&](auto set) {
+      if (s + decltype(set)::value < ns) step(s + decltype(set)::value, set, Int<0>());
+    });
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int j = 0; j < T; ++j) acc[i][j] += low[i][j];
+}
+
+// BT: 128 or 64 (tiled), kHalves (64, by two halves of a workgroup), 32 (split over NT / 64 waves), kWave (a 32x32 tile per wave)
+constexpr int kWave = 1, kHalves = 2;
+template <int BT, int NT, bool AKM, bool BKM> constexpr int mlp_lds_bytes() {
+  if constexpr (BT == kHalves) return mlp_lds_bytes<64, NT, AKM, BKM>();
+  else
+  // (kWave: the bias sums beside it)
+  return 4 * (BT == kWave ? NT / 32 * 33 : BT == 32 ? NT / 64 * 32 * 33
+              : NT / 256 * std::max(Lds<AKM, BT>::FLOATS + Lds<BKM, BT>::FLOATS, kSlots * kSlotBytes<BT, AKM, BKM> / 4));
+}
+// A workgroup of 512 threads takes two tiles, side by side: both have the same number of steps and so of barriers; the last
+// one's second tile may be past the end (it walks along on the last tile and keeps nothing).
+// With HALVES the two of them take half of one tile's steps each and the second one's sums are added to the first one's: a wave alone
+// on its SIMD waits for LDS and barriers most of a 64x64 tile's step (4096 -> 1024 on 1024 rows forward 104 us, in halves 79).
+template <int BT, bool AKM, bool BKM, int OP, bool HALVES = false>
+__device__ __forceinline__ void tiled_body(const Prod& p, const Out& o, int tile, float* smem, int part = 0) {
+  constexpr int T = kTileEdge<BT>;
+  const int all = (p.M + BT - 1) / BT * p.tiles_n;
+  const bool live = tile < all;        // (uniform in 256 threads)
+  tile = live ? tile : all - 1;
+  const int m0 = tile / p.tiles_n * BT, n0 = tile % p.tiles_n * BT;
+  const int wave = threadIdx.x % 256 >> 6, l = threadIdx.x & 63, wm = (wave & 1) * 32 * T, wn = (wave >> 1) * 32 * T;
+  TileAcc<BT> acc;
+  if constexpr (HALVES) {
+    static_assert(!AKM && BKM, "operands of a forward product");
+    Prod h = p;
+    const int steps = (p.K + SK - 1) / SK, mine = (steps + 1) / 2, k1 = mine * SK;
+    if (part) { h.A += k1; h.B += (int64_t)k1 * p.ldb; h.K -= k1; } else { h.K = k1; }
+    planes_walk<BT, AKM, BKM>(acc, h, m0, n0, reinterpret_cast<char*>(smem));
+    if (part && steps - mine < mine) __syncthreads();      // (the barrier of the step that the first half has more)
+    const float* mem = smem + (part ? 0 : mlp_lds_bytes<BT, 256, AKM, BKM>() / 4);
+    f32x4* x = reinterpret_cast<f32x4*>(const_cast<float*>(mem)) + threadIdx.x % 256;
+#pragma unroll
+    for (int r = 0; r < 16 * T * T; r += 4) {
+      f32x16& v = acc[r / 16 / T][r / 16 % T];
+      if (part) x[r / 4 * 256] = f32x4{v[r % 16], v[r % 16 + 1], v[r % 16 + 2], v[r % 16 + 3]};
     }
     __syncthreads();
-  };
-  int t = 0;
-  if (inside)
-    for (; (t + 3) * BK <= p.K; ++t) step(t, Int<1>());
-  for (; t < nk; ++t) step(t, Int<0>());
-  if (!live) return;
+#pragma unroll
+    for (int r = 0; r < 16 * T * T; r += 4) {
+      f32x16& v = acc[r / 16 / T][r / 16 % T];
+      if (!part) {
+        const f32x4 y = x[r / 4 * 256];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[r % 16 + e] += y[e];
+      }
+    }
+  } else {
+    planes_walk<BT, AKM, BKM>(acc, p, m0, n0, reinterpret_cast<char*>(smem));
+  }
+  // The pieces of an infinity hold a NaN, and those of numbers near the smallest ones are not exact: a tile with a
+  // result that is not finite, or with none but tiny ones, is walked again in fp32.
+  bool finite = true;
+  float top = 0.f;
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int j = 0; j < T; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        finite = finite && fabsf(acc[i][j][r]) < __builtin_inff();
+        top = fmaxf(top, fabsf(acc[i][j][r]));
+      }
+  if (__syncthreads_or(!finite) || (!__syncthreads_or(top >= 1e-30f) && __syncthreads_or(top > 0.f)))
+    fp32_walk<BT, AKM, BKM>(acc, p, m0, n0, smem);
+  if (!live || (HALVES && part)) return;
 #pragma unroll
   for (int i = 0; i < T; ++i)
 #pragma unroll
@@ -467,19 +687,16 @@ __device__ __forceinline__ void bias_body(const float* __restrict__ D, int M, in
   }
 }
 
-// BT: 128 or 64 (tiled), 32 (split over NT / 64 waves), kWave (a 32x32 tile per wave)
-constexpr int kWave = 1;
-template <int BT, int NT, bool AKM, bool BKM> constexpr int mlp_lds_bytes() {
-  // (kWave: the bias sums beside it)
-  return 4 * (BT == kWave ? NT / 32 * 33 : BT == 32 ? NT / 64 * 32 * 33
-              : NT / 256 * 2 * (Lds<AKM, BT>::FLOATS + Lds<BKM, BT>::FLOATS));
-}
 template <int BT, int NT, bool AKM, bool BKM, int OP>
 __device__ __forceinline__ void mlp_body(const Prod& p, const Out& o, int tile, float* smem) {
   if constexpr (BT == kWave) {
     wave_body<NT, AKM, BKM, OP>(p, o, tile);
   } else if constexpr (BT == 32) {
     split_body<NT / 64, AKM, BKM, OP>(p, o, tile, smem);
+  } else if constexpr (BT == kHalves) {
+    static_assert(NT == 512, "eight waves a tile");
+    const int part = __builtin_amdgcn_readfirstlane(threadIdx.x / 256);
+    tiled_body<64, AKM, BKM, OP, true>(p, o, tile, smem + part * (mlp_lds_bytes<64, 256, AKM, BKM>() / 4), part);
   } else {
     static_assert(NT == 256 || NT == 512, "four waves a tile");
     const int part = NT == 256 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / 256);
@@ -489,7 +706,7 @@ __device__ __forceinline__ void mlp_body(const Prod& p, const Out& o, int tile, 
 extern __shared__ __align__(16) float mlp_smem[];
 
 template <int BT, int NT>
-__global__ __launch_bounds__(NT) void mlp_fwd_kernel(Prod p, Out o, float* __restrict__ copy) {
+__global__ __launch_bounds__(NT, 2) void mlp_fwd_kernel(Prod p, Out o, float* __restrict__ copy) {
   // The stage's input goes into the stash beside the product that reads it, by workgroups of their own behind its
   // tiles, four 16-byte pieces of a lane in flight.  (Dealt out over the tiles, one float at a time ahead of the
   // product, it was what a narrow layer behind a wide input lasted: there are few tiles then.  4096 -> 32 on 1024 rows
@@ -513,7 +730,7 @@ __global__ __launch_bounds__(NT) void mlp_fwd_kernel(Prod p, Out o, float* __res
 
 // input gradient (tiles 0 .. dx.tiles), weight gradient, bias gradient in one launch
 template <int BX, int BW, int NT>
-__global__ __launch_bounds__(NT) void mlp_bwd_kernel(Prod dx, Out ox, Prod dw, Out ow, const float* __restrict__ d, int M, int N,
+__global__ __launch_bounds__(NT, 2) void mlp_bwd_kernel(Prod dx, Out ox, Prod dw, Out ow, const float* __restrict__ d, int M, int N,
                                                      size_t offb) {
   int b = blockIdx.x;
   if (b < dx.tiles) { mlp_body<BX, NT, false, false, DX>(dx, ox, b, mlp_smem); return; }
@@ -523,18 +740,16 @@ __global__ __launch_bounds__(NT) void mlp_bwd_kernel(Prod dx, Out ox, Prod dw, O
 }
 
 Prod product(const float* A, int lda, const float* B, int ldb, int M, int N, int K, int bt, int nt) {
-  const int edge = bt == kWave ? 32 : bt, tn = (N + edge - 1) / edge, tiles = (M + edge - 1) / edge * tn, waves = nt / 64;
-  const int per = bt == kWave ? waves : bt > 32 ? nt / 256 : 1;   // tiles a workgroup
+  const int edge = bt == kWave ? 32 : bt == kHalves ? 64 : bt, tn = (N + edge - 1) / edge, tiles = (M + edge - 1) / edge * tn, waves = nt / 64;
+  const int per = bt == kWave ? waves : bt > 32 ? nt / 256 : 1;   // tiles a workgroup (kHalves: 1)
   return Prod{A, B, lda, ldb, M, N, K, tn, (tiles + per - 1) / per};   // (tiles: workgroups)
 }
 int tile_count(int M, int N, int bt) { return (M + bt - 1) / bt * ((N + bt - 1) / bt); }
 constexpr int kCUs = 256;
 // The largest tile that still gives every CU one (of 64x64 tiles half of them: such a workgroup
-// keeps up with two CUs' worth of 32x32 ones, whose operands all come through L2).  Measured: forward
-// + backward + update of 1024-4096-4096-1024 on 1024 rows 11.0 -> 1.43 ms against plain 16x16 vector
-// tiles with separate bias and update launches (108 of 157 TFLOP/s; 4096^3 alone 128 / 140 / 133
-// TFLOP/s forward / input / weight gradient), 300-1000-1000-77 on 100 rows with momentum
-// 304 -> 68 us, where 64x64 tiles for the 100-row products would take 120.
+// keeps up with two CUs' worth of 32x32 ones, whose operands all come through L2).  Measured: a stage step of
+// 1024-4096-4096-1024 on 1024 rows 0.90 ms (172 TFLOP/s), 300-1000-1000-77 on 100 rows with momentum
+// 67 us, where 64x64 tiles of fp32 instructions took 120 for the 100-row products.
 // A result of at most 32 rows or columns fills at best half of such a tile's matrix instructions, so there the tile
 // count says nothing about the chip: it takes 32x32 tiles, one per wave where the contraction is short (the work is the
 // results' memory traffic), split where it is long.  Times in us against the tiles that the count alone would take:
@@ -547,7 +762,7 @@ int pick(int M, int N, int K) {
   if (thin <= 32 && tile_count(M, N, 64) >= kCUs / 2) return K <= 128 ? kWave : 32;
   return thin > 64 && tile_count(M, N, 128) >= kCUs ? 128 : tile_count(M, N, 64) >= kCUs / 2 ? 64 : 32;
 }
-int threads(int bt) { return bt == 32 ? 64 * kSplitWaves : 256; }
+int threads(int bt) { return bt == 32 || bt == kHalves ? 64 * kSplitWaves : 256; }
 
 template <typename K>
 rv_status allow_lds(K kern, int bytes) {
@@ -930,7 +1145,8 @@ rv_status rv_mlp_forward(rv_stage* s, rv_slot& slot, const void* in, void* out) 
   for (int i = 0; i < p->n; ++i) {
     const bool last = i == p->n - 1, first = i == 0 && !copy_first;
     const int K = (int)s->dims[i], N = (int)s->dims[i + 1];
-    const int bt = pick(mb, N, K);
+    int bt = pick(mb, N, K);
+    if (bt == 64 && tile_count(mb, N, 64) <= kCUs && K >= 256) bt = kHalves;   // one tile to a CU; shorter walks are mostly beginning
     const Prod pr = product(first ? (const float*)in : stash + p->offA[i], K, w + p->offW[i], N, mb, N, K, bt, threads(bt));
     Out o = {};
     o.C = last ? (float*)out : stash + p->offA[i + 1]; o.bias = w + p->offB[i]; o.relu = !last;
@@ -938,6 +1154,7 @@ rv_status rv_mlp_forward(rv_stage* s, rv_slot& slot, const void* in, void* out) 
     const rv_status rc = bt == 128  ? launch_fwd<128, 256>(s->st, pr, o, copy)
                          : bt == 64 ? launch_fwd<64, 256>(s->st, pr, o, copy)
                          : bt == kWave ? launch_fwd<kWave, 256>(s->st, pr, o, copy)
+                         : bt == kHalves ? launch_fwd<kHalves, 512>(s->st, pr, o, copy)
                                     : launch_fwd<32, 64 * kSplitWaves>(s->st, pr, o, copy);
     RV_TRY(rc);
   }

@@ -337,3 +337,47 @@ def test_more_version_slots_than_one_launch_clears():
                          [([K, 40], 9, 0.0) for K in (256, 264, 512, 513, 769, 1030)])
 def test_two_tiles_a_workgroup_and_the_split_walk(dims, mb, momentum):
     test_product_forms_at_their_edges(dims, mb, momentum)
+
+
+# LDS tiles walked in three bf16 planes, steps of 16 in k.  Tiles of 128: up to five steps are loaded by the general form, from six on
+# whole steps by pieces (one less where a row is no multiple of a piece).  Tiles of 64: the same at 18 steps; from 256 in
+# k on by two halves of a workgroup, an even or odd number of steps.
+@pytest.mark.parametrize("dims,mb", [([K, 4100], 1030) for K in (95, 96, 97, 113, 130)] + [([96, 4101], 1030)] +
+                         [([K, 700], 900) for K in (255, 256, 257, 288, 576, 577)] + [([600, 701], 900), ([592, 702], 900)])
+def test_products_in_three_planes(dims, mb):
+    """Bar: sums of K products with random signs in fp32 stay within sqrt(K) * 2^-24 normwise in any order; the pieces left out
+    are 2^-25 of a product."""
+    import paper_2401_01728_amd as rv
+    w0 = kaiming_uniform_flat(66, dims)
+    g = rv.Stage.mlp(dims, mb, 0, 1e-3); g.set_params(dev(w0))
+    o = ostage.Stage("mlp", 0, 1e-3, w0, dims=dims)
+    x = gen.normal_f32(66, 1, mb * dims[0]).reshape(mb, dims[0])
+    dy = gen.normal_f32(66, 2, mb * dims[1], std=0.1).reshape(mb, dims[1])
+    bar = lambda k: float(np.sqrt(k) * 2.0 ** -24 + 2.0 ** -24)
+    close(host64(g.forward(0, dev(x))), o.forward(0, x), bar(dims[0]), "t", group="MLP in three planes: out")
+    close(host64(g.backward(0, dev(dy))), o.backward(0, dy), bar(dims[1]), "t", group="MLP in three planes: grad_in")
+    close(host64(g.last_grad()), o.last_grad, bar(mb), "t", group="MLP in three planes: gradient")
+
+
+@pytest.mark.parametrize("where", ["first weight row", "activation"])
+@pytest.mark.filterwarnings("ignore::RuntimeWarning")
+def test_an_infinity_in_a_large_tile(where):
+    test_an_infinity_stays_where_it_belongs(where, [301, 4100], 1030)
+
+
+@pytest.mark.parametrize("scale", [1e-26, 1e-31, 1e-34])
+def test_gradients_near_the_smallest_numbers(scale):
+    """The third piece of 1e-33 is no normal number: such tiles are multiplied in fp32.  Bar: sums of fp32 products as above; of
+    results down to 1e-37 the smallest number's half, 7e-46, is far below 2^-24."""
+    import paper_2401_01728_amd as rv
+    dims, mb = [1500, 4100], 1030
+    w0 = kaiming_uniform_flat(67, dims)
+    g = rv.Stage.mlp(dims, mb, 0, 1e-3); g.set_params(dev(w0))
+    o = ostage.Stage("mlp", 0, 1e-3, w0, dims=dims)
+    x = gen.normal_f32(67, 1, mb * dims[0]).reshape(mb, dims[0])
+    dy = gen.normal_f32(67, 2, mb * dims[1]).reshape(mb, dims[1]) * np.float32(scale)
+    g.forward(0, dev(x)); o.forward(0, x)
+    dx, dxo = host64(g.backward(0, dev(dy))), o.backward(0, dy)
+    up = 1.0 / scale                       # (the comparison's own squares would underflow)
+    close(dx * up, dxo * up, 1e-5, "t", group="MLP near the smallest numbers, bar 1e-5")
+    close(host64(g.last_grad()) * up, o.last_grad * up, 1e-5, "t", group="MLP near the smallest numbers, bar 1e-5")
