@@ -18,6 +18,7 @@
 // gradient, the weight gradient with the update in its epilogue, and the bias gradient together
 // (they read the same gradient and do not depend on one another).
 #include <new>
+#include <type_traits>
 #include "internal.h"
 
 namespace {
@@ -793,6 +794,8 @@ rv_status launch_bwd(hipStream_t st, const Prod& dx, const Out& ox, const Prod& 
 struct Tiny {
   int mb, dim[kTinyLayers + 1];
   unsigned offW[kTinyLayers], offB[kTinyLayers], offA[kTinyLayers], zero;   // zero: the number of parameters
+  unsigned over[kTinyLayers];   // t / tn of a layer's gradient tiles, tn to a row: t * over >> 16 (t * tn < 65536)
+  int skip[kTinyLayers];        // the layer's gradient tiles modulo the waves of the launch
 };
 constexpr int kTinyDepth = 128;   // contraction a wave requests at a time
 constexpr int kTinyThreads = 512, kTinyWaves = kTinyThreads / 64;
@@ -800,13 +803,19 @@ __host__ __device__ constexpr int tiny_pitch(int w) { return (w + 15) / 16 * 16 
 
 // What bounds these kernels is one memory round trip after another (1 - 2 us each: the lines were
 // written by other launches, which leaves every XCD's L2 without them) and the number of lines a
-// load instruction touches.  So a wave requests everything its first tiles of a layer read one
-// layer ahead, the rows of a transposed weight tile come in 16-byte pieces, and no load waits behind
+// load instruction touches.  So a wave requests everything its first tiles of a layer read up to two layers
+// ahead (what the registers hold), the rows of a transposed weight tile come in 16-byte pieces, and no load waits behind
 // a branch: an index past an end is clamped where its result is not stored, and points at a zero behind the
 // parameters where it enters a sum (the zero on the other side would not do: zero times an infinity is no zero).
-// These kernels run through their code once, so its length is time too: device time of 64-128-64 on 8 rows, forward /
-// backward, 5.4 / 8.1 us like this; with that index chosen in every group 6.2 / 8.5, clamped values zeroed in registers
-// 6.0 / 8.1, the range check of a buffer descriptor 5.7 / 8.6 (clamped and left as they are: 5.5 / 8.0).
+// These kernels run through their code once, so its length is time too, about 0.3 us to a KiB: the copy of the input moved as
+// pieces of 16 bytes (element by element with a test each: forward + 0.8 us), rows of gradient tiles by a multiplication in
+// place of divisions, lane offsets of 32 bits.  A launch of 64-128-64 on 8 rows, forward / backward, 5.8 / 8.6 us before
+// that and 5.5 / 7.3 with it; 16 microbatches through two such stages 437 -> 386 us, which is what issuing them takes.
+// element i of a vector of less than 4 GiB: a lane offset from a uniform base, without 64-bit arithmetic per lane
+template <typename T>
+__device__ __forceinline__ T& at(T* base, unsigned i) {
+  return *reinterpret_cast<T*>(reinterpret_cast<std::conditional_t<std::is_const<T>::value, const char, char>*>(base) + i * 4u);
+}
 template <int N>
 __device__ __forceinline__ void pin(float (&v)[N]) {   // the values have arrived here
 #pragma unroll
@@ -842,7 +851,7 @@ __device__ __forceinline__ void tiny_request_rest(TinyB& r, const float* __restr
   const int k = K / 16 * 16 + 4 * ((threadIdx.x & 63) >> 4);
   if (K % 16 != 0) {                                       // (uniform)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) r.rest[e] = W[k + e < K ? (BT ? c * ldw + (unsigned)(k + e) : (unsigned)(k + e) * ldw + c) : zero];
+    for (int e = 0; e < 4; ++e) r.rest[e] = at(W, k + e < K ? (BT ? c * ldw + (unsigned)(k + e) : (unsigned)(k + e) * ldw + c) : zero);
   }
 }
 template <int MT, bool BT>
@@ -874,14 +883,30 @@ __device__ __forceinline__ void tiny_tile(f32x4 (&acc)[MT], TinyB& r, const floa
   }
 }
 
-// rows [mb][w] of memory -> LDS, rows and columns past the end zero
+// rows [mb][w] of memory -> LDS, rows and columns past the end zero.  All is requested before the first value is used: piece by piece
+// this was a round trip to a piece.
 template <int MT>
 __device__ __forceinline__ void tiny_rows(float* s, const float* __restrict__ g, int mb, int w) {
-  const int pitch = tiny_pitch(w), l = threadIdx.x & 63;
-  for (int m = threadIdx.x >> 6; m < 16 * MT; m += kTinyWaves)
-    for (int c = l; c < pitch; c += 64) {
-      const float x = g[(m < mb ? m : mb - 1) * w + (c < w ? c : w - 1)];
-      s[m * pitch + c] = m < mb && c < w ? x : 0.f;
+  constexpr int R = 16 * MT / kTinyWaves, C = MT == 4 ? 2 : 5;   // pieces of 64: rows of up to 64 or 256, and the pitch
+  const int pitch = tiny_pitch(w), wave = threadIdx.x >> 6, l = threadIdx.x & 63;
+  float v[C][R];
+#pragma unroll
+  for (int k = 0; k < C; ++k)
+    if (64 * k < w) {                                      // (uniform)
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int m = wave + kTinyWaves * r, c = l + 64 * k;
+        v[k][r] = at(g, (m < mb ? m : mb - 1) * w + (c < w ? c : w - 1));
+      }
+    }
+#pragma unroll
+  for (int k = 0; k < C; ++k)
+    if (64 * k < pitch) {                                  // (uniform)
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int m = wave + kTinyWaves * r, c = l + 64 * k;
+        if (c < pitch) s[m * pitch + c] = m < mb && c < w ? v[k][r] : 0.f;
+      }
     }
 }
 
@@ -897,12 +922,21 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_fwd_kernel(Tiny p, const fl
     const int N = p.dim[i + 1], c = t * 16 + (l & 15), cc = c < N ? c : N - 1;
     tiny_request<false>(r.b, w + p.offW[i], N, p.dim[i], 0, cc);
     tiny_request_rest<false>(r.b, w + p.offW[i], p.zero - p.offW[i], N, p.dim[i], cc);
-    r.bias[0] = w[p.offB[i] + cc];
+    r.bias[0] = at(w, p.offB[i] + cc);
   };
-  TinyFwdReq cur, nxt;
-  request(cur, 0, first(0));
+  TinyFwdReq req[NL];
+  request(req[0], 0, first(0));
+  request(req[1], 1, first(1));
+  // (the stash copy of the input: the first piece of a thread is on its way with the rows)
+  const int n = p.mb * p.dim[0], i0 = (blockIdx.x * kTinyThreads + threadIdx.x) * 4;
+  float* copy = stash + p.offA[0];
+  f32x4 piece = 0.f;
+  if (i0 + 4 <= n) piece = *reinterpret_cast<const f32x4_u*>(in + i0);
   tiny_rows<MT>(act, in, p.mb, p.dim[0]);
-  for (int i = blockIdx.x * kTinyThreads + threadIdx.x; i < p.mb * p.dim[0]; i += gridDim.x * kTinyThreads) stash[p.offA[0] + i] = in[i];
+  if (i0 + 4 <= n) *reinterpret_cast<f32x4_u*>(copy + i0) = piece;
+  for (int i = i0 + 4 <= n ? i0 + 4 * kTinyThreads * gridDim.x : i0; i < n; i += 4 * kTinyThreads * gridDim.x)
+#pragma unroll 1
+    for (int e = i; e < i + 4 && e < n; ++e) copy[e] = in[e];
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
@@ -911,8 +945,8 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_fwd_kernel(Tiny p, const fl
     const float* src = act + (i & 1) * half;
     float* dst = act + ((i + 1) & 1) * half;
     const int dp = tiny_pitch(N), tiles = (N + 15) / 16, step = last ? kTinyWaves * gridDim.x : kTinyWaves;
-    nxt = cur;
-    if (!last) request(nxt, i + 1, first(i + 1));
+    TinyFwdReq& cur = req[i];
+    if (i + 2 < NL) request(req[i + 2], i + 2, first(i + 2));
     for (int t = first(i); t < tiles; t += step) {
       if (t != first(i)) request(cur, i, t);
       const int c = t * 16 + (l & 15);
@@ -928,14 +962,13 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_fwd_kernel(Tiny p, const fl
           if (!last) {
             v = c < N ? fmaxf(v, 0.f) : 0.f;
             dst[m * dp + c] = v;
-            if (t % gridDim.x == blockIdx.x && m < p.mb && c < N) stash[p.offA[i + 1] + m * N + c] = v;
+            if (t % gridDim.x == blockIdx.x && m < p.mb && c < N) at(stash, p.offA[i + 1] + m * N + c) = v;
           } else if (m < p.mb && c < N) {
-            out[m * N + c] = v;
+            at(out, m * N + c) = v;
           }
         }
     }
-    cur = nxt;
-    __syncthreads();
+    if (!last) __syncthreads();
   }
 }
 
@@ -955,28 +988,32 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_bwd_kernel(Tiny p, const fl
 #pragma unroll
     for (int k = 0; k < 4 * MT; ++k) {
       const int m = k / 4 * 16 + 4 * q + k % 4;
-      r.gate[k] = stash[p.offA[i] + (unsigned)((m < p.mb ? m : p.mb - 1) * K + cc)];
+      r.gate[k] = at(stash, p.offA[i] + (m < p.mb ? m : p.mb - 1) * K + cc);
     }
   };
   // dW_i = a_i^T d_i and db_i = column sums of d_i (a row K of ones below a_i): 16x16 tiles dealt out over all waves
-  auto offset = [&](int i, int t, int r) -> size_t {
-    const int K = p.dim[i], N = p.dim[i + 1], tn = (N + 15) / 16, k = t / tn * 16 + 4 * q + r, c = t % tn * 16 + (l & 15);
-    const int cc = c < N ? c : N - 1;
-    return k < K ? p.offW[i] + (unsigned)(k * N + cc) : p.offB[i] + cc;
+  auto row = [&](int i, int t) -> int { return (unsigned)t * p.over[i] >> 16; };   // of tiles
+  auto offsets = [&](int i, int t, unsigned (&o)[4]) {     // of a lane's four results
+    const int K = p.dim[i], N = p.dim[i + 1], tn = (N + 15) / 16, tk = row(i, t), k = tk * 16 + 4 * q, c = (t - tk * tn) * 16 + (l & 15);
+    const unsigned cc = c < N ? c : N - 1, bias = p.offB[i] + cc, weight = p.offW[i] + k * N + cc;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) o[r] = k + r < K ? weight + r * N : bias;
   };
   auto request_grad = [&](TinyBwdReq<MT>& r, int i, int t) {
-    const int K = p.dim[i], N = p.dim[i + 1], tn = (N + 15) / 16, kr = t / tn * 16 + (l & 15);
+    const int K = p.dim[i], kr = row(i, t) * 16 + (l & 15);
 #pragma unroll
     for (int k = 0; k < 4 * MT; ++k) {
       const int m = 4 * k + q;
-      r.a[k] = stash[p.offA[i] + (unsigned)((m < p.mb ? m : p.mb - 1) * K + (kr < K ? kr : K - 1))];
+      r.a[k] = at(stash, p.offA[i] + (m < p.mb ? m : p.mb - 1) * K + (kr < K ? kr : K - 1));
     }
     if (u.w) {
+      unsigned o[4];
+      offsets(i, t, o);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) r.w[k] = u.w[offset(i, t, k)];
+      for (int k = 0; k < 4; ++k) r.w[k] = at(u.w, o[k]);
       if (u.vel) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) r.v[k] = u.vel[offset(i, t, k)];
+        for (int k = 0; k < 4; ++k) r.v[k] = at(u.vel, o[k]);
       }
     }
   };
@@ -987,11 +1024,21 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_bwd_kernel(Tiny p, const fl
   };
   auto first_chain = [&](int i) { return i == 0 ? me : wave; };
 
-  int tg = me;                                             // this wave's first tile of layer i (the deal goes on from layer to layer)
-  TinyBwdReq<MT> cur, nxt;
+  int first_grad[NL];                                      // this wave's first tile of layer i (the deal goes on from layer to layer)
 #pragma unroll
-  for (int k = 0; k < 4; ++k) { cur.w[k] = 0.f; cur.v[k] = 0.f; }
-  request(cur, NL - 1, first_chain(NL - 1), tg);
+  for (int i = NL - 1, t = me; i >= 0; --i) {
+    first_grad[i] = t;
+    t -= p.skip[i];
+    if (t < 0) t += waves;
+  }
+  constexpr int AHEAD = MT == 1 || (MT == 2 && NL == 2) ? 2 : 1;   // layers requested ahead (what the registers hold)
+  TinyBwdReq<MT> req[NL];
+#pragma unroll
+  for (int i = 0; i < NL; ++i)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) { req[i].w[k] = 0.f; req[i].v[k] = 0.f; }
+#pragma unroll
+  for (int i = NL - 1; i >= NL - AHEAD; --i) request(req[i], i, first_chain(i), first_grad[i]);
   tiny_rows<MT>(act, dout, p.mb, p.dim[NL]);
   __syncthreads();
 #pragma unroll
@@ -1000,10 +1047,9 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_bwd_kernel(Tiny p, const fl
     const int K = p.dim[i], N = p.dim[i + 1];
     const float* d = act + side * half;                    // dL/dz_i
     float* below = act + (side ^ 1) * half;
-    const int dp = tiny_pitch(N), bp = tiny_pitch(K), gt = grad_tiles(i);
-    const int tg_next = ((tg - gt) % waves + waves) % waves;
-    nxt = cur;
-    if (i > 0) request(nxt, i - 1, first_chain(i - 1), tg_next);
+    const int dp = tiny_pitch(N), bp = tiny_pitch(K), gt = grad_tiles(i), tg = first_grad[i];
+    TinyBwdReq<MT>& cur = req[i];
+    if (i >= AHEAD) request(req[i - AHEAD], i - AHEAD, first_chain(i - AHEAD), first_grad[i - AHEAD]);
     if (i > 0 || din) {
       const bool share = i == 0;
       const int tiles = (K + 15) / 16;
@@ -1018,13 +1064,13 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_bwd_kernel(Tiny p, const fl
           const int m = k / 4 * 16 + 4 * q + k % 4;
           const float v = acc[k / 4][k % 4];
           if (!share) below[m * bp + c] = m < p.mb && c < K && cur.gate[k] > 0.f ? v : 0.f;
-          else if (m < p.mb && c < K) din[m * K + c] = v;
+          else if (m < p.mb && c < K) at(din, m * K + c) = v;
         }
       }
     }
     for (int t = tg; t < gt; t += waves) {
       if (t != tg) request_grad(cur, i, t);
-      const int tn = (N + 15) / 16, kr = t / tn * 16 + (l & 15), c = t % tn * 16 + (l & 15);
+      const int tn = (N + 15) / 16, tk = row(i, t), kr = tk * 16 + (l & 15), c = (t - tk * tn) * 16 + (l & 15);
       f32x4 acc = 0.f;
       pin(cur.a); pin(cur.w); pin(cur.v);
 #pragma unroll
@@ -1032,28 +1078,28 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_bwd_kernel(Tiny p, const fl
         const float a = 4 * k + q < p.mb ? kr < K ? cur.a[k] : 1.f : 0.f;
         acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, d[(4 * k + q) * dp + c], acc, 0, 0, 0);
       }
+      unsigned to[4];
+      offsets(i, t, to);
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        if (c < N && t / tn * 16 + 4 * q + r <= K) {
-          const size_t o = offset(i, t, r);
-          u.grad[o] = acc[r];
+        if (c < N && tk * 16 + 4 * q + r <= K) {
+          const unsigned o = to[r];
+          at(u.grad, o) = acc[r];
           if (u.w) {
             float x = cur.w[r];
             if (u.vel) {
               const float v = next_velocity(u, x, cur.v[r], acc[r]);
-              u.vel[o] = v;
+              at(u.vel, o) = v;
               x = __fmaf_rn(-u.eta, v, x);
             } else {
               x = __fmaf_rn(-u.eta, acc[r], x);
             }
-            u.w[o] = x;
-            u.ver[o] = x;
+            at(u.w, o) = x;
+            at(u.ver, o) = x;
           }
         }
     }
-    tg = tg_next;
-    cur = nxt;
-    __syncthreads();
+    if (i > 0) __syncthreads();
   }
 }
 
@@ -1061,12 +1107,17 @@ int tiny_half(const rv_stage* s) {   // floats of one LDS activation buffer
   const int rows = (s->microbatch + 15) / 16;
   return 16 * (rows > 2 ? 4 : rows) * tiny_pitch((int)((MlpPlan*)s->impl)->maxw);
 }
-Tiny tiny_desc(const rv_stage* s) {
+Tiny tiny_desc(const rv_stage* s, int wgs) {
   const MlpPlan* p = (const MlpPlan*)s->impl;
   Tiny t = {};
   t.mb = s->microbatch; t.zero = (unsigned)s->P;
   for (int i = 0; i <= p->n; ++i) t.dim[i] = (int)s->dims[i];
   for (int i = 0; i < p->n; ++i) { t.offW[i] = (unsigned)p->offW[i]; t.offB[i] = (unsigned)p->offB[i]; t.offA[i] = (unsigned)p->offA[i]; }
+  for (int i = 0; i < p->n; ++i) {
+    const int tn = (t.dim[i + 1] + 15) / 16;
+    t.over[i] = (65536u + tn - 1) / tn;
+    t.skip[i] = (t.dim[i] + 16) / 16 * tn % (wgs * kTinyWaves);
+  }
   return t;
 }
 template <typename F>
@@ -1128,9 +1179,9 @@ rv_status rv_mlp_forward(rv_stage* s, rv_slot& slot, const void* in, void* out) 
   // a caller may hand the same buffer in and out: then nothing may be written before all of it is read
   const bool in_place = overlap(s, in, s->dims[0], out, s->dims[p->n]);
   if (p->tiny && !in_place) {
-    const Tiny t = tiny_desc(s);
     const int half = tiny_half(s), mt = (mb + 15) / 16;
     const int wgs = ((int)s->dims[p->n] + 16 * kTinyWaves - 1) / (16 * kTinyWaves);
+    const Tiny t = tiny_desc(s, wgs);
     const size_t lds = 2 * (size_t)half * 4;
     return tiny_by_shape(p->n, mt, [&](auto nl, auto m) -> rv_status {
       constexpr auto kern = tiny_fwd_kernel<decltype(nl)::value, decltype(m)::value>;
@@ -1171,11 +1222,11 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
   Upd u = {s->grad, nullptr, nullptr, nullptr, s->eta, s->momentum, s->weight_decay};
   if (s->fused) { u.w = s->master; u.vel = s->vel; u.ver = (float*)s->ver[s->upd_dst]; }
   if (p->tiny && !overlap(s, grad_out, s->dims[p->n], grad_in, s->dims[0])) {
-    const Tiny t = tiny_desc(s);
     const int half = tiny_half(s), mt = (mb + 15) / 16;
     int tiles = 0;
-    for (int i = 0; i < p->n; ++i) tiles += (t.dim[i] + 16) / 16 * ((t.dim[i + 1] + 15) / 16);
+    for (int i = 0; i < p->n; ++i) tiles += ((int)s->dims[i] + 16) / 16 * (((int)s->dims[i + 1] + 15) / 16);
     const int wgs = std::min(64, (tiles + kTinyWaves - 1) / kTinyWaves);
+    const Tiny t = tiny_desc(s, wgs);
     const size_t lds = 2 * (size_t)half * 4;
     return tiny_by_shape(p->n, mt, [&](auto nl, auto m) -> rv_status {
       constexpr auto kern = tiny_bwd_kernel<decltype(nl)::value, decltype(m)::value>;
