@@ -448,13 +448,14 @@ __device__ __forceinline__ void planes_walk(TileAcc<BT>& acc, const Prod& p, int
     for (int j = 0; j < T; ++j) acc[i][j] += low[i][j];
 }
 
-// BT: 128 or 64 (tiled), kHalves (64, by two halves of a workgroup), 32 (split over NT / 64 waves), kWave (a 32x32 tile per wave)
-constexpr int kWave = 1, kHalves = 2;
+// BT: 128 or 64 (tiled), kHalves (64, by two halves of a workgroup), 32 (split over NT / 64 waves), kSlim (the same, 32x16),
+// kWave (a 32x32 tile per wave)
+constexpr int kWave = 1, kHalves = 2, kSlim = 16;
 template <int BT, int NT, bool AKM, bool BKM> constexpr int mlp_lds_bytes() {
   if constexpr (BT == kHalves) return mlp_lds_bytes<64, NT, AKM, BKM>();
   else
   // (kWave: the bias sums beside it)
-  return 4 * (BT == kWave ? NT / 32 * 33 : BT == 32 ? NT / 64 * 32 * 33
+  return 4 * (BT == kWave ? NT / 32 * 33 : BT == 32 || BT == kSlim ? NT / 64 * 32 * 33
               : NT / 256 * std::max(Lds<AKM, BT>::FLOATS + Lds<BKM, BT>::FLOATS, kSlots * kSlotBytes<BT, AKM, BKM> / 4));
 }
 // A workgroup of 512 threads takes two tiles, side by side: both have the same number of steps and so of barriers; the last
@@ -612,6 +613,62 @@ __device__ __forceinline__ void split_body(const Prod& p, const Out& o, int tile
   f.complete(o, v);
 }
 
+// The same on 32x16 tiles, in products of 16x16: where 32x32 tiles leave half of the CUs without one.  A group is 16 deep, so
+// that a wave has a contraction of up to 1024 on the way at once and touches fewer lines to a request.
+template <bool AKM, bool BKM, int OP>
+__device__ __forceinline__ void slim_body(const Prod& p, const Out& o, int tile, float* smem) {
+  constexpr int NW = kSplitWaves, U = 4, P = 17;
+  const int m0 = tile / p.tiles_n * 32, n0 = tile % p.tiles_n * 16;
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, q = l >> 4;
+  const int ra0 = m0 + (l & 15) < p.M ? m0 + (l & 15) : p.M - 1, ra1 = m0 + 16 + (l & 15) < p.M ? m0 + 16 + (l & 15) : p.M - 1;
+  const int rb = n0 + (l & 15) < p.N ? n0 + (l & 15) : p.N - 1;
+  const int ng = (p.K + 15) / 16, whole = p.K / 16;
+  f32x4 fa[2][U][2], fb[2][U];
+  auto request = [&](int set, int g0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int g = g0 + u * NW;                  // wave-uniform
+      fa[set][u][0] = 0.f; fa[set][u][1] = 0.f; fb[set][u] = 0.f;
+      if (g < ng) {
+        fa[set][u][0] = direct_frag<AKM>(p.A, p.lda, ra0, 16 * g + 4 * q, p.K, g < whole);
+        fa[set][u][1] = direct_frag<AKM>(p.A, p.lda, ra1, 16 * g + 4 * q, p.K, g < whole);
+        fb[set][u] = direct_frag<BKM>(p.B, p.ldb, rb, 16 * g + 4 * q, p.K, g < whole);
+      }
+    }
+  };
+  const int ml = threadIdx.x >> 4, nl = threadIdx.x & 15;   // one result to a thread
+  const int m[1] = {m0 + ml};
+  Finish<OP, 1> f;
+  request(0, wave);
+  if (wave + U * NW < ng) request(1, wave + U * NW);
+  f.request(o, m, n0 + nl, p.M, p.N);
+  f32x4 acc[2] = {0.f, 0.f};
+  auto products = [&](int set) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[set][u][t][e], fb[set][u][e], acc[t], 0, 0, 0);
+  };
+  for (int g0 = wave; g0 < ng; g0 += 2 * U * NW) {
+    products(0);
+    if (g0 + 2 * U * NW < ng) request(0, g0 + 2 * U * NW);
+    if (g0 + U * NW >= ng) break;
+    products(1);
+    if (g0 + 3 * U * NW < ng) request(1, g0 + 3 * U * NW);
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) smem[(wave * 32 + 16 * t + 4 * q + r) * P + (l & 15)] = acc[t][r];
+  __syncthreads();
+  float v[1] = {smem[ml * P + nl]};
+#pragma unroll
+  for (int w = 1; w < NW; ++w) v[0] += smem[(w * 32 + ml) * P + nl];
+  f.complete(o, v);
+}
+
 // ---- one wave per tile ---------------------------------------------------------------------
 // A short contraction behind a thin result (see pick): a 32x32 tile per wave straight from its accumulators,
 // nothing to add up between waves, no LDS, no barrier.  What bounds it is the results' own memory traffic.
@@ -692,6 +749,8 @@ template <int BT, int NT, bool AKM, bool BKM, int OP>
 __device__ __forceinline__ void mlp_body(const Prod& p, const Out& o, int tile, float* smem) {
   if constexpr (BT == kWave) {
     wave_body<NT, AKM, BKM, OP>(p, o, tile);
+  } else if constexpr (BT == kSlim) {
+    slim_body<AKM, BKM, OP>(p, o, tile, smem);
   } else if constexpr (BT == 32) {
     split_body<NT / 64, AKM, BKM, OP>(p, o, tile, smem);
   } else if constexpr (BT == kHalves) {
@@ -741,7 +800,8 @@ __global__ __launch_bounds__(NT, 2) void mlp_bwd_kernel(Prod dx, Out ox, Prod dw
 }
 
 Prod product(const float* A, int lda, const float* B, int ldb, int M, int N, int K, int bt, int nt) {
-  const int edge = bt == kWave ? 32 : bt == kHalves ? 64 : bt, tn = (N + edge - 1) / edge, tiles = (M + edge - 1) / edge * tn, waves = nt / 64;
+  const int edge = bt == kWave || bt == kSlim ? 32 : bt == kHalves ? 64 : bt, en = bt == kSlim ? 16 : edge;
+  const int tn = (N + en - 1) / en, tiles = (M + edge - 1) / edge * tn, waves = nt / 64;
   const int per = bt == kWave ? waves : bt > 32 ? nt / 256 : 1;   // tiles a workgroup (kHalves: 1)
   return Prod{A, B, lda, ldb, M, N, K, tn, (tiles + per - 1) / per};   // (tiles: workgroups)
 }
@@ -763,7 +823,12 @@ int pick(int M, int N, int K) {
   if (thin <= 32 && tile_count(M, N, 64) >= kCUs / 2) return K <= 128 ? kWave : 32;
   return thin > 64 && tile_count(M, N, 128) >= kCUs ? 128 : tile_count(M, N, 64) >= kCUs / 2 ? 64 : 32;
 }
-int threads(int bt) { return bt == 32 || bt == kHalves ? 64 * kSplitWaves : 256; }
+// 32x16 tiles where 32x32 ones leave CUs without one: a forward product up to half of them, an input gradient up to a quarter, for the
+// weight gradient's tiles come beside it.  us, 32x32 / 32x16: forward 1000 -> 1000 on 100 rows 10.5 / 8.8, 4096 -> 256 on 16 29.1 / 19.4,
+// 128 -> 128 on 64 6.9 / 5.2; backward 300 -> 1000 on 100 rows 11.1 / 9.1, 256 -> 4000 on 20 31.4 / 22.9, 128 -> 128 on 64 5.0 / 4.7;
+// past the quarter 200 -> 200 on 500 rows 7.3 / 8.9, 1000 -> 1000 on 100 15.6 / 19.7, 1000 -> 77 on 100 5.3 / 7.7.
+bool slim(int M, int N, int bt, int cus) { return bt == 32 && tile_count(M, N, 32) <= cus; }
+int threads(int bt) { return bt == 32 || bt == kSlim || bt == kHalves ? 64 * kSplitWaves : 256; }
 
 template <typename K>
 rv_status allow_lds(K kern, int bytes) {
@@ -1197,6 +1262,7 @@ rv_status rv_mlp_forward(rv_stage* s, rv_slot& slot, const void* in, void* out) 
     const bool last = i == p->n - 1, first = i == 0 && !copy_first;
     const int K = (int)s->dims[i], N = (int)s->dims[i + 1];
     int bt = pick(mb, N, K);
+    if (slim(mb, N, bt, kCUs / 2)) bt = kSlim;
     if (bt == 64 && tile_count(mb, N, 64) <= kCUs && K >= 256) bt = kHalves;   // one tile to a CU; shorter walks are mostly beginning
     const Prod pr = product(first ? (const float*)in : stash + p->offA[i], K, w + p->offW[i], N, mb, N, K, bt, threads(bt));
     Out o = {};
@@ -1205,6 +1271,7 @@ rv_status rv_mlp_forward(rv_stage* s, rv_slot& slot, const void* in, void* out) 
     const rv_status rc = bt == 128  ? launch_fwd<128, 256>(s->st, pr, o, copy)
                          : bt == 64 ? launch_fwd<64, 256>(s->st, pr, o, copy)
                          : bt == kWave ? launch_fwd<kWave, 256>(s->st, pr, o, copy)
+                         : bt == kSlim ? launch_fwd<kSlim, 64 * kSplitWaves>(s->st, pr, o, copy)
                          : bt == kHalves ? launch_fwd<kHalves, 512>(s->st, pr, o, copy)
                                     : launch_fwd<32, 64 * kSplitWaves>(s->st, pr, o, copy);
     RV_TRY(rc);
@@ -1253,7 +1320,8 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
     // 64x64 weight-gradient tiles beside an input gradient whose walk is dealt out over eight waves: two to a workgroup
     const int bx = pick(mb, K, N), bw = pick(K, N, mb);
     const int nt = std::max(bx, bw) == 32 || (bx == 32 && bw == 64) ? threads(32) : 256;
-    Prod px = product(d, N, w + p->offW[i], N, mb, K, N, bx, nt);
+    const int form = nt == threads(32) && want_dx && slim(mb, K, bx, kCUs / 4) ? kSlim : bx;
+    Prod px = product(d, N, w + p->offW[i], N, mb, K, N, form, nt);
     const Prod pw = product(a, K, d, N, K, N, mb, bw, nt);
     if (!want_dx) px.tiles = 0;
     Out ox = {}, ow = {};
@@ -1265,10 +1333,13 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
     // 49 instead of 23 at 4096 -> 1024 on 8 rows, 188 / 87 at 4096 -> 4096 on 16, 273 / 98 on 64.
     auto by_bw = [&](auto x) {
       constexpr int BX = decltype(x)::value, NT = BX <= 32 ? 64 * kSplitWaves : 256;
+      if constexpr (BX == kSlim)
+        return bw == 64 ? go(launch_bwd<BX, 64, NT>) : bw == 32 ? go(launch_bwd<BX, 32, NT>) : go(launch_bwd<BX, kWave, NT>);
+      else
       return bw == 128 ? go(launch_bwd<BX, 128, 256>) : bw == 64 ? go(launch_bwd<BX, 64, BX == 32 ? NT : 256>)
              : bw == 32 ? go(launch_bwd<BX, 32, NT>) : go(launch_bwd<BX, kWave, BX == 32 ? NT : 256>);
     };
-    const rv_status rc = bx == 128 ? by_bw(Int<128>()) : bx == 64 ? by_bw(Int<64>()) : bx == 32 ? by_bw(Int<32>()) : by_bw(Int<kWave>());
+    const rv_status rc = form == kSlim ? by_bw(Int<kSlim>()) : bx == 128 ? by_bw(Int<128>()) : bx == 64 ? by_bw(Int<64>()) : bx == 32 ? by_bw(Int<32>()) : by_bw(Int<kWave>());
     RV_TRY(rc);
     if (want_dx) d = dst;
   }

@@ -381,3 +381,13 @@ def test_gradients_near_the_smallest_numbers(scale):
     up = 1.0 / scale                       # (the comparison's own squares would underflow)
     close(dx * up, dxo * up, 1e-5, "t", group="MLP near the smallest numbers, bar 1e-5")
     close(host64(g.last_grad()) * up, o.last_grad * up, 1e-5, "t", group="MLP near the smallest numbers, bar 1e-5")
+
+
+# 32x16 tiles: contractions of less than a group of 16, exactly one per wave, one more, both sets of requests exactly, a third begun; the
+# last row and column counts on each side of a tile's edge; forward and input gradient at the limits of the rule and one past them
+@pytest.mark.parametrize("dims,mb", [([K, 40], 33) for K in (7, 128, 129, 1024, 1025)] + [([300, 17], 32), ([300, 16], 65), ([31, 600], 70),
+                                     ([40, 4096], 17), ([2048, 300], 9), ([2049, 300], 9), ([300, 4097], 9)])
+def test_slim_tiles(dims, mb):
+    """Bar as test_product_forms_at_their_edges."""
+    test_product_forms_at_their_edges(dims, mb, 0.0)
+    test_product_forms_at_their_edges(dims, mb, 0.9)
