@@ -316,7 +316,8 @@ __device__ __forceinline__ bf16x8 plane_frag(const char* s, int row0, int plane)
 template <int BT, bool AKM, bool BKM> constexpr int kSlotBytes = 3 * (Planes<AKM, BT>::BYTES + Planes<BKM, BT>::BYTES);
 
 // While step s is multiplied, step s + 2 goes into the slot that step s - 1 was read from and step s + 2 + D is requested (D steps
-// are on the way, what the registers hold): one barrier a step.  Fragments have one set of registers: the order of the products lets those of pieces 1 and 2 be read anew behind
+// are on the way: on 128x128 tiles what the registers hold; on 64x64 ones 8 in place of 4 are no faster on long walks and make
+// the code longer, 129 -> 3001 on 300 rows backward 33 us in place of 20): one barrier a step.  Fragments have one set of registers: the order of the products lets those of pieces 1 and 2 be read anew behind
 // the last products of the step before, those of piece 0 behind the first of their own.  Two workgroups share a CU.
 template <int BT, bool AKM, bool BKM>
 __device__ __forceinline__ void planes_walk(TileAcc<BT>& acc, const Prod& p, int m0, int n0, char* smem) {
@@ -327,7 +328,7 @@ __device__ __forceinline__ void planes_walk(TileAcc<BT>& acc, const Prod& p, int
   for (int i = 0; i < T; ++i)
 #pragma unroll
     for (int j = 0; j < T; ++j) { acc[i][j] = 0.f; low[i][j] = 0.f; }
-  constexpr int D = T == 2 ? 2 : 8;
+  constexpr int D = T == 2 ? 2 : 4;
   f32x4 va[D][Planes<AKM, BT>::PIECES], vb[D][Planes<BKM, BT>::PIECES];   // step s in set s % D
   unsigned oa[Planes<AKM, BT>::PIECES], ob[Planes<BKM, BT>::PIECES];
   plane_offsets<AKM, BT>(p.lda, m0, p.M, oa);
@@ -826,7 +827,8 @@ int pick(int M, int N, int K) {
 // 32x16 tiles where 32x32 ones leave CUs without one: a forward product up to half of them, an input gradient up to a quarter, for the
 // weight gradient's tiles come beside it.  us, 32x32 / 32x16: forward 1000 -> 1000 on 100 rows 10.5 / 8.8, 4096 -> 256 on 16 29.1 / 19.4,
 // 128 -> 128 on 64 6.9 / 5.2; backward 300 -> 1000 on 100 rows 11.1 / 9.1, 256 -> 4000 on 20 31.4 / 22.9, 128 -> 128 on 64 5.0 / 4.7;
-// past the quarter 200 -> 200 on 500 rows 7.3 / 8.9, 1000 -> 1000 on 100 15.6 / 19.7, 1000 -> 77 on 100 5.3 / 7.7.
+// past the quarter 200 -> 200 on 500 rows 7.3 / 8.9, 1000 -> 1000 on 100 15.6 / 19.7, 1000 -> 77 on 100 5.3 / 7.7; of a contraction below
+// 128, 100 -> 100 on 300 rows 6.5 / 6.9.
 bool slim(int M, int N, int bt, int cus) { return bt == 32 && tile_count(M, N, 32) <= cus; }
 int threads(int bt) { return bt == 32 || bt == kSlim || bt == kHalves ? 64 * kSplitWaves : 256; }
 
@@ -1320,7 +1322,7 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
     // 64x64 weight-gradient tiles beside an input gradient whose walk is dealt out over eight waves: two to a workgroup
     const int bx = pick(mb, K, N), bw = pick(K, N, mb);
     const int nt = std::max(bx, bw) == 32 || (bx == 32 && bw == 64) ? threads(32) : 256;
-    const int form = nt == threads(32) && want_dx && slim(mb, K, bx, kCUs / 4) ? kSlim : bx;
+    const int form = nt == threads(32) && want_dx && N >= 128 && slim(mb, K, bx, kCUs / 4) ? kSlim : bx;
     Prod px = product(d, N, w + p->offW[i], N, mb, K, N, form, nt);
     const Prod pw = product(a, K, d, N, K, N, mb, bw, nt);
     if (!want_dx) px.tiles = 0;
