@@ -17,8 +17,7 @@
 //   dX       dx = dy W^T   : A = dy k-contiguous, B = W  k-contiguous (its rows are the n's)
 //   dW       dW = x^T dy   : A = x  k-major,      B = dy k-major      (contraction over tokens)
 //
-// Tiling: a workgroup of 4 or 8 waves owns a BM x BN tile and walks K in steps of BK (32 or
-// 64); a wave owns a block of MFMA products (v_mfma_f32_32x32x16_bf16 or _16x16x32_bf16).  Operand tiles go
+// Tiling: a workgroup of 4 or 8 waves owns a BM x BN tile and walks K in steps of BK = 32; a wave owns a block of MFMA products (v_mfma_f32_32x32x16_bf16 or _16x16x32_bf16).  Operand tiles go
 // global -> LDS directly (global_load_lds_dwordx4) through a ring of NS stages, unpadded, bank
 // conflicts removed by an XOR swizzle (see "direct-to-LDS pipeline" below);
 //   k-contiguous operands sit in LDS as [row][BK k], read as one 16-byte fragment per lane;
@@ -316,8 +315,8 @@ __device__ __forceinline__ void write_tile_staged(const V (&acc)[TM][TN], const 
       for (int c = 0; c < Q; ++c) {
         f32x4 v;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = kEdge<V> == 32 ? rv_half_wave_sum(cs[c][k]) : rv_row_sum(cs[c][k]);
-        if ((l & (kEdge<V> - 1)) == 0) *reinterpret_cast<f32x4*>(red + (wm0 ? BN : 0) + wn0 + quad_col<V>(c)) = v;
+        for (int k = 0; k < 4; ++k) v[k] = rv_row_sum(cs[c][k]);
+        if ((l & 15) == 0) *reinterpret_cast<f32x4*>(red + (wm0 ? BN : 0) + wn0 + quad_col<V>(c)) = v;
       }
     }
     __syncthreads();
@@ -359,11 +358,10 @@ __device__ __forceinline__ void write_tile_staged(const V (&acc)[TM][TN], const 
 //                                 (fragments of 16 rows) or 64 bytes of rows k .. k + 3 (of 32): physical chunk =
 //                                 c ^ ((k & 3) << 2) ^ ((k & 8) >> 2); split forms with 64 columns (fragments of 32 rows),
 //                                 two rows to a 256-byte bank line, c ^ ((k & 2) << 1)
-// NS stages form a ring.  Plain form (four-wave tiles): the loads of tile t+NS-1 are issued
-// right after the barrier that opens tile t.  Pipelined form (the eight-wave 256x256 tile): see
-// gemm_dtl_body - the products are bound by how fast operand tiles arrive, inside a stage step
+// NS stages form a ring (see gemm_dtl_body): the products are bound by how fast operand tiles arrive, inside a stage step
 // even more than alone (with seven of eight MFMAs taken out the step is 3 % shorter, without
-// the loads 24 %), so that tile keeps three 32-deep tiles in flight instead of one 64-deep one.
+// the loads 24 %), so a workgroup keeps two or three 32-deep tiles in flight.  (One 64-deep tile, requested behind the barrier
+// that opens the one before, on the four-wave tiles: 10 - 20 % slower alone, 4 blocks of d 1024 on 4096 tokens 1796 / 1747 us a step.)
 __host__ __device__ constexpr int dtl_tile_bytes(int rows, int bk) { return rows * bk * 2; }
 
 template <int ROWS>
@@ -394,25 +392,6 @@ __device__ __forceinline__ void dtl_init(Dtl<KM, ROWS, BK, NW>& s, int64_t ld, i
       col = col < rows ? col : rows - 8;
       s.off[i] = kr * (int)ld + (col >> 5) * (int)bs + (col & 31);
     }
-  }
-}
-
-template <bool KM, int ROWS, int BK, int NW>
-__device__ __forceinline__ void dtl_issue(const Dtl<KM, ROWS, BK, NW>& s, const uint16_t* __restrict__ g,
-                                          int64_t ld, int64_t bs, int k0, char* lds, int wave) {
-  const uint16_t* base = KM ? g + (int64_t)k0 * ld : g + (k0 >> 5) * bs;
-#pragma unroll
-  for (int i = 0; i < Dtl<KM, ROWS, BK, NW>::N; ++i) {
-    // LDS byte address of this wave's 1 KiB block (wave-uniform, goes to M0; the hardware
-    // adds 16 * lane).  Issued as inline assembly: the compiler would otherwise make every
-    // later LDS read wait for ALL outstanding loads, which defeats the ring.  The kernel
-    // orders them itself with explicit vmcnt waits and barriers.
-    const int m0v = __builtin_amdgcn_readfirstlane((int)(size_t)lds + (i * NW + wave) * 1024);
-    const uint16_t* src = base + s.off[i];
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :
-                 : "v"(src), "s"(m0v)
-                 : "memory", "m0");
   }
 }
 
@@ -463,6 +442,8 @@ __device__ __forceinline__ bf16x8 dtl_frag32(const char* lds, int row0, int kk) 
   }
 }
 
+// Issued as inline assembly: the compiler would otherwise make every later LDS read wait for ALL outstanding loads, which
+// defeats the ring.  The kernels order them with explicit vmcnt waits and barriers.
 // Direct-to-LDS load in the scalar-base form: wave-uniform 64-bit base in SGPRs, per-lane byte
 // offset in one VGPR (no per-load address arithmetic), LDS block = lb + IMM through M0.
 __device__ __forceinline__ void dtl_load_s(const void* base, unsigned off, int m0v) {
@@ -580,19 +561,14 @@ template <int BM, int BN, int BK, int NS, int NW, bool AKM, bool BKM, int EPI>
 __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, int64_t lda, int64_t a_bs,
                                               const uint16_t* __restrict__ B, int64_t ldb, int64_t b_bs, int M, int N,
                                               int K, int bm, int bn, const Epi& e) {
-  // The eight-wave 256x256 tile runs the pipelined ring below, on products of 16x16: with those the matrix cores do 1717
-  // TFLOP/s out of LDS at the board's power cap, with 32x32 ones 1586 (registers alone 2028 / 1807; half the accumulator
-  // traffic per flop).  The four-wave tiles keep the plain ring (loads of tile t+NS-1 right after the barrier that
-  // opens tile t) and 32x32, of which they need half as many instructions: 4096x1024x4096 on 128x128 tiles 43.7 against 46.0 us.
-  constexpr bool PIPELINED = NW == 8 && BM == 256 && BN == 256;
-  typedef std::conditional_t<PIPELINED, f32x4, f32x16> V;
+  // Products of 16x16: the matrix cores do 1717 TFLOP/s out of LDS at the board's power cap with those, 1586 with 32x32 ones
+  // (registers alone 2028 / 1807; half the accumulator traffic per flop).
   // NW waves laid out 2 (m) x NW/2 (n)
-  constexpr int WM = BM / 2, WN = BN / (NW / 2), TM = WM / kEdge<V>, TN = WN / kEdge<V>, KSTEPS = PIPELINED ? BK / 32 : BK / 16;
+  typedef f32x4 V;
+  constexpr int WM = BM / 2, WN = BN / (NW / 2), TM = WM / 16, TN = WN / 16;
   constexpr int A_BYTES = dtl_tile_bytes(BM, BK), B_BYTES = dtl_tile_bytes(BN, BK);
   constexpr int BUF = A_BYTES + B_BYTES;
   constexpr int NL = NW;                                                    // loader waves per tile
-  constexpr int LPT = Dtl<AKM, BM, BK, NL>::N + Dtl<BKM, BN, BK, NL>::N;   // loads per lane per tile
-  static_assert(LPT * (NS - 2) < 64, "vmcnt range");
   char* smem = dtl_smem;
 
   const int m0 = bm * BM, n0 = bn * BN;
@@ -611,7 +587,7 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
   dtl_init<AKM, BM, BK, NL>(da, lda, a_bs, m0, M, lw);
   dtl_init<BKM, BN, BK, NL>(db, ldb, b_bs, n0, N, lw);
   const int nk = K / BK;
-  if constexpr (PIPELINED) {
+  {
     // Ring of NS slots, the slot hand-over INSIDE a k-tile.  A tile is one step of 32 in k, multiplied in two halves: the upper
     // TM / 2 rows of fragments, column by column, then the lower ones.  Between the halves (all fragments of the tile are
     // in registers) the workgroup meets once: tile s+1 has landed and nobody reads tile s's slot any more.  Behind
@@ -621,7 +597,7 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
     // tile boundary.
     constexpr int NA = Dtl<AKM, BM, BK, NL>::N, NB = Dtl<BKM, BN, BK, NL>::N, LPS = NA + NB;
     constexpr int HM = TM / 2, STRIDE = HM * TN / LPS; // MFMAs per load in the lower half
-    static_assert(KSTEPS == 1 && TM % 2 == 0 && STRIDE >= 1 && STRIDE * LPS == HM * TN, "loads are dealt out evenly behind the MFMAs of the lower half");
+    static_assert(BK == 32 && TM % 2 == 0 && STRIDE >= 1, "a load behind every STRIDE MFMAs of the lower half");
     static_assert((NS - 1) * LPS < 64, "vmcnt range");
     unsigned oa[NA], ob[NB];               // per-lane byte offsets of this wave's loads inside a tile
 #pragma unroll
@@ -702,7 +678,7 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
           __builtin_amdgcn_sched_barrier(0);
           if (has_next && j == 0) fa[i] = dtl_frag<AKM, BM, BK>(nxt, wm0 + i * 16, 0);
           const int m = j * HM + i;
-          if (has_load && m % STRIDE == STRIDE - 1) {
+          if (has_load && m % STRIDE == STRIDE - 1 && m / STRIDE < LPS) {
             const int q = m / STRIDE;
             if (q < NA) dtl_load_s(pa, oa[q], lb + q * NL * 1024);
             else dtl_load_s(pb, ob[q - NA], lb + A_BYTES + (q - NA) * NL * 1024);
@@ -736,67 +712,13 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
     upper_half(smem + slot * BUF);
     lower_half(no, nullptr, no, nullptr, nullptr, 0);
     }
-  } else {
-#pragma unroll
-    for (int t = 0; t < NS - 1; ++t)
-      if (t < nk) {
-        dtl_issue<AKM, BM, BK, NL>(da, A, lda, a_bs, t * BK, smem + t * BUF, lw);
-        dtl_issue<BKM, BN, BK, NL>(db, B, ldb, b_bs, t * BK, smem + t * BUF + A_BYTES, lw);
-      }
-    int stage = 0;               // ring slot of tile `it`
-    int fill = NS - 1;           // ring slot the next issued tile goes to
-    for (int it = 0; it < nk; ++it) {
-      // tile `it` has landed once at most the loads of the newer tiles are outstanding
-      const int newer = nk - 1 - it;
-      if (NS >= 4 && newer >= NS - 2) RV_WAIT_VMCNT(LPT * (NS - 2));
-      else if (NS >= 3 && newer >= 1) { if (NS >= 4 && newer >= 2) RV_WAIT_VMCNT(LPT * 2); else RV_WAIT_VMCNT(LPT * 1); }
-      else RV_WAIT_VMCNT(0);
-      __syncthreads();           // everyone's part of tile `it` is in LDS; everyone left tile it-1
-      if (it + NS - 1 < nk) {
-        dtl_issue<AKM, BM, BK, NL>(da, A, lda, a_bs, (it + NS - 1) * BK, smem + fill * BUF, lw);
-        dtl_issue<BKM, BN, BK, NL>(db, B, ldb, b_bs, (it + NS - 1) * BK, smem + fill * BUF + A_BYTES, lw);
-      }
-      const char* curA = smem + stage * BUF;
-      const char* curB = curA + A_BYTES;
-      bf16x8 fa[2][TM], fb[2][TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) fa[0][i] = dtl_frag32<AKM, BM, BK>(curA, wm0 + i * 32, 0);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) fb[0][j] = dtl_frag32<BKM, BN, BK>(curB, wn0 + j * 32, 0);
-#pragma unroll
-      for (int kk = 0; kk < KSTEPS; ++kk) {
-        if (kk + 1 < KSTEPS) {
-#pragma unroll
-          for (int i = 0; i < TM; ++i) fa[(kk + 1) & 1][i] = dtl_frag32<AKM, BM, BK>(curA, wm0 + i * 32, kk + 1);
-#pragma unroll
-          for (int j = 0; j < TN; ++j) fb[(kk + 1) & 1][j] = dtl_frag32<BKM, BN, BK>(curB, wn0 + j * 32, kk + 1);
-        }
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kk & 1][j], fa[kk & 1][i], acc[i][j], 0, 0, 0);
-        if (kk + 1 < KSTEPS) {
-          constexpr int NREAD = (AKM ? 2 : 1) * TM + (BKM ? 2 : 1) * TN;
-          constexpr int NMFMA = TM * TN;
-          constexpr int PER = NMFMA / NREAD > 0 ? NMFMA / NREAD : 1;
-#pragma unroll
-          for (int g = 0; g < NREAD; ++g) {
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, PER, 0);
-          }
-        }
-      }
-      stage = stage + 1 == NS ? 0 : stage + 1;
-      fill = fill + 1 == NS ? 0 : fill + 1;
-    }
   }
   if constexpr (staged_epi(EPI)) {
     write_tile_staged<BM, BN, 64 * NW, V, TM, TN, EPI>(acc, e, m0, n0, wm0, wn0, M, N, smem);
   } else if constexpr (EPI == EPI_F32_UPD) {
     if (e.upd_w) f32_tile_through_lds<BM, BN, NW, V, TM, TN, 0, true>(acc, e, m0, n0, wm0, wn0, M, N, smem);   // workgroup-uniform
     else write_tile<V, TM, TN, EPI>(acc, e, m0 + wm0, n0 + wn0, M, N);
-  } else if constexpr (epi_has_resid(EPI) && PIPELINED && RV_RESID_LDS) {
+  } else if constexpr (epi_has_resid(EPI) && NW == 8 && RV_RESID_LDS) {
     f32_tile_through_lds<BM, BN, NW, V, TM, TN, 1, EPI == EPI_F32_BIAS_RESID_BF16>(acc, e, m0, n0, wm0, wn0, M, N, smem);
   } else {
     write_tile<V, TM, TN, EPI>(acc, e, m0 + wm0, n0 + wn0, M, N);
@@ -1189,16 +1111,18 @@ rv_status pick_part(const rv_gemm_args& g, int S, float* part, hipStream_t st) {
 //   5256  256x256, eight waves of 128x64, BK 32, ring of four slots run in the pipelined form
 //         (three tiles in flight, loads dealt out behind the MFMAs), one workgroup per CU:
 //         lowest LDS traffic per MFMA, two waves per SIMD cover each other's stalls;
-//   2192  128x256, four waves of 64x128, BK 32, three stages, two workgroups per CU;
-//   2128  128x128, four waves of 64x64, BK 64, two stages, two workgroups per CU;
+//   2192  128x256, four waves of 64x128, ring of three slots, two workgroups per CU;
+//   2128  128x128, four waves of 64x64, ring of four slots, two workgroups per CU;
 //   1128  128x128, 1065 / 1064 64x64, 1032 32x64: the contraction split inside the workgroup over
 //         2, 2 / 4 and 8 groups of waves.
 // The automatic choice among the first three minimises  rounds * tile area * workgroups per CU / efficiency,
 // rounds = ceil(tiles / (256 CUs * workgroups per CU)), efficiencies measured ratios: over 309 launches of 256 .. 8192 rows
-// alone on average 0.3 % above the best of the three; with 0.85 for 2128 the rule takes 132 us for 8192x4800x1600 instead of 121.
+// alone on average 0.3 % above the best of the three before 2192 and 2128 had the pipelined ring (us, bound loads / ring: 4096x1024x4096
+// 2128 43.7 / 38.0, 4096x6144x2048 2192 116 / 98, 8192x1600x6400 2192 189 / 154; 5256 75, 103, 150): 2192 0.92 -> 0.98.
 // Whether the contraction is split is decided by the modelled time, us,
 //   rounds * (f + turns * t) + out * M N / 1e6,  turns = k-tiles per group,
-// t between t0 (a launch that leaves most CUs idle) and t1 (one that fills them), fitted to 488 launches of 64 .. 8192 rows
+// t between t0 (a launch that leaves most CUs idle) and t1 (one that fills them; with 2192 and 2128 as they were before the pipelined ring:
+// with 0.88 of their times four microbatches of 6 blocks of d 768, 1152 tokens take 0.2 - 0.5 % longer), fitted to 488 launches of 64 .. 8192 rows
 // alone, operands in blocks of columns, weights cold.  A product of few tiles is one walk along K: 256x448x1792 takes 43 us
 // with 5256, 22 with 2128 and 7 with 1032; 512x4096x1024 with GELU' 32 / 17 / 11 (1065); 1152x768x3072 65 / 36 / 14 (1064);
 // 1152x2048x8192 152 / 108 / 72 (1128); 2048x1024x4096 82 / 44 / 29 (1065); 8192x6400x1600 183 / 204 / 261.
@@ -1225,7 +1149,7 @@ int in_order_form(int M, int N) {
     const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
     return (double)((tiles + 256 * bpc - 1) / (256 * bpc)) * bm * bn * bpc / eff;
   };
-  const double c256 = cost(256, 256, 1, 1.0), c192 = cost(128, 256, 2, 0.92), c128 = cost(128, 128, 2, 0.83);
+  const double c256 = cost(256, 256, 1, 1.0), c192 = cost(128, 256, 2, 0.98), c128 = cost(128, 128, 2, 0.83);
   return c256 <= c192 && c256 <= c128 ? 5256 : c192 <= c128 ? 2192 : 2128;
 }
 // the form of a whole product where nobody shares the chip, and its modelled time (k32: form 1032 is there)
@@ -1262,7 +1186,7 @@ rv_status pick_tile(const rv_gemm_args& g, hipStream_t st) {
   if (tile == 1128) return launch_split<128, 128, 2, 4, 4, AKM, BKM, EPI>(g, st);
   if (tile == 2256) return launch_dtl<256, 256, 32, 4, 4, 1, AKM, BKM, EPI>(g, st);
   if (tile == 2192) return launch_dtl<128, 256, 32, 3, 4, 2, AKM, BKM, EPI>(g, st);
-  if (tile == 2128) return launch_dtl<128, 128, 64, 2, 4, 2, AKM, BKM, EPI>(g, st);
+  if (tile == 2128) return launch_dtl<128, 128, 32, 4, 4, 2, AKM, BKM, EPI>(g, st);
   if (tile == 5256) return launch_dtl<256, 256, 32, 4, 8, 2, AKM, BKM, EPI>(g, st);
   return RV_E_INVAL;
 }

@@ -104,6 +104,29 @@ def test_ring_depths_of_the_256_tile(K):
     assert torch.equal(g32, o32)
 
 
+# the other tiles on the same ring, of three or four slots: fewer 32-deep tiles than slots, exactly as many, more
+@pytest.mark.parametrize("tile", [2128, 2192, 2256])
+@pytest.mark.parametrize("K", [64, 128, 192, 256, 576])
+def test_ring_depths_of_the_other_tiles(K, tile):
+    """The bars of test_ring_depths_of_the_256_tile, on an output ragged for each of the tiles, one wave of which has nothing to
+    multiply."""
+    from paper_2401_01728_amd import kernels as k
+    M, N = 328, 328
+    x, x64 = bf16_normal(12, 0, (M, K)); w, w64 = bf16_normal(12, 1, (K, N), std=0.05)
+    b, b64 = bf16_normal(12, 2, (N,), std=0.5)
+    o = _out((M, N), torch.bfloat16)
+    k.gemm_bf16(x, 0, w, 1, M, N, K, k.EPI_BF16_BIAS, o, bias=b, tile=tile)
+    close(host64(o), x64 @ w64 + b64, 4e-3, "gemm", group=GROUP[4e-3])
+    wt, wt64 = bf16_normal(12, 3, (N, K), std=0.05)
+    o = _out((M, N), torch.bfloat16)
+    k.gemm_bf16(x, 0, wt, 0, M, N, K, k.EPI_BF16, o, tile=tile)
+    close(host64(o), x64 @ wt64.T, 4e-3, "gemm", group=GROUP[4e-3])
+    xt, xt64 = bf16_normal(12, 4, (K, M)); dy, dy64 = bf16_normal(12, 5, (K, N), std=1e-2)
+    o32 = _out((M, N), torch.float32)
+    k.gemm_bf16(xt, 1, dy, 1, M, N, K, k.EPI_F32, o32, tile=tile)
+    close(host64(o32), xt64.T @ dy64, 1e-5, "gemm", group=GROUP[1e-5])
+
+
 def test_strided_operands_and_rejects():
     """Operands that are column blocks of wider matrices (pitch > width), as q|k|v are."""
     from paper_2401_01728_amd import kernels as k
