@@ -32,11 +32,12 @@ __device__ __forceinline__ unsigned rv_ver_tile(unsigned block, unsigned blocks)
   const unsigned whole = blocks / 256 * 256;
   return block < whole ? block / 256 * 256 + block % 8 * 32 + block % 256 / 8 : block;
 }
-// copy_kind: 0 none, 1 bf16 bits, 2 fp32, 3 bf16 bits through `map`
+// copy_kind: 0 none, 1 bf16 bits, 2 fp32, 3 bf16 bits through `map`; acc: the gradient is acc + g (kinds 2 and 3)
 rv_status rv_launch_update(float* w, const float* g, size_t n, float eta, void* copy, int copy_kind,
-                           hipStream_t st, const rv_ver_map& map = rv_ver_map());
+                           hipStream_t st, const rv_ver_map& map = rv_ver_map(), const float* acc = nullptr);
 rv_status rv_launch_update_momentum(float* w, const float* g, float* v, size_t n, float eta, float mu, float wd,
-                                    void* copy, int copy_kind, hipStream_t st, const rv_ver_map& map = rv_ver_map());
+                                    void* copy, int copy_kind, hipStream_t st, const rv_ver_map& map = rv_ver_map(),
+                                    const float* acc = nullptr);
 rv_status rv_launch_accumulate(float* acc, const float* g, size_t n, bool first, hipStream_t st);
 rv_status rv_launch_copy(float* dst, const float* src, size_t n, hipStream_t st);
 // master <- w and copy <- w in the version's type

@@ -301,16 +301,14 @@ rv_status rv_stage_update_range(rv_stage* s, size_t off, size_t n, hipStream_t s
   const int kind = copy_kind(s);
   const float* g = s->grad + off;
   if (s->defer) return RV_OK;   // the update stays pending
-  if (s->accum > 1) {   // sum the group's gradients; only its last microbatch updates
-    RV_TRY(rv_launch_accumulate(s->gacc + off, g, n, s->acc_count == 0, st));
-    if (s->acc_count + 1 < s->accum) return RV_OK;
-    g = s->gacc + off;
-  }
+  // sum the group's gradients; only its last microbatch updates, by the sum before it and its own gradient together
+  if (s->acc_count + 1 < s->accum) return rv_launch_accumulate(s->gacc + off, g, n, s->acc_count == 0, st);
+  const float* acc = s->accum > 1 ? s->gacc + off : nullptr;
   void* copy = (char*)s->ver[s->upd_dst] + off * s->ver_elem;
   if (s->vel)
     return rv_launch_update_momentum(s->master + off, g, s->vel + off, n, s->eta, s->momentum, s->weight_decay,
-                                     copy, kind, st, s->ver_map);
-  return rv_launch_update(s->master + off, g, n, s->eta, copy, kind, st, s->ver_map);   // (decoder: a range of whole blocks)
+                                     copy, kind, st, s->ver_map, acc);
+  return rv_launch_update(s->master + off, g, n, s->eta, copy, kind, st, s->ver_map, acc);   // (decoder: a range of whole blocks)
 }
 
 namespace {

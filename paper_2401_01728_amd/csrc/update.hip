@@ -24,11 +24,13 @@ constexpr int kTile = kThreads * kVec * 4;
 // non-temporal access to w or to the version measured 3-5 % slower there (73 % -> 69-70 %), and so
 // did 8 consecutive parameters per lane for a 16-byte bf16 store (the lanes of a wave must stay
 // 16 bytes apart on w and g).
-template <int COPY>
+// ADD: the gradient is acc + g, the sum of a group's microbatches before this one and this one's: the last accumulation pass
+// and the update in one, 8 B/param less than one after the other.
+template <int COPY, bool ADD>
 __global__ __launch_bounds__(kThreads) void update_kernel(float* __restrict__ w,
                                                           const float* __restrict__ g, uint64_t n,
                                                           float eta, void* __restrict__ copy,
-                                                          int aligned, rv_ver_map map) {
+                                                          int aligned, rv_ver_map map, const float* __restrict__ acc) {
   const uint64_t base = (uint64_t)(COPY == 3 ? rv_ver_tile(blockIdx.x, gridDim.x) : blockIdx.x) * kTile;
   if (aligned && base + kTile <= n) {
     f4 wv[kVec], gv[kVec];
@@ -38,6 +40,7 @@ __global__ __launch_bounds__(kThreads) void update_kernel(float* __restrict__ w,
       if (COPY == 1 || COPY == 3) wv[u] = *reinterpret_cast<const f4*>(w + e);
       else wv[u] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(w + e));
       gv[u] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(g + e));
+      if (ADD) gv[u] += __builtin_nontemporal_load(reinterpret_cast<const f4*>(acc + e));
     }
 #pragma unroll
     for (int u = 0; u < kVec; ++u) {
@@ -63,7 +66,7 @@ __global__ __launch_bounds__(kThreads) void update_kernel(float* __restrict__ w,
   for (int k = threadIdx.x; k < kTile; k += kThreads) {
     uint64_t i = base + k;
     if (i >= n) break;
-    float r = __fmaf_rn(-eta, g[i], w[i]);
+    float r = __fmaf_rn(-eta, ADD ? acc[i] + g[i] : g[i], w[i]);
     w[i] = r;
     if (COPY == 1 || COPY == 3) reinterpret_cast<uint16_t*>(copy)[COPY == 3 ? rv_ver_at(map, base, i) : i] = rv_f32_to_bf16(r);
     if (COPY == 2) reinterpret_cast<float*>(copy)[i] = r;
@@ -75,12 +78,13 @@ __global__ __launch_bounds__(kThreads) void update_kernel(float* __restrict__ w,
 //   d = g + wd * w;   v <- mu * v + d;   w <- w - eta * v
 // (three fused multiply-adds per element; wd = mu = 0 gives Eq. 2 bit for bit).
 // 22 B/param with a bf16 copy: reads w, g, v, writes w, v, copy.
-template <int COPY>
+template <int COPY, bool ADD>
 __global__ __launch_bounds__(kThreads) void update_momentum_kernel(float* __restrict__ w,
                                                                    const float* __restrict__ g,
                                                                    float* __restrict__ v, uint64_t n,
                                                                    float eta, float mu, float wd,
-                                                                   void* __restrict__ copy, int aligned, rv_ver_map map) {
+                                                                   void* __restrict__ copy, int aligned, rv_ver_map map,
+                                                                   const float* __restrict__ acc) {
   const uint64_t base = (uint64_t)(COPY == 3 ? rv_ver_tile(blockIdx.x, gridDim.x) : blockIdx.x) * kTile;
   auto step = [&](float wi, float gi, float& vi) {
     const float d = __fmaf_rn(wd, wi, gi);
@@ -92,7 +96,8 @@ __global__ __launch_bounds__(kThreads) void update_momentum_kernel(float* __rest
     for (int u = 0; u < kVec; ++u) {
       const uint64_t e = base + (uint64_t)(u * kThreads + threadIdx.x) * 4;
       const f4 wv = *reinterpret_cast<const f4*>(w + e);
-      const f4 gv = __builtin_nontemporal_load(reinterpret_cast<const f4*>(g + e));
+      f4 gv = __builtin_nontemporal_load(reinterpret_cast<const f4*>(g + e));
+      if (ADD) gv += __builtin_nontemporal_load(reinterpret_cast<const f4*>(acc + e));
       f4 vv = *reinterpret_cast<const f4*>(v + e);
       f4 r;
 #pragma unroll
@@ -118,7 +123,7 @@ __global__ __launch_bounds__(kThreads) void update_momentum_kernel(float* __rest
     const uint64_t i = base + k;
     if (i >= n) break;
     float vi = v[i];
-    const float r = step(w[i], g[i], vi);
+    const float r = step(w[i], ADD ? acc[i] + g[i] : g[i], vi);
     w[i] = r; v[i] = vi;
     if (COPY == 1 || COPY == 3) reinterpret_cast<uint16_t*>(copy)[COPY == 3 ? rv_ver_at(map, base, i) : i] = rv_f32_to_bf16(r);
     if (COPY == 2) reinterpret_cast<float*>(copy)[i] = r;
@@ -205,37 +210,37 @@ __global__ __launch_bounds__(kPadSlots * RV_VER_PAD / 4) void clear_pads_kernel(
 }  // namespace
 
 rv_status rv_launch_update(float* w, const float* g, size_t n, float eta, void* copy, int copy_kind,
-                           hipStream_t st, const rv_ver_map& map) {
+                           hipStream_t st, const rv_ver_map& map, const float* acc) {
   if (n == 0) return RV_OK;
-  int aligned = ((((uintptr_t)w) | ((uintptr_t)g)) & 15) == 0;
+  int aligned = ((((uintptr_t)w) | ((uintptr_t)g) | ((uintptr_t)acc)) & 15) == 0;
   if (copy && (((uintptr_t)copy) & 15)) aligned = 0;
-  unsigned blocks = (unsigned)((n + kTile - 1) / kTile);
-  if (!copy || copy_kind == 0)
-    hipLaunchKernelGGL(update_kernel<0>, dim3(blocks), dim3(kThreads), 0, st, w, g, n, eta, nullptr, aligned, map);
-  else if (copy_kind == 1)
-    hipLaunchKernelGGL(update_kernel<1>, dim3(blocks), dim3(kThreads), 0, st, w, g, n, eta, copy, aligned, map);
-  else if (copy_kind == 3)
-    hipLaunchKernelGGL(update_kernel<3>, dim3(blocks), dim3(kThreads), 0, st, w, g, n, eta, copy, aligned, map);
-  else
-    hipLaunchKernelGGL(update_kernel<2>, dim3(blocks), dim3(kThreads), 0, st, w, g, n, eta, copy, aligned, map);
-  return rv_launch_status();
+  const int kind = copy ? copy_kind : 0;
+  if (acc && kind < 2) return RV_E_INVAL;      // (only a stage has one)
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)((n + kTile - 1) / kTile)), dim3(kThreads), 0, st, w, g, n, eta, kind ? copy : nullptr, aligned,
+                       map, acc);
+    return rv_launch_status();
+  };
+  if (acc) return kind == 3 ? go(update_kernel<3, true>) : go(update_kernel<2, true>);
+  return kind == 0 ? go(update_kernel<0, false>) : kind == 1 ? go(update_kernel<1, false>)
+         : kind == 3 ? go(update_kernel<3, false>) : go(update_kernel<2, false>);
 }
 
 rv_status rv_launch_update_momentum(float* w, const float* g, float* v, size_t n, float eta, float mu, float wd,
-                                    void* copy, int copy_kind, hipStream_t st, const rv_ver_map& map) {
+                                    void* copy, int copy_kind, hipStream_t st, const rv_ver_map& map, const float* acc) {
   if (n == 0) return RV_OK;
-  int aligned = ((((uintptr_t)w) | ((uintptr_t)g) | ((uintptr_t)v)) & 15) == 0;
+  int aligned = ((((uintptr_t)w) | ((uintptr_t)g) | ((uintptr_t)v) | ((uintptr_t)acc)) & 15) == 0;
   if (copy && (((uintptr_t)copy) & 15)) aligned = 0;
-  unsigned blocks = (unsigned)((n + kTile - 1) / kTile);
-  if (!copy || copy_kind == 0)
-    hipLaunchKernelGGL(update_momentum_kernel<0>, dim3(blocks), dim3(kThreads), 0, st, w, g, v, n, eta, mu, wd, nullptr, aligned, map);
-  else if (copy_kind == 1)
-    hipLaunchKernelGGL(update_momentum_kernel<1>, dim3(blocks), dim3(kThreads), 0, st, w, g, v, n, eta, mu, wd, copy, aligned, map);
-  else if (copy_kind == 3)
-    hipLaunchKernelGGL(update_momentum_kernel<3>, dim3(blocks), dim3(kThreads), 0, st, w, g, v, n, eta, mu, wd, copy, aligned, map);
-  else
-    hipLaunchKernelGGL(update_momentum_kernel<2>, dim3(blocks), dim3(kThreads), 0, st, w, g, v, n, eta, mu, wd, copy, aligned, map);
-  return rv_launch_status();
+  const int kind = copy ? copy_kind : 0;
+  if (acc && kind < 2) return RV_E_INVAL;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)((n + kTile - 1) / kTile)), dim3(kThreads), 0, st, w, g, v, n, eta, mu, wd,
+                       kind ? copy : nullptr, aligned, map, acc);
+    return rv_launch_status();
+  };
+  if (acc) return kind == 3 ? go(update_momentum_kernel<3, true>) : go(update_momentum_kernel<2, true>);
+  return kind == 0 ? go(update_momentum_kernel<0, false>) : kind == 1 ? go(update_momentum_kernel<1, false>)
+         : kind == 3 ? go(update_momentum_kernel<3, false>) : go(update_momentum_kernel<2, false>);
 }
 
 rv_status rv_launch_accumulate(float* acc, const float* g, size_t n, bool first, hipStream_t st) {
