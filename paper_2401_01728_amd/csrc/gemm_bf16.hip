@@ -562,7 +562,8 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
                                               const uint16_t* __restrict__ B, int64_t ldb, int64_t b_bs, int M, int N,
                                               int K, int bm, int bn, const Epi& e) {
   // Products of 16x16: the matrix cores do 1717 TFLOP/s out of LDS at the board's power cap with those, 1586 with 32x32 ones
-  // (registers alone 2028 / 1807; half the accumulator traffic per flop).
+  // (registers alone 2028 / 1807; half the accumulator traffic per flop).  Stage steps at the cap 2 % shorter (8 blocks of d 2048
+  // 10.92 -> 10.72 ms), below it, after seconds under load, 0.6 - 0.9 % longer (9.31 -> 9.39).
   // NW waves laid out 2 (m) x NW/2 (n)
   typedef f32x4 V;
   constexpr int WM = BM / 2, WN = BN / (NW / 2), TM = WM / 16, TN = WN / 16;
