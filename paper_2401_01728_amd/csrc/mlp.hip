@@ -235,8 +235,11 @@ __device__ __forceinline__ void fp32_walk(TileAcc<BT>& acc, const Prod& p, int m
   }
 }
 
-// A float is the sum of three bf16 numbers, exactly: the nearest one (a0), the one nearest to what is left, and what is left
-// then.  Of the nine products of pieces six are formed; the three left out are below 2^-25 of the product, of either sign.
+// A float is the sum of three bf16 numbers: the nearest one (a0), the one nearest to what is left, and what is left then.  bf16
+// ends at 2^-133 and the last bit of a float below 2^-110 lies lower: operands are multiplied by 2^16 on the way in and the sums
+// by 2^-32 on the way out, and so every float below 2^112 is the sum of its pieces, exactly.  (Without that a gradient's row at
+// 1e-36 came out 3e-5 off.)  Of the nine products of pieces six are formed; the three left out are together at most 2^-24
+// of the product, of either sign.
 // Six bf16 instructions of 32 cycles stand against eight fp32 ones of 64.  a0 b0 is summed by itself: the instruction drops what
 // lies below its sum towards minus infinity several times in 16 k, and with all six in one sum 1024-4096-4096-1024 on
 // 1024 rows is 1.43e-6 from 64 bits and 4096 in k low by 2e-7 in the mean (fp32 instructions 1.28e-6 and 0).
@@ -245,8 +248,9 @@ __device__ __forceinline__ void fp32_walk(TileAcc<BT>& acc, const Prod& p, int m
 // of reading nor the 8-byte writes have bank conflicts.
 // What bounds it: with two workgroups to a CU the matrix cores (1024 rows, 4096 -> 8192 forward 328 us = 209 TFLOP/s, 1255 of
 // bf16), with one the LDS and barrier latency of a wave alone on its SIMD (4096 -> 4096 forward 188 us, 183 TFLOP/s).  Against the
-// fp32 walk that ran here before, 1024 rows, forward / backward with the update, us: 4096 -> 4096 303 / 538 -> 188 / 349,
-// 1024 -> 4096 90 / 157 -> 61 / 115; 2051 rows, 1030 -> 2052 174 / 240 -> 85 / 160; distance from 64 bits 0.31 - 0.36 times.
+// fp32 walk that ran here before, 1024 rows, forward / backward with the update, us: 4096 -> 4096 303 / 538 -> 208 / 362,
+// 1024 -> 4096 90 / 157 -> 62 / 114; 2051 rows, 1030 -> 2052 174 / 240 -> 88 / 161; distance from 64 bits 0.31 - 0.36 times.
+// (The factors of 2^16, on the vector ALU, are 1 - 4 % of a walk.)
 constexpr int SK = 16, kSlots = 3;                         // of k to a step
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
@@ -279,6 +283,7 @@ template <bool KM, int ROWS>
 __device__ __forceinline__ int plane_chunk(int row, int c) {   // byte of 16-byte chunk c of a row
   return KM ? row * (ROWS * 2) + (c ^ (ROWS == 64 ? (row & 2) << 1 : (row & 3) << 2)) * 16 : row * 32 + (c ^ (row >> 3 & 1)) * 16;
 }
+constexpr float kUp = 0x1p16f, kDown = 0x1p-32f;
 template <bool KM, int ROWS>
 __device__ __forceinline__ void planes_park(const f32x4* v, char* s, int left) {   // left: K - k0
 #pragma unroll
@@ -290,6 +295,7 @@ __device__ __forceinline__ void planes_park(const f32x4* v, char* s, int left) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) x[e] = (KM ? row : c * 4 + e) < left ? x[e] : 0.f;
     }
+    x *= kUp;
     char* d = s + plane_chunk<KM, ROWS>(row, c >> 1) + (c & 1) * 8;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -446,7 +452,7 @@ __device__ __forceinline__ void planes_walk(TileAcc<BT>& acc, const Prod& p, int
 #pragma unroll
   for (int i = 0; i < T; ++i)
 #pragma unroll
-    for (int j = 0; j < T; ++j) acc[i][j] += low[i][j];
+    for (int j = 0; j < T; ++j) acc[i][j] = (acc[i][j] + low[i][j]) * kDown;
 }
 
 // BT: 128 or 64 (tiled), kHalves (64, by two halves of a workgroup), 32 (split over NT / 64 waves), kSlim (the same, 32x16),
@@ -499,20 +505,16 @@ __device__ __forceinline__ void tiled_body(const Prod& p, const Out& o, int tile
   } else {
     planes_walk<BT, AKM, BKM>(acc, p, m0, n0, reinterpret_cast<char*>(smem));
   }
-  // The pieces of an infinity hold a NaN, and those of numbers near the smallest ones are not exact: a tile with a
-  // result that is not finite, or with none but tiny ones, is walked again in fp32.
+  // The pieces of an infinity hold a NaN, and large numbers may pass the largest one on the way: a tile with a result that is not
+  // finite is walked again in fp32, and with it the other one of its workgroup.
   bool finite = true;
-  float top = 0.f;
 #pragma unroll
   for (int i = 0; i < T; ++i)
 #pragma unroll
     for (int j = 0; j < T; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        finite = finite && fabsf(acc[i][j][r]) < __builtin_inff();
-        top = fmaxf(top, fabsf(acc[i][j][r]));
-      }
-  if (__syncthreads_or(!finite) || (!__syncthreads_or(top >= 1e-30f) && __syncthreads_or(top > 0.f)))
+      for (int r = 0; r < 16; ++r) finite = finite && fabsf(acc[i][j][r]) < __builtin_inff();
+  if (__syncthreads_or(!finite))
     fp32_walk<BT, AKM, BKM>(acc, p, m0, n0, smem);
   if (!live || (HALVES && part)) return;
 #pragma unroll

@@ -346,7 +346,7 @@ def test_two_tiles_a_workgroup_and_the_split_walk(dims, mb, momentum):
                          [([K, 700], 900) for K in (255, 256, 257, 288, 576, 577)] + [([600, 701], 900), ([592, 702], 900)])
 def test_products_in_three_planes(dims, mb):
     """Bar: sums of K products with random signs in fp32 stay within sqrt(K) * 2^-24 normwise in any order; the pieces left out
-    are 2^-25 of a product."""
+    are together at most 2^-24 of a product."""
     import paper_2401_01728_amd as rv
     w0 = kaiming_uniform_flat(66, dims)
     g = rv.Stage.mlp(dims, mb, 0, 1e-3); g.set_params(dev(w0))
@@ -367,7 +367,7 @@ def test_an_infinity_in_a_large_tile(where):
 
 @pytest.mark.parametrize("scale", [1e-26, 1e-31, 1e-34])
 def test_gradients_near_the_smallest_numbers(scale):
-    """The third piece of 1e-33 is no normal number: such tiles are multiplied in fp32.  Bar: sums of fp32 products as above; of
+    """The third piece of 1e-33 is no bf16 number unless the operands are scaled.  Bar: sums of fp32 products as above; of
     results down to 1e-37 the smallest number's half, 7e-46, is far below 2^-24."""
     import paper_2401_01728_amd as rv
     dims, mb = [1500, 4100], 1030
@@ -381,6 +381,46 @@ def test_gradients_near_the_smallest_numbers(scale):
     up = 1.0 / scale                       # (the comparison's own squares would underflow)
     close(dx * up, dxo * up, 1e-5, "t", group="MLP near the smallest numbers, bar 1e-5")
     close(host64(g.last_grad()) * up, o.last_grad * up, 1e-5, "t", group="MLP near the smallest numbers, bar 1e-5")
+
+
+# forward / input gradient / weight gradient: tiles of 128 / 64 / 128; by two halves of a workgroup / split / split; split / split /
+# 64x64 tiles two to a workgroup, an odd number of them
+_PLANES = [([1500, 4100], 1030), ([300, 700], 900), ([700, 830], 40)]
+
+
+@pytest.mark.parametrize("small", ["rows", "columns", "weights", "gradient"])
+@pytest.mark.parametrize("dims,mb", _PLANES)
+def test_small_operands_beside_ordinary_ones(dims, mb, small):
+    """Every row and column against its own scale: every other row of x and of the other rows of dy at 1e-36; the first 64 columns
+    of W and of dy, which are tiles of their own beside ordinary ones; weights of few bits near 1e-42 under activations and
+    gradients of 1e8; a gradient of 1e-41 with activations of 1e8.  Bar as test_products_in_three_planes."""
+    import paper_2401_01728_amd as rv
+    K, N = dims
+    s = {"weights": 1e-41, "gradient": 1e-41}.get(small, 1e-36)
+    one = lambda n: np.ones(n)
+    xr, wc, dr, dc = one(mb), one(N), one(mb), one(N)      # scales of x's rows, W's columns, dy's rows and columns
+    if small == "rows": xr[::2] = s; dr[1::2] = s
+    if small == "columns": wc[:64] = s; dc[:64] = s
+    if small == "weights": wc[:] = s; xr[:] = 1e8; dr[:] = 1e8
+    if small == "gradient": dr[:] = s; xr[:] = 1e8
+    w0 = kaiming_uniform_flat(68, dims)
+    w0[K * N:] = 0.0
+    w0[:K * N] = (w0[:K * N].reshape(K, N) * wc).astype(np.float32).ravel()
+    x = (gen.normal_f32(68, 1, mb * K).reshape(mb, K) * xr[:, None]).astype(np.float32)
+    dy = (gen.normal_f32(68, 2, mb * N).reshape(mb, N) * dr[:, None] * dc).astype(np.float32)
+    g = rv.Stage.mlp(dims, mb, 0, 0.0); g.set_params(dev(w0))
+    o = ostage.Stage("mlp", 0, 0.0, w0, dims=dims)
+    bar = lambda k: float(np.sqrt(k) * 2.0 ** -24 + 2.0 ** -24)
+    grp = "MLP, small operands: "
+    up = 1.0 / (xr[:, None] * wc)
+    close(host64(g.forward(0, dev(x))) * up, o.forward(0, x) * up, bar(K), "t", group=grp + "out")
+    dx, dxo = host64(g.backward(0, dev(dy))), o.backward(0, dy)
+    if small != "gradient":                # (there the input gradient is as small as the gradient: nothing of 24 bits)
+        up = 1.0 / (dr[:, None] * wc.max())
+        close(dx * up, dxo * up, bar(N), "t", group=grp + "grad_in")
+    up = 1.0 / ((xr * dr).max() * dc)      # (rows: each of the products has one small operand)
+    gr, gro = host64(g.last_grad())[:K * N].reshape(K, N), o.last_grad[:K * N].reshape(K, N)
+    close(gr * up, gro * up, bar(mb), "t", group=grp + "gradient")
 
 
 # 32x16 tiles: contractions of less than a group of 16, exactly one per wave, one more, both sets of requests exactly, a third begun; the
