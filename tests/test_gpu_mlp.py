@@ -423,6 +423,30 @@ def test_small_operands_beside_ordinary_ones(dims, mb, small):
     close(gr * up, gro * up, bar(mb), "t", group=grp + "gradient")
 
 
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+@pytest.mark.parametrize("dims,mb", [([4096, 1024], 512), ([16384, 1024], 512), ([256, 16384], 2100), ([512, 1100], 16400)])
+def test_sums_of_one_sign(dims, mb, sign):
+    """Uniform operands without cancellation (the weights' sign times `sign`): nothing is lost to one side.  In k: 4096 and 16384 by two
+    halves of a workgroup, an input gradient of 16384, a weight gradient of 16400 rows.  Bars: normwise as
+    test_products_in_three_planes; the mean error 2^-22 of the result, four roundings - a sum that lost half a unit in its last
+    place every 16 in k would be off by K / 16 * 2^-26 or more, 3.8e-6 at 4096."""
+    import paper_2401_01728_amd as rv
+    K, N = dims
+    w0 = np.concatenate([gen.uniform_f32(69, 0, K * N, 0.0, 1.0) * np.float32(sign), np.zeros(N, np.float32)]).astype(np.float32)
+    x = gen.uniform_f32(69, 1, mb * K, 0.0, 1.0).reshape(mb, K)
+    dy = gen.uniform_f32(69, 2, mb * N, 0.0, 1.0).reshape(mb, N)
+    g = rv.Stage.mlp(dims, mb, 0, 0.0); g.set_params(dev(w0))
+    o = ostage.Stage("mlp", 0, 0.0, w0, dims=dims)
+
+    def check(got, ref, k, what):
+        close(got, ref, float(np.sqrt(k) * 2.0 ** -24 + 2.0 ** -24), "t", group="MLP, sums of one sign: " + what)
+        assert abs((got - ref).mean()) <= 2.0 ** -22 * np.abs(ref).mean(), (what, (got - ref).mean() / np.abs(ref).mean())
+
+    check(host64(g.forward(0, dev(x))), o.forward(0, x), K, "out")
+    check(host64(g.backward(0, dev(dy))), o.backward(0, dy), N, "grad_in")
+    check(host64(g.last_grad())[:K * N], o.last_grad[:K * N], mb, "gradient")
+
+
 # 32x16 tiles: contractions of less than a group of 16, exactly one per wave, one more, both sets of requests exactly, a third begun; the
 # last row and column counts on each side of a tile's edge; forward and input gradient at the limits of the rule and one past them
 @pytest.mark.parametrize("dims,mb", [([K, 40], 33) for K in (7, 128, 129, 1024, 1025)] + [([300, 17], 32), ([300, 16], 65), ([31, 600], 70),
