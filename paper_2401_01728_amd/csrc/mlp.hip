@@ -829,10 +829,9 @@ int pick(int M, int N, int K) {
   return thin > 64 && tile_count(M, N, 128) >= kCUs ? 128 : tile_count(M, N, 64) >= kCUs / 2 ? 64 : 32;
 }
 // 32x16 tiles where 32x32 ones leave CUs without one: a forward product up to half of them, an input gradient up to a quarter, for the
-// weight gradient's tiles come beside it.  us, 32x32 / 32x16: forward 1000 -> 1000 on 100 rows 10.5 / 8.8, 4096 -> 256 on 16 29.1 / 19.4,
-// 128 -> 128 on 64 6.9 / 5.2; backward 300 -> 1000 on 100 rows 11.1 / 9.1, 256 -> 4000 on 20 31.4 / 22.9, 128 -> 128 on 64 5.0 / 4.7;
-// past the quarter 200 -> 200 on 500 rows 7.3 / 8.9, 1000 -> 1000 on 100 15.6 / 19.7, 1000 -> 77 on 100 5.3 / 7.7; of a contraction below
-// 128, 100 -> 100 on 300 rows 6.5 / 6.9.
+// weight gradient's tiles come beside it (and more below).  us, 32x32 / 32x16: forward 1000 -> 1000 on 100 rows 10.5 / 8.8, 4096 -> 256 on
+// 16 29.1 / 19.4, 128 -> 128 on 64 6.9 / 5.2; backward 300 -> 1000 on 100 rows 11.1 / 9.1, 256 -> 4000 on 20 31.4 / 22.9;
+// past the quarter 200 -> 200 on 500 rows 7.3 / 8.9, 1000 -> 1000 on 100 15.6 / 19.7, 1000 -> 77 on 100 5.3 / 7.7.
 bool slim(int M, int N, int bt, int cus) { return bt == 32 && tile_count(M, N, 32) <= cus; }
 int threads(int bt) { return bt == 32 || bt == kSlim || bt == kHalves ? 64 * kSplitWaves : 256; }
 
@@ -840,13 +839,35 @@ template <typename K>
 rv_status allow_lds(K kern, int bytes) {
   return hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess ? RV_OK : RV_E_DEVICE;
 }
+// workgroups that copy the stage's input beside a forward product's tiles
+int copy_groups(int M, int K, int nt) {
+  const int64_t per = 16 * nt;   // floats a workgroup copies per turn
+  return (int)std::min<int64_t>(4 * kCUs, ((int64_t)M * K + per - 1) / per);
+}
+// A workgroup of 32x16 tiles has a CU to itself, so the copying ones of a first layer come behind the tiles where both are more than
+// the CUs.  That pays only where the walk is long against them: us, 32x32 / 32x16, of 256 tiles and 13 - 17 copying
+// workgroups 128 -> 128 on 1000 rows 4.8 / 6.3, 256 -> 256 on 500 5.0 / 6.8; 1400 -> 256 on 500 (84 of them) 14.4 / 12.5, 1400 -> 128 on 1000
+// (171) 14.8 / 15.3, 2000 -> 128 on 1000 (245) 20.0 / 18.5.
+bool slim_forward(int M, int N, int K, int bt, bool copy) {
+  if (!slim(M, N, bt, kCUs / 2)) return false;
+  const int copies = copy ? copy_groups(M, K, 64 * kSplitWaves) : 0;
+  return (M + 31) / 32 * ((N + 15) / 16) + copies <= kCUs || 5 * copies <= K - 750;
+}
+// The input gradient of mb rows, width K and contraction N beside a weight gradient of `others` workgroups, bias ones among them.  It
+// has to be the longer walk: us, 32x32 / 32x16, 20 -> 128 on 1000 rows 9.8 / 10.5, 128 -> 300 on 300 6.5 / 7.0, 20 -> 1000 on 1000 10.5 / 11.1,
+// 100 -> 600 on 500 8.0 / 7.7, 64 -> 1000 on 64 10.2 / 8.3; contractions of 128, 1000 -> 128 on 60 4.6 / 4.8, 300 -> 128 on 100 4.7 / 4.7.  And workgroups have
+// a CU to themselves here too: another turn of the CUs is worth it only for a long walk: 1900 -> 600 on 20 rows 9.4 / 13.8, 300 -> 600 on 100
+// 8.2 / 7.9, 1000 -> 900 on 60 11.9 / 11.2, 100 -> 900 on 500 10.7 / 9.0.
+bool slim_backward(int mb, int K, int N, int bx, int others) {
+  if (!slim(mb, K, bx, kCUs / 4) || N < 256 || N <= mb) return false;
+  return (mb + 31) / 32 * ((K + 15) / 16) + others <= kCUs || tile_count(mb, K, 32) + others > kCUs || N >= 800;
+}
 template <int BT, int NT>
 rv_status launch_fwd(hipStream_t st, const Prod& p, const Out& o, float* copy) {
   constexpr int lds = mlp_lds_bytes<BT, NT, false, true>();
   static const rv_status ok = allow_lds(mlp_fwd_kernel<BT, NT>, lds);
   RV_TRY(ok);
-  const int64_t per = 16 * NT;   // floats a workgroup copies per turn
-  const int extra = copy ? (int)std::min<int64_t>(4 * kCUs, ((int64_t)p.M * p.K + per - 1) / per) : 0;
+  const int extra = copy ? copy_groups(p.M, p.K, NT) : 0;
   hipLaunchKernelGGL((mlp_fwd_kernel<BT, NT>), dim3(p.tiles + extra), dim3(NT), lds, st, p, o, copy);
   return rv_launch_status();
 }
@@ -1268,7 +1289,7 @@ rv_status rv_mlp_forward(rv_stage* s, rv_slot& slot, const void* in, void* out) 
     const bool last = i == p->n - 1, first = i == 0 && !copy_first;
     const int K = (int)s->dims[i], N = (int)s->dims[i + 1];
     int bt = pick(mb, N, K);
-    if (slim(mb, N, bt, kCUs / 2)) bt = kSlim;
+    if (slim_forward(mb, N, K, bt, first)) bt = kSlim;
     if (bt == 64 && tile_count(mb, N, 64) <= kCUs && K >= 256) bt = kHalves;   // one tile to a CU; shorter walks are mostly beginning
     const Prod pr = product(first ? (const float*)in : stash + p->offA[i], K, w + p->offW[i], N, mb, N, K, bt, threads(bt));
     Out o = {};
@@ -1326,9 +1347,9 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
     // 64x64 weight-gradient tiles beside an input gradient whose walk is dealt out over eight waves: two to a workgroup
     const int bx = pick(mb, K, N), bw = pick(K, N, mb);
     const int nt = std::max(bx, bw) == 32 || (bx == 32 && bw == 64) ? threads(32) : 256;
-    const int form = nt == threads(32) && want_dx && N >= 128 && slim(mb, K, bx, kCUs / 4) ? kSlim : bx;
-    Prod px = product(d, N, w + p->offW[i], N, mb, K, N, form, nt);
     const Prod pw = product(a, K, d, N, K, N, mb, bw, nt);
+    const int form = nt == threads(32) && want_dx && slim_backward(mb, K, N, bx, pw.tiles + (N + 31) / 32) ? kSlim : bx;
+    Prod px = product(d, N, w + p->offW[i], N, mb, K, N, form, nt);
     if (!want_dx) px.tiles = 0;
     Out ox = {}, ow = {};
     ox.C = dst; ox.gate = i > 0 ? a : nullptr;

@@ -450,7 +450,10 @@ def test_sums_of_one_sign(dims, mb, sign):
 # 32x16 tiles: contractions of less than a group of 16, exactly one per wave, one more, both sets of requests exactly, a third begun; the
 # last row and column counts on each side of a tile's edge; forward and input gradient at the limits of the rule and one past them
 @pytest.mark.parametrize("dims,mb", [([K, 40], 33) for K in (7, 128, 129, 1024, 1025)] + [([300, 17], 32), ([300, 16], 65), ([31, 600], 70),
-                                     ([40, 4096], 17), ([2048, 300], 9), ([2049, 300], 9), ([300, 4097], 9)])
+                                     ([40, 4096], 17), ([2048, 300], 9), ([2049, 300], 9), ([300, 4097], 9),
+                                     # forward tiles and copying workgroups together as many as the CUs; input gradients of a contraction
+                                     # of 256 and one less, longer than the weight gradient's and not; one turn of the CUs more
+                                     ([40, 4080], 17), ([300, 256], 20), ([300, 255], 20), ([64, 260], 259), ([64, 260], 260), ([1900, 600], 20)])
 def test_slim_tiles(dims, mb):
     """Bar as test_product_forms_at_their_edges."""
     test_product_forms_at_their_edges(dims, mb, 0.0)
