@@ -844,14 +844,17 @@ int copy_groups(int M, int K, int nt) {
   const int64_t per = 16 * nt;   // floats a workgroup copies per turn
   return (int)std::min<int64_t>(4 * kCUs, ((int64_t)M * K + per - 1) / per);
 }
-// A workgroup of 32x16 tiles has a CU to itself, so the copying ones of a first layer come behind the tiles where both are more than
-// the CUs.  That pays only where the walk is long against them: us, 32x32 / 32x16, of 256 tiles and 13 - 17 copying
-// workgroups 128 -> 128 on 1000 rows 4.8 / 6.3, 256 -> 256 on 500 5.0 / 6.8; 1400 -> 256 on 500 (84 of them) 14.4 / 12.5, 1400 -> 128 on 1000
-// (171) 14.8 / 15.3, 2000 -> 128 on 1000 (245) 20.0 / 18.5.
+// A workgroup of 32x16 tiles has a CU to itself and workgroups are dealt to the eight XCDs in turn, so the copying ones of a first
+// layer run on the CUs that the tiles leave of each XCD, a short turn after another, and behind the tiles where they leave none.
+// That pays only where the walk is long against it: us, 32x32 / 32x16: no CU left, 128 -> 128 on 1000 rows 4.8 / 6.3, 256 -> 256 on 500 5.0 / 6.8,
+// 1400 -> 256 on 500 (84 copying workgroups) 14.4 / 12.5, 1400 -> 128 on 1000 (171) 14.8 / 15.3, 2000 -> 128 on 1000 (245) 20.0 / 18.5;
+// four of an XCD left, 500 -> 100 on 1000 (two turns) 7.2 / 5.7, 1000 -> 100 on 1000 (four) 10.6 / 9.7; one left, 300 -> 128 on 970 (five)
+// 6.4 / 6.8, 1000 -> 128 on 970 (15) 10.5 / 11.2.
 bool slim_forward(int M, int N, int K, int bt, bool copy) {
   if (!slim(M, N, bt, kCUs / 2)) return false;
-  const int copies = copy ? copy_groups(M, K, 64 * kSplitWaves) : 0;
-  return (M + 31) / 32 * ((N + 15) / 16) + copies <= kCUs || 5 * copies <= K - 750;
+  const int copies = copy ? copy_groups(M, K, 64 * kSplitWaves) : 0, groups = (M + 31) / 32 * ((N + 15) / 16);
+  const int left = kCUs / 8 - (groups + 7) / 8, each = (copies + 7) / 8;   // of an XCD
+  return groups + copies <= kCUs || each <= left * std::max(1, K / 250) || 5 * copies <= K - 750;
 }
 // The input gradient of mb rows, width K and contraction N beside a weight gradient of `others` workgroups, bias ones among them.  It
 // has to be the longer walk: us, 32x32 / 32x16, 20 -> 128 on 1000 rows 9.8 / 10.5, 128 -> 300 on 300 6.5 / 7.0, 20 -> 1000 on 1000 10.5 / 11.1,
