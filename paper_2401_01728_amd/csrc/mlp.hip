@@ -1293,7 +1293,9 @@ rv_status rv_mlp_forward(rv_stage* s, rv_slot& slot, const void* in, void* out) 
     const int K = (int)s->dims[i], N = (int)s->dims[i + 1];
     int bt = pick(mb, N, K);
     if (slim_forward(mb, N, K, bt, first)) bt = kSlim;
-    if (bt == 64 && tile_count(mb, N, 64) <= kCUs && K >= 256) bt = kHalves;   // one tile to a CU; shorter walks are mostly beginning
+    // one tile to a CU; the shortest walks are mostly beginning (1024 -> 1024 rows, us, whole / halves: 32 in k 6.3 / 6.6, 64 7.2 / 7.2, 100 9.0 / 8.5,
+    // 128 9.2 / 8.6, 200 10.9 / 10.6)
+    if (bt == 64 && tile_count(mb, N, 64) <= kCUs && K >= 80) bt = kHalves;
     const Prod pr = product(first ? (const float*)in : stash + p->offA[i], K, w + p->offW[i], N, mb, N, K, bt, threads(bt));
     Out o = {};
     o.C = last ? (float*)out : stash + p->offA[i + 1]; o.bias = w + p->offB[i]; o.relu = !last;
@@ -1347,9 +1349,12 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
     const float* a = stash + p->offA[i];
     const bool want_dx = i > 0 || grad_in;
     float* dst = i == 0 ? (float*)grad_in : (d == ping ? pong : ping);
-    // 64x64 weight-gradient tiles beside an input gradient whose walk is dealt out over eight waves: two to a workgroup
+    // 64x64 tiles beside a walk that is dealt out over eight waves go two to a workgroup: weight-gradient tiles always, those of an input
+    // gradient where the weight gradient's walk is much the longer one (us, four waves / eight: 700 -> 60 on 1000 rows 14.8 / 12.2, 1024 -> 128
+    // on 1024 15.7 / 12.3, 500 -> 250 on 2000 28.2 / 22.3, 2000 -> 60 on 300 9.2 / 7.9; 2000 -> 77 on 300 9.8 / 10.6, 1024 -> 200 on 1024 17.7 / 18.9)
     const int bx = pick(mb, K, N), bw = pick(K, N, mb);
-    const int nt = std::max(bx, bw) == 32 || (bx == 32 && bw == 64) ? threads(32) : 256;
+    const bool pairs = (bx == 32 && bw == 64) || (bx == 64 && bw == 32 && mb >= (N <= 64 ? 4 : 6) * N);
+    const int nt = std::max(bx, bw) == 32 || pairs ? threads(32) : 256;
     const Prod pw = product(a, K, d, N, K, N, mb, bw, nt);
     const int form = nt == threads(32) && want_dx && slim_backward(mb, K, N, bx, pw.tiles + (N + 31) / 32) ? kSlim : bx;
     Prod px = product(d, N, w + p->offW[i], N, mb, K, N, form, nt);
@@ -1367,6 +1372,7 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
         return bw == 64 ? go(launch_bwd<BX, 64, NT>) : bw == 32 ? go(launch_bwd<BX, 32, NT>) : go(launch_bwd<BX, kWave, NT>);
       else
       return bw == 128 ? go(launch_bwd<BX, 128, 256>) : bw == 64 ? go(launch_bwd<BX, 64, BX == 32 ? NT : 256>)
+             : bw == 32 && pairs ? go(launch_bwd<BX, 32, 64 * kSplitWaves>)
              : bw == 32 ? go(launch_bwd<BX, 32, NT>) : go(launch_bwd<BX, kWave, BX == 32 ? NT : 256>);
     };
     const rv_status rc = form == kSlim ? by_bw(Int<kSlim>()) : bx == 128 ? by_bw(Int<128>()) : bx == 64 ? by_bw(Int<64>()) : bx == 32 ? by_bw(Int<32>()) : by_bw(Int<kWave>());

@@ -340,10 +340,12 @@ def test_two_tiles_a_workgroup_and_the_split_walk(dims, mb, momentum):
 
 
 # LDS tiles walked in three bf16 planes, steps of 16 in k.  Tiles of 128: up to five steps are loaded by the general form, from six on
-# whole steps by pieces (one less where a row is no multiple of a piece).  Tiles of 64: the same at 18 steps; from 256 in
-# k on by two halves of a workgroup, an even or odd number of steps.
+# whole steps by pieces (one less where a row is no multiple of a piece).  Tiles of 64: the same at 10 steps; from 80 in
+# k on by two halves of a workgroup, an even or odd number of steps.  The last ones: input gradient tiles of 64 two to a workgroup beside
+# split weight gradients, an odd and an even number of them, on each side of the rule.
 @pytest.mark.parametrize("dims,mb", [([K, 4100], 1030) for K in (95, 96, 97, 113, 130)] + [([96, 4101], 1030)] +
-                         [([K, 700], 900) for K in (255, 256, 257, 288, 576, 577)] + [([600, 701], 900), ([592, 702], 900)])
+                         [([K, 700], 900) for K in (79, 80, 81, 96, 97, 255, 256, 257, 288, 576, 577)] + [([600, 701], 900), ([592, 702], 900)] +
+                         [([832, 24], 700), ([700, 110], 660), ([700, 111], 660)])
 def test_products_in_three_planes(dims, mb):
     """Bar: sums of K products with random signs in fp32 stay within sqrt(K) * 2^-24 normwise in any order; the pieces left out
     are together at most 2^-24 of a product."""
