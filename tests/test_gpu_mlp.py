@@ -367,6 +367,33 @@ def test_an_infinity_in_a_large_tile(where):
     test_an_infinity_stays_where_it_belongs(where, [301, 4100], 1030)
 
 
+@pytest.mark.parametrize("dims,mb,what,at", [
+    # forward by two halves of a workgroup: in the first half's part of the contraction, in the second one's, in both operands' last element
+    ([300, 700], 900, "weight", (5, 350)), ([300, 700], 900, "weight", (299, 699)), ([300, 700], 900, "activation", (899, 5)),
+    ([300, 700], 900, "activation", (450, 299)),
+    # 64x64 tiles two to a workgroup, an odd number of them: weight gradient (activation, gradient), input gradient (weight, gradient)
+    ([700, 830], 40, "activation", (39, 699)), ([700, 830], 40, "activation", (0, 0)), ([700, 830], 40, "gradient", (20, 829)),
+    ([832, 24], 700, "weight", (831, 23)), ([832, 24], 700, "gradient", (699, 0)),
+])
+@pytest.mark.filterwarnings("ignore::RuntimeWarning")
+def test_an_infinity_in_tiles_that_share_a_workgroup(dims, mb, what, at):
+    """As test_an_infinity_stays_where_it_belongs: both tiles, or both halves of one, walk again together."""
+    import paper_2401_01728_amd as rv
+    K, N = dims
+    w0 = kaiming_uniform_flat(70, dims)
+    x = gen.normal_f32(70, 1, mb * K).reshape(mb, K)
+    dy = gen.normal_f32(70, 2, mb * N, std=0.1).reshape(mb, N)
+    if what == "weight": w0[at[0] * N + at[1]] = np.inf
+    else: (x if what == "activation" else dy)[at] = np.inf
+    g = rv.Stage.mlp(dims, mb, 0, 0.05); g.set_params(dev(w0))
+    o = ostage.Stage("mlp", 0, 0.05, w0, dims=dims)
+    grp = "MLP stage, bar 1e-5"
+    _same(host64(g.forward(0, dev(x))), o.forward(0, x), 1e-5, grp)
+    dx, dxo = g.backward(0, dev(dy)), o.backward(0, dy)
+    _same(host64(dx), dxo, 1e-5, grp)
+    _same(host64(g.last_grad()), o.last_grad, 1e-5, grp)
+
+
 @pytest.mark.parametrize("scale", [1e-26, 1e-31, 1e-34])
 def test_gradients_near_the_smallest_numbers(scale):
     """The third piece of 1e-33 is no bf16 number unless the operands are scaled.  Bar: sums of fp32 products as above; of
