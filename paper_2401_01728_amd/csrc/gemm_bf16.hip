@@ -609,13 +609,12 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
     auto baseB = [&](int t) { return BKM ? B + (int64_t)t * BK * ldb : B + (int64_t)t * (BK / 32) * b_bs; };
     // wait until at most `tiles` of this wave's newest tile loads are still in flight
     auto wait_tiles = [&](int tiles) {
-      if (NS >= 5 && tiles >= 4) RV_WAIT_VMCNT(4 * LPS);
-      else if (NS >= 5 && tiles == 3) RV_WAIT_VMCNT(3 * LPS);
-      else if (NS >= 4 && tiles >= 2) RV_WAIT_VMCNT(2 * LPS);
-      else if (NS >= 3 && tiles >= 1) RV_WAIT_VMCNT(1 * LPS);
+      if (NS >= 4 && tiles >= 3) RV_WAIT_VMCNT(3 * LPS);
+      else if (NS >= 3 && tiles >= 2) RV_WAIT_VMCNT(2 * LPS);
+      else if (tiles >= 1) RV_WAIT_VMCNT(1 * LPS);
       else RV_WAIT_VMCNT(0);
     };
-    static_assert(NS <= 5, "wait_tiles covers up to four tiles in flight behind the awaited one");
+    static_assert(NS <= 4, "wait_tiles covers up to three tiles in flight behind the awaited one");
     const int pre = nk < NS ? nk : NS;
     for (int t = 0; t < pre; ++t) {
       const int lb = __builtin_amdgcn_readfirstlane((int)(size_t)(smem + t * BUF) + lw * 1024);
