@@ -407,7 +407,7 @@ __device__ __forceinline__ bf16x8 dtl_read_tr(const char* lds, int kr, int col) 
   return __builtin_bit_cast(bf16x8, r);
 }
 
-// Fragment of one v_mfma_f32_16x16x32_bf16 (the pipelined 256x256 tile): rows row0 .. + 15, k-step kk of 32.  Lane l holds row l % 16, k = 8 (l / 16) .. + 7.
+// Fragment of one v_mfma_f32_16x16x32_bf16 (whole tiles): rows row0 .. + 15, k-step kk of 32.  Lane l holds row l % 16, k = 8 (l / 16) .. + 7.
 template <bool KM, int ROWS, int BK>
 __device__ __forceinline__ bf16x8 dtl_frag(const char* lds, int row0, int kk) {
   const int l = threadIdx.x & 63;
@@ -563,7 +563,7 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
                                               int K, int bm, int bn, const Epi& e) {
   // Products of 16x16: the matrix cores do 1717 TFLOP/s out of LDS at the board's power cap with those, 1586 with 32x32 ones
   // (registers alone 2028 / 1807; half the accumulator traffic per flop).  Stage steps at the cap 2 % shorter (8 blocks of d 2048
-  // 10.92 -> 10.72 ms), below it, after seconds under load, 0.6 - 0.9 % longer (9.31 -> 9.39).
+  // 10.92 -> 10.72 ms), below it, after seconds under load, 0.3 - 0.7 %.
   // NW waves laid out 2 (m) x NW/2 (n)
   typedef f32x4 V;
   constexpr int WM = BM / 2, WN = BN / (NW / 2), TM = WM / 16, TN = WN / 16;
@@ -598,7 +598,7 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
     // tile boundary.
     constexpr int NA = Dtl<AKM, BM, BK, NL>::N, NB = Dtl<BKM, BN, BK, NL>::N, LPS = NA + NB;
     constexpr int HM = TM / 2, STRIDE = HM * TN / LPS; // MFMAs per load in the lower half
-    static_assert(BK == 32 && TM % 2 == 0 && STRIDE >= 1, "a load behind every STRIDE MFMAs of the lower half");
+    static_assert(BK == 32 && TM % 2 == 0 && HM <= TN && STRIDE >= 1, "a column to each lower fragment, a load to every STRIDE MFMAs");
     static_assert((NS - 1) * LPS < 64, "vmcnt range");
     unsigned oa[NA], ob[NB];               // per-lane byte offsets of this wave's loads inside a tile
 #pragma unroll
@@ -654,21 +654,24 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
     for (int i = 0; i < HM; ++i) fa[i] = dtl_frag<AKM, BM, BK>(smem, wm0 + i * 16, 0);
 #pragma unroll
     for (int j = 0; j < TN; ++j) fb[j] = dtl_frag<BKM, BN, BK>(smem + A_BYTES, wn0 + j * 16, 0);
-    // the upper half of the tile at `cur`, and the reads of its lower fragments, one behind each of the first MFMAs
+    // the upper half of the tile at `cur`, and the reads of its lower fragments, one behind the first MFMA of each column
+    // (all of them behind the first column's MFMAs: warm stage steps 0.6 % longer, see the loads below)
     auto upper_half = [&](const char* cur) {
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int i = 0; i < HM; ++i) {
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
-          if (j == 0) {
+          if (i == 0 && j < HM) {
             __builtin_amdgcn_sched_barrier(0);
-            fa[HM + i] = dtl_frag<AKM, BM, BK>(cur, wm0 + (HM + i) * 16, 0);
+            fa[HM + j] = dtl_frag<AKM, BM, BK>(cur, wm0 + (HM + j) * 16, 0);
             __builtin_amdgcn_sched_barrier(0);
           }
         }
     };
-    // the lower half; with `nxt` the first fragments of the tile there, with `pa` the loads of a tile into the block at `lb`
+    // the lower half; with `nxt` the first fragments of the tile there, with `pa` the loads of a tile into the block at `lb`, the
+    // first one behind the first MFMA.  (Three MFMAs later, together with the reads above: 8 blocks of d 2048 9.28 -> 9.43 ms,
+    // 12 of d 1600 18.04 -> 18.20, warm; products of 32x32 9.35 and 18.10.)
     auto lower_half = [&](auto has_next, const char* nxt, auto has_load, const uint16_t* pa, const uint16_t* pb, int lb) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
@@ -678,7 +681,7 @@ __device__ __forceinline__ void gemm_dtl_body(const uint16_t* __restrict__ A, in
           __builtin_amdgcn_sched_barrier(0);
           if (has_next && j == 0) fa[i] = dtl_frag<AKM, BM, BK>(nxt, wm0 + i * 16, 0);
           const int m = j * HM + i;
-          if (has_load && m % STRIDE == STRIDE - 1 && m / STRIDE < LPS) {
+          if (has_load && m % STRIDE == 0 && m / STRIDE < LPS) {
             const int q = m / STRIDE;
             if (q < NA) dtl_load_s(pa, oa[q], lb + q * NL * 1024);
             else dtl_load_s(pb, ob[q - NA], lb + A_BYTES + (q - NA) * NL * 1024);
