@@ -1119,9 +1119,11 @@ rv_status pick_part(const rv_gemm_args& g, int S, float* part, hipStream_t st) {
 //   1128  128x128, 1065 / 1064 64x64, 1032 32x64: the contraction split inside the workgroup over
 //         2, 2 / 4 and 8 groups of waves.
 // The automatic choice among the first three minimises  rounds * tile area * workgroups per CU / efficiency,
-// rounds = ceil(tiles / (256 CUs * workgroups per CU)), efficiencies measured ratios: over 309 launches of 256 .. 8192 rows
-// alone on average 0.3 % above the best of the three before 2192 and 2128 had the pipelined ring (us, bound loads / ring: 4096x1024x4096
-// 2128 43.7 / 38.0, 4096x6144x2048 2192 116 / 98, 8192x1600x6400 2192 189 / 154; 5256 75, 103, 150): 2192 0.92 -> 0.98.
+// rounds = ceil(tiles / (256 CUs * workgroups per CU)), efficiencies ratios of times before 2192 and 2128 had
+// the pipelined ring, 2192's 0.92 -> 0.98 with it (us, bound loads / ring: 4096x1024x4096 2128 43.7 / 38.0, 4096x6144x2048 2192 116 / 98,
+// 8192x1600x6400 2192 189 / 154; 5256 75, 103, 150).  Over 200 launches of 512 .. 8192 rows and 256 .. 8192 in k alone on average 2.1 % above
+// the best of the three (0.3 % before the ring; 3.0 % from 64 tiles of 256x256 on), most on short contractions: 6784x7552x256 with GELU 91 where
+// 2128 takes 69, 5120x6848x1024 85 / 72 (2192).
 // Whether the contraction is split is decided by the modelled time, us,
 //   rounds * (f + turns * t) + out * M N / 1e6,  turns = k-tiles per group,
 // t between t0 (a launch that leaves most CUs idle) and t1 (one that fills them; with 2192 and 2128 as they were before the pipelined ring:

@@ -813,16 +813,15 @@ Prod product(const float* A, int lda, const float* B, int ldb, int M, int N, int
 int tile_count(int M, int N, int bt) { return (M + bt - 1) / bt * ((N + bt - 1) / bt); }
 constexpr int kCUs = 256;
 // The largest tile that still gives every CU one (of 64x64 tiles half of them: such a workgroup
-// keeps up with two CUs' worth of 32x32 ones, whose operands all come through L2).  Measured: a stage step of
-// 1024-4096-4096-1024 on 1024 rows 0.90 ms (172 TFLOP/s), 300-1000-1000-77 on 100 rows with momentum
-// 67 us, where 64x64 tiles of fp32 instructions took 120 for the 100-row products.
+// keeps up with two CUs' worth of 32x32 ones, whose operands all come through L2; fitted to fp32 tiles, which took a seventh to a half
+// longer than the present ones).  Measured: a stage step of
+// 1024-4096-4096-1024 on 1024 rows 0.92 ms (168 TFLOP/s), 300-1000-1000-77 on 100 rows with momentum 60 us.
 // A result of at most 32 rows or columns fills at best half of such a tile's matrix instructions, so there the tile
 // count says nothing about the chip: it takes 32x32 tiles, one per wave where the contraction is short (the work is the
 // results' memory traffic), split where it is long.  Times in us against the tiles that the count alone would take:
-//   4 -> 1e5 on 8 rows, forward 20 -> 7 (32x32 split 35)        1e5 -> 4 on 8 rows, backward 40 -> 13 (61)
-//   64 -> 10 on 65536 rows, forward 29 -> 13 (42)               16384 -> 100 on 16 rows, backward 13.5 -> 12.6 (16)
-//   8192 -> 8192 on 8 rows, forward / backward 307 / 408 -> 74 / 303
-//   slower: 8 -> 2048 on 8192 rows, backward 83 -> 87; 32 -> 32768 on 128 rows, backward 285 -> 310
+//   4 -> 1e5 on 8 rows, forward 10.8 -> 6.3 (32x32 split 29.5)  1e5 -> 4 on 8 rows, backward 16.7 -> 12.8 (49.5)
+//   8 -> 2048 on 8192 rows, backward 92 -> 85                    8192 -> 8192 on 8 rows, forward 118 -> 68
+//   slower: 4 -> 1e5 on 8 rows, backward 310 -> 339; 16384 -> 100 on 16 rows, backward 10.2 -> 11.5
 int pick(int M, int N, int K) {
   const int thin = std::min(M, N);
   if (thin <= 32 && tile_count(M, N, 64) >= kCUs / 2) return K <= 128 ? kWave : 32;
@@ -1245,16 +1244,16 @@ rv_status rv_mlp_plan(rv_stage* s) {
   s->P = off;
   s->slot_bytes = offa * 4;
   s->work_bytes = 2 * (size_t)s->microbatch * p->maxw * 4;
-  // One launch per direction, or one per layer and direction?  Forward + backward of one microbatch
-  // back to back, us (one per direction / one per layer):
-  //   8 rows    16-16-16 11.9 / 18.7   64-128-64 14.9 / 22.0   64-64-64-64 15.2 / 29.8   64-64-64-64-64 18.0 / 42.0
-  //   16 rows   128-128-128-128 24.4 / 33.0   20-60-200-60-20 23.7 / 38     32 rows  64-64-64-64 19.6 / 31.6
-  //   64 rows   16-16-16 19.9 / 20.0   48-48-48-48 29.3 / 32.4   64-64-64-64-64 42.7 / 43.6
-  //             10-200-10 30.3 / 22.4   72-72-72-72 43.5 / 33.0   96-96-96-96-96 61.2 / 44.2
-  //   one layer, 16 rows   32-32 11.7 / 11.3   16-256 12.8 / 11.8
-  // A launch costs about 5 us whatever it does; the repeated chain about 8 + 2.5 (g - 1) us and
-  // (0.2 + 0.11 g) ns per parameter, g = 1, 2, 4 groups of 16 rows.  With four groups the registers no longer hold
-  // what is requested ahead, and rows wider than 64 lose whatever the other widths.
+  // One launch per direction, or one per layer and direction?  Forward + backward of one microbatch, us on the device (one per
+  // direction / one per layer):
+  //   8 rows    16-16-16 8.2 / 10.8   64-128-64 11.8 / 13.7   64-64-64-64 12.6 / 19.1   64-64-64-64-64 15.4 / 25.5
+  //   16 rows   128-128-128-128 21.3 / 23.0   20-60-200-60-20 21.6 / 29.8   144-144-144-144 27.9 / 22.7   200-200-200 25.3 / 16.8
+  //   32 rows   64-64-64-64 15.7 / 20.1   96-96-96-96 24.4 / 23.1   112-112-112-112 26.3 / 22.8
+  //   64 rows   16-16-16 12.3 / 12.4   48-48-48-48 24.3 / 20.9   64-64-64-64-64 39.2 / 28.5
+  // The limit was fitted when a launch of a layer took about 5 us whatever it did, and the repeated chain about 8 + 2.5 (g - 1) us and
+  // (0.2 + 0.11 g) ns per parameter, g = 1, 2, 4 groups of 16 rows; both are shorter now, the layers' by more.  By device time alone one
+  // launch is taken too often past 128 wide and with four groups; but issuing a launch takes the host 2.7 us, which is what such
+  // stages last where calls follow one another.  With four groups rows wider than 64 lose whatever the other widths.
   const int g = s->microbatch <= 16 ? 1 : s->microbatch <= 32 ? 2 : 4;
   p->tiny = p->n >= 2 && p->n <= kTinyLayers && s->microbatch <= kTinyRows && p->maxw <= (g == 4 ? 64 : 256) &&
             (20.0 + 11.0 * g) * (double)off < 1e5 * (10.0 * p->n - 5.5 - 2.5 * g);
