@@ -353,7 +353,11 @@ __device__ __forceinline__ void write_tile_staged(const V (&acc)[TM][TN], const 
 // tile is unpadded and bank conflicts are removed by an XOR swizzle of the 16-byte chunk
 // index instead; because a lane's LDS slot is fixed, the swizzle is applied to the GLOBAL
 // address a lane fetches.
-//   k-contiguous tile [rows][BK]: physical chunk = c ^ ((row / rows_per_256B) % chunks_per_row)
+//   k-contiguous tile [rows][32]: four rows to a 256-byte bank line; a 16-byte read goes out in groups of lanes 0-3, 12-15, 20-27 / 4-11,
+//                                 16-19, 28-31 and the same of the upper half, which with fragments of 16 rows are one chunk of
+//                                 rows 0-3 and 12-15 and the next one of rows 4-11: physical chunk = c ^ (-(row / 4) & 3) is free of
+//                                 conflicts with them and with fragments of 32 rows.  (c ^ (row / 4 & 3) is so with 32 rows alone: with 16,
+//                                 every read of 8192x8192x8192 took twice its LDS cycles, 2.04e8 for 1.03e8)
 //   k-major tile [BK][cols]     : half a wave's transposing read takes 32 bytes of rows k .. k + 3 and k + 8 .. k + 11
 //                                 (fragments of 16 rows) or 64 bytes of rows k .. k + 3 (of 32): physical chunk =
 //                                 c ^ ((k & 3) << 2) ^ ((k & 8) >> 2); split forms with 64 columns (fragments of 32 rows),
@@ -364,6 +368,11 @@ __device__ __forceinline__ void write_tile_staged(const V (&acc)[TM][TN], const 
 // that opens the one before, on the four-wave tiles: 10 - 20 % slower alone, 4 blocks of d 1024 on 4096 tokens 1796 / 1747 us a step.)
 __host__ __device__ constexpr int dtl_tile_bytes(int rows, int bk) { return rows * bk * 2; }
 
+template <int BK>
+__device__ __forceinline__ int kc_swizzle(int row) {
+  static_assert(BK == 32, "four chunks to a row, four rows to a bank line");
+  return -(row >> 2) & 3;
+}
 template <int ROWS>
 __device__ __forceinline__ int km_swizzle(int k) { return ROWS == 64 ? (k & 2) << 1 : ((k & 3) << 2) ^ ((k & 8) >> 2); }
 
@@ -380,8 +389,8 @@ __device__ __forceinline__ void dtl_init(Dtl<KM, ROWS, BK, NW>& s, int64_t ld, i
   for (int i = 0; i < Dtl<KM, ROWS, BK, NW>::N; ++i) {
     const int slot = (i * NW + wave) * 64 + l;
     if (!KM) {
-      constexpr int CPR = BK / 8, R256 = 256 / (BK * 2);
-      const int row = slot / CPR, c = (slot % CPR) ^ ((row / R256) % CPR);
+      constexpr int CPR = BK / 8;
+      const int row = slot / CPR, c = (slot % CPR) ^ kc_swizzle<BK>(row);
       int gr = r0 + row;
       gr = gr < rows ? gr : rows - 1;
       s.off[i] = gr * (int)ld + (c * 8 / 32) * (int)bs + c * 8 % 32;
@@ -412,9 +421,8 @@ template <bool KM, int ROWS, int BK>
 __device__ __forceinline__ bf16x8 dtl_frag(const char* lds, int row0, int kk) {
   const int l = threadIdx.x & 63;
   if (!KM) {
-    constexpr int CPR = BK / 8, R256 = 256 / (BK * 2);
     const int row = row0 + (l & 15);
-    const int c = (kk * 4 + (l >> 4)) ^ ((row / R256) % CPR);
+    const int c = (kk * 4 + (l >> 4)) ^ kc_swizzle<BK>(row);
     return *reinterpret_cast<const bf16x8*>(lds + row * (BK * 2) + c * 16);
   } else {
     static_assert(!KM || ROWS > 64, "the swizzle of narrower tiles is that of 32-row fragments");
@@ -430,9 +438,8 @@ template <bool KM, int ROWS, int BK>
 __device__ __forceinline__ bf16x8 dtl_frag32(const char* lds, int row0, int kk) {
   const int l = threadIdx.x & 63;
   if (!KM) {
-    constexpr int CPR = BK / 8, R256 = 256 / (BK * 2);
     const int row = row0 + (l & 31);
-    const int c = (kk * 2 + (l >> 5)) ^ ((row / R256) % CPR);
+    const int c = (kk * 2 + (l >> 5)) ^ kc_swizzle<BK>(row);
     return *reinterpret_cast<const bf16x8*>(lds + row * (BK * 2) + c * 16);
   } else {
     const int q = l >> 4, i = l & 15;
