@@ -452,6 +452,25 @@ def test_small_operands_beside_ordinary_ones(dims, mb, small):
     close(gr * up, gro * up, bar(mb), "t", group=grp + "gradient")
 
 
+@pytest.mark.parametrize("xs,ws,ds", [(1e18, 1e14, 1e17), (1e35, 1e-2, 1e-3), (1e-3, 1e36, 1e-2), (1e-2, 1e-3, 1e35)])
+@pytest.mark.parametrize("dims,mb", _PLANES)
+def test_large_operands(dims, mb, xs, ws, ds):
+    """Results past 2^96, operands past 2^112: such tiles leave the range of the scaled sums or pieces and are walked again; the
+    results are ordinary floats.  Bar as test_products_in_three_planes."""
+    import paper_2401_01728_amd as rv
+    K, N = dims
+    w0 = (kaiming_uniform_flat(71, dims) * np.float32(ws)).astype(np.float32)
+    x = gen.normal_f32(71, 1, mb * K).reshape(mb, K) * np.float32(xs)
+    dy = gen.normal_f32(71, 2, mb * N).reshape(mb, N) * np.float32(ds)
+    g = rv.Stage.mlp(dims, mb, 0, 0.0); g.set_params(dev(w0))
+    o = ostage.Stage("mlp", 0, 0.0, w0, dims=dims)
+    bar = lambda k: float(np.sqrt(k) * 2.0 ** -24 + 2.0 ** -24)
+    grp = "MLP, large operands: "
+    close(host64(g.forward(0, dev(x))), o.forward(0, x), bar(K), "t", group=grp + "out")
+    close(host64(g.backward(0, dev(dy))), o.backward(0, dy), bar(N), "t", group=grp + "grad_in")
+    close(host64(g.last_grad()), o.last_grad, bar(mb), "t", group=grp + "gradient")
+
+
 @pytest.mark.parametrize("sign", [1.0, -1.0])
 @pytest.mark.parametrize("dims,mb", [([4096, 1024], 512), ([16384, 1024], 512), ([256, 16384], 2100), ([512, 1100], 16400)])
 def test_sums_of_one_sign(dims, mb, sign):
