@@ -1371,7 +1371,7 @@ rv_status rv_mlp_backward(rv_stage* s, rv_slot& slot, const void* grad_out, void
         return bw == 64 ? go(launch_bwd<BX, 64, NT>) : bw == 32 ? go(launch_bwd<BX, 32, NT>) : go(launch_bwd<BX, kWave, NT>);
       else
       return bw == 128 ? go(launch_bwd<BX, 128, 256>) : bw == 64 ? go(launch_bwd<BX, 64, BX == 32 ? NT : 256>)
-             : bw == 32 && pairs ? go(launch_bwd<BX, 32, 64 * kSplitWaves>)
+             : bw == 32 && BX == 64 && pairs ? go(launch_bwd<BX, 32, BX == 64 ? 64 * kSplitWaves : NT>)
              : bw == 32 ? go(launch_bwd<BX, 32, NT>) : go(launch_bwd<BX, kWave, BX == 32 ? NT : 256>);
     };
     const rv_status rc = form == kSlim ? by_bw(Int<kSlim>()) : bx == 128 ? by_bw(Int<128>()) : bx == 64 ? by_bw(Int<64>()) : bx == 32 ? by_bw(Int<32>()) : by_bw(Int<kWave>());
