@@ -248,11 +248,12 @@ __device__ __forceinline__ void fp32_walk(TileAcc<BT>& acc, const Prod& p, int m
 // LDS keeps the planes of an operand as memory has it: k-contiguous rows of 32 bytes, read as one 16-byte fragment per
 // lane, k-major rows of the tile's width, read by the transposing LDS read; 16-byte chunks are exchanged so that neither way
 // of reading nor the 8-byte writes have bank conflicts.
-// What bounds it: with two workgroups to a CU the matrix cores (1024 rows, 4096 -> 8192 forward 328 us = 209 TFLOP/s, 1255 of
-// bf16), with one the LDS and barrier latency of a wave alone on its SIMD (4096 -> 4096 forward 188 us, 183 TFLOP/s).  Against the
-// fp32 walk that ran here before, 1024 rows, forward / backward with the update, us: 4096 -> 4096 303 / 538 -> 208 / 362,
-// 1024 -> 4096 90 / 157 -> 62 / 114; 2051 rows, 1030 -> 2052 174 / 240 -> 88 / 161; distance from 64 bits 0.31 - 0.36 times.
-// (The factors of 2^16, on the vector ALU, are 1 - 4 % of a walk.)
+// What bounds it: with two workgroups to a CU the matrix cores (1024 rows, 4096 -> 8192 forward 344 us = 200 TFLOP/s, 1200 of
+// bf16), with one the LDS and barrier latency of a wave alone on its SIMD (4096 -> 4096 forward 197 us, 174 TFLOP/s).  Against the
+// fp32 walk that ran here before, 1024 rows, forward / backward with the update, us: 4096 -> 4096 310 / 548 -> 197 / 371,
+// 1024 -> 4096 90 / 159 -> 60 / 111; 2051 rows, 1030 -> 2052 177 / 244 -> 84 / 160; distance from 64 bits 0.31 - 0.36 times.
+// (The factors of 2^16, on the vector ALU, are up to 5 % of a walk: 187 / 367 without, and 6 instructions of it behind a matrix
+// instruction instead of the 5 before: 202 / 380.)
 constexpr int SK = 16, kSlots = 3;                         // of k to a step
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
@@ -395,7 +396,7 @@ __device__ __forceinline__ void planes_walk(TileAcc<BT>& acc, const Prod& p, int
 #pragma unroll
       for (int q = 0; q < decltype(matrix)::value * T * T; ++q) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, T == 2 ? 5 : 10, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, T == 2 ? 6 : 11, 0);
         __builtin_amdgcn_sched_group_barrier(0x080, decltype(lds)::value, 0);
         __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
       }
@@ -815,7 +816,7 @@ constexpr int kCUs = 256;
 // The largest tile that still gives every CU one (of 64x64 tiles half of them: such a workgroup
 // keeps up with two CUs' worth of 32x32 ones, whose operands all come through L2; fitted to fp32 tiles, which took a seventh to a half
 // longer than the present ones).  Measured: a stage step of
-// 1024-4096-4096-1024 on 1024 rows 0.92 ms (168 TFLOP/s), 300-1000-1000-77 on 100 rows with momentum 60 us.
+// 1024-4096-4096-1024 on 1024 rows 0.90 ms (171 TFLOP/s), 300-1000-1000-77 on 100 rows with momentum 60 us.
 // A result of at most 32 rows or columns fills at best half of such a tile's matrix instructions, so there the tile
 // count says nothing about the chip: it takes 32x32 tiles, one per wave where the contraction is short (the work is the
 // results' memory traffic), split where it is long.  Times in us against the tiles that the count alone would take:
